@@ -29,6 +29,7 @@
 //   k_logits_hlds    one wave per tile, the sentence's hidden rows staged in LDS (up to 32 beams:
 //                    the bandwidth-bound case; more beams in groups of 16 rows);
 //   k_logits_estage  33..64 beams: hidden rows in registers, candidate rows through LDS;
+//   k_logits_few, k_logits_rows   the full vocabulary: all hidden rows of the call against all words;
 //   fused.h          the same tiles inside the kernels that also produce the candidate list.
 #pragma once
 #include "candidates.h"
@@ -82,6 +83,10 @@ __host__ __device__ inline int group_records(int ntiles, int G) {   // record sl
 }
 
 constexpr int kTileN = 16;  // candidates per tile
+// Columns per record of the kernels that serve the full vocabulary.  (Their selection is bound by what
+// the one CU per sentence pulls in: a record per 16 words was 240 KB for 12 rows and V = 40000,
+// 15.5 us; a record per 64 words: 8 us.  Opening a wide tile reads 48 more logits.)
+constexpr int kWideN = 64;
 constexpr int kTileM = 16;  // hidden rows per tile
 constexpr int kMaxSentencesLogits = 4096;
 
@@ -1120,6 +1125,382 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
             }
         }
     }
+}
+
+// Full vocabulary: every hidden row meets every word, so sentences do not matter and the contraction
+// is one matrix product, R rows x V words.  (Taken sentence by sentence each of them gathered all of
+// E again: 32 sentences x 160 MB.)  Few rows: bound by the one pass over E (k_logits_few); many: by the
+// matrix pipe.
+//
+// A workgroup of four waves makes MT * 16 rows x 64 WF words, in blocks of 32 k.  The hidden rows pass
+// through LDS (double-buffered; fp32, or for bf16 words as the three bf16 planes of k_logits_hlds, split
+// on the way in).  A wave owns 16 WF words and all the rows; nobody else needs those words, so their
+// chunks go from memory straight into the A operand registers, kRowsAhead blocks ahead.  With WF = 2
+// (fp32, 4 MT WF instructions of 32 cycles per MT 16-byte LDS reads) and WF = 4 (bf16, 3 MT WF of 16
+// cycles per 3 MT reads) the LDS rate is no bound.  Words are the A operand, so that a lane ends up with
+// four consecutive words of one hidden row (a 16-byte store).  The operands of a block are read from
+// LDS in two halves, each while the other half's instructions run; without that, and with the loads
+// placed by the compiler, the same tiles took 283 instead of 222 us.  MT is the host's choice.
+// Any d >= one chunk and any pitch: chunks are loaded from any element's address.
+// 320 rows, V = 40000, d = 1000: fp32 689 -> 222 us (116 TFLOP/s; the matrix pipe is busy 72 % of the
+// time, 79 % while a CU has work), bf16 369 -> 95 us (d = 1024).
+constexpr int kRowsK = 32;
+template <typename ET> __host__ __device__ constexpr int rows_planes() { return sizeof(ET) == 2 ? 3 : 1; }
+// LDS bytes per hidden row and plane: 16-byte reads without conflicts
+template <typename ET> __host__ __device__ constexpr int rows_pitch() { return sizeof(ET) == 2 ? 40 * 2 : 36 * 4; }
+template <typename ET> __host__ __device__ constexpr size_t rows_lds_bytes(int MT) {
+    return (size_t)2 * rows_planes<ET>() * ((MT + 1) / 2 * 32) * rows_pitch<ET>() + 4 * kTileM * sizeof(float2);
+}
+struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };    // 16 bytes at any float's address
+template <typename ET> struct __attribute__((packed, aligned(sizeof(ET)))) Chunk16U { uint32_t w[4]; };   // at any element's
+
+// The 16 bytes of a row of d >= 16 / sizeof(ET) elements that begin at element k, zeros past the row's
+// end: what lies past it is never read (one clamped load, then shifted into place in registers).
+template <typename ET>
+__device__ __forceinline__ Chunk16U<ET> load_chunk_end(const ET* row, int k, int d) {
+    constexpr int CK = 16 / (int)sizeof(ET);
+    const int at = min(k, d - CK);
+    Chunk16U<ET> c = *reinterpret_cast<const Chunk16U<ET>*>(row + at);
+    const int s = min(k - at, CK);                  // elements to drop in front
+    if constexpr (sizeof(ET) == 2) {
+        if (s & 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c.w[i] = (c.w[i] >> 16) | (i < 3 ? c.w[i < 3 ? i + 1 : 3] << 16 : 0u);
+        }
+    }
+    constexpr int ONE = 4 / (int)sizeof(ET);        // elements per word
+    if (s & ONE) { c.w[0] = c.w[1]; c.w[1] = c.w[2]; c.w[2] = c.w[3]; c.w[3] = 0u; }
+    if (s & (2 * ONE)) { c.w[0] = c.w[2]; c.w[1] = c.w[3]; c.w[2] = 0u; c.w[3] = 0u; }
+    if (s & (4 * ONE)) { c.w[0] = 0u; c.w[1] = 0u; c.w[2] = 0u; c.w[3] = 0u; }
+    return c;
+}
+// Four hidden values as the three bf16 planes of k_logits_hlds (exactly x = hi + mid + lo), to LDS.
+__device__ __forceinline__ void store_planes4(char* dst, size_t plane_bytes, const float (&x)[4]) {
+    uint32_t hi[4], mid[4], lo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        hi[q] = __float_as_uint(x[q]) & 0xFFFF0000u;
+        const float r1 = x[q] - __uint_as_float(hi[q]);          // exact
+        mid[q] = __float_as_uint(r1) & 0xFFFF0000u;
+        lo[q] = __float_as_uint(r1 - __uint_as_float(mid[q]));   // exact, <= 8 bits
+    }
+    *reinterpret_cast<uint2*>(dst) = make_uint2((hi[0] >> 16) | (hi[1] & 0xFFFF0000u), (hi[2] >> 16) | (hi[3] & 0xFFFF0000u));
+    *reinterpret_cast<uint2*>(dst + plane_bytes) =
+        make_uint2((mid[0] >> 16) | (mid[1] & 0xFFFF0000u), (mid[2] >> 16) | (mid[3] & 0xFFFF0000u));
+    *reinterpret_cast<uint2*>(dst + 2 * plane_bytes) =
+        make_uint2((lo[0] >> 16) | (lo[1] & 0xFFFF0000u), (lo[2] >> 16) | (lo[3] & 0xFFFF0000u));
+}
+template <typename ET> __device__ __forceinline__ bf16x8 as_bf16x8(const Chunk16U<ET>& c) {
+    return __builtin_bit_cast(bf16x8, make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]));
+}
+
+// The end of both kernels: lane (col, kk) holds, in x[m][f], the logits of hidden row row0 + 16 m + col
+// and the words word0 + 16 f + 4 kk + (0..3).  Stores them and a record (max, sum exp) per row and 64
+// words, which are one, two or four waves' (WF = 4, 2, 1); part: LDS for 4 x 16 pairs.  Called by all
+// four waves.
+template <int MT, int WF>
+__device__ __forceinline__ void finish_wide(const floatx4 (&x)[MT][WF], int row0, int word0, int R, int V,
+                                            float* __restrict__ logits, int64_t cpitch, TileRecords recs, float2* part) {
+    static_assert(WF == 4 || WF == 2 || WF == 1, "64 words are one, two or four waves'");
+    const int ln = lane_id(), wv = wave_id(), col = ln & 15, kk = ln >> 4;
+    const int w0 = word0 + 4 * kk;
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const int row = row0 + m * kTileM + col;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int f = 0; f < WF; ++f) {
+            const int w = w0 + 16 * f;
+            if (row < R && w < V)   // (columns past V inside the row's pitch are never read)
+                *reinterpret_cast<float4*>(&logits[(size_t)row * cpitch + w]) = make_float4(x[m][f][0], x[m][f][1], x[m][f][2], x[m][f][3]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mx = fmaxf(mx, w + r < V ? x[m][f][r] : -INFINITY);
+        }
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        float se = 0.f;
+#pragma unroll
+        for (int f = 0; f < WF; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) se += w0 + 16 * f + r < V ? expf(x[m][f][r] - mx) : 0.f;
+        se += __shfl_xor(se, 16);
+        se += __shfl_xor(se, 32);
+        float2 a = make_float2(mx, se);
+        if constexpr (WF < 4) {
+            if (kk == 0) part[wv * kTileM + col] = a;
+            lds_barrier();
+#pragma unroll
+            for (int o = 1; o < 4 / WF; ++o) {
+                const float2 q = part[((wv + o) & 3) * kTileM + col];   // (a wave past V: -inf, 0)
+                const float hi = fmaxf(a.x, q.x);
+                a = make_float2(hi, a.y * expf(a.x - hi) + q.y * expf(q.x - hi));
+            }
+            lds_barrier();
+        }
+        if ((wv & (4 / WF - 1)) == 0 && kk == 0 && row < R && word0 < V)
+            reinterpret_cast<float2*>(recs.rec)[(size_t)row * recs.pitch + word0 / kWideN] = a;
+    }
+}
+
+template <typename ET, int MT, int WF>
+__global__ void __launch_bounds__(256, 2)
+k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int R, int V,
+              int gx /*tiles of 64 WF words*/, int ngroups, float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
+    constexpr bool BF = sizeof(ET) == 2;
+    constexpr int PITCH = rows_pitch<ET>(), NP = rows_planes<ET>();
+    constexpr int HP = (MT + 1) / 2, LROWS = HP * 32;         // hidden rows are staged 32 at a time
+    constexpr int PER_WF = BF ? 1 : 2, NC = PER_WF * WF;      // 16-byte chunks of E per lane and block
+    constexpr int kRowsAhead = NC <= 2 ? 8 / NC : 3;          // blocks of E in registers: 8 to 12 loads in flight
+    constexpr int CK = 16 / (int)sizeof(ET);                  // elements per chunk
+    constexpr int M0 = BF ? (MT + 1) / 2 : MT;                // row tiles in the first half of a block (bf16)
+    constexpr int kBuf = NP * LROWS * PITCH;                  // bytes per buffer
+    extern __shared__ uint32_t rsm[];
+    char* sm = reinterpret_cast<char*>(rsm);
+    // (the row groups of one tile of words run on one XCD, one after the other: they share its L2)
+    const uint32_t slot = blockIdx.x >> 3;
+    const int bx = (int)((slot / (uint32_t)ngroups) * 8u + (blockIdx.x & 7u));
+    if (bx >= gx) return;
+    const int row0 = (int)(slot % (uint32_t)ngroups) * MT * kTileM;
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
+    const int col = ln & 15, kk = ln >> 4;
+    const int word0 = bx * (64 * WF) + wv * (16 * WF);
+    const int lr = tid >> 3, lc = 4 * (tid & 7);              // this thread's hidden row (of 32) and k inside a block
+    const float* hsrc[HP];
+#pragma unroll
+    for (int p = 0; p < HP; ++p) hsrc[p] = H + (size_t)min(row0 + 32 * p + lr, R - 1) * d;
+    const ET* esrc[WF];
+#pragma unroll
+    for (int f = 0; f < WF; ++f) esrc[f] = E + (int64_t)min(word0 + 16 * f + col, V - 1) * ld;
+
+    Float4U st[HP];
+    Chunk16U<ET> ev[kRowsAhead][NC];
+    auto load_hidden = [&](int i) {
+#pragma unroll
+        for (int p = 0; p < HP; ++p) st[p] = *reinterpret_cast<const Float4U*>(hsrc[p] + i * kRowsK + lc);
+    };
+    auto load_words = [&](int i, Chunk16U<ET> (&e)[NC]) {     // chunk f * PER_WF + s: step s of word tile f
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            e[c] = *reinterpret_cast<const Chunk16U<ET>*>(esrc[c / PER_WF] + i * kRowsK + (c % PER_WF) * 4 * CK + kk * CK);
+    };
+    auto store_hidden = [&](int buf) {
+#pragma unroll
+        for (int p = 0; p < HP; ++p) {
+            char* dst = sm + buf * kBuf + (32 * p + lr) * PITCH + lc * (BF ? 2 : 4);
+            const float x[4] = {st[p].x, st[p].y, st[p].z, st[p].w};
+            if constexpr (!BF) {
+                *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
+            } else {
+                store_planes4(dst, (size_t)LROWS * PITCH, x);
+            }
+        }
+    };
+    floatx4 acc[MT][WF];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int f = 0; f < WF; ++f) acc[m][f] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // half h of a block: fp32, k 16 h .. 16 h + 15; bf16, row tiles [0, M0) or [M0, MT)
+    struct Operands { uint4 b[M0][NP]; };
+    auto read_half = [&](int buf, int h, Operands& o) {
+        const char* hb = sm + buf * kBuf + col * PITCH + 16 * kk + (BF ? h * M0 * kTileM * PITCH : 64 * h);
+#pragma unroll
+        for (int m = 0; m < M0; ++m)
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+                if (!BF || h == 0 || M0 + m < MT)
+                    o.b[m][p] = *reinterpret_cast<const uint4*>(hb + (p * LROWS + m * kTileM) * PITCH);
+    };
+    auto contract = [&](const Operands& o, int h, const Chunk16U<ET> (&e)[NC]) {
+        if constexpr (BF) {
+#pragma unroll
+            for (int p = 0; p < NP; ++p)
+#pragma unroll
+                for (int m = 0; m < M0; ++m)
+#pragma unroll
+                    for (int f = 0; f < WF; ++f)
+                        if (h * M0 + m < MT) {
+                            const int mm = h * M0 + m < MT ? h * M0 + m : 0;
+                            acc[mm][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                as_bf16x8(e[f]), __builtin_bit_cast(bf16x8, o.b[m][p]), acc[mm][f], 0, 0, 0);
+                        }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    const uint32_t bq = q == 0 ? o.b[m][0].x : q == 1 ? o.b[m][0].y : q == 2 ? o.b[m][0].z : o.b[m][0].w;
+#pragma unroll
+                    for (int f = 0; f < WF; ++f)
+                        acc[m][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[f * PER_WF + (h & (PER_WF - 1))].w[q]),
+                                                                         __uint_as_float(bq), acc[m][f], 0, 0, 0);
+                }
+        }
+    };
+    const int nfull = d / kRowsK, rem = d - nfull * kRowsK;
+    auto load_rest = [&](Chunk16U<ET> (&e)[NC]) {             // (zeros past d on both sides)
+        const int k0 = nfull * kRowsK;
+#pragma unroll
+        for (int p = 0; p < HP; ++p) {
+            const Chunk16U<float> c = load_chunk_end<float>(hsrc[p], k0 + lc, d);
+            st[p] = __builtin_bit_cast(Float4U, c);
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) e[c] = load_chunk_end<ET>(esrc[c / PER_WF], k0 + (c % PER_WF) * 4 * CK + kk * CK, d);
+    };
+    Operands o0, o1;
+    int buf = 0;
+    if (nfull) {
+        // (the order in which the loop issues its loads, so that its waits count the same on both ways in)
+        load_hidden(0);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j + 1 < kRowsAhead; ++j) {
+            load_words(min(j, nfull - 1), ev[j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        store_hidden(0);
+        load_hidden(min(1, nfull - 1));
+        __builtin_amdgcn_sched_barrier(0);
+        load_words(min(kRowsAhead - 1, nfull - 1), ev[kRowsAhead - 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
+        read_half(0, 0, o0);
+        for (int i0 = 0; i0 < nfull; i0 += kRowsAhead) {
+#pragma unroll
+            for (int j = 0; j < kRowsAhead; ++j) {
+                const int i = i0 + j;
+                if (i >= nfull) break;              // (uniform)
+                read_half(buf, 1, o1);
+                contract(o0, 0, ev[j]);
+                __builtin_amdgcn_sched_barrier(0);  // (the wait for the hidden rows stays behind the instructions)
+                store_hidden(buf ^ 1);              // (last read before the previous barrier; past the last block: unused)
+                load_hidden(min(i + 2, nfull - 1));
+                lds_barrier();
+                read_half(buf ^ 1, 0, o0);
+                contract(o1, 1, ev[j]);
+                load_words(min(i + kRowsAhead, nfull - 1), ev[j]);
+                __builtin_amdgcn_sched_barrier(0);
+                buf ^= 1;
+            }
+        }
+        buf ^= 1;                                   // (the other buffer may still be being read)
+    }
+    if (rem) {
+        load_rest(ev[0]);
+        store_hidden(buf);
+        lds_barrier();
+        read_half(buf, 0, o0);
+        contract(o0, 0, ev[0]);
+        read_half(buf, 1, o1);
+        contract(o1, 1, ev[0]);
+    }
+    finish_wide<MT, WF>(acc, row0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
+}
+
+// The same for a few hidden rows (MT * 16, at most 48): bound by the pass over E.  A wave owns 16 words; what
+// counts is that every wave keeps long pieces of its rows in flight: blocks of 128 k (512 or 256 bytes
+// of a row, asked for together -- asked for 128 bytes at a time, memory gave 4.2 TB/s), the next block
+// under way while the current one meets the hidden rows in LDS (double-buffered, as above).
+// 12 rows, V = 40000, d = 1000 fp32: 40.1 -> 37.6 us (a fifth of it launch and ramp; 5.0 TB/s at
+// V = 200000); bf16, d = 1024: 24.6 -> 16.5 us.
+constexpr int kFewK = 128;
+template <typename ET> __host__ __device__ constexpr int few_pitch() {   // LDS bytes per hidden row and plane
+    return sizeof(ET) == 2 ? (kFewK + 8) * 2 : (kFewK + 4) * 4;
+}
+template <typename ET> __host__ __device__ constexpr size_t few_lds_bytes(int MT) {
+    return (size_t)2 * rows_planes<ET>() * MT * kTileM * few_pitch<ET>() + 4 * kTileM * sizeof(float2);
+}
+template <typename ET, int MT>
+__global__ void __launch_bounds__(256, 3)
+k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int R, int V,
+             float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
+    constexpr bool BF = sizeof(ET) == 2;
+    constexpr int PITCH = few_pitch<ET>(), NP = rows_planes<ET>(), CK = 16 / (int)sizeof(ET);
+    constexpr int NC = kFewK / (4 * CK);                      // chunks (steps) per lane and block
+    constexpr int HP = MT * 2;                                // 16-byte chunks of hidden rows per thread and block
+    constexpr int kPlane = MT * kTileM * PITCH, kBuf = NP * kPlane;
+    extern __shared__ uint32_t rsm[];
+    char* sm = reinterpret_cast<char*>(rsm);
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
+    const int col = ln & 15, kk = ln >> 4;
+    const int word0 = blockIdx.x * kWideN + wv * kTileN;
+    const int lr = tid >> 5, lc = 4 * (tid & 31);             // this thread's hidden row (of 8) and k inside a block
+    const float* hsrc[HP];
+#pragma unroll
+    for (int p = 0; p < HP; ++p) hsrc[p] = H + (size_t)min(8 * p + lr, R - 1) * d;
+    const ET* esrc = E + (int64_t)min(word0 + col, V - 1) * ld;
+    const int nfull = d / kFewK, rem = d - nfull * kFewK, nblk = nfull + (rem ? 1 : 0);
+
+    Float4U st[HP];
+    Chunk16U<ET> e0[NC], e1[NC];
+    auto load_words = [&](int i, Chunk16U<ET> (&e)[NC]) {
+        if (i < nfull) {   // (uniform)
+#pragma unroll
+            for (int c = 0; c < NC; ++c) e[c] = *reinterpret_cast<const Chunk16U<ET>*>(esrc + i * kFewK + c * 4 * CK + kk * CK);
+        } else {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) e[c] = load_chunk_end<ET>(esrc, i * kFewK + c * 4 * CK + kk * CK, d);
+        }
+    };
+    auto load_hidden = [&](int i) {
+#pragma unroll
+        for (int p = 0; p < HP; ++p) st[p] = __builtin_bit_cast(Float4U, load_chunk_end<float>(hsrc[p], i * kFewK + lc, d));
+    };
+    auto store_hidden = [&](int buf) {
+#pragma unroll
+        for (int p = 0; p < HP; ++p) {
+            char* dst = sm + buf * kBuf + (8 * p + lr) * PITCH + lc * (BF ? 2 : 4);
+            const float x[4] = {st[p].x, st[p].y, st[p].z, st[p].w};
+            if constexpr (BF) store_planes4(dst, kPlane, x);
+            else *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
+        }
+    };
+    floatx4 acc[MT][1];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[m][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto contract = [&](int buf, const Chunk16U<ET> (&e)[NC]) {
+        const char* hb = sm + buf * kBuf + col * PITCH + 16 * kk;
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                if constexpr (BF) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p)
+                        acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            as_bf16x8(e[c]), *reinterpret_cast<const bf16x8*>(hb + p * kPlane + m * kTileM * PITCH + 64 * c), acc[m][0], 0, 0, 0);
+                } else {
+                    const float4 b = *reinterpret_cast<const float4*>(hb + m * kTileM * PITCH + 64 * c);
+                    acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[c].w[0]), b.x, acc[m][0], 0, 0, 0);
+                    acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[c].w[1]), b.y, acc[m][0], 0, 0, 0);
+                    acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[c].w[2]), b.z, acc[m][0], 0, 0, 0);
+                    acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[c].w[3]), b.w, acc[m][0], 0, 0, 0);
+                }
+            }
+    };
+    // block i is contracted from `cur` while block i + 1 is on its way to `nxt`
+    auto turn = [&](int i, Chunk16U<ET> (&cur)[NC], Chunk16U<ET> (&nxt)[NC]) {
+        const int buf = i & 1;
+        if (i + 1 < nblk) {   // (uniform)
+            load_hidden(i + 1);
+            load_words(i + 1, nxt);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        contract(buf, cur);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 1 < nblk) store_hidden(buf ^ 1);              // (last read before the previous barrier)
+        lds_barrier();
+    };
+    load_hidden(0);
+    load_words(0, e0);
+    store_hidden(0);
+    lds_barrier();
+    for (int i = 0; i < nblk; i += 2) {
+        turn(i, e0, e1);
+        if (i + 1 < nblk) turn(i + 1, e1, e0);
+    }
+    finish_wide<MT, 1>(acc, 0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
 }
 
 }  // namespace lshbeam

@@ -475,6 +475,49 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
     return 0;
 }
 
+// Full vocabulary: one matrix product over all hidden rows of the call.  Up to 48 rows (fp32; 32 with bf16
+// words) the pass over E is what counts: k_logits_few.  Beyond that k_logits_rows; its row groups are as
+// even as they come in units of 16 rows, and among the splits the accumulators leave room for, the one
+// with the least work on the fullest CU is taken: rounds of 256 workgroups, a round with m row tiles costing
+// 8 (m + 1) us at d = 1000 (measured for m = 2 .. 6; m = 1: 20).
+constexpr int kRowsMaxMT = 6, kRowsMinD = 8;   // (a row holds at least one 16-byte chunk)
+bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an option that names another driver wins)
+    return sp->full_vocab && t->d >= kRowsMinD && t->opt[kOptLogitsWaves] == kAuto && t->opt[kOptLogitsEstage] == kAuto &&
+           t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto;
+}
+template <typename ET>
+void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspace& w) {
+    const lsh_tables* t = cx.t;
+    const int tiles = (R + kTileM - 1) / kTileM;
+    constexpr int WF = sizeof(ET) == 2 ? 4 : 2, FEW = sizeof(ET) == 2 ? 2 : 3;
+    if (tiles <= FEW) {
+        const dim3 grid((unsigned)((t->V + kWideN - 1) / kWideN)), block(256);
+#define LSH_FEW(MTV)                                                                                           \
+    launch(cx, 1, k_logits_few<ET, MTV>, grid, block, few_lds_bytes<ET>(MTV), (const ET*)t->E, t->ld, t->d, H, R, t->V, \
+           w.logits, w.cpitch, w.records())
+        if (tiles == 1) LSH_FEW(1); else if (tiles == 2) LSH_FEW(2); else LSH_FEW(3);
+#undef LSH_FEW
+        return;
+    }
+    const int gx = (t->V + 64 * WF - 1) / (64 * WF);
+    int mt = kRowsMaxMT;
+    int64_t best = INT64_MAX;
+    for (int m = 1; m <= kRowsMaxMT; ++m) {
+        const int64_t cost = (((int64_t)((tiles + m - 1) / m) * gx + 255) / 256) * (m == 1 ? 5 : 2 * m + 2);
+        if (cost < best) { best = cost; mt = m; }
+    }
+    const int ng = (tiles + mt - 1) / mt;
+    const dim3 grid((unsigned)((gx + 7) / 8 * 8 * ng)), block(256);
+#define LSH_ROWS(MTV)                                                                                          \
+    launch(cx, 1, k_logits_rows<ET, MTV, WF>, grid, block, rows_lds_bytes<ET>(MTV), (const ET*)t->E, t->ld, t->d, H, R, \
+           t->V, gx, ng, w.logits, w.cpitch, w.records())
+    switch (mt) {
+        case 1: LSH_ROWS(1); break; case 2: LSH_ROWS(2); break; case 3: LSH_ROWS(3); break;
+        case 4: LSH_ROWS(4); break; case 5: LSH_ROWS(5); break; default: LSH_ROWS(6);
+    }
+#undef LSH_ROWS
+}
+
 template <typename ET>
 hipError_t allow_logits_lds() {
     constexpr int U1 = 8 / (ElemTraits<ET>::VEC / 4), U2 = 4 / (ElemTraits<ET>::VEC / 4);
@@ -769,6 +812,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
         parts = w.row_bitmaps;
     }
     bool selected = false;   // the step's tail already ran inside the fused kernel
+    bool wide = false;       // tile records of kWideN columns
     int rec_groups = 0;      // tile records per hidden row, if not one per tile (launch_logits)
     if (fused) {
         // One launch per step: the last workgroup of each sentence also runs the selection
@@ -831,17 +875,24 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
             cand = w.cand;
             count = w.count;
         }
-        rec_groups = t->dtype == LSH_F32 ? launch_logits<float>(cx, H_dev, sp, cand, count, w, fold ? &un : nullptr)
-                                         : launch_logits<uint16_t>(cx, H_dev, sp, cand, count, w);
+        // (on the full vocabulary all hidden rows of the call meet the same words: the contraction
+        // takes them as the rows of one sentence, so that E is not read again for every sentence)
+        lsh_step_params rows = *sp;
+        if (sp->full_vocab) { rows.S = 1; rows.B = sp->S * sp->B; }
+        wide = takes_rows(t, sp);
+        if (wide && t->dtype == LSH_F32) launch_logits_rows<float>(cx, H_dev, rows.B, w);
+        else if (wide) launch_logits_rows<uint16_t>(cx, H_dev, rows.B, w);
+        else if (t->dtype == LSH_F32) rec_groups = launch_logits<float>(cx, H_dev, &rows, cand, count, w, fold ? &un : nullptr);
+        else launch_logits<uint16_t>(cx, H_dev, &rows, cand, count, w);
     }
     if (!selected) {
-#define LSH_SELECT(RICHV, GROUPSV)                                                                    \
-    launch(cx, 2, k_select<RICHV, GROUPSV>, dim3(sp->S), dim3(kSelThreads), 0, (const float*)w.logits,  \
+#define LSH_SELECT(...)                                                                               \
+    launch(cx, 2, k_select<__VA_ARGS__>, dim3(sp->S), dim3(kSelThreads), 0, (const float*)w.logits,  \
            w.cpitch, (const TileRecord*)w.partials, (const int32_t*)w.ids2, w.ppitch, cand, count, t->V, \
            sp->B, beam_scores_dev, w.lse, out_beam_dev, out_word_dev, out_score_dev,                   \
            fused ? std::max(0, t->option(kOptFusedTile, 0)) : 0, rec_groups)
         // (the fused kernels leave rich records, k_logits_estage one record for a group of tiles)
-        if (fused) LSH_SELECT(true, false); else if (rec_groups > 0) LSH_SELECT(false, true); else LSH_SELECT(false, false);
+        if (fused) LSH_SELECT(true, false); else if (wide) LSH_SELECT(false, false, true); else if (rec_groups > 0) LSH_SELECT(false, true); else LSH_SELECT(false, false);
 #undef LSH_SELECT
     }
     HIP_TRY(hipGetLastError());

@@ -595,7 +595,7 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
                                                   out_score);
 }
 
-template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false>
+template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false, bool WIDE = false>
 __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const float* logits, int64_t cpitch,
                                                 const TileRecord* records, const int32_t* ids2, int64_t ppitch,
                                                 const int32_t* cand, const int32_t* count, int C_known,
@@ -642,8 +642,10 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
         }
     }
     const int C = C_known >= 0 ? C_known : (count ? count[s] : V);
-    // candidates per tile: 16, or what the fused kernel that wrote the records was told to use
-    const int tn = RICH ? select_tile_width(C, tile_forced, ppitch) : 16;
+    // candidates per tile: 16, what the fused kernel that wrote the records was told to use, or the
+    // wide tiles of the kernels that serve the full vocabulary
+    static_assert(!(WIDE && (RICH || GROUPS)), "wide records are plain pairs, one per wide tile");
+    const int tn = RICH ? select_tile_width(C, tile_forced, ppitch) : WIDE ? kWideN : 16;
     const int ntiles = (C + tn - 1) / tn;
     // GROUPS: the records stand for groups of tiles (select_front_grouped; rec_groups = the
     // workgroups per sentence of the kernel that wrote them; at most 64 beams)
@@ -1019,7 +1021,37 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     //     when that makes one round trip to memory of two (the logits were written by other
     //     XCDs: every sweep batch is a cold read)
     const uint32_t n_open = sh.misc[5];
-    if (n_open <= (uint32_t)kSelOpenCap) {
+    if (WIDE && n_open <= (uint32_t)kSelOpenCap) {
+        // (a wide tile: four consecutive columns per lane, two sweeps in flight)
+        for (uint32_t g0 = (uint32_t)(tid >> 4); g0 < n_open; g0 += 2 * (kSelThreads / 16)) {
+            float4 x[2];
+            int iq[2], c[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const uint32_t j = g0 + u * (kSelThreads / 16);
+                const uint32_t ent = sh.open_list[min(j, n_open - 1)];
+                iq[u] = (int)(ent >> 20);
+                const int cc = (int)(ent & 0xFFFFFu) * tn + 4 * (ln & 15);   // (the row pitch is a multiple of 64)
+                c[u] = j < n_open ? cc : C;
+                x[u] = *reinterpret_cast<const float4*>(lg + (size_t)iq[u] * cpitch + cc);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const float lsev = sh.lse[iq[u]], bsv = sh.bs[iq[u]];
+                const float xs[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float sc = bsv + (xs[e] - lsev);
+                    if (c[u] + e < C && f32_sortable(sc + 0.0f) >= tau) {
+                        const uint32_t pos = atomicAdd(&sh.misc[4], 1u);
+                        if (pos < (uint32_t)kSelListCap)
+                            sh.list[pos] = make_key(sc, ((uint32_t)iq[u] << 24) | (uint32_t)(c[u] + e));
+                    }
+                }
+            }
+        }
+        LSH_TRACE_ANY(2, 8);
+    } else if (n_open <= (uint32_t)kSelOpenCap) {
         auto open_tiles = [&](auto in_flight) {
             constexpr int U = decltype(in_flight)::value;
             for (uint32_t g0 = (uint32_t)(tid >> 4); g0 < n_open; g0 += U * (kSelThreads / 16)) {
@@ -1102,7 +1134,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
 
 // grid = S workgroups (one per sentence), kSelThreads threads: the selection as a kernel of its
 // own, after kernels that left rich (fused plans) or plain tile records.
-template <bool RICH, bool GROUPS>
+template <bool RICH, bool GROUPS, bool WIDE = false>
 __global__ void __launch_bounds__(kSelThreads)
 k_select(const float* __restrict__ logits, int64_t cpitch, const TileRecord* __restrict__ records,
          const int32_t* __restrict__ ids2, int64_t ppitch, const int32_t* __restrict__ cand,
@@ -1110,7 +1142,7 @@ k_select(const float* __restrict__ logits, int64_t cpitch, const TileRecord* __r
          float* __restrict__ lse_out /*[R]*/, int32_t* __restrict__ out_beam,
          int32_t* __restrict__ out_word, float* __restrict__ out_score, int tile_forced, int rec_groups) {
     __shared__ SelShared sh;
-    select_sentence<RICH, false, GROUPS>(sh, (int)blockIdx.x, logits, cpitch, records, ids2, ppitch, cand, count, -1,
+    select_sentence<RICH, false, GROUPS, WIDE>(sh, (int)blockIdx.x, logits, cpitch, records, ids2, ppitch, cand, count, -1,
                                          V, B, beam_scores, lse_out, out_beam, out_word, out_score, tile_forced,
                                          rec_groups);
 }
