@@ -63,15 +63,17 @@ typedef struct {
  *   perms_dev  int32 [P, K]: row p holds the first K entries of permutation p of 0..d-1
  *              (Eq. 5: Permute_p(x)[k] = x[perms[p][k]]).  Copied; validated to lie in [0, d).
  * Computes the band code of every row on the device (ties in the argmax go to the lowest k),
- * groups word ids by band code into one flat array per band (ids ascending inside a span; one
- * device radix sort over all bands) and stores (start, length) of every span in a two-choice
- * cuckoo table per band (parallel insertion on the device; the host only draws the hash
- * parameters and takes over if a band cannot be placed).
+ * groups word ids by band code into one flat array per band (ids ascending inside a span; a device
+ * radix sort of every band) and stores (start, length) of every span in a two-choice
+ * cuckoo table per band (parallel insertion on the device; the host takes over if a band cannot be
+ * placed).
  * Synchronous.  On success *out receives the handle. */
 lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const lsh_build_params* p,
                             void* hip_stream, lsh_tables** out);
 
-void lsh_free_tables(lsh_tables* t); /* NULL-safe */
+/* Frees a handle.  Its device memory, up to 64 MiB per device, is kept for the next build there and given
+ * back by lsh_free_tables(NULL) (or when a build runs out of memory). */
+void lsh_free_tables(lsh_tables* t);
 
 /* Per-call shape of a decode step; the paper's remaining hyper-parameters {B, T, t}. */
 typedef struct {

@@ -2,107 +2,345 @@
 // lookup", first step: T_w = {band code: [word ids]} flattened, CuckooT_w = {band code:
 // (start, length)}).
 //
-//   1. One 64-bit key per (band, word): band | band code | word id, most significant first.
-//      A single radix sort of all W*V keys groups every band's words by code with ids ascending
-//      inside a code (the sort is a library primitive, hipCUB; only the bits in use are sorted).
-//   2. Position p of the sorted array belongs to band p / V: the id field is the band's flat
-//      word array; a position whose code differs from its predecessor's starts a span.
-//   3. An exclusive scan of the span-start flags numbers the spans ("keys") of all bands; each
-//      start writes (code, start) of its key, the length is the distance to the next start.
-//   4. Cuckoo insertion, one thread per key, all bands at once (Alcantara et al.'s scheme for
+//   1. k_build_begin: permutations checked and copied, hash parameters drawn, tables cleared.
+//   2. k_row_codes (candidates.h): band codes of every embedding row, [W, V].
+//   3. Every band's words are grouped by code, ids ascending inside a code: a stable radix sort of
+//      the code alone (words start in id order), up to kRadixBits bits of it per pass -- ONE pass for
+//      codes of up to 12 bits.  k_radix_count, k_radix_scan, k_radix_scatter.
+//   4. The distinct codes ("keys") of a band and where their spans start: with one pass they are the
+//      digits that occur and come out of the scan; otherwise k_key_count / k_key_emit find the span
+//      starts in the sorted codes.
+//   5. Cuckoo insertion, one thread per key, all bands at once (Alcantara et al.'s scheme for
 //      two hash functions): a thread swaps its item into its first slot with a 64-bit
 //      atomicExch; if that evicts an item, the thread carries the evicted item to that item's
-//      other slot, and so on.  A chain longer than the limit marks the band as failed; the host
-//      draws new hash parameters for failed bands and only those are redone.
-//   5. The 8-byte (code, key index) words are expanded into the 16-byte slots the probe reads.
+//      other slot, and so on.  A chain longer than the limit marks the band as failed; failed bands
+//      alone are redone with new hash parameters.
+//   6. The 8-byte (code, key index) words are expanded into the 16-byte slots the probe reads.
+//
+// What bounds it is the pass over the embedding rows (2); the rest is a chain of short kernels.  Nothing
+// is copied to the host before the whole chain is under way: tables are sized for the most keys a band
+// can have, parameters are drawn on the device, and one copy of the status words ends the build.
+// V = 40000, d = 1000 fp32, 8 bands of 12 bits: 127 us, of which 36 us k_row_codes (160 MB at 4.4 TB/s) and
+// 45 us the other kernels; 700 us with a library sort of (band, code, id) keys, ten small copies, three
+// waits and an allocation for every array.
 #pragma once
 #include "candidates.h"
 
 namespace lshbeam {
 
 constexpr uint64_t kCuckooEmpty = ~0ull;
+constexpr int kRadixThreads = 512, kRadixWaves = kRadixThreads / kWave, kRadixBits = 12, kScanThreads = 1024;
+constexpr int kBuildBeginBlocks = 64;   // x extent of k_build_begin; as many "bad permutation" words
 
-struct SortKeyLayout {
-    int id_bits, code_bits;  // key = band << (id_bits + code_bits) | code << id_bits | id
-};
+// Elements of a band per workgroup of the sort: enough that the digit counters (2^12 of them to write,
+// scan and read per workgroup) do not outweigh the elements, few enough to use the chip.  At most
+// 65535 elements, which the 16-bit counters hold.
+inline int radix_chunk(int64_t V, int W) {
+    int64_t c = (V * W / 256 + 1023) / 1024 * 1024;
+    if (c < 4096) c = 4096;
+    if (c > 32768) c = 32768;
+    return (int)c;
+}
+inline size_t radix_scatter_lds(int digits) { return (size_t)digits * (kRadixWaves * 2 + 4); }
 
-__global__ void __launch_bounds__(256)
-k_make_sort_keys(const int32_t* __restrict__ codes /*[V, W]*/, int64_t V, int W, SortKeyLayout lay,
-                 uint64_t* __restrict__ keys /*[W * V]*/) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // = j * W + w
-    if (idx >= V * W) return;
-    const int64_t j = idx / W;
-    const int w = (int)(idx - j * W);
-    const uint64_t code = (uint64_t)(uint32_t)codes[idx];
-    keys[(int64_t)w * V + j] =
-        ((uint64_t)w << (lay.id_bits + lay.code_bits)) | (code << lay.id_bits) | (uint64_t)j;
+// Hash parameters of band w at the given attempt: a SplitMix64 sequence read at that place.
+__host__ __device__ inline BandMeta draw_band_meta(uint64_t seed, int w, int W, int attempt, uint32_t cap, int lg) {
+    uint32_t r[4];
+    for (int i = 0; i < 4; ++i) {
+        uint64_t z = seed + 0x9E3779B97F4A7C15ull * (4ull * ((uint64_t)attempt * (uint32_t)W + (uint32_t)w) + (uint64_t)i + 1ull);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        r[i] = (uint32_t)(z ^ (z >> 31));
+    }
+    BandMeta m{};
+    m.slot_off = (uint32_t)w * cap;
+    m.shift = 32u - (uint32_t)lg;
+    m.a0 = r[0] | 1u; m.b0 = r[1]; m.a1 = r[2] | 1u; m.b1 = r[3];
+    return m;
 }
 
-// words[p] = id field; head[p] = 1 iff p starts a span (first of its band, or a new code).
+// grid (kBuildBeginBlocks, W + 1).  Row w < W: band w's hash parameters and empty table (only the bands
+// flagged in `redo`, if given), its `failed` flag cleared.  Row W (first attempt): the permutations are
+// copied, entries outside [0, d) replaced by 0 and reported (bad_perms[block]), the tickets zeroed.
 __global__ void __launch_bounds__(256)
-k_split_sorted(const uint64_t* __restrict__ sorted, int64_t V, int W, SortKeyLayout lay,
-               int32_t* __restrict__ words, uint32_t* __restrict__ head) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= V * W) return;
-    const uint64_t k = sorted[p];
-    words[p] = (int32_t)(k & ((1ull << lay.id_bits) - 1ull));
-    // band and code together: everything above the id field
-    head[p] = (p % V == 0 || (k >> lay.id_bits) != (sorted[p - 1] >> lay.id_bits)) ? 1u : 0u;
+k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W, uint32_t cap, int lg, uint64_t seed,
+              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed,
+              const int32_t* __restrict__ perms_in, int n_perms, int d, int32_t* __restrict__ perms,
+              uint32_t* __restrict__ bad_perms, unsigned int* __restrict__ tickets, int n_tickets) {
+    const int w = blockIdx.y, tid = threadIdx.x;
+    const uint32_t first = blockIdx.x * blockDim.x + tid, step = gridDim.x * blockDim.x;
+    if (w < W) {
+        const bool again = !redo || redo[w];
+        if (first == 0) {
+            failed[w] = 0u;
+            if (again) bands[w] = draw_band_meta(seed, w, W, attempt, cap, lg);
+        }
+        if (again)
+            for (uint32_t i = first; i < cap; i += step) table[(size_t)w * cap + i] = kCuckooEmpty;
+        return;
+    }
+    if (!perms_in) return;
+    __shared__ uint32_t bad;
+    if (tid == 0) bad = 0u;
+    __syncthreads();
+    for (uint32_t i = first; i < (uint32_t)n_perms; i += step) {
+        const int32_t x = perms_in[i];
+        const bool ok = x >= 0 && x < d;
+        perms[i] = ok ? x : 0;
+        if (!ok) bad = 1u;
+    }
+    for (uint32_t i = first; i < (uint32_t)n_tickets; i += step) tickets[i] = 0u;
+    __syncthreads();
+    if (tid == 0) bad_perms[blockIdx.x] = bad;
 }
 
-// Every span start writes its key: code, start inside the band, band.
-__global__ void __launch_bounds__(256)
-k_emit_keys(const uint64_t* __restrict__ sorted, const uint32_t* __restrict__ head,
-            const uint32_t* __restrict__ key_index /*exclusive scan of head*/, int64_t V, int W,
-            SortKeyLayout lay, int32_t* __restrict__ key_code, uint32_t* __restrict__ key_start,
-            int32_t* __restrict__ key_band) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= V * W || !head[p]) return;
-    const uint32_t k = key_index[p];
-    const int w = (int)(p / V);
-    key_code[k] = (int32_t)((sorted[p] >> lay.id_bits) & ((1ull << lay.code_bits) - 1ull));
-    key_start[k] = (uint32_t)(p - (int64_t)w * V);
-    key_band[k] = w;
+// ---- the sort: grid (chunks, W) each ------------------------------------------------------------
+
+// counts[w][chunk][digit] (16 bits, digits in pairs)
+__global__ void __launch_bounds__(kRadixThreads)
+k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, int chunk, int shift, int digits,
+              uint32_t* __restrict__ counts) {
+    extern __shared__ uint32_t hist[];
+    const int tid = threadIdx.x, w = blockIdx.y, c = blockIdx.x;
+    for (int i = tid; i < digits / 2; i += kRadixThreads) hist[i] = 0u;
+    __syncthreads();
+    const int64_t begin = (int64_t)c * chunk, end = min(begin + chunk, V);
+    const int32_t* src = codes + (size_t)w * V;
+#pragma unroll 4
+    for (int64_t i = begin + tid; i < end; i += kRadixThreads) {
+        const uint32_t dg = ((uint32_t)src[i] >> shift) & (uint32_t)(digits - 1);
+        atomicAdd(&hist[dg >> 1], (dg & 1u) ? 65536u : 1u);
+    }
+    __syncthreads();
+    uint32_t* out = counts + ((size_t)w * gridDim.x + c) * (digits / 2);
+    for (int i = tid; i < digits / 2; i += kRadixThreads) out[i] = hist[i];
 }
 
-// Length of key k's span: up to the next key of the same band, or to the end of the band.
+// Sum over the chunks [0, n) of the counts of two digits.
+__device__ __forceinline__ uint2 sum_counts(const uint32_t* __restrict__ pair, int n, int pitch) {
+    uint32_t lo = 0, hi = 0;
+    int c = 0;
+    for (; c + 8 <= n; c += 8) {
+        uint32_t x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = pair[(size_t)(c + j) * pitch];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { lo += x[j] & 0xFFFFu; hi += x[j] >> 16; }
+    }
+    for (; c < n; ++c) { const uint32_t x = pair[(size_t)c * pitch]; lo += x & 0xFFFFu; hi += x >> 16; }
+    return make_uint2(lo, hi);
+}
+
+// One workgroup per band: where the words of each digit start in the band.  EMIT (the only pass): the
+// digits that occur are the band's keys.
+template <bool EMIT>
+__global__ void __launch_bounds__(kScanThreads)
+k_radix_scan(const uint32_t* __restrict__ counts, int chunks, int digits, uint32_t* __restrict__ starts /*[W][digit]*/,
+             int32_t* __restrict__ key_code, uint32_t* __restrict__ key_start, uint32_t key_pitch,
+             uint32_t* __restrict__ n_keys) {
+    constexpr int PER = (1 << kRadixBits) / kScanThreads;    // consecutive digits per thread
+    __shared__ uint32_t wsum[kScanThreads / kWave + 1];
+    const int tid = threadIdx.x, w = blockIdx.x, d0 = tid * PER;
+    const uint32_t* mine = counts + (size_t)w * chunks * (digits / 2) + d0 / 2;
+    uint32_t tot[PER] = {};
+#pragma unroll
+    for (int j = 0; j < PER; j += 2)
+        if (d0 + j < digits) {
+            const uint2 n = sum_counts(mine + j / 2, chunks, digits / 2);
+            tot[j] = n.x; tot[j + 1] = n.y;
+        }
+    uint32_t sum = 0, keys = 0, all;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) { sum += tot[j]; keys += tot[j] ? 1u : 0u; }
+    uint32_t at[PER];
+    at[0] = block_incl_scan(sum, wsum, &all) - sum;
+#pragma unroll
+    for (int j = 1; j < PER; ++j) at[j] = at[j - 1] + tot[j - 1];
+    if constexpr (EMIT) {
+        uint32_t k = block_incl_scan(keys, wsum, &all) - keys;
+        if (tid == 0) n_keys[w] = all;
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (tot[j]) {
+                key_code[(size_t)w * key_pitch + k] = d0 + j;
+                key_start[(size_t)w * key_pitch + k] = at[j];
+                ++k;
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (d0 + j < digits) starts[(size_t)w * digits + d0 + j] = at[j];
+}
+
+// Stable scatter of one chunk.  A wave owns a contiguous piece of the chunk and has digit counters of
+// its own in LDS (16 bits: a chunk has at most 65535 words), so order inside the chunk needs no
+// exchange but one prefix over the waves; inside a wave, words of equal digit are ranked by ballots, one
+// per digit bit.  (The vector instructions of the ballots bound it -- about 100 per 64 words -- which is why
+// a band is cut into chunks.)  ids_in == null: ids are the positions.
+__global__ void __launch_bounds__(kRadixThreads)
+k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict__ ids_in, int64_t V, int chunk, int shift,
+                int bits, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ starts, int32_t* __restrict__ codes_out,
+                int32_t* __restrict__ ids_out) {
+    extern __shared__ uint32_t rsm[];
+    const int digits = 1 << bits;
+    uint32_t* base = rsm;                                                   // [digit]
+    uint16_t* wpos = reinterpret_cast<uint16_t*>(rsm + digits);             // [wave][digit]
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id(), w = blockIdx.y, c = blockIdx.x;
+    const int32_t* src = codes_in + (size_t)w * V;
+    uint32_t* wpos32 = rsm + digits;
+    for (int i = tid; i < digits * kRadixWaves / 2; i += kRadixThreads) wpos32[i] = 0u;   // (digits >= 2)
+    // where this chunk's words of a digit go: behind those of the chunks in front (all digit pairs of a
+    // thread side by side: every load waits for memory once, not once per pair)
+    {
+        constexpr int PAIRS = (1 << kRadixBits) / 2 / kRadixThreads, BATCH = 4;
+        const uint2* st = reinterpret_cast<const uint2*>(starts + (size_t)w * digits);
+        const uint32_t* cn = counts + (size_t)w * gridDim.x * (digits / 2);
+        const int last = digits / 2 - 1;
+        uint2 at[PAIRS];
+#pragma unroll
+        for (int j = 0; j < PAIRS; ++j) at[j] = st[min(tid + j * kRadixThreads, last)];
+        for (int c0 = 0; c0 < c; c0 += BATCH) {
+            uint32_t x[BATCH][PAIRS];
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q)
+#pragma unroll
+                for (int j = 0; j < PAIRS; ++j)
+                    x[q][j] = c0 + q < c ? cn[(size_t)(c0 + q) * (digits / 2) + min(tid + j * kRadixThreads, last)] : 0u;
+#pragma unroll
+            for (int q = 0; q < BATCH; ++q)
+#pragma unroll
+                for (int j = 0; j < PAIRS; ++j) { at[j].x += x[q][j] & 0xFFFFu; at[j].y += x[q][j] >> 16; }
+        }
+#pragma unroll
+        for (int j = 0; j < PAIRS; ++j)
+            if (tid + j * kRadixThreads <= last) {
+                base[2 * (tid + j * kRadixThreads)] = at[j].x;
+                base[2 * (tid + j * kRadixThreads) + 1] = at[j].y;
+            }
+    }
+    __syncthreads();
+    const int64_t begin = (int64_t)c * chunk, end = min(begin + chunk, V);
+    const int piece = (((int)(end - begin) + kRadixWaves - 1) / kRadixWaves + kWave - 1) / kWave * kWave;
+    const int64_t p0 = begin + (int64_t)wv * piece, p1 = min(p0 + piece, end);
+    const uint32_t mask = (uint32_t)digits - 1u;
+    constexpr int AHEAD = 8;                                // words per lane asked for at a time
+    for (int64_t i0 = p0; i0 < p1; i0 += AHEAD * kWave) {
+        uint32_t code[AHEAD];
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) code[j] = (uint32_t)src[min(i0 + j * kWave + ln, p1 - 1)];
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j)
+            if (i0 + j * kWave + ln < p1) {
+                const uint32_t dg = (code[j] >> shift) & mask;
+                atomicAdd(&wpos32[((uint32_t)wv * digits + dg) >> 1], (dg & 1u) ? 65536u : 1u);
+            }
+    }
+    __syncthreads();
+    for (int i = tid; i < digits / 2; i += kRadixThreads) {  // exclusive prefix over the waves, two digits at a time
+        uint32_t n[kRadixWaves], run = 0;                    // (no carry from the low half: a chunk fits 16 bits)
+#pragma unroll
+        for (int v = 0; v < kRadixWaves; ++v) n[v] = wpos32[v * (digits / 2) + i];
+#pragma unroll
+        for (int v = 0; v < kRadixWaves; ++v) {
+            wpos32[v * (digits / 2) + i] = run;
+            run += n[v];
+        }
+    }
+    __syncthreads();
+    uint16_t* pos = wpos + wv * digits;
+    for (int64_t i0 = p0; i0 < p1; i0 += AHEAD * kWave) {   // (uniform in the wave)
+        uint32_t code[AHEAD];
+        int32_t id[AHEAD];
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            const int64_t i = min(i0 + j * kWave + ln, p1 - 1);
+            code[j] = (uint32_t)src[i];
+            id[j] = ids_in ? ids_in[(size_t)w * V + i] : (int32_t)i;
+        }
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            const uint32_t dg = (code[j] >> shift) & mask;
+            const bool in = i0 + j * kWave + ln < p1;
+            uint64_t same = __ballot(in);
+            for (int b = 0; b < bits; ++b) {
+                const uint64_t set = __ballot((dg >> b) & 1u);
+                same &= ((dg >> b) & 1u) ? set : ~set;
+            }
+            const uint32_t rank = lanes_below(same), n = (uint32_t)__popcll(same);
+            if (in) {
+                const uint32_t before = pos[dg];
+                const size_t at = (size_t)w * V + base[dg] + before + rank;
+                if (codes_out) codes_out[at] = (int32_t)code[j];
+                ids_out[at] = id[j];
+                if (rank == n - 1u) pos[dg] = (uint16_t)(before + n);   // (after every lane's read: one wave, LDS in order)
+            }
+        }
+    }
+}
+
+// ---- keys of a band sorted in several passes: grid (chunks, W) -----------------------------------
+
+__device__ __forceinline__ bool starts_span(const int32_t* __restrict__ codes, int64_t i) {
+    return i == 0 || codes[i] != codes[i - 1];
+}
+// spans[w][chunk]: span starts in the chunk
+__global__ void __launch_bounds__(kRadixThreads)
+k_key_count(const int32_t* __restrict__ codes /*[W, V] sorted*/, int64_t V, int chunk, uint32_t* __restrict__ spans) {
+    __shared__ uint32_t wsum[kRadixWaves + 1];
+    const int32_t* src = codes + (size_t)blockIdx.y * V;
+    const int64_t begin = (int64_t)blockIdx.x * chunk, end = min(begin + chunk, V);
+    uint32_t n = 0, all;
+    for (int64_t i = begin + threadIdx.x; i < end; i += kRadixThreads) n += starts_span(src, i) ? 1u : 0u;
+    block_incl_scan(n, wsum, &all);
+    if (threadIdx.x == 0) spans[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = all;
+}
+__global__ void __launch_bounds__(kRadixThreads)
+k_key_emit(const int32_t* __restrict__ codes, int64_t V, int chunk, const uint32_t* __restrict__ spans,
+           int32_t* __restrict__ key_code, uint32_t* __restrict__ key_start, uint32_t key_pitch, uint32_t* __restrict__ n_keys) {
+    __shared__ uint32_t wsum[kRadixWaves + 1];
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id(), w = blockIdx.y, c = blockIdx.x;
+    const int32_t* src = codes + (size_t)w * V;
+    uint32_t n = 0, before, mine = 0, all;
+    for (int i = tid; i < c; i += kRadixThreads) n += spans[(size_t)w * gridDim.x + i];
+    block_incl_scan(n, wsum, &before);                       // keys of the chunks in front
+    const int64_t begin = (int64_t)c * chunk, end = min(begin + chunk, V);
+    const int piece = (((int)(end - begin) + kRadixWaves - 1) / kRadixWaves + kWave - 1) / kWave * kWave;
+    const int64_t p0 = begin + (int64_t)wv * piece, p1 = min(p0 + piece, end);
+    for (int64_t i = p0 + ln; i < p1; i += kWave) mine += starts_span(src, i) ? 1u : 0u;
+    // (lane totals scanned over the workgroup: the waves in front, then the wave's own from its ballots)
+    const uint32_t incl = block_incl_scan(mine, wsum, &all);
+    uint32_t k = before + wave_read_lane(incl - mine, 0);
+    for (int64_t i0 = p0; i0 < p1; i0 += kWave) {
+        const int64_t i = i0 + ln;
+        const bool head = i < p1 && starts_span(src, i);
+        const uint64_t heads = __ballot(head);
+        if (head) {
+            const size_t at = (size_t)w * key_pitch + k + lanes_below(heads);
+            key_code[at] = src[i];
+            key_start[at] = (uint32_t)i;
+        }
+        k += (uint32_t)__popcll(heads);
+    }
+    if (c == (int)gridDim.x - 1 && tid == 0) n_keys[w] = before + all;
+}
+
+// ---- cuckoo tables -------------------------------------------------------------------------------
+
+// grid (key_pitch / 256, W), one thread per key.  Item = code << 32 | key index.  `failed[w]` is set when
+// a chain in band w exceeds max_chain (the item in hand is dropped: the band is redone).
 __global__ void __launch_bounds__(256)
-k_key_lengths(const uint32_t* __restrict__ key_start, const int32_t* __restrict__ key_band,
-              uint32_t n_keys, uint32_t V, uint32_t* __restrict__ key_len) {
+k_cuckoo_insert(uint64_t* __restrict__ table, const BandMeta* __restrict__ bands, const int32_t* __restrict__ key_code,
+                uint32_t key_pitch, const uint32_t* __restrict__ n_keys, int max_chain,
+                const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed) {
     const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_keys) return;
-    const bool last = (k + 1 == n_keys) || key_band[k + 1] != key_band[k];
-    key_len[k] = (last ? V : key_start[k + 1]) - key_start[k];
-}
-
-// table[i] = empty for the slots of the bands flagged in `redo` (all bands if redo == nullptr).
-__global__ void __launch_bounds__(256)
-k_cuckoo_clear(uint64_t* __restrict__ table, const BandMeta* __restrict__ bands,
-               const uint32_t* __restrict__ band_cap, int W, const uint32_t* __restrict__ redo) {
     const int w = blockIdx.y;
-    if (w >= W || (redo && !redo[w])) return;
-    const uint32_t cap = band_cap[w];
-    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < cap; i += gridDim.x * blockDim.x)
-        table[bands[w].slot_off + i] = kCuckooEmpty;
-}
-
-// One thread per key.  Item = code << 32 | key index.  `failed[w]` is set when a chain in band w
-// exceeds max_chain (the item in hand is dropped: the band is redone with new parameters).
-__global__ void __launch_bounds__(256)
-k_cuckoo_insert(uint64_t* __restrict__ table, const BandMeta* __restrict__ bands,
-                const int32_t* __restrict__ key_code, const int32_t* __restrict__ key_band,
-                uint32_t n_keys, int max_chain, const uint32_t* __restrict__ redo,
-                uint32_t* __restrict__ failed) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_keys) return;
-    const int w = key_band[k];
-    if (redo && !redo[w]) return;
+    if (k >= n_keys[w] || (redo && !redo[w])) return;
     const BandMeta m = bands[w];
-    uint64_t item = ((uint64_t)(uint32_t)key_code[k] << 32) | (uint64_t)k;
-    uint32_t pos = cuckoo_hash(m.a0, m.b0, (uint32_t)key_code[k], m.shift);
+    const uint32_t my_code = (uint32_t)key_code[(size_t)w * key_pitch + k];
+    uint64_t item = ((uint64_t)my_code << 32) | (uint64_t)k;
+    uint32_t pos = cuckoo_hash(m.a0, m.b0, my_code, m.shift);
     for (int step = 0; step < max_chain; ++step) {
-        const uint64_t old = atomicExch((unsigned long long*)&table[m.slot_off + pos],
-                                        (unsigned long long)item);
+        const uint64_t old = atomicExch((unsigned long long*)&table[m.slot_off + pos], (unsigned long long)item);
         if (old == kCuckooEmpty) return;
         item = old;  // carry the evicted item to its other slot
         const uint32_t code = (uint32_t)(old >> 32);
@@ -113,49 +351,41 @@ k_cuckoo_insert(uint64_t* __restrict__ table, const BandMeta* __restrict__ bands
     failed[w] = 1u;
 }
 
-// Where the vocabulary slices 1, 2, 3 of the hit-count kernel begin inside key k's span (ids are
-// ascending inside a span): lower bounds of slice * slice_ids, relative to the span's start.
+// grid (cap / 256, W).  8-byte table words -> the 16-byte slots of the probe, and beside every used slot
+// where the vocabulary slices 1, 2, 3 of the hit-count kernel begin inside its span (ids are ascending
+// there): lower bounds of slice * slice_ids, relative to the span's start.  (Cuts of empty slots are never used.)
 __global__ void __launch_bounds__(256)
-k_slice_cuts(const int32_t* __restrict__ words, const uint32_t* __restrict__ key_start,
-             const uint32_t* __restrict__ key_len, const int32_t* __restrict__ key_band,
-             uint32_t n_keys, uint32_t V, int slice_ids, uint4* __restrict__ key_cut) {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n_keys) return;
-    const int32_t* span = words + (size_t)key_band[k] * V + key_start[k];
-    const uint32_t len = key_len[k];
-    uint32_t cut[3];
-    for (int q = 1; q <= 3; ++q) {
-        const int32_t bound = q * slice_ids;
-        uint32_t lo = 0, hi = len;  // first position whose id is >= bound
-        while (lo < hi) {
-            const uint32_t mid = (lo + hi) >> 1;
-            if (span[mid] < bound) lo = mid + 1; else hi = mid;
-        }
-        cut[q - 1] = lo;
-    }
-    key_cut[k] = make_uint4(cut[0], cut[1], cut[2], len);
-}
-
-// 8-byte table words -> the 16-byte slots of the probe (and the slice cuts beside them).
-__global__ void __launch_bounds__(256)
-k_cuckoo_finalize(const uint64_t* __restrict__ table, uint64_t n_slots,
-                  const uint32_t* __restrict__ key_start, const uint32_t* __restrict__ key_len,
-                  const uint4* __restrict__ key_cut, Slot* __restrict__ slots,
-                  uint4* __restrict__ cuts) {
-    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n_slots) return;
-    const uint64_t e = table[i];
+k_cuckoo_finalize(const uint64_t* __restrict__ table, uint32_t cap, const uint32_t* __restrict__ key_start,
+                  uint32_t key_pitch, const uint32_t* __restrict__ n_keys, const int32_t* __restrict__ words, uint32_t V,
+                  int slice_ids, Slot* __restrict__ slots, uint4* __restrict__ cuts) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int w = blockIdx.y;
+    if (i >= cap) return;
+    const size_t at = (size_t)w * cap + i;
+    const uint64_t e = table[at];
     Slot s{-1, 0u, 0u, 0u};
-    uint4 c = make_uint4(0u, 0u, 0u, 0u);
     if (e != kCuckooEmpty) {
         const uint32_t k = (uint32_t)e;
+        const uint32_t* starts = key_start + (size_t)w * key_pitch;
         s.key = (int32_t)(uint32_t)(e >> 32);
-        s.start = key_start[k];
-        s.len = key_len[k];
-        c = key_cut[k];
+        s.start = starts[k];
+        s.len = (k + 1 < n_keys[w] ? starts[k + 1] : V) - s.start;
+        const int32_t* span = words + (size_t)w * V + s.start;
+        // first position whose id is >= the bound: the three searches side by side, since each step waits
+        // for its load
+        uint32_t lo[3] = {0u, 0u, 0u};
+        for (uint32_t n = s.len; n; n >>= 1) {   // (answers lie in [lo, lo + n])
+            int32_t id[3];
+            const uint32_t half = n >> 1;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) id[q] = span[min(lo[q] + half, s.len - 1u)];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                if (lo[q] + half < s.len && id[q] < (q + 1) * slice_ids) lo[q] += half + 1u;
+        }
+        cuts[at] = make_uint4(lo[0], lo[1], lo[2], s.len);
     }
-    slots[i] = s;
-    cuts[i] = c;
+    slots[at] = s;
 }
 
 }  // namespace lshbeam

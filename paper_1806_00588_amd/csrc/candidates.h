@@ -1,6 +1,6 @@
 // Winner-take-all hashing, cuckoo probe, bucket walk and candidate-list compaction.
 //
-//   k_band_codes  : band codes (Eq. 4-8) of n rows; used on E at build time and for inspection.
+//   k_row_codes   : band codes (Eq. 4-8) of n rows; used on E at build time and for inspection.
 //   k_candidates  : one workgroup per sentence.  Hashes the sentence's B hidden rows, probes the
 //                   per-band cuckoo tables (Algorithm 1, lines 1-2), walks the hit spans
 //                   (lines 3-6) marking a V-bit presence bitmap held in LDS, ORs in the
@@ -91,35 +91,96 @@ __device__ __forceinline__ void cuckoo_find_slice(const Slot* __restrict__ slots
     *len = (ln && hi > lo) ? min(hi, ln) - min(lo, ln) : 0u;
 }
 
-// Eq. 4-8 for one (row, band): u windowed argmaxes (strict '>', so the lowest k wins a tie),
-// packed with the first code in the most significant bits.
-template <typename ET>
-__device__ __forceinline__ int32_t band_code_of(const ET* __restrict__ row,
-                                                const int32_t* __restrict__ perms, int w, int u,
-                                                int K, int bits) {
-    int32_t code = 0;
-    for (int i = 0; i < u; ++i) {
-        const int32_t* pm = perms + (size_t)(w * u + i) * K;
-        int best = 0;
-        float bv = elem_f32(row + pm[0]);
-        for (int k = 1; k < K; ++k) {
-            const float v = elem_f32(row + pm[k]);
-            if (v > bv) { bv = v; best = k; }
-        }
-        code = (code << bits) | best;
-    }
-    return code;
+// Band codes (Eq. 4-8) of n rows, any pitch and alignment.  A workgroup copies `rows` = 2^lg_rows of
+// them to LDS in 16-byte pieces, a wave per row; one thread per (row, permutation) takes the windowed
+// argmax there (strict '>', so the lowest k wins a tie; a permutation's window positions stay in
+// registers from row to row), one per (row, band) packs the codes, first code in the most significant
+// bits.  The floor is one pass over the rows: a thread per (row, band) gathering from memory took 151 us
+// for V = 40000, d = 1000, P = 32, K = 8 (160 MB), this takes 36 (55 with one row's loads in flight per
+// wave); bf16, V = 200000, d = 1024, P = 64, K = 16 (410 MB): 158 us, the windows' LDS reads counting as much.
+// LDS: rows x pitch bytes (a multiple of 16), then rows x P 16-bit codes.
+constexpr int kRowCodeThreads = 256, kRowCodeWindow = 16;   // (longer windows are read again for every row)
+inline size_t row_codes_pitch(int d, size_t elem) { return ((size_t)d * elem + 15) & ~(size_t)15; }
+inline size_t row_codes_lds(int rows, int d, size_t elem, int P) { return rows * (row_codes_pitch(d, elem) + 2 * (size_t)P); }
+// Rows per workgroup: up to 16 while four workgroups fit a CU and there are two workgroups per CU.
+inline int row_codes_lg_rows(int64_t n, int d, size_t elem, int P) {
+    int lg = 4;
+    const size_t lds = P > kRowCodeThreads ? 78 * 1024 : 39 * 1024;   // (many permutations: their loads are shared by more rows)
+    while (lg > 0 && (row_codes_lds(1 << lg, d, elem, P) > lds || (n >> lg) < 512)) --lg;
+    return lg;
 }
-
 template <typename ET>
-__global__ void __launch_bounds__(256)
-k_band_codes(const ET* __restrict__ X, int64_t ld, int64_t n, const int32_t* __restrict__ perms,
-             int P, int K, int W, int bits, int32_t* __restrict__ out) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= n * W) return;
-    const int64_t row = idx / W;
-    const int w = (int)(idx - row * W);
-    out[idx] = band_code_of<ET>(X + row * ld, perms, w, P / W, K, bits);
+__global__ void __launch_bounds__(kRowCodeThreads)
+k_row_codes(const ET* __restrict__ X, int64_t ld, int64_t n, int d, const int32_t* __restrict__ perms, int P, int K,
+            int W, int bits, int lg_rows, int32_t* __restrict__ out, int64_t row_stride, int64_t band_stride) {
+    constexpr int CK = 16 / (int)sizeof(ET), NW = kRowCodeThreads / kWave, AHEAD = 8;
+    extern __shared__ uint4 row_sm[];
+    const int rows = 1 << lg_rows, pitch = (int)((d * sizeof(ET) + 15) & ~(size_t)15);
+    char* stage = reinterpret_cast<char*>(row_sm);
+    uint16_t* codes = reinterpret_cast<uint16_t*>(stage + (size_t)rows * pitch);   // [rows][P]
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
+    const int64_t row0 = (int64_t)blockIdx.x << lg_rows;
+    const int nch = d / CK;
+    const int rw = __builtin_amdgcn_readfirstlane(wv);
+    // the wave's rows rw, rw + NW, ... as one run of pieces of up to 64 chunks, AHEAD pieces in flight
+    for (int r = rw, c = 0; nch > 0 && r < rows;) {
+        Chunk16U<ET> v[AHEAD];
+        int r1 = r, c1 = c;
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            if (r1 >= rows) break;   // (uniform)
+            v[j] = *reinterpret_cast<const Chunk16U<ET>*>(X + min(row0 + r1, n - 1) * ld + (size_t)CK * min(c1 + ln, nch - 1));
+            c1 += kWave;
+            if (c1 >= nch) { c1 = 0; r1 += NW; }
+        }
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            if (r >= rows) break;
+            if (c + ln < nch)
+                *reinterpret_cast<uint4*>(stage + (size_t)r * pitch + 16 * (c + ln)) = make_uint4(v[j].w[0], v[j].w[1], v[j].w[2], v[j].w[3]);
+            c += kWave;
+            if (c >= nch) { c = 0; r += NW; }
+        }
+    }
+    for (int r = rw; r < rows; r += NW)
+        if (ln < d - nch * CK)
+            reinterpret_cast<ET*>(stage + (size_t)r * pitch)[nch * CK + ln] = X[min(row0 + r, n - 1) * ld + nch * CK + ln];
+    __syncthreads();
+    for (int p0 = 0; p0 < P; p0 += kRowCodeThreads) {
+        const int np = min(P - p0, kRowCodeThreads), at_once = kRowCodeThreads / np;   // (uniform)
+        const int r0 = small_div(tid, np), p = p0 + tid - r0 * np;
+        if (r0 >= at_once) continue;
+        const int32_t* pm = perms + (size_t)p * K;
+        int idx[kRowCodeWindow];
+#pragma unroll
+        for (int k = 0; k < kRowCodeWindow; ++k)
+            if (k < K) idx[k] = pm[k];
+        for (int r = r0; r < rows; r += at_once) {
+            const ET* row = reinterpret_cast<const ET*>(stage + (size_t)r * pitch);
+            float v[kRowCodeWindow];
+#pragma unroll
+            for (int k = 0; k < kRowCodeWindow; ++k)
+                if (k < K) v[k] = elem_f32(row + idx[k]);   // (uniform)
+            int best = 0;
+            float bv = v[0];
+#pragma unroll
+            for (int k = 1; k < kRowCodeWindow; ++k)
+                if (k < K && v[k] > bv) { bv = v[k]; best = k; }
+            for (int k = kRowCodeWindow; k < K; ++k) {
+                const float x = elem_f32(row + pm[k]);
+                if (x > bv) { bv = x; best = k; }
+            }
+            codes[r * P + p] = (uint16_t)best;
+        }
+    }
+    __syncthreads();
+    const int u = P / W;
+    for (int i = tid; i < (W << lg_rows); i += kRowCodeThreads) {
+        const int r = i & (rows - 1), w = i >> lg_rows;
+        int32_t code = 0;
+        for (int q = 0; q < u; ++q) code = (code << bits) | codes[r * P + w * u + q];
+        if (row0 + r < n) out[(row0 + r) * row_stride + w * band_stride] = code;
+    }
 }
 
 constexpr int kCandThreads = 1024;

@@ -136,6 +136,9 @@ __device__ __forceinline__ float elem_f32(const uint16_t* p) {
     return __uint_as_float((uint32_t)(*p) << 16);
 }
 
+struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };    // 16 bytes at any float's address
+template <typename ET> struct __attribute__((packed, aligned(sizeof(ET)))) Chunk16U { uint32_t w[4]; };   // at any element's
+
 // Stores that other workgroups of the SAME kernel will read (the one-launch plan's last workgroup
 // reads what the others computed): device-scope atomic stores, which go through to memory instead
 // of staying dirty in the L2 of the writer's XCD -- the eight XCDs' L2s are not coherent with each

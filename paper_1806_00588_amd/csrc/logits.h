@@ -1151,8 +1151,6 @@ template <typename ET> __host__ __device__ constexpr int rows_pitch() { return s
 template <typename ET> __host__ __device__ constexpr size_t rows_lds_bytes(int MT) {
     return (size_t)2 * rows_planes<ET>() * ((MT + 1) / 2 * 32) * rows_pitch<ET>() + 4 * kTileM * sizeof(float2);
 }
-struct __attribute__((packed, aligned(4))) Float4U { float x, y, z, w; };    // 16 bytes at any float's address
-template <typename ET> struct __attribute__((packed, aligned(sizeof(ET)))) Chunk16U { uint32_t w[4]; };   // at any element's
 
 // The 16 bytes of a row of d >= 16 / sizeof(ET) elements that begin at element k, zeros past the row's
 // end: what lies past it is never read (one clamped load, then shifted into place in registers).

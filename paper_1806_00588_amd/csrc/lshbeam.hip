@@ -20,8 +20,6 @@
 #include <type_traits>
 #include <vector>
 
-#include <hipcub/hipcub.hpp>
-
 #include "beam.h"
 #include "build_tables.h"
 #include "candidates.h"
@@ -67,11 +65,14 @@ constexpr int kTicketSlots = 256;   // workspaces per handle that can take the o
 constexpr int kTicketBlock = 64;    // counters per workspace = sentences of a fused step at most
 
 
-struct HostBand {
+struct Band {
+    int n_keys = 0;      // distinct codes
+    int capacity = 0;    // slots of its cuckoo table
+    BandMeta meta{};
+};
+struct HostBand : Band {           // a band being built on the host
     std::vector<int32_t> keys;     // distinct band codes, ascending
     std::vector<int32_t> offsets;  // keys.size() + 1 span boundaries into the band's word array
-    int capacity = 0;
-    BandMeta meta{};
 };
 
 // Launch-plan options of a handle (lsh_set_option); kAuto = the library's own rule.
@@ -100,13 +101,16 @@ struct lsh_tables {
     const void* E = nullptr;
     int V = 0, d = 0, dtype = 0, K = 0, P = 0, W = 0, u = 0, bits = 0;
     int64_t ld = 0;
+    void* arena = nullptr;           // device memory of everything below, and what the build worked in
+    size_t arena_bytes = 0;
+    void* slot_arena = nullptr;      // ... but the slots and cuts, where their number was not known before the rest
     int32_t* perms_dev = nullptr;    // [P, K]
-    int32_t* codes_dev = nullptr;    // [V, W] band codes of the embedding rows
+    int32_t* codes_dev = nullptr;    // [W, V] band codes of the embedding rows
     int32_t* words_dev = nullptr;    // [W, V] word ids grouped by band code
     Slot* slots_dev = nullptr;       // all bands' cuckoo slots, concatenated
     uint4* cuts_dev = nullptr;       // per slot: where vocabulary slices 1..3 begin in its span
     BandMeta* bands_dev = nullptr;   // [W]
-    std::vector<HostBand> bands;
+    std::vector<Band> bands;         // what the inspection calls know about each band
     int wg_candidates_lds = 0;
     int wg_fused_lds = 0;
     int wg_hit_rows_lds = 0;   // 0: the hit-count kernel cannot run on these tables (t > 1 unsupported)
@@ -545,15 +549,76 @@ hipError_t allow_logits_lds() {
         }                                               \
     } while (0)
 
+// The device memory of a freed handle stays with the library for the next build there: one block per
+// device, at most kKeptBytes (a driver allocation or release of a few MiB takes 20 to 60 us, as long as the
+// kernels of the build; an index is rebuilt where the embeddings change).  Given back by
+// lsh_free_tables(NULL) and wherever an allocation of a build fails; guarded by its own mutex.  A block is
+// kept only once the device has finished everything that was launched before.
+constexpr size_t kKeptBytes = (size_t)64 << 20;
+struct KeptBlock { void* p = nullptr; size_t bytes = 0; };
+std::mutex g_kept_mu;
+KeptBlock g_kept[kMaxDevices];
+
+KeptBlock swap_kept(int dev, KeptBlock b) {
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    std::swap(b, g_kept[dev]);
+    return b;
+}
+void give_back_kept() {
+    for (int d = 0; d < kMaxDevices; ++d) (void)hipFree(swap_kept(d, KeptBlock{}).p);
+}
+hipError_t alloc_arena(int dev, size_t bytes, void** p, size_t* got) {
+    if (dev < kMaxDevices && bytes <= kKeptBytes) {
+        const KeptBlock b = swap_kept(dev, KeptBlock{});
+        if (b.p && b.bytes >= bytes) { *p = b.p; *got = b.bytes; return hipSuccess; }
+        (void)hipFree(b.p);
+    }
+    *got = bytes;
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        give_back_kept();
+        e = hipMalloc(p, bytes);
+    }
+    return e;
+}
+void release_arena(int dev, void* p, size_t bytes) {
+    if (!p) return;
+    if (dev < kMaxDevices && bytes <= kKeptBytes) {
+        int cur = 0;
+        const bool ok = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess) &&
+                        hipDeviceSynchronize() == hipSuccess;   // (as hipFree would)
+        if (cur != dev) (void)hipSetDevice(cur);
+        if (ok) { p = swap_kept(dev, KeptBlock{p, bytes}).p; }
+    }
+    (void)hipFree(p);
+}
+
+// Regions of one device allocation, each 256-byte aligned: sized with base = null, then placed.
+struct Carver {
+    char* base;
+    size_t bytes = 0;
+    template <typename T> T* take(size_t n) {
+        T* p = reinterpret_cast<T*>(base + bytes);
+        bytes += align_up(n * sizeof(T));
+        return base ? p : nullptr;
+    }
+};
+
+lsh_status place_slots(lsh_tables* t, uint64_t n_slots) {
+    (void)hipFree(t->slot_arena);
+    t->slot_arena = nullptr;
+    const size_t slot_bytes = align_up(n_slots * sizeof(Slot));
+    HIP_TRY(hipMalloc(&t->slot_arena, slot_bytes + n_slots * sizeof(uint4)));
+    t->slots_dev = (Slot*)t->slot_arena;
+    t->cuts_dev = (uint4*)((char*)t->slot_arena + slot_bytes);
+    return LSH_OK;
+}
+
 // Host path of the table build: codes are copied back, every band's (code, id) pairs are sorted
 // and inserted into its cuckoo table on the host, then uploaded.
 lsh_status build_on_host(lsh_tables* t, hipStream_t st, SplitMix64& rng) {
     const size_t V = t->V, W = t->W;
-    (void)hipFree(t->words_dev); t->words_dev = nullptr;
-    (void)hipFree(t->slots_dev); t->slots_dev = nullptr;
-    (void)hipFree(t->cuts_dev); t->cuts_dev = nullptr;
-    (void)hipFree(t->bands_dev); t->bands_dev = nullptr;
-    t->bands.clear();
     std::vector<Slot> slots_host;
     std::vector<int32_t> codes(V * W);
     HIP_TRY(hipMemcpyAsync(codes.data(), t->codes_dev, V * W * sizeof(int32_t), hipMemcpyDeviceToHost, st));
@@ -562,12 +627,12 @@ lsh_status build_on_host(lsh_tables* t, hipStream_t st, SplitMix64& rng) {
     // per band: group word ids by code (ids ascending inside a span), then the cuckoo table
     std::vector<int32_t> words(V * W);
     std::vector<uint64_t> order(V);
-    t->bands.resize(W);
+    std::vector<HostBand> hbs(W);
     for (size_t w = 0; w < W; ++w) {
         for (size_t j = 0; j < V; ++j)
-            order[j] = ((uint64_t)(uint32_t)codes[j * W + w] << 32) | (uint64_t)j;
+            order[j] = ((uint64_t)(uint32_t)codes[w * V + j] << 32) | (uint64_t)j;
         std::sort(order.begin(), order.end());
-        HostBand& hb = t->bands[w];
+        HostBand& hb = hbs[w];
         for (size_t i = 0; i < V; ++i) {
             const int32_t code = (int32_t)(order[i] >> 32);
             if (i == 0 || code != hb.keys.back()) {
@@ -577,20 +642,19 @@ lsh_status build_on_host(lsh_tables* t, hipStream_t st, SplitMix64& rng) {
             words[w * V + i] = (int32_t)(uint32_t)order[i];
         }
         hb.offsets.push_back((int32_t)V);
+        hb.n_keys = (int)hb.keys.size();
         const lsh_status rc = build_cuckoo(hb, rng, slots_host, (uint32_t)slots_host.size());
         if (rc != LSH_OK) return rc;
     }
     std::vector<BandMeta> metas(W);
-    for (size_t w = 0; w < W; ++w) metas[w] = t->bands[w].meta;
+    for (size_t w = 0; w < W; ++w) metas[w] = hbs[w].meta;
 
-    // 16 bytes of slack: k_hit_rows reads ids with 16-byte loads that may straddle the end
-    HIP_TRY(hipMalloc((void**)&t->words_dev, V * W * sizeof(int32_t) + 16));
     // where the vocabulary slices of the hit-count kernel begin inside every span
     std::vector<uint4> cuts_host(slots_host.size(), make_uint4(0u, 0u, 0u, 0u));
     const int slice_ids = hit_slice_words(t->V);
     for (size_t w = 0; w < W; ++w) {
-        const BandMeta& m = t->bands[w].meta;
-        for (int i = 0; i < t->bands[w].capacity; ++i) {
+        const BandMeta& m = hbs[w].meta;
+        for (int i = 0; i < hbs[w].capacity; ++i) {
             const Slot& sl = slots_host[m.slot_off + i];
             if (sl.key < 0) continue;
             const int32_t* span = words.data() + w * V + sl.start;
@@ -600,174 +664,183 @@ lsh_status build_on_host(lsh_tables* t, hipStream_t st, SplitMix64& rng) {
             cuts_host[m.slot_off + i] = make_uint4(c[0], c[1], c[2], sl.len);
         }
     }
-    HIP_TRY(hipMalloc((void**)&t->cuts_dev, cuts_host.size() * sizeof(uint4)));
+    const lsh_status rc = place_slots(t, slots_host.size());
+    if (rc != LSH_OK) return rc;
     HIP_TRY(hipMemcpyAsync(t->cuts_dev, cuts_host.data(), cuts_host.size() * sizeof(uint4),
                            hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMalloc((void**)&t->slots_dev, slots_host.size() * sizeof(Slot)));
-    HIP_TRY(hipMalloc((void**)&t->bands_dev, W * sizeof(BandMeta)));
     HIP_TRY(hipMemcpyAsync(t->words_dev, words.data(), V * W * sizeof(int32_t), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(t->slots_dev, slots_host.data(), slots_host.size() * sizeof(Slot),
                            hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(t->bands_dev, metas.data(), W * sizeof(BandMeta), hipMemcpyHostToDevice, st));
     HIP_TRY(hipStreamSynchronize(st));
-
+    t->bands.assign(hbs.begin(), hbs.end());   // (their Band parts)
     return LSH_OK;
 }
 
 struct DevBuf {  // temporary device memory of the build, released on every exit path
     void* p = nullptr;
     ~DevBuf() { (void)hipFree(p); }
-    template <typename T> T* as() const { return (T*)p; }
     hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1); }
 };
 
-inline int bits_for(uint64_t max_value) {  // bits needed to write max_value (at least 1)
-    int b = 1;
-    while (b < 64 && (max_value >> b)) ++b;
-    return b;
+template <typename ET>
+hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, int d, const int32_t* perms, int P, int K,
+                            int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride) {
+    const hipError_t e = allow_whole_lds<k_row_codes<ET>>();
+    if (e != hipSuccess) return e;
+    const int lg = row_codes_lg_rows(n, d, sizeof(ET), P);
+    hipLaunchKernelGGL(k_row_codes<ET>, dim3((unsigned)((n + (1 << lg) - 1) >> lg)), dim3(kRowCodeThreads),
+                       row_codes_lds(1 << lg, d, sizeof(ET), P), st, X, ld, n, d, perms, P, K, W, bits, lg, out,
+                       row_stride, band_stride);
+    return hipGetLastError();
 }
 
-// Device path of the table build (build_tables.h).  LSH_ERR_BUILD_FAILED = some band could not
-// be inserted after all attempts (or the problem is too large for the 32-bit item counts of the
-// sort): the caller falls back to the host path.
-lsh_status build_on_device(lsh_tables* t, hipStream_t st, SplitMix64& rng) {
-    const int64_t V = t->V, W = t->W, N = V * W;
-    if (N >= (int64_t)INT32_MAX) return LSH_ERR_BUILD_FAILED;
-    const SortKeyLayout lay{bits_for((uint64_t)V - 1), std::max(1, t->u * t->bits)};
-    const int key_bits = lay.id_bits + lay.code_bits + bits_for((uint64_t)W - 1);
-    const dim3 blk(256), grdN((unsigned)((N + 255) / 256));
+// The table build (build_tables.h).  The bucket and cuckoo tables are made on the device; `on_host`, a band
+// that keeps failing its insertion or a table beyond 32-bit slot numbers takes the host path instead.
+lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uint64_t seed, bool on_host) {
+    const int64_t V = t->V, W = t->W;
+    const size_t n_perms = (size_t)t->P * t->K, n_tickets = (size_t)kTicketSlots * kTicketBlock;
+    const int code_bits = t->u * t->bits;
+    const int passes = (code_bits + kRadixBits - 1) / kRadixBits, pass_bits = (code_bits + passes - 1) / passes;
+    const int digits = 1 << pass_bits, chunk = radix_chunk(V, (int)W), chunks = (int)((V + chunk - 1) / chunk);
+    // a band has at most key_pitch keys; a table has a power of two of at least three slots per key (load
+    // <= 1/3: two-choice cuckoo insertion then succeeds at the first attempt almost always)
+    const uint32_t key_pitch = (uint32_t)std::min<int64_t>(V, (int64_t)1 << code_bits);
+    auto lg_for = [](uint32_t keys) { int lg = 1; while ((1ull << lg) < 3ull * keys) ++lg; return lg; };
+    int lg = lg_for(key_pitch);
+    // tables for the most keys there can be, so that nothing has to be known before they are placed --
+    // unless that took a gigabyte: then the keys are counted first
+    constexpr uint64_t kPlaceBlind = (1ull << 30) / (sizeof(Slot) + sizeof(uint4) + sizeof(uint64_t));
+    const bool blind = ((uint64_t)W << lg) <= kPlaceBlind;
 
-    DevBuf keys_a, keys_b, head, key_index, tmp;
-    HIP_TRY(keys_a.alloc(N * sizeof(uint64_t)));
-    HIP_TRY(keys_b.alloc(N * sizeof(uint64_t)));
-    HIP_TRY(head.alloc(N * sizeof(uint32_t)));
-    HIP_TRY(key_index.alloc(N * sizeof(uint32_t)));
-    hipLaunchKernelGGL(k_make_sort_keys, grdN, blk, 0, st, (const int32_t*)t->codes_dev, V, (int)W, lay,
-                       keys_a.as<uint64_t>());
-    size_t sort_bytes = 0, scan_bytes = 0;
-    HIP_TRY(hipcub::DeviceRadixSort::SortKeys(nullptr, sort_bytes, keys_a.as<uint64_t>(),
-                                              keys_b.as<uint64_t>(), (int)N, 0, key_bits, st));
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(nullptr, scan_bytes, head.as<uint32_t>(),
-                                             key_index.as<uint32_t>(), (int)N, st));
-    HIP_TRY(tmp.alloc(std::max(sort_bytes, scan_bytes)));
-    HIP_TRY(hipcub::DeviceRadixSort::SortKeys(tmp.p, sort_bytes, keys_a.as<uint64_t>(),
-                                              keys_b.as<uint64_t>(), (int)N, 0, key_bits, st));
-    // 16 bytes of slack: k_hit_rows reads ids with 16-byte loads that may straddle the end
-    HIP_TRY(hipMalloc((void**)&t->words_dev, N * sizeof(int32_t) + 16));
-    hipLaunchKernelGGL(k_split_sorted, grdN, blk, 0, st, (const uint64_t*)keys_b.p, V, (int)W, lay,
-                       t->words_dev, head.as<uint32_t>());
-    HIP_TRY(hipcub::DeviceScan::ExclusiveSum(tmp.p, scan_bytes, head.as<uint32_t>(),
-                                             key_index.as<uint32_t>(), (int)N, st));
-    // keys per band: the scan value at each band's first position, and the total
-    std::vector<uint32_t> first_key(W + 1);
-    uint32_t last_index = 0, last_head = 0;
-    HIP_TRY(hipMemcpy2DAsync(first_key.data(), sizeof(uint32_t), key_index.p, (size_t)V * sizeof(uint32_t),
-                             sizeof(uint32_t), (size_t)W, hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(&last_index, key_index.as<uint32_t>() + (N - 1), sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(&last_head, head.as<uint32_t>() + (N - 1), sizeof(uint32_t),
-                           hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    const uint32_t n_keys = last_index + last_head;
-    first_key[W] = n_keys;
-
-    DevBuf key_code, key_start, key_band, key_len;
-    HIP_TRY(key_code.alloc(n_keys * sizeof(int32_t)));
-    HIP_TRY(key_start.alloc(n_keys * sizeof(uint32_t)));
-    HIP_TRY(key_band.alloc(n_keys * sizeof(int32_t)));
-    HIP_TRY(key_len.alloc(n_keys * sizeof(uint32_t)));
-    hipLaunchKernelGGL(k_emit_keys, grdN, blk, 0, st, (const uint64_t*)keys_b.p, (const uint32_t*)head.p,
-                       (const uint32_t*)key_index.p, V, (int)W, lay, key_code.as<int32_t>(),
-                       key_start.as<uint32_t>(), key_band.as<int32_t>());
-    const dim3 grdK((n_keys + 255) / 256);
-    hipLaunchKernelGGL(k_key_lengths, grdK, blk, 0, st, (const uint32_t*)key_start.p,
-                       (const int32_t*)key_band.p, n_keys, (uint32_t)V, key_len.as<uint32_t>());
-    DevBuf key_cut;
-    HIP_TRY(key_cut.alloc(n_keys * sizeof(uint4)));
-    hipLaunchKernelGGL(k_slice_cuts, grdK, blk, 0, st, (const int32_t*)t->words_dev,
-                       (const uint32_t*)key_start.p, (const uint32_t*)key_len.p, (const int32_t*)key_band.p,
-                       n_keys, (uint32_t)V, hit_slice_words(t->V), key_cut.as<uint4>());
-
-    // table geometry: a power of two of at least three slots per key and band (load <= 1/3:
-    // two-choice cuckoo insertion then succeeds at the first attempt almost always)
-    t->bands.assign(W, HostBand{});
-    std::vector<BandMeta> metas(W);
-    std::vector<uint32_t> caps(W), flags(W, 0u);
-    uint64_t n_slots = 0;
-    int max_lg = 1;
-    for (int64_t w = 0; w < W; ++w) {
-        const uint32_t nk = first_key[w + 1] - first_key[w];
-        int lg = 1;
-        while ((uint64_t)(1u << lg) < 3ull * nk) ++lg;
-        max_lg = std::max(max_lg, lg);
-        caps[w] = 1u << lg;
-        metas[w] = BandMeta{};
-        metas[w].slot_off = (uint32_t)n_slots;
-        metas[w].shift = 32u - (uint32_t)lg;
-        n_slots += caps[w];
+    struct Status { uint32_t *bad, *failed[2], *n_keys; } stat{};
+    uint32_t *status_dev = nullptr, *counts = nullptr, *starts = nullptr, *key_start = nullptr;
+    uint64_t* table = nullptr;
+    int32_t *key_code = nullptr, *code_buf[2] = {}, *id_buf[2] = {};
+    const size_t status_words = kBuildBeginBlocks + 3 * (size_t)W;
+    for (int pass = 0; pass < 2; ++pass) {
+        Carver c{(char*)t->arena};
+        t->perms_dev = c.take<int32_t>(n_perms);
+        t->tickets_dev = c.take<unsigned int>(n_tickets);
+        t->bands_dev = c.take<BandMeta>(W);
+        status_dev = c.take<uint32_t>(status_words);
+        t->codes_dev = c.take<int32_t>((size_t)V * W);
+        // 16 bytes of slack: k_hit_rows reads ids with 16-byte loads that may straddle the end
+        t->words_dev = c.take<int32_t>((size_t)V * W + 4);
+        if (blind) {
+            t->slots_dev = c.take<Slot>((size_t)W << lg);
+            t->cuts_dev = c.take<uint4>((size_t)W << lg);
+        }
+        // (what only the build needs)
+        if (blind) table = c.take<uint64_t>((size_t)W << lg);
+        counts = c.take<uint32_t>((size_t)W * chunks * (digits / 2));
+        starts = c.take<uint32_t>((size_t)W * digits);
+        key_code = c.take<int32_t>((size_t)W * key_pitch);
+        key_start = c.take<uint32_t>((size_t)W * key_pitch);
+        for (int b = 0; passes > 1 && b < 2; ++b) {
+            code_buf[b] = c.take<int32_t>((size_t)V * W);
+            id_buf[b] = c.take<int32_t>((size_t)V * W);
+        }
+        if (!pass) HIP_TRY(alloc_arena(t->device, c.bytes, &t->arena, &t->arena_bytes));
     }
-    if (n_slots >= (1ull << 32)) return LSH_ERR_BUILD_FAILED;
-    auto draw = [&](BandMeta& m) {
-        m.a0 = (uint32_t)rng.next() | 1u; m.b0 = (uint32_t)rng.next();
-        m.a1 = (uint32_t)rng.next() | 1u; m.b1 = (uint32_t)rng.next();
+    stat.bad = status_dev;
+    stat.n_keys = stat.bad + kBuildBeginBlocks;
+    stat.failed[0] = stat.n_keys + W;
+    stat.failed[1] = stat.failed[0] + W;
+    DevBuf late_table;
+
+    const dim3 begin_grid(kBuildBeginBlocks, (unsigned)W + 1), b256(256);
+    auto begin = [&](int attempt, const uint32_t* redo, bool with_tables) {
+        hipLaunchKernelGGL(k_build_begin, begin_grid, b256, 0, st, table, t->bands_dev, (int)W,
+                           with_tables ? 1u << lg : 0u, lg, seed, attempt, redo, stat.failed[attempt & 1],
+                           attempt || (with_tables && !blind) ? nullptr : perms_in, (int)n_perms, t->d, t->perms_dev, stat.bad,
+                           t->tickets_dev, (int)n_tickets);
     };
-    for (auto& m : metas) draw(m);
+    begin(0, nullptr, blind);
+    HIP_TRY(t->dtype == LSH_F32
+        ? launch_row_codes<float>(st, (const float*)t->E, t->ld, V, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V)
+        : launch_row_codes<uint16_t>(st, (const uint16_t*)t->E, t->ld, V, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V));
 
-    DevBuf table, caps_dev, redo_dev, failed_dev;
-    HIP_TRY(table.alloc(n_slots * sizeof(uint64_t)));
-    HIP_TRY(caps_dev.alloc(W * sizeof(uint32_t)));
-    HIP_TRY(redo_dev.alloc(W * sizeof(uint32_t)));
-    HIP_TRY(failed_dev.alloc(W * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc((void**)&t->bands_dev, W * sizeof(BandMeta)));
-    HIP_TRY(hipMalloc((void**)&t->slots_dev, n_slots * sizeof(Slot)));
-    HIP_TRY(hipMalloc((void**)&t->cuts_dev, n_slots * sizeof(uint4)));
-    HIP_TRY(hipMemcpyAsync(caps_dev.p, caps.data(), W * sizeof(uint32_t), hipMemcpyHostToDevice, st));
-    const dim3 grdClear((unsigned)std::min<uint64_t>(64, ((1ull << max_lg) + 255) / 256), (unsigned)W);
-    // LSHBEAM_CUCKOO_CHAIN shortens the eviction chains (tests of the retry and fallback paths)
-    const int max_chain = env_int("LSHBEAM_CUCKOO_CHAIN", 16 * (max_lg + 1));
-    bool done = false;
-    for (int attempt = 0; attempt < 24 && !done; ++attempt) {
-        t->build_attempts = attempt + 1;
-        const uint32_t* redo = attempt ? redo_dev.as<uint32_t>() : nullptr;
-        HIP_TRY(hipMemcpyAsync(t->bands_dev, metas.data(), W * sizeof(BandMeta), hipMemcpyHostToDevice, st));
-        HIP_TRY(hipMemsetAsync(failed_dev.p, 0, W * sizeof(uint32_t), st));
-        hipLaunchKernelGGL(k_cuckoo_clear, grdClear, blk, 0, st, table.as<uint64_t>(),
-                           (const BandMeta*)t->bands_dev, (const uint32_t*)caps_dev.p, (int)W, redo);
-        if (n_keys)
-            hipLaunchKernelGGL(k_cuckoo_insert, grdK, blk, 0, st, table.as<uint64_t>(),
-                               (const BandMeta*)t->bands_dev, (const int32_t*)key_code.p,
-                               (const int32_t*)key_band.p, n_keys, max_chain, redo,
-                               failed_dev.as<uint32_t>());
-        HIP_TRY(hipMemcpyAsync(flags.data(), failed_dev.p, W * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    std::vector<uint32_t> status(status_words);
+    auto read_status = [&]() -> lsh_status {
+        HIP_TRY(hipMemcpyAsync(status.data(), status_dev, status_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
-        done = true;
-        for (int64_t w = 0; w < W; ++w)
-            if (flags[w]) { done = false; draw(metas[w]); }
-        if (!done)
-            HIP_TRY(hipMemcpyAsync(redo_dev.p, flags.data(), W * sizeof(uint32_t), hipMemcpyHostToDevice, st));
+        for (int i = 0; i < kBuildBeginBlocks; ++i)
+            if (status[i]) return LSH_ERR_INVALID_ARG;
+        return LSH_OK;
+    };
+    const uint32_t* keys_h = status.data() + kBuildBeginBlocks;
+    SplitMix64 host_rng{seed};
+    if (on_host) {
+        const lsh_status rc = read_status();
+        return rc != LSH_OK ? rc : build_on_host(t, st, host_rng);
     }
-    if (!done) return LSH_ERR_BUILD_FAILED;
-    hipLaunchKernelGGL(k_cuckoo_finalize, dim3((unsigned)((n_slots + 255) / 256)), blk, 0, st,
-                       (const uint64_t*)table.p, n_slots, (const uint32_t*)key_start.p,
-                       (const uint32_t*)key_len.p, (const uint4*)key_cut.p, t->slots_dev, t->cuts_dev);
-    HIP_TRY(hipGetLastError());
 
-    // host mirrors for the inspection calls: distinct codes and span boundaries of every band
-    std::vector<int32_t> codes_h(n_keys);
-    std::vector<uint32_t> starts_h(n_keys);
-    HIP_TRY(hipMemcpyAsync(codes_h.data(), key_code.p, n_keys * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipMemcpyAsync(starts_h.data(), key_start.p, n_keys * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    for (int64_t w = 0; w < W; ++w) {
-        HostBand& hb = t->bands[w];
-        hb.keys.assign(codes_h.begin() + first_key[w], codes_h.begin() + first_key[w + 1]);
-        hb.offsets.assign(starts_h.begin() + first_key[w], starts_h.begin() + first_key[w + 1]);
-        hb.offsets.push_back((int32_t)V);
-        hb.capacity = (int)caps[w];
-        hb.meta = metas[w];
+    const dim3 sort_grid((unsigned)chunks, (unsigned)W), sort_block(kRadixThreads), scan_block(kScanThreads);
+    HIP_TRY(allow_whole_lds<k_radix_scatter>());
+    const int32_t *codes_in = t->codes_dev, *ids_in = nullptr;
+    for (int p = 0; p < passes; ++p) {
+        const int shift = p * pass_bits;
+        hipLaunchKernelGGL(k_radix_count, sort_grid, sort_block, (size_t)digits * 2, st, codes_in, V, chunk, shift, digits, counts);
+        if (passes == 1)
+            hipLaunchKernelGGL(k_radix_scan<true>, dim3((unsigned)W), scan_block, 0, st, counts, chunks, digits, starts, key_code,
+                               key_start, key_pitch, stat.n_keys);
+        else
+            hipLaunchKernelGGL(k_radix_scan<false>, dim3((unsigned)W), scan_block, 0, st, counts, chunks, digits, starts, nullptr,
+                               nullptr, 0u, nullptr);
+        int32_t* ids_out = p == passes - 1 ? t->words_dev : id_buf[p & 1];
+        hipLaunchKernelGGL(k_radix_scatter, sort_grid, sort_block, radix_scatter_lds(digits), st, codes_in, ids_in, V, chunk,
+                           shift, pass_bits, counts, starts, code_buf[p & 1], ids_out);
+        codes_in = code_buf[p & 1];
+        ids_in = ids_out;
     }
-    t->built_on_device = 1;
-    return LSH_OK;
+    if (passes > 1) {   // (the counters are free again: at least one per chunk and band)
+        hipLaunchKernelGGL(k_key_count, sort_grid, sort_block, 0, st, codes_in, V, chunk, counts);
+        hipLaunchKernelGGL(k_key_emit, sort_grid, sort_block, 0, st, codes_in, V, chunk, (const uint32_t*)counts, key_code,
+                           key_start, key_pitch, stat.n_keys);
+    }
+    if (!blind) {
+        lsh_status rc = read_status();
+        if (rc != LSH_OK) return rc;
+        lg = lg_for(*std::max_element(keys_h, keys_h + W));
+        if (((uint64_t)W << lg) >= (1ull << 32)) return build_on_host(t, st, host_rng);
+        rc = place_slots(t, (uint64_t)W << lg);
+        if (rc != LSH_OK) return rc;
+        HIP_TRY(late_table.alloc(((size_t)W << lg) * sizeof(uint64_t)));
+        table = (uint64_t*)late_table.p;
+        begin(0, nullptr, true);
+    }
+    // LSHBEAM_CUCKOO_CHAIN shortens the eviction chains (tests of the retry and fallback paths)
+    const int max_chain = env_int("LSHBEAM_CUCKOO_CHAIN", 16 * (lg + 1));
+    const dim3 insert_grid((key_pitch + 255) / 256, (unsigned)W), slot_grid(((1u << lg) + 255) / 256, (unsigned)W);
+    std::vector<int> drawn(W, 0);   // the attempt whose parameters each band has
+    for (int attempt = 0; attempt < 24; ++attempt) {
+        t->build_attempts = attempt + 1;
+        const uint32_t* redo = attempt ? stat.failed[(attempt - 1) & 1] : nullptr;
+        if (attempt) begin(attempt, redo, true);
+        hipLaunchKernelGGL(k_cuckoo_insert, insert_grid, b256, 0, st, table, (const BandMeta*)t->bands_dev,
+                           (const int32_t*)key_code, key_pitch, (const uint32_t*)stat.n_keys, max_chain, redo,
+                           stat.failed[attempt & 1]);
+        hipLaunchKernelGGL(k_cuckoo_finalize, slot_grid, b256, 0, st, (const uint64_t*)table, 1u << lg,
+                           (const uint32_t*)key_start, key_pitch, (const uint32_t*)stat.n_keys,
+                           (const int32_t*)t->words_dev, (uint32_t)V, hit_slice_words(t->V), t->slots_dev, t->cuts_dev);
+        HIP_TRY(hipGetLastError());
+        const lsh_status rc = read_status();
+        if (rc != LSH_OK) return rc;
+        if (attempt) for (int64_t w = 0; w < W; ++w)
+            if (status[(stat.failed[(attempt - 1) & 1] - status_dev) + w]) drawn[w] = attempt;
+        const uint32_t* failed_h = status.data() + (stat.failed[attempt & 1] - status_dev);
+        if (std::any_of(failed_h, failed_h + W, [](uint32_t f) { return f != 0; })) continue;
+        t->bands.resize(W);
+        for (int64_t w = 0; w < W; ++w) {
+            t->bands[w].n_keys = (int)keys_h[w];
+            t->bands[w].capacity = 1 << lg;
+            t->bands[w].meta = draw_band_meta(seed, (int)w, (int)W, drawn[w], 1u << lg, lg);
+        }
+        t->built_on_device = 1;
+        return LSH_OK;
+    }
+    return build_on_host(t, st, host_rng);
 }
 
 // The decode step behind every public variant of it: validation, launch plan, launches.
@@ -933,14 +1006,9 @@ const char* lsh_kernel_name(int32_t which) {
 }
 
 void lsh_free_tables(lsh_tables* t) {
-    if (!t) return;
-    (void)hipFree(t->perms_dev);
-    (void)hipFree(t->codes_dev);
-    (void)hipFree(t->words_dev);
-    (void)hipFree(t->slots_dev);
-    (void)hipFree(t->cuts_dev);
-    (void)hipFree(t->bands_dev);
-    (void)hipFree(t->tickets_dev);
+    if (!t) { give_back_kept(); return; }
+    release_arena(t->device, t->arena, t->arena_bytes);
+    (void)hipFree(t->slot_arena);
     delete t;
 }
 
@@ -964,9 +1032,6 @@ lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const l
     struct Guard { lsh_tables* t; ~Guard() { if (t) lsh_free_tables(t); } } guard{t};
     HIP_TRY(hipGetDevice(&t->device));
     HIP_TRY(scratch_of_device(t->device, &t->scratch_dev));
-    HIP_TRY(hipMalloc((void**)&t->tickets_dev, (size_t)kTicketSlots * kTicketBlock * sizeof(unsigned int)));
-    HIP_TRY(hipMemsetAsync(t->tickets_dev, 0, (size_t)kTicketSlots * kTicketBlock * sizeof(unsigned int),
-                           (hipStream_t)hip_stream));
     // launch-plan options: the library's own rules unless LSHBEAM_<NAME> is set in the environment
     // at this point (read once, here) or lsh_set_option changes them later
     for (int i = 0; i < kNumOpts; ++i) {
@@ -976,35 +1041,7 @@ lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const l
     }
     t->E = E_dev; t->V = p->V; t->d = p->d; t->ld = p->ld_e; t->dtype = p->e_dtype;
     t->K = p->K; t->P = p->P; t->W = p->bands; t->u = u; t->bits = bits;
-    const size_t V = t->V, W = t->W, PK = (size_t)t->P * t->K;
-
-    // permutations: copy, validate on the host
-    std::vector<int32_t> perms(PK);
-    HIP_TRY(hipMemcpyAsync(perms.data(), perms_dev, PK * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-    HIP_TRY(hipStreamSynchronize(st));
-    for (int32_t x : perms)
-        if (x < 0 || x >= t->d) return LSH_ERR_INVALID_ARG;
-    HIP_TRY(hipMalloc((void**)&t->perms_dev, PK * sizeof(int32_t)));
-    HIP_TRY(hipMemcpyAsync(t->perms_dev, perms.data(), PK * sizeof(int32_t), hipMemcpyHostToDevice, st));
-
-    // band codes of every embedding row, on the device
-    HIP_TRY(hipMalloc((void**)&t->codes_dev, V * W * sizeof(int32_t)));
-    {
-        const int64_t n = (int64_t)V * W;
-        const dim3 grid((unsigned)((n + 255) / 256)), block(256);
-        if (t->dtype == LSH_F32)
-            hipLaunchKernelGGL(k_band_codes<float>, grid, block, 0, st, (const float*)E_dev, t->ld,
-                               (int64_t)V, t->perms_dev, t->P, t->K, t->W, bits, t->codes_dev);
-        else
-            hipLaunchKernelGGL(k_band_codes<uint16_t>, grid, block, 0, st, (const uint16_t*)E_dev,
-                               t->ld, (int64_t)V, t->perms_dev, t->P, t->K, t->W, bits, t->codes_dev);
-        HIP_TRY(hipGetLastError());
-    }
-    // bucket tables + cuckoo tables: on the device; LSHBEAM_HOST_BUILD=1 (tests) or a band that
-    // keeps failing its insertion takes the host path instead
-    SplitMix64 rng{p->seed ^ 0xC0FFEE1234ABCDEFull};
-    lsh_status brc = env_int("LSHBEAM_HOST_BUILD", 0) ? LSH_ERR_BUILD_FAILED : build_on_device(t, st, rng);
-    if (brc == LSH_ERR_BUILD_FAILED) brc = build_on_host(t, st, rng);
+    const lsh_status brc = build_all(t, st, perms_dev, p->seed ^ 0xC0FFEE1234ABCDEFull, env_int("LSHBEAM_HOST_BUILD", 0) != 0);
     if (brc != LSH_OK) return brc;
 
     // (with the minimum stage; a step may ask for more)
@@ -1103,10 +1140,8 @@ lsh_status lsh_debug_codes(const lsh_tables* t, const float* H_dev, int32_t R, i
     int32_t* tmp = nullptr;
     const int64_t n = (int64_t)R * t->W;
     HIP_TRY(hipMalloc((void**)&tmp, n * sizeof(int32_t)));
-    hipLaunchKernelGGL(k_band_codes<float>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, H_dev,
-                       (int64_t)t->d, (int64_t)R, (const int32_t*)t->perms_dev, t->P, t->K, t->W,
-                       t->bits, tmp);
-    hipError_t e = hipMemcpy(codes_host, tmp, n * sizeof(int32_t), hipMemcpyDeviceToHost);
+    hipError_t e = launch_row_codes<float>(nullptr, H_dev, t->d, R, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, tmp, t->W, 1);
+    if (e == hipSuccess) e = hipMemcpy(codes_host, tmp, n * sizeof(int32_t), hipMemcpyDeviceToHost);
     (void)hipFree(tmp);
     HIP_TRY(e);
     return LSH_OK;
@@ -1114,8 +1149,12 @@ lsh_status lsh_debug_codes(const lsh_tables* t, const float* H_dev, int32_t R, i
 
 lsh_status lsh_debug_embedding_codes(const lsh_tables* t, int32_t row0, int32_t n, int32_t* codes_host) {
     if (!t || !codes_host || row0 < 0 || n < 0 || (int64_t)row0 + n > t->V) return LSH_ERR_INVALID_ARG;
-    HIP_TRY(hipMemcpy(codes_host, t->codes_dev + (size_t)row0 * t->W, (size_t)n * t->W * sizeof(int32_t),
-                      hipMemcpyDeviceToHost));
+    // (band by band, turned into rows on the host)
+    std::vector<int32_t> band(n);
+    for (int w = 0; w < t->W && n > 0; ++w) {
+        HIP_TRY(hipMemcpy(band.data(), t->codes_dev + (size_t)w * t->V + row0, (size_t)n * sizeof(int32_t), hipMemcpyDeviceToHost));
+        for (int i = 0; i < n; ++i) codes_host[(size_t)i * t->W + w] = band[i];
+    }
     return LSH_OK;
 }
 
@@ -1147,11 +1186,17 @@ lsh_status lsh_debug_bucket(const lsh_tables* t, int32_t band, int32_t code, int
 lsh_status lsh_debug_csr(const lsh_tables* t, int32_t band, int32_t* n_keys_out, int32_t* keys_host,
                          int32_t* offsets_host, int32_t cap_keys, int32_t* words_host) {
     if (!t || band < 0 || band >= t->W || !n_keys_out) return LSH_ERR_INVALID_ARG;
-    const HostBand& hb = t->bands[band];
-    *n_keys_out = (int32_t)hb.keys.size();
-    if (keys_host && offsets_host && cap_keys >= (int32_t)hb.keys.size()) {
-        std::memcpy(keys_host, hb.keys.data(), hb.keys.size() * sizeof(int32_t));
-        std::memcpy(offsets_host, hb.offsets.data(), hb.offsets.size() * sizeof(int32_t));
+    const Band& b = t->bands[band];
+    *n_keys_out = b.n_keys;
+    if (keys_host && offsets_host && cap_keys >= b.n_keys) {
+        // the used slots of the band's cuckoo table, in key order
+        std::vector<Slot> slots(b.capacity);
+        HIP_TRY(hipMemcpy(slots.data(), t->slots_dev + b.meta.slot_off, slots.size() * sizeof(Slot), hipMemcpyDeviceToHost));
+        slots.erase(std::remove_if(slots.begin(), slots.end(), [](const Slot& x) { return x.key < 0; }), slots.end());
+        std::sort(slots.begin(), slots.end(), [](const Slot& x, const Slot& y) { return x.key < y.key; });
+        if ((int)slots.size() != b.n_keys) return LSH_ERR_BUILD_FAILED;
+        for (int i = 0; i < b.n_keys; ++i) { keys_host[i] = slots[i].key; offsets_host[i] = (int32_t)slots[i].start; }
+        offsets_host[b.n_keys] = b.n_keys ? (int32_t)(slots[b.n_keys - 1].start + slots[b.n_keys - 1].len) : 0;
     }
     if (words_host)
         HIP_TRY(hipMemcpy(words_host, t->words_dev + (size_t)band * t->V, (size_t)t->V * sizeof(int32_t),
@@ -1170,7 +1215,7 @@ lsh_status lsh_debug_cuckoo_shape(const lsh_tables* t, int32_t band, int32_t* ca
                                   int32_t* n_keys_out) {
     if (!t || band < 0 || band >= t->W || !capacity_out || !n_keys_out) return LSH_ERR_INVALID_ARG;
     *capacity_out = t->bands[band].capacity;
-    *n_keys_out = (int32_t)t->bands[band].keys.size();
+    *n_keys_out = t->bands[band].n_keys;
     return LSH_OK;
 }
 

@@ -1,0 +1,59 @@
+"""The table build at the edges of its kernels: vocabularies around one and several chunks of the sort,
+codes of one, two and three passes, bands whose words share one code, rows of every alignment, windows
+longer than the registers hold, many permutations per row -- bucket for bucket against the oracle; and
+permutations out of range."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from gpu_harness import GpuCase, to_dev
+
+pytestmark = pytest.mark.gpu
+
+_SHAPES = [
+    # V, d, K, u, W, bf16, equal rows
+    (1, 2, 2, 1, 1, False, False),
+    (63, 9, 3, 2, 3, True, False),
+    (4096, 33, 8, 4, 2, False, False),
+    (4097, 16, 2, 12, 2, True, False),
+    (5000, 77, 16, 4, 5, True, False),
+    (9001, 40, 8, 8, 2, False, False),
+    (3000, 64, 4, 15, 3, False, False),
+    (20000, 130, 24, 4, 3, False, True),
+    (2500, 515, 8, 3, 100, True, False),
+]
+
+
+@pytest.mark.parametrize("shape", _SHAPES, ids=lambda s: "V%d-d%d-K%d-u%d-W%d" % s[:5])
+def test_build_matches_the_oracle(shape):
+    V, d, K, u, W, bf16, equal = shape
+    rng = np.random.default_rng(V + d)
+    E = rng.standard_normal((V, d)).astype(np.float32)
+    if equal:                                       # long spans: most words are one of two vectors
+        E[: V - V // 8] = E[rng.integers(0, 2, V - V // 8)]
+    E = workloads.f32_to_bf16_bits(E) if bf16 else E
+    perms = np.stack([rng.permutation(d)[:K] for _ in range(u * W)]).astype(np.int32)
+    gc = GpuCase(E, perms, np.zeros(0, np.int32), W)
+    assert np.array_equal(gc.tables.debug_embedding_codes(), oracle.band_codes(oracle.wta_codes(E, perms), W, K))
+    assert gc.tables.debug_build_info()[0]
+    for w in range(W) if W < 10 else (0, 1, W - 1):
+        keys, offs, words = gc.tables.debug_csr(w)
+        okeys = np.sort(gc.index.bucket_keys(w))
+        buckets = [gc.index.bucket(w, int(k)) for k in okeys]
+        assert np.array_equal(keys, okeys) and np.array_equal(words, np.concatenate(buckets))
+        assert np.array_equal(np.diff(offs), [len(b) for b in buckets])
+        for k in okeys[:: max(1, len(okeys) // 50)]:
+            assert np.array_equal(gc.tables.debug_bucket(w, int(k)), gc.index.bucket(w, int(k)))
+
+
+def test_permutations_out_of_range_are_refused():
+    import paper_1806_00588_amd as lsh
+    E = to_dev(np.random.default_rng(0).standard_normal((500, 12)).astype(np.float32))
+    perms = np.tile(np.arange(4, dtype=np.int32), (300, 1))
+    for bad in (-1, 12, 1 << 30):
+        p = perms.copy()
+        p[299, 3] = bad
+        with pytest.raises(lsh.binding.LshBeamError):
+            lsh.build_tables(E, to_dev(p), 4, 100)
+    lsh.build_tables(E, to_dev(perms), 4, 100).close()
