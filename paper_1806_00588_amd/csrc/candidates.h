@@ -330,12 +330,11 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
     const int32_t tf_first = (tid < T) ? topfreq[tid] : -1;
     const int32_t tf_second = DEEP ? id_list_second(topfreq, T) : -1;
     const float* H0 = H + (size_t)s * B * d;
-    const bool vec_ok = (((uintptr_t)H0 | ((uintptr_t)d * 4)) & 15) == 0;
-    float4 r0 = {}, r1 = {}, r2 = {}, r3 = {};
+    Float4U r0 = {}, r1 = {}, r2 = {}, r3 = {};   // (rows start at any float)
     {
         const int n4 = (min(rows_per_chunk, row_end - row_begin) * d) >> 2;
-        if (vec_ok && n4 > 0) {
-            const float4* H4 = reinterpret_cast<const float4*>(H0 + (size_t)row_begin * d);
+        if (n4 > 0) {
+            const Float4U* H4 = reinterpret_cast<const Float4U*>(H0 + (size_t)row_begin * d);
             r0 = H4[min(tid, n4 - 1)];
             r1 = H4[min(tid + kCandThreads, n4 - 1)];
             r2 = H4[min(tid + 2 * kCandThreads, n4 - 1)];
@@ -359,9 +358,10 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
         // permuted gathers of Eq. 5 are LDS reads and no global load depends on another.
         const float* Hc = H0 + (size_t)row0 * d;
         const int nval = rows * d;
-        if (vec_ok) {
-            const float4* H4 = reinterpret_cast<const float4*>(Hc);
+        {
+            const Float4U* H4 = reinterpret_cast<const Float4U*>(Hc);
             float4* S4 = reinterpret_cast<float4*>(stage);
+            auto put = [&](int e, const Float4U& r) { S4[e] = make_float4(r.x, r.y, r.z, r.w); };
             const int n4 = nval >> 2;
             for (int e0 = tid; e0 < n4; e0 += 4 * kCandThreads) {  // 4 independent loads in flight
                 if (row0 != row_begin || e0 != tid) {  // the very first batch is already in registers
@@ -370,13 +370,12 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
                     r2 = H4[min(e0 + 2 * kCandThreads, n4 - 1)];
                     r3 = H4[min(e0 + 3 * kCandThreads, n4 - 1)];
                 }
-                S4[e0] = r0;
-                if (e0 + kCandThreads < n4) S4[e0 + kCandThreads] = r1;
-                if (e0 + 2 * kCandThreads < n4) S4[e0 + 2 * kCandThreads] = r2;
-                if (e0 + 3 * kCandThreads < n4) S4[e0 + 3 * kCandThreads] = r3;
+                put(e0, r0);
+                if (e0 + kCandThreads < n4) put(e0 + kCandThreads, r1);
+                if (e0 + 2 * kCandThreads < n4) put(e0 + 2 * kCandThreads, r2);
+                if (e0 + 3 * kCandThreads < n4) put(e0 + 3 * kCandThreads, r3);
             }
-        } else {
-            for (int e = tid; e < nval; e += kCandThreads) stage[e] = Hc[e];
+            if (tid < (nval & 3)) stage[(nval & ~3) + tid] = Hc[(nval & ~3) + tid];
         }
         LSH_TRACE(0, 12);
         if (tid == 0) wsum[kDirectFlag] = 0u;   // "a span of this chunk is too long for the direct walk"

@@ -69,7 +69,7 @@ struct TailArgs {
 // `tile_ids` has kFusedRound * 16 words, `wsum` >= 17, `red` is the cross-wave reduction buffer;
 // h_lds (or null) are the sentence's hidden rows staged in LDS as [B][d].
 constexpr int kCoopBits = 8;   // list positions of one tile in one thread from which its wave shares the work
-template <typename ET, bool ALIGNED, bool ONE_LAUNCH>
+template <typename ET, bool CHUNKS, bool ONE_LAUNCH>
 __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* wsum, uint32_t* tile_ids,
                                                   float (*red)[4][kWave], const float* h_lds,
                                                   const ET* __restrict__ E, int64_t ld, int d,
@@ -144,7 +144,7 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
             if (tid < kTileN && in_list)
                 store_shared_result<ONE_LAUNCH>(&cand[(size_t)s * V + nt * tn + col], id);
             LSH_TRACE(1, 2);
-            logits_tile_all_rows<ET, kFusedWaves, 64 / kFusedWaves, ALIGNED, 0, true, ONE_LAUNCH>(
+            logits_tile_all_rows<ET, kFusedWaves, 64 / kFusedWaves, CHUNKS, 0, true, ONE_LAUNCH>(
                 E, ld, d, H, B, s, nt, C, (int64_t)id, logits, cpitch, recs, red, h_lds, 0, 0, -1, tn);
         }
         // (a tile ends with a barrier: the table is free for the next round)
@@ -183,7 +183,7 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
 
 // grid = S * G workgroups: workgroup b works for sentence b % S and takes that sentence's tiles
 // (b / S), (b / S) + G, ...
-template <typename ET, bool ALIGNED, bool ONE_LAUNCH>
+template <typename ET, bool CHUNKS, bool ONE_LAUNCH>
 __global__ void __launch_bounds__(kCandThreads)
 k_cand_logits(CandArgs a, const ET* __restrict__ E, int64_t ld, int S, int32_t* __restrict__ cand,
               int32_t* __restrict__ count, float* __restrict__ logits, int64_t cpitch,
@@ -202,9 +202,9 @@ k_cand_logits(CandArgs a, const ET* __restrict__ E, int64_t ld, int S, int32_t* 
     // when the whole sentence was hashed in one chunk its hidden rows are still staged in LDS:
     // the contraction takes its A operands from there instead of reading H again
     const float* h_lds = nullptr;
-    if (a.rows_chunk >= B && (a.d & 3) == 0)
+    if (a.rows_chunk >= B)
         h_lds = reinterpret_cast<const float*>(smem + bitmap_words_padded(V));
-    tiles_from_bitmap<ET, ALIGNED, ONE_LAUNCH>(bm, wsum, tile_ids, red, h_lds, E, ld, a.d, a.H, B, V, s, g, G, cand,
+    tiles_from_bitmap<ET, CHUNKS, ONE_LAUNCH>(bm, wsum, tile_ids, red, h_lds, E, ld, a.d, a.H, B, V, s, g, G, cand,
                                    count, logits, cpitch, recs, tail, smem);
     LSH_TRACE_WG(6);
 }
@@ -219,7 +219,7 @@ __host__ __device__ inline size_t union_logits_lds_words(int V) {
     return need > kSelSharedWords ? need : kSelSharedWords;
 }
 
-template <typename ET, bool ALIGNED, bool ONE_LAUNCH>
+template <typename ET, bool CHUNKS, bool ONE_LAUNCH>
 __global__ void __launch_bounds__(kCandThreads)
 k_union_logits(const uint32_t* __restrict__ part_bitmaps, int nparts, const int32_t* __restrict__ topfreq,
                int T, const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S,
@@ -240,7 +240,7 @@ k_union_logits(const uint32_t* __restrict__ part_bitmaps, int nparts, const int3
     __syncthreads();
     mark_id_list(bm, V, topfreq, T, tf_first);
     __syncthreads();
-    tiles_from_bitmap<ET, ALIGNED, ONE_LAUNCH>(bm, wsum, tile_ids, red, nullptr, E, ld, d, H, B, V, s, g, G, cand,
+    tiles_from_bitmap<ET, CHUNKS, ONE_LAUNCH>(bm, wsum, tile_ids, red, nullptr, E, ld, d, H, B, V, s, g, G, cand,
                                    count, logits, cpitch, recs, tail, smem);
 }
 

@@ -42,20 +42,19 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 template <typename ET> struct ElemTraits;
 template <> struct ElemTraits<float> {
     static constexpr int VEC = 4;  // elements per 16-byte load
-    __device__ static __forceinline__ void load16(const float* p, float (&out)[4]) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
+    __device__ static __forceinline__ void load16(const float* p, float (&out)[4]) {   // (any alignment)
+        const Float4U v = *reinterpret_cast<const Float4U*>(p);
         out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
     }
 };
 template <> struct ElemTraits<uint16_t> {
     static constexpr int VEC = 8;
     __device__ static __forceinline__ void load16(const uint16_t* p, float (&out)[8]) {
-        const uint4 v = *reinterpret_cast<const uint4*>(p);
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+        const Chunk16U<uint16_t> v = *reinterpret_cast<const Chunk16U<uint16_t>*>(p);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            out[2 * i] = __uint_as_float(w[i] << 16);
-            out[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+            out[2 * i] = __uint_as_float(v.w[i] << 16);
+            out[2 * i + 1] = __uint_as_float(v.w[i] & 0xFFFF0000u);
         }
     }
 };
@@ -129,9 +128,11 @@ __device__ __forceinline__ void tile_record_store(const TileRecords& recs, size_
 // rows (16-byte aligned, pitch h_pitch floats; 0 = d).  [row_lo, row_hi) restricts the call to
 // a range of the sentence's rows (mt counts groups of 16 from row_lo; h_lds then holds that range).
 //
-// ALIGNED: E rows and H rows can be read with 16-byte vector loads (pointers 16-byte aligned,
-// d and the pitches multiples of the vector width).  Otherwise elements are read one by one.
-template <typename ET, int WAVES, int UNROLL, bool ALIGNED, int MTB = 1, bool RICH = false, bool SHARE = false>
+// CHUNKS: a row holds at least one 16-byte chunk of E.  Rows are then read with 16-byte loads from whatever
+// address they start at (d = 1001 fp32, rows 4 bytes off a multiple of 16: element by element was three times
+// slower); the chunk that would reach past the row's end is read from the row's last VEC elements instead, and
+// the hidden values of elements that were counted already are zero.  Otherwise elements are read one by one.
+template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int MTB = 1, bool RICH = false, bool SHARE = false>
 __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld, int d,
                                             const float* __restrict__ H, int B, int s, int mt,
                                             int nt, int C, int64_t j, float* __restrict__ logits,
@@ -167,10 +168,11 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
 #pragma unroll
         for (int uu = 0; uu < UNROLL; ++uu) {
             const int k = (ks0 + uu * WAVES) * KSTEP + kq * VEC;
-            if (ALIGNED) {
+            if (CHUNKS) {
                 if (k < d) {
+                    const int at = min(k, d - VEC), drop = k - at;   // (leading elements counted before)
                     if (col_used) {
-                        ElemTraits<ET>::load16(erow + k, ev[uu]);
+                        ElemTraits<ET>::load16(erow + at, ev[uu]);
                     } else {
 #pragma unroll
                         for (int q = 0; q < VEC; ++q) ev[uu][q] = 0.f;
@@ -179,9 +181,10 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
                     for (int m = 0; m < MTB; ++m)
 #pragma unroll
                         for (int q = 0; q < VEC; q += 4) {
-                            const float4 h4 = *reinterpret_cast<const float4*>(hrow[m] + k + q);
-                            hv[m][uu][q] = h4.x; hv[m][uu][q + 1] = h4.y;
-                            hv[m][uu][q + 2] = h4.z; hv[m][uu][q + 3] = h4.w;
+                            const Float4U h4 = *reinterpret_cast<const Float4U*>(hrow[m] + at + q);
+                            const float x[4] = {h4.x, h4.y, h4.z, h4.w};
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) hv[m][uu][q + i] = q + i >= drop ? x[i] : 0.f;
                         }
                 } else {
 #pragma unroll
@@ -239,7 +242,7 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
 
 // All row groups of one tile of candidates, the candidate rows being read once for up to four
 // groups (64 beams) at a time.
-template <typename ET, int WAVES, int UNROLL, bool ALIGNED, int FIXED_MT = 0, bool RICH = false, bool SHARE = false>
+template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int FIXED_MT = 0, bool RICH = false, bool SHARE = false>
 __device__ __forceinline__ void logits_tile_all_rows(const ET* __restrict__ E, int64_t ld, int d,
                                                      const float* __restrict__ H, int B, int s,
                                                      int nt, int C, int64_t j,
@@ -257,23 +260,23 @@ __device__ __forceinline__ void logits_tile_all_rows(const ET* __restrict__ E, i
     // instantiated, so its registers do not count against the others)
     const int MT = FIXED_MT ? FIXED_MT : ((row_hi < 0 ? B : row_hi - row_lo) + kTileM - 1) / kTileM;
     if (MT == 1) {
-        logits_tile<ET, WAVES, UNROLL, ALIGNED, 1, RICH, SHARE>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
+        logits_tile<ET, WAVES, UNROLL, CHUNKS, 1, RICH, SHARE>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     } else if (MT == 2) {
-        logits_tile<ET, WAVES, U2, ALIGNED, 2, RICH, SHARE>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
+        logits_tile<ET, WAVES, U2, CHUNKS, 2, RICH, SHARE>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     } else if (ElemTraits<ET>::VEC > 4) {  // bf16: twice the registers per load, two groups at most
         for (int mt = 0; mt < MT; mt += 2)
-            logits_tile<ET, WAVES, U2, ALIGNED, 2, RICH, SHARE>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
+            logits_tile<ET, WAVES, U2, CHUNKS, 2, RICH, SHARE>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     } else {
         for (int mt = 0; mt < MT; mt += 4)
-            logits_tile<ET, WAVES, U4, ALIGNED, 4, RICH, SHARE>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
+            logits_tile<ET, WAVES, U4, CHUNKS, 4, RICH, SHARE>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     }
 }
 
-template <typename ET, int WAVES, int UNROLL, bool ALIGNED>
+template <typename ET, int WAVES, int UNROLL, bool CHUNKS>
 __global__ void __launch_bounds__(WAVES * kWave)
 k_logits(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
          const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
@@ -345,7 +348,7 @@ k_logits(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ 
         else
             j = cand ? cand[(size_t)s * V + cidx] : cidx;
         LSH_TRACE(1, 2);
-        logits_tile<ET, WAVES, UNROLL, ALIGNED>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch, recs, red);
+        logits_tile<ET, WAVES, UNROLL, CHUNKS>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch, recs, red);
     }
 }
 
@@ -361,7 +364,7 @@ k_logits(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ 
 // wave's latency-bound rate, and that tail was a sixth of the kernel.  Such a remainder is
 // therefore dealt to whole workgroups, whose four waves split k and sum their partial tiles
 // through LDS in wave order (logits_tile): four times as many waves share the same bytes.
-template <typename ET, int MT, int UNROLL, bool ALIGNED>
+template <typename ET, int MT, int UNROLL, bool CHUNKS>
 __global__ void __launch_bounds__(256)
 k_logits_wave(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
               const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
@@ -428,16 +431,18 @@ k_logits_wave(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 #pragma unroll
             for (int uu = 0; uu < UNROLL; ++uu) {
                 const int k = (ks0 + uu) * KSTEP + kq * VEC;
-                if (ALIGNED) {
+                if (CHUNKS) {
                     if (k < d) {
-                        ElemTraits<ET>::load16(erow + k, ev[uu]);
+                        const int at = min(k, d - VEC), drop = k - at;
+                        ElemTraits<ET>::load16(erow + at, ev[uu]);
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                             for (int q = 0; q < VEC; q += 4) {
-                                const float4 h4 = *reinterpret_cast<const float4*>(hrow[mt] + k + q);
-                                hv[mt][uu][q] = h4.x; hv[mt][uu][q + 1] = h4.y;
-                                hv[mt][uu][q + 2] = h4.z; hv[mt][uu][q + 3] = h4.w;
+                                const Float4U h4 = *reinterpret_cast<const Float4U*>(hrow[mt] + at + q);
+                                const float x[4] = {h4.x, h4.y, h4.z, h4.w};
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) hv[mt][uu][q + i] = q + i >= drop ? x[i] : 0.f;
                             }
                     } else {
 #pragma unroll
@@ -487,7 +492,7 @@ k_logits_wave(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         const int C = count ? count[s] : V;
         const int cidx = min(nt * kTileN + col, C - 1);
         const int64_t j = cand ? cand[(size_t)s * V + cidx] : cidx;
-        logits_tile_all_rows<ET, 4, (UNROLL < 4 ? UNROLL : 4), ALIGNED, MT>(E, ld, d, H, B, s, nt, C, j,
+        logits_tile_all_rows<ET, 4, (UNROLL < 4 ? UNROLL : 4), CHUNKS, MT>(E, ld, d, H, B, s, nt, C, j,
                                                                         logits, cpitch, recs, red);
     }
 }
@@ -504,11 +509,15 @@ k_logits_wave(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 // pitch is the next value >= d that is 4 modulo 32: consecutive rows then start 4 banks apart
 // and eight lanes x 16 bytes (eight rows, same k) cover all 32 banks exactly once.
 __host__ __device__ inline int hlds_pitch(int d) {
-    int p = (d + 3) & ~3;
+    int p = (d + 7) & ~7;
     while (p % 32 != 4) p += 4;
     return p;
 }
-// bf16 candidate rows with 16-byte aligned operands: the hidden rows are staged as three bf16
+// The last chunk of a row whose length is no multiple of the chunk is read from the row's last VEC elements
+// (addresses of any alignment are fine for 16-byte loads); in LDS the hidden row continues with the matching
+// chunk -- its last VEC values, those counted already replaced by zero -- so the loop knows nothing of it.
+//
+// bf16 candidate rows: the hidden rows are staged as three bf16
 // planes hi + mid + lo = h exactly (8 + 8 + 8 significand bits: each plane is the remainder so
 // far truncated to bf16), and the contraction runs on v_mfma_f32_16x16x32_bf16 -- a lane's
 // 16-byte chunk of its candidate row IS that instruction's B operand (8 consecutive k), no
@@ -528,43 +537,107 @@ __host__ __device__ inline size_t hlds_lds_bytes(int S, int rows, int d, int wav
     return ((size_t)((S + 1 + 3) & ~3) + (size_t)waves * 4 * kWave) * 4 + hidden;
 }
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ uint4 load_chunk(const uint16_t* p) {   // 16 bytes, any alignment
+    const Chunk16U<uint16_t> c = *reinterpret_cast<const Chunk16U<uint16_t>*>(p);
+    return make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]);
+}
+// Four hidden values as the three bf16 planes of k_logits_hlds (exactly x = hi + mid + lo), to LDS.
+__device__ __forceinline__ void store_planes4(char* dst, size_t plane_bytes, const float (&x)[4]) {
+    uint32_t hi[4], mid[4], lo[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        hi[q] = __float_as_uint(x[q]) & 0xFFFF0000u;
+        const float r1 = x[q] - __uint_as_float(hi[q]);          // exact
+        mid[q] = __float_as_uint(r1) & 0xFFFF0000u;
+        lo[q] = __float_as_uint(r1 - __uint_as_float(mid[q]));   // exact, <= 8 bits
+    }
+    *reinterpret_cast<uint2*>(dst) = make_uint2((hi[0] >> 16) | (hi[1] & 0xFFFF0000u), (hi[2] >> 16) | (hi[3] & 0xFFFF0000u));
+    *reinterpret_cast<uint2*>(dst + plane_bytes) =
+        make_uint2((mid[0] >> 16) | (mid[1] & 0xFFFF0000u), (mid[2] >> 16) | (mid[3] & 0xFFFF0000u));
+    *reinterpret_cast<uint2*>(dst + 2 * plane_bytes) =
+        make_uint2((lo[0] >> 16) | (lo[1] & 0xFFFF0000u), (lo[2] >> 16) | (lo[3] & 0xFFFF0000u));
+}
 
-template <typename ET, int MT, int WAVES, int UNROLL, bool ALIGNED, bool PLANES = false>
+// Tiles are dealt to the XCDs by their number inside the sentence: tile t of every sentence below `shared`
+// (the tiles that surely lie among the top-frequent words all sentences have in common, where those are the
+// lowest ids) goes to XCD t mod 8, so that its 16 rows enter one L2 and serve the other sentences from there;
+// tiles beyond go to XCD (t + s) mod 8.  What bounds the kernel is the fabric behind the L2s (6.5 TB/s).
+struct XcdTiles {   // the tiles of one sentence that belong to XCD x
+    uint32_t n0;        // how many of them lie below `shared`
+    uint32_t first1;    // the first one beyond
+    uint32_t n;         // all
+};
+__host__ __device__ __forceinline__ uint32_t tiles_mod8(uint32_t begin, uint32_t end, uint32_t r) {   // t in [begin, end), t mod 8 == r
+    return end > begin ? ((end + 7u - r) >> 3) - ((begin + 7u - r) >> 3) : 0u;
+}
+__host__ __device__ __forceinline__ XcdTiles xcd_tiles(uint32_t ntiles, uint32_t shared, uint32_t s, uint32_t x) {
+    XcdTiles t;
+    const uint32_t cut = shared < ntiles ? shared : ntiles, r1 = (x - s) & 7u;
+    t.n0 = tiles_mod8(0u, cut, x);
+    t.first1 = ((cut + 7u - r1) >> 3) * 8u + r1;
+    t.n = t.n0 + tiles_mod8(cut, ntiles, r1);
+    return t;
+}
+__host__ __device__ __forceinline__ uint32_t xcd_tile(const XcdTiles& t, uint32_t x, uint32_t i) {   // its i-th
+    return i < t.n0 ? x + 8u * i : t.first1 + 8u * (i - t.n0);
+}
+
+// Eight hidden values as the A operands of three v_mfma_f32_16x16x32_bf16: their planes.
+__device__ __forceinline__ void split_planes8(const float (&x)[8], uint4 (&out)[3]) {
+    uint32_t w[3][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        uint32_t a[2][3];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const float v = x[2 * i + j];
+            a[j][0] = __float_as_uint(v) & 0xFFFF0000u;
+            const float r1 = v - __uint_as_float(a[j][0]);        // exact
+            a[j][1] = __float_as_uint(r1) & 0xFFFF0000u;
+            a[j][2] = __float_as_uint(r1 - __uint_as_float(a[j][1]));   // exact, <= 8 bits
+        }
+#pragma unroll
+        for (int p = 0; p < 3; ++p) w[p][i] = (a[0][p] >> 16) | (a[1][p] & 0xFFFF0000u);
+    }
+#pragma unroll
+    for (int p = 0; p < 3; ++p) out[p] = make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]);
+}
+
+template <typename ET, int MT, int WAVES, int UNROLL, bool PLANES = false>
 __global__ void __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(4)))
 k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
               int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence;
                                group_rows <= 16 MT*/,
-              int gx /*workgroups per row group*/, int ngroups, int rem_div,
+              int gx /*workgroups per row group, a multiple of 8*/, int ngroups, int rem_div, int shared /*see above*/,
               const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
               float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
     constexpr int VEC = ElemTraits<ET>::VEC;
     constexpr int KSTEP = 4 * VEC;
     extern __shared__ uint32_t hsm[];
-    // grid = round_up(gx, 8) * ngroups workgroups.  Workgroup ids go round the 8 XCDs, and the
-    // row groups that read the same candidate rows should share an L2: ids that are congruent
-    // modulo 8 and consecutive otherwise form the row groups of one block of tiles.
-    const uint32_t wg_slot = blockIdx.x >> 3;
-    const uint32_t bx = (wg_slot / (uint32_t)ngroups) * 8u + (blockIdx.x & 7u);
+    // grid = gx * ngroups workgroups.  Workgroup ids go round the 8 XCDs, and the row groups that read
+    // the same candidate rows should share an L2: ids that are congruent modulo 8 and consecutive
+    // otherwise form the row groups of one block of tiles.
+    const uint32_t wg_slot = blockIdx.x >> 3, xcd = blockIdx.x & 7u;
+    const uint32_t bx = wg_slot / (uint32_t)ngroups, wgs = (uint32_t)gx >> 3;   // this workgroup of its XCD's
     const int by = (int)(wg_slot % (uint32_t)ngroups);
-    if (bx >= (uint32_t)gx) return;
     const int row0 = by * group_rows, Bg = min(group_rows, B - row0);
     uint32_t* tile_pref = hsm;
     float (*red)[4][kWave] = reinterpret_cast<float (*)[4][kWave]>(hsm + ((S + 1 + 3) & ~3));
     float* hl = reinterpret_cast<float*>(hsm + ((S + 1 + 3) & ~3) + WAVES * 4 * kWave);
     const int pitch = hlds_pitch(d);
-    // PLANES (bf16 rows, ALIGNED): hidden rows as three bf16 planes, bf16 matrix instructions
-    static_assert(!PLANES || (ALIGNED && VEC == 8), "bf16 planes need aligned bf16 rows");
+    // PLANES (bf16 rows): hidden rows as three bf16 planes, bf16 matrix instructions
+    static_assert(!PLANES || VEC == 8, "bf16 planes need bf16 rows");
     const int ppitch_h = hlds_pitch_planes(d);
     uint16_t* hplane = reinterpret_cast<uint16_t*>(hl);
     const size_t plane_stride = (size_t)group_rows * ppitch_h;
     const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
+    auto ntiles_of = [&](int s) { return (uint32_t)(((count ? count[s] : V) + kTileN - 1) / kTileN); };
     LSH_TRACE(1, 0);
-    if (wv == 0) {
+    if (wv == 0) {   // exclusive prefix of the XCD's tiles over the sentences
         uint32_t carry = 0;
         for (int base = 0; base < S; base += kWave) {
             const int s = base + ln;
-            uint32_t n = 0;
-            if (s < S) n = (uint32_t)(((count ? count[s] : V) + kTileN - 1) / kTileN);
+            const uint32_t n = s < S ? xcd_tiles(ntiles_of(s), (uint32_t)shared, (uint32_t)s, xcd).n : 0u;
             const uint32_t incl = wave_incl_scan(n);
             if (s < S) tile_pref[s] = carry + incl - n;
             carry += wave_read_lane(incl, kWave - 1);
@@ -574,7 +647,7 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
     __syncthreads();
     LSH_TRACE(1, 1);
     const uint32_t total_tiles = tile_pref[S];
-    const uint32_t nwaves = (uint32_t)gx * (uint32_t)WAVES;
+    const uint32_t nwaves = wgs * (uint32_t)WAVES;
     const int col = ln & 15, kq = ln >> 4;
     const int nks = (d + KSTEP - 1) / KSTEP;
     const uint32_t whole = total_tiles / nwaves * nwaves;
@@ -595,38 +668,41 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         if (s == staged) return;
         __syncthreads();  // everyone is done with the previous sentence's rows
         const float* Hs = H + ((size_t)s * B + row0) * d;
-        if constexpr (PLANES) {  // (ALIGNED: d is a multiple of 8 and H is 16-byte aligned)
-            const int d4 = d >> 2;
-            for (int e = tid; e < Bg * d4; e += WAVES * kWave) {
-                const int r = e / d4, c = e - r * d4;
-                const float4 v = reinterpret_cast<const float4*>(Hs)[e];
-                const float x[4] = {v.x, v.y, v.z, v.w};
-                uint32_t pl[3][4];
+        const int whole_k = d - d % VEC;
+        auto put = [&](int r, int k, const float (&x)[4]) {
+            if constexpr (PLANES)
+                store_planes4(reinterpret_cast<char*>(hplane + (size_t)r * ppitch_h + k), plane_stride * 2, x);
+            else
+                *reinterpret_cast<float4*>(hl + (size_t)r * pitch + k) = make_float4(x[0], x[1], x[2], x[3]);
+        };
+        constexpr int AHEAD = 4, T = WAVES * kWave;
+        const int w4 = whole_k >> 2, n = Bg * w4;   // (e / w4 below: e < 2^16, exact as small_div is)
+        const float inv = __builtin_amdgcn_rcpf((float)w4);
+        for (int e0 = tid; e0 < n; e0 += AHEAD * T) {
+            Float4U v[AHEAD];
+            int r[AHEAD], k[AHEAD];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t hi = __float_as_uint(x[q]) & 0xFFFF0000u;
-                    const float r1 = x[q] - __uint_as_float(hi);          // exact
-                    const uint32_t mid = __float_as_uint(r1) & 0xFFFF0000u;
-                    const float r2 = r1 - __uint_as_float(mid);           // exact, <= 8 bits
-                    pl[0][q] = hi >> 16; pl[1][q] = mid >> 16; pl[2][q] = __float_as_uint(r2) >> 16;
-                }
+            for (int j = 0; j < AHEAD; ++j) {
+                const int e = min(e0 + j * T, n - 1);
+                r[j] = (int)(((float)e + 0.5f) * inv);
+                k[j] = 4 * (e - r[j] * w4);
+                v[j] = *reinterpret_cast<const Float4U*>(Hs + (size_t)r[j] * d + k[j]);
+            }
 #pragma unroll
-                for (int pnum = 0; pnum < 3; ++pnum)
-                    *reinterpret_cast<uint2*>(hplane + pnum * plane_stride + (size_t)r * ppitch_h + 4 * c) =
-                        make_uint2(pl[pnum][0] | (pl[pnum][1] << 16), pl[pnum][2] | (pl[pnum][3] << 16));
+            for (int j = 0; j < AHEAD; ++j) {
+                const float x[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+                if (e0 + j * T < n) put(r[j], k[j], x);
             }
-        } else if ((d & 3) == 0 && ((uintptr_t)Hs & 15) == 0) {
-            const int d4 = d >> 2;
-            for (int e = tid; e < Bg * d4; e += WAVES * kWave) {
-                const int r = e / d4, c = e - r * d4;
-                *reinterpret_cast<float4*>(hl + (size_t)r * pitch + 4 * c) =
-                    reinterpret_cast<const float4*>(Hs)[e];
+        }
+        if (whole_k < d && tid < Bg * (VEC / 4)) {   // the partial chunk that ends each row
+            const int r = tid / (VEC / 4), k0 = 4 * (tid % (VEC / 4));
+            float x[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int k = d - VEC + k0 + q;
+                x[q] = k >= whole_k ? Hs[(size_t)r * d + k] : 0.f;
             }
-        } else {
-            for (int e = tid; e < Bg * d; e += WAVES * kWave) {
-                const int r = e / d, c = e - r * d;
-                hl[(size_t)r * pitch + c] = Hs[e];
-            }
+            put(r, whole_k + k0, x);
         }
         __syncthreads();
         staged = s;
@@ -634,7 +710,7 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 
     // whole rounds: one wave per tile; the workgroup walks its consecutive tiles sentence by
     // sentence (all of its waves in the same sentence, so one staging serves them)
-    const uint32_t per_wg = (wave_tiles + (uint32_t)gx - 1) / (uint32_t)gx;
+    const uint32_t per_wg = (wave_tiles + wgs - 1) / wgs;
     const uint32_t wg_begin = min(wave_tiles, bx * per_wg);
     const uint32_t wg_end = min(wave_tiles, wg_begin + per_wg);
     for (uint32_t seg = wg_begin; seg < wg_end;) {
@@ -642,9 +718,10 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         const uint32_t seg_end = min(wg_end, tile_pref[s + 1]);
         stage(s);
         LSH_TRACE(1, 2);
+        const XcdTiles xt = xcd_tiles(ntiles_of(s), (uint32_t)shared, (uint32_t)s, xcd);
         const int C = count ? count[s] : V;
         for (uint32_t t = seg + wv; t < seg_end; t += WAVES) {
-            const int nt = (int)(t - tile_pref[s]);
+            const int nt = (int)xcd_tile(xt, xcd, t - tile_pref[s]);
             const int n0 = nt * kTileN;
             const int cidx = min(n0 + col, C - 1);  // clamped lanes are never stored
             const int64_t j = cand ? cand[(size_t)s * V + cidx] : cidx;
@@ -667,7 +744,7 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                 const int klast = d - VEC;
 #pragma unroll
                 for (int uu = 0; uu < UP; ++uu) {
-                    eb[uu] = *reinterpret_cast<const uint4*>(er + min(uu * KSTEP + kq * VEC, klast));
+                    eb[uu] = load_chunk(er + min(uu * KSTEP + kq * VEC, klast));
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 uint4 hn[MT][3];
@@ -700,11 +777,11 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                             for (int mt = 0; mt < MT; ++mt)
                                 acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
                                     __builtin_bit_cast(bf16x8, hv[mt][pnum]), b, acc[mt], 0, 0, 0);
-                        eb[uu] = *reinterpret_cast<const uint4*>(er + min(k + UP * KSTEP, klast));
+                        eb[uu] = load_chunk(er + min(k + UP * KSTEP, klast));
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-            } else if (ALIGNED) {
+            } else {
                 // Rolling prefetch: UNROLL candidate-row loads stay in flight all the time.  Slot
                 // uu is consumed (LDS read of the hidden rows, VEC matrix instructions) and at
                 // once refilled with the chunk UNROLL k-steps ahead, so memory latency and
@@ -712,7 +789,7 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                 // the row are clamped into it (no branch around a load); such chunks meet
                 // hidden values forced to zero.
                 float ev[UNROLL][VEC];
-                const int klast = d - VEC;  // d is a multiple of VEC here
+                const int klast = d - VEC;
 #pragma unroll
                 for (int uu = 0; uu < UNROLL; ++uu) {
                     ElemTraits<ET>::load16(erow + min(uu * KSTEP + kq * VEC, klast), ev[uu]);
@@ -758,30 +835,6 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-            } else {
-                for (int ks0 = 0; ks0 < nks; ks0 += UNROLL) {
-                    float ev[UNROLL][VEC];
-#pragma unroll
-                    for (int uu = 0; uu < UNROLL; ++uu) {
-                        const int k = (ks0 + uu) * KSTEP + kq * VEC;
-#pragma unroll
-                        for (int q = 0; q < VEC; ++q) ev[uu][q] = (k + q < d) ? elem_f32(erow + k + q) : 0.f;
-                    }
-#pragma unroll
-                    for (int uu = 0; uu < UNROLL; ++uu) {
-                        const int k = (ks0 + uu) * KSTEP + kq * VEC;
-#pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) {
-                            float hv[VEC];
-#pragma unroll
-                            for (int q = 0; q < VEC; ++q)
-                                hv[q] = (k + q < d) ? hrow[mt][min(k + q, d - 1)] : 0.f;
-#pragma unroll
-                            for (int q = 0; q < VEC; ++q)
-                                acc[mt] = __builtin_amdgcn_mfma_f32_16x16x4f32(hv[q], ev[uu][q], acc[mt], 0, 0, 0);
-                        }
-                    }
-                }
             }
             LSH_TRACE(1, 3);
 #pragma unroll
@@ -801,18 +854,336 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
     LSH_TRACE(1, 4);
 
     // the remainder: one workgroup per tile, k split over its waves, hidden rows from LDS
-    for (uint32_t t = wave_tiles + bx; t < total_tiles; t += (uint32_t)gx) {
+    for (uint32_t t = wave_tiles + bx; t < total_tiles; t += wgs) {
         const int s = sentence_of(t);
         stage(s);
-        const int nt = (int)(t - tile_pref[s]);
+        const int nt = (int)xcd_tile(xcd_tiles(ntiles_of(s), (uint32_t)shared, (uint32_t)s, xcd), xcd, t - tile_pref[s]);
         const int C = count ? count[s] : V;
         const int cidx = min(nt * kTileN + col, C - 1);
         const int64_t j = cand ? cand[(size_t)s * V + cidx] : cidx;
         // (the split-k tile code reads fp32 rows: from global memory when LDS holds bf16 planes)
-        logits_tile_all_rows<ET, WAVES, (UNROLL < 4 ? UNROLL : 4), ALIGNED, MT>(
+        logits_tile_all_rows<ET, WAVES, (UNROLL < 4 ? UNROLL : 4), true, MT>(
             E, ld, d, H, B, s, nt, C, j, logits, cpitch, recs, red,
             PLANES ? nullptr : hl, PLANES ? 0 : pitch, row0, row0 + Bg);
     }
+}
+
+// Many tiles.  What bounded k_logits_hlds was neither the fabric nor the matrix pipe but the load path of
+// the CU: a lane that fetches the matrix operand it needs itself makes every 16 lanes touch 16 rows -- 16
+// cache lines for 256 bytes -- and such a gather stops at 8.5 TB/s even where every line hits in L2, 6 TB/s
+// on the lists of a real step.  Here candidate rows travel in contiguous pieces, straight from memory
+// to LDS (global_load_lds, 16 bytes per lane, any row alignment), and the lanes pick their operands out of
+// LDS: 13.5 TB/s from L2, 7.7 from memory, 8.7 on a step's lists.
+//
+// The four waves of a workgroup share a tile, each with a quarter of k, and keep the A operands of all MT * 16
+// hidden rows for their quarter in REGISTERS for as long as the workgroup stays with the sentence.  A step is 64
+// bytes of every candidate row (16 fp32 values for four v_mfma_f32_16x16x4, or 32 bf16 for three
+// v_mfma_f32_16x16x32_bf16, one per plane of the hidden values).  What a wave asks for at a time is a unit: KSN
+// steps of TS tiles -- TS > 1 where rows are short, or one of PARTS parts of its quarter where they are
+// long.  Two units' places in LDS per wave: one arrives while the other is contracted.  The 16-byte piece p of row
+// c lies at piece p ^ (c >> shift) of the row's place, so that 16 lanes reading the same piece of 16 rows meet
+// different banks.  The quarters' partial tiles are summed through LDS in order; the results are stored behind the
+// next unit's wait, so that the stores never stand between a wait and the loads it is for.
+//
+// The tiles of a sentence are dealt to the XCDs by their number (XcdTiles above).
+// 16 bytes per lane from each lane's address to LDS, lane after lane from `to` (wave-uniform) on.  (Not the
+// builtin: for that the compiler waits for ALL such loads before the next read of LDS, whatever it reads.  M0
+// serves nothing else in these kernels.)
+__device__ __forceinline__ void load_to_lds16(const void* from, void* to) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "memory");
+}
+constexpr int kStreamTiles = 32;   // tiles of a stretch whose rows' addresses are in LDS
+constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? 1 : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
+// Workgroups per CU: LDS (52 KB at most) and the registers of the A operands.
+constexpr int stream_wgs(bool bf16, int MT, int KSN, int PARTS) { return (bf16 ? 3 : 1) * MT * KSN * PARTS * 4 <= (bf16 ? 96 : 80) ? 3 : 2; }
+__host__ __device__ inline size_t stream_lds_bytes(int S, int MT, int KSN) {
+    const size_t ts = stream_ts(KSN, MT);
+    return 4 * 2 * ts * KSN * 1024 + 4 * ts * MT * 4 * kWave * 4 + kStreamTiles * kTileN * 8 + (size_t)(2 * ((S + 2 + 3) & ~3)) * 4;
+}
+template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
+template <typename ET, int MT, int KSN, int PARTS>
+__global__ void __launch_bounds__(256, (stream_wgs(sizeof(ET) == 2, MT, KSN, PARTS)))
+k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
+                int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence; <= 16 MT*/,
+                int wgs /*workgroups per XCD and row group*/, int ngroups, int shared,
+                const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
+                float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
+    constexpr bool BF = sizeof(ET) == 2;
+    constexpr int VEC = ElemTraits<ET>::VEC, KSTEP = 4 * VEC, TS = stream_ts(KSN, MT);
+    constexpr int PP = 4 * KSN;                                               // 16-byte pieces of a row in a unit
+    static_assert(KSN == 1 || KSN == 2 || KSN == 4, "");
+    constexpr int SH = PP == 4 ? 2 : PP == 8 ? 1 : 0;
+    // 16-byte registers of A operands per step and row group: fp32 values; their three bf16 planes; for two parts
+    // of those registers run out, and the values are split when they are used
+    constexpr bool LATE = BF && PARTS > 2;
+    constexpr int NH = LATE ? 2 : BF ? 3 : 1;
+    constexpr int NI = TS * KSN;                                              // load instructions of a unit, KiB of its place
+    extern __shared__ uint4 ssm[];
+    char* sm = reinterpret_cast<char*>(ssm);
+    float (*red)[TS][MT][4][kWave] = reinterpret_cast<float (*)[TS][MT][4][kWave]>(sm + 8 * NI * 1024);   // [wave]
+    const ET** rows = reinterpret_cast<const ET**>(sm + 8 * NI * 1024 + 4 * TS * MT * 4 * kWave * 4);   // [tile][16]
+    uint32_t* tile_pref = reinterpret_cast<uint32_t*>(rows + kStreamTiles * kTileN);  // [S + 1], then "own"
+    uint32_t* counts = tile_pref + ((S + 2 + 3) & ~3);                                // [S]
+    // grid = 8 * wgs * ngroups; ids go round the XCDs, the row groups of one block of tiles follow each other on one
+    const uint32_t xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
+    const uint32_t bx = slot / (uint32_t)ngroups;
+    const int row0 = (int)(slot % (uint32_t)ngroups) * group_rows, Bg = min(group_rows, B - row0);
+    const int tid = threadIdx.x, ln = lane_id(), q = __builtin_amdgcn_readfirstlane(wave_id());   // q: the wave's quarter of k
+    const int col = ln & 15, kq = ln >> 4;
+    char* ring = sm + q * (2 * NI * 1024);
+    auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
+    LSH_TRACE(1, 0);
+    // Who takes what.  All tiles of all sentences in a row, cut evenly: then a workgroup may change sentences, which
+    // takes as long as a few tiles.  Or every sentence's tiles cut into stretches of at most `most` -- the fewest
+    // that need no more workgroups than there are -- where that is not much longer than the even share ("own").
+    // tile_pref counts tiles or, own, workgroups.
+    if (q == 0) {
+        uint32_t carry = 0;
+        bool own = false;
+        for (int base = 0; base < S; base += kWave) {
+            const int s = base + ln;
+            const int C = s < S ? (count ? count[s] : V) : 0;
+            uint32_t n = s < S ? xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd).n : 0u;
+            if (S <= min(wgs, kWave)) {
+                constexpr uint32_t kSwitch = KSN * PARTS >= 8 ? 1u : 8u / (KSN * PARTS);
+                const uint32_t even = max((wave_sum(n) + (uint32_t)wgs - 1) / (uint32_t)wgs, 1u);
+                for (uint32_t most = even; most <= even + kSwitch && !own; ++most) {
+                    const uint32_t need = n ? (uint32_t)(int)(((float)(n + most) - 0.5f) * __builtin_amdgcn_rcpf((float)most)) : 0u;   // ceil
+                    if (wave_sum(need) <= (uint32_t)wgs) { own = true; n = need; }
+                }
+            }
+            const uint32_t incl = wave_incl_scan(n);
+            if (s < S) { tile_pref[s] = carry + incl - n; counts[s] = (uint32_t)C; }
+            carry += wave_read_lane(incl, kWave - 1);
+        }
+        if (ln == 0) { tile_pref[S] = carry; tile_pref[S + 1] = own; }
+    }
+    const int nks = (d + KSTEP - 1) / KSTEP, nst = (nks + 3) >> 2, k0 = q * nst * KSTEP;   // steps of a wave's quarter
+    __syncthreads();
+    LSH_TRACE(1, 1);
+    // piece (4 st + kq) of row col: the low two bits of st change lanes' places, the others move on
+    const char* place[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) place[j] = ring + (col * PP + (((4 * j + kq) & (PP - 1)) ^ (col >> SH))) * 16;
+    auto sentence_of = [&](uint32_t at) {   // last s with tile_pref[s] <= at
+        int lo = 0, hi = S;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (tile_pref[mid] <= at) lo = mid; else hi = mid;
+        }
+        return __builtin_amdgcn_readfirstlane(lo);
+    };
+    auto xcd_tiles_of = [&](int s) { return xcd_tiles(ntiles_of((int)counts[s]), (uint32_t)shared, (uint32_t)s, xcd); };
+    const uint32_t total = tile_pref[S];
+    const bool own = __builtin_amdgcn_readfirstlane((int)tile_pref[S + 1]) != 0;
+    uint32_t wg_begin, wg_end;               // own: tiles of its sentence on this XCD; else of all of them
+    if (own) {
+        if (bx >= total) return;
+        const int s = sentence_of(bx);
+        const uint32_t n = xcd_tiles_of(s).n, w = tile_pref[s + 1] - tile_pref[s], i = bx - tile_pref[s];
+        wg_begin = i * n / w;                // (n < 2^20, w <= 64)
+        wg_end = (i + 1) * n / w;
+    } else {
+        const uint32_t per_wg = (total + (uint32_t)wgs - 1) / (uint32_t)wgs;
+        wg_begin = min(total, bx * per_wg);
+        wg_end = min(total, wg_begin + per_wg);
+    }
+    for (uint32_t seg = wg_begin; seg < wg_end;) {
+        const int s = sentence_of(own ? bx : seg);
+        const uint32_t pref = own ? 0u : tile_pref[s];
+        const uint32_t seg_end = min(own ? wg_end : min(wg_end, tile_pref[s + 1]), seg + kStreamTiles);
+        const int C = __builtin_amdgcn_readfirstlane((int)counts[s]);
+        const XcdTiles xt = xcd_tiles_of(s);
+        const int n = (int)(seg_end - seg);                                   // tiles of this stretch
+        auto tile_of = [&](int t) { return (int)xcd_tile(xt, xcd, seg + (uint32_t)t - pref); };
+        constexpr int PER = kStreamTiles * kTileN / 256;
+        int32_t my_id[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (i * 256 >= n * kTileN) break;   // (uniform)
+            const int c = min(tile_of(min(i * 16 + (tid >> 4), n - 1)) * kTileN + col, C - 1);   // clamped columns are never stored
+            my_id[i] = cand ? cand[(size_t)s * V + c] : c;
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // A operands: hidden row col of every row group (clamped: results dropped), zeros past d; a partial chunk
+        // holds the row's last VEC values, those counted already replaced by zero, as `fill` reads it
+        uint4 h[MT][PARTS * KSN][NH];
+        const float* hb = H + ((size_t)s * B + row0) * d;
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const float* hrow = hb + (size_t)min(m * kTileM + col, Bg - 1) * d;
+#pragma unroll
+            for (int st = 0; st < PARTS * KSN; ++st) {
+                const int k = st < nst ? k0 + st * KSTEP + kq * VEC : d, at = min(k, d - VEC), drop = k - at;
+                float x[VEC];
+#pragma unroll
+                for (int e = 0; e < VEC; e += 4) {
+                    const Float4U v = *reinterpret_cast<const Float4U*>(hrow + at + e);
+                    x[e] = v.x; x[e + 1] = v.y; x[e + 2] = v.z; x[e + 3] = v.w;
+                }
+                if ((st & (BF ? 1 : 3)) == (BF ? 1 : 3)) __builtin_amdgcn_sched_barrier(0);   // (a few addresses at a time)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) x[e] = e >= drop ? x[e] : 0.f;
+                if constexpr (LATE) {
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        h[m][st][e] = make_uint4(__float_as_uint(x[4 * e]), __float_as_uint(x[4 * e + 1]), __float_as_uint(x[4 * e + 2]), __float_as_uint(x[4 * e + 3]));
+                } else if constexpr (BF) split_planes8(x, h[m][st]);
+                else h[m][st][0] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);                                    // (waited for before the units' loads are issued)
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (i * 256 >= n * kTileN) break;
+            rows[i * 256 + tid] = E + (int64_t)my_id[i] * ld;
+        }
+        lds_barrier();
+        // unit u = part u % PARTS of the tiles (u / PARTS) TS ..; instruction i of a tile brings its pieces 64 i .. 64 i + 63
+        const int units = (n + TS - 1) / TS * PARTS;
+        auto fill = [&](int u) {
+            const int part = PARTS == 1 ? 0 : u % PARTS, t0 = (PARTS == 1 ? u : u / PARTS) * TS;
+            char* to = ring + (u & 1) * (NI * 1024);
+            const int left = 4 * min(nst - part * KSN, KSN), k1 = k0 + part * (KSN * KSTEP);   // pieces (>= 4), first k
+            const bool simple = left == PP && k1 + KSN * KSTEP <= d;          // (uniform)
+            constexpr int RPI = kWave / PP;                                   // rows per instruction
+            const int lr = ln / PP;
+            int swz = (ln % PP) ^ (lr >> SH);                                 // (row i RPI + lr: piece swz ^ (i RPI >> SH))
+            asm volatile("" : "+v"(swz));   // (every part's offsets worked out in advance would take too many registers)
+#pragma unroll
+            for (int t = 0; t < TS; ++t) {
+                if (t0 + t >= n) break;   // (uniform)
+                const ET* row[KSN];
+#pragma unroll
+                for (int i = 0; i < KSN; ++i) row[i] = rows[(t0 + t) * kTileN + i * RPI + lr];
+                char* at = to + t * (KSN * 1024);
+                if (simple) {
+#pragma unroll
+                    for (int i = 0; i < KSN; ++i)
+                        load_to_lds16(reinterpret_cast<const char*>(row[i]) + ((uint32_t)((16 * swz) ^ (16 * (i * RPI >> SH))) + (uint32_t)(k1 * (int)sizeof(ET))),
+                                      at + i * 1024);
+                } else {                  // pieces past the quarter: not loaded; past the row: its last chunk
+#pragma unroll
+                    for (int i = 0; i < KSN; ++i) {
+                        const int p = swz ^ (i * RPI >> SH);
+                        if (p < left) load_to_lds16(row[i] + min(k1 + p * VEC, d - VEC), at + i * 1024);
+                    }
+                }
+            }
+        };
+        auto whole = [&](int u) { return u < units && (PARTS == 1 ? u : u / PARTS) * TS + TS <= n; };   // NI loads were issued
+        fill(0);
+        if (units > 1) fill(1);
+        float out[TS][MT];
+        int out_t0 = -1;                                                      // first tile of `out`
+        // thread (i, col) has row 16 m + i, column col of every tile: 16 lanes per row (waves without rows: nothing)
+        float* lrow = logits + ((size_t)s * B + row0 + (tid >> 4)) * cpitch + col;
+        float2* rrow = reinterpret_cast<float2*>(recs.rec) + ((size_t)s * B + row0 + (tid >> 4)) * recs.pitch;
+        auto store_out = [&]() {
+#pragma unroll
+            for (int t = 0; t < TS; ++t) {
+                if (out_t0 + t >= n) break;
+                const int nt = tile_of(out_t0 + t);
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    if (4 * q + m * kTileM >= Bg) break;                      // (uniform)
+                    const bool row_ok = (tid >> 4) + m * kTileM < Bg, valid = row_ok && nt * kTileN + col < C;
+                    if (valid) lrow[(size_t)(m * kTileM) * cpitch + nt * kTileN] = out[t][m];
+                    const float mx = row16_max(valid ? out[t][m] : -INFINITY);
+                    const float se = row16_sum(valid ? expf(out[t][m] - mx) : 0.f);
+                    if (col == 0 && row_ok) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
+                }
+            }
+        };
+        floatx4 acc[TS][MT];
+        for (int u0 = 0; u0 < units; u0 += PARTS) {
+#pragma unroll
+            for (int t = 0; t < TS; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int part = 0; part < PARTS; ++part) {
+                const int u = u0 + part;
+                // (the unit's own loads are older than the next unit's NI; a shorter or no next unit: all of them)
+                if (whole(u + 1)) wait_vmem<NI>(); else wait_vmem<0>();
+                if (part == 0 && out_t0 >= 0) store_out();
+                const int at = (u & 1) * (NI * 1024);
+                const int steps = PARTS * KSN == 1 ? 1 : min(nst - part * KSN, KSN);
+                auto operand = [&](int t, int st) {
+                    return *reinterpret_cast<const uint4*>(place[st & 3] + at + t * (KSN * 1024) + (st >> 2) * 256);
+                };
+#pragma unroll
+                for (int t = 0; t < TS; ++t) {
+                    uint4 e_next = operand(t, 0);
+#pragma unroll
+                    for (int st = 0; st < KSN; ++st) {
+                        if (st >= steps) break;   // (uniform)
+                        const uint4 e = e_next;
+                        if (st + 1 < KSN) e_next = operand(t, st + 1);
+                        const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
+                        if constexpr (BF) {
+#pragma unroll
+                            for (int m = 0; m < MT; ++m) {
+                                uint4 hp[3];
+                                if constexpr (LATE) {
+                                    const uint4 a = h[m][part * KSN + st][0], b = h[m][part * KSN + st][1];
+                                    const float x[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+                                                        __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+                                    split_planes8(x, hp);
+                                } else {
+#pragma unroll
+                                    for (int p = 0; p < 3; ++p) hp[p] = h[m][part * KSN + st][p];
+                                }
+#pragma unroll
+                                for (int p = 0; p < 3; ++p)
+                                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hp[p]),
+                                                                                        __builtin_bit_cast(bf16x8, e), acc[t][m], 0, 0, 0);
+                            }
+                        } else {
+#pragma unroll
+                            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                                for (int m = 0; m < MT; ++m) {
+                                    const uint4 hv = h[m][part * KSN + st][0];
+                                    const uint32_t hx = x == 0 ? hv.x : x == 1 ? hv.y : x == 2 ? hv.z : hv.w;
+                                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(hx), __uint_as_float(ew[x]), acc[t][m], 0, 0, 0);
+                                }
+                        }
+                    }
+                }
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // (every operand has left the unit's place)
+                __builtin_amdgcn_sched_barrier(0);
+                if (u + 2 < units) fill(u + 2);
+            }
+#pragma unroll
+            for (int t = 0; t < TS; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) red[q][t][m][r][ln] = acc[t][m][r];
+            lds_barrier();
+            // thread (i, col) sums row i, column col of every tile: 16 lanes per row
+            const int i = tid >> 4;
+#pragma unroll
+            for (int t = 0; t < TS; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    if (4 * q + m * kTileM >= Bg) { out[t][m] = 0.f; continue; }
+                    float sum = 0.f;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) sum += red[w][t][m][i & 3][(i >> 2) * 16 + col];
+                    out[t][m] = sum;
+                }
+            out_t0 = u0 / PARTS * TS;
+            lds_barrier();
+        }
+        store_out();
+        seg = seg_end;
+        if (seg < wg_end) __syncthreads();                                    // (the table of rows is read no more)
+    }
+    LSH_TRACE(1, 4);
 }
 
 // 33..64 beams, fp32 rows, d <= 1024: the operands change places.  The hidden rows do not fit in
@@ -1171,22 +1542,6 @@ __device__ __forceinline__ Chunk16U<ET> load_chunk_end(const ET* row, int k, int
     if (s & (2 * ONE)) { c.w[0] = c.w[2]; c.w[1] = c.w[3]; c.w[2] = 0u; c.w[3] = 0u; }
     if (s & (4 * ONE)) { c.w[0] = 0u; c.w[1] = 0u; c.w[2] = 0u; c.w[3] = 0u; }
     return c;
-}
-// Four hidden values as the three bf16 planes of k_logits_hlds (exactly x = hi + mid + lo), to LDS.
-__device__ __forceinline__ void store_planes4(char* dst, size_t plane_bytes, const float (&x)[4]) {
-    uint32_t hi[4], mid[4], lo[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        hi[q] = __float_as_uint(x[q]) & 0xFFFF0000u;
-        const float r1 = x[q] - __uint_as_float(hi[q]);          // exact
-        mid[q] = __float_as_uint(r1) & 0xFFFF0000u;
-        lo[q] = __float_as_uint(r1 - __uint_as_float(mid[q]));   // exact, <= 8 bits
-    }
-    *reinterpret_cast<uint2*>(dst) = make_uint2((hi[0] >> 16) | (hi[1] & 0xFFFF0000u), (hi[2] >> 16) | (hi[3] & 0xFFFF0000u));
-    *reinterpret_cast<uint2*>(dst + plane_bytes) =
-        make_uint2((mid[0] >> 16) | (mid[1] & 0xFFFF0000u), (mid[2] >> 16) | (mid[3] & 0xFFFF0000u));
-    *reinterpret_cast<uint2*>(dst + 2 * plane_bytes) =
-        make_uint2((lo[0] >> 16) | (lo[1] & 0xFFFF0000u), (lo[2] >> 16) | (lo[3] & 0xFFFF0000u));
 }
 template <typename ET> __device__ __forceinline__ bf16x8 as_bf16x8(const Chunk16U<ET>& c) {
     return __builtin_bit_cast(bf16x8, make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]));

@@ -304,14 +304,17 @@ int part_rows_of(const lsh_tables* t, const lsh_step_params* sp, int stage_words
     return sp->B > candidates_rows_per_chunk(sp->B, t->d, t->W, stage_words) ? rpc : 0;
 }
 
+// Whether a row of E holds a 16-byte chunk: what every contraction but the elementwise forms needs.
+inline bool has_chunks(const lsh_tables* t) { return t->d >= (t->dtype == LSH_F32 ? 4 : 8); }
+
 template <typename ET, int WAVES>
-void launch_logits_w(const StepCtx& cx, int grid, bool aligned, const float* H,
+void launch_logits_w(const StepCtx& cx, int grid, bool chunks, const float* H,
                      const lsh_step_params* sp, const int32_t* cand, const int32_t* count,
                      const Workspace& w) {
     const lsh_tables* t = cx.t;
     constexpr int UNROLL = (WAVES >= 16) ? 4 : 8;
     const ET* E = (const ET*)t->E;
-    if (aligned)
+    if (chunks)
         launch(cx, 1, k_logits<ET, WAVES, UNROLL, true>, dim3(grid), dim3(WAVES * kWave), 0, E,
                t->ld, t->d, H, sp->S, sp->B, cand, count, t->V, w.logits, w.cpitch, w.records());
     else
@@ -320,14 +323,14 @@ void launch_logits_w(const StepCtx& cx, int grid, bool aligned, const float* H,
 }
 
 template <typename ET, int MT>
-void launch_logits_wave(const StepCtx& cx, int grid, bool aligned, const float* H,
+void launch_logits_wave(const StepCtx& cx, int grid, bool chunks, const float* H,
                         const lsh_step_params* sp, const int32_t* cand, const int32_t* count,
                         const Workspace& w) {
     const lsh_tables* t = cx.t;
     // loads in flight per lane: 32 (fp32) / 64 (bf16) bytes of E per step, plus MT times that of H
     constexpr int UNROLL = ((MT == 1) ? 8 : 4) / (ElemTraits<ET>::VEC / 4);
     const ET* E = (const ET*)t->E;
-    if (aligned)
+    if (chunks)
         launch(cx, 1, k_logits_wave<ET, MT, UNROLL, true>, dim3(grid), dim3(256), 0, E, t->ld, t->d,
                H, sp->S, sp->B, cand, count, t->V, w.logits, w.cpitch, w.records());
     else
@@ -354,7 +357,7 @@ inline int hlds_group_rows(const lsh_tables* t, int S, int B, int d) {
 }
 
 template <typename ET>
-void launch_logits_hlds(const StepCtx& cx, int64_t tiles_n, bool aligned, const float* H,
+void launch_logits_hlds(const StepCtx& cx, int64_t tiles_n, const float* H,
                         const lsh_step_params* sp, const int32_t* cand, const int32_t* count,
                         const Workspace& w, int group_rows) {
     const lsh_tables* t = cx.t;
@@ -365,37 +368,82 @@ void launch_logits_hlds(const StepCtx& cx, int64_t tiles_n, bool aligned, const 
     // one launch: a workgroup serves one group of `rows` hidden rows (the last group may be smaller)
     const int rows = std::min(group_rows, sp->B);
     const int ngroups = (sp->B + rows - 1) / rows;
-#define LSH_HLDS(MTV, WV, UV, AL, PL)                                                                \
+    // tiles that surely lie among the top-frequent words (T distinct ones, where they are the lowest ids); a
+    // few such tiles are not worth the uneven shares of the XCDs
+    const int shared = cand && sp->T >= 32 * kTileN ? sp->T / kTileN : 0;
+#define LSH_HLDS(MTV, WV, UV, PL)                                                                    \
     do {                                                                                             \
-        auto kfn = k_logits_hlds<ET, MTV, WV, UV, AL, PL>;                                           \
+        auto kfn = k_logits_hlds<ET, MTV, WV, UV, PL>;                                               \
         const size_t lds = hlds_lds_bytes(sp->S, rows, t->d, WV, PL);                                \
-        const int gx = (int)std::min<int64_t>(                                                       \
-            tiles_n, std::max(1, t->option(kOptLogitsGrid, 4096 / WV) / ngroups));              \
-        const int grid = ((gx + 7) / 8 * 8) * ngroups;                                               \
-        launch(cx, 1, kfn, dim3(grid), dim3(WV * kWave), lds, E, t->ld, t->d, H, sp->S, sp->B,   \
-               rows, gx, ngroups, t->option(kOptHldsRem, 4), cand, count, t->V, w.logits,      \
+        const int gx = (int)(std::min<int64_t>(                                                      \
+            tiles_n, std::max(1, t->option(kOptLogitsGrid, 4096 / WV) / ngroups)) + 7) / 8 * 8;      \
+        launch(cx, 1, kfn, dim3(gx * ngroups), dim3(WV * kWave), lds, E, t->ld, t->d, H, sp->S, sp->B,   \
+               rows, gx, ngroups, t->option(kOptHldsRem, 4), shared, cand, count, t->V, w.logits,      \
                w.cpitch, w.records());                                                      \
     } while (0)
     // bf16 rows, up to 16 hidden rows per group, two workgroups per CU: the hidden rows go to LDS
     // as three bf16 planes and the contraction runs on bf16 matrix instructions
     // (LSHBEAM_LOGITS_PLANES=0: widened to fp32 as for every other shape)
     if constexpr (std::is_same<ET, uint16_t>::value) {
-        if (aligned && rows <= kTileM && hlds_lds_bytes(sp->S, rows, t->d, 8, true) <= kHldsHalf &&
+        if (rows <= kTileM && hlds_lds_bytes(sp->S, rows, t->d, 8, true) <= kHldsHalf &&
             t->option(kOptLogitsPlanes, 1)) {
-            LSH_HLDS(1, 8, U1, true, true);
+            LSH_HLDS(1, 8, U1, true);
             return;
         }
     }
     const bool two = rows > kTileM;
     const bool small = hlds_lds_bytes(sp->S, rows, t->d, 8) <= kHldsHalf;
-    if (small) {
-        if (two) { if (aligned) LSH_HLDS(2, 8, U2, true, false); else LSH_HLDS(2, 8, U2, false, false); }
-        else { if (aligned) LSH_HLDS(1, 8, U1, true, false); else LSH_HLDS(1, 8, U1, false, false); }
-    } else {
-        if (two) { if (aligned) LSH_HLDS(2, 16, U2W, true, false); else LSH_HLDS(2, 16, U2W, false, false); }
-        else { if (aligned) LSH_HLDS(1, 16, U1, true, false); else LSH_HLDS(1, 16, U1, false, false); }
-    }
+    if (small) { if (two) LSH_HLDS(2, 8, U2, false); else LSH_HLDS(1, 8, U1, false); }
+    else { if (two) LSH_HLDS(2, 16, U2W, false); else LSH_HLDS(1, 16, U1, false); }
 #undef LSH_HLDS
+}
+
+// Whether an option names k_logits_hlds (or its absence): it wins over k_logits_stream.
+inline bool names_hlds(const lsh_tables* t) {
+    return t->opt[kOptLogitsHlds] != kAuto || t->opt[kOptHldsRows] != kAuto || t->opt[kOptHldsRem] != kAuto ||
+           t->opt[kOptLogitsPlanes] != kAuto;
+}
+// k_logits_stream: steps of 64 bytes per unit and parts of a wave's quarter of the row.
+struct StreamPlan { int ksn, parts; };
+template <typename ET> StreamPlan stream_plan(int d) {
+    constexpr int kstep = 4 * ElemTraits<ET>::VEC;
+    const int nst = ((d + kstep - 1) / kstep + 3) / 4;
+    return nst <= 1 ? StreamPlan{1, 1} : nst <= 2 ? StreamPlan{2, 1} : StreamPlan{4, (nst + 3) / 4};
+}
+// Hidden rows per workgroup (0: the kernel does not take the step).  Registers bound the operands a wave keeps:
+// two row groups of 16 where they are at most 128 of them.
+template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
+    if (!has_chunks(t)) return 0;
+    const StreamPlan p = stream_plan<ET>(t->d);
+    if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
+    const bool two = p.parts <= (sizeof(ET) == 2 ? 1 : 4) && sp->B > kTileM;
+    if (stream_lds_bytes(sp->S, two ? 2 : 1, p.ksn) > kMaxDynLds) return 0;
+    return std::min<int>(sp->B, two ? 2 * kTileM : kTileM);
+}
+template <typename ET>
+void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, const lsh_step_params* sp,
+                          const int32_t* cand, const int32_t* count, const Workspace& w, int rows) {
+    const lsh_tables* t = cx.t;
+    const StreamPlan p = stream_plan<ET>(t->d);
+    const int ngroups = (sp->B + rows - 1) / rows;
+    // tiles that surely lie among the top-frequent words (T distinct ones, where they are the lowest ids); a
+    // few such tiles are not worth the uneven shares of the XCDs
+    const int shared = cand && sp->T >= 32 * kTileN ? sp->T / kTileN : 0;
+    const int wgs = (int)std::min<int64_t>((tiles_n + 7) / 8, std::max(1, t->option(kOptLogitsGrid, 256 * stream_wgs(sizeof(ET) == 2, rows > kTileM ? 2 : 1, p.ksn, p.parts)) / 8 / ngroups));
+#define LSH_STREAM(MTV, KSNV, PV)                                                                             \
+    launch(cx, 1, k_logits_stream<ET, MTV, KSNV, PV>, dim3(8 * wgs * ngroups), dim3(256), stream_lds_bytes(sp->S, MTV, KSNV), \
+           (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, shared, cand, count, t->V, w.logits, w.cpitch, \
+           w.records())
+#define LSH_STREAM2(KSNV, PV) do { if (rows > kTileM) LSH_STREAM(2, KSNV, PV); else LSH_STREAM(1, KSNV, PV); } while (0)
+    if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2) LSH_STREAM2(2, 1); else if (p.parts == 1) LSH_STREAM2(4, 1);
+    else if constexpr (sizeof(ET) == 2) switch (p.parts) { case 2: LSH_STREAM(1, 4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; default: LSH_STREAM(1, 4, 4); }
+    else switch (p.parts) {
+        case 2: LSH_STREAM2(4, 2); break; case 3: LSH_STREAM2(4, 3); break; case 4: LSH_STREAM2(4, 4); break;
+        case 5: LSH_STREAM(1, 4, 5); break; case 6: LSH_STREAM(1, 4, 6); break; case 7: LSH_STREAM(1, 4, 7); break;
+        default: LSH_STREAM(1, 4, 8);
+    }
+#undef LSH_STREAM2
+#undef LSH_STREAM
 }
 
 // k_logits_estage: 33..64 beams, fp32 rows of at most 1024 values, 16-byte aligned operands, at
@@ -439,9 +487,7 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
                   const int32_t* cand, const int32_t* count, const Workspace& w,
                   const EstageUnion* un = nullptr) {
     const lsh_tables* t = cx.t;
-    constexpr int VEC = ElemTraits<ET>::VEC;
-    const bool aligned = (t->d % VEC == 0) && (t->ld % VEC == 0) && ((uintptr_t)t->E % 16 == 0) &&
-                         (t->d % 4 == 0) && ((uintptr_t)H % 16 == 0);
+    const bool chunks = has_chunks(t);
     const int MT = (sp->B + kTileM - 1) / kTileM;
     const int64_t tiles_n = (int64_t)sp->S * ((t->V + kTileN - 1) / kTileN);  // upper bound
     const int64_t max_tiles = tiles_n * MT;
@@ -459,22 +505,24 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
     // the other drivers)
     if (takes_estage(t, sp, H)) {
         return launch_logits_estage(cx, H, sp, cand, count, w, un);
-    } else if (mode == 1 && group_rows > 0 && t->option(kOptLogitsHlds, 1)) {
-        launch_logits_hlds<ET>(cx, tiles_n, aligned, H, sp, cand, count, w, group_rows);
+    } else if (const int rows = stream_rows<ET>(t, sp); mode == 1 && rows > 0 && !names_hlds(t)) {
+        launch_logits_stream<ET>(cx, tiles_n, H, sp, cand, count, w, rows);
+    } else if (mode == 1 && chunks && group_rows > 0 && t->option(kOptLogitsHlds, 1)) {
+        launch_logits_hlds<ET>(cx, tiles_n, H, sp, cand, count, w, group_rows);
     } else if (mode == 1 && MT <= 4) {
         const int grid = (int)std::min<int64_t>((tiles_n + 3) / 4, t->option(kOptLogitsGrid, 1024));
         switch (MT) {
-            case 1: launch_logits_wave<ET, 1>(cx, grid, aligned, H, sp, cand, count, w); break;
-            case 2: launch_logits_wave<ET, 2>(cx, grid, aligned, H, sp, cand, count, w); break;
-            case 3: launch_logits_wave<ET, 3>(cx, grid, aligned, H, sp, cand, count, w); break;
-            default: launch_logits_wave<ET, 4>(cx, grid, aligned, H, sp, cand, count, w); break;
+            case 1: launch_logits_wave<ET, 1>(cx, grid, chunks, H, sp, cand, count, w); break;
+            case 2: launch_logits_wave<ET, 2>(cx, grid, chunks, H, sp, cand, count, w); break;
+            case 3: launch_logits_wave<ET, 3>(cx, grid, chunks, H, sp, cand, count, w); break;
+            default: launch_logits_wave<ET, 4>(cx, grid, chunks, H, sp, cand, count, w); break;
         }
     } else if (mode >= 16) {
         const int grid = (int)std::min<int64_t>(max_tiles, t->option(kOptLogitsGrid, 256));
-        launch_logits_w<ET, 16>(cx, grid, aligned, H, sp, cand, count, w);
+        launch_logits_w<ET, 16>(cx, grid, chunks, H, sp, cand, count, w);
     } else {
         const int grid = (int)std::min<int64_t>(max_tiles, t->option(kOptLogitsGrid, 2048));
-        launch_logits_w<ET, 4>(cx, grid, aligned, H, sp, cand, count, w);
+        launch_logits_w<ET, 4>(cx, grid, chunks, H, sp, cand, count, w);
     }
     return 0;
 }
@@ -531,11 +579,17 @@ hipError_t allow_logits_lds() {
     do {                                                                 \
         if (e == hipSuccess) e = allow_whole_lds<k_logits_hlds<ET, __VA_ARGS__>>(); \
     } while (0)
-    LSH_ALLOW(1, 8, U1, true, false);  LSH_ALLOW(1, 8, U1, false, false);
-    LSH_ALLOW(2, 8, U2, true, false);  LSH_ALLOW(2, 8, U2, false, false);
-    LSH_ALLOW(1, 16, U1, true, false); LSH_ALLOW(1, 16, U1, false, false);
-    LSH_ALLOW(2, 16, U2W, true, false); LSH_ALLOW(2, 16, U2W, false, false);
-    if constexpr (std::is_same<ET, uint16_t>::value) LSH_ALLOW(1, 8, U1, true, true);
+    LSH_ALLOW(1, 8, U1, false); LSH_ALLOW(2, 8, U2, false);
+    LSH_ALLOW(1, 16, U1, false); LSH_ALLOW(2, 16, U2W, false);
+    if constexpr (std::is_same<ET, uint16_t>::value) LSH_ALLOW(1, 8, U1, true);
+#undef LSH_ALLOW
+#define LSH_ALLOW(...) do { if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, __VA_ARGS__>>(); } while (0)
+    LSH_ALLOW(1, 1, 1); LSH_ALLOW(1, 2, 1); LSH_ALLOW(1, 4, 1); LSH_ALLOW(1, 4, 2); LSH_ALLOW(1, 4, 3); LSH_ALLOW(1, 4, 4);
+    LSH_ALLOW(2, 1, 1); LSH_ALLOW(2, 2, 1); LSH_ALLOW(2, 4, 1);
+    if constexpr (sizeof(ET) == 4) {
+        LSH_ALLOW(2, 4, 2); LSH_ALLOW(2, 4, 3); LSH_ALLOW(2, 4, 4);
+        LSH_ALLOW(1, 4, 5); LSH_ALLOW(1, 4, 6); LSH_ALLOW(1, 4, 7); LSH_ALLOW(1, 4, 8);
+    }
 #undef LSH_ALLOW
     return e;
 }
@@ -897,9 +951,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
         selected = tail.tickets != nullptr;
         const int per_sentence = std::min(kMaxFusedGrid, std::max(1, t->option(kOptFusedGrid, 256) / sp->S));
         const dim3 grid((unsigned)(per_sentence * sp->S)), block(kCandThreads);
-        const bool aligned16 = ((uintptr_t)t->E % 16 == 0) && (t->d % 4 == 0) && ((uintptr_t)H_dev % 16 == 0);
-        const bool f32 = t->dtype == LSH_F32;
-        const bool al = f32 ? (aligned16 && t->ld % 4 == 0) : (aligned16 && t->ld % 8 == 0 && t->d % 8 == 0);
+        const bool f32 = t->dtype == LSH_F32, al = has_chunks(t);
         if (parts) {
             const size_t lds = (size_t)t->wg_union_logits_lds;
 #define LSH_UNION_LOGITS(ET, AL, OL)                                                              \
