@@ -265,6 +265,16 @@ hipError_t allow_whole_lds() {
     return e;
 }
 
+// How many candidates a sentence's list will hold at least: its top-frequent words and what its hidden rows
+// hit by chance (bands independent, codes evenly spread; rows near clustered words hit more).
+inline double expected_candidates(const lsh_tables* t, const lsh_step_params* sp) {
+    const double m = t->W * std::pow((double)t->K, -(double)t->u);   // expected bands in which a row and a word collide
+    double below = 0.0, p = std::exp(-m);
+    for (int i = 0; i < std::min<int>(sp->threshold, 64); ++i) { below += p; p *= m / (i + 1); }
+    const double missed = (1.0 - std::min(1.0, (double)sp->T / t->V)) * std::pow(std::min(1.0, below), sp->B);
+    return t->V * (1.0 - missed);
+}
+
 // Little work per step (few sentences x 16-row groups): every workgroup of the logits grid
 // regenerates the candidates itself (k_cand_logits); otherwise one candidates workgroup per
 // sentence, then the logits grid.  LSHBEAM_FUSED=0/1 overrides the size rule (for tests and
@@ -274,8 +284,10 @@ bool step_is_fused(const lsh_tables* t, const lsh_step_params* sp) {
     const bool possible = !sp->full_vocab && (size_t)t->wg_fused_lds <= kMaxDynLds && sp->S <= 64;
     // (with three or more groups of 16 beams the separate split-k kernel, one (tile, group) per
     // workgroup at a time, is faster than the fused kernel's all-groups-per-tile loop)
-    const bool wanted = t->option(kOptFused, (sp->S * MT <= 8 && MT <= 2) ? 1 : 0) != 0;
-    return possible && wanted;
+    if (t->opt[kOptFused] != kAuto) return possible && t->opt[kOptFused] != 0;
+    // (with more than about 1.5 tiles for each of the 256 workgroups, what they do one after the other outweighs the
+    // kernels saved: S = 8, B = 5, V = 40000 bf16: 32.1 -> 29.8 us a step; 468 bands, t = 3, 19000 candidates: 143 -> 56)
+    return possible && sp->S * MT <= 8 && MT <= 2 && sp->S * expected_candidates(t, sp) <= 1.5 * 256 * kTileN;
 }
 
 // LDS words for the staged hidden rows of a step: room for all B rows of a sentence (up to
@@ -450,6 +462,7 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
 // most 256 sentences.  About one workgroup per CU, dealt evenly to the sentences.
 // Returns its workgroups per sentence: each leaves one record per hidden row for all its tiles.
 // un, if given: the kernel makes the candidate list itself, from the bitmaps of the sentence's parts.
+constexpr int kEsMinD = 512;
 int launch_logits_estage(const StepCtx& cx, const float* H, const lsh_step_params* sp,
                          const int32_t* cand, const int32_t* count, const Workspace& w,
                          const EstageUnion* un = nullptr) {
@@ -471,12 +484,14 @@ int launch_logits_estage(const StepCtx& cx, const float* H, const lsh_step_param
     return per_sentence;
 }
 
-// Whether a step's contraction is k_logits_estage: 33..64 beams, fp32 rows of at most 1024 values,
+// Whether a step's contraction is k_logits_estage: 33..64 beams, fp32 rows of 513 to 1024 values (shorter ones
+// leave half of its four slices of k or more without work: k_logits_stream is 1.2 to 1.9 times faster there,
+// 1.1 to 1.3 times slower beyond; fifty shapes),
 // 16-byte aligned operands, at most 256 sentences (option logits_estage = 0: the other drivers).
 bool takes_estage(const lsh_tables* t, const lsh_step_params* sp, const float* H) {
     const bool aligned = (t->d % 4 == 0) && (t->ld % 4 == 0) && ((uintptr_t)t->E % 16 == 0) && ((uintptr_t)H % 16 == 0);
     return t->dtype == LSH_F32 && aligned && sp->B > 2 * kTileM && sp->B <= 4 * kTileM &&
-           t->d <= kEsSlices * kEsSlice && sp->S <= 256 && estage_lds_bytes(true) <= kMaxDynLds &&
+           t->d > kEsMinD && t->d <= kEsSlices * kEsSlice && sp->S <= 256 && estage_lds_bytes(true) <= kMaxDynLds &&
            t->option(kOptLogitsEstage, 1) && !t->option(kOptLogitsWaves, 0);
 }
 
@@ -497,7 +512,10 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
     // (the full-vocabulary mode has V / 16 tiles per sentence, known here: thousands of tiles
     // are "many" even for one sentence -- 29.9 against 37.1 us at V = 40000)
     const bool few = sp->S * MT <= 8 && !(count == nullptr && tiles_n >= 1024);
-    const int mode = t->option(kOptLogitsWaves, few ? 16 : 1);
+    // (fused = 0 asks for the fused plan's arithmetic in kernels of its own: k split over 16 waves as there)
+    const bool as_fused = few && MT <= 2 && t->opt[kOptFused] == 0;
+    const int rows = names_hlds(t) || as_fused ? 0 : stream_rows<ET>(t, sp);
+    const int mode = t->option(kOptLogitsWaves, few && !rows ? 16 : 1);
     // one wave per tile with the sentence's hidden rows staged in LDS, more than 32 rows in
     // groups; LSHBEAM_LOGITS_HLDS=0 keeps the rows in global memory (k_logits_wave)
     const int group_rows = hlds_group_rows(t, sp->S, sp->B, t->d);
@@ -505,7 +523,7 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
     // the other drivers)
     if (takes_estage(t, sp, H)) {
         return launch_logits_estage(cx, H, sp, cand, count, w, un);
-    } else if (const int rows = stream_rows<ET>(t, sp); mode == 1 && rows > 0 && !names_hlds(t)) {
+    } else if (mode == 1 && rows > 0) {
         launch_logits_stream<ET>(cx, tiles_n, H, sp, cand, count, w, rows);
     } else if (mode == 1 && chunks && group_rows > 0 && t->option(kOptLogitsHlds, 1)) {
         launch_logits_hlds<ET>(cx, tiles_n, H, sp, cand, count, w, group_rows);

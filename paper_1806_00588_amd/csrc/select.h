@@ -414,14 +414,24 @@ __device__ __forceinline__ uint32_t select_front_grouped(SelShared& sh, int s, c
 // of up to 256 tiles -- a dozen beams over a few thousand candidates -- then runs the code for
 // four (Q = 4), a longer one asks for the rest and runs the code for eight.  The word id of a tile's second largest logit is
 // fetched only when that logit reaches the threshold (on the benchmark's chained steps: never).
+// A second largest among the B best: the tiles whose second reaches the threshold -- the only ones that
+// can hide a third -- are opened here, 16 lanes each, their other words join the list and it is ranked again
+// (two trips to memory; the general path, which starts over, took 4 us more: V = 1000, 4 beams 7.4 us).
 constexpr int kSmallQ = 8;
+struct OpenSrc {            // what opening a tile takes
+    const float* logits;    // first row of the sentence
+    int64_t cpitch;
+    const int32_t* cand;    // the sentence's list, null: all words
+    int C, tn;              // its length, candidates per tile
+};
 template <bool SAME_KERNEL, int Q>
 __device__ __forceinline__ bool select_rich_small_body(SelShared& sh, int s, float bsi, float4 (&rec)[kSmallQ],
                                                        const int32_t* ids2_row, int ntiles, int B, float* lse_out,
-                                                       int32_t* out_beam, int32_t* out_word, float* out_score) {
+                                                       int32_t* out_beam, int32_t* out_word, float* out_score,
+                                                       const OpenSrc& open) {
     const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
     const bool has_row = wv < B;
-    if (tid == 0) { sh.misc[4] = 0; sh.misc[6] = 0; }
+    if (tid == 0) { sh.misc[4] = 0; sh.misc[5] = 0; sh.misc[6] = 0; }
 
     // log-sum-exp of the row, the lane's best tile maximum
     // (the arithmetic of the general path, operation for operation: the plans agree bit for bit)
@@ -442,7 +452,7 @@ __device__ __forceinline__ bool select_rich_small_body(SelShared& sh, int s, flo
         const float M = wave_max_f32(m);
         const float part = wave_sum_f32((m == -INFINITY) ? 0.f : sum * __expf(m - M));
         lse = M + logf(part);
-        if (ln == 0) lse_out[s * B + wv] = lse;
+        if (ln == 0) { lse_out[s * B + wv] = lse; sh.lse[wv] = lse; sh.bs[wv] = bsi; }
         if (m != -INFINITY) best = f32_sortable(bsi + (m - lse) + 0.0f);
     }
     // tau: the largest over the rows of "B-th largest lane value of the row" (B distinct tile
@@ -485,6 +495,14 @@ __device__ __forceinline__ bool select_rich_small_body(SelShared& sh, int s, flo
                 if (key2[q]) id2[q] = load_id2<SAME_KERNEL>(ids2_row + ln + q * kWave);
                 if (id2[q] < 0) key2[q] = 0;
                 mine += key2[q] ? 1u : 0u;
+                if (!SAME_KERNEL && key2[q]) {   // (its tile, should it have to be opened)
+                    const uint32_t at = atomicAdd(&sh.misc[5], 1u);
+                    if (at < (uint32_t)kWave) {
+                        sh.rank[at] = ((uint32_t)wv << 20) | (uint32_t)(ln + q * kWave);
+                        sh.hist[at] = (uint32_t)__float_as_int(rec[q].w);
+                        sh.hist[kWave + at] = (uint32_t)id2[q];
+                    }
+                }
             }
         }
         if (__ballot(mine != 0) != 0ull) {   // (uniform)
@@ -515,51 +533,81 @@ __device__ __forceinline__ bool select_rich_small_body(SelShared& sh, int s, flo
         }
     }
     __syncthreads();
-    const int mr = (int)sh.misc[4];
-    LSH_TRACE_ANY(2, 3);
-    if (mr > kWave) return false;   // (uniform; a longer list is the general path's)
-
-    // ranks by ballot: in every wave lane j holds entry j, wave w ranks entries 4w .. 4w + 3
     const size_t o0 = (size_t)s * B;
-    const uint64_t mine = (ln < mr) ? sh.list[ln] : 0ull;
-    const uint32_t second = (ln < mr && sh.open_list[ln] != 0u) ? 1u : 0u;
-    const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
-    uint64_t key = 0;
-    uint32_t rank = 0xFFFFFFFFu, sec = 0;
+    LSH_TRACE_ANY(2, 3);
+    // Ranks by ballot: in every wave lane j holds entry j, wave w ranks entries 4w .. 4w + 3; the B best are
+    // written out.  False (uniform): one of them is a second largest (`verdict`).
+    auto rank_and_write = [&](int mr, bool verdict) {
+        const uint64_t mine = (ln < mr) ? sh.list[ln] : 0ull;
+        const uint32_t second = (verdict && ln < mr && sh.open_list[ln] != 0u) ? 1u : 0u;
+        const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
+        uint64_t key = 0;
+        uint32_t rank = 0xFFFFFFFFu, sec = 0;
 #pragma unroll
-    for (int q = 0; q < kWave / kSelWaves; ++q) {
-        const int e = wv * (kWave / kSelWaves) + q;   // (wave-uniform)
-        if (e >= mr) break;
-        const uint64_t ke = ((uint64_t)wave_read_lane(hi, e) << 32) | wave_read_lane(lo, e);
-        const uint32_t r = (uint32_t)__popcll(__ballot(mine > ke));
-        const uint32_t se = wave_read_lane(second, e);
-        if (ln == q) { key = ke; rank = r; sec = se; }
-    }
-    if (rank < (uint32_t)B) {   // (lanes 0..3 at most)
-        if (sec) sh.misc[6] = 1u;
-        const size_t o = o0 + rank;
-        const float score = key_value(key);
-        const uint32_t idx = key_index(key);
-        const bool none = score == -INFINITY || score != score;
-        out_beam[o] = none ? -1 : (int)(idx >> 24);
-        out_word[o] = none ? -1 : (int)(idx & 0xFFFFFFu);
-        out_score[o] = none ? -INFINITY : score;
-    }
-    if (wv == 0)
-        for (int e = ln + min(mr, B); e < B; e += kWave) {
-            out_beam[o0 + e] = -1; out_word[o0 + e] = -1; out_score[o0 + e] = -INFINITY;
+        for (int q = 0; q < kWave / kSelWaves; ++q) {
+            const int e = wv * (kWave / kSelWaves) + q;   // (wave-uniform)
+            if (e >= mr) break;
+            const uint64_t ke = ((uint64_t)wave_read_lane(hi, e) << 32) | wave_read_lane(lo, e);
+            const uint32_t r = (uint32_t)__popcll(__ballot(mine > ke));
+            const uint32_t se = wave_read_lane(second, e);
+            if (ln == q) { key = ke; rank = r; sec = se; }
         }
-    LSH_TRACE_ANY(2, 4);
+        if (rank < (uint32_t)B) {   // (lanes 0..3 at most)
+            if (sec) sh.misc[6] = 1u;
+            const size_t o = o0 + rank;
+            const float score = key_value(key);
+            const uint32_t idx = key_index(key);
+            const bool none = score == -INFINITY || score != score;
+            out_beam[o] = none ? -1 : (int)(idx >> 24);
+            out_word[o] = none ? -1 : (int)(idx & 0xFFFFFFu);
+            out_score[o] = none ? -INFINITY : score;
+        }
+        if (wv == 0)
+            for (int e = ln + min(mr, B); e < B; e += kWave) {
+                out_beam[o0 + e] = -1; out_word[o0 + e] = -1; out_score[o0 + e] = -INFINITY;
+            }
+        if (!verdict) return true;
+        LSH_TRACE_ANY(2, 4);
+        __syncthreads();
+        LSH_TRACE_ANY(2, 5);
+        return sh.misc[6] == 0u;
+    };
+    const int mr = (int)sh.misc[4];
+    if (mr > kWave) return false;   // (uniform; a longer list is the general path's)
+    if (rank_and_write(mr, true)) return true;
+    if constexpr (SAME_KERNEL) return false;
+    const int n2 = (int)sh.misc[5];
+    if (n2 > kWave) return false;
+    {   // entry tid / 16: column tid % 16 of its tile
+        const int e = tid >> 4, col = ln & 15;
+        const uint32_t where = sh.rank[min(e, kWave - 1)];
+        const int i = e < n2 ? (int)(where >> 20) : 0, c = e < n2 ? (int)(where & 0xFFFFFu) * open.tn + col : 0;
+        bool ok = e < n2 && col < open.tn && c < open.C;
+        const float x = open.logits[(size_t)i * open.cpitch + (ok ? c : 0)];
+        const int32_t id = open.cand ? open.cand[ok ? c : 0] : c;
+        const uint32_t key = f32_sortable(sh.bs[i] + (x - sh.lse[i]) + 0.0f);
+        ok = ok && key >= tau && (uint32_t)id != sh.hist[e & (kWave - 1)] && (uint32_t)id != sh.hist[kWave + (e & (kWave - 1))];
+        const uint64_t more = __ballot(ok);
+        if (more) {
+            uint32_t base = 0;
+            if (ln == 0) base = atomicAdd(&sh.misc[4], (uint32_t)__popcll(more));
+            const uint32_t pos = wave_read_lane(base, 0) + lanes_below(more);
+            if (ok && pos < (uint32_t)kWave)
+                sh.list[pos] = ((uint64_t)key << 32) | (uint64_t)(~(((uint32_t)i << 24) | (uint32_t)id));
+        }
+    }
     __syncthreads();
-    LSH_TRACE_ANY(2, 5);
-    return sh.misc[6] == 0u;
+    const int all = (int)sh.misc[4];
+    if (all > kWave) return false;
+    return rank_and_write(all, false);
 }
 
 template <bool SAME_KERNEL>
 __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const TileRecord* records, const int32_t* ids2,
                                                   int64_t ppitch, const int32_t* count, int C_known, int V, int B,
                                                   const float* beam_scores, float* lse_out, int32_t* out_beam,
-                                                  int32_t* out_word, float* out_score, int tile_forced, int* C_out) {
+                                                  int32_t* out_word, float* out_score, int tile_forced, int* C_out,
+                                                  const float* logits, int64_t cpitch, const int32_t* cand) {
     const int ln = lane_id(), wv = wave_id();
     LSH_TRACE_ANY(2, 0);
     // what is asked for at once, before the list's length is known: the row's beam score, its
@@ -581,10 +629,11 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
     const int tn = select_tile_width(C, tile_forced, ppitch);
     const int ntiles = (C + tn - 1) / tn;
     *C_out = C;
+    const OpenSrc open{logits + (size_t)s * B * cpitch, cpitch, cand ? cand + (size_t)s * V : nullptr, C, tn};
     if (ntiles == 0 || ntiles > kSmallQ * kWave) return false;   // (uniform, like every return here)
     if (ntiles <= 4 * kWave)
         return select_rich_small_body<SAME_KERNEL, 4>(sh, s, bsi, rec, ids2 + r0, ntiles, B, lse_out, out_beam, out_word,
-                                                      out_score);
+                                                      out_score, open);
 #pragma unroll
     for (int q = 4; q < kSmallQ; ++q) {
         rec[q] = empty_record<float4>();
@@ -592,7 +641,7 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
             rec[q] = load_record<SAME_KERNEL>(records + r0 + min((int64_t)(ln + q * kWave), ppitch - 1));
     }
     return select_rich_small_body<SAME_KERNEL, 8>(sh, s, bsi, rec, ids2 + r0, ntiles, B, lse_out, out_beam, out_word,
-                                                  out_score);
+                                                  out_score, open);
 }
 
 template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false, bool WIDE = false>
@@ -606,7 +655,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
         if (B <= kSelWaves) {
             int C_seen = C_known;
             if (select_rich_small<SAME_KERNEL>(sh, s, records, ids2, ppitch, count, C_known, V, B, beam_scores, lse_out,
-                                               out_beam, out_word, out_score, tile_forced, &C_seen))
+                                               out_beam, out_word, out_score, tile_forced, &C_seen, logits, cpitch, cand))
                 return;
             C_known = C_seen;   // (the general path need not ask again)
             __syncthreads();    // (not this shape, or a tile may hide a winner: everybody has read the verdict)

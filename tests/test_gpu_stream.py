@@ -1,0 +1,57 @@
+"""The contraction of many tiles at the edges of its units, and the selection of winners that share a tile:
+rows of one step, of a unit, of every number of parts and a bit more, odd lengths, both element types, one and
+two row groups and several of them; few and many sentences (stretches of their own and an even cut), lists of
+less than a tile up to several stretches of tiles."""
+import numpy as np
+import pytest
+
+import workloads
+from gpu_harness import GpuCase
+from test_gpu_parity import run_and_check
+
+pytestmark = pytest.mark.gpu
+
+_SHAPES = [
+    # V, d, T, (S, B) ...
+    (700, 8, 300, [(9, 3), (12, 17)]),
+    (300, 63, 7, [(20, 1), (9, 16)]),
+    (900, 129, 513, [(10, 5), (3, 40)]),
+    (2500, 255, 1100, [(9, 20), (70, 2)]),
+    (600, 516, 250, [(11, 16), (9, 33)]),
+    (500, 780, 100, [(9, 4), (10, 17)]),
+    (9000, 1000, 5000, [(9, 2), (9, 18)]),
+    (400, 1025, 90, [(10, 12), (9, 20)]),
+    (300, 1281, 130, [(9, 16)]),
+    (350, 1666, 60, [(17, 3)]),
+    (260, 2047, 40, [(9, 17)]),
+]
+
+
+def _case(V, d, T, bf16, run=1):
+    """run: words in a row that are near copies of each other."""
+    rng = np.random.default_rng(V + 3 * d)
+    E = rng.standard_normal((V, d)).astype(np.float32)
+    E = (E[np.arange(V) // run * run] + 0.05 * rng.standard_normal((V, d)).astype(np.float32)) / np.sqrt(d)
+    K = min(4, d)
+    perms = np.stack([rng.permutation(d)[:K] for _ in range(9)]).astype(np.int32)
+    E = E.astype(np.float32)
+    return rng, GpuCase(workloads.f32_to_bf16_bits(E) if bf16 else E, perms, np.arange(T, dtype=np.int32), 3)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("shape", _SHAPES, ids=lambda s: "V%d-d%d" % s[:2])
+def test_many_tiles(shape, bf16):
+    V, d, T, calls = shape
+    rng, gc = _case(V, d, T, bf16)
+    for S, B in calls:
+        H = (3.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+        run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
+
+
+@pytest.mark.parametrize("run", [2, 3, 5, 16])
+@pytest.mark.parametrize("B", [1, 2, 7, 16])
+def test_winners_that_share_a_tile(B, run):
+    rng, gc = _case(1500, 40, 400, False, run)
+    words = gc.E[rng.integers(0, 1500, 2 * B)]
+    H = (6.0 * words * np.sqrt(40.0) / np.sqrt((words * words).sum(1, keepdims=True)) / 2).astype(np.float32)
+    run_and_check(None, gc, H, np.linspace(0, -1, 2 * B).astype(np.float32), 2, B)
