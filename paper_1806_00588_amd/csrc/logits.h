@@ -170,7 +170,7 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
             const int k = (ks0 + uu * WAVES) * KSTEP + kq * VEC;
             if (CHUNKS) {
                 if (k < d) {
-                    const int at = min(k, d - VEC), drop = k - at;   // (leading elements counted before)
+                    const int at = min(k, d - VEC);
                     if (col_used) {
                         ElemTraits<ET>::load16(erow + at, ev[uu]);
                     } else {
@@ -182,9 +182,8 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
 #pragma unroll
                         for (int q = 0; q < VEC; q += 4) {
                             const Float4U h4 = *reinterpret_cast<const Float4U*>(hrow[m] + at + q);
-                            const float x[4] = {h4.x, h4.y, h4.z, h4.w};
-#pragma unroll
-                            for (int i = 0; i < 4; ++i) hv[m][uu][q + i] = q + i >= drop ? x[i] : 0.f;
+                            hv[m][uu][q] = h4.x; hv[m][uu][q + 1] = h4.y;
+                            hv[m][uu][q + 2] = h4.z; hv[m][uu][q + 3] = h4.w;
                         }
                 } else {
 #pragma unroll
@@ -202,6 +201,16 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
 #pragma unroll
                     for (int m = 0; m < MTB; ++m) hv[m][uu][q] = in ? hrow[m][k + q] : 0.f;
                 }
+            }
+        }
+        if (CHUNKS && d % VEC != 0) {   // (uniform) leading elements of a row's last chunk that were counted before
+#pragma unroll
+            for (int uu = 0; uu < UNROLL; ++uu) {
+                const int drop = (ks0 + uu * WAVES) * KSTEP + kq * VEC - (d - VEC);
+#pragma unroll
+                for (int m = 0; m < MTB; ++m)
+#pragma unroll
+                    for (int q = 0; q < VEC; ++q) hv[m][uu][q] = q >= drop ? hv[m][uu][q] : 0.f;
             }
         }
 #pragma unroll

@@ -490,7 +490,7 @@ int launch_logits_estage(const StepCtx& cx, const float* H, const lsh_step_param
 // 16-byte aligned operands, at most 256 sentences (option logits_estage = 0: the other drivers).
 bool takes_estage(const lsh_tables* t, const lsh_step_params* sp, const float* H) {
     const bool aligned = (t->d % 4 == 0) && (t->ld % 4 == 0) && ((uintptr_t)t->E % 16 == 0) && ((uintptr_t)H % 16 == 0);
-    return t->dtype == LSH_F32 && aligned && sp->B > 2 * kTileM && sp->B <= 4 * kTileM &&
+    return t->dtype == LSH_F32 && aligned && !sp->full_vocab && sp->B > 2 * kTileM && sp->B <= 4 * kTileM &&
            t->d > kEsMinD && t->d <= kEsSlices * kEsSlice && sp->S <= 256 && estage_lds_bytes(true) <= kMaxDynLds &&
            t->option(kOptLogitsEstage, 1) && !t->option(kOptLogitsWaves, 0);
 }
@@ -550,8 +550,17 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
 // even as they come in units of 16 rows, and among the splits the accumulators leave room for, the one
 // with the least work on the fullest CU is taken: rounds of 256 workgroups, a round with m row tiles costing
 // 8 (m + 1) us at d = 1000 (measured for m = 2 .. 6; m = 1: 20).
+// Where even k_logits_stream, with a tile of 16 words and one or two row groups per workgroup and k split over
+// its waves, fills the chip at most twice over, it is the faster one: the others then run few workgroups through
+// a long chain of k blocks (31 rows, V = 2009, d = 1181: 22.8 -> 10.6 us).
 constexpr int kRowsMaxMT = 6, kRowsMinD = 8;   // (a row holds at least one 16-byte chunk)
 bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an option that names another driver wins)
+    lsh_step_params all = *sp;
+    all.S = 1;
+    all.B = sp->S * sp->B;
+    const int rows = t->dtype == LSH_F32 ? stream_rows<float>(t, &all) : stream_rows<uint16_t>(t, &all);
+    const int64_t tiles = (t->V + kTileN - 1) / kTileN;
+    if (rows > 0 && tiles * ((all.B + rows - 1) / rows) <= 512) return false;
     return sp->full_vocab && t->d >= kRowsMinD && t->opt[kOptLogitsWaves] == kAuto && t->opt[kOptLogitsEstage] == kAuto &&
            t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto;
 }
