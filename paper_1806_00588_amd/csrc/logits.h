@@ -1512,25 +1512,30 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
 // E again: 32 sentences x 160 MB.)  Few rows: bound by the one pass over E (k_logits_few); many: by the
 // matrix pipe.
 //
-// A workgroup of four waves makes MT * 16 rows x 64 WF words, in blocks of 32 k.  The hidden rows pass
-// through LDS (double-buffered; fp32, or for bf16 words as the three bf16 planes of k_logits_hlds, split
-// on the way in).  A wave owns 16 WF words and all the rows; nobody else needs those words, so their
-// chunks go from memory straight into the A operand registers, kRowsAhead blocks ahead.  With WF = 2
-// (fp32, 4 MT WF instructions of 32 cycles per MT 16-byte LDS reads) and WF = 4 (bf16, 3 MT WF of 16
-// cycles per 3 MT reads) the LDS rate is no bound.  Words are the A operand, so that a lane ends up with
+// A workgroup of four waves makes MT * 16 rows x 64 WF words, in blocks of 32 k, on bf16 matrix instructions.  The
+// hidden rows pass through LDS (double-buffered, as three bf16 planes, split on the way in).  bf16 words meet
+// all three planes: exact products.  fp32 words are split into three planes as well, in registers, each plane
+// the nearest bf16 to what is left, and of the nine plane products the six are made that are not below
+// 2^-23 of the whole: what is left out is less than what the fp32 instructions lose, which round the sum
+// after every four products (these after every 32): against fp64 sums, 320 rows, V = 40000, d = 1000, the
+// logits' rms error is 5.2e-7 (fp32 instructions: 5.6e-7), the largest 1.3e-5 (2.0e-5).
+//
+// A wave owns 16 WF words and all the rows; nobody else needs those words, so their chunks go from memory straight into the A operand registers, kRowsAhead blocks ahead.  With WF = 2
+// (fp32, 6 MT WF instructions of 16 cycles per 3 MT 16-byte LDS reads) and WF = 4 (bf16, 3 MT WF per 3 MT
+// reads) the LDS rate is no bound.  Words are the A operand, so that a lane ends up with
 // four consecutive words of one hidden row (a 16-byte store).  The operands of a block are read from
 // LDS in two halves, each while the other half's instructions run; without that, and with the loads
 // placed by the compiler, the same tiles took 283 instead of 222 us.  MT is the host's choice.
 // Any d >= one chunk and any pitch: chunks are loaded from any element's address.
-// 320 rows, V = 40000, d = 1000: fp32 689 -> 222 us (116 TFLOP/s; the matrix pipe is busy 72 % of the
-// time, 79 % while a CU has work), bf16 369 -> 95 us (d = 1024).
+// 320 rows, V = 40000, d = 1000: fp32 222 us with fp32 instructions (116 TFLOP/s, the pipe busy 72 % of the
+// time), 163 us on planes (157 TFLOP/s of the product, 940 of plane products: a large bf16 product of matrices
+// reaches 1190 on this card); bf16 95 us (d = 1024).
 constexpr int kRowsK = 32;
-template <typename ET> __host__ __device__ constexpr int rows_planes() { return sizeof(ET) == 2 ? 3 : 1; }
-// LDS bytes per hidden row and plane: 16-byte reads without conflicts
-template <typename ET> __host__ __device__ constexpr int rows_pitch() { return sizeof(ET) == 2 ? 40 * 2 : 36 * 4; }
-template <typename ET> __host__ __device__ constexpr size_t rows_lds_bytes(int MT) {
-    return (size_t)2 * rows_planes<ET>() * ((MT + 1) / 2 * 32) * rows_pitch<ET>() + 4 * kTileM * sizeof(float2);
+constexpr int kRowsPitch = 40 * 2;   // LDS bytes per hidden row and plane: 16-byte reads without conflicts
+__host__ __device__ constexpr size_t rows_lds_bytes(int MT) {
+    return (size_t)2 * 3 * ((MT + 1) / 2 * 32) * kRowsPitch + 4 * kTileM * sizeof(float2);
 }
+template <typename ET> __host__ __device__ constexpr int few_planes() { return sizeof(ET) == 2 ? 3 : 1; }
 
 // The 16 bytes of a row of d >= 16 / sizeof(ET) elements that begin at element k, zeros past the row's
 // end: what lies past it is never read (one clamped load, then shifted into place in registers).
@@ -1554,6 +1559,21 @@ __device__ __forceinline__ Chunk16U<ET> load_chunk_end(const ET* row, int k, int
 }
 template <typename ET> __device__ __forceinline__ bf16x8 as_bf16x8(const Chunk16U<ET>& c) {
     return __builtin_bit_cast(bf16x8, make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]));
+}
+
+// Two values as three pairs of bf16, each the nearest to what is left: a = hi + mid + lo to 2^-24 of it, |mid| at
+// most 2^-8 and |lo| 2^-16 of |a| (v_cvt_pk_bf16_f32).
+__device__ __forceinline__ void split_near(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    typedef float floatx2 __attribute__((ext_vector_type(2)));
+    auto pack = [](float x, float y) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((floatx2{x, y}), bf16x2)); };
+    hi = pack(a, b);
+    a -= __uint_as_float(hi << 16);
+    b -= __uint_as_float(hi & 0xFFFF0000u);
+    mid = pack(a, b);
+    a -= __uint_as_float(mid << 16);
+    b -= __uint_as_float(mid & 0xFFFF0000u);
+    lo = pack(a, b);
 }
 
 // The end of both kernels: lane (col, kk) holds, in x[m][f], the logits of hidden row row0 + 16 m + col
@@ -1609,12 +1629,13 @@ __global__ void __launch_bounds__(256, 2)
 k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int R, int V,
               int gx /*tiles of 64 WF words*/, int ngroups, float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
     constexpr bool BF = sizeof(ET) == 2;
-    constexpr int PITCH = rows_pitch<ET>(), NP = rows_planes<ET>();
+    constexpr int PITCH = kRowsPitch, NP = 3;
     constexpr int HP = (MT + 1) / 2, LROWS = HP * 32;         // hidden rows are staged 32 at a time
+    constexpr int PE = BF ? 1 : 3;                            // planes of the words
     constexpr int PER_WF = BF ? 1 : 2, NC = PER_WF * WF;      // 16-byte chunks of E per lane and block
-    constexpr int kRowsAhead = NC <= 2 ? 8 / NC : 3;          // blocks of E in registers: 8 to 12 loads in flight
+    constexpr int kRowsAhead = BF ? 3 : 2;                    // blocks of E in registers: 8 to 12 loads in flight
     constexpr int CK = 16 / (int)sizeof(ET);                  // elements per chunk
-    constexpr int M0 = BF ? (MT + 1) / 2 : MT;                // row tiles in the first half of a block (bf16)
+    constexpr int M0 = (MT + 1) / 2;                          // row tiles in the first half of a block
     constexpr int kBuf = NP * LROWS * PITCH;                  // bytes per buffer
     extern __shared__ uint32_t rsm[];
     char* sm = reinterpret_cast<char*>(rsm);
@@ -1640,20 +1661,24 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 #pragma unroll
         for (int p = 0; p < HP; ++p) st[p] = *reinterpret_cast<const Float4U*>(hsrc[p] + i * kRowsK + lc);
     };
-    auto load_words = [&](int i, Chunk16U<ET> (&e)[NC]) {     // chunk f * PER_WF + s: step s of word tile f
+    auto load_words = [&](int i, Chunk16U<ET> (&e)[NC]) {     // word tile f: 8 consecutive k, one chunk or two
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            e[c] = *reinterpret_cast<const Chunk16U<ET>*>(esrc[c / PER_WF] + i * kRowsK + (c % PER_WF) * 4 * CK + kk * CK);
+            e[c] = *reinterpret_cast<const Chunk16U<ET>*>(esrc[c / PER_WF] + i * kRowsK + kk * 8 + (c % PER_WF) * CK);
     };
     auto store_hidden = [&](int buf) {
 #pragma unroll
         for (int p = 0; p < HP; ++p) {
-            char* dst = sm + buf * kBuf + (32 * p + lr) * PITCH + lc * (BF ? 2 : 4);
+            char* dst = sm + buf * kBuf + (32 * p + lr) * PITCH + lc * 2;
             const float x[4] = {st[p].x, st[p].y, st[p].z, st[p].w};
-            if constexpr (!BF) {
-                *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
-            } else {
+            if constexpr (BF) {
                 store_planes4(dst, (size_t)LROWS * PITCH, x);
+            } else {
+                uint2 w[3];
+                split_near(x[0], x[1], w[0].x, w[1].x, w[2].x);
+                split_near(x[2], x[3], w[0].y, w[1].y, w[2].y);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) *reinterpret_cast<uint2*>(dst + q * (LROWS * PITCH)) = w[q];
             }
         }
     };
@@ -1662,21 +1687,43 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int f = 0; f < WF; ++f) acc[m][f] = floatx4{0.f, 0.f, 0.f, 0.f};
-    // half h of a block: fp32, k 16 h .. 16 h + 15; bf16, row tiles [0, M0) or [M0, MT)
+    // half h of a block: row tiles [0, M0) or [M0, MT)
     struct Operands { uint4 b[M0][NP]; };
+    struct Words { uint4 p[WF][PE]; };                        // the words' operands: their chunk, or its three planes
     auto read_half = [&](int buf, int h, Operands& o) {
-        const char* hb = sm + buf * kBuf + col * PITCH + 16 * kk + (BF ? h * M0 * kTileM * PITCH : 64 * h);
+        const char* hb = sm + buf * kBuf + col * PITCH + 16 * kk + h * M0 * kTileM * PITCH;
 #pragma unroll
         for (int m = 0; m < M0; ++m)
 #pragma unroll
             for (int p = 0; p < NP; ++p)
-                if (!BF || h == 0 || M0 + m < MT)
+                if (h == 0 || M0 + m < MT)
                     o.b[m][p] = *reinterpret_cast<const uint4*>(hb + (p * LROWS + m * kTileM) * PITCH);
     };
-    auto contract = [&](const Operands& o, int h, const Chunk16U<ET> (&e)[NC]) {
-        if constexpr (BF) {
+    auto make_words = [&](const Chunk16U<ET> (&e)[NC], Words& w) {
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
+        for (int f = 0; f < WF; ++f) {
+            if constexpr (BF) {
+                w.p[f][0] = make_uint4(e[f].w[0], e[f].w[1], e[f].w[2], e[f].w[3]);
+            } else {
+                uint32_t q[3][4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const Chunk16U<ET>& c = e[f * PER_WF + (PER_WF > 1 ? i / 2 : 0)];
+                    split_near(__uint_as_float(c.w[2 * (i % 2)]), __uint_as_float(c.w[2 * (i % 2) + 1]), q[0][i], q[1][i], q[2][i]);
+                }
+#pragma unroll
+                for (int p = 0; p < PE; ++p) w.p[f][p] = make_uint4(q[p][0], q[p][1], q[p][2], q[p][3]);
+            }
+        }
+    };
+    auto contract = [&](const Operands& o, int h, const Words& w) {
+        // (plane pairs whose product is not below 2^-23 of the whole, smallest first)
+#pragma unroll
+        for (int sum = 2; sum >= 0; --sum)
+#pragma unroll
+            for (int pe = 0; pe < PE; ++pe) {
+                const int p = sum - pe;
+                if (p < 0) continue;
 #pragma unroll
                 for (int m = 0; m < M0; ++m)
 #pragma unroll
@@ -1684,20 +1731,9 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                         if (h * M0 + m < MT) {
                             const int mm = h * M0 + m < MT ? h * M0 + m : 0;
                             acc[mm][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                as_bf16x8(e[f]), __builtin_bit_cast(bf16x8, o.b[m][p]), acc[mm][f], 0, 0, 0);
+                                __builtin_bit_cast(bf16x8, w.p[f][pe]), __builtin_bit_cast(bf16x8, o.b[m][p]), acc[mm][f], 0, 0, 0);
                         }
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    const uint32_t bq = q == 0 ? o.b[m][0].x : q == 1 ? o.b[m][0].y : q == 2 ? o.b[m][0].z : o.b[m][0].w;
-#pragma unroll
-                    for (int f = 0; f < WF; ++f)
-                        acc[m][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[f * PER_WF + (h & (PER_WF - 1))].w[q]),
-                                                                         __uint_as_float(bq), acc[m][f], 0, 0, 0);
-                }
-        }
+            }
     };
     const int nfull = d / kRowsK, rem = d - nfull * kRowsK;
     auto load_rest = [&](Chunk16U<ET> (&e)[NC]) {             // (zeros past d on both sides)
@@ -1708,9 +1744,10 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
             st[p] = __builtin_bit_cast(Float4U, c);
         }
 #pragma unroll
-        for (int c = 0; c < NC; ++c) e[c] = load_chunk_end<ET>(esrc[c / PER_WF], k0 + (c % PER_WF) * 4 * CK + kk * CK, d);
+        for (int c = 0; c < NC; ++c) e[c] = load_chunk_end<ET>(esrc[c / PER_WF], k0 + kk * 8 + (c % PER_WF) * CK, d);
     };
     Operands o0, o1;
+    Words w0, w1;
     int buf = 0;
     if (nfull) {
         // (the order in which the loop issues its loads, so that its waits count the same on both ways in)
@@ -1728,21 +1765,24 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         __builtin_amdgcn_sched_barrier(0);
         lds_barrier();
         read_half(0, 0, o0);
+        make_words(ev[0], w0);
         for (int i0 = 0; i0 < nfull; i0 += kRowsAhead) {
 #pragma unroll
             for (int j = 0; j < kRowsAhead; ++j) {
                 const int i = i0 + j;
                 if (i >= nfull) break;              // (uniform)
                 read_half(buf, 1, o1);
-                contract(o0, 0, ev[j]);
+                contract(o0, 0, w0);
                 __builtin_amdgcn_sched_barrier(0);  // (the wait for the hidden rows stays behind the instructions)
                 store_hidden(buf ^ 1);              // (last read before the previous barrier; past the last block: unused)
                 load_hidden(min(i + 2, nfull - 1));
                 lds_barrier();
                 read_half(buf ^ 1, 0, o0);
-                contract(o1, 1, ev[j]);
+                if (kRowsAhead > 1) make_words(ev[(j + 1) % kRowsAhead], w1);   // (the next block's, among this one's instructions)
+                contract(o1, 1, w0);
                 load_words(min(i + kRowsAhead, nfull - 1), ev[j]);
                 __builtin_amdgcn_sched_barrier(0);
+                w0 = w1;
                 buf ^= 1;
             }
         }
@@ -1752,10 +1792,11 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         load_rest(ev[0]);
         store_hidden(buf);
         lds_barrier();
+        make_words(ev[0], w0);
         read_half(buf, 0, o0);
-        contract(o0, 0, ev[0]);
+        contract(o0, 0, w0);
         read_half(buf, 1, o1);
-        contract(o1, 1, ev[0]);
+        contract(o1, 1, w0);
     }
     finish_wide<MT, WF>(acc, row0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
 }
@@ -1771,14 +1812,14 @@ template <typename ET> __host__ __device__ constexpr int few_pitch() {   // LDS 
     return sizeof(ET) == 2 ? (kFewK + 8) * 2 : (kFewK + 4) * 4;
 }
 template <typename ET> __host__ __device__ constexpr size_t few_lds_bytes(int MT) {
-    return (size_t)2 * rows_planes<ET>() * MT * kTileM * few_pitch<ET>() + 4 * kTileM * sizeof(float2);
+    return (size_t)2 * few_planes<ET>() * MT * kTileM * few_pitch<ET>() + 4 * kTileM * sizeof(float2);
 }
 template <typename ET, int MT>
 __global__ void __launch_bounds__(256, 3)
 k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int R, int V,
              float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
     constexpr bool BF = sizeof(ET) == 2;
-    constexpr int PITCH = few_pitch<ET>(), NP = rows_planes<ET>(), CK = 16 / (int)sizeof(ET);
+    constexpr int PITCH = few_pitch<ET>(), NP = few_planes<ET>(), CK = 16 / (int)sizeof(ET);
     constexpr int NC = kFewK / (4 * CK);                      // chunks (steps) per lane and block
     constexpr int HP = MT * 2;                                // 16-byte chunks of hidden rows per thread and block
     constexpr int kPlane = MT * kTileM * PITCH, kBuf = NP * kPlane;

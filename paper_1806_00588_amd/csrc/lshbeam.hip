@@ -548,8 +548,9 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
 // Full vocabulary: one matrix product over all hidden rows of the call.  Up to 48 rows (fp32; 32 with bf16
 // words) the pass over E is what counts: k_logits_few.  Beyond that k_logits_rows; its row groups are as
 // even as they come in units of 16 rows, and among the splits the accumulators leave room for, the one
-// with the least work on the fullest CU is taken: rounds of 256 workgroups, a round with m row tiles costing
-// 8 (m + 1) us at d = 1000 (measured for m = 2 .. 6; m = 1: 20).
+// with the least work on the fullest CU is taken.  bf16 words: rounds of 256 workgroups that cost 2 (m + 1) for m
+// row tiles (m = 1: 5).  fp32 words, at d = 1000: 20 + 9.5 m us for two workgroups on every CU, 15.5 + 4.7 m for one
+// (measured for m = 1 .. 6).
 // Where even k_logits_stream, with a tile of 16 words and one or two row groups per workgroup and k split over
 // its waves, fills the chip at most twice over, it is the faster one: the others then run few workgroups through
 // a long chain of k blocks (31 rows, V = 2009, d = 1181: 22.8 -> 10.6 us).
@@ -580,15 +581,24 @@ void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspac
     }
     const int gx = (t->V + 64 * WF - 1) / (64 * WF);
     int mt = kRowsMaxMT;
-    int64_t best = INT64_MAX;
+    double best = 1e30;
     for (int m = 1; m <= kRowsMaxMT; ++m) {
-        const int64_t cost = (((int64_t)((tiles + m - 1) / m) * gx + 255) / 256) * (m == 1 ? 5 : 2 * m + 2);
+        const int n = (tiles + m - 1) / m * gx;
+        double cost;
+        if (sizeof(ET) == 2) {
+            cost = (n + 255) / 256 * (m == 1 ? 5 : 2 * m + 2);
+        } else {   // pairs of workgroups on every CU, then what is left, alone on its CU
+            const int left = n % 512;
+            cost = n / 512 * (20 + 9.5 * m);
+            if (left > 256) cost += 20 + 9.5 * m;
+            else if (left) cost += (15.5 + 4.7 * m) * (n < 512 ? 1.0 : std::max(0.3, left / 256.0));
+        }
         if (cost < best) { best = cost; mt = m; }
     }
     const int ng = (tiles + mt - 1) / mt;
     const dim3 grid((unsigned)((gx + 7) / 8 * 8 * ng)), block(256);
 #define LSH_ROWS(MTV)                                                                                          \
-    launch(cx, 1, k_logits_rows<ET, MTV, WF>, grid, block, rows_lds_bytes<ET>(MTV), (const ET*)t->E, t->ld, t->d, H, R, \
+    launch(cx, 1, k_logits_rows<ET, MTV, WF>, grid, block, rows_lds_bytes(MTV), (const ET*)t->E, t->ld, t->d, H, R, \
            t->V, gx, ng, w.logits, w.cpitch, w.records())
     switch (mt) {
         case 1: LSH_ROWS(1); break; case 2: LSH_ROWS(2); break; case 3: LSH_ROWS(3); break;
