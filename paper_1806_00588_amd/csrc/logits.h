@@ -59,6 +59,45 @@ template <> struct ElemTraits<uint16_t> {
     }
 };
 
+// One logit by its definition: products in the order of k, summed in fp32 by one lane (any d, any alignment).
+template <typename ET>
+__device__ __forceinline__ float plain_dot(const ET* e, const float* h, int d) {
+    constexpr int VEC = ElemTraits<ET>::VEC;
+    float sum = 0.f;
+    int k = 0;
+    for (; k + VEC <= d; k += VEC) {
+        float x[VEC];
+        ElemTraits<ET>::load16(e + k, x);
+#pragma unroll
+        for (int q = 0; q < VEC; ++q) sum = fmaf(x[q], h[k + q], sum);
+    }
+    for (; k < d; ++k) sum = fmaf(elem_f32(e + k), h[k], sum);
+    return sum;
+}
+
+// Logits made of bf16 planes, or of rows whose last elements met zeros, are right wherever they are finite.  An
+// infinite element meets zero planes and makes NaN, one within 2^119 of the end of the fp32 range rounds to an
+// infinite plane: any such value, of either side, leaves an infinity or a NaN in every sum it enters.  Those are
+// made again here, by redo(i) = plain_dot of logit i (per lane; addresses must be valid on lanes without a logit
+// too).  Costs a fused multiply-add per logit and one test; a logit that is redone costs its wave about 20 us.
+template <int N, typename Redo>
+__device__ __forceinline__ void settle_non_finite(float (&x)[N], Redo&& redo) {
+    float t = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) t = fmaf(x[i], 0.f, t);   // (0 or NaN)
+    if (__ballot(t != t) == 0ull) return;
+#pragma unroll 1
+    for (int i = 0; i < N; ++i) {
+        float v = x[0];
+#pragma unroll
+        for (int j = 1; j < N; ++j) v = i == j ? x[j] : v;   // (a variable index would put x in memory)
+        if (__ballot(!(fabsf(v) < INFINITY)) == 0ull) continue;
+        if (!(fabsf(v) < INFINITY)) v = redo(i);
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = i == j ? v : x[j];
+    }
+}
+
 // Per (hidden row, tile) record of the fused kernels (the other kernels store the first two fields
 // only, as a float2 array in the same place): x = largest logit of the tile's candidates,
 // y = sum exp(logit - x), z = second largest logit (-inf if the tile has one candidate), w = word id
@@ -1578,14 +1617,26 @@ __device__ __forceinline__ void split_near(float a, float b, uint32_t& hi, uint3
 
 // The end of both kernels: lane (col, kk) holds, in x[m][f], the logits of hidden row row0 + 16 m + col
 // and the words word0 + 16 f + 4 kk + (0..3).  Stores them and a record (max, sum exp) per row and 64
-// words, which are one, two or four waves' (WF = 4, 2, 1); part: LDS for 4 x 16 pairs.  Called by all
-// four waves.
-template <int MT, int WF>
-__device__ __forceinline__ void finish_wide(const floatx4 (&x)[MT][WF], int row0, int word0, int R, int V,
+// words, which are one, two or four waves' (WF = 4, 2, 1); part: LDS for 4 x 16 pairs.  PLANES: the logits come
+// from bf16 planes (settle_non_finite).  Called by all four waves.
+template <bool PLANES, typename ET, int MT, int WF>
+__device__ __forceinline__ void finish_wide(floatx4 (&x)[MT][WF], const ET* __restrict__ E, int64_t ld, int d,
+                                            const float* __restrict__ H, int row0, int word0, int R, int V,
                                             float* __restrict__ logits, int64_t cpitch, TileRecords recs, float2* part) {
     static_assert(WF == 4 || WF == 2 || WF == 1, "64 words are one, two or four waves'");
     const int ln = lane_id(), wv = wave_id(), col = ln & 15, kk = ln >> 4;
     const int w0 = word0 + 4 * kk;
+    if constexpr (PLANES) {
+        float v[MT * WF * 4];
+#pragma unroll
+        for (int i = 0; i < MT * WF * 4; ++i) v[i] = x[i / (4 * WF)][i / 4 % WF][i % 4];
+        settle_non_finite(v, [&](int i) {
+            const int row = min(row0 + i / (4 * WF) * kTileM + col, R - 1), w = min(w0 + 16 * (i / 4 % WF) + i % 4, V - 1);
+            return plain_dot(E + (int64_t)w * ld, H + (size_t)row * d, d);
+        });
+#pragma unroll
+        for (int i = 0; i < MT * WF * 4; ++i) x[i / (4 * WF)][i / 4 % WF][i % 4] = v[i];
+    }
 #pragma unroll
     for (int m = 0; m < MT; ++m) {
         const int row = row0 + m * kTileM + col;
@@ -1798,7 +1849,7 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         read_half(buf, 1, o1);
         contract(o1, 1, w0);
     }
-    finish_wide<MT, WF>(acc, row0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
+    finish_wide<true>(acc, E, ld, d, H, row0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
 }
 
 // The same for a few hidden rows (MT * 16, at most 48): bound by the pass over E.  A wave owns 16 words; what
@@ -1903,7 +1954,7 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
         turn(i, e0, e1);
         if (i + 1 < nblk) turn(i + 1, e1, e0);
     }
-    finish_wide<MT, 1>(acc, 0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
+    finish_wide<BF>(acc, E, ld, d, H, 0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
 }
 
 }  // namespace lshbeam

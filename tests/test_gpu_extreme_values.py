@@ -1,0 +1,72 @@
+"""Embeddings that mask a word (the type's lowest value, -inf) and hidden values at the end of the fp32 range,
+through every contraction driver: the masked words get a hugely negative or -inf log-probability, every other
+result stays what the oracle says.  The hidden values that meet a masked element are 1 and 0.5, whose lower
+bf16 planes are zero; the elements lie at both ends of the row and in its middle."""
+import numpy as np
+import pytest
+
+import workloads
+from gpu_harness import GpuCase, assert_close_logprobs, assert_topb_matches
+
+pytestmark = pytest.mark.gpu
+
+# driver: S, B, V, full vocabulary, options, hidden sizes, element types
+_HIDDEN = (200, 203)                     # whole 16-byte chunks that fill no step or unit; a partial chunk
+_BOTH = ("fp32", "bf16")
+_DRIVERS = {
+    "rows": (4, 20, 9000, True, {}, _HIDDEN, _BOTH),
+    "few": (1, 12, 9000, True, {}, _HIDDEN, _BOTH),
+}
+_CASES = [(n, d, ty) for n, (_, _, _, _, _, ds, tys) in _DRIVERS.items() for d in ds for ty in tys]
+
+
+def _inputs(name, d, ty):
+    S, B, V, full, options, _, _ = _DRIVERS[name]
+    rng = np.random.default_rng(d + len(name))
+    E = (rng.standard_normal((V, d)) / np.sqrt(d)).astype(np.float32)
+    H = (4.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+    return rng, S, B, V, full, options, E, H
+
+
+def _check(rng, S, B, V, full, options, E, H, ty):
+    """Log-probabilities and winners of every sentence; returns how many words had none."""
+    perms = np.stack([rng.permutation(E.shape[1])[:4] for _ in range(9)]).astype(np.int32)
+    gc = GpuCase(workloads.f32_to_bf16_bits(E) if ty == "bf16" else E, perms, np.arange(min(V, 600), dtype=np.int32), 3)
+    gc.tables.set_options(**options)
+    bs = rng.standard_normal(S * B).astype(np.float32)
+    gb, gw, gs, sp, ws = gc.step(H, bs, S, B, full_vocab=full)
+    masked = 0
+    for s in range(S):
+        rows = slice(s * B, (s + 1) * B)
+        with np.errstate(invalid="ignore"):
+            ref = gc.oracle_sentence(H[rows], bs[rows], B, full_vocab=full)
+        lp = gc.tables.debug_logprobs(ws, sp, s, cap=len(ref.cand))
+        out = ref.lp < -1e30             # a masked word: as unlikely as the oracle says, if fp32 can say it
+        assert np.all(lp[out] < -1e30) and np.all(np.isneginf(lp[np.isneginf(ref.lp)]))
+        masked += int(out.sum())
+        ref = ref._replace(lp=np.where(out, -1e30, ref.lp), logits=np.where(out, -1e30, ref.logits))
+        assert_close_logprobs(np.where(out, np.float32(-1e30), lp), ref)
+        assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
+    return masked
+
+
+@pytest.mark.parametrize("value", ["lowest", "-inf"])
+@pytest.mark.parametrize("case", _CASES, ids=lambda c: "%s-%d-%s" % c)
+def test_masked_words(case, value):
+    rng, S, B, V, full, options, E, H = _inputs(*case)
+    d, ty = case[1:]
+    low = -np.inf if value == "-inf" else np.float32(-3.3895314e38) if ty == "bf16" else np.finfo(np.float32).min
+    for word, k in ((3, 0), (17, d // 2), (40, d - 2), (599, d - 1)):
+        H[:, k] = 1.0
+        H[::3, k] = 0.5
+        E[word, k] = low
+    assert _check(rng, S, B, V, full, options, E, H, ty) == 4 * S * B
+
+
+@pytest.mark.parametrize("case", _CASES, ids=lambda c: "%s-%d-%s" % c)
+def test_largest_hidden_values(case):
+    rng, S, B, V, full, options, E, H = _inputs(*case)
+    E[:, 5] = 0.0                        # the values meet nothing but zeros
+    E[17, 5] = 2.0 ** -120
+    H[0, 5], H[S * B - 1, 5] = np.finfo(np.float32).max, np.finfo(np.float32).min
+    assert _check(rng, S, B, V, full, options, E, H, case[2]) == 0
