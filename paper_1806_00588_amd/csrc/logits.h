@@ -909,10 +909,12 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         const int C = count ? count[s] : V;
         const int cidx = min(nt * kTileN + col, C - 1);
         const int64_t j = cand ? cand[(size_t)s * V + cidx] : cidx;
-        // (the split-k tile code reads fp32 rows: from global memory when LDS holds bf16 planes)
+        // (the split-k tile code reads fp32 rows as they are in memory: from there when LDS holds bf16 planes, or rows
+        // that end in a partial chunk, which `stage` has moved)
+        const bool as_is = !PLANES && d % VEC == 0;
         logits_tile_all_rows<ET, WAVES, (UNROLL < 4 ? UNROLL : 4), true, MT>(
             E, ld, d, H, B, s, nt, C, j, logits, cpitch, recs, red,
-            PLANES ? nullptr : hl, PLANES ? 0 : pitch, row0, row0 + Bg);
+            as_is ? hl : nullptr, as_is ? pitch : 0, row0, row0 + Bg);
     }
 }
 

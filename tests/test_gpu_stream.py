@@ -55,3 +55,14 @@ def test_winners_that_share_a_tile(B, run):
     words = gc.E[rng.integers(0, 1500, 2 * B)]
     H = (6.0 * words * np.sqrt(40.0) / np.sqrt((words * words).sum(1, keepdims=True)) / 2).astype(np.float32)
     run_and_check(None, gc, H, np.linspace(0, -1, 2 * B).astype(np.float32), 2, B)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("d", [2050, 2052, 2056])
+def test_longer_rows_end_in_a_split_round(d, bf16):
+    """Rows too long for k_logits_stream, that end in a partial chunk of 16 bytes (or not): few tiles, all of them in
+    the last round, which splits k."""
+    rng, gc = _case(300, d, 60, bf16)
+    for S, B in [(9, 3), (9, 17)]:
+        H = (3.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+        run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
