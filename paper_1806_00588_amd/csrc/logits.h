@@ -885,13 +885,21 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                 }
             }
             LSH_TRACE(1, 3);
+            float out[MT * 4];
+#pragma unroll
+            for (int i = 0; i < MT * 4; ++i) out[i] = acc[i / 4][i % 4];
+            settle_non_finite(out, [&](int i) {
+                int quad = 4 * kq;
+                asm volatile("" : "+v"(quad));   // (no address of this is worked out in advance)
+                return plain_dot(erow, H + ((size_t)s * B + row0 + min(i / 4 * kTileM + quad + i % 4, Bg - 1)) * d, d);
+            });
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int row = row0 + mt * kTileM + 4 * kq + r, c = n0 + col;
                     const bool valid = row < row0 + Bg && c < C;
-                    const float x = acc[mt][r];
+                    const float x = out[4 * mt + r];
                     if (valid) logits[((size_t)s * B + row) * cpitch + c] = x;
                     tile_record_store<false, false>(recs, ((size_t)s * B + row) * recs.pitch + nt, row < row0 + Bg, valid,
                                              x, col, (int32_t)j);
@@ -1128,6 +1136,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         if (units > 1) fill(1);
         float out[TS][MT];
         int out_t0 = -1;                                                      // first tile of `out`
+        uint32_t again = 0;                                                   // tiles in which this wave has logits to settle
+        static_assert(kStreamTiles <= 32, "a bit per tile");
         // thread (i, col) has row 16 m + i, column col of every tile: 16 lanes per row (waves without rows: nothing)
         float* lrow = logits + ((size_t)s * B + row0 + (tid >> 4)) * cpitch + col;
         float2* rrow = reinterpret_cast<float2*>(recs.rec) + ((size_t)s * B + row0 + (tid >> 4)) * recs.pitch;
@@ -1143,6 +1153,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                     if (valid) lrow[(size_t)(m * kTileM) * cpitch + nt * kTileN] = out[t][m];
                     const float mx = row16_max(valid ? out[t][m] : -INFINITY);
                     const float se = row16_sum(valid ? expf(out[t][m] - mx) : 0.f);
+                    // (a NaN or +inf among the logits.  -inf is right: a value's planes, each cut off, agree in sign)
+                    if (__ballot(se != se) != 0ull) again |= 1u << (out_t0 + t);
                     if (col == 0 && row_ok) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
                 }
             }
@@ -1230,6 +1242,25 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             lds_barrier();
         }
         store_out();
+        // as settle_non_finite, with the logits each thread has stored
+        for (; again; again &= again - 1u) {
+            int me = tid;
+            asm volatile("" : "+v"(me));   // (nothing of this is worked out in advance: the loop above has no register left)
+            const int t = __ffs(again) - 1, nt = tile_of(t), c = nt * kTileN + (me & 15);
+#pragma unroll 1
+            for (int r = me >> 4; (r & ~3) < Bg; r += kTileM) {               // (uniform: four rows per wave)
+                const bool valid = r < Bg && c < C;
+                float* at = logits + ((size_t)s * B + row0 + r) * cpitch + c;
+                float x = valid ? *at : -INFINITY;
+                if (valid && !(fabsf(x) < INFINITY)) {
+                    const int32_t id = cand ? cand[(size_t)s * V + c] : c;
+                    *at = x = plain_dot(E + (int64_t)id * ld, hb + (size_t)r * d, d);
+                }
+                const float mx = row16_max(x);
+                const float se = row16_sum(valid ? expf(x - mx) : 0.f);
+                if ((me & 15) == 0 && r < Bg) reinterpret_cast<float2*>(recs.rec)[((size_t)s * B + row0 + r) * recs.pitch + nt] = make_float2(mx, se);
+            }
+        }
         seg = seg_end;
         if (seg < wg_end) __syncthreads();                                    // (the table of rows is read no more)
     }

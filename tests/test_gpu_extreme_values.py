@@ -16,6 +16,12 @@ _BOTH = ("fp32", "bf16")
 _DRIVERS = {
     "rows": (4, 20, 9000, True, {}, _HIDDEN, _BOTH),
     "few": (1, 12, 9000, True, {}, _HIDDEN, _BOTH),
+    "stream": (9, 5, 1200, False, {}, (24, 200, 203), _BOTH),
+    "stream, two row groups": (9, 20, 1200, False, {}, (200, 203), _BOTH),
+    "stream, four parts": (9, 3, 1200, False, {}, (1540,), ("bf16",)),
+    "stream, all words": (2, 5, 700, True, {}, (203,), _BOTH),
+    "hidden rows in LDS": (9, 5, 1200, False, {"logits_hlds": 1}, (200, 203), _BOTH),
+    "hidden rows in LDS, two row groups": (9, 20, 1200, False, {"logits_hlds": 1}, (200, 203), _BOTH),
 }
 _CASES = [(n, d, ty) for n, (_, _, _, _, _, ds, tys) in _DRIVERS.items() for d in ds for ty in tys]
 
