@@ -247,9 +247,11 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
             for (int uu = 0; uu < UNROLL; ++uu) {
                 const int drop = (ks0 + uu * WAVES) * KSTEP + kq * VEC - (d - VEC);
 #pragma unroll
-                for (int m = 0; m < MTB; ++m)
+                for (int q = 0; q < VEC; ++q) {   // (on both sides: either may hold an infinity)
+                    ev[uu][q] = q >= drop ? ev[uu][q] : 0.f;
 #pragma unroll
-                    for (int q = 0; q < VEC; ++q) hv[m][uu][q] = q >= drop ? hv[m][uu][q] : 0.f;
+                    for (int m = 0; m < MTB; ++m) hv[m][uu][q] = q >= drop ? hv[m][uu][q] : 0.f;
+                }
             }
         }
 #pragma unroll
@@ -483,6 +485,8 @@ k_logits_wave(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
                     if (k < d) {
                         const int at = min(k, d - VEC), drop = k - at;
                         ElemTraits<ET>::load16(erow + at, ev[uu]);
+#pragma unroll
+                        for (int q = 0; q < VEC; ++q) ev[uu][q] = q >= drop ? ev[uu][q] : 0.f;   // (on both sides: either may hold an infinity)
 #pragma unroll
                         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll

@@ -20,6 +20,12 @@ _DRIVERS = {
     "stream, two row groups": (9, 20, 1200, False, {}, (200, 203), _BOTH),
     "stream, four parts": (9, 3, 1200, False, {}, (1540,), ("bf16",)),
     "stream, all words": (2, 5, 700, True, {}, (203,), _BOTH),
+    "fused": (1, 5, 1200, False, {}, (200, 201, 203), _BOTH),
+    "fused, t = 1 and parts": (1, 20, 1200, False, {"part_rows": 7}, (203,), _BOTH),
+    "hidden rows in memory": (9, 20, 1200, False, {"logits_hlds": 0}, (200, 203), _BOTH),
+    "k over 16 waves": (2, 5, 1200, False, {"fused": 0}, (203,), _BOTH),
+    "k over 4 waves": (1, 70, 1200, False, {"logits_waves": 4}, (203,), _BOTH),
+    "candidate rows in LDS": (2, 40, 1200, False, {}, (516, 1000), ("fp32",)),
     "hidden rows in LDS": (9, 5, 1200, False, {"logits_hlds": 1}, (200, 203), _BOTH),
     "hidden rows in LDS, two row groups": (9, 20, 1200, False, {"logits_hlds": 1}, (200, 203), _BOTH),
 }
