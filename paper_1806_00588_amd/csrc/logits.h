@@ -32,6 +32,8 @@
 //   k_logits_few, k_logits_rows   the full vocabulary: all hidden rows of the call against all words;
 //   fused.h          the same tiles inside the kernels that also produce the candidate list.
 #pragma once
+#include <cfloat>
+
 #include "candidates.h"
 #include "device_utils.h"
 
@@ -98,6 +100,10 @@ __device__ __forceinline__ void settle_non_finite(float (&x)[N], Redo&& redo) {
     }
 }
 
+// exp(x - mx) for a logit and the largest of its record.  A record whose logits are all -inf has (-inf, 0): the
+// difference to the lowest finite value is -inf too, that to -inf would be NaN, and the row's log-sum-exp with it.
+__device__ __forceinline__ float exp_below(float x, float mx) { return expf(x - fmaxf(mx, -FLT_MAX)); }
+
 // Per (hidden row, tile) record of the fused kernels (the other kernels store the first two fields
 // only, as a float2 array in the same place): x = largest logit of the tile's candidates,
 // y = sum exp(logit - x), z = second largest logit (-inf if the tile has one candidate), w = word id
@@ -139,7 +145,7 @@ template <bool SHARE, bool RICH>
 __device__ __forceinline__ void tile_record_store(const TileRecords& recs, size_t at, bool row_ok, bool valid,
                                                   float x, int jc, int32_t id) {
     const float mx = row16_max(valid ? x : -INFINITY);
-    const float se = row16_sum(valid ? expf(x - mx) : 0.f);
+    const float se = row16_sum(valid ? exp_below(x, mx) : 0.f);
     if constexpr (!RICH) {
         if (jc == 0 && row_ok) reinterpret_cast<float2*>(recs.rec)[at] = make_float2(mx, se);
     } else {
@@ -1156,7 +1162,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                     const bool row_ok = (tid >> 4) + m * kTileM < Bg, valid = row_ok && nt * kTileN + col < C;
                     if (valid) lrow[(size_t)(m * kTileM) * cpitch + nt * kTileN] = out[t][m];
                     const float mx = row16_max(valid ? out[t][m] : -INFINITY);
-                    const float se = row16_sum(valid ? expf(out[t][m] - mx) : 0.f);
+                    const float se = row16_sum(valid ? exp_below(out[t][m], mx) : 0.f);
                     // (a NaN or +inf among the logits.  -inf is right: a value's planes, each cut off, agree in sign)
                     if (__ballot(se != se) != 0ull) again |= 1u << (out_t0 + t);
                     if (col == 0 && row_ok) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
@@ -1261,7 +1267,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                     *at = x = plain_dot(E + (int64_t)id * ld, hb + (size_t)r * d, d);
                 }
                 const float mx = row16_max(x);
-                const float se = row16_sum(valid ? expf(x - mx) : 0.f);
+                const float se = row16_sum(valid ? exp_below(x, mx) : 0.f);
                 if ((me & 15) == 0 && r < Bg) reinterpret_cast<float2*>(recs.rec)[((size_t)s * B + row0 + r) * recs.pitch + nt] = make_float2(mx, se);
             }
         }
@@ -1564,13 +1570,13 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
             const bool valid = row < B && c < C;
             if (valid) logits[((size_t)s * B + row) * cpitch + c] = x;
             const float mx = row16_max(valid ? x : -INFINITY);
-            const float se = row16_sum(valid ? expf(x - mx) : 0.f);
+            const float se = row16_sum(valid ? exp_below(x, mx) : 0.f);
             if (col == 0) {
                 // (one fast exponential, no branch: 16 waves share the CU's issue slots, and every
                 // instruction here is paid once per tile by each of them)
                 float2 acc2 = run[g * kTileM + 4 * kk + q];
                 const float hi = fmaxf(acc2.x, mx);
-                const float e = __expf(fminf(acc2.x, mx) - hi);      // exp(-|difference|); 0 for the first tile
+                const float e = __expf(fminf(acc2.x, mx) - fmaxf(hi, -FLT_MAX));   // exp(-|difference|); 0 for the first tile
                 acc2.y = (mx > acc2.x) ? fmaf(acc2.y, e, se) : fmaf(se, e, acc2.y);
                 acc2.x = hi;
                 const bool group_end = kt % kGroupTiles == kGroupTiles - 1 || !more;
@@ -1692,7 +1698,7 @@ __device__ __forceinline__ void finish_wide(floatx4 (&x)[MT][WF], const ET* __re
 #pragma unroll
         for (int f = 0; f < WF; ++f)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) se += w0 + 16 * f + r < V ? expf(x[m][f][r] - mx) : 0.f;
+            for (int r = 0; r < 4; ++r) se += w0 + 16 * f + r < V ? exp_below(x[m][f][r], mx) : 0.f;
         se += __shfl_xor(se, 16);
         se += __shfl_xor(se, 32);
         float2 a = make_float2(mx, se);
@@ -1703,7 +1709,7 @@ __device__ __forceinline__ void finish_wide(floatx4 (&x)[MT][WF], const ET* __re
             for (int o = 1; o < 4 / WF; ++o) {
                 const float2 q = part[((wv + o) & 3) * kTileM + col];   // (a wave past V: -inf, 0)
                 const float hi = fmaxf(a.x, q.x);
-                a = make_float2(hi, a.y * expf(a.x - hi) + q.y * expf(q.x - hi));
+                a = make_float2(hi, a.y * exp_below(a.x, hi) + q.y * exp_below(q.x, hi));
             }
             lds_barrier();
         }

@@ -82,3 +82,12 @@ def test_largest_hidden_values(case):
     E[17, 5] = 2.0 ** -120
     H[0, 5], H[S * B - 1, 5] = np.finfo(np.float32).max, np.finfo(np.float32).min
     assert _check(rng, S, B, V, full, options, E, H, case[2]) == 0
+
+
+@pytest.mark.parametrize("case", _CASES, ids=lambda c: "%s-%d-%s" % c)
+def test_tiles_and_records_without_a_word(case):
+    """A hundred words in a row masked: whole tiles of 16 and whole records of 64 with nothing but -inf."""
+    rng, S, B, V, full, options, E, H = _inputs(*case)
+    H[:, 5] = 1.0
+    E[60:160, 5] = -np.inf
+    assert _check(rng, S, B, V, full, options, E, H, case[2]) == 100 * S * B
