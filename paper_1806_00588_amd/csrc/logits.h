@@ -87,7 +87,7 @@ __device__ __forceinline__ void settle_non_finite(float (&x)[N], Redo&& redo) {
     float t = 0.f;
 #pragma unroll
     for (int i = 0; i < N; ++i) t = fmaf(x[i], 0.f, t);   // (0 or NaN)
-    if (__ballot(t != t) == 0ull) return;
+    if (__builtin_expect(__ballot(t != t) == 0ull, 1)) return;
 #pragma unroll 1
     for (int i = 0; i < N; ++i) {
         float v = x[0];
@@ -1253,7 +1253,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         }
         store_out();
         // as settle_non_finite, with the logits each thread has stored
-        for (; again; again &= again - 1u) {
+        // (out of line: in line it cost a step of 8 sentences x 5 beams in bf16 1 %, 27.1 us; 26.8 without it and so)
+        for (; __builtin_expect(again != 0u, 0); again &= again - 1u) {
             int me = tid;
             asm volatile("" : "+v"(me));   // (nothing of this is worked out in advance: the loop above has no register left)
             const int t = __ffs(again) - 1, nt = tile_of(t), c = nt * kTileN + (me & 15);
