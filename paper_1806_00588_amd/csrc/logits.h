@@ -1598,21 +1598,30 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
 // A workgroup of four waves makes MT * 16 rows x 64 WF words, in blocks of 32 k, on bf16 matrix instructions.  The
 // hidden rows pass through LDS (double-buffered, as three bf16 planes, split on the way in).  bf16 words meet
 // all three planes: exact products.  fp32 words are split into three planes as well, in registers, each plane
-// the nearest bf16 to what is left, and of the nine plane products the six are made that are not below
-// 2^-23 of the whole: what is left out is less than what the fp32 instructions lose, which round the sum
-// after every four products (these after every 32): against fp64 sums, 320 rows, V = 40000, d = 1000, the
-// logits' rms error is 5.2e-7 (fp32 instructions: 5.6e-7), the largest 1.3e-5 (2.0e-5).
+// the nearest bf16 to what is left, and eight of the nine plane products are made; the ninth is at most 2^-34 of the
+// whole.  The products of two first planes have an accumulator of their own: these instructions cut off what an addend
+// has below the accumulator's last place, and all the smaller products lost their ends there, every 32 k.
+// rms of the error over the sum of the products' sizes, n of d = 1000 products not zero, against fp64 sums:
+//                                        n = 1      8        32      1000
+//   fp32 instructions                  2.53e-8  2.73e-8  2.78e-8  2.81e-8
+//   fp32 words, 8 products             2.53e-8  1.44e-8  1.16e-8  0.91e-8
+//     in one accumulator               3.40e-8  5.39e-8  5.52e-8  2.38e-8
+//     6 products (those from 2^-23 on) 2.60e-8  1.47e-8  1.17e-8  0.91e-8
+//   bf16 words                         2.52e-8  1.44e-8  1.16e-8  0.91e-8
+//     in one accumulator               3.35e-8  3.77e-8  3.75e-8  1.65e-8
+// Six products are 10 % faster (below) and leave out up to 2^-24 of a product, as much as rounding it once: a sum of
+// one product was off by up to 1.0e-7 instead of 6.0e-8.
 //
 // A wave owns 16 WF words and all the rows; nobody else needs those words, so their chunks go from memory straight into the A operand registers, kRowsAhead blocks ahead.  With WF = 2
-// (fp32, 6 MT WF instructions of 16 cycles per 3 MT 16-byte LDS reads) and WF = 4 (bf16, 3 MT WF per 3 MT
+// (fp32, 8 MT WF instructions of 16 cycles per 3 MT 16-byte LDS reads) and WF = 4 (bf16, 3 MT WF per 3 MT
 // reads) the LDS rate is no bound.  Words are the A operand, so that a lane ends up with
 // four consecutive words of one hidden row (a 16-byte store).  The operands of a block are read from
 // LDS in two halves, each while the other half's instructions run; without that, and with the loads
 // placed by the compiler, the same tiles took 283 instead of 222 us.  MT is the host's choice.
 // Any d >= one chunk and any pitch: chunks are loaded from any element's address.
 // 320 rows, V = 40000, d = 1000: fp32 222 us with fp32 instructions (116 TFLOP/s, the pipe busy 72 % of the
-// time), 163 us on planes (157 TFLOP/s of the product, 940 of plane products: a large bf16 product of matrices
-// reaches 1190 on this card); bf16 95 us (d = 1024).
+// time), 177 us on planes (145 TFLOP/s of the product, 1160 of plane products: a large bf16 product of matrices
+// reaches 1190 on this card), 157 us with six products in one accumulator; bf16 (d = 1024) 87 us, 86 us in one.
 constexpr int kRowsK = 32;
 constexpr int kRowsPitch = 40 * 2;   // LDS bytes per hidden row and plane: 16-byte reads without conflicts
 __host__ __device__ constexpr size_t rows_lds_bytes(int MT) {
@@ -1644,8 +1653,10 @@ template <typename ET> __device__ __forceinline__ bf16x8 as_bf16x8(const Chunk16
     return __builtin_bit_cast(bf16x8, make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]));
 }
 
-// Two values as three pairs of bf16, each the nearest to what is left: a = hi + mid + lo to 2^-24 of it, |mid| at
-// most 2^-8 and |lo| 2^-16 of |a| (v_cvt_pk_bf16_f32).
+// Two values as three pairs of bf16, each the nearest to what is left (v_cvt_pk_bf16_f32): a = hi + mid + lo exactly,
+// |mid| at most 2^-8 and |lo| 2^-17 of |a|'s power of two.  (Not where the nearest bf16 is infinite, which
+// settle_non_finite mends; and a plane ends at 2^-133, so that values below 2^-110 lose bits: that shows in a logit
+// only where the other side holds values beyond 2^100.)
 __device__ __forceinline__ void split_near(float a, float b, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     typedef float floatx2 __attribute__((ext_vector_type(2)));
@@ -1728,7 +1739,7 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
     constexpr int HP = (MT + 1) / 2, LROWS = HP * 32;         // hidden rows are staged 32 at a time
     constexpr int PE = BF ? 1 : 3;                            // planes of the words
     constexpr int PER_WF = BF ? 1 : 2, NC = PER_WF * WF;      // 16-byte chunks of E per lane and block
-    constexpr int kRowsAhead = BF ? 3 : 2;                    // blocks of E in registers: 8 to 12 loads in flight
+    constexpr int kRowsAhead = 2;                             // blocks of E in registers: 8 loads in flight
     constexpr int CK = 16 / (int)sizeof(ET);                  // elements per chunk
     constexpr int M0 = (MT + 1) / 2;                          // row tiles in the first half of a block
     constexpr int kBuf = NP * LROWS * PITCH;                  // bytes per buffer
@@ -1777,11 +1788,11 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
             }
         }
     };
-    floatx4 acc[MT][WF];
+    floatx4 acc[MT][WF], low[MT][WF];                         // products of two first planes; all others
 #pragma unroll
     for (int m = 0; m < MT; ++m)
 #pragma unroll
-        for (int f = 0; f < WF; ++f) acc[m][f] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int f = 0; f < WF; ++f) acc[m][f] = low[m][f] = floatx4{0.f, 0.f, 0.f, 0.f};
     // half h of a block: row tiles [0, M0) or [M0, MT)
     struct Operands { uint4 b[M0][NP]; };
     struct Words { uint4 p[WF][PE]; };                        // the words' operands: their chunk, or its three planes
@@ -1812,21 +1823,22 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         }
     };
     auto contract = [&](const Operands& o, int h, const Words& w) {
-        // (plane pairs whose product is not below 2^-23 of the whole, smallest first)
+        // (smallest products first; the third planes' own, at most 2^-34 of the whole, is left out)
 #pragma unroll
-        for (int sum = 2; sum >= 0; --sum)
+        for (int sum = PE == 1 ? 2 : 3; sum >= 0; --sum)
 #pragma unroll
             for (int pe = 0; pe < PE; ++pe) {
                 const int p = sum - pe;
-                if (p < 0) continue;
+                if (p < 0 || p >= NP) continue;
 #pragma unroll
                 for (int m = 0; m < M0; ++m)
 #pragma unroll
                     for (int f = 0; f < WF; ++f)
                         if (h * M0 + m < MT) {
                             const int mm = h * M0 + m < MT ? h * M0 + m : 0;
-                            acc[mm][f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                                __builtin_bit_cast(bf16x8, w.p[f][pe]), __builtin_bit_cast(bf16x8, o.b[m][p]), acc[mm][f], 0, 0, 0);
+                            floatx4& to = sum ? low[mm][f] : acc[mm][f];
+                            to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                __builtin_bit_cast(bf16x8, w.p[f][pe]), __builtin_bit_cast(bf16x8, o.b[m][p]), to, 0, 0, 0);
                         }
             }
     };
@@ -1893,6 +1905,10 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
         read_half(buf, 1, o1);
         contract(o1, 1, w0);
     }
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int f = 0; f < WF; ++f) acc[m][f] += low[m][f];
     finish_wide<true>(acc, E, ld, d, H, row0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
 }
 
@@ -1954,9 +1970,9 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
             else *reinterpret_cast<float4*>(dst) = make_float4(x[0], x[1], x[2], x[3]);
         }
     };
-    floatx4 acc[MT][1];
+    floatx4 acc[MT][1], low[MT];                              // low: bf16, as in k_logits_rows
 #pragma unroll
-    for (int m = 0; m < MT; ++m) acc[m][0] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int m = 0; m < MT; ++m) acc[m][0] = low[m] = floatx4{0.f, 0.f, 0.f, 0.f};
     auto contract = [&](int buf, const Chunk16U<ET> (&e)[NC]) {
         const char* hb = sm + buf * kBuf + col * PITCH + 16 * kk;
 #pragma unroll
@@ -1965,9 +1981,11 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
             for (int m = 0; m < MT; ++m) {
                 if constexpr (BF) {
 #pragma unroll
-                    for (int p = 0; p < NP; ++p)
-                        acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            as_bf16x8(e[c]), *reinterpret_cast<const bf16x8*>(hb + p * kPlane + m * kTileM * PITCH + 64 * c), acc[m][0], 0, 0, 0);
+                    for (int p = 0; p < NP; ++p) {
+                        floatx4& to = p ? low[m] : acc[m][0];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            as_bf16x8(e[c]), *reinterpret_cast<const bf16x8*>(hb + p * kPlane + m * kTileM * PITCH + 64 * c), to, 0, 0, 0);
+                    }
                 } else {
                     const float4 b = *reinterpret_cast<const float4*>(hb + m * kTileM * PITCH + 64 * c);
                     acc[m][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(e[c].w[0]), b.x, acc[m][0], 0, 0, 0);
@@ -1997,6 +2015,10 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
     for (int i = 0; i < nblk; i += 2) {
         turn(i, e0, e1);
         if (i + 1 < nblk) turn(i + 1, e1, e0);
+    }
+    if constexpr (BF) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m][0] += low[m];
     }
     finish_wide<BF>(acc, E, ld, d, H, 0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
 }

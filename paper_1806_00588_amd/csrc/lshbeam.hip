@@ -554,7 +554,9 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
 // Where even k_logits_stream, with a tile of 16 words and one or two row groups per workgroup and k split over
 // its waves, fills the chip at most twice over, it is the faster one: the others then run few workgroups through
 // a long chain of k blocks (31 rows, V = 2009, d = 1181: 22.8 -> 10.6 us).
-constexpr int kRowsMaxMT = 6, kRowsMinD = 8;   // (a row holds at least one 16-byte chunk)
+constexpr int kRowsMinD = 8;   // (a row holds at least one 16-byte chunk)
+// Row tiles per workgroup at most: what the 256 registers of a lane leave room for.
+template <typename ET> constexpr int rows_max_mt() { return sizeof(ET) == 2 ? 4 : 5; }
 bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an option that names another driver wins)
     lsh_step_params all = *sp;
     all.S = 1;
@@ -580,9 +582,9 @@ void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspac
         return;
     }
     const int gx = (t->V + 64 * WF - 1) / (64 * WF);
-    int mt = kRowsMaxMT;
+    int mt = rows_max_mt<ET>();
     double best = 1e30;
-    for (int m = 1; m <= kRowsMaxMT; ++m) {
+    for (int m = 1; m <= rows_max_mt<ET>(); ++m) {
         const int n = (tiles + m - 1) / m * gx;
         double cost;
         if (sizeof(ET) == 2) {
@@ -601,8 +603,8 @@ void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspac
     launch(cx, 1, k_logits_rows<ET, MTV, WF>, grid, block, rows_lds_bytes(MTV), (const ET*)t->E, t->ld, t->d, H, R, \
            t->V, gx, ng, w.logits, w.cpitch, w.records())
     switch (mt) {
-        case 1: LSH_ROWS(1); break; case 2: LSH_ROWS(2); break; case 3: LSH_ROWS(3); break;
-        case 4: LSH_ROWS(4); break; case 5: LSH_ROWS(5); break; default: LSH_ROWS(6);
+        case 1: LSH_ROWS(1); break; case 2: LSH_ROWS(2); break; case 3: LSH_ROWS(3); break; case 4: LSH_ROWS(4); break;
+        default: if constexpr (rows_max_mt<ET>() == 5) LSH_ROWS(5);
     }
 #undef LSH_ROWS
 }

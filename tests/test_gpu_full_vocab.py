@@ -35,3 +35,48 @@ def test_full_vocabulary_tiles(shape, bf16):
         H = (4.0 * rng.standard_normal((S * B, d))).astype(np.float32)
         bs = rng.standard_normal(S * B).astype(np.float32)
         run_and_check(None, gc, H, bs, S, B, full_vocab=True)
+
+
+def _logits(gc, H, S, B):
+    """The step's logits, from its workspace (behind the candidate counts; rows are pitched to 64 words)."""
+    import torch
+    ws = gc.step(H, np.zeros(S * B, np.float32), S, B, full_vocab=True)[4]
+    at, pitch = (4 * S + 255) // 256 * 256, (gc.V + 63) // 64 * 64
+    return ws[at:at + 4 * S * B * pitch].view(torch.float32).view(S * B, pitch)[:, :gc.V].double()
+
+
+@pytest.mark.parametrize("n", [1, 2, 4, 16, 0], ids=lambda n: "%d" % n if n else "all")
+@pytest.mark.parametrize("case", [("rows", 9000, 5, 16, False), ("rows", 9000, 5, 16, True), ("few", 9000, 2, 12, False),
+                                  ("few", 9000, 2, 12, True)],
+                         ids=lambda c: "%s-%s" % (c[0], "bf16" if c[4] else "fp32"))
+def test_logits_are_as_near_as_fp32_sums(case, n):
+    """Logits with n products that are not zero (0: all) against fp64, beside a chain of fused multiply-adds in fp32.
+    The error, over the sum of the products' sizes, is no larger in the mean square; and of a single product no
+    larger than rounding it once: half a unit, 2^-24, and what the smaller planes' own sum loses, 2^-8 of that."""
+    import torch
+    _, V, S, B, bf16 = case
+    d = 600
+    rng = np.random.default_rng(V + B + n)
+    E = (rng.standard_normal((V, d)) / np.sqrt(d)).astype(np.float32)
+    if n:
+        keep = np.argpartition(rng.random((V, d)), n, axis=1)[:, :n]
+        E *= np.put_along_axis(m := np.zeros((V, d), np.float32), keep, 1.0, axis=1) or m
+    H = (4.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+    bits = workloads.f32_to_bf16_bits(E)
+    if bf16:
+        E = (bits.astype(np.uint32) << 16).view(np.float32)
+    perms = np.stack([rng.permutation(d)[:4] for _ in range(4)]).astype(np.int32)
+    gc = GpuCase(bits if bf16 else E, perms, np.zeros(0, np.int32), 2)
+    e, h = torch.from_numpy(E).cuda().double(), torch.from_numpy(H).cuda().double()
+    exact, size = h @ e.T, h.abs() @ e.abs().T
+    chain = torch.zeros(S * B, V, device="cuda")
+    for k in range(d):                   # (a product of two fp32 values is exact in fp64)
+        chain = (chain.double() + torch.outer(h[:, k], e[:, k])).float()
+
+    def error(x):
+        r = (x.double() - exact) / size
+        return r.square().mean().sqrt().item(), r.abs().max().item()
+    got, ref = error(_logits(gc, H, S, B)), error(chain)
+    assert got[0] <= 1.02 * ref[0], (got, ref)
+    if n == 1:
+        assert got[1] <= 2.0 ** -24 * (1 + 2.0 ** -7), got
