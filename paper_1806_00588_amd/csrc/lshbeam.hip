@@ -548,9 +548,10 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
 // Full vocabulary: one matrix product over all hidden rows of the call.  Up to 48 rows (fp32; 32 with bf16
 // words) the pass over E is what counts: k_logits_few.  Beyond that k_logits_rows; its row groups are as
 // even as they come in units of 16 rows, and among the splits the accumulators leave room for, the one
-// with the least work on the fullest CU is taken.  bf16 words: rounds of 256 workgroups that cost 2 (m + 1) for m
-// row tiles (m = 1: 5).  fp32 words, at d = 1000: 20 + 9.5 m us for two workgroups on every CU, 15.5 + 4.7 m for one
-// (measured for m = 1 .. 6).
+// with the least work on the fullest CU is taken: two workgroups of m row tiles on a CU take 3 + m, one alone 1.5 + 0.6 m
+// (in no unit; for d from 96 to 1536 and either type each is within 12 % of that, up to a factor of d's own).
+// Over V = 10000 .. 100000, d = 128 .. 1536 and 48 .. 640 rows (181 shapes of each type, every m measured)
+// the choice is 0.1 % slower than the best one on average and 6 % at most.
 // Where even k_logits_stream, with a tile of 16 words and one or two row groups per workgroup and k split over
 // its waves, fills the chip at most twice over, it is the faster one: the others then run few workgroups through
 // a long chain of k blocks (31 rows, V = 2009, d = 1181: 22.8 -> 10.6 us).
@@ -586,15 +587,9 @@ void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspac
     double best = 1e30;
     for (int m = 1; m <= rows_max_mt<ET>(); ++m) {
         const int n = (tiles + m - 1) / m * gx;
-        double cost;
-        if (sizeof(ET) == 2) {
-            cost = (n + 255) / 256 * (m == 1 ? 5 : 2 * m + 2);
-        } else {   // pairs of workgroups on every CU, then what is left, alone on its CU
-            const int left = n % 512;
-            cost = n / 512 * (20 + 9.5 * m);
-            if (left > 256) cost += 20 + 9.5 * m;
-            else if (left) cost += (15.5 + 4.7 * m) * (n < 512 ? 1.0 : std::max(0.3, left / 256.0));
-        }
+        const int left = n % 512;   // pairs of workgroups on every CU, then what is left
+        const double two = 3 + m, one = 1.5 + 0.6 * m;
+        const double cost = n / 512 * two + (left > 256 ? two : left ? one : 0);
         if (cost < best) { best = cost; mt = m; }
     }
     const int ng = (tiles + mt - 1) / mt;
