@@ -9,8 +9,8 @@
  *
  * Conventions
  *  - Every pointer named *_dev is DEVICE memory owned by the caller; *_host is host memory.
- *  - The library allocates device memory only inside lsh_build_tables (freed by
- *    lsh_free_tables).  lsh_decode_step allocates nothing, works in a caller workspace, is
+ *  - The library allocates device memory only inside lsh_build_tables (freed by lsh_free_tables, but
+ *    for what is kept for the next build).  lsh_decode_step allocates nothing, works in a caller workspace, is
  *    asynchronous on the given HIP stream and performs no host synchronisation and no
  *    device-to-host copy.
  *  - Errors are return codes; arguments are validated on the host before any launch and a
@@ -71,9 +71,12 @@ typedef struct {
 lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const lsh_build_params* p,
                             void* hip_stream, lsh_tables** out);
 
-/* Frees a handle.  Its device memory, up to 64 MiB per device, is kept for the next build there and given
- * back by lsh_free_tables(NULL) (or when a build runs out of memory). */
+/* Frees a handle (NULL: nothing).  Device memory that held a handle, and that a build worked in, is kept for the
+ * next build on the device: at most 192 MiB together, until lsh_release_kept or until a build runs out of memory. */
 void lsh_free_tables(lsh_tables* t);
+
+/* Gives the kept memory of all devices back to the driver (waits for them). */
+void lsh_release_kept(void);
 
 /* Per-call shape of a decode step; the paper's remaining hyper-parameters {B, T, t}. */
 typedef struct {

@@ -21,7 +21,7 @@ EXPORTED_SYMBOLS = (
     "lsh_profiler_destroy", "lsh_profiler_read", "lsh_decode_step_timed", "lsh_kernel_name",
     "lsh_status_string", "lsh_step_is_fused", "lsh_debug_build_info", "lsh_beam_advance",
     "lsh_beam_backtrace", "lsh_set_option", "lsh_get_option", "lsh_decode_step_static",
-    "lsh_static_scratch_bytes", "lsh_debug_counts",
+    "lsh_static_scratch_bytes", "lsh_debug_counts", "lsh_release_kept",
 )
 
 OPTION_AUTO = -1
@@ -74,6 +74,8 @@ def load_library():
     lib.lsh_build_tables.argtypes = [vp, vp, ctypes.POINTER(BuildParams), vp, ctypes.POINTER(vp)]
     lib.lsh_free_tables.argtypes = [vp]
     lib.lsh_free_tables.restype = None
+    lib.lsh_release_kept.argtypes = []
+    lib.lsh_release_kept.restype = None
     lib.lsh_step_workspace_bytes.argtypes = [vp, ctypes.POINTER(StepParams)]
     lib.lsh_step_workspace_bytes.restype = sz
     lib.lsh_decode_step.argtypes = [vp, vp, vp, vp, ctypes.POINTER(StepParams), vp, sz, vp, vp, vp, vp]
@@ -318,6 +320,11 @@ class Tables:
         self._prof = None
         _check(rc, "lsh_profiler_read")
         return {name: (ms[i], n[i]) for i, name in enumerate(kernel_names())}
+
+
+def release_kept():
+    """lsh_release_kept: device memory kept for the next build goes back to the driver."""
+    load_library().lsh_release_kept()
 
 
 def build_tables(E, perms, K: int, bands: int, seed: int = 0, stream=None) -> Tables:

@@ -75,6 +75,8 @@ struct HostBand : Band {           // a band being built on the host
     std::vector<int32_t> offsets;  // keys.size() + 1 span boundaries into the band's word array
 };
 
+struct KeptBlock { void* p = nullptr; size_t bytes = 0; };   // device memory that may be kept for the next build
+
 // Launch-plan options of a handle (lsh_set_option); kAuto = the library's own rule.
 enum Opt {
     kOptFused, kOptFusedGrid, kOptLogitsGrid, kOptLogitsWaves, kOptLogitsHlds, kOptLogitsEstage,
@@ -101,9 +103,8 @@ struct lsh_tables {
     const void* E = nullptr;
     int V = 0, d = 0, dtype = 0, K = 0, P = 0, W = 0, u = 0, bits = 0;
     int64_t ld = 0;
-    void* arena = nullptr;           // device memory of everything below, and what the build worked in
-    size_t arena_bytes = 0;
-    void* slot_arena = nullptr;      // ... but the slots and cuts, where their number was not known before the rest
+    KeptBlock arena;                 // device memory of everything below
+    KeptBlock slot_block;            // ... but the slots and cuts, where their number was not known before the rest
     int32_t* perms_dev = nullptr;    // [P, K]
     int32_t* codes_dev = nullptr;    // [W, V] band codes of the embedding rows
     int32_t* words_dev = nullptr;    // [W, V] word ids grouped by band code
@@ -637,49 +638,64 @@ hipError_t allow_logits_lds() {
         }                                               \
     } while (0)
 
-// The device memory of a freed handle stays with the library for the next build there: one block per
-// device, at most kKeptBytes (a driver allocation or release of a few MiB takes 20 to 60 us, as long as the
-// kernels of the build; an index is rebuilt where the embeddings change).  Given back by
-// lsh_free_tables(NULL) and wherever an allocation of a build fails; guarded by its own mutex.  A block is
-// kept only once the device has finished everything that was launched before.
-constexpr size_t kKeptBytes = (size_t)64 << 20;
-struct KeptBlock { void* p = nullptr; size_t bytes = 0; };
+// Device memory that stays with the library for the next build on the device: a block that held a handle, one that
+// held the slots of one, and one that a build worked in, together at most kKeptBytes (a driver allocation or release of a few MiB takes 20 to
+// 60 us, as long as the kernels of the build; an index is rebuilt where the embeddings change).  Given back by
+// lsh_release_kept() and wherever an allocation of a build fails; guarded by its own mutex.  A block is kept only
+// once the device has finished everything that was launched with it.
+constexpr size_t kKeptBytes = (size_t)192 << 20;
+enum KeptKind { kHandleBlock, kSlotBlock, kBuildBlock, kKeptKinds };
 std::mutex g_kept_mu;
-KeptBlock g_kept[kMaxDevices];
+KeptBlock g_kept[kMaxDevices][kKeptKinds];
 
-KeptBlock swap_kept(int dev, KeptBlock b) {
+// Puts b in the block's place and returns what was there; b itself where there is no room for it.
+KeptBlock swap_kept(int dev, KeptKind kind, KeptBlock b) {
     std::lock_guard<std::mutex> lock(g_kept_mu);
-    std::swap(b, g_kept[dev]);
+    size_t others = 0;
+    for (int k = 0; k < kKeptKinds; ++k)
+        if (k != kind) others += g_kept[dev][k].bytes;
+    if (b.bytes + others <= kKeptBytes) std::swap(b, g_kept[dev][kind]);
     return b;
 }
 void give_back_kept() {
-    for (int d = 0; d < kMaxDevices; ++d) (void)hipFree(swap_kept(d, KeptBlock{}).p);
+    for (int d = 0; d < kMaxDevices; ++d)
+        for (int k = 0; k < kKeptKinds; ++k) {
+            const KeptBlock b = swap_kept(d, (KeptKind)k, KeptBlock{});
+            if (b.p) (void)hipFree(b.p);
+        }
 }
-hipError_t alloc_arena(int dev, size_t bytes, void** p, size_t* got) {
-    if (dev < kMaxDevices && bytes <= kKeptBytes) {
-        const KeptBlock b = swap_kept(dev, KeptBlock{});
-        if (b.p && b.bytes >= bytes) { *p = b.p; *got = b.bytes; return hipSuccess; }
-        (void)hipFree(b.p);
-    }
-    *got = bytes;
-    hipError_t e = hipMalloc(p, bytes);
+// An allocation of a build: where memory has run out, once more without the kept blocks.
+hipError_t alloc_device(void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes ? bytes : 1);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
         give_back_kept();
-        e = hipMalloc(p, bytes);
+        e = hipMalloc(p, bytes ? bytes : 1);
     }
     return e;
 }
-void release_arena(int dev, void* p, size_t bytes) {
-    if (!p) return;
+hipError_t take_block(int dev, KeptKind kind, size_t bytes, KeptBlock* out) {
     if (dev < kMaxDevices && bytes <= kKeptBytes) {
-        int cur = 0;
-        const bool ok = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess) &&
-                        hipDeviceSynchronize() == hipSuccess;   // (as hipFree would)
-        if (cur != dev) (void)hipSetDevice(cur);
-        if (ok) { p = swap_kept(dev, KeptBlock{p, bytes}).p; }
+        const KeptBlock b = swap_kept(dev, kind, KeptBlock{});
+        if (b.p && b.bytes >= bytes) { *out = b; return hipSuccess; }
+        if (b.p) (void)hipFree(b.p);
     }
-    (void)hipFree(p);
+    out->bytes = bytes;
+    return alloc_device(&out->p, bytes);
+}
+// idle: nothing that was launched uses the block any more (set where this waits for it).
+void release_block(int dev, KeptKind kind, KeptBlock b, bool& idle) {
+    if (!b.p) return;
+    if (dev < kMaxDevices && b.bytes <= kKeptBytes) {
+        if (!idle) {   // (as hipFree would)
+            int cur = 0;
+            idle = hipGetDevice(&cur) == hipSuccess && (cur == dev || hipSetDevice(dev) == hipSuccess) &&
+                   hipDeviceSynchronize() == hipSuccess;
+            if (cur != dev) (void)hipSetDevice(cur);
+        }
+        if (idle) b = swap_kept(dev, kind, b);
+    }
+    if (b.p) (void)hipFree(b.p);
 }
 
 // Regions of one device allocation, each 256-byte aligned: sized with base = null, then placed.
@@ -694,12 +710,12 @@ struct Carver {
 };
 
 lsh_status place_slots(lsh_tables* t, uint64_t n_slots) {
-    (void)hipFree(t->slot_arena);
-    t->slot_arena = nullptr;
+    if (t->slot_block.p) (void)hipFree(t->slot_block.p);
+    t->slot_block = KeptBlock{};
     const size_t slot_bytes = align_up(n_slots * sizeof(Slot));
-    HIP_TRY(hipMalloc(&t->slot_arena, slot_bytes + n_slots * sizeof(uint4)));
-    t->slots_dev = (Slot*)t->slot_arena;
-    t->cuts_dev = (uint4*)((char*)t->slot_arena + slot_bytes);
+    HIP_TRY(take_block(t->device, kSlotBlock, slot_bytes + n_slots * sizeof(uint4), &t->slot_block));
+    t->slots_dev = (Slot*)t->slot_block.p;
+    t->cuts_dev = (uint4*)((char*)t->slot_block.p + slot_bytes);
     return LSH_OK;
 }
 
@@ -767,8 +783,15 @@ lsh_status build_on_host(lsh_tables* t, hipStream_t st, SplitMix64& rng) {
 
 struct DevBuf {  // temporary device memory of the build, released on every exit path
     void* p = nullptr;
-    ~DevBuf() { (void)hipFree(p); }
-    hipError_t alloc(size_t bytes) { return hipMalloc(&p, bytes ? bytes : 1); }
+    ~DevBuf() { if (p) (void)hipFree(p); }
+    hipError_t alloc(size_t bytes) { return alloc_device(&p, bytes); }
+};
+
+struct BuildBlock {  // what a build works in, kept for the next one
+    int dev = 0;
+    KeptBlock block;
+    bool idle = false;
+    ~BuildBlock() { release_block(dev, kBuildBlock, block, idle); }
 };
 
 template <typename ET>
@@ -796,22 +819,33 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     const uint32_t key_pitch = (uint32_t)std::min<int64_t>(V, (int64_t)1 << code_bits);
     auto lg_for = [](uint32_t keys) { int lg = 1; while ((1ull << lg) < 3ull * keys) ++lg; return lg; };
     int lg = lg_for(key_pitch);
-    // tables for the most keys there can be, so that nothing has to be known before they are placed --
-    // unless that took a gigabyte: then the keys are counted first
-    constexpr uint64_t kPlaceBlind = (1ull << 30) / (sizeof(Slot) + sizeof(uint4) + sizeof(uint64_t));
-    const bool blind = ((uint64_t)W << lg) <= kPlaceBlind;
+    // Tables for the most keys there can be, so that nothing has to be known before they are placed, where those are
+    // at most 32 MiB (V = 14000, 10 bands of 16-bit codes, 26 MB: 118 us, 141 with the keys counted first: one wait),
+    // or where so many words share the codes that hardly one will be missing.  Otherwise the keys are counted: 16-bit
+    // codes have room for 65536 keys and 27000 to 42000 come up (V = 100000, 12 bands: 100 MB of slots, 50 for the
+    // keys there are; 370 us, 340 so).
+    constexpr uint64_t kSlotBytes = sizeof(Slot) + sizeof(uint4) + sizeof(uint64_t);
+    const uint64_t most_bytes = ((uint64_t)W << lg) * kSlotBytes;
+    const bool blind = most_bytes <= (32ull << 20) || (V >= 8ll << code_bits && most_bytes <= (1ull << 30));
+    auto table_bytes = [&]() { return ((uint64_t)W << lg) * sizeof(uint64_t); };
+    // A counted table takes the place of what the sort is through with, where that is large enough or can be made so
+    // within reason.
+    const size_t sort_buf = align_up((size_t)V * W * sizeof(int32_t));
+    const size_t spare_bytes = blind ? (passes > 1 ? sort_buf * std::min(passes, 3) : 0)
+                                     : std::max<size_t>(passes > 1 ? sort_buf * std::min(passes, 3) : 0, std::min<uint64_t>(table_bytes(), 64ull << 20));
 
     struct Status { uint32_t *bad, *failed[2], *n_keys; } stat{};
     uint32_t *status_dev = nullptr, *counts = nullptr, *starts = nullptr, *key_start = nullptr;
     uint64_t* table = nullptr;
     int32_t *key_code = nullptr, *code_buf[2] = {}, *id_buf[2] = {};
     const size_t status_words = kBuildBeginBlocks + 3 * (size_t)W;
+    BuildBlock work;   // (what only the build needs)
+    work.dev = t->device;
     for (int pass = 0; pass < 2; ++pass) {
-        Carver c{(char*)t->arena};
+        Carver c{(char*)t->arena.p};
         t->perms_dev = c.take<int32_t>(n_perms);
         t->tickets_dev = c.take<unsigned int>(n_tickets);
         t->bands_dev = c.take<BandMeta>(W);
-        status_dev = c.take<uint32_t>(status_words);
         t->codes_dev = c.take<int32_t>((size_t)V * W);
         // 16 bytes of slack: k_hit_rows reads ids with 16-byte loads that may straddle the end
         t->words_dev = c.take<int32_t>((size_t)V * W + 4);
@@ -819,23 +853,31 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
             t->slots_dev = c.take<Slot>((size_t)W << lg);
             t->cuts_dev = c.take<uint4>((size_t)W << lg);
         }
-        // (what only the build needs)
-        if (blind) table = c.take<uint64_t>((size_t)W << lg);
-        counts = c.take<uint32_t>((size_t)W * chunks * (digits / 2));
-        starts = c.take<uint32_t>((size_t)W * digits);
-        key_code = c.take<int32_t>((size_t)W * key_pitch);
-        key_start = c.take<uint32_t>((size_t)W * key_pitch);
-        for (int b = 0; passes > 1 && b < 2; ++b) {
-            code_buf[b] = c.take<int32_t>((size_t)V * W);
-            id_buf[b] = c.take<int32_t>((size_t)V * W);
+        Carver b{(char*)work.block.p};
+        status_dev = b.take<uint32_t>(status_words);
+        if (blind) table = b.take<uint64_t>((size_t)W << lg);
+        counts = b.take<uint32_t>((size_t)W * chunks * (digits / 2));
+        starts = b.take<uint32_t>((size_t)W * digits);
+        key_code = b.take<int32_t>((size_t)W * key_pitch);
+        key_start = b.take<uint32_t>((size_t)W * key_pitch);
+        char* spare = b.take<char>(spare_bytes);
+        if (passes > 1) {   // (pass p writes code_buf[p % 2] and, but for the last, id_buf[p % 2])
+            code_buf[(passes - 1) & 1] = b.take<int32_t>((size_t)V * W);
+            code_buf[passes & 1] = (int32_t*)spare;
+            id_buf[0] = spare ? (int32_t*)(spare + sort_buf) : nullptr;
+            id_buf[1] = spare && passes > 2 ? (int32_t*)(spare + 2 * sort_buf) : nullptr;
         }
-        if (!pass) HIP_TRY(alloc_arena(t->device, c.bytes, &t->arena, &t->arena_bytes));
+        if (!blind) table = (uint64_t*)spare;
+        if (!pass) {
+            HIP_TRY(take_block(t->device, kHandleBlock, c.bytes, &t->arena));
+            HIP_TRY(take_block(t->device, kBuildBlock, b.bytes, &work.block));
+        }
     }
     stat.bad = status_dev;
     stat.n_keys = stat.bad + kBuildBeginBlocks;
     stat.failed[0] = stat.n_keys + W;
     stat.failed[1] = stat.failed[0] + W;
-    DevBuf late_table;
+    DevBuf late;
 
     const dim3 begin_grid(kBuildBeginBlocks, (unsigned)W + 1), b256(256);
     auto begin = [&](int attempt, const uint32_t* redo, bool with_tables) {
@@ -853,6 +895,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     auto read_status = [&]() -> lsh_status {
         HIP_TRY(hipMemcpyAsync(status.data(), status_dev, status_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
+        work.idle = true;   // (until the next launch)
         for (int i = 0; i < kBuildBeginBlocks; ++i)
             if (status[i]) return LSH_ERR_INVALID_ARG;
         return LSH_OK;
@@ -894,8 +937,11 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
         if (((uint64_t)W << lg) >= (1ull << 32)) return build_on_host(t, st, host_rng);
         rc = place_slots(t, (uint64_t)W << lg);
         if (rc != LSH_OK) return rc;
-        HIP_TRY(late_table.alloc(((size_t)W << lg) * sizeof(uint64_t)));
-        table = (uint64_t*)late_table.p;
+        if (table_bytes() > spare_bytes) {
+            HIP_TRY(late.alloc(table_bytes()));
+            table = (uint64_t*)late.p;
+        }
+        work.idle = false;
         begin(0, nullptr, true);
     }
     // LSHBEAM_CUCKOO_CHAIN shortens the eviction chains (tests of the retry and fallback paths)
@@ -905,6 +951,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     for (int attempt = 0; attempt < 24; ++attempt) {
         t->build_attempts = attempt + 1;
         const uint32_t* redo = attempt ? stat.failed[(attempt - 1) & 1] : nullptr;
+        work.idle = false;
         if (attempt) begin(attempt, redo, true);
         hipLaunchKernelGGL(k_cuckoo_insert, insert_grid, b256, 0, st, table, (const BandMeta*)t->bands_dev,
                            (const int32_t*)key_code, key_pitch, (const uint32_t*)stat.n_keys, max_chain, redo,
@@ -1092,11 +1139,14 @@ const char* lsh_kernel_name(int32_t which) {
 }
 
 void lsh_free_tables(lsh_tables* t) {
-    if (!t) { give_back_kept(); return; }
-    release_arena(t->device, t->arena, t->arena_bytes);
-    (void)hipFree(t->slot_arena);
+    if (!t) return;
+    bool idle = false;
+    release_block(t->device, kHandleBlock, t->arena, idle);
+    release_block(t->device, kSlotBlock, t->slot_block, idle);
     delete t;
 }
+
+void lsh_release_kept(void) { give_back_kept(); }
 
 lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const lsh_build_params* p,
                             void* hip_stream, lsh_tables** out) {

@@ -57,3 +57,31 @@ def test_permutations_out_of_range_are_refused():
         with pytest.raises(lsh.binding.LshBeamError):
             lsh.build_tables(E, to_dev(p), 4, 100)
     lsh.build_tables(E, to_dev(perms), 4, 100).close()
+
+
+def test_a_handle_holds_its_tables_and_no_more():
+    """Codes, ids and slots for the keys there are -- not for all 65536 a band could have, and not what the build
+    worked in; a freed handle's memory is given back by release_kept, and freeing nothing does nothing."""
+    import torch
+    import paper_1806_00588_amd as lsh
+    from paper_1806_00588_amd import binding
+    V, d, K, u, W = 30000, 20, 16, 4, 12
+    rng = np.random.default_rng(11)
+    E = to_dev(rng.standard_normal((500, d)).astype(np.float32)[rng.integers(0, 500, V)])
+    perms = to_dev(np.stack([rng.permutation(d)[:K] for _ in range(u * W)]).astype(np.int32))
+    lsh.build_tables(E, perms, K, W).close()          # (whatever a first build brings with it)
+    binding.release_kept()
+    free = torch.cuda.mem_get_info()[0]
+    t = lsh.build_tables(E, perms, K, W)
+    slots = sum(t.debug_cuckoo_shape(w)[0] for w in range(W))
+    assert slots <= W * 2048                          # at most 500 keys a band
+    binding.release_kept()
+    held = free - torch.cuda.mem_get_info()[0]
+    assert held <= 2 * 4 * V * W + 32 * slots + (6 << 20), held      # (blocks of 2 MiB)
+    t.close()
+    kept = free - torch.cuda.mem_get_info()[0]
+    assert kept <= 192 << 20
+    binding.load_library().lsh_free_tables(None)
+    assert free - torch.cuda.mem_get_info()[0] == kept
+    binding.release_kept()
+    assert torch.cuda.mem_get_info()[0] == free
