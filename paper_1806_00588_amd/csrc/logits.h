@@ -957,11 +957,10 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 //
 // The tiles of a sentence are dealt to the XCDs by their number (XcdTiles above).
 // 16 bytes per lane from each lane's address to LDS, lane after lane from `to` (wave-uniform) on.  (Not the
-// builtin: for that the compiler waits for ALL such loads before the next read of LDS, whatever it reads.  M0
-// serves nothing else in these kernels.)
+// builtin: for that the compiler waits for ALL such loads before the next read of LDS, whatever it reads.)
 __device__ __forceinline__ void load_to_lds16(const void* from, void* to) {
     const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
 }
 constexpr int kStreamTiles = 32;   // tiles of a stretch whose rows' addresses are in LDS
 constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? 1 : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
