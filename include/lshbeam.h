@@ -236,7 +236,8 @@ lsh_status lsh_debug_logprobs(const lsh_tables* t, const void* workspace_dev,
  *   "estage_union"   0: sentences hashed in parts get their candidate list from a kernel of its own
  *                    before that driver, instead of inside it
  *   "hlds_rem"       n: a last round of tiles filling at most 1/n of the waves is split over k (4)
- *   "logits_planes"  0: bf16 rows are widened to fp32 instead of meeting bf16 planes of H
+ *   "logits_planes"  0: no bf16 planes: bf16 rows are widened to fp32 instead of meeting planes of H,
+ *                    and the full vocabulary's fp32 rows take the fp32 instructions
  *   "hlds_rows"      16 / 32: hidden rows per group of the LDS-staged driver
  *   "part_rows"      n: sentences are hashed in parts of n rows, a workgroup each
  *   "stage_rows"     n: the hashing stage in LDS is sized for at most n rows (0: the minimum)

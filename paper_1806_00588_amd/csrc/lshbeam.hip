@@ -567,7 +567,8 @@ bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an optio
     const int64_t tiles = (t->V + kTileN - 1) / kTileN;
     if (rows > 0 && tiles * ((all.B + rows - 1) / rows) <= 512) return false;
     return sp->full_vocab && t->d >= kRowsMinD && t->opt[kOptLogitsWaves] == kAuto && t->opt[kOptLogitsEstage] == kAuto &&
-           t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto;
+           t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto &&
+           t->option(kOptLogitsPlanes, 1) != 0;
 }
 template <typename ET>
 void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspace& w) {

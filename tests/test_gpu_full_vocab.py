@@ -59,8 +59,9 @@ def test_logits_are_as_near_as_fp32_sums(case, n):
     rng = np.random.default_rng(V + B + n)
     E = (rng.standard_normal((V, d)) / np.sqrt(d)).astype(np.float32)
     if n:
-        keep = np.argpartition(rng.random((V, d)), n, axis=1)[:, :n]
-        E *= np.put_along_axis(m := np.zeros((V, d), np.float32), keep, 1.0, axis=1) or m
+        keep = np.zeros((V, d), np.float32)
+        np.put_along_axis(keep, np.argpartition(rng.random((V, d)), n, axis=1)[:, :n], 1.0, axis=1)
+        E *= keep
     H = (4.0 * rng.standard_normal((S * B, d))).astype(np.float32)
     bits = workloads.f32_to_bf16_bits(E)
     if bf16:
@@ -80,3 +81,22 @@ def test_logits_are_as_near_as_fp32_sums(case, n):
     assert got[0] <= 1.02 * ref[0], (got, ref)
     if n == 1:
         assert got[1] <= 2.0 ** -24 * (1 + 2.0 ** -7), got
+
+
+@pytest.mark.parametrize("S, B", [(2, 12), (5, 16)])
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+def test_without_planes(S, B, bf16):
+    """logits_planes = 0: the fp32 instructions, as k_logits_hlds has them, and not the planes' result."""
+    import torch
+    rng = np.random.default_rng(S)
+    E = (rng.standard_normal((9000, 300)) / 17).astype(np.float32)
+    H = (4.0 * rng.standard_normal((S * B, 300))).astype(np.float32)
+    perms = np.stack([rng.permutation(300)[:4] for _ in range(4)]).astype(np.int32)
+    gc = GpuCase(workloads.f32_to_bf16_bits(E) if bf16 else E, perms, np.zeros(0, np.int32), 2)
+    planes = _logits(gc, H, S, B)
+    gc.tables.set_option("logits_planes", 0)
+    without = _logits(gc, H, S, B)
+    gc.tables.set_option("logits_hlds", 1)
+    assert torch.equal(without, _logits(gc, H, S, B))
+    assert not torch.equal(without, planes)
+    assert (without - planes).abs().max() < 1e-4
