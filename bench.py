@@ -34,7 +34,7 @@ def log(*a):
 def committed_traffic(workload: str):
     """(HBM bytes per launch of the dominant kernel, file) from the committed rocprofv3 --pmc
     summary of that workload; measured by hand with the counters, not during this run."""
-    for kernel in ("k_cand_logits", "k_union_logits", "k_logits_hlds", "k_logits_estage", "k_logits_wave"):
+    for kernel in ("k_cand_logits", "k_union_logits", "k_logits_stream", "k_logits_estage"):
         name = f"{kernel}_{workload}_pmc.md"
         try:
             for line in open(os.path.join(ROOT, "profiles", name)):

@@ -18,10 +18,10 @@
 //   6. The 8-byte (code, key index) words are expanded into the 16-byte slots the probe reads.
 //
 // What bounds it is the pass over the embedding rows (2); the rest is a chain of short kernels.  Nothing
-// is copied to the host before the whole chain is under way: tables are sized for the most keys a band
-// can have, parameters are drawn on the device, and one copy of the status words ends the build.
-// V = 40000, d = 1000 fp32, 8 bands of 12 bits: 127 us, of which 36 us k_row_codes (160 MB at 4.4 TB/s) and
-// 45 us the other kernels; 700 us with a library sort of (band, code, id) keys, ten small copies, three
+// is copied to the host before the whole chain is under way where tables for the most keys a band can have
+// are small or nearly full (lshbeam.hip); parameters are drawn on the device, and one copy of the status words ends the
+// build.  V = 40000, d = 1000 fp32, 8 bands of 12 bits: 125 us, of which 36 us k_row_codes (160 MB at 4.4 TB/s) and
+// 45 us the other kernels; 770 us with a library sort of (band, code, id) keys, ten small copies, three
 // waits and an allocation for every array.
 #pragma once
 #include "candidates.h"

@@ -22,14 +22,17 @@
 // element per instruction: per load instruction a wave touches 16 rows x 64 contiguous bytes.
 //
 // Drivers of the tile code:
-//   k_logits<WAVES>  a workgroup of 16 or 4 waves per (tile, row group), k split over the waves
-//                    (few sentences; more than 64 beams);
-//   k_logits_wave    one wave per tile, up to four row groups in the wave, hidden rows read from
-//                    global memory (kept as the LSHBEAM_LOGITS_HLDS=0 path);
-//   k_logits_hlds    one wave per tile, the sentence's hidden rows staged in LDS (up to 32 beams:
-//                    the bandwidth-bound case; more beams in groups of 16 rows);
-//   k_logits_estage  33..64 beams: hidden rows in registers, candidate rows through LDS;
+//   k_logits_stream  many tiles, rows of at most 2048 values: candidate rows through LDS in contiguous
+//                    pieces, hidden rows in registers (up to 32 beams at a time);
+//   k_logits_estage  33..64 beams, fp32 rows of 513 to 1024 values: the same change of places, all
+//                    beams at once;
 //   k_logits_few, k_logits_rows   the full vocabulary: all hidden rows of the call against all words;
+//   k_logits_hlds    one wave per tile, the sentence's hidden rows staged in LDS: rows of more than 2048
+//                    values, and where an option names it;
+//   k_logits<WAVES>  a workgroup of 16 or 4 waves per (tile, row group), k split over the waves: rows
+//                    shorter than a 16-byte chunk, hidden rows that do not fit in LDS, options;
+//   k_logits_wave    one wave per tile, up to four row groups in the wave, hidden rows read from
+//                    global memory (the same cases with many tiles; logits_hlds = 0);
 //   fused.h          the same tiles inside the kernels that also produce the candidate list.
 #pragma once
 #include <cfloat>
@@ -175,8 +178,8 @@ __device__ __forceinline__ void tile_record_store(const TileRecords& recs, size_
 //
 // CHUNKS: a row holds at least one 16-byte chunk of E.  Rows are then read with 16-byte loads from whatever
 // address they start at (d = 1001 fp32, rows 4 bytes off a multiple of 16: element by element was three times
-// slower); the chunk that would reach past the row's end is read from the row's last VEC elements instead, and
-// the hidden values of elements that were counted already are zero.  Otherwise elements are read one by one.
+// slower); the chunk that would reach past the row's end is read from the row's last VEC elements instead, of
+// which those that were counted already are zeroed on both sides.  Otherwise elements are read one by one.
 template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int MTB = 1, bool RICH = false, bool SHARE = false>
 __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld, int d,
                                             const float* __restrict__ H, int B, int s, int mt,
@@ -621,7 +624,7 @@ __device__ __forceinline__ void store_planes4(char* dst, size_t plane_bytes, con
 // Tiles are dealt to the XCDs by their number inside the sentence: tile t of every sentence below `shared`
 // (the tiles that surely lie among the top-frequent words all sentences have in common, where those are the
 // lowest ids) goes to XCD t mod 8, so that its 16 rows enter one L2 and serve the other sentences from there;
-// tiles beyond go to XCD (t + s) mod 8.  What bounds the kernel is the fabric behind the L2s (6.5 TB/s).
+// tiles beyond go to XCD (t + s) mod 8.  What bounds the kernel lies behind the L2s.
 struct XcdTiles {   // the tiles of one sentence that belong to XCD x
     uint32_t n0;        // how many of them lie below `shared`
     uint32_t first1;    // the first one beyond
@@ -940,10 +943,11 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 
 // Many tiles.  What bounded k_logits_hlds was neither the fabric nor the matrix pipe but the load path of
 // the CU: a lane that fetches the matrix operand it needs itself makes every 16 lanes touch 16 rows -- 16
-// cache lines for 256 bytes -- and such a gather stops at 8.5 TB/s even where every line hits in L2, 6 TB/s
-// on the lists of a real step.  Here candidate rows travel in contiguous pieces, straight from memory
+// cache lines for 256 bytes.  Here candidate rows travel in contiguous pieces, straight from memory
 // to LDS (global_load_lds, 16 bytes per lane, any row alignment), and the lanes pick their operands out of
-// LDS: 13.5 TB/s from L2, 7.7 from memory, 8.7 on a step's lists.
+// LDS.  32 sentences x 10 beams, V = 40000, d = 1000 fp32 (261 MB of rows): 47.6 -> 35.5 us, 5.5 -> 7.4 TB/s, of
+// which 146 MB come from memory (186 before; 62 % L2 hits, 45 before); 64 x 10, V = 200000, d = 1024 bf16 (1.38 GB, 1.27
+// from memory): 224 -> 182 us, 7.6 TB/s.
 //
 // The four waves of a workgroup share a tile, each with a quarter of k, and keep the A operands of all MT * 16
 // hidden rows for their quarter in REGISTERS for as long as the workgroup stays with the sentence.  A step is 64
@@ -1618,11 +1622,11 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
 // reads) the LDS rate is no bound.  Words are the A operand, so that a lane ends up with
 // four consecutive words of one hidden row (a 16-byte store).  The operands of a block are read from
 // LDS in two halves, each while the other half's instructions run; without that, and with the loads
-// placed by the compiler, the same tiles took 283 instead of 222 us.  MT is the host's choice.
+// placed by the compiler, the same tiles took a quarter longer.  MT is the host's choice.
 // Any d >= one chunk and any pitch: chunks are loaded from any element's address.
-// 320 rows, V = 40000, d = 1000: fp32 222 us with fp32 instructions (116 TFLOP/s, the pipe busy 72 % of the
-// time), 177 us on planes (145 TFLOP/s of the product, 1160 of plane products: a large bf16 product of matrices
-// reaches 1190 on this card), 157 us with six products in one accumulator; bf16 (d = 1024) 87 us, 86 us in one.
+// 320 rows, V = 40000, d = 1000: fp32 175 us (146 TFLOP/s of the product, 1170 of plane products: a large bf16 product
+// of matrices reaches 1230 on this card, a large fp32 one 154), 157 us with six products in one accumulator;
+// k_logits_hlds with fp32 instructions 370 us.  bf16 (d = 1024) 87 us, in one accumulator 86; widened 334.
 constexpr int kRowsK = 32;
 constexpr int kRowsPitch = 40 * 2;   // LDS bytes per hidden row and plane: 16-byte reads without conflicts
 __host__ __device__ constexpr size_t rows_lds_bytes(int MT) {
@@ -1915,10 +1919,10 @@ k_logits_rows(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 
 // The same for a few hidden rows (MT * 16, at most 48): bound by the pass over E.  A wave owns 16 words; what
 // counts is that every wave keeps long pieces of its rows in flight: blocks of 128 k (512 or 256 bytes
-// of a row, asked for together -- asked for 128 bytes at a time, memory gave 4.2 TB/s), the next block
-// under way while the current one meets the hidden rows in LDS (double-buffered, as above).
-// 12 rows, V = 40000, d = 1000 fp32: 40.1 -> 37.6 us (a fifth of it launch and ramp; 5.0 TB/s at
-// V = 200000); bf16, d = 1024: 24.6 -> 16.5 us.
+// of a row, asked for together), the next block under way while the current one meets the hidden rows in LDS
+// (double-buffered, as above).
+// 12 rows, V = 40000, d = 1000 fp32: 30.8 us (5.2 TB/s), as k_logits_hlds, but records of 64 words: the selection takes
+// 9.4 us after them, 16.1 after records of 16; V = 200000: 161 and 174 us; bf16, d = 1024: 17.0 us, widened 24.3.
 constexpr int kFewK = 128;
 template <typename ET> __host__ __device__ constexpr int few_pitch() {   // LDS bytes per hidden row and plane
     return sizeof(ET) == 2 ? (kFewK + 8) * 2 : (kFewK + 4) * 4;

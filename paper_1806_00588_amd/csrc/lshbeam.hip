@@ -424,7 +424,9 @@ template <typename ET> StreamPlan stream_plan(int d) {
     return nst <= 1 ? StreamPlan{1, 1} : nst <= 2 ? StreamPlan{2, 1} : StreamPlan{4, (nst + 3) / 4};
 }
 // Hidden rows per workgroup (0: the kernel does not take the step).  Registers bound the operands a wave keeps:
-// two row groups of 16 where they are at most 128 of them.
+// two row groups of 16 where they are at most 128 of them.  (The longest bf16 rows, four parts, need 16 registers more
+// than there are; the spills cost less than the other kernel does: 32 sentences x 10 beams, V = 40000, 34 us against
+// 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
 template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
     if (!has_chunks(t)) return 0;
     const StreamPlan p = stream_plan<ET>(t->d);
@@ -459,8 +461,7 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
 #undef LSH_STREAM
 }
 
-// k_logits_estage: 33..64 beams, fp32 rows of at most 1024 values, 16-byte aligned operands, at
-// most 256 sentences.  About one workgroup per CU, dealt evenly to the sentences.
+// k_logits_estage (takes_estage).  About one workgroup per CU, dealt evenly to the sentences.
 // Returns its workgroups per sentence: each leaves one record per hidden row for all its tiles.
 // un, if given: the kernel makes the candidate list itself, from the bitmaps of the sentence's parts.
 constexpr int kEsMinD = 512;
@@ -487,7 +488,7 @@ int launch_logits_estage(const StepCtx& cx, const float* H, const lsh_step_param
 
 // Whether a step's contraction is k_logits_estage: 33..64 beams, fp32 rows of 513 to 1024 values (shorter ones
 // leave half of its four slices of k or more without work: k_logits_stream is 1.2 to 1.9 times faster there,
-// 1.1 to 1.3 times slower beyond; fifty shapes),
+// 1.1 to 1.3 times slower beyond),
 // 16-byte aligned operands, at most 256 sentences (option logits_estage = 0: the other drivers).
 bool takes_estage(const lsh_tables* t, const lsh_step_params* sp, const float* H) {
     const bool aligned = (t->d % 4 == 0) && (t->ld % 4 == 0) && ((uintptr_t)t->E % 16 == 0) && ((uintptr_t)H % 16 == 0);
@@ -507,9 +508,9 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
     const int MT = (sp->B + kTileM - 1) / kTileM;
     const int64_t tiles_n = (int64_t)sp->S * ((t->V + kTileN - 1) / kTileN);  // upper bound
     const int64_t max_tiles = tiles_n * MT;
-    // Few (sentence, M-tile) groups: little work per step and it is latency that counts, so k is
-    // split across the 16 waves of a workgroup and the partial tiles are summed through LDS.
-    // Otherwise one wave per 16-candidate tile, no LDS and no barrier (up to 4 M-tiles per wave).
+    // k_logits_stream wherever it takes the rows.  Where it does not and there are few (sentence, M-tile) groups,
+    // little work per step and it is latency that counts, so k is split across the 16 waves of a workgroup and
+    // the partial tiles are summed through LDS; otherwise one wave per 16-candidate tile.
     // (the full-vocabulary mode has V / 16 tiles per sentence, known here: thousands of tiles
     // are "many" even for one sentence -- 29.9 against 37.1 us at V = 40000)
     const bool few = sp->S * MT <= 8 && !(count == nullptr && tiles_n >= 1024);
