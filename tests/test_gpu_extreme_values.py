@@ -91,3 +91,24 @@ def test_tiles_and_records_without_a_word(case):
     H[:, 5] = 1.0
     E[60:160, 5] = -np.inf
     assert _check(rng, S, B, V, full, options, E, H, case[2]) == 100 * S * B
+
+
+@pytest.mark.parametrize("case", [c for c in _CASES if c[1] in (203, 1000)], ids=lambda c: "%s-%d-%s" % c)
+def test_a_hidden_row_of_nan_is_alone(case):
+    """A beam whose hidden row holds a NaN has no results; the others of its sentence have theirs."""
+    rng, S, B, V, full, options, E, H = _inputs(*case)
+    perms = np.stack([rng.permutation(E.shape[1])[:4] for _ in range(9)]).astype(np.int32)
+    gc = GpuCase(workloads.f32_to_bf16_bits(E) if case[2] == "bf16" else E, perms, np.arange(min(V, 600), dtype=np.int32), 3)
+    gc.tables.set_options(**options)
+    H[1, 20] = np.nan
+    bs = rng.standard_normal(S * B).astype(np.float32)
+    gb, gw, gs, sp, ws = gc.step(H, bs, S, B, full_vocab=full)
+    for s in range(S):
+        rows = slice(s * B, (s + 1) * B)
+        ref = gc.oracle_sentence(H[rows], bs[rows], B, full_vocab=full)
+        lp = gc.tables.debug_logprobs(ws, sp, s, cap=len(ref.cand))
+        bad = np.isnan(ref.lp)
+        assert bad.sum() == (len(ref.cand) if s == 0 else 0) and np.array_equal(bad, np.isnan(lp))
+        ref = ref._replace(lp=np.where(bad, -1e30, ref.lp), logits=np.where(bad, -1e30, ref.logits))
+        assert_close_logprobs(np.where(bad, np.float32(-1e30), lp), ref)
+        assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
