@@ -1000,6 +1000,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     const ET** rows = reinterpret_cast<const ET**>(sm + 8 * NI * 1024 + 4 * TS * MT * 4 * kWave * 4);   // [tile][16]
     uint32_t* tile_pref = reinterpret_cast<uint32_t*>(rows + kStreamTiles * kTileN);  // [S + 1], then "own"
     uint32_t* counts = tile_pref + ((S + 2 + 3) & ~3);                                // [S]
+    uint32_t* again = counts + S;   // [2]: a bit for every tile of the stretch with logits to settle; its first hidden row
+    static_assert(kStreamTiles <= 32, "a bit per tile");
     // grid = 8 * wgs * ngroups; ids go round the XCDs, the row groups of one block of tiles follow each other on one
     const uint32_t xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
     const uint32_t bx = slot / (uint32_t)ngroups;
@@ -1114,6 +1116,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             if (i * 256 >= n * kTileN) break;
             rows[i * 256 + tid] = E + (int64_t)my_id[i] * ld;
         }
+        if (tid == 0) { again[0] = 0u; again[1] = (uint32_t)(s * B + row0); }
         lds_barrier();
         // unit u = part u % PARTS of the tiles (u / PARTS) TS ..; instruction i of a tile brings its pieces 64 i .. 64 i + 63
         const int units = (n + TS - 1) / TS * PARTS;
@@ -1152,8 +1155,6 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         if (units > 1) fill(1);
         float out[TS][MT];
         int out_t0 = -1;                                                      // first tile of `out`
-        uint32_t again = 0;                                                   // tiles in which this wave has logits to settle
-        static_assert(kStreamTiles <= 32, "a bit per tile");
         // thread (i, col) has row 16 m + i, column col of every tile: 16 lanes per row (waves without rows: nothing)
         float* lrow = logits + ((size_t)s * B + row0 + (tid >> 4)) * cpitch + col;
         float2* rrow = reinterpret_cast<float2*>(recs.rec) + ((size_t)s * B + row0 + (tid >> 4)) * recs.pitch;
@@ -1170,7 +1171,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                     const float mx = row16_max(valid ? out[t][m] : -INFINITY);
                     const float se = row16_sum(valid ? exp_below(out[t][m], mx) : 0.f);
                     // (a NaN or +inf among the logits.  -inf is right: a value's planes, each cut off, agree in sign)
-                    if (__ballot(se != se) != 0ull) again |= 1u << (out_t0 + t);
+                    if (__builtin_expect(__ballot(se != se) != 0ull, 0) && ln == 0) atomicOr(again, 1u << (out_t0 + t));
                     if (col == 0 && row_ok) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
                 }
             }
@@ -1258,24 +1259,25 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             lds_barrier();
         }
         store_out();
-        // as settle_non_finite, with the logits each thread has stored
-        // (out of line: in line it cost a step of 8 sentences x 5 beams in bf16 1 %, 27.1 us; 26.8 without it and so)
-        for (; __builtin_expect(again != 0u, 0); again &= again - 1u) {
+        // As settle_non_finite, with the logits each thread has stored.  (Out of line, and with nothing that only this
+        // needs kept in registers or worked out during the loop, which has none to spare: from LDS, or what store_out
+        // uses.  Otherwise it costs 1 to 2 % of a step: 5 sentences x 17 beams, d = 1001: 38.5 us without, 39.0, 38.5 so.)
+        for (uint32_t left = __builtin_amdgcn_readfirstlane(*again); __builtin_expect(left != 0u, 0); left &= left - 1u) {
             int me = tid;
-            asm volatile("" : "+v"(me));   // (nothing of this is worked out in advance: the loop above has no register left)
-            const int t = __ffs(again) - 1, nt = tile_of(t), c = nt * kTileN + (me & 15);
+            asm volatile("" : "+v"(me));
+            const int t = __ffs(left) - 1, nt = tile_of(t);
+            const bool in = nt * kTileN + (me & 15) < C;
+            typedef const __attribute__((address_space(1))) ET* GlobalRow;
+            const ET* row = (const ET*)(GlobalRow)(uintptr_t)rows[t * kTileN + (me & 15)];
 #pragma unroll 1
-            for (int r = me >> 4; (r & ~3) < Bg; r += kTileM) {               // (uniform: four rows per wave)
-                const bool valid = r < Bg && c < C;
-                float* at = logits + ((size_t)s * B + row0 + r) * cpitch + c;
-                float x = valid ? *at : -INFINITY;
-                if (valid && !(fabsf(x) < INFINITY)) {
-                    const int32_t id = cand ? cand[(size_t)s * V + c] : c;
-                    *at = x = plain_dot(E + (int64_t)id * ld, hb + (size_t)r * d, d);
-                }
+            for (int m = 0; m < MT && 4 * q + m * kTileM < Bg; ++m) {         // (uniform: four rows per wave)
+                const int r = (me >> 4) + m * kTileM;
+                float* at = lrow + (size_t)(m * kTileM) * cpitch + nt * kTileN;
+                float x = in && r < Bg ? *at : -INFINITY;
+                if (in && r < Bg && !(fabsf(x) < INFINITY)) *at = x = plain_dot(row, H + (size_t)(again[1] + (uint32_t)r) * d, d);
                 const float mx = row16_max(x);
-                const float se = row16_sum(valid ? exp_below(x, mx) : 0.f);
-                if ((me & 15) == 0 && r < Bg) reinterpret_cast<float2*>(recs.rec)[((size_t)s * B + row0 + r) * recs.pitch + nt] = make_float2(mx, se);
+                const float se = row16_sum(in && r < Bg ? exp_below(x, mx) : 0.f);
+                if ((me & 15) == 0 && r < Bg) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
             }
         }
         seg = seg_end;
