@@ -124,6 +124,37 @@ static void check_hlds(int S, int rows, int d) {
         }
 }
 
+// k_logits_stream: its regions as the kernel lays them out (the bits of tiles to settle and their first hidden row sit
+// behind the counts), and the tiles of a sentence dealt to the XCDs, each once.
+static void check_stream(int S) {
+    for (int mt : {1, 2})
+        for (int ksn : {1, 2, 4}) {
+            const size_t ts = stream_ts(ksn, mt), words = (size_t)((S + 2 + 3) & ~3);
+            const size_t ring = 4 * 2 * ts * ksn * 1024, red = 4 * ts * mt * 4 * kWave * 4, rows = kStreamTiles * kTileN * sizeof(void*);
+            CHECK(ring + red + rows + 2 * words * 4 == stream_lds_bytes(S, mt, ksn), "stream regions (S=%d MT=%d KSN=%d)", S, mt, ksn);
+            CHECK((ring + red) % 8 == 0 && words >= (size_t)S + 2, "stream words (S=%d)", S);
+            CHECK(S > 64 || stream_lds_bytes(S, mt, ksn) <= kLdsLimit / 2, "two workgroups do not share a CU");
+        }
+}
+static void check_xcd_tiles() {
+    for (uint32_t n : {0u, 1u, 7u, 8u, 9u, 130u, 1003u})
+        for (uint32_t shared : {0u, 1u, 8u, 62u, 125u, 5000u})
+            for (uint32_t s : {0u, 3u, 13u}) {
+                std::vector<int> seen(n, 0);
+                for (uint32_t x = 0; x < 8; ++x) {
+                    const XcdTiles t = xcd_tiles(n, shared, s, x);
+                    uint32_t before = 0;
+                    for (uint32_t i = 0; i < t.n; ++i) {
+                        const uint32_t tile = xcd_tile(t, x, i);
+                        CHECK(tile < n && (i == 0 || tile > before), "tile %u of %u (XCD %u)", tile, n, x);
+                        if (tile < n) ++seen[tile];
+                        before = tile;
+                    }
+                }
+                for (uint32_t i = 0; i < n; ++i) CHECK(seen[i] == 1, "tile %u of %u dealt %d times", i, n, seen[i]);
+            }
+}
+
 // small_div() of the kernels: (int)((x + 0.5f) * r) with r = the hardware's reciprocal of y, which may
 // differ from the correctly rounded 1 / y by one unit in the last place; checked here with r two
 // units off either way, for every x < 1024 and y <= 1024.
@@ -180,6 +211,10 @@ int main() {
     for (int S : {1, 32, 64, 4096})
         for (int rows : {1, 10, 16, 32})
             for (int d : {8, 50, 1000, 1024, 1026, 4099}) check_hlds(S, rows, d);
+    for (int S : {1, 2, 3, 63, 64, 65, 4096}) check_stream(S);
+    check_xcd_tiles();
+    CHECK(2 * rows_lds_bytes(5) <= kLdsLimit && 2 * few_lds_bytes<float>(3) <= kLdsLimit && 2 * few_lds_bytes<uint16_t>(2) <= kLdsLimit,
+          "full-vocabulary kernels: two workgroups do not share a CU");
     CHECK(estage_lds_bytes() <= kLdsLimit, "estage LDS");
     CHECK(sizeof(SelShared) + 1024 <= 64 * 1024, "static LDS of the selection kernel");
     CHECK(kSelSharedWords * 4 >= sizeof(SelShared), "selection state words");
