@@ -7,10 +7,11 @@
 //   3. Every band's words are grouped by code, ids ascending inside a code: a stable radix sort of
 //      the code alone (words start in id order), up to kRadixBits bits of it per pass -- ONE pass for
 //      codes of up to 12 bits.  k_radix_count, k_radix_scan, k_radix_scatter.
-//   4. The distinct codes ("keys") of a band and where their spans start: with one pass they are the
-//      digits that occur and come out of the scan; otherwise k_key_count / k_key_emit find the span
-//      starts in the sorted codes.
-//   5. Cuckoo insertion, one thread per key, all bands at once (Alcantara et al.'s scheme for
+//   4. The table code -> span.  Direct tables, where all the codes there can be have room for little: both hash
+//      functions are the code itself (direct_band_meta), so that every key has its own slot, no insertion can fail,
+//      and with one pass the slots come straight out of the scan.  Otherwise k_key_count / k_key_emit find the span
+//      starts in the sorted codes ("keys"), and
+//   5. cuckoo insertion follows, one thread per key, all bands at once (Alcantara et al.'s scheme for
 //      two hash functions): a thread swaps its item into its first slot with a 64-bit
 //      atomicExch; if that evicts an item, the thread carries the evicted item to that item's
 //      other slot, and so on.  A chain longer than the limit marks the band as failed; failed bands
@@ -20,26 +21,43 @@
 // What bounds it is the pass over the embedding rows (2); the rest is a chain of short kernels.  Nothing
 // is copied to the host before the whole chain is under way where tables for the most keys a band can have
 // are small or nearly full (lshbeam.hip); parameters are drawn on the device, and one copy of the status words ends the
-// build.  V = 40000, d = 1000 fp32, 8 bands of 12 bits: 125 us, of which 36 us k_row_codes (160 MB at 4.4 TB/s) and
-// 45 us the other kernels; 770 us with a library sort of (band, code, id) keys, ten small copies, three
-// waits and an allocation for every array.
+// build.  V = 40000, d = 1000 fp32, 8 bands of 12 bits, with the first step on the tables: 118 us, of which 36 us
+// k_row_codes (160 MB at 4.4 TB/s), 25 us the sort and the slots (count 4.8, scan 6.5, scatter 11) and 17 us the step;
+// with cuckoo insertion for these codes 156, or 206 where it failed once; with the scan in one workgroup per band and a
+// sum over the chunks in front in every workgroup of the scatter 130.
 #pragma once
 #include "candidates.h"
 
 namespace lshbeam {
 
 constexpr uint64_t kCuckooEmpty = ~0ull;
-constexpr int kRadixThreads = 512, kRadixWaves = kRadixThreads / kWave, kRadixBits = 12, kScanThreads = 1024;
+constexpr int kRadixThreads = 512, kRadixWaves = kRadixThreads / kWave, kRadixBits = 12, kRadixMinChunk = 2048;
+constexpr int kScanDigits = 256;   // digits per workgroup of the scan
 constexpr int kBuildBeginBlocks = 64;   // x extent of k_build_begin; as many "bad permutation" words
 
-// Elements of a band per workgroup of the sort: enough that the digit counters (2^12 of them to write,
-// scan and read per workgroup) do not outweigh the elements, few enough to use the chip.  At most
-// 65535 elements, which the 16-bit counters hold.
-inline int radix_chunk(int64_t V, int W) {
+// A band is cut into chunks, a workgroup of the sort each: every vocabulary slice of the hit-count kernel into
+// `per_slice` of them, so that where the slices begin inside a span is a sum over whole chunks.  Elements per chunk:
+// enough that the digit counters (2^12 of them to write, scan and read per workgroup) do not outweigh the
+// elements, few enough to use the chip, and at most 65535, which the 16-bit counters hold.
+struct RadixChunks {
+    int slice, per_slice, size;
+    __host__ __device__ int count() const { return kHitSlices * per_slice; }
+    __device__ void range(int c, int64_t V, int64_t* begin, int64_t* end) const {
+        const int q = c / per_slice;
+        const int64_t first = (int64_t)q * slice, last = min(first + slice, V);
+        *begin = min(first + (int64_t)(c - q * per_slice) * size, last);
+        *end = min(*begin + size, last);
+    }
+};
+inline RadixChunks radix_chunks(int64_t V, int W) {
     int64_t c = (V * W / 256 + 1023) / 1024 * 1024;
-    if (c < 4096) c = 4096;
+    if (c < kRadixMinChunk) c = kRadixMinChunk;
     if (c > 32768) c = 32768;
-    return (int)c;
+    RadixChunks r;
+    r.slice = hit_slice_words((int)V);
+    r.per_slice = (int)((r.slice + c - 1) / c);
+    r.size = ((r.slice + r.per_slice - 1) / r.per_slice + kWave - 1) / kWave * kWave;
+    return r;
 }
 inline size_t radix_scatter_lds(int digits) { return (size_t)digits * (kRadixWaves * 2 + 4); }
 
@@ -59,12 +77,21 @@ __host__ __device__ inline BandMeta draw_band_meta(uint64_t seed, int w, int W, 
     return m;
 }
 
+// Both hash functions the code itself: a direct table has 2^lg slots for codes of fewer than lg bits.
+__host__ __device__ inline BandMeta direct_band_meta(int w, int lg) {
+    BandMeta m{};
+    m.slot_off = (uint32_t)w << lg;
+    m.shift = 32u - (uint32_t)lg;
+    m.a0 = m.a1 = 1u << m.shift;
+    return m;
+}
+
 // grid (kBuildBeginBlocks, W + 1).  Row w < W: band w's hash parameters and empty table (only the bands
 // flagged in `redo`, if given), its `failed` flag cleared.  Row W (first attempt): the permutations are
-// copied, entries outside [0, d) replaced by 0 and reported (bad_perms[block]), the tickets zeroed.
+// copied, entries outside [0, d) replaced by 0 and reported (bad_perms[block], zeroed before, in host memory), the tickets zeroed.
 __global__ void __launch_bounds__(256)
-k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W, uint32_t cap, int lg, uint64_t seed,
-              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed,
+k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W, uint32_t cap, int lg, bool direct, uint64_t seed,
+              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed, uint32_t* __restrict__ n_keys,
               const int32_t* __restrict__ perms_in, int n_perms, int d, int32_t* __restrict__ perms,
               uint32_t* __restrict__ bad_perms, unsigned int* __restrict__ tickets, int n_tickets) {
     const int w = blockIdx.y, tid = threadIdx.x;
@@ -73,7 +100,8 @@ k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W,
         const bool again = !redo || redo[w];
         if (first == 0) {
             failed[w] = 0u;
-            if (again) bands[w] = draw_band_meta(seed, w, W, attempt, cap, lg);
+            if (n_keys) n_keys[w] = 0u;
+            if (again) bands[w] = direct ? direct_band_meta(w, lg) : draw_band_meta(seed, w, W, attempt, 1u << lg, lg);
         }
         if (again)
             for (uint32_t i = first; i < cap; i += step) table[(size_t)w * cap + i] = kCuckooEmpty;
@@ -91,20 +119,21 @@ k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W,
     }
     for (uint32_t i = first; i < (uint32_t)n_tickets; i += step) tickets[i] = 0u;
     __syncthreads();
-    if (tid == 0) bad_perms[blockIdx.x] = bad;
+    if (tid == 0 && bad) bad_perms[blockIdx.x] = 1u;
 }
 
 // ---- the sort: grid (chunks, W) each ------------------------------------------------------------
 
-// counts[w][chunk][digit] (16 bits, digits in pairs)
+// counts[w][chunk][digit] (16 bits, digits in pairs); groups[w][chunk][group]: their sums over kScanDigits digits
 __global__ void __launch_bounds__(kRadixThreads)
-k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, int chunk, int shift, int digits,
-              uint32_t* __restrict__ counts) {
+k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, RadixChunks ch, int shift, int digits,
+              uint32_t* __restrict__ counts, uint32_t* __restrict__ groups) {
     extern __shared__ uint32_t hist[];
     const int tid = threadIdx.x, w = blockIdx.y, c = blockIdx.x;
     for (int i = tid; i < digits / 2; i += kRadixThreads) hist[i] = 0u;
     __syncthreads();
-    const int64_t begin = (int64_t)c * chunk, end = min(begin + chunk, V);
+    int64_t begin, end;
+    ch.range(c, V, &begin, &end);
     const int32_t* src = codes + (size_t)w * V;
 #pragma unroll 4
     for (int64_t i = begin + tid; i < end; i += kRadixThreads) {
@@ -114,62 +143,88 @@ k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, int chunk
     __syncthreads();
     uint32_t* out = counts + ((size_t)w * gridDim.x + c) * (digits / 2);
     for (int i = tid; i < digits / 2; i += kRadixThreads) out[i] = hist[i];
-}
-
-// Sum over the chunks [0, n) of the counts of two digits.
-__device__ __forceinline__ uint2 sum_counts(const uint32_t* __restrict__ pair, int n, int pitch) {
-    uint32_t lo = 0, hi = 0;
-    int c = 0;
-    for (; c + 8 <= n; c += 8) {
-        uint32_t x[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = pair[(size_t)(c + j) * pitch];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) { lo += x[j] & 0xFFFFu; hi += x[j] >> 16; }
-    }
-    for (; c < n; ++c) { const uint32_t x = pair[(size_t)c * pitch]; lo += x & 0xFFFFu; hi += x >> 16; }
-    return make_uint2(lo, hi);
-}
-
-// One workgroup per band: where the words of each digit start in the band.  EMIT (the only pass): the
-// digits that occur are the band's keys.
-template <bool EMIT>
-__global__ void __launch_bounds__(kScanThreads)
-k_radix_scan(const uint32_t* __restrict__ counts, int chunks, int digits, uint32_t* __restrict__ starts /*[W][digit]*/,
-             int32_t* __restrict__ key_code, uint32_t* __restrict__ key_start, uint32_t key_pitch,
-             uint32_t* __restrict__ n_keys) {
-    constexpr int PER = (1 << kRadixBits) / kScanThreads;    // consecutive digits per thread
-    __shared__ uint32_t wsum[kScanThreads / kWave + 1];
-    const int tid = threadIdx.x, w = blockIdx.x, d0 = tid * PER;
-    const uint32_t* mine = counts + (size_t)w * chunks * (digits / 2) + d0 / 2;
-    uint32_t tot[PER] = {};
-#pragma unroll
-    for (int j = 0; j < PER; j += 2)
-        if (d0 + j < digits) {
-            const uint2 n = sum_counts(mine + j / 2, chunks, digits / 2);
-            tot[j] = n.x; tot[j + 1] = n.y;
+    const int ng = (digits + kScanDigits - 1) / kScanDigits;
+    for (int g = wave_id(); g < ng; g += kRadixWaves) {
+        uint32_t n = 0;
+        for (int i = lane_id(); i < kScanDigits / 2 && g * (kScanDigits / 2) + i < digits / 2; i += kWave) {
+            const uint32_t x = hist[g * (kScanDigits / 2) + i];
+            n += (x & 0xFFFFu) + (x >> 16);
         }
-    uint32_t sum = 0, keys = 0, all;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) { sum += tot[j]; keys += tot[j] ? 1u : 0u; }
-    uint32_t at[PER];
-    at[0] = block_incl_scan(sum, wsum, &all) - sum;
-#pragma unroll
-    for (int j = 1; j < PER; ++j) at[j] = at[j - 1] + tot[j - 1];
-    if constexpr (EMIT) {
-        uint32_t k = block_incl_scan(keys, wsum, &all) - keys;
-        if (tid == 0) n_keys[w] = all;
-#pragma unroll
-        for (int j = 0; j < PER; ++j)
-            if (tot[j]) {
-                key_code[(size_t)w * key_pitch + k] = d0 + j;
-                key_start[(size_t)w * key_pitch + k] = at[j];
-                ++k;
-            }
+        n = wave_sum(n);
+        if (lane_id() == 0) groups[((size_t)w * gridDim.x + c) * ng + g] = n;
     }
+}
+
+// grid (groups of kScanDigits digits, W), a thread per pair of digits: where the words of each digit of each
+// chunk go in the band (starts[w][chunk][digit]).  EMIT (the only pass, direct tables): a digit is a code, its slot is
+// written here, with the places where the vocabulary slices begin in its span (sums over the chunks in front); slots
+// past the codes are empty.
+template <bool EMIT>
+__global__ void __launch_bounds__(kScanDigits / 2)
+k_radix_scan(const uint32_t* __restrict__ counts, const uint32_t* __restrict__ groups, RadixChunks ch, int digits,
+             uint32_t* __restrict__ starts, Slot* __restrict__ slots, uint4* __restrict__ cuts, uint32_t* __restrict__ n_keys) {
+    constexpr int AHEAD = 24;
+    static_assert(kScanDigits / 2 == 2 * kWave && (1 << kRadixBits) / kScanDigits <= 16, "two waves; a lane of 16 per group");
+    __shared__ uint32_t wsum[4];
+    const int tid = threadIdx.x, w = blockIdx.y, g = blockIdx.x, ng = gridDim.x, chunks = ch.count();
+    const int pair = g * (kScanDigits / 2) + tid, pitch = digits / 2;
+    const bool in = pair < pitch;
+    const uint32_t* mine = counts + (size_t)w * chunks * pitch + min(pair, pitch - 1);
+    uint32_t* out = starts + (size_t)w * chunks * digits + 2 * pair;
+    // (the counters and the sums are asked for together: one trip to memory for up to AHEAD chunks)
+    uint32_t x[AHEAD];
+    auto load = [&](int c0) {
 #pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (d0 + j < digits) starts[(size_t)w * digits + d0 + j] = at[j];
+        for (int j = 0; j < AHEAD; ++j) x[j] = mine[(size_t)min(c0 + j, chunks - 1) * pitch];
+    };
+    load(0);
+    uint32_t before = 0;                                        // words of lower groups: 16 lanes per chunk
+    for (int c = tid >> 4; c < chunks; c += kScanDigits / 32)
+        if ((tid & 15) < g) before += groups[((size_t)w * chunks + c) * ng + (tid & 15)];
+    uint32_t lo = 0, hi = 0, cut_lo[3] = {}, cut_hi[3] = {};
+    for (int c0 = 0;;) {
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            if constexpr (EMIT) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (c0 + j == (q + 1) * ch.per_slice) { cut_lo[q] = lo; cut_hi[q] = hi; }
+            }
+            const uint32_t n = c0 + j < chunks ? x[j] : 0u;
+            lo += n & 0xFFFFu; hi += n >> 16;
+        }
+        c0 += AHEAD;
+        if (c0 >= chunks) break;
+        load(c0);
+    }
+    if (!in) lo = hi = 0;
+    // words of lower digits: of the lower groups, and of the lanes and the wave in front
+    const uint32_t incl = wave_incl_scan(lo + hi), keys = wave_sum((lo ? 1u : 0u) + (hi ? 1u : 0u));
+    before = wave_sum(before);
+    if (lane_id() == kWave - 1) { wsum[2 * wave_id()] = incl; wsum[2 * wave_id() + 1] = before; }
+    __syncthreads();
+    const uint32_t at = wsum[1] + wsum[3] + (tid >= kWave ? wsum[0] : 0u) + incl - (lo + hi);
+    if constexpr (EMIT) {
+        if (lane_id() == 0) atomicAdd(&n_keys[w], keys);
+        if (in) {
+            const size_t s0 = (size_t)w * 2 * digits + 2 * pair;
+            slots[s0] = Slot{lo ? 2 * pair : -1, at, lo, 0u};
+            slots[s0 + 1] = Slot{hi ? 2 * pair + 1 : -1, at + lo, hi, 0u};
+            slots[s0 + digits] = slots[s0 + digits + 1] = Slot{-1, 0u, 0u, 0u};
+            cuts[s0] = make_uint4(cut_lo[0], cut_lo[1], cut_lo[2], lo);
+            cuts[s0 + 1] = make_uint4(cut_hi[0], cut_hi[1], cut_hi[2], hi);
+        }
+    }
+    if (!in) return;
+    uint2 run = make_uint2(at, at + lo);
+    for (int c0 = 0; c0 < chunks; c0 += AHEAD) {
+        if (chunks > AHEAD) load(c0);                           // (once more, from the caches)
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) {
+            if (c0 + j < chunks) *reinterpret_cast<uint2*>(out + (size_t)(c0 + j) * digits) = run;
+            run.x += x[j] & 0xFFFFu; run.y += x[j] >> 16;
+        }
+    }
 }
 
 // Stable scatter of one chunk.  A wave owns a contiguous piece of the chunk and has digit counters of
@@ -178,8 +233,8 @@ k_radix_scan(const uint32_t* __restrict__ counts, int chunks, int digits, uint32
 // per digit bit.  (The vector instructions of the ballots bound it -- about 100 per 64 words -- which is why
 // a band is cut into chunks.)  ids_in == null: ids are the positions.
 __global__ void __launch_bounds__(kRadixThreads)
-k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict__ ids_in, int64_t V, int chunk, int shift,
-                int bits, const uint32_t* __restrict__ counts, const uint32_t* __restrict__ starts, int32_t* __restrict__ codes_out,
+k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict__ ids_in, int64_t V, RadixChunks ch, int shift,
+                int bits, const uint32_t* __restrict__ starts, int32_t* __restrict__ codes_out,
                 int32_t* __restrict__ ids_out) {
     extern __shared__ uint32_t rsm[];
     const int digits = 1 << bits;
@@ -189,37 +244,13 @@ k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict_
     const int32_t* src = codes_in + (size_t)w * V;
     uint32_t* wpos32 = rsm + digits;
     for (int i = tid; i < digits * kRadixWaves / 2; i += kRadixThreads) wpos32[i] = 0u;   // (digits >= 2)
-    // where this chunk's words of a digit go: behind those of the chunks in front (all digit pairs of a
-    // thread side by side: every load waits for memory once, not once per pair)
-    {
-        constexpr int PAIRS = (1 << kRadixBits) / 2 / kRadixThreads, BATCH = 4;
-        const uint2* st = reinterpret_cast<const uint2*>(starts + (size_t)w * digits);
-        const uint32_t* cn = counts + (size_t)w * gridDim.x * (digits / 2);
-        const int last = digits / 2 - 1;
-        uint2 at[PAIRS];
-#pragma unroll
-        for (int j = 0; j < PAIRS; ++j) at[j] = st[min(tid + j * kRadixThreads, last)];
-        for (int c0 = 0; c0 < c; c0 += BATCH) {
-            uint32_t x[BATCH][PAIRS];
-#pragma unroll
-            for (int q = 0; q < BATCH; ++q)
-#pragma unroll
-                for (int j = 0; j < PAIRS; ++j)
-                    x[q][j] = c0 + q < c ? cn[(size_t)(c0 + q) * (digits / 2) + min(tid + j * kRadixThreads, last)] : 0u;
-#pragma unroll
-            for (int q = 0; q < BATCH; ++q)
-#pragma unroll
-                for (int j = 0; j < PAIRS; ++j) { at[j].x += x[q][j] & 0xFFFFu; at[j].y += x[q][j] >> 16; }
-        }
-#pragma unroll
-        for (int j = 0; j < PAIRS; ++j)
-            if (tid + j * kRadixThreads <= last) {
-                base[2 * (tid + j * kRadixThreads)] = at[j].x;
-                base[2 * (tid + j * kRadixThreads) + 1] = at[j].y;
-            }
-    }
+    const uint2* st = reinterpret_cast<const uint2*>(starts) + ((size_t)w * gridDim.x + c) * (digits / 2);
+    uint2* base2 = reinterpret_cast<uint2*>(base);
+#pragma unroll 4
+    for (int i = tid; i < digits / 2; i += kRadixThreads) base2[i] = st[i];
     __syncthreads();
-    const int64_t begin = (int64_t)c * chunk, end = min(begin + chunk, V);
+    int64_t begin, end;
+    ch.range(c, V, &begin, &end);
     const int piece = (((int)(end - begin) + kRadixWaves - 1) / kRadixWaves + kWave - 1) / kWave * kWave;
     const int64_t p0 = begin + (int64_t)wv * piece, p1 = min(p0 + piece, end);
     const uint32_t mask = (uint32_t)digits - 1u;
@@ -278,24 +309,25 @@ k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict_
     }
 }
 
-// ---- keys of a band sorted in several passes: grid (chunks, W) -----------------------------------
+// ---- keys of a band, from its sorted codes: grid (chunks, W) ---------------------------------------------
 
 __device__ __forceinline__ bool starts_span(const int32_t* __restrict__ codes, int64_t i) {
     return i == 0 || codes[i] != codes[i - 1];
 }
 // spans[w][chunk]: span starts in the chunk
 __global__ void __launch_bounds__(kRadixThreads)
-k_key_count(const int32_t* __restrict__ codes /*[W, V] sorted*/, int64_t V, int chunk, uint32_t* __restrict__ spans) {
+k_key_count(const int32_t* __restrict__ codes /*[W, V] sorted*/, int64_t V, RadixChunks ch, uint32_t* __restrict__ spans) {
     __shared__ uint32_t wsum[kRadixWaves + 1];
     const int32_t* src = codes + (size_t)blockIdx.y * V;
-    const int64_t begin = (int64_t)blockIdx.x * chunk, end = min(begin + chunk, V);
+    int64_t begin, end;
+    ch.range(blockIdx.x, V, &begin, &end);
     uint32_t n = 0, all;
     for (int64_t i = begin + threadIdx.x; i < end; i += kRadixThreads) n += starts_span(src, i) ? 1u : 0u;
     block_incl_scan(n, wsum, &all);
     if (threadIdx.x == 0) spans[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = all;
 }
 __global__ void __launch_bounds__(kRadixThreads)
-k_key_emit(const int32_t* __restrict__ codes, int64_t V, int chunk, const uint32_t* __restrict__ spans,
+k_key_emit(const int32_t* __restrict__ codes, int64_t V, RadixChunks ch, const uint32_t* __restrict__ spans,
            int32_t* __restrict__ key_code, uint32_t* __restrict__ key_start, uint32_t key_pitch, uint32_t* __restrict__ n_keys) {
     __shared__ uint32_t wsum[kRadixWaves + 1];
     const int tid = threadIdx.x, ln = lane_id(), wv = wave_id(), w = blockIdx.y, c = blockIdx.x;
@@ -303,7 +335,8 @@ k_key_emit(const int32_t* __restrict__ codes, int64_t V, int chunk, const uint32
     uint32_t n = 0, before, mine = 0, all;
     for (int i = tid; i < c; i += kRadixThreads) n += spans[(size_t)w * gridDim.x + i];
     block_incl_scan(n, wsum, &before);                       // keys of the chunks in front
-    const int64_t begin = (int64_t)c * chunk, end = min(begin + chunk, V);
+    int64_t begin, end;
+    ch.range(c, V, &begin, &end);
     const int piece = (((int)(end - begin) + kRadixWaves - 1) / kRadixWaves + kWave - 1) / kWave * kWave;
     const int64_t p0 = begin + (int64_t)wv * piece, p1 = min(p0 + piece, end);
     for (int64_t i = p0 + ln; i < p1; i += kWave) mine += starts_span(src, i) ? 1u : 0u;

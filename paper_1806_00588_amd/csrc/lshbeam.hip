@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -17,6 +18,7 @@
 #include <cctype>
 #include <new>
 #include <string>
+#include <thread>
 #include <type_traits>
 #include <vector>
 
@@ -66,7 +68,7 @@ constexpr int kTicketBlock = 64;    // counters per workspace = sentences of a f
 
 
 struct Band {
-    int n_keys = 0;      // distinct codes
+    int n_keys = 0;      // distinct codes (-1: in n_keys_dev)
     int capacity = 0;    // slots of its cuckoo table
     BandMeta meta{};
 };
@@ -111,6 +113,7 @@ struct lsh_tables {
     Slot* slots_dev = nullptr;       // all bands' cuckoo slots, concatenated
     uint4* cuts_dev = nullptr;       // per slot: where vocabulary slices 1..3 begin in its span
     BandMeta* bands_dev = nullptr;   // [W]
+    uint32_t* n_keys_dev = nullptr;  // [W] distinct codes of each band, where `bands` does not know them
     std::vector<Band> bands;         // what the inspection calls know about each band
     int wg_candidates_lds = 0;
     int wg_fused_lds = 0;
@@ -659,19 +662,22 @@ KeptBlock swap_kept(int dev, KeptKind kind, KeptBlock b) {
     if (b.bytes + others <= kKeptBytes) std::swap(b, g_kept[dev][kind]);
     return b;
 }
-void give_back_kept() {
+size_t give_back_kept(int dev = -1) {   // bytes given back on that device
+    size_t bytes = 0;
     for (int d = 0; d < kMaxDevices; ++d)
         for (int k = 0; k < kKeptKinds; ++k) {
             const KeptBlock b = swap_kept(d, (KeptKind)k, KeptBlock{});
+            if (b.p && d == dev) bytes += b.bytes;
             if (b.p) (void)hipFree(b.p);
         }
+    return bytes;
 }
 // An allocation of a build: where memory has run out, once more without the kept blocks.
 hipError_t alloc_device(void** p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes ? bytes : 1);
     if (e == hipErrorOutOfMemory) {
         (void)hipGetLastError();
-        give_back_kept();
+        (void)give_back_kept();
         e = hipMalloc(p, bytes ? bytes : 1);
     }
     return e;
@@ -796,6 +802,46 @@ struct BuildBlock {  // what a build works in, kept for the next one
     ~BuildBlock() { release_block(dev, kBuildBlock, block, idle); }
 };
 
+// Pinned host words that a build's kernels report to (a copy of them from the device, and the wait for the copy, was
+// 10 us of a build).  One page for the life of the process serves the builds that run at the same time; what it does
+// not hold has memory of its own.
+struct Report {
+    static constexpr int kPlaces = 16;
+    uint32_t* words = nullptr;
+    int place = -1;
+    bool idle = false;   // no kernel that may write to it is under way
+    static std::mutex mu;
+    static uint32_t* page;
+    static uint32_t used;   // bit i: place i
+    hipError_t take() {
+        constexpr size_t n = kBuildBeginBlocks * sizeof(uint32_t);
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            if (!page) {
+                const hipError_t e = hipHostMalloc((void**)&page, kPlaces * n, hipHostMallocPortable);
+                if (e != hipSuccess) { page = nullptr; return e; }
+            }
+            for (int i = 0; i < kPlaces && place < 0; ++i)
+                if (!(used >> i & 1u)) { used |= 1u << i; place = i; words = page + (size_t)i * kBuildBeginBlocks; }
+        }
+        if (place < 0) {
+            const hipError_t e = hipHostMalloc((void**)&words, n, hipHostMallocPortable);
+            if (e != hipSuccess) { words = nullptr; return e; }
+        }
+        std::memset(words, 0, n);
+        return hipSuccess;
+    }
+    ~Report() {
+        if (words && place < 0) (void)hipHostFree(words);   // (waits)
+        if (place < 0 || !idle) return;                     // (a build that failed half-way: the place is lost)
+        std::lock_guard<std::mutex> lock(mu);
+        used &= ~(1u << place);
+    }
+};
+std::mutex Report::mu;
+uint32_t* Report::page = nullptr;
+uint32_t Report::used = 0;
+
 template <typename ET>
 hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, int d, const int32_t* perms, int P, int K,
                             int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride) {
@@ -815,32 +861,48 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     const size_t n_perms = (size_t)t->P * t->K, n_tickets = (size_t)kTicketSlots * kTicketBlock;
     const int code_bits = t->u * t->bits;
     const int passes = (code_bits + kRadixBits - 1) / kRadixBits, pass_bits = (code_bits + passes - 1) / passes;
-    const int digits = 1 << pass_bits, chunk = radix_chunk(V, (int)W), chunks = (int)((V + chunk - 1) / chunk);
-    // a band has at most key_pitch keys; a table has a power of two of at least three slots per key (load
+    const int digits = 1 << pass_bits, groups_n = (digits + kScanDigits - 1) / kScanDigits;
+    const RadixChunks ch = radix_chunks(V, (int)W);
+    const int chunks = ch.count();
+    // a band has at most key_pitch keys; a cuckoo table has a power of two of at least three slots per key (load
     // <= 1/3: two-choice cuckoo insertion then succeeds at the first attempt almost always)
     const uint32_t key_pitch = (uint32_t)std::min<int64_t>(V, (int64_t)1 << code_bits);
+    constexpr uint64_t kSlotBytes = sizeof(Slot) + sizeof(uint4) + sizeof(uint64_t);
     auto lg_for = [](uint32_t keys) { int lg = 1; while ((1ull << lg) < 3ull * keys) ++lg; return lg; };
     int lg = lg_for(key_pitch);
+    // Direct tables, with a slot for every code there can be (and as many empty ones: twice the keys at least), where
+    // they are no larger than cuckoo tables for the keys, or where they are small.  Nothing is inserted there, and
+    // the tables a step probes are half as large or less.  What they save: an insertion that fails ends with its
+    // longest chain, 100 us (12-bit codes that all occur failed the first attempt one build in two: 8 bands, V = 40000,
+    // d = 1000, with the first step: 156 or 206 us, 130 so).  (LSHBEAM_CUCKOO_CHAIN, for the tests of the insertion, asks for cuckoo tables.)
+    const int chain = env_int("LSHBEAM_CUCKOO_CHAIN", -1);
+    auto takes_direct = [&](int cuckoo_lg) {
+        return chain < 0 && (code_bits + 1 <= cuckoo_lg || (passes == 1 && ((uint64_t)W << (code_bits + 1)) * (sizeof(Slot) + sizeof(uint4)) <= (4ull << 20)));
+    };
+    bool direct = takes_direct(lg);
+    if (direct) lg = code_bits + 1;
     // Tables for the most keys there can be, so that nothing has to be known before they are placed, where those are
     // at most 32 MiB (V = 14000, 10 bands of 16-bit codes, 26 MB: 118 us, 141 with the keys counted first: one wait),
     // or where so many words share the codes that hardly one will be missing.  Otherwise the keys are counted: 16-bit
     // codes have room for 65536 keys and 27000 to 42000 come up (V = 100000, 12 bands: 100 MB of slots, 50 for the
     // keys there are; 370 us, 340 so).
-    constexpr uint64_t kSlotBytes = sizeof(Slot) + sizeof(uint4) + sizeof(uint64_t);
     const uint64_t most_bytes = ((uint64_t)W << lg) * kSlotBytes;
     const bool blind = most_bytes <= (32ull << 20) || (V >= 8ll << code_bits && most_bytes <= (1ull << 30));
+    const bool emit = direct && passes == 1 && blind;   // the scan writes the slots
     auto table_bytes = [&]() { return ((uint64_t)W << lg) * sizeof(uint64_t); };
     // A counted table takes the place of what the sort is through with, where that is large enough or can be made so
     // within reason.
     const size_t sort_buf = align_up((size_t)V * W * sizeof(int32_t));
-    const size_t spare_bytes = blind ? (passes > 1 ? sort_buf * std::min(passes, 3) : 0)
-                                     : std::max<size_t>(passes > 1 ? sort_buf * std::min(passes, 3) : 0, std::min<uint64_t>(table_bytes(), 64ull << 20));
+    const size_t sort_spare = passes > 1 ? sort_buf * std::min(passes, 3) : 0;
+    const size_t spare_bytes = blind ? sort_spare : std::max<size_t>(sort_spare, std::min<uint64_t>(table_bytes(), 64ull << 20));
 
-    struct Status { uint32_t *bad, *failed[2], *n_keys; } stat{};
-    uint32_t *status_dev = nullptr, *counts = nullptr, *starts = nullptr, *key_start = nullptr;
+    struct Status { uint32_t *failed[2], *n_keys; } stat{};
+    uint32_t *status_dev = nullptr, *counts = nullptr, *groups = nullptr, *starts = nullptr, *key_start = nullptr;
     uint64_t* table = nullptr;
     int32_t *key_code = nullptr, *code_buf[2] = {}, *id_buf[2] = {};
-    const size_t status_words = kBuildBeginBlocks + 3 * (size_t)W;
+    const size_t status_words = 3 * (size_t)W;
+    Report report;
+    HIP_TRY(report.take());
     BuildBlock work;   // (what only the build needs)
     work.dev = t->device;
     for (int pass = 0; pass < 2; ++pass) {
@@ -848,6 +910,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
         t->perms_dev = c.take<int32_t>(n_perms);
         t->tickets_dev = c.take<unsigned int>(n_tickets);
         t->bands_dev = c.take<BandMeta>(W);
+        t->n_keys_dev = c.take<uint32_t>(W);
         t->codes_dev = c.take<int32_t>((size_t)V * W);
         // 16 bytes of slack: k_hit_rows reads ids with 16-byte loads that may straddle the end
         t->words_dev = c.take<int32_t>((size_t)V * W + 4);
@@ -857,16 +920,19 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
         }
         Carver b{(char*)work.block.p};
         status_dev = b.take<uint32_t>(status_words);
-        if (blind) table = b.take<uint64_t>((size_t)W << lg);
+        if (blind && !emit) table = b.take<uint64_t>((size_t)W << lg);
         counts = b.take<uint32_t>((size_t)W * chunks * (digits / 2));
-        starts = b.take<uint32_t>((size_t)W * digits);
-        key_code = b.take<int32_t>((size_t)W * key_pitch);
-        key_start = b.take<uint32_t>((size_t)W * key_pitch);
+        groups = b.take<uint32_t>((size_t)W * chunks * groups_n);
+        starts = b.take<uint32_t>((size_t)W * chunks * digits);
+        if (!emit) {
+            key_code = b.take<int32_t>((size_t)W * key_pitch);
+            key_start = b.take<uint32_t>((size_t)W * key_pitch);
+        }
         char* spare = b.take<char>(spare_bytes);
-        if (passes > 1) {   // (pass p writes code_buf[p % 2] and, but for the last, id_buf[p % 2])
+        if (!emit) {        // (pass p writes code_buf[p % 2] and, but for the last, id_buf[p % 2])
             code_buf[(passes - 1) & 1] = b.take<int32_t>((size_t)V * W);
-            code_buf[passes & 1] = (int32_t*)spare;
-            id_buf[0] = spare ? (int32_t*)(spare + sort_buf) : nullptr;
+            code_buf[passes & 1] = passes > 1 ? (int32_t*)spare : nullptr;
+            id_buf[0] = spare && passes > 1 ? (int32_t*)(spare + sort_buf) : nullptr;
             id_buf[1] = spare && passes > 2 ? (int32_t*)(spare + 2 * sort_buf) : nullptr;
         }
         if (!blind) table = (uint64_t*)spare;
@@ -875,17 +941,17 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
             HIP_TRY(take_block(t->device, kBuildBlock, b.bytes, &work.block));
         }
     }
-    stat.bad = status_dev;
-    stat.n_keys = stat.bad + kBuildBeginBlocks;
-    stat.failed[0] = stat.n_keys + W;
+    stat.n_keys = emit ? t->n_keys_dev : status_dev;
+    stat.failed[0] = status_dev + W;
     stat.failed[1] = stat.failed[0] + W;
     DevBuf late;
 
     const dim3 begin_grid(kBuildBeginBlocks, (unsigned)W + 1), b256(256);
     auto begin = [&](int attempt, const uint32_t* redo, bool with_tables) {
         hipLaunchKernelGGL(k_build_begin, begin_grid, b256, 0, st, table, t->bands_dev, (int)W,
-                           with_tables ? 1u << lg : 0u, lg, seed, attempt, redo, stat.failed[attempt & 1],
-                           attempt || (with_tables && !blind) ? nullptr : perms_in, (int)n_perms, t->d, t->perms_dev, stat.bad,
+                           with_tables && !emit ? 1u << lg : 0u, lg, direct, seed, attempt, redo, stat.failed[attempt & 1],
+                           emit ? stat.n_keys : nullptr,
+                           attempt || (with_tables && !blind) ? nullptr : perms_in, (int)n_perms, t->d, t->perms_dev, report.words,
                            t->tickets_dev, (int)n_tickets);
     };
     begin(0, nullptr, blind);
@@ -894,48 +960,69 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
         : launch_row_codes<uint16_t>(st, (const uint16_t*)t->E, t->ld, V, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V));
 
     std::vector<uint32_t> status(status_words);
-    auto read_status = [&]() -> lsh_status {
-        HIP_TRY(hipMemcpyAsync(status.data(), status_dev, status_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    auto wait = [&]() -> lsh_status {
         HIP_TRY(hipStreamSynchronize(st));
-        work.idle = true;   // (until the next launch)
+        work.idle = report.idle = true;   // (until the next launch)
         for (int i = 0; i < kBuildBeginBlocks; ++i)
-            if (status[i]) return LSH_ERR_INVALID_ARG;
+            if (report.words[i]) return LSH_ERR_INVALID_ARG;
         return LSH_OK;
     };
-    const uint32_t* keys_h = status.data() + kBuildBeginBlocks;
+    auto read_status = [&]() -> lsh_status {
+        HIP_TRY(hipMemcpyAsync(status.data(), status_dev, status_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+        return wait();
+    };
+    const uint32_t* keys_h = status.data();
     SplitMix64 host_rng{seed};
     if (on_host) {
         const lsh_status rc = read_status();
         return rc != LSH_OK ? rc : build_on_host(t, st, host_rng);
     }
 
-    const dim3 sort_grid((unsigned)chunks, (unsigned)W), sort_block(kRadixThreads), scan_block(kScanThreads);
+    const dim3 sort_grid((unsigned)chunks, (unsigned)W), sort_block(kRadixThreads);
     HIP_TRY(allow_whole_lds<k_radix_scatter>());
     const int32_t *codes_in = t->codes_dev, *ids_in = nullptr;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * pass_bits;
-        hipLaunchKernelGGL(k_radix_count, sort_grid, sort_block, (size_t)digits * 2, st, codes_in, V, chunk, shift, digits, counts);
-        if (passes == 1)
-            hipLaunchKernelGGL(k_radix_scan<true>, dim3((unsigned)W), scan_block, 0, st, counts, chunks, digits, starts, key_code,
-                               key_start, key_pitch, stat.n_keys);
+        hipLaunchKernelGGL(k_radix_count, sort_grid, sort_block, (size_t)digits * 2, st, codes_in, V, ch, shift, digits, counts, groups);
+        const dim3 scan_grid((unsigned)groups_n, (unsigned)W), scan_block(kScanDigits / 2);
+        if (emit)
+            hipLaunchKernelGGL(k_radix_scan<true>, scan_grid, scan_block, 0, st, (const uint32_t*)counts, (const uint32_t*)groups, ch,
+                               digits, starts, t->slots_dev, t->cuts_dev, stat.n_keys);
         else
-            hipLaunchKernelGGL(k_radix_scan<false>, dim3((unsigned)W), scan_block, 0, st, counts, chunks, digits, starts, nullptr,
-                               nullptr, 0u, nullptr);
+            hipLaunchKernelGGL(k_radix_scan<false>, scan_grid, scan_block, 0, st, (const uint32_t*)counts, (const uint32_t*)groups, ch,
+                               digits, starts, nullptr, nullptr, nullptr);
         int32_t* ids_out = p == passes - 1 ? t->words_dev : id_buf[p & 1];
-        hipLaunchKernelGGL(k_radix_scatter, sort_grid, sort_block, radix_scatter_lds(digits), st, codes_in, ids_in, V, chunk,
-                           shift, pass_bits, counts, starts, code_buf[p & 1], ids_out);
+        hipLaunchKernelGGL(k_radix_scatter, sort_grid, sort_block, radix_scatter_lds(digits), st, codes_in, ids_in, V, ch,
+                           shift, pass_bits, (const uint32_t*)starts, code_buf[p & 1], ids_out);
         codes_in = code_buf[p & 1];
         ids_in = ids_out;
     }
-    if (passes > 1) {   // (the counters are free again: at least one per chunk and band)
-        hipLaunchKernelGGL(k_key_count, sort_grid, sort_block, 0, st, codes_in, V, chunk, counts);
-        hipLaunchKernelGGL(k_key_emit, sort_grid, sort_block, 0, st, codes_in, V, chunk, (const uint32_t*)counts, key_code,
-                           key_start, key_pitch, stat.n_keys);
+    t->bands.resize(W);
+    auto finish = [&](auto&& n_keys, auto&& meta) {
+        for (int64_t w = 0; w < W; ++w) {
+            t->bands[w].n_keys = n_keys(w);
+            t->bands[w].capacity = 1 << lg;
+            t->bands[w].meta = meta(w);
+        }
+        t->built_on_device = 1;
+        return LSH_OK;
+    };
+    if (emit) {
+        HIP_TRY(hipGetLastError());
+        const lsh_status rc = wait();
+        t->build_attempts = 1;
+        return rc != LSH_OK ? rc : finish([](int64_t) { return -1; }, [&](int64_t w) { return direct_band_meta((int)w, lg); });
     }
+    // (the counters are free again: at least one per chunk and band)
+    hipLaunchKernelGGL(k_key_count, sort_grid, sort_block, 0, st, codes_in, V, ch, counts);
+    hipLaunchKernelGGL(k_key_emit, sort_grid, sort_block, 0, st, codes_in, V, ch, (const uint32_t*)counts, key_code,
+                       key_start, key_pitch, stat.n_keys);
     if (!blind) {
         lsh_status rc = read_status();
         if (rc != LSH_OK) return rc;
         lg = lg_for(*std::max_element(keys_h, keys_h + W));
+        direct = takes_direct(lg);
+        if (direct) lg = code_bits + 1;
         if (((uint64_t)W << lg) >= (1ull << 32)) return build_on_host(t, st, host_rng);
         rc = place_slots(t, (uint64_t)W << lg);
         if (rc != LSH_OK) return rc;
@@ -943,17 +1030,17 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
             HIP_TRY(late.alloc(table_bytes()));
             table = (uint64_t*)late.p;
         }
-        work.idle = false;
+        work.idle = report.idle = false;
         begin(0, nullptr, true);
     }
     // LSHBEAM_CUCKOO_CHAIN shortens the eviction chains (tests of the retry and fallback paths)
-    const int max_chain = env_int("LSHBEAM_CUCKOO_CHAIN", 16 * (lg + 1));
+    const int max_chain = chain >= 0 ? chain : 16 * (lg + 1);
     const dim3 insert_grid((key_pitch + 255) / 256, (unsigned)W), slot_grid(((1u << lg) + 255) / 256, (unsigned)W);
     std::vector<int> drawn(W, 0);   // the attempt whose parameters each band has
     for (int attempt = 0; attempt < 24; ++attempt) {
         t->build_attempts = attempt + 1;
         const uint32_t* redo = attempt ? stat.failed[(attempt - 1) & 1] : nullptr;
-        work.idle = false;
+        work.idle = report.idle = false;
         if (attempt) begin(attempt, redo, true);
         hipLaunchKernelGGL(k_cuckoo_insert, insert_grid, b256, 0, st, table, (const BandMeta*)t->bands_dev,
                            (const int32_t*)key_code, key_pitch, (const uint32_t*)stat.n_keys, max_chain, redo,
@@ -968,14 +1055,9 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
             if (status[(stat.failed[(attempt - 1) & 1] - status_dev) + w]) drawn[w] = attempt;
         const uint32_t* failed_h = status.data() + (stat.failed[attempt & 1] - status_dev);
         if (std::any_of(failed_h, failed_h + W, [](uint32_t f) { return f != 0; })) continue;
-        t->bands.resize(W);
-        for (int64_t w = 0; w < W; ++w) {
-            t->bands[w].n_keys = (int)keys_h[w];
-            t->bands[w].capacity = 1 << lg;
-            t->bands[w].meta = draw_band_meta(seed, (int)w, (int)W, drawn[w], 1u << lg, lg);
-        }
-        t->built_on_device = 1;
-        return LSH_OK;
+        return finish([&](int64_t w) { return (int)keys_h[w]; }, [&](int64_t w) {
+            return direct ? direct_band_meta((int)w, lg) : draw_band_meta(seed, (int)w, (int)W, drawn[w], 1u << lg, lg);
+        });
     }
     return build_on_host(t, st, host_rng);
 }
@@ -1148,7 +1230,17 @@ void lsh_free_tables(lsh_tables* t) {
     delete t;
 }
 
-void lsh_release_kept(void) { give_back_kept(); }
+void lsh_release_kept(void) {
+    // (hipMemGetInfo shows a released block up to some milliseconds late; who asks for the memory may look there first)
+    size_t before = 0, now = 0, total = 0;
+    int dev = -1;
+    const bool look = hipGetDevice(&dev) == hipSuccess && hipMemGetInfo(&before, &total) == hipSuccess;
+    const size_t bytes = give_back_kept(dev) >> 21 << 21;
+    for (int i = 0; look && bytes && i < 100; ++i) {
+        if (hipMemGetInfo(&now, &total) != hipSuccess || now >= before + bytes) break;
+        std::this_thread::sleep_for(std::chrono::microseconds(200));
+    }
+}
 
 lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const lsh_build_params* p,
                             void* hip_stream, lsh_tables** out) {
@@ -1321,20 +1413,30 @@ lsh_status lsh_debug_bucket(const lsh_tables* t, int32_t band, int32_t code, int
     return LSH_OK;
 }
 
+// Distinct codes of a band.
+static lsh_status keys_of_band(const lsh_tables* t, int32_t band, int32_t* n) {
+    *n = t->bands[band].n_keys;
+    if (*n < 0) HIP_TRY(hipMemcpy(n, t->n_keys_dev + band, sizeof(int32_t), hipMemcpyDeviceToHost));
+    return LSH_OK;
+}
+
 lsh_status lsh_debug_csr(const lsh_tables* t, int32_t band, int32_t* n_keys_out, int32_t* keys_host,
                          int32_t* offsets_host, int32_t cap_keys, int32_t* words_host) {
     if (!t || band < 0 || band >= t->W || !n_keys_out) return LSH_ERR_INVALID_ARG;
     const Band& b = t->bands[band];
-    *n_keys_out = b.n_keys;
-    if (keys_host && offsets_host && cap_keys >= b.n_keys) {
+    int32_t n_keys = 0;
+    const lsh_status rc = keys_of_band(t, band, &n_keys);
+    if (rc != LSH_OK) return rc;
+    *n_keys_out = n_keys;
+    if (keys_host && offsets_host && cap_keys >= n_keys) {
         // the used slots of the band's cuckoo table, in key order
         std::vector<Slot> slots(b.capacity);
         HIP_TRY(hipMemcpy(slots.data(), t->slots_dev + b.meta.slot_off, slots.size() * sizeof(Slot), hipMemcpyDeviceToHost));
         slots.erase(std::remove_if(slots.begin(), slots.end(), [](const Slot& x) { return x.key < 0; }), slots.end());
         std::sort(slots.begin(), slots.end(), [](const Slot& x, const Slot& y) { return x.key < y.key; });
-        if ((int)slots.size() != b.n_keys) return LSH_ERR_BUILD_FAILED;
-        for (int i = 0; i < b.n_keys; ++i) { keys_host[i] = slots[i].key; offsets_host[i] = (int32_t)slots[i].start; }
-        offsets_host[b.n_keys] = b.n_keys ? (int32_t)(slots[b.n_keys - 1].start + slots[b.n_keys - 1].len) : 0;
+        if ((int)slots.size() != n_keys) return LSH_ERR_BUILD_FAILED;
+        for (int i = 0; i < n_keys; ++i) { keys_host[i] = slots[i].key; offsets_host[i] = (int32_t)slots[i].start; }
+        offsets_host[n_keys] = n_keys ? (int32_t)(slots[n_keys - 1].start + slots[n_keys - 1].len) : 0;
     }
     if (words_host)
         HIP_TRY(hipMemcpy(words_host, t->words_dev + (size_t)band * t->V, (size_t)t->V * sizeof(int32_t),
@@ -1353,8 +1455,7 @@ lsh_status lsh_debug_cuckoo_shape(const lsh_tables* t, int32_t band, int32_t* ca
                                   int32_t* n_keys_out) {
     if (!t || band < 0 || band >= t->W || !capacity_out || !n_keys_out) return LSH_ERR_INVALID_ARG;
     *capacity_out = t->bands[band].capacity;
-    *n_keys_out = t->bands[band].n_keys;
-    return LSH_OK;
+    return keys_of_band(t, band, n_keys_out);
 }
 
 lsh_status lsh_debug_candidates(const lsh_tables* t, const void* workspace_dev,

@@ -47,6 +47,29 @@ def test_build_matches_the_oracle(shape):
             assert np.array_equal(gc.tables.debug_bucket(w, int(k)), gc.index.bucket(w, int(k)))
 
 
+@pytest.mark.parametrize("V", [1, 127, 129, 513, 2048 * 4 + 1, 40001])
+def test_slices_of_direct_tables(V):
+    """Codes few enough for direct tables: the slots and the places where the vocabulary slices begin in every span
+    come out of the sort's counters.  The hit-count kernel reads both: its lists at V around the edges of slices and of
+    the sort's chunks, and those of the cuckoo tables a short chain asks for, against the oracle's."""
+    import os
+    d, K, u, W, B, t = 24, 4, 2, 9, 3, 3
+    rng = np.random.default_rng(V)
+    E = rng.standard_normal((V, d)).astype(np.float32)
+    perms = np.stack([rng.permutation(d)[:K] for _ in range(u * W)]).astype(np.int32)
+    H = rng.standard_normal((B, d)).astype(np.float32)
+    bs = np.zeros(B, np.float32)
+    for chain in (None, "64"):
+        if chain:
+            os.environ["LSHBEAM_CUCKOO_CHAIN"] = chain
+        try:
+            gc = GpuCase(E, perms, np.arange(min(V, 3), dtype=np.int32), W)
+        finally:
+            os.environ.pop("LSHBEAM_CUCKOO_CHAIN", None)
+        _, _, _, sp, ws = gc.step(H, bs, 1, B, threshold=t)
+        assert np.array_equal(gc.tables.debug_candidates(ws, sp, 0), gc.oracle_sentence(H, bs, B, threshold=t).cand)
+
+
 def test_permutations_out_of_range_are_refused():
     import paper_1806_00588_amd as lsh
     E = to_dev(np.random.default_rng(0).standard_normal((500, 12)).astype(np.float32))
