@@ -636,14 +636,14 @@ __host__ __device__ __forceinline__ uint32_t tiles_mod8(uint32_t begin, uint32_t
 }
 __host__ __device__ __forceinline__ XcdTiles xcd_tiles(uint32_t ntiles, uint32_t shared, uint32_t s, uint32_t x) {
     XcdTiles t;
-    const uint32_t cut = shared < ntiles ? shared : ntiles, r1 = (x - s) & 7u;
+    const uint32_t cut = shared < ntiles ? shared : ntiles, m = ntiles - cut;
     t.n0 = tiles_mod8(0u, cut, x);
-    t.first1 = ((cut + 7u - r1) >> 3) * 8u + r1;
-    t.n = t.n0 + tiles_mod8(cut, ntiles, r1);
+    t.first1 = cut + m * x / 8u;
+    t.n = t.n0 + (cut + m * (x + 1u) / 8u - t.first1);
     return t;
 }
 __host__ __device__ __forceinline__ uint32_t xcd_tile(const XcdTiles& t, uint32_t x, uint32_t i) {   // its i-th
-    return i < t.n0 ? x + 8u * i : t.first1 + 8u * (i - t.n0);
+    return i < t.n0 ? x + 8u * i : t.first1 + (i - t.n0);
 }
 
 // Eight hidden values as the A operands of three v_mfma_f32_16x16x32_bf16: their planes.
@@ -967,124 +967,201 @@ __device__ __forceinline__ void load_to_lds16(const void* from, void* to) {
     const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
 }
-constexpr int kStreamTiles = 32;   // tiles of a stretch whose rows' addresses are in LDS
-constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? 1 : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
+// The same to LDS address base + PLUS, with an offset in the instruction, which counts on both sides.
+template <int PLUS, int OFF> __device__ __forceinline__ void load_to_lds16_at(const void* from, uint32_t base) {
+    asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%3" ::"s"(base), "v"(from), "n"(PLUS - OFF), "n"(OFF) : "m0", "memory", "scc");
+}
+// 4 bytes per lane.
+__device__ __forceinline__ void load_to_lds4(const void* from, void* to) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
+}
+constexpr int kStreamTiles = 32;   // tiles of a block, whose candidates come to LDS together
+constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? (MT == 1 ? 2 : 1) : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
 // Workgroups per CU: LDS (52 KB at most) and the registers of the A operands.
-constexpr int stream_wgs(bool bf16, int MT, int KSN, int PARTS) { return (bf16 ? 3 : 1) * MT * KSN * PARTS * 4 <= (bf16 ? 96 : 80) ? 3 : 2; }
+constexpr int stream_wgs(bool bf16, int MT, int KSN, int PARTS) { return KSN == 4 && MT == 1 ? 2 : (bf16 ? 3 : 1) * MT * KSN * PARTS * 4 <= (bf16 ? 96 : 80) ? 3 : 2; }
 __host__ __device__ inline size_t stream_lds_bytes(int S, int MT, int KSN) {
     const size_t ts = stream_ts(KSN, MT);
     return 4 * 2 * ts * KSN * 1024 + 4 * ts * MT * 4 * kWave * 4 + kStreamTiles * kTileN * 8 + (size_t)(2 * ((S + 2 + 3) & ~3)) * 4;
 }
 template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+// f(integral_constant 0), ..., f(integral_constant N - 1)
+template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>{});
+        static_for<N, I + 1>(f);
+    }
+}
 
 template <typename ET, int MT, int KSN, int PARTS>
 __global__ void __launch_bounds__(256, (stream_wgs(sizeof(ET) == 2, MT, KSN, PARTS)))
 k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
                 int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence; <= 16 MT*/,
-                int wgs /*workgroups per XCD and row group*/, int ngroups, int shared,
-                const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
+                int wgs /*workgroups per XCD and row group*/, int ngroups, int per /*... and sentence; 0: all tiles cut evenly*/,
+                int shared, const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
                 float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
     constexpr bool BF = sizeof(ET) == 2;
-    constexpr int VEC = ElemTraits<ET>::VEC, KSTEP = 4 * VEC, TS = stream_ts(KSN, MT);
+    constexpr int VEC = ElemTraits<ET>::VEC, KSTEP = 4 * VEC;
     constexpr int PP = 4 * KSN;                                               // 16-byte pieces of a row in a unit
     static_assert(KSN == 1 || KSN == 2 || KSN == 4, "");
     constexpr int SH = PP == 4 ? 2 : PP == 8 ? 1 : 0;
+    constexpr int TS = KSN == 4 ? 1 : stream_ts(KSN, MT);                     // tiles of a unit
+    constexpr int RING = KSN == 4 ? 2 * stream_ts(KSN, MT) : 2;               // units' places per wave
+    constexpr int GT = stream_ts(KSN, MT), GU = GT / TS;                      // tiles whose quarters are summed together; their units of a part
     // 16-byte registers of A operands per step and row group: fp32 values; their three bf16 planes; for two parts
-    // of those registers run out, and the values are split when they are used
+    // those registers run out, and the values are split when they are used
     constexpr bool LATE = BF && PARTS > 2;
     constexpr int NH = LATE ? 2 : BF ? 3 : 1;
     constexpr int NI = TS * KSN;                                              // load instructions of a unit, KiB of its place
+    constexpr int RPI = kWave / PP;                                           // rows per load instruction
     extern __shared__ uint4 ssm[];
+    // (the ring behind other things: the address in M0 is its place less the load's offset, and must not be negative)
     char* sm = reinterpret_cast<char*>(ssm);
-    float (*red)[TS][MT][4][kWave] = reinterpret_cast<float (*)[TS][MT][4][kWave]>(sm + 8 * NI * 1024);   // [wave]
-    const ET** rows = reinterpret_cast<const ET**>(sm + 8 * NI * 1024 + 4 * TS * MT * 4 * kWave * 4);   // [tile][16]
-    uint32_t* tile_pref = reinterpret_cast<uint32_t*>(rows + kStreamTiles * kTileN);  // [S + 1], then "own"
-    uint32_t* counts = tile_pref + ((S + 2 + 3) & ~3);                                // [S]
-    uint32_t* again = counts + S;   // [2]: a bit for every tile of the stretch with logits to settle; its first hidden row
-    static_assert(kStreamTiles <= 32, "a bit per tile");
+    float (*red)[GT][MT][4][kWave] = reinterpret_cast<float (*)[GT][MT][4][kWave]>(sm);   // [wave]
+    constexpr size_t RED = (size_t)4 * GT * MT * 4 * kWave * 4;
+    static_assert(RED >= (PARTS - 1) * KSN * 64, "");
+    int32_t* ids = reinterpret_cast<int32_t*>(sm + RED + 4 * RING * NI * 1024);       // [two blocks of tiles][16]
+    uint32_t* tile_pref = reinterpret_cast<uint32_t*>(ids + 2 * kStreamTiles * kTileN);   // [S + 1]
+    uint32_t* counts = tile_pref + ((S + 2 + 3) & ~3);                                    // [S]
     // grid = 8 * wgs * ngroups; ids go round the XCDs, the row groups of one block of tiles follow each other on one
-    const uint32_t xcd = blockIdx.x & 7u, slot = blockIdx.x >> 3;
-    const uint32_t bx = slot / (uint32_t)ngroups;
-    const int row0 = (int)(slot % (uint32_t)ngroups) * group_rows, Bg = min(group_rows, B - row0);
+    const uint32_t xcd = blockIdx.x & 7u, slot_x = blockIdx.x >> 3;
+    const uint32_t bx = slot_x / (uint32_t)ngroups;
+    const int row0 = (int)(slot_x % (uint32_t)ngroups) * group_rows, Bg = min(group_rows, B - row0);
     const int tid = threadIdx.x, ln = lane_id(), q = __builtin_amdgcn_readfirstlane(wave_id());   // q: the wave's quarter of k
     const int col = ln & 15, kq = ln >> 4;
-    char* ring = sm + q * (2 * NI * 1024);
+    char* ring = sm + RED + q * (RING * NI * 1024);
+    const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
-    LSH_TRACE(1, 0);
-    // Who takes what.  All tiles of all sentences in a row, cut evenly: then a workgroup may change sentences, which
-    // takes as long as a few tiles.  Or every sentence's tiles cut into stretches of at most `most` -- the fewest
-    // that need no more workgroups than there are -- where that is not much longer than the even share ("own").
-    // tile_pref counts tiles or, own, workgroups.
-    if (q == 0) {
-        uint32_t carry = 0;
-        bool own = false;
-        for (int base = 0; base < S; base += kWave) {
-            const int s = base + ln;
-            const int C = s < S ? (count ? count[s] : V) : 0;
-            uint32_t n = s < S ? xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd).n : 0u;
-            if (S <= min(wgs, kWave)) {
-                constexpr uint32_t kSwitch = KSN * PARTS >= 8 ? 1u : 8u / (KSN * PARTS);
-                const uint32_t even = max((wave_sum(n) + (uint32_t)wgs - 1) / (uint32_t)wgs, 1u);
-                for (uint32_t most = even; most <= even + kSwitch && !own; ++most) {
-                    const uint32_t need = n ? (uint32_t)(int)(((float)(n + most) - 0.5f) * __builtin_amdgcn_rcpf((float)most)) : 0u;   // ceil
-                    if (wave_sum(need) <= (uint32_t)wgs) { own = true; n = need; }
-                }
+    LSH_TRACE_WG(0);
+    // Who takes what.  Every sentence has `per` workgroups of this XCD, workgroup i of them the tiles i, i + per, ... of
+    // those the XCD has of the sentence; or (more sentences than workgroups, or hardly fewer) all tiles of all
+    // sentences in a row, cut evenly.
+    int s = 0;
+    uint32_t first = 0, every = 1, seg = 0, seg_end = 0, wg_end = 0;
+    if (per > 0) {
+        s = (int)(bx / (uint32_t)per);
+        first = bx - (uint32_t)s * (uint32_t)per;
+        every = (uint32_t)per;
+        // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
+        const char* hb = reinterpret_cast<const char*>(H + ((size_t)s * B + row0) * d);
+        for (uint32_t at = tid * 128u; at < (uint32_t)(Bg * d) * 4u; at += 256u * 128u) load_to_lds4(hb + at, ring);
+    } else {
+        if (q == 0) {
+            uint32_t carry = 0;
+            for (int base = 0; base < S; base += kWave) {
+                const int sl = base + ln;
+                const int C = sl < S ? (count ? count[sl] : V) : 0;
+                const uint32_t n = sl < S ? xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)sl, xcd).n : 0u;
+                const uint32_t incl = wave_incl_scan(n);
+                if (sl < S) { tile_pref[sl] = carry + incl - n; counts[sl] = (uint32_t)C; }
+                carry += wave_read_lane(incl, kWave - 1);
             }
-            const uint32_t incl = wave_incl_scan(n);
-            if (s < S) { tile_pref[s] = carry + incl - n; counts[s] = (uint32_t)C; }
-            carry += wave_read_lane(incl, kWave - 1);
+            if (ln == 0) tile_pref[S] = carry;
         }
-        if (ln == 0) { tile_pref[S] = carry; tile_pref[S + 1] = own; }
+        __syncthreads();
+        const uint32_t total = tile_pref[S], per_wg = (total + (uint32_t)wgs - 1) / (uint32_t)wgs;
+        seg = min(total, bx * per_wg);
+        wg_end = min(total, seg + per_wg);
+        if (seg == wg_end) return;
     }
     const int nks = (d + KSTEP - 1) / KSTEP, nst = (nks + 3) >> 2, k0 = q * nst * KSTEP;   // steps of a wave's quarter
-    __syncthreads();
-    LSH_TRACE(1, 1);
+    // parts of which the wave's quarter has every piece, inside the row
+    uint32_t whole_parts = 0;
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p)
+        if (nst - p * KSN >= KSN && k0 + (p + 1) * KSN * KSTEP <= d) whole_parts |= 1u << p;
     // piece (4 st + kq) of row col: the low two bits of st change lanes' places, the others move on
     const char* place[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) place[j] = ring + (col * PP + (((4 * j + kq) & (PP - 1)) ^ (col >> SH))) * 16;
-    auto sentence_of = [&](uint32_t at) {   // last s with tile_pref[s] <= at
-        int lo = 0, hi = S;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (tile_pref[mid] <= at) lo = mid; else hi = mid;
-        }
-        return __builtin_amdgcn_readfirstlane(lo);
-    };
-    auto xcd_tiles_of = [&](int s) { return xcd_tiles(ntiles_of((int)counts[s]), (uint32_t)shared, (uint32_t)s, xcd); };
-    const uint32_t total = tile_pref[S];
-    const bool own = __builtin_amdgcn_readfirstlane((int)tile_pref[S + 1]) != 0;
-    uint32_t wg_begin, wg_end;               // own: tiles of its sentence on this XCD; else of all of them
-    if (own) {
-        if (bx >= total) return;
-        const int s = sentence_of(bx);
-        const uint32_t n = xcd_tiles_of(s).n, w = tile_pref[s + 1] - tile_pref[s], i = bx - tile_pref[s];
-        wg_begin = i * n / w;                // (n < 2^20, w <= 64)
-        wg_end = (i + 1) * n / w;
-    } else {
-        const uint32_t per_wg = (total + (uint32_t)wgs - 1) / (uint32_t)wgs;
-        wg_begin = min(total, bx * per_wg);
-        wg_end = min(total, wg_begin + per_wg);
-    }
-    for (uint32_t seg = wg_begin; seg < wg_end;) {
-        const int s = sentence_of(own ? bx : seg);
-        const uint32_t pref = own ? 0u : tile_pref[s];
-        const uint32_t seg_end = min(own ? wg_end : min(wg_end, tile_pref[s + 1]), seg + kStreamTiles);
-        const int C = __builtin_amdgcn_readfirstlane((int)counts[s]);
-        const XcdTiles xt = xcd_tiles_of(s);
-        const int n = (int)(seg_end - seg);                                   // tiles of this stretch
-        auto tile_of = [&](int t) { return (int)xcd_tile(xt, xcd, seg + (uint32_t)t - pref); };
-        constexpr int PER = kStreamTiles * kTileN / 256;
-        int32_t my_id[PER];
+    // instruction i of a tile brings its pieces 64 i .. 64 i + 63: row i RPI + lr, piece swz ^ (i RPI >> SH)
+    const int lr = ln / PP, swz = (ln % PP) ^ (lr >> SH);
+    uint32_t loff[KSN];                                                       // byte of its row a lane brings in part 0
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if (i * 256 >= n * kTileN) break;   // (uniform)
-            const int c = min(tile_of(min(i * 16 + (tid >> 4), n - 1)) * kTileN + col, C - 1);   // clamped columns are never stored
-            my_id[i] = cand ? cand[(size_t)s * V + c] : c;
+    for (int i = 0; i < KSN; ++i) loff[i] = (uint32_t)(16 * (swz ^ (i * RPI >> SH))) + (uint32_t)(k0 * (int)sizeof(ET));
+    const uint32_t ld_bytes = (uint32_t)(ld * (int64_t)sizeof(ET));           // (the host: below 2^31)
+    for (;;) {
+        int C;
+        if (per > 0) {
+            C = __builtin_amdgcn_readfirstlane(count ? count[s] : V);
+        } else {
+            int lo = 0, hi = S;                                               // last sentence with tile_pref <= seg
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (tile_pref[mid] <= seg) lo = mid; else hi = mid;
+            }
+            s = __builtin_amdgcn_readfirstlane(lo);
+            C = __builtin_amdgcn_readfirstlane((int)counts[s]);
+            first = seg - tile_pref[s];
+            seg_end = min(wg_end, tile_pref[s + 1]);
         }
-        __builtin_amdgcn_sched_barrier(0);
+        const XcdTiles xt = xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd);
+        if (per > 0 && xt.n <= first) { wait_vmem<0>(); return; }
+        const int n = __builtin_amdgcn_readfirstlane((int)(per > 0 ? (xt.n - first + every - 1) / every : seg_end - seg));   // tiles
+        auto tile_of = [&](int t) __attribute__((always_inline)) { return (int)xcd_tile(xt, xcd, first + (uint32_t)t * every); };
+        // candidates of block b (kStreamTiles tiles): two loads per wave
+        auto load_ids = [&](int b) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < kStreamTiles * kTileN / 256; ++j) {
+                const int e = q * (kStreamTiles * kTileN / 4) + j * kWave;
+                const int c = min(tile_of(min(b * kStreamTiles + (e + ln) / kTileN, n - 1)) * kTileN + col, C - 1);   // clamped columns are never stored
+                int32_t* to = ids + (b & 1) * kStreamTiles * kTileN + e;
+                if (cand) load_to_lds4(cand + (size_t)s * V + c, to); else to[ln] = c;
+            }
+        };
+        load_ids(0);
+        wait_vmem<0>();
+        lds_barrier();
+        LSH_TRACE_WG(1);
+        const int groups = (n + GT - 1) / GT, sets = (n + TS - 1) / TS, units = sets * PARTS;
+        // unit u = part u % PARTS of the TS tiles of set u / PARTS; ptr: the addresses of its tiles' part 0
+        const char* ptr[TS][KSN];
+        auto address = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < TS; ++t) {
+                const int32_t* at = ids + (min(g * TS + t, n - 1) & (2 * kStreamTiles - 1)) * kTileN + lr;
+#pragma unroll
+                for (int i = 0; i < KSN; ++i) ptr[t][i] = reinterpret_cast<const char*>(E) + ((uint64_t)(uint32_t)at[i * RPI] * ld_bytes + loff[i]);
+            }
+        };
+        // where a lane's pieces of a unit's part are: ptr, but for pieces past the quarter (not needed) and past the row,
+        // which are the row's last chunk
+        const char* from[TS][KSN];
+        auto locate = [&](auto part_c) __attribute__((always_inline)) {
+            constexpr int part = decltype(part_c)::value;
+            const bool is_whole = whole_parts >> part & 1u;                   // (uniform)
+#pragma unroll
+            for (int i = 0; i < KSN; ++i) {
+                int64_t move = 0;
+                if (!is_whole) {
+                    int p = swz ^ (i * RPI >> SH);
+                    asm volatile("" : "+v"(p));   // (every part's offsets worked out in advance would take too many registers)
+                    const int left = 4 * (nst - part * KSN);
+                    const int k = p < left ? min(k0 + part * (KSN * KSTEP) + p * VEC, d - VEC) : d - VEC;
+                    move = k * (int)sizeof(ET) - (int)loff[i] - part * KSN * 64;
+                }
+#pragma unroll
+                for (int t = 0; t < TS; ++t) from[t][i] = is_whole ? ptr[t][i] : ptr[t][i] + move;
+            }
+        };
+        // the loads of a unit of that part, step i of its tiles; at: LDS address of its place
+        auto fill1 = [&](auto part_c, uint32_t at, auto i_c) __attribute__((always_inline)) {
+            constexpr int off = decltype(part_c)::value * KSN * 64, i = decltype(i_c)::value;
+            static_for<TS>([&](auto t) __attribute__((always_inline)) {
+                load_to_lds16_at<(decltype(t)::value * KSN + i) * 1024, off>(from[decltype(t)::value][i], at);
+            });
+        };
+        static_for<RING>([&](auto u_c) __attribute__((always_inline)) {
+            constexpr int u = decltype(u_c)::value;
+            using Part = std::integral_constant<int, u % PARTS>;
+            if (u < units) {
+                if constexpr (u % PARTS == 0) address(u / PARTS);
+                locate(Part{});
+                static_for<KSN>([&](auto i) __attribute__((always_inline)) { fill1(Part{}, ring_at + u * (NI * 1024), i); });
+            }
+        });
         // A operands: hidden row col of every row group (clamped: results dropped), zeros past d; a partial chunk
-        // holds the row's last VEC values, those counted already replaced by zero, as `fill` reads it
+        // holds the row's last VEC values, those counted already replaced by zero, as `fill1` reads it
         uint4 h[MT][PARTS * KSN][NH];
         const float* hb = H + ((size_t)s * B + row0) * d;
 #pragma unroll
@@ -1110,97 +1187,98 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                 else h[m][st][0] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
             }
         }
-        __builtin_amdgcn_sched_barrier(0);                                    // (waited for before the units' loads are issued)
-#pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            if (i * 256 >= n * kTileN) break;
-            rows[i * 256 + tid] = E + (int64_t)my_id[i] * ld;
-        }
-        if (tid == 0) { again[0] = 0u; again[1] = (uint32_t)(s * B + row0); }
-        lds_barrier();
-        // unit u = part u % PARTS of the tiles (u / PARTS) TS ..; instruction i of a tile brings its pieces 64 i .. 64 i + 63
-        const int units = (n + TS - 1) / TS * PARTS;
-        auto fill = [&](int u) {
-            const int part = PARTS == 1 ? 0 : u % PARTS, t0 = (PARTS == 1 ? u : u / PARTS) * TS;
-            char* to = ring + (u & 1) * (NI * 1024);
-            const int left = 4 * min(nst - part * KSN, KSN), k1 = k0 + part * (KSN * KSTEP);   // pieces (>= 4), first k
-            const bool simple = left == PP && k1 + KSN * KSTEP <= d;          // (uniform)
-            constexpr int RPI = kWave / PP;                                   // rows per instruction
-            const int lr = ln / PP;
-            int swz = (ln % PP) ^ (lr >> SH);                                 // (row i RPI + lr: piece swz ^ (i RPI >> SH))
-            asm volatile("" : "+v"(swz));   // (every part's offsets worked out in advance would take too many registers)
-#pragma unroll
-            for (int t = 0; t < TS; ++t) {
-                if (t0 + t >= n) break;   // (uniform)
-                const ET* row[KSN];
-#pragma unroll
-                for (int i = 0; i < KSN; ++i) row[i] = rows[(t0 + t) * kTileN + i * RPI + lr];
-                char* at = to + t * (KSN * 1024);
-                if (simple) {
-#pragma unroll
-                    for (int i = 0; i < KSN; ++i)
-                        load_to_lds16(reinterpret_cast<const char*>(row[i]) + ((uint32_t)((16 * swz) ^ (16 * (i * RPI >> SH))) + (uint32_t)(k1 * (int)sizeof(ET))),
-                                      at + i * 1024);
-                } else {                  // pieces past the quarter: not loaded; past the row: its last chunk
-#pragma unroll
-                    for (int i = 0; i < KSN; ++i) {
-                        const int p = swz ^ (i * RPI >> SH);
-                        if (p < left) load_to_lds16(row[i] + min(k1 + p * VEC, d - VEC), at + i * 1024);
-                    }
-                }
-            }
-        };
-        auto whole = [&](int u) { return u < units && (PARTS == 1 ? u : u / PARTS) * TS + TS <= n; };   // NI loads were issued
-        fill(0);
-        if (units > 1) fill(1);
-        float out[TS][MT];
-        int out_t0 = -1;                                                      // first tile of `out`
+        __builtin_amdgcn_s_waitcnt(0x0F70);                                   // vmcnt(0): the compiler must not wait for them in the loop
+        __builtin_amdgcn_sched_barrier(0);
+        LSH_TRACE_WG(2);
+        float out[GT][MT];
         // thread (i, col) has row 16 m + i, column col of every tile: 16 lanes per row (waves without rows: nothing)
         float* lrow = logits + ((size_t)s * B + row0 + (tid >> 4)) * cpitch + col;
         float2* rrow = reinterpret_cast<float2*>(recs.rec) + ((size_t)s * B + row0 + (tid >> 4)) * recs.pitch;
-        auto store_out = [&]() {
-#pragma unroll
-            for (int t = 0; t < TS; ++t) {
-                if (out_t0 + t >= n) break;
-                const int nt = tile_of(out_t0 + t);
-#pragma unroll
-                for (int m = 0; m < MT; ++m) {
-                    if (4 * q + m * kTileM >= Bg) break;                      // (uniform)
-                    const bool row_ok = (tid >> 4) + m * kTileM < Bg, valid = row_ok && nt * kTileN + col < C;
-                    if (valid) lrow[(size_t)(m * kTileM) * cpitch + nt * kTileN] = out[t][m];
-                    const float mx = row16_max(valid ? out[t][m] : -INFINITY);
-                    const float se = row16_sum(valid ? exp_below(out[t][m], mx) : 0.f);
-                    // (a NaN or +inf among the logits.  -inf is right: a value's planes, each cut off, agree in sign)
-                    if (__builtin_expect(__ballot(se != se) != 0ull, 0) && ln == 0) atomicOr(again, 1u << (out_t0 + t));
-                    if (col == 0 && row_ok) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
+        uint32_t again = 0;                                                   // a bit for every tile of the block with logits to settle
+        // As settle_non_finite, with the logits each thread has stored, for the tiles of a block.
+        auto settle = [&](int t0) __attribute__((always_inline)) {
+            for (uint32_t left = again; left; left &= left - 1u) {
+                int me = tid;
+                asm volatile("" : "+v"(me));   // (nothing of this is kept in registers during the loop)
+                const int t = t0 + __ffs(left) - 1, nt = tile_of(t);
+                const bool in = nt * kTileN + (me & 15) < C;
+                const ET* row = E + (int64_t)ids[(t & (2 * kStreamTiles - 1)) * kTileN + (me & 15)] * ld;
+#pragma unroll 1
+                for (int m = 0; m < MT && 4 * q + m * kTileM < Bg; ++m) {     // (uniform: four rows per wave)
+                    const int r = (me >> 4) + m * kTileM;
+                    float* at = lrow + (size_t)(m * kTileM) * cpitch + nt * kTileN;
+                    float x = in && r < Bg ? *at : -INFINITY;
+                    if (in && r < Bg && !(fabsf(x) < INFINITY)) *at = x = plain_dot(row, hb + (size_t)r * d, d);
+                    const float mx = row16_max(x);
+                    const float se = row16_sum(in && r < Bg ? exp_below(x, mx) : 0.f);
+                    if ((me & 15) == 0 && r < Bg) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
                 }
             }
+            again = 0;
         };
-        floatx4 acc[TS][MT];
-        for (int u0 = 0; u0 < units; u0 += PARTS) {
+        // (without branches up to the stores: the tiles' chains of dependent instructions run side by side)
+        auto store_out = [&](int g) __attribute__((always_inline)) {
+            if (4 * q >= Bg) return;                                          // (uniform)
+            float mx[GT][MT], se[GT][MT];
+            int nt[GT];
+            bool valid[GT][MT];
 #pragma unroll
-            for (int t = 0; t < TS; ++t)
+            for (int t = 0; t < GT; ++t) {
+                nt[t] = tile_of(g * GT + t);
 #pragma unroll
-                for (int m = 0; m < MT; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int m = 0; m < MT; ++m)
+                    valid[t][m] = (tid >> 4) + m * kTileM < Bg && g * GT + t < n && nt[t] * kTileN + col < C;
+            }
 #pragma unroll
-            for (int part = 0; part < PARTS; ++part) {
-                const int u = u0 + part;
-                // (the unit's own loads are older than the next unit's NI; a shorter or no next unit: all of them)
-                if (whole(u + 1)) wait_vmem<NI>(); else wait_vmem<0>();
-                if (part == 0 && out_t0 >= 0) store_out();
-                const int at = (u & 1) * (NI * 1024);
-                const int steps = PARTS * KSN == 1 ? 1 : min(nst - part * KSN, KSN);
-                auto operand = [&](int t, int st) {
-                    return *reinterpret_cast<const uint4*>(place[st & 3] + at + t * (KSN * 1024) + (st >> 2) * 256);
-                };
+            for (int t = 0; t < GT; ++t)
 #pragma unroll
-                for (int t = 0; t < TS; ++t) {
-                    uint4 e_next = operand(t, 0);
+                for (int m = 0; m < MT; ++m) mx[t][m] = row16_max(valid[t][m] ? out[t][m] : -INFINITY);
 #pragma unroll
-                    for (int st = 0; st < KSN; ++st) {
-                        if (st >= steps) break;   // (uniform)
-                        const uint4 e = e_next;
-                        if (st + 1 < KSN) e_next = operand(t, st + 1);
+            for (int t = 0; t < GT; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) se[t][m] = row16_sum(valid[t][m] ? exp_below(out[t][m], mx[t][m]) : 0.f);
+#pragma unroll
+            for (int t = 0; t < GT; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) {
+                    if (valid[t][m]) lrow[(size_t)(m * kTileM) * cpitch + nt[t] * kTileN] = out[t][m];
+                    // (column 0 of a tile is always a candidate)
+                    if (valid[t][m] && col == 0) rrow[(size_t)(m * kTileM) * recs.pitch + nt[t]] = make_float2(mx[t][m], se[t][m]);
+                    // (a NaN or +inf among the logits.  -inf is right: a value's planes, each cut off, agree in sign)
+                    if (__builtin_expect(__ballot(se[t][m] != se[t][m]) != 0ull, 0)) again |= 1u << ((g * GT + t) & (kStreamTiles - 1));
+                }
+            // (a block's candidates are replaced a barrier after its last tile at the earliest)
+            const int last = min(g * GT + GT, n) - 1;
+            if (__builtin_expect(again != 0u, 0) && ((last & (kStreamTiles - 1)) == kStreamTiles - 1 || last == n - 1)) settle(last & ~(kStreamTiles - 1));
+        };
+        floatx4 acc[GT][MT];
+        uint32_t slot = 0;                                                    // byte of the ring where the next unit is
+        // The units of a group.  STEADY: every one of them is there and is followed by another RING units on.
+        auto contract = [&](auto steady_c, int g) __attribute__((always_inline)) {
+            constexpr bool STEADY = decltype(steady_c)::value;
+            static_for<GU * PARTS>([&](auto i_c) __attribute__((always_inline)) {
+                constexpr int part = decltype(i_c)::value % PARTS, gu = decltype(i_c)::value / PARTS, next = (part + RING) % PARTS;
+                using Next = std::integral_constant<int, next>;
+                if (!STEADY && gu > 0 && g * GU + gu >= sets) return;         // (uniform: the last group's)
+                const int u = (g * GU + gu) * PARTS + part;
+                // (the unit's own loads are older than those of the units behind it, NI each)
+                if (STEADY || u + RING - 1 < units) wait_vmem<(RING - 1) * NI>(); else wait_vmem<0>();
+                uint4 ev[TS][KSN];
+#pragma unroll
+                for (int t = 0; t < TS; ++t)
+#pragma unroll
+                    for (int st = 0; st < KSN; ++st)
+                        ev[t][st] = *reinterpret_cast<const uint4*>(place[st & 3] + slot + t * (KSN * 1024) + (st >> 2) * 256);
+                const bool more = STEADY || u + RING < units;
+                if constexpr (next == 0) address(min(g * GU + gu + (part + RING) / PARTS, sets - 1));
+                locate(Next{});
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // (every operand has left the unit's place)
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<KSN>([&](auto st_c) __attribute__((always_inline)) {
+                    constexpr int st = decltype(st_c)::value;
+#pragma unroll
+                    for (int t = 0; t < TS; ++t) {
+                        const uint4 e = ev[t][st];
                         const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
                         if constexpr (BF) {
 #pragma unroll
@@ -1217,8 +1295,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                                 }
 #pragma unroll
                                 for (int p = 0; p < 3; ++p)
-                                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hp[p]),
-                                                                                        __builtin_bit_cast(bf16x8, e), acc[t][m], 0, 0, 0);
+                                    acc[gu * TS + t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hp[p]),
+                                                                                        __builtin_bit_cast(bf16x8, e), acc[gu * TS + t][m], 0, 0, 0);
                             }
                         } else {
 #pragma unroll
@@ -1227,17 +1305,27 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                                 for (int m = 0; m < MT; ++m) {
                                     const uint4 hv = h[m][part * KSN + st][0];
                                     const uint32_t hx = x == 0 ? hv.x : x == 1 ? hv.y : x == 2 ? hv.z : hv.w;
-                                    acc[t][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(hx), __uint_as_float(ew[x]), acc[t][m], 0, 0, 0);
+                                    acc[gu * TS + t][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(hx), __uint_as_float(ew[x]), acc[gu * TS + t][m], 0, 0, 0);
                                 }
                         }
                     }
-                }
-                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // (every operand has left the unit's place)
-                __builtin_amdgcn_sched_barrier(0);
-                if (u + 2 < units) fill(u + 2);
-            }
+                    // the next unit for this place, its loads between the matrix instructions
+                    if (more) fill1(Next{}, ring_at + slot, st_c);
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                slot = slot + NI * 1024 == RING * NI * 1024 ? 0u : slot + NI * 1024;
+            });
+        };
+        for (int g = 0;; ++g) {
+            if (g > 0) store_out(g - 1);
+            if (g == groups) break;
 #pragma unroll
-            for (int t = 0; t < TS; ++t)
+            for (int t = 0; t < GT; ++t)
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+            if ((g + 1) * (GU * PARTS) + RING <= units) contract(std::true_type{}, g); else contract(std::false_type{}, g);
+#pragma unroll
+            for (int t = 0; t < GT; ++t)
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
 #pragma unroll
@@ -1246,7 +1334,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             // thread (i, col) sums row i, column col of every tile: 16 lanes per row
             const int i = tid >> 4;
 #pragma unroll
-            for (int t = 0; t < TS; ++t)
+            for (int t = 0; t < GT; ++t)
 #pragma unroll
                 for (int m = 0; m < MT; ++m) {
                     if (4 * q + m * kTileM >= Bg) { out[t][m] = 0.f; continue; }
@@ -1255,35 +1343,16 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                     for (int w = 0; w < 4; ++w) sum += red[w][t][m][i & 3][(i >> 2) * 16 + col];
                     out[t][m] = sum;
                 }
-            out_t0 = u0 / PARTS * TS;
+            // the candidates of the next block, once this one is under way (every wave is through with the one before)
+            if ((g * GT & (kStreamTiles - 1)) == GT && g * GT / kStreamTiles * kStreamTiles + kStreamTiles < n) load_ids(g * GT / kStreamTiles + 1);
             lds_barrier();
         }
-        store_out();
-        // As settle_non_finite, with the logits each thread has stored.  (Out of line, and with nothing that only this
-        // needs kept in registers or worked out during the loop, which has none to spare: from LDS, or what store_out
-        // uses.  Otherwise it costs 1 to 2 % of a step: 5 sentences x 17 beams, d = 1001: 38.5 us without, 39.0, 38.5 so.)
-        for (uint32_t left = __builtin_amdgcn_readfirstlane(*again); __builtin_expect(left != 0u, 0); left &= left - 1u) {
-            int me = tid;
-            asm volatile("" : "+v"(me));
-            const int t = __ffs(left) - 1, nt = tile_of(t);
-            const bool in = nt * kTileN + (me & 15) < C;
-            typedef const __attribute__((address_space(1))) ET* GlobalRow;
-            const ET* row = (const ET*)(GlobalRow)(uintptr_t)rows[t * kTileN + (me & 15)];
-#pragma unroll 1
-            for (int m = 0; m < MT && 4 * q + m * kTileM < Bg; ++m) {         // (uniform: four rows per wave)
-                const int r = (me >> 4) + m * kTileM;
-                float* at = lrow + (size_t)(m * kTileM) * cpitch + nt * kTileN;
-                float x = in && r < Bg ? *at : -INFINITY;
-                if (in && r < Bg && !(fabsf(x) < INFINITY)) *at = x = plain_dot(row, H + (size_t)(again[1] + (uint32_t)r) * d, d);
-                const float mx = row16_max(x);
-                const float se = row16_sum(in && r < Bg ? exp_below(x, mx) : 0.f);
-                if ((me & 15) == 0 && r < Bg) rrow[(size_t)(m * kTileM) * recs.pitch + nt] = make_float2(mx, se);
-            }
-        }
+        LSH_TRACE_WG(15);
+        if (per > 0) return;
         seg = seg_end;
-        if (seg < wg_end) __syncthreads();                                    // (the table of rows is read no more)
+        if (seg == wg_end) return;
+        __syncthreads();                                                      // (the candidates are read no more)
     }
-    LSH_TRACE(1, 4);
 }
 
 // 33..64 beams, fp32 rows, d <= 1024: the operands change places.  The hidden rows do not fit in

@@ -431,7 +431,7 @@ template <typename ET> StreamPlan stream_plan(int d) {
 // than there are; the spills cost less than the other kernel does: 32 sentences x 10 beams, V = 40000, 34 us against
 // 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
 template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
-    if (!has_chunks(t)) return 0;
+    if (!has_chunks(t) || t->ld * (int64_t)sizeof(ET) >= (int64_t)1 << 31) return 0;
     const StreamPlan p = stream_plan<ET>(t->d);
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
     const bool two = p.parts <= (sizeof(ET) == 2 ? 1 : 4) && sp->B > kTileM;
@@ -447,11 +447,14 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     // tiles that surely lie among the top-frequent words (T distinct ones, where they are the lowest ids); a
     // few such tiles are not worth the uneven shares of the XCDs
     const int shared = cand && sp->T >= 32 * kTileN ? sp->T / kTileN : 0;
-    const int wgs = (int)std::min<int64_t>((tiles_n + 7) / 8, std::max(1, t->option(kOptLogitsGrid, 256 * stream_wgs(sizeof(ET) == 2, rows > kTileM ? 2 : 1, p.ksn, p.parts)) / 8 / ngroups));
+    int wgs = (int)std::min<int64_t>((tiles_n + 7) / 8, std::max(1, t->option(kOptLogitsGrid, 256 * stream_wgs(sizeof(ET) == 2, rows > kTileM ? 2 : 1, p.ksn, p.parts)) / 8 / ngroups));
+    int per = wgs / sp->S;
+    if (per * sp->S * 4 < wgs * 3) per = 0;
+    if (per) wgs = per * sp->S;
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \
     launch(cx, 1, k_logits_stream<ET, MTV, KSNV, PV>, dim3(8 * wgs * ngroups), dim3(256), stream_lds_bytes(sp->S, MTV, KSNV), \
-           (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, shared, cand, count, t->V, w.logits, w.cpitch, \
-           w.records())
+           (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per, shared, cand, count, t->V, w.logits, \
+           w.cpitch, w.records())
 #define LSH_STREAM2(KSNV, PV) do { if (rows > kTileM) LSH_STREAM(2, KSNV, PV); else LSH_STREAM(1, KSNV, PV); } while (0)
     if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2) LSH_STREAM2(2, 1); else if (p.parts == 1) LSH_STREAM2(4, 1);
     else if constexpr (sizeof(ET) == 2) switch (p.parts) { case 2: LSH_STREAM(1, 4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; default: LSH_STREAM(1, 4, 4); }

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import workloads
-from gpu_harness import GpuCase
+from gpu_harness import GpuCase, assert_close_logprobs, assert_topb_matches
 from test_gpu_parity import run_and_check
 
 pytestmark = pytest.mark.gpu
@@ -66,3 +66,40 @@ def test_longer_rows_end_in_a_split_round(d, bf16):
     for S, B in [(9, 3), (9, 17)]:
         H = (3.0 * rng.standard_normal((S * B, d))).astype(np.float32)
         run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("S,d", [(40, 600), (100, 300), (40, 40)])
+def test_tiles_cut_evenly(S, d, bf16):
+    """Sentences that would leave many workgroups without work, or more of them than workgroups: all tiles in a row,
+    a workgroup goes from one sentence to the next."""
+    rng, gc = _case(3000, d, 1500, bf16)
+    H = (3.0 * rng.standard_normal((S * 3, d))).astype(np.float32)
+    run_and_check(None, gc, H, rng.standard_normal(S * 3).astype(np.float32), S, 3)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("B,d", [(3, 130), (3, 300), (18, 300)])
+def test_lists_of_several_blocks(B, d, bf16):
+    """Lists so long that a workgroup takes its candidates in several blocks, with masked words (logits that are made
+    again) in the first, a middle and the last block."""
+    S, V = 60, 12000
+    rng, gc = _case(V, d, V, bf16)
+    E = gc.E.copy()
+    masked = [5, 16 * 8 * 34, V - 3]
+    E[masked, 7] = 0xFF80 if bf16 else -np.inf
+    gc = GpuCase(E, gc.perms, np.arange(V, dtype=np.int32), 3)
+    H = (3.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+    H[:, 7] = 1.0
+    bs = rng.standard_normal(S * B).astype(np.float32)
+    gb, gw, gs, sp, ws = gc.step(H, bs, S, B)
+    for s in (0, 17, S - 1):
+        rows = slice(s * B, (s + 1) * B)
+        with np.errstate(invalid="ignore"):
+            ref = gc.oracle_sentence(H[rows], bs[rows], B)
+        lp = gc.tables.debug_logprobs(ws, sp, s, cap=len(ref.cand))
+        assert np.all(np.isneginf(lp[:, masked]))
+        ref.lp[:, masked] = ref.logits[:, masked] = -1e30
+        lp[:, masked] = -1e30
+        assert_close_logprobs(lp, ref)
+        assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
