@@ -95,91 +95,118 @@ __device__ __forceinline__ void cuckoo_find_slice(const Slot* __restrict__ slots
 // them to LDS in 16-byte pieces, a wave per row; one thread per (row, permutation) takes the windowed
 // argmax there (strict '>', so the lowest k wins a tie; a permutation's window positions stay in
 // registers from row to row), one per (row, band) packs the codes, first code in the most significant
-// bits.  The floor is one pass over the rows: a thread per (row, band) gathering from memory took 151 us
-// for V = 40000, d = 1000, P = 32, K = 8 (160 MB), this takes 36 (55 with one row's loads in flight per
-// wave); bf16, V = 200000, d = 1024, P = 64, K = 16 (410 MB): 158 us, the windows' LDS reads counting as much.
-// LDS: rows x pitch bytes (a multiple of 16), then rows x P 16-bit codes.
+// bits.  The floor is one pass over the rows.  AHEAD (one permutation per thread, so that nothing else is read from
+// memory): a workgroup stays for many groups of rows, and the next one is on its way, straight to the other half of
+// its LDS, while this one is hashed.  V = 40000, d = 1000, P = 32, K = 8 (160 MB): 36 -> 30 us, 5.4 TB/s
+// (a thread per (row, band) gathering from memory took 151).
+// LDS: rows x pitch bytes (a multiple of 16; AHEAD: twice), then rows x P 16-bit codes.
 constexpr int kRowCodeThreads = 256, kRowCodeWindow = 16;   // (longer windows are read again for every row)
 inline size_t row_codes_pitch(int d, size_t elem) { return ((size_t)d * elem + 15) & ~(size_t)15; }
-inline size_t row_codes_lds(int rows, int d, size_t elem, int P) { return rows * (row_codes_pitch(d, elem) + 2 * (size_t)P); }
-// Rows per workgroup: up to 16 while four workgroups fit a CU and there are two workgroups per CU.
-inline int row_codes_lg_rows(int64_t n, int d, size_t elem, int P) {
+inline size_t row_codes_lds(int rows, int d, size_t elem, int P, bool ahead) {
+    return rows * ((ahead ? 2 : 1) * row_codes_pitch(d, elem) + 2 * (size_t)P);
+}
+// Window positions in registers, room for two rows; and few permutations: with more the windows' LDS reads bound the
+// kernel, and fewer, larger groups of rows do better (bf16, V = 200000, d = 1024: 64 permutations 109 us, 132 AHEAD;
+// V = 150000, d = 300, 60: 59, 63; fp32, V = 100000, d = 1000, 48 of 16 positions: 122, 97; d = 512 bf16, 24: 33, 28;
+// d = 64, 16: 32, 23).
+constexpr int kRowCodeAheadP = 48;
+inline bool row_codes_ahead(int d, size_t elem, int P, int K) {
+    return P <= kRowCodeAheadP && K <= kRowCodeWindow && row_codes_lds(1, d, elem, P, true) <= 78 * 1024;
+}
+// Rows per workgroup, at most 16.  AHEAD: as few as have a window for every thread.  Otherwise as many as leave room for
+// four workgroups on a CU and for two on every CU.
+inline int row_codes_lg_rows(int64_t n, int d, size_t elem, int P, bool ahead) {
     int lg = 4;
-    const size_t lds = P > kRowCodeThreads ? 78 * 1024 : 39 * 1024;   // (many permutations: their loads are shared by more rows)
-    while (lg > 0 && (row_codes_lds(1 << lg, d, elem, P) > lds || (n >> lg) < 512)) --lg;
+    if (ahead)
+        while (lg > 0 && (P << (lg - 1)) >= kRowCodeThreads) --lg;
+    const size_t lds = ahead || P > kRowCodeThreads ? 78 * 1024 : 39 * 1024;   // (many permutations: their loads are shared by more rows)
+    while (lg > 0 && (row_codes_lds(1 << lg, d, elem, P, ahead) > lds || (n >> lg) < 512)) --lg;
     return lg;
 }
-template <typename ET>
+template <typename ET, bool AHEAD>
 __global__ void __launch_bounds__(kRowCodeThreads)
 k_row_codes(const ET* __restrict__ X, int64_t ld, int64_t n, int d, const int32_t* __restrict__ perms, int P, int K,
             int W, int bits, int lg_rows, int32_t* __restrict__ out, int64_t row_stride, int64_t band_stride) {
-    constexpr int CK = 16 / (int)sizeof(ET), NW = kRowCodeThreads / kWave, AHEAD = 8;
+    constexpr int CK = 16 / (int)sizeof(ET), NW = kRowCodeThreads / kWave;
     extern __shared__ uint4 row_sm[];
     const int rows = 1 << lg_rows, pitch = (int)((d * sizeof(ET) + 15) & ~(size_t)15);
-    char* stage = reinterpret_cast<char*>(row_sm);
-    uint16_t* codes = reinterpret_cast<uint16_t*>(stage + (size_t)rows * pitch);   // [rows][P]
-    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
-    const int64_t row0 = (int64_t)blockIdx.x << lg_rows;
-    const int nch = d / CK;
-    const int rw = __builtin_amdgcn_readfirstlane(wv);
-    // the wave's rows rw, rw + NW, ... as one run of pieces of up to 64 chunks, AHEAD pieces in flight
-    for (int r = rw, c = 0; nch > 0 && r < rows;) {
-        Chunk16U<ET> v[AHEAD];
-        int r1 = r, c1 = c;
+    char* half[2] = {reinterpret_cast<char*>(row_sm), reinterpret_cast<char*>(row_sm) + (AHEAD ? (size_t)rows * pitch : 0)};
+    uint16_t* codes = reinterpret_cast<uint16_t*>(half[1] + (size_t)rows * pitch);   // [rows][P]
+    const int tid = threadIdx.x, ln = lane_id(), rw = __builtin_amdgcn_readfirstlane(wave_id());
+    const int nch = d / CK, rest = d - nch * CK, u = P / W;
+    const int64_t groups = (n + rows - 1) >> lg_rows;
+    constexpr int MOST = 16 / NW;   // rows of a wave
+    ET tail[MOST];                  // the elements behind a row's whole chunks, a lane each
+    auto load = [&](int64_t g, char* to) {
 #pragma unroll
-        for (int j = 0; j < AHEAD; ++j) {
-            if (r1 >= rows) break;   // (uniform)
-            v[j] = *reinterpret_cast<const Chunk16U<ET>*>(X + min(row0 + r1, n - 1) * ld + (size_t)CK * min(c1 + ln, nch - 1));
-            c1 += kWave;
-            if (c1 >= nch) { c1 = 0; r1 += NW; }
+        for (int j = 0; j < MOST; ++j) {
+            const int r = rw + j * NW;
+            if (r >= rows) break;   // (uniform)
+            const ET* row = X + min((g << lg_rows) + r, n - 1) * ld;
+            if (ln < rest) tail[j] = row[nch * CK + ln];
+            for (int p = 0; p < nch; p += kWave)
+                if (p + ln < nch) load_to_lds16(row + (size_t)CK * (p + ln), to + (size_t)r * pitch + 16 * p);
         }
+    };
+    auto argmax = [&](const ET* row, const int (&idx)[kRowCodeWindow], const int32_t* pm) {
+        float v[kRowCodeWindow];
 #pragma unroll
-        for (int j = 0; j < AHEAD; ++j) {
-            if (r >= rows) break;
-            if (c + ln < nch)
-                *reinterpret_cast<uint4*>(stage + (size_t)r * pitch + 16 * (c + ln)) = make_uint4(v[j].w[0], v[j].w[1], v[j].w[2], v[j].w[3]);
-            c += kWave;
-            if (c >= nch) { c = 0; r += NW; }
+        for (int k = 0; k < kRowCodeWindow; ++k)
+            if (k < K) v[k] = elem_f32(row + idx[k]);   // (uniform)
+        int best = 0;
+        float bv = v[0];
+#pragma unroll
+        for (int k = 1; k < kRowCodeWindow; ++k)
+            if (k < K && v[k] > bv) { bv = v[k]; best = k; }
+        for (int k = kRowCodeWindow; k < K; ++k) {
+            const float x = elem_f32(row + pm[k]);
+            if (x > bv) { bv = x; best = k; }
         }
-    }
-    for (int r = rw; r < rows; r += NW)
-        if (ln < d - nch * CK)
-            reinterpret_cast<ET*>(stage + (size_t)r * pitch)[nch * CK + ln] = X[min(row0 + r, n - 1) * ld + nch * CK + ln];
-    __syncthreads();
-    for (int p0 = 0; p0 < P; p0 += kRowCodeThreads) {
-        const int np = min(P - p0, kRowCodeThreads), at_once = kRowCodeThreads / np;   // (uniform)
-        const int r0 = small_div(tid, np), p = p0 + tid - r0 * np;
-        if (r0 >= at_once) continue;
+        return best;
+    };
+    int idx[kRowCodeWindow];
+    auto window = [&](int p) {
         const int32_t* pm = perms + (size_t)p * K;
-        int idx[kRowCodeWindow];
 #pragma unroll
         for (int k = 0; k < kRowCodeWindow; ++k)
             if (k < K) idx[k] = pm[k];
-        for (int r = r0; r < rows; r += at_once) {
-            const ET* row = reinterpret_cast<const ET*>(stage + (size_t)r * pitch);
-            float v[kRowCodeWindow];
+    };
+    const int np0 = min(P, kRowCodeThreads), at_once = kRowCodeThreads / np0;  // (AHEAD) rows hashed side by side
+    const int my_r = small_div(tid, np0), my_p = tid - my_r * np0;
+    if (AHEAD) window(my_p);
+    load(blockIdx.x, half[0]);
+    int b = 0;
+    for (int64_t g = blockIdx.x; g < groups; g += gridDim.x) {                // (without AHEAD: once)
+        char* stage = half[b];
+        wait_vmem<0>();
 #pragma unroll
-            for (int k = 0; k < kRowCodeWindow; ++k)
-                if (k < K) v[k] = elem_f32(row + idx[k]);   // (uniform)
-            int best = 0;
-            float bv = v[0];
-#pragma unroll
-            for (int k = 1; k < kRowCodeWindow; ++k)
-                if (k < K && v[k] > bv) { bv = v[k]; best = k; }
-            for (int k = kRowCodeWindow; k < K; ++k) {
-                const float x = elem_f32(row + pm[k]);
-                if (x > bv) { bv = x; best = k; }
+        for (int j = 0; j < MOST; ++j)
+            if (rw + j * NW < rows && ln < rest) reinterpret_cast<ET*>(stage + (size_t)(rw + j * NW) * pitch)[nch * CK + ln] = tail[j];
+        lds_barrier();
+        if (AHEAD && g + gridDim.x < groups) load(g + gridDim.x, half[b ^ 1]);
+        if (AHEAD) {
+            if (my_r < at_once)
+                for (int r = my_r; r < rows; r += at_once)
+                    codes[r * P + my_p] = (uint16_t)argmax(reinterpret_cast<const ET*>(stage + (size_t)r * pitch), idx, nullptr);
+        } else {
+            for (int p0 = 0; p0 < P; p0 += kRowCodeThreads) {
+                const int np = min(P - p0, kRowCodeThreads), side = kRowCodeThreads / np;   // (uniform)
+                const int r0 = small_div(tid, np), p = p0 + tid - r0 * np;
+                if (r0 >= side) continue;
+                window(p);
+                for (int r = r0; r < rows; r += side)
+                    codes[r * P + p] = (uint16_t)argmax(reinterpret_cast<const ET*>(stage + (size_t)r * pitch), idx, perms + (size_t)p * K);
             }
-            codes[r * P + p] = (uint16_t)best;
         }
-    }
-    __syncthreads();
-    const int u = P / W;
-    for (int i = tid; i < (W << lg_rows); i += kRowCodeThreads) {
-        const int r = i & (rows - 1), w = i >> lg_rows;
-        int32_t code = 0;
-        for (int q = 0; q < u; ++q) code = (code << bits) | codes[r * P + w * u + q];
-        if (row0 + r < n) out[(row0 + r) * row_stride + w * band_stride] = code;
+        lds_barrier();
+        const int64_t row0 = g << lg_rows;
+        for (int i = tid; i < (W << lg_rows); i += kRowCodeThreads) {
+            const int r = i & (rows - 1), w = i >> lg_rows;
+            int32_t code = 0;
+            for (int q = 0; q < u; ++q) code = (code << bits) | codes[r * P + w * u + q];
+            if (row0 + r < n) out[(row0 + r) * row_stride + w * band_stride] = code;
+        }
+        b ^= 1;
     }
 }
 

@@ -179,6 +179,24 @@ __host__ __device__ __forceinline__ uint32_t nth_set_bit(uint32_t bits, uint32_t
 // issued early on purpose stay in flight across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// 16 bytes per lane from each lane's address to LDS, lane after lane from `to` (wave-uniform) on.  (Not the
+// builtin: for that the compiler waits for ALL such loads before the next read of LDS, whatever it reads.)
+__device__ __forceinline__ void load_to_lds16(const void* from, void* to) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
+}
+// The same to LDS address base + PLUS, with an offset in the instruction, which counts on both sides.
+template <int PLUS, int OFF> __device__ __forceinline__ void load_to_lds16_at(const void* from, uint32_t base) {
+    asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%3" ::"s"(base), "v"(from), "n"(PLUS - OFF), "n"(OFF) : "m0", "memory", "scc");
+}
+// 4 bytes per lane.
+__device__ __forceinline__ void load_to_lds4(const void* from, void* to) {
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
+}
+// At most N loads and stores of this wave are still under way.
+template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
+
 // Workgroup inclusive scan; `wsum` is LDS with at least blockDim.x/64 + 1 words.  Returns the
 // inclusive prefix of v for this thread and the workgroup total in *total.  Ends with a barrier,
 // so wsum may be reused right after.  LDS_ONLY: its barriers are lds_barrier.

@@ -961,21 +961,6 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 // next unit's wait, so that the stores never stand between a wait and the loads it is for.
 //
 // The tiles of a sentence are dealt to the XCDs by their number (XcdTiles above).
-// 16 bytes per lane from each lane's address to LDS, lane after lane from `to` (wave-uniform) on.  (Not the
-// builtin: for that the compiler waits for ALL such loads before the next read of LDS, whatever it reads.)
-__device__ __forceinline__ void load_to_lds16(const void* from, void* to) {
-    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
-}
-// The same to LDS address base + PLUS, with an offset in the instruction, which counts on both sides.
-template <int PLUS, int OFF> __device__ __forceinline__ void load_to_lds16_at(const void* from, uint32_t base) {
-    asm volatile("s_add_u32 m0, %0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off offset:%3" ::"s"(base), "v"(from), "n"(PLUS - OFF), "n"(OFF) : "m0", "memory", "scc");
-}
-// 4 bytes per lane.
-__device__ __forceinline__ void load_to_lds4(const void* from, void* to) {
-    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
-}
 constexpr int kStreamTiles = 32;   // tiles of a block, whose candidates come to LDS together
 constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? (MT == 1 ? 2 : 1) : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
 // Workgroups per CU: LDS (52 KB at most) and the registers of the A operands.
@@ -984,7 +969,6 @@ __host__ __device__ inline size_t stream_lds_bytes(int S, int MT, int KSN) {
     const size_t ts = stream_ts(KSN, MT);
     return 4 * 2 * ts * KSN * 1024 + 4 * ts * MT * 4 * kWave * 4 + kStreamTiles * kTileN * 8 + (size_t)(2 * ((S + 2 + 3) & ~3)) * 4;
 }
-template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 // f(integral_constant 0), ..., f(integral_constant N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) {

@@ -848,12 +848,15 @@ uint32_t Report::used = 0;
 template <typename ET>
 hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, int d, const int32_t* perms, int P, int K,
                             int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride) {
-    const hipError_t e = allow_whole_lds<k_row_codes<ET>>();
+    const bool ahead = row_codes_ahead(d, sizeof(ET), P, K);
+    const hipError_t e = ahead ? allow_whole_lds<k_row_codes<ET, true>>() : allow_whole_lds<k_row_codes<ET, false>>();
     if (e != hipSuccess) return e;
-    const int lg = row_codes_lg_rows(n, d, sizeof(ET), P);
-    hipLaunchKernelGGL(k_row_codes<ET>, dim3((unsigned)((n + (1 << lg) - 1) >> lg)), dim3(kRowCodeThreads),
-                       row_codes_lds(1 << lg, d, sizeof(ET), P), st, X, ld, n, d, perms, P, K, W, bits, lg, out,
-                       row_stride, band_stride);
+    const int lg = row_codes_lg_rows(n, d, sizeof(ET), P, ahead);
+    const size_t lds = row_codes_lds(1 << lg, d, sizeof(ET), P, ahead);
+    int64_t groups = (n + (1 << lg) - 1) >> lg;
+    if (ahead) groups = std::min<int64_t>(groups, 256 * std::min<size_t>(8, 158 * 1024 / lds));   // (as many as run at a time)
+    hipLaunchKernelGGL((ahead ? k_row_codes<ET, true> : k_row_codes<ET, false>), dim3((unsigned)groups), dim3(kRowCodeThreads),
+                       lds, st, X, ld, n, d, perms, P, K, W, bits, lg, out, row_stride, band_stride);
     return hipGetLastError();
 }
 
