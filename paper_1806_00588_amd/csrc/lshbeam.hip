@@ -289,9 +289,17 @@ bool step_is_fused(const lsh_tables* t, const lsh_step_params* sp) {
     // (with three or more groups of 16 beams the separate split-k kernel, one (tile, group) per
     // workgroup at a time, is faster than the fused kernel's all-groups-per-tile loop)
     if (t->opt[kOptFused] != kAuto) return possible && t->opt[kOptFused] != 0;
-    // (with more than about 1.5 tiles for each of the 256 workgroups, what they do one after the other outweighs the
-    // kernels saved: S = 8, B = 5, V = 40000 bf16: 32.1 -> 29.8 us a step; 468 bands, t = 3, 19000 candidates: 143 -> 56)
-    return possible && sp->S * MT <= 8 && MT <= 2 && sp->S * expected_candidates(t, sp) <= 1.5 * 256 * kTileN;
+    // What the workgroups do one after the other, in tiles for each of the 256, outweighs the kernel saved beyond
+    // (measured over S = 1 .. 16 and B = 4 .. 32 on six shapes, us a step fused / in three kernels):
+    //   one row group, 2.4 with long fp32 rows (d = 1000: 4 x 12 beams, 1.9 tiles, 23.2 / 27.4; 6 x 8, 2.4, 26.1 / 26.7;
+    //   8 x 4, 2.6, 27.3 / 24.7), 1.9 with shorter ones (d = 512: 8 x 12, 1.9, 20.7 / 22.9; 12 x 8, 2.4, 22.2 / 21.7), 1.8 with bf16
+    //   (d = 1024: 3 x 16, 1.6, 22.0 / 25.0; 4 x 12, 1.9, 24.7 / 23.9; V = 100000: 2 x 12, 2.05, 26.8 / 26.1);
+    //   two, 1.25 (d = 1000: 1 x 20, 0.6, 23.8 / 27.7; 2 x 20, 1.2, 30.6 / 31.3; V = 100000 bf16: 1 x 20, 1.4, 32.5 / 30.6), unless
+    //   the hidden rows alone fill most of LDS (1 x 32, 0.8, 36.0 / 33.3).
+    const double tiles = sp->S * expected_candidates(t, sp) / (256 * kTileN);
+    if (!possible || sp->S * MT > 8 || MT > 2) return false;
+    if (MT == 2) return tiles <= 1.25 && (size_t)sp->B * t->d * sizeof(float) <= 96 * 1024;
+    return tiles <= (t->dtype != LSH_F32 ? 1.8 : t->d > 512 ? 2.4 : 1.9);
 }
 
 // LDS words for the staged hidden rows of a step: room for all B rows of a sentence (up to
@@ -426,17 +434,22 @@ template <typename ET> StreamPlan stream_plan(int d) {
     const int nst = ((d + kstep - 1) / kstep + 3) / 4;
     return nst <= 1 ? StreamPlan{1, 1} : nst <= 2 ? StreamPlan{2, 1} : StreamPlan{4, (nst + 3) / 4};
 }
-// Hidden rows per workgroup (0: the kernel does not take the step).  Registers bound the operands a wave keeps:
-// two row groups of 16 where they are at most 128 of them.  (The longest bf16 rows, four parts, need 16 registers more
+// Hidden rows per workgroup (0: the kernel does not take the step): more than 16 beams in even groups of at most 16, every
+// group with its own pass over the candidate rows (from the XCD's L2), or of at most 32 where the rows are so short that
+// this pass is what counts, or the call so large.  fp32, d = 1000, V = 40000: 1 x 32 beams 40 us with 32 rows per
+// workgroup, 33 with 16; 9 x 17: 50, 48; d = 512, V = 20000: 9 x 32 44, 38; 32 x 50 118, 125; d = 256, V = 10000: 9 x 32
+// 29, 28; 64 x 20 43, 48.  (The longest bf16 rows, four parts, need 16 registers more
 // than there are; the spills cost less than the other kernel does: 32 sentences x 10 beams, V = 40000, 34 us against
 // 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
 template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
     if (!has_chunks(t) || t->ld * (int64_t)sizeof(ET) >= (int64_t)1 << 31) return 0;
     const StreamPlan p = stream_plan<ET>(t->d);
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
-    const bool two = p.parts <= (sizeof(ET) == 2 ? 1 : 4) && sp->B > kTileM;
+    const bool two = sp->B > kTileM && (p.ksn < 4 || p.parts == 1 || (sizeof(ET) == 4 && p.parts == 2 &&
+                                                                      sp->S * ((sp->B + kTileM - 1) / kTileM) >= 128));
     if (stream_lds_bytes(sp->S, two ? 2 : 1, p.ksn) > kMaxDynLds) return 0;
-    return std::min<int>(sp->B, two ? 2 * kTileM : kTileM);
+    const int most = two ? 2 * kTileM : kTileM, groups = (sp->B + most - 1) / most;
+    return (sp->B + groups - 1) / groups;
 }
 template <typename ET>
 void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, const lsh_step_params* sp,
@@ -459,7 +472,7 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2) LSH_STREAM2(2, 1); else if (p.parts == 1) LSH_STREAM2(4, 1);
     else if constexpr (sizeof(ET) == 2) switch (p.parts) { case 2: LSH_STREAM(1, 4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; default: LSH_STREAM(1, 4, 4); }
     else switch (p.parts) {
-        case 2: LSH_STREAM2(4, 2); break; case 3: LSH_STREAM2(4, 3); break; case 4: LSH_STREAM2(4, 4); break;
+        case 2: LSH_STREAM2(4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; case 4: LSH_STREAM(1, 4, 4); break;
         case 5: LSH_STREAM(1, 4, 5); break; case 6: LSH_STREAM(1, 4, 6); break; case 7: LSH_STREAM(1, 4, 7); break;
         default: LSH_STREAM(1, 4, 8);
     }
@@ -630,7 +643,7 @@ hipError_t allow_logits_lds() {
     LSH_ALLOW(1, 1, 1); LSH_ALLOW(1, 2, 1); LSH_ALLOW(1, 4, 1); LSH_ALLOW(1, 4, 2); LSH_ALLOW(1, 4, 3); LSH_ALLOW(1, 4, 4);
     LSH_ALLOW(2, 1, 1); LSH_ALLOW(2, 2, 1); LSH_ALLOW(2, 4, 1);
     if constexpr (sizeof(ET) == 4) {
-        LSH_ALLOW(2, 4, 2); LSH_ALLOW(2, 4, 3); LSH_ALLOW(2, 4, 4);
+        LSH_ALLOW(2, 4, 2);
         LSH_ALLOW(1, 4, 5); LSH_ALLOW(1, 4, 6); LSH_ALLOW(1, 4, 7); LSH_ALLOW(1, 4, 8);
     }
 #undef LSH_ALLOW
