@@ -977,11 +977,12 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
     }
 }
 
-template <typename ET, int MT, int KSN, int PARTS>
+template <typename ET, int MT, int KSN, int PARTS, bool DEALT>
 __global__ void __launch_bounds__(256, (stream_wgs(sizeof(ET) == 2, MT, KSN, PARTS)))
 k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
                 int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence; <= 16 MT*/,
-                int wgs /*workgroups per XCD and row group*/, int ngroups, int per /*... and sentence; 0: all tiles cut evenly*/,
+                int wgs /*workgroups per XCD and row group*/, int ngroups,
+                int per /*workgroups per XCD and sentence; DEALT: 1; -1: none stays with a sentence*/,
                 int shared, const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
                 float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
     constexpr bool BF = sizeof(ET) == 2;
@@ -992,9 +993,9 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     constexpr int TS = KSN == 4 ? 1 : stream_ts(KSN, MT);                     // tiles of a unit
     constexpr int RING = KSN == 4 ? 2 * stream_ts(KSN, MT) : 2;               // units' places per wave
     constexpr int GT = stream_ts(KSN, MT), GU = GT / TS;                      // tiles whose quarters are summed together; their units of a part
-    // 16-byte registers of A operands per step and row group: fp32 values; their three bf16 planes; for two parts
+    // 16-byte registers of A operands per step and row group: fp32 values; their three bf16 planes; for four parts
     // those registers run out, and the values are split when they are used
-    constexpr bool LATE = BF && PARTS > 2;
+    constexpr bool LATE = BF && PARTS > 3;
     constexpr int NH = LATE ? 2 : BF ? 3 : 1;
     constexpr int NI = TS * KSN;                                              // load instructions of a unit, KiB of its place
     constexpr int RPI = kWave / PP;                                           // rows per load instruction
@@ -1017,18 +1018,37 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
     LSH_TRACE_WG(0);
-    // Who takes what.  Every sentence has `per` workgroups of this XCD, workgroup i of them the tiles i, i + per, ... of
-    // those the XCD has of the sentence; or (more sentences than workgroups, or hardly fewer) all tiles of all
-    // sentences in a row, cut evenly.
-    int s = 0;
-    uint32_t first = 0, every = 1, seg = 0, seg_end = 0, wg_end = 0;
-    if (per > 0) {
-        s = (int)(bx / (uint32_t)per);
-        first = bx - (uint32_t)s * (uint32_t)per;
-        every = (uint32_t)per;
+    // Who takes what.  A workgroup knows its sentence before any count, and takes turns with the sentence's others:
+    //   per > 0: workgroup i of a sentence's `per` on this XCD has the tiles i, i + per, ... of those of the XCD (XcdTiles);
+    //   DEALT, where that would leave many without work: XCD x has for sentence s the workgroups from (s wgs + r) / S on, r =
+    //     x S / 8, a few more or less per XCD and nearly the same number in all.  Of the tiles that all sentences share
+    //     they take turns, of the others every XCD has its share;
+    //   per < 0 (more sentences than workgroups): all tiles of all sentences in a row, cut evenly.
+    // (40 sentences x 6, d = 1096 fp32: 47.4 us a step cut evenly, 37.9 dealt; 33 x 15: 53.3, 45.9; what is to be known for dealing
+    // costs a microsecond: 8 x 5, d = 1024 bf16: 10.3 us with per, 10.9 dealt; hence a kernel of its own.)
+    int s = 0, own_count = 0;
+    uint32_t first = 0, every = 1, before = 0, mine = 0, all = 1, seg = 0, seg_end = 0, wg_end = 0;
+    const bool own = DEALT || per > 0;
+    if (own) {
+        const uint32_t uS = (uint32_t)S, G = (uint32_t)wgs;
+        s = (int)(!DEALT ? bx / (uint32_t)per : ((bx + 1u) * uS - (xcd * uS >> 3) - 1u) / G);
+        s = __builtin_amdgcn_readfirstlane(s);
+        own_count = count ? count[s] : V;
         // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
         const char* hb = reinterpret_cast<const char*>(H + ((size_t)s * B + row0) * d);
         for (uint32_t at = tid * 128u; at < (uint32_t)(Bg * d) * 4u; at += 256u * 128u) load_to_lds4(hb + at, ring);
+        if (!DEALT) {
+            first = bx - (uint32_t)s * (uint32_t)per;
+            every = (uint32_t)per;
+        } else {
+            const uint32_t r = (ln & 7u) * uS >> 3;                           // (lane x: XCD x)
+            const uint32_t b0 = ((uint32_t)s * G + r) / uS, b1 = ((uint32_t)(s + 1) * G + r) / uS;
+            const uint32_t incl = wave_incl_scan(ln < 8 ? b1 - b0 : 0u);
+            all = wave_read_lane(incl, 7);
+            mine = every = wave_read_lane(b1 - b0, (int)xcd);
+            before = wave_read_lane(incl, (int)xcd) - mine;
+            first = bx - wave_read_lane(b0, (int)xcd);
+        }
     } else {
         if (q == 0) {
             uint32_t carry = 0;
@@ -1050,6 +1070,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     }
     const int nks = (d + KSTEP - 1) / KSTEP, nst = (nks + 3) >> 2, k0 = q * nst * KSTEP;   // steps of a wave's quarter
     // parts of which the wave's quarter has every piece, inside the row
+    const int last_steps = nst - (PARTS - 1) * KSN;                           // steps of the last part
     uint32_t whole_parts = 0;
 #pragma unroll
     for (int p = 0; p < PARTS; ++p)
@@ -1066,8 +1087,24 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     const uint32_t ld_bytes = (uint32_t)(ld * (int64_t)sizeof(ET));           // (the host: below 2^31)
     for (;;) {
         int C;
-        if (per > 0) {
-            C = __builtin_amdgcn_readfirstlane(count ? count[s] : V);
+        int n;                                                                // tiles of this workgroup, one after the other:
+        XcdTiles xt{};                                                        // of the XCD's, from `first` on; or, dealt:
+        uint32_t head = 0, rest0 = 0;                                         // `head` shared ones, then from rest0 on
+        if (own) {
+            C = __builtin_amdgcn_readfirstlane(own_count);
+            if (!DEALT) {
+                xt = xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd);
+                n = xt.n > first ? (int)((xt.n - first + every - 1u) / every) : 0;
+            } else {
+                const uint32_t nt = ntiles_of(C), cut = min((uint32_t)shared, nt), at = before + first;
+                auto share = [&](uint32_t w) { return cut + (uint32_t)((uint64_t)(nt - cut) * w / all); };
+                head = cut > at ? (cut - at + all - 1u) / all : 0u;
+                rest0 = share(before) + first;
+                const uint32_t end = share(before + mine);
+                n = (int)(head + (end > rest0 ? (end - rest0 + every - 1u) / every : 0u));
+            }
+            n = __builtin_amdgcn_readfirstlane(n);
+            if (n == 0) { wait_vmem<0>(); return; }
         } else {
             int lo = 0, hi = S;                                               // last sentence with tile_pref <= seg
             while (hi - lo > 1) {
@@ -1078,11 +1115,13 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             C = __builtin_amdgcn_readfirstlane((int)counts[s]);
             first = seg - tile_pref[s];
             seg_end = min(wg_end, tile_pref[s + 1]);
+            xt = xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd);
+            n = __builtin_amdgcn_readfirstlane((int)(seg_end - seg));
         }
-        const XcdTiles xt = xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd);
-        if (per > 0 && xt.n <= first) { wait_vmem<0>(); return; }
-        const int n = __builtin_amdgcn_readfirstlane((int)(per > 0 ? (xt.n - first + every - 1) / every : seg_end - seg));   // tiles
-        auto tile_of = [&](int t) __attribute__((always_inline)) { return (int)xcd_tile(xt, xcd, first + (uint32_t)t * every); };
+        auto tile_of = [&](int t) __attribute__((always_inline)) { 
+            const uint32_t u = (uint32_t)t;
+            return (int)(!DEALT ? xcd_tile(xt, xcd, first + u * every) : u < head ? before + first + u * all : rest0 + (u - head) * every);
+        };
         // candidates of block b (kStreamTiles tiles): two loads per wave
         auto load_ids = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
@@ -1260,8 +1299,11 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                 __builtin_amdgcn_sched_barrier(0);
                 static_for<KSN>([&](auto st_c) __attribute__((always_inline)) {
                     constexpr int st = decltype(st_c)::value;
+                    // (steps past the quarter meet zeros.  Where a step is dear they are left out; elsewhere the branch
+                    // costs more: 32 x 10 beams, d = 1000: 33.3 us, 34.3 with it)
+                    const bool is_step = !LATE || part < PARTS - 1 || st == 0 || st < last_steps;   // (uniform)
 #pragma unroll
-                    for (int t = 0; t < TS; ++t) {
+                    for (int t = 0; t < TS && is_step; ++t) {
                         const uint4 e = ev[t][st];
                         const uint32_t ew[4] = {e.x, e.y, e.z, e.w};
                         if constexpr (BF) {
@@ -1270,8 +1312,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                                 uint4 hp[3];
                                 if constexpr (LATE) {
                                     const uint4 a = h[m][part * KSN + st][0], b = h[m][part * KSN + st][1];
-                                    const float x[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
-                                                        __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+                                    float x[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+                                                  __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
                                     split_planes8(x, hp);
                                 } else {
 #pragma unroll
@@ -1332,7 +1374,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             lds_barrier();
         }
         LSH_TRACE_WG(15);
-        if (per > 0) return;
+        if (own) return;
         seg = seg_end;
         if (seg == wg_end) return;
         __syncthreads();                                                      // (the candidates are read no more)

@@ -432,7 +432,7 @@ struct StreamPlan { int ksn, parts; };
 template <typename ET> StreamPlan stream_plan(int d) {
     constexpr int kstep = 4 * ElemTraits<ET>::VEC;
     const int nst = ((d + kstep - 1) / kstep + 3) / 4;
-    return nst <= 1 ? StreamPlan{1, 1} : nst <= 2 ? StreamPlan{2, 1} : StreamPlan{4, (nst + 3) / 4};
+    return nst <= 1 ? StreamPlan{1, 1} : nst <= 4 ? StreamPlan{2, (nst + 1) / 2} : StreamPlan{4, (nst + 3) / 4};
 }
 // Hidden rows per workgroup (0: the kernel does not take the step): more than 16 beams in even groups of at most 16, every
 // group with its own pass over the candidate rows (from the XCD's L2), or of at most 32 where the rows are so short that
@@ -445,7 +445,7 @@ template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_param
     if (!has_chunks(t) || t->ld * (int64_t)sizeof(ET) >= (int64_t)1 << 31) return 0;
     const StreamPlan p = stream_plan<ET>(t->d);
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
-    const bool two = sp->B > kTileM && (p.ksn < 4 || p.parts == 1 || (sizeof(ET) == 4 && p.parts == 2 &&
+    const bool two = sp->B > kTileM && (p.ksn < 4 || (sizeof(ET) == 4 && p.parts == 2 &&
                                                                       sp->S * ((sp->B + kTileM - 1) / kTileM) >= 128));
     if (stream_lds_bytes(sp->S, two ? 2 : 1, p.ksn) > kMaxDynLds) return 0;
     const int most = two ? 2 * kTileM : kTileM, groups = (sp->B + most - 1) / most;
@@ -462,14 +462,14 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     const int shared = cand && sp->T >= 32 * kTileN ? sp->T / kTileN : 0;
     int wgs = (int)std::min<int64_t>((tiles_n + 7) / 8, std::max(1, t->option(kOptLogitsGrid, 256 * stream_wgs(sizeof(ET) == 2, rows > kTileM ? 2 : 1, p.ksn, p.parts)) / 8 / ngroups));
     int per = wgs / sp->S;
-    if (per * sp->S * 4 < wgs * 3) per = 0;
-    if (per) wgs = per * sp->S;
+    if (per * sp->S * 8 < wgs * 7) per = sp->S <= 8 * wgs ? 0 : -1;   // (would leave more than an eighth of them without work)
+    if (per > 0) wgs = per * sp->S;
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \
-    launch(cx, 1, k_logits_stream<ET, MTV, KSNV, PV>, dim3(8 * wgs * ngroups), dim3(256), stream_lds_bytes(sp->S, MTV, KSNV), \
-           (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per, shared, cand, count, t->V, w.logits, \
+    launch(cx, 1, per ? k_logits_stream<ET, MTV, KSNV, PV, false> : k_logits_stream<ET, MTV, KSNV, PV, true>, dim3(8 * wgs * ngroups), dim3(256), stream_lds_bytes(sp->S, MTV, KSNV), \
+           (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per ? per : 1, shared, cand, count, t->V, w.logits, \
            w.cpitch, w.records())
 #define LSH_STREAM2(KSNV, PV) do { if (rows > kTileM) LSH_STREAM(2, KSNV, PV); else LSH_STREAM(1, KSNV, PV); } while (0)
-    if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2) LSH_STREAM2(2, 1); else if (p.parts == 1) LSH_STREAM2(4, 1);
+    if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2 && p.parts == 2) LSH_STREAM2(2, 2); else if (p.ksn == 2) LSH_STREAM2(2, 1);
     else if constexpr (sizeof(ET) == 2) switch (p.parts) { case 2: LSH_STREAM(1, 4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; default: LSH_STREAM(1, 4, 4); }
     else switch (p.parts) {
         case 2: LSH_STREAM2(4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; case 4: LSH_STREAM(1, 4, 4); break;
@@ -584,8 +584,9 @@ bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an optio
     all.S = 1;
     all.B = sp->S * sp->B;
     const int rows = t->dtype == LSH_F32 ? stream_rows<float>(t, &all) : stream_rows<uint16_t>(t, &all);
+    const int wide = t->dtype == LSH_F32 ? 2 * kTileM : std::max(rows, kTileM);
     const int64_t tiles = (t->V + kTileN - 1) / kTileN;
-    if (rows > 0 && tiles * ((all.B + rows - 1) / rows) <= 512) return false;
+    if (rows > 0 && tiles * ((all.B + wide - 1) / wide) <= 512) return false;
     return sp->full_vocab && t->d >= kRowsMinD && t->opt[kOptLogitsWaves] == kAuto && t->opt[kOptLogitsEstage] == kAuto &&
            t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto &&
            t->option(kOptLogitsPlanes, 1) != 0;
@@ -639,9 +640,13 @@ hipError_t allow_logits_lds() {
     LSH_ALLOW(1, 16, U1, false); LSH_ALLOW(2, 16, U2W, false);
     if constexpr (std::is_same<ET, uint16_t>::value) LSH_ALLOW(1, 8, U1, true);
 #undef LSH_ALLOW
-#define LSH_ALLOW(...) do { if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, __VA_ARGS__>>(); } while (0)
-    LSH_ALLOW(1, 1, 1); LSH_ALLOW(1, 2, 1); LSH_ALLOW(1, 4, 1); LSH_ALLOW(1, 4, 2); LSH_ALLOW(1, 4, 3); LSH_ALLOW(1, 4, 4);
-    LSH_ALLOW(2, 1, 1); LSH_ALLOW(2, 2, 1); LSH_ALLOW(2, 4, 1);
+#define LSH_ALLOW(...)                                                                              \
+    do {                                                                                            \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, __VA_ARGS__, false>>();        \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, __VA_ARGS__, true>>();         \
+    } while (0)
+    LSH_ALLOW(1, 1, 1); LSH_ALLOW(1, 2, 1); LSH_ALLOW(1, 4, 2); LSH_ALLOW(1, 4, 3); LSH_ALLOW(1, 4, 4);
+    LSH_ALLOW(2, 1, 1); LSH_ALLOW(2, 2, 1); LSH_ALLOW(1, 2, 2); LSH_ALLOW(2, 2, 2);
     if constexpr (sizeof(ET) == 4) {
         LSH_ALLOW(2, 4, 2);
         LSH_ALLOW(1, 4, 5); LSH_ALLOW(1, 4, 6); LSH_ALLOW(1, 4, 7); LSH_ALLOW(1, 4, 8);
