@@ -507,13 +507,22 @@ int launch_logits_estage(const StepCtx& cx, const float* H, const lsh_step_param
 
 // Whether a step's contraction is k_logits_estage: 33..64 beams, fp32 rows of 513 to 1024 values (shorter ones
 // leave half of its four slices of k or more without work: k_logits_stream is 1.2 to 1.9 times faster there,
-// 1.1 to 1.3 times slower beyond),
-// 16-byte aligned operands, at most 256 sentences (option logits_estage = 0: the other drivers).
+// 1.1 to 1.3 times slower beyond), 16-byte aligned operands, at most 256 sentences (option logits_estage = 0: the other
+// drivers).  Not one sentence of up to two tiles for each of the workgroups: all 256 make the sentence's union and load its
+// hidden rows for those, which the stream's row groups share out.  A fourth row group draws the line closer on both
+// sides (us a step, estage / stream; d = 1000, 8 bands of 12 bits: V = 40000, 33 beams 43.2 / 36.0, 40: 45.1 / 37.2, 64: 49.9 /
+// 47.2; V = 60000, 50: 50.2 / 48.0, 64: 55.8 / 61.4; V = 100000, 33: 51.9 / 50.3, 50: 58.9 / 62.7; V = 4000, 33: 28.1 / 27.7, 64:
+// 34.1 / 35.1; V = 1000, 33: 27.0 / 27.2; d = 600: 1.0 to 1.35 times faster on this side of the line).  With two sentences
+// only the shorter rows gain (V = 40000, 33 beams: d = 600 42.6 / 39.0, d = 1000 40.8 / 42.6; 64: 54.2 / 53.7, 53.6 / 57.2).
 bool takes_estage(const lsh_tables* t, const lsh_step_params* sp, const float* H) {
     const bool aligned = (t->d % 4 == 0) && (t->ld % 4 == 0) && ((uintptr_t)t->E % 16 == 0) && ((uintptr_t)H % 16 == 0);
-    return t->dtype == LSH_F32 && aligned && !sp->full_vocab && sp->B > 2 * kTileM && sp->B <= 4 * kTileM &&
-           t->d > kEsMinD && t->d <= kEsSlices * kEsSlice && sp->S <= 256 && estage_lds_bytes(true) <= kMaxDynLds &&
-           t->option(kOptLogitsEstage, 1) && !t->option(kOptLogitsWaves, 0);
+    const bool able = t->dtype == LSH_F32 && aligned && !sp->full_vocab && sp->B > 2 * kTileM && sp->B <= 4 * kTileM &&
+                      t->d > kEsMinD && t->d <= kEsSlices * kEsSlice && sp->S <= 256 && estage_lds_bytes(true) <= kMaxDynLds &&
+                      t->option(kOptLogitsEstage, 1) && !t->option(kOptLogitsWaves, 0);
+    const bool named = t->opt[kOptLogitsEstage] != kAuto || t->opt[kOptEstageUnion] != kAuto || t->opt[kOptLogitsGrid] != kAuto;
+    if (!able || sp->S > 1 || named || names_hlds(t) || !stream_rows<float>(t, sp)) return able;
+    const double tiles = expected_candidates(t, sp) / kTileN;
+    return sp->B > 3 * kTileM ? tiles < 64 || tiles > 430 : tiles < 8 || tiles > 512;
 }
 
 // Returns 0 if the kernel it launched leaves one record per hidden row and tile, else the number

@@ -103,3 +103,16 @@ def test_lists_of_several_blocks(B, d, bf16):
         lp[:, masked] = -1e30
         assert_close_logprobs(lp, ref)
         assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
+
+
+@pytest.mark.parametrize("V,T", [(3000, 100), (12000, 3000)], ids=["few", "many"])
+@pytest.mark.parametrize("B,d", [(33, 516), (40, 1000), (64, 1024)])
+def test_one_sentence_of_many_beams(V, T, B, d):
+    """One sentence of 33 to 64 beams on either side of the number of candidates from which all its rows are taken at
+    once, and both kernels where the other one is the rule."""
+    rng, gc = _case(V, d, T, False)
+    H = (3.0 * rng.standard_normal((B, d))).astype(np.float32)
+    bs = rng.standard_normal(B).astype(np.float32)
+    for estage, t in ((-1, 1), (-1, 2), (0, 1), (1, 1)):
+        gc.tables.set_options(logits_estage=estage)
+        run_and_check(None, gc, H, bs, 1, B, threshold=t)
