@@ -625,7 +625,10 @@ __device__ __forceinline__ void store_planes4(char* dst, size_t plane_bytes, con
 // Tiles are dealt to the XCDs by their number inside the sentence: tile t of every sentence below `shared`
 // (the tiles that surely lie among the top-frequent words all sentences have in common, where those are the
 // lowest ids) goes to XCD t mod 8, so that its 16 rows enter one L2 and serve the other sentences from there;
-// tiles beyond go to XCD (t + s) mod 8.  What bounds the kernel lies behind the L2s.
+// of the tiles beyond, in the order of the words, every XCD has an eighth in one piece, so that words that
+// several sentences want are mostly on the same XCD for all of them; and as its workgroups take them interleaved,
+// at about the same time (64 x 10 beams, V = 200000, d = 1024 bf16: 48 % of the requests hit the L2; 17 % where tiles
+// beyond went to XCD (t + s) mod 8, every workgroup with a stretch of its own).
 struct XcdTiles {   // the tiles of one sentence that belong to XCD x
     uint32_t n0;        // how many of them lie below `shared`
     uint32_t first1;    // the first one beyond
@@ -946,16 +949,19 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 // the CU: a lane that fetches the matrix operand it needs itself makes every 16 lanes touch 16 rows -- 16
 // cache lines for 256 bytes.  Here candidate rows travel in contiguous pieces, straight from memory
 // to LDS (global_load_lds, 16 bytes per lane, any row alignment), and the lanes pick their operands out of
-// LDS.  32 sentences x 10 beams, V = 40000, d = 1000 fp32 (261 MB of rows): 47.6 -> 35.5 us, 5.5 -> 7.4 TB/s, of
-// which 146 MB come from memory (186 before; 62 % L2 hits, 45 before); 64 x 10, V = 200000, d = 1024 bf16 (1.38 GB, 1.27
-// from memory): 224 -> 182 us, 7.6 TB/s.
+// LDS.  What bounds it then is the instructions a wave issues (with every row in L2 it took as long), and how
+// much of what several sentences want one L2 serves.  32 sentences x 10 beams, V = 40000, d = 1000 fp32 (261 MB of
+// rows): 38 -> 33 us since the kernel works addresses out once per tile, has its loads between the matrix
+// instructions and four units of them in flight; 64 x 10, V = 200000, d = 1024 bf16 (1.38 GB): 183 -> 139 us, 9.9 TB/s
+// of rows; 8 x 5, d = 1024 bf16: 11.4 -> 10.4 us.
 //
 // The four waves of a workgroup share a tile, each with a quarter of k, and keep the A operands of all MT * 16
 // hidden rows for their quarter in REGISTERS for as long as the workgroup stays with the sentence.  A step is 64
 // bytes of every candidate row (16 fp32 values for four v_mfma_f32_16x16x4, or 32 bf16 for three
 // v_mfma_f32_16x16x32_bf16, one per plane of the hidden values).  What a wave asks for at a time is a unit: KSN
 // steps of TS tiles -- TS > 1 where rows are short, or one of PARTS parts of its quarter where they are
-// long.  Two units' places in LDS per wave: one arrives while the other is contracted.  The 16-byte piece p of row
+// long.  RING units' places in LDS per wave (four for long rows, two for short ones, whose units are larger): the
+// others arrive while one is contracted.  GT tiles are summed and stored together.  The 16-byte piece p of row
 // c lies at piece p ^ (c >> shift) of the row's place, so that 16 lanes reading the same piece of 16 rows meet
 // different banks.  The quarters' partial tiles are summed through LDS in order; the results are stored behind the
 // next unit's wait, so that the stores never stand between a wait and the loads it is for.
