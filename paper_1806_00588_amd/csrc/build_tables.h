@@ -77,12 +77,17 @@ __host__ __device__ inline BandMeta draw_band_meta(uint64_t seed, int w, int W, 
     return m;
 }
 
-// Both hash functions the code itself: a direct table has 2^lg slots for codes of fewer than lg bits.
+// Both hash functions the code itself and an even offset, modulo the slots: a direct table has 2^lg slots for codes of
+// fewer than lg bits.  (Every thread without work of its own probes code 0 of its band: with offsets of their own the
+// bands' slots for it are on different memory channels.  A step of V = 20000, d = 512, 2 x 4 beams, 16 bands of 12 bits, took
+// 0.22 us more than with cuckoo tables where every band's was its first slot, and takes the same so.)
+__host__ __device__ inline uint32_t direct_offset(int w, int lg) { return ((uint32_t)w * 0x9E3779B1u >> (32 - lg)) & ~1u; }
 __host__ __device__ inline BandMeta direct_band_meta(int w, int lg) {
     BandMeta m{};
     m.slot_off = (uint32_t)w << lg;
     m.shift = 32u - (uint32_t)lg;
     m.a0 = m.a1 = 1u << m.shift;
+    m.b0 = m.b1 = direct_offset(w, lg) << m.shift;
     return m;
 }
 
@@ -207,10 +212,11 @@ k_radix_scan(const uint32_t* __restrict__ counts, const uint32_t* __restrict__ g
     if constexpr (EMIT) {
         if (lane_id() == 0) atomicAdd(&n_keys[w], keys);
         if (in) {
-            const size_t s0 = (size_t)w * 2 * digits + 2 * pair;
+            const uint32_t mask = 2u * digits - 1u, offset = direct_offset(w, 32 - __clz(mask));
+            const size_t b0 = (size_t)w * 2 * digits, s0 = b0 + ((2 * pair + offset) & mask), e0 = b0 + ((2 * pair + digits + offset) & mask);
             slots[s0] = Slot{lo ? 2 * pair : -1, at, lo, 0u};
             slots[s0 + 1] = Slot{hi ? 2 * pair + 1 : -1, at + lo, hi, 0u};
-            slots[s0 + digits] = slots[s0 + digits + 1] = Slot{-1, 0u, 0u, 0u};
+            slots[e0] = slots[e0 + 1] = Slot{-1, 0u, 0u, 0u};
             cuts[s0] = make_uint4(cut_lo[0], cut_lo[1], cut_lo[2], lo);
             cuts[s0 + 1] = make_uint4(cut_hi[0], cut_hi[1], cut_hi[2], hi);
         }
