@@ -438,7 +438,9 @@ template <typename ET> StreamPlan stream_plan(int d) {
 // group with its own pass over the candidate rows (from the XCD's L2), or of at most 32 where the rows are so short that
 // this pass is what counts, or the call so large.  fp32, d = 1000, V = 40000: 1 x 32 beams 40 us with 32 rows per
 // workgroup, 33 with 16; 9 x 17: 50, 48; d = 512, V = 20000: 9 x 32 44, 38; 32 x 50 118, 125; d = 256, V = 10000: 9 x 32
-// 29, 28; 64 x 20 43, 48.  (The longest bf16 rows, four parts, need 16 registers more
+// 29, 28; 64 x 20 43, 48.  Two parts, from 96 groups of 16 on (V = 40000 / 107641 with 16-bit codes, groups of 16, of 32): 48 x 24,
+// d = 295, 110, 96 / 58, 54; d = 512 103, 93 / 58, 57; 32 x 31, d = 512 85, 82 / 51, 52; 21 x 31 67, 71 / 42, 48.  (The longest
+// bf16 rows, four parts, need 16 registers more
 // than there are; the spills cost less than the other kernel does: 32 sentences x 10 beams, V = 40000, 34 us against
 // 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
 template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
@@ -446,7 +448,7 @@ template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_param
     const StreamPlan p = stream_plan<ET>(t->d);
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
     const bool two = sp->B > kTileM && (p.ksn < 4 || (sizeof(ET) == 4 && p.parts == 2 &&
-                                                                      sp->S * ((sp->B + kTileM - 1) / kTileM) >= 128));
+                                                                      sp->S * ((sp->B + kTileM - 1) / kTileM) >= 96));
     if (stream_lds_bytes(sp->S, two ? 2 : 1, p.ksn) > kMaxDynLds) return 0;
     const int most = two ? 2 * kTileM : kTileM, groups = (sp->B + most - 1) / most;
     return (sp->B + groups - 1) / groups;
