@@ -969,12 +969,20 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 // The tiles of a sentence are dealt to the XCDs by their number (XcdTiles above).
 constexpr int kStreamTiles = 32;   // tiles of a block, whose candidates come to LDS together
 constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? (MT == 1 ? 2 : 1) : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
-// Workgroups per CU: LDS (52 KB at most) and the registers of the A operands.
+// Workgroups per CU: the registers of the A operands, and LDS -- of one row group of long rows, 76 KB, two.
 constexpr int stream_wgs(bool bf16, int MT, int KSN, int PARTS) { return KSN == 4 && MT == 1 ? 2 : (bf16 ? 3 : 1) * MT * KSN * PARTS * 4 <= (bf16 ? 96 : 80) ? 3 : 2; }
-__host__ __device__ inline size_t stream_lds_bytes(int S, int MT, int KSN) {
-    const size_t ts = stream_ts(KSN, MT);
-    return 4 * 2 * ts * KSN * 1024 + 4 * ts * MT * 4 * kWave * 4 + kStreamTiles * kTileN * 8 + (size_t)(2 * ((S + 2 + 3) & ~3)) * 4;
-}
+// Its LDS: the waves' partial tiles, the waves' rings, two blocks of candidates, and for an even cut the tiles in front of
+// every 64 sentences.  (The same for any number of sentences.  With tables of all of them only one workgroup of long rows
+// ran on a CU from 510 sentences on: fp32, V = 5000, d = 1000: 600 x 2 beams 188 us a step, 83 so; 2048 x 1 542, 199.)
+template <int MT, int KSN> struct StreamLds {
+    static constexpr int TS = KSN == 4 ? 1 : stream_ts(KSN, MT);                   // tiles of a unit
+    static constexpr int RING = KSN == 4 ? 2 * stream_ts(KSN, MT) : 2;             // units' places per wave
+    static constexpr int GT = stream_ts(KSN, MT);                                  // tiles whose quarters are summed together
+    static constexpr int NI = TS * KSN;                                            // load instructions of a unit, KiB of its place
+    static constexpr size_t kRed = (size_t)4 * GT * MT * 4 * kWave * 4, kRings = (size_t)4 * RING * NI * 1024;
+    static constexpr size_t kIds = kRed + kRings, kPref = kIds + (size_t)2 * kStreamTiles * kTileN * 4;
+    static constexpr size_t kBytes = kPref + kWave * 4;
+};
 // f(integral_constant 0), ..., f(integral_constant N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) {
@@ -996,31 +1004,28 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     constexpr int PP = 4 * KSN;                                               // 16-byte pieces of a row in a unit
     static_assert(KSN == 1 || KSN == 2 || KSN == 4, "");
     constexpr int SH = PP == 4 ? 2 : PP == 8 ? 1 : 0;
-    constexpr int TS = KSN == 4 ? 1 : stream_ts(KSN, MT);                     // tiles of a unit
-    constexpr int RING = KSN == 4 ? 2 * stream_ts(KSN, MT) : 2;               // units' places per wave
-    constexpr int GT = stream_ts(KSN, MT), GU = GT / TS;                      // tiles whose quarters are summed together; their units of a part
+    using Lds = StreamLds<MT, KSN>;
+    constexpr int TS = Lds::TS, RING = Lds::RING, GT = Lds::GT, GU = GT / TS; // GU: units of a part of GT tiles
     // 16-byte registers of A operands per step and row group: fp32 values; their three bf16 planes; for four parts
     // those registers run out, and the values are split when they are used
     constexpr bool LATE = BF && PARTS > 3;
     constexpr int NH = LATE ? 2 : BF ? 3 : 1;
-    constexpr int NI = TS * KSN;                                              // load instructions of a unit, KiB of its place
+    constexpr int NI = Lds::NI;
     constexpr int RPI = kWave / PP;                                           // rows per load instruction
     extern __shared__ uint4 ssm[];
     // (the ring behind other things: the address in M0 is its place less the load's offset, and must not be negative)
     char* sm = reinterpret_cast<char*>(ssm);
     float (*red)[GT][MT][4][kWave] = reinterpret_cast<float (*)[GT][MT][4][kWave]>(sm);   // [wave]
-    constexpr size_t RED = (size_t)4 * GT * MT * 4 * kWave * 4;
-    static_assert(RED >= (PARTS - 1) * KSN * 64, "");
-    int32_t* ids = reinterpret_cast<int32_t*>(sm + RED + 4 * RING * NI * 1024);       // [two blocks of tiles][16]
-    uint32_t* tile_pref = reinterpret_cast<uint32_t*>(ids + 2 * kStreamTiles * kTileN);   // [S + 1]
-    uint32_t* counts = tile_pref + ((S + 2 + 3) & ~3);                                    // [S]
+    static_assert(Lds::kRed >= (PARTS - 1) * KSN * 64, "");
+    int32_t* ids = reinterpret_cast<int32_t*>(sm + Lds::kIds);                         // [two blocks of tiles][16]
+    uint32_t* chunk_pref = reinterpret_cast<uint32_t*>(sm + Lds::kPref);                   // [64]: tiles in front of every 64 sentences
     // grid = 8 * wgs * ngroups; ids go round the XCDs, the row groups of one block of tiles follow each other on one
     const uint32_t xcd = blockIdx.x & 7u, slot_x = blockIdx.x >> 3;
     const uint32_t bx = slot_x / (uint32_t)ngroups;
     const int row0 = (int)(slot_x % (uint32_t)ngroups) * group_rows, Bg = min(group_rows, B - row0);
     const int tid = threadIdx.x, ln = lane_id(), q = __builtin_amdgcn_readfirstlane(wave_id());   // q: the wave's quarter of k
     const int col = ln & 15, kq = ln >> 4;
-    char* ring = sm + RED + q * (RING * NI * 1024);
+    char* ring = sm + Lds::kRed + q * (RING * NI * 1024);
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
     LSH_TRACE_WG(0);
@@ -1029,7 +1034,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     //   DEALT, where that would leave many without work: XCD x has for sentence s the workgroups from (s wgs + r) / S on, r =
     //     x S / 8, a few more or less per XCD and nearly the same number in all.  Of the tiles that all sentences share
     //     they take turns, of the others every XCD has its share;
-    //   per < 0 (more sentences than workgroups): all tiles of all sentences in a row, cut evenly.
+    //   per < 0 (more sentences than workgroups): all tiles of all sentences in a row, cut evenly; an XCD has whole
+    //   sentences so far as that goes (a workgroup that took an eighth of a list of eight tiles went through a sentence per tile).
     // (40 sentences x 6, d = 1096 fp32: 47.4 us a step cut evenly, 37.9 dealt; 33 x 15: 53.3, 45.9; what is to be known for dealing
     // costs a microsecond: 8 x 5, d = 1024 bf16: 10.3 us with per, 10.9 dealt; hence a kernel of its own.)
     int s = 0, own_count = 0;
@@ -1055,22 +1061,25 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             before = wave_read_lane(incl, (int)xcd) - mine;
             first = bx - wave_read_lane(b0, (int)xcd);
         }
-    } else {
-        if (q == 0) {
-            uint32_t carry = 0;
-            for (int base = 0; base < S; base += kWave) {
-                const int sl = base + ln;
-                const int C = sl < S ? (count ? count[sl] : V) : 0;
-                const uint32_t n = sl < S ? xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)sl, xcd).n : 0u;
-                const uint32_t incl = wave_incl_scan(n);
-                if (sl < S) { tile_pref[sl] = carry + incl - n; counts[sl] = (uint32_t)C; }
-                carry += wave_read_lane(incl, kWave - 1);
+    }
+    auto count_of = [&](int at) { const int n = count ? count[min(at, S - 1)] : V; return at < S ? n : 0; };   // (no branch around the load)
+    if (!own) {   // (every wave for itself, to the same result)
+        static_assert(kMaxSentencesLogits <= kWave * kWave, "a lane per 64 sentences");
+        constexpr int AHEAD = 8;
+        uint32_t total = 0, in_front = ~0u;                                   // (lane c: tiles in front of sentence 64 c)
+        for (int c0 = 0; c0 * kWave < S; c0 += AHEAD) {
+            int n[AHEAD];
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) n[j] = count_of((c0 + j) * kWave + ln);
+#pragma unroll
+            for (int j = 0; j < AHEAD; ++j) {
+                if (ln == c0 + j && (c0 + j) * kWave < S) in_front = total;
+                total += wave_sum(ntiles_of(n[j]));
             }
-            if (ln == 0) tile_pref[S] = carry;
         }
-        __syncthreads();
-        const uint32_t total = tile_pref[S], per_wg = (total + (uint32_t)wgs - 1) / (uint32_t)wgs;
-        seg = min(total, bx * per_wg);
+        chunk_pref[ln] = in_front;
+        const uint32_t per_wg = (total + 8u * (uint32_t)wgs - 1u) / (8u * (uint32_t)wgs);
+        seg = min(total, (xcd * (uint32_t)wgs + bx) * per_wg);
         wg_end = min(total, seg + per_wg);
         if (seg == wg_end) return;
     }
@@ -1112,17 +1121,17 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             n = __builtin_amdgcn_readfirstlane(n);
             if (n == 0) { wait_vmem<0>(); return; }
         } else {
-            int lo = 0, hi = S;                                               // last sentence with tile_pref <= seg
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (tile_pref[mid] <= seg) lo = mid; else hi = mid;
-            }
-            s = __builtin_amdgcn_readfirstlane(lo);
-            C = __builtin_amdgcn_readfirstlane((int)counts[s]);
-            first = seg - tile_pref[s];
-            seg_end = min(wg_end, tile_pref[s + 1]);
-            xt = xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd);
-            n = __builtin_amdgcn_readfirstlane((int)(seg_end - seg));
+            // the last sentence with at most `seg` tiles in front of it
+            const uint32_t in_front = chunk_pref[ln];
+            const int c = kWave - 1 - __clzll(__ballot(in_front <= seg)), at = c * kWave + ln, mine_c = count_of(at);
+            const uint32_t incl = wave_read_lane(in_front, c) + wave_incl_scan(ntiles_of(mine_c)), pref = incl - ntiles_of(mine_c);
+            const int i = kWave - 1 - __clzll(__ballot(at < S && pref <= seg));
+            s = c * kWave + i;
+            C = wave_read_lane((uint32_t)mine_c, i);
+            first = seg - wave_read_lane(pref, i);
+            seg_end = min(wg_end, wave_read_lane(incl, i));
+            xt = {0u, 0u, ntiles_of(C)};
+            n = (int)(seg_end - seg);
         }
         auto tile_of = [&](int t) __attribute__((always_inline)) { 
             const uint32_t u = (uint32_t)t;

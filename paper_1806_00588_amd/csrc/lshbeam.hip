@@ -449,7 +449,6 @@ template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_param
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
     const bool two = sp->B > kTileM && (p.ksn < 4 || (sizeof(ET) == 4 && p.parts == 2 &&
                                                                       sp->S * ((sp->B + kTileM - 1) / kTileM) >= 96));
-    if (stream_lds_bytes(sp->S, two ? 2 : 1, p.ksn) > kMaxDynLds) return 0;
     const int most = two ? 2 * kTileM : kTileM, groups = (sp->B + most - 1) / most;
     return (sp->B + groups - 1) / groups;
 }
@@ -467,7 +466,7 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     if (per * sp->S * 8 < wgs * 7) per = sp->S <= 8 * wgs ? 0 : -1;   // (would leave more than an eighth of them without work)
     if (per > 0) wgs = per * sp->S;
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \
-    launch(cx, 1, per ? k_logits_stream<ET, MTV, KSNV, PV, false> : k_logits_stream<ET, MTV, KSNV, PV, true>, dim3(8 * wgs * ngroups), dim3(256), stream_lds_bytes(sp->S, MTV, KSNV), \
+    launch(cx, 1, per ? k_logits_stream<ET, MTV, KSNV, PV, false> : k_logits_stream<ET, MTV, KSNV, PV, true>, dim3(8 * wgs * ngroups), dim3(256), StreamLds<MTV, KSNV>::kBytes, \
            (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per ? per : 1, shared, cand, count, t->V, w.logits, \
            w.cpitch, w.records())
 #define LSH_STREAM2(KSNV, PV) do { if (rows > kTileM) LSH_STREAM(2, KSNV, PV); else LSH_STREAM(1, KSNV, PV); } while (0)

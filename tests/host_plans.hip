@@ -124,17 +124,20 @@ static void check_hlds(int S, int rows, int d) {
         }
 }
 
-// k_logits_stream: its regions as the kernel lays them out (the bits of tiles to settle and their first hidden row sit
-// behind the counts), and the tiles of a sentence dealt to the XCDs, each once.
-static void check_stream(int S) {
-    for (int mt : {1, 2})
-        for (int ksn : {1, 2, 4}) {
-            const size_t ts = stream_ts(ksn, mt), words = (size_t)((S + 2 + 3) & ~3);
-            const size_t ring = 4 * 2 * ts * ksn * 1024, red = 4 * ts * mt * 4 * kWave * 4, rows = kStreamTiles * kTileN * sizeof(void*);
-            CHECK(ring + red + rows + 2 * words * 4 == stream_lds_bytes(S, mt, ksn), "stream regions (S=%d MT=%d KSN=%d)", S, mt, ksn);
-            CHECK((ring + red) % 8 == 0 && words >= (size_t)S + 2, "stream words (S=%d)", S);
-            CHECK(S > 64 || stream_lds_bytes(S, mt, ksn) <= kLdsLimit / 2, "two workgroups do not share a CU");
-        }
+// k_logits_stream: its regions in LDS, which the kernel takes from the same constants; and the tiles of a sentence dealt to
+// the XCDs, each once.
+template <int MT, int KSN> static void check_stream_regions() {
+    using L = StreamLds<MT, KSN>;
+    // partial tiles [wave][tile][row group][register][lane], rings [wave][place][load][64 lanes of 16 bytes], candidates
+    CHECK(L::kRed == sizeof(float[4][L::GT][MT][4][kWave]) && L::kRings == sizeof(char[4][L::RING][L::NI][kWave][16]) &&
+          L::kPref - L::kIds == sizeof(int32_t[2][kStreamTiles][kTileN]), "stream regions (MT=%d KSN=%d)", MT, KSN);
+    CHECK(L::kRed % 16 == 0 && L::kIds % 16 == 0 && L::kPref % 16 == 0 && L::kIds == L::kRed + L::kRings, "stream regions (MT=%d KSN=%d)", MT, KSN);
+    CHECK(L::kPref + sizeof(uint32_t[kWave]) == L::kBytes && kWave * kWave >= kMaxSentencesLogits, "sentences in front (MT=%d KSN=%d)", MT, KSN);
+    CHECK(L::kBytes <= kLdsLimit / 2, "two workgroups do not share a CU (MT=%d KSN=%d)", MT, KSN);
+}
+static void check_stream() {
+    check_stream_regions<1, 1>(); check_stream_regions<1, 2>(); check_stream_regions<1, 4>();
+    check_stream_regions<2, 1>(); check_stream_regions<2, 2>(); check_stream_regions<2, 4>();
 }
 static void check_xcd_tiles() {
     for (uint32_t n : {0u, 1u, 7u, 8u, 9u, 130u, 1003u})
@@ -211,7 +214,7 @@ int main() {
     for (int S : {1, 32, 64, 4096})
         for (int rows : {1, 10, 16, 32})
             for (int d : {8, 50, 1000, 1024, 1026, 4099}) check_hlds(S, rows, d);
-    for (int S : {1, 2, 3, 63, 64, 65, 4096}) check_stream(S);
+    check_stream();
     check_xcd_tiles();
     CHECK(2 * rows_lds_bytes(5) <= kLdsLimit && 2 * few_lds_bytes<float>(3) <= kLdsLimit && 2 * few_lds_bytes<uint16_t>(2) <= kLdsLimit,
           "full-vocabulary kernels: two workgroups do not share a CU");

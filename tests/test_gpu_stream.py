@@ -1,7 +1,7 @@
 """The contraction of many tiles at the edges of its units, and the selection of winners that share a tile:
 rows of one step, of a unit, of every number of parts and a bit more, odd lengths, both element types, one and
-two row groups and several of them; few and many sentences (stretches of their own and an even cut), lists of
-less than a tile up to several stretches of tiles."""
+two row groups and several of them; few and many sentences (workgroups of their own, dealt to them, and an even cut),
+lists of less than a tile up to several blocks of tiles."""
 import numpy as np
 import pytest
 
@@ -70,12 +70,34 @@ def test_longer_rows_end_in_a_split_round(d, bf16):
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("S,d", [(40, 600), (100, 300), (40, 40)])
-def test_tiles_cut_evenly(S, d, bf16):
-    """Sentences that would leave many workgroups without work, or more of them than workgroups: all tiles in a row,
-    a workgroup goes from one sentence to the next."""
+def test_sentences_dealt_to_workgroups(S, d, bf16):
+    """Numbers of sentences that would leave many workgroups without work if every sentence had as many on every XCD."""
     rng, gc = _case(3000, d, 1500, bf16)
     H = (3.0 * rng.standard_normal((S * 3, d))).astype(np.float32)
     run_and_check(None, gc, H, rng.standard_normal(S * 3).astype(np.float32), S, 3)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("B", [3, 18])
+@pytest.mark.parametrize("d", [40, 100, 200, 300, 600, 1000, 1500, 2047])
+def test_tiles_cut_evenly(d, B, bf16):
+    """More sentences than workgroups (eight here, of one or two row groups): all tiles in a row, a workgroup goes from one
+    sentence to the next, and through several blocks of candidates; rows of one and two steps and of several numbers of parts."""
+    S = 20
+    rng, gc = _case(1200, d, 700, bf16)
+    gc.tables.set_options(logits_grid=8)
+    H = (3.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+    run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
+
+
+def test_more_sentences_than_workgroups():
+    """Several times 64 sentences on eight workgroups, short lists."""
+    S, B, d = 150, 2, 24
+    rng, gc = _case(900, d, 0, False)
+    gc.tables.set_options(logits_grid=8)
+    H = (3.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+    H[2 * B:70 * B] = H[:1]                              # (one list for all of these)
+    run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
