@@ -648,6 +648,42 @@ __host__ __device__ __forceinline__ XcdTiles xcd_tiles(uint32_t ntiles, uint32_t
 __host__ __device__ __forceinline__ uint32_t xcd_tile(const XcdTiles& t, uint32_t x, uint32_t i) {   // its i-th
     return i < t.n0 ? x + 8u * i : t.first1 + (i - t.n0);
 }
+// The tiles of one sentence that a workgroup takes, in two arithmetic progressions.
+struct TileRun {
+    uint32_t n, head, a0, a1, b0, b1;   // tile u < n: a0 + u a1 below `head`, else b0 + u b1
+    __host__ __device__ __forceinline__ uint32_t tile(uint32_t u) const { return u < head ? a0 + u * a1 : b0 + u * b1; }
+};
+// of an XCD's tiles those from `first` on, every `every`-th, n in all
+__host__ __device__ __forceinline__ TileRun xcd_run(const XcdTiles& t, uint32_t x, uint32_t first, uint32_t every, uint32_t n) {
+    const uint32_t head = t.n0 > first ? (t.n0 - first + every - 1u) / every : 0u;
+    return {n, head, x + 8u * first, 8u * every, t.first1 + first - t.n0, every};
+}
+// G workgroups on each of 8 XCDs dealt to sentences by weight (equal ones: 1 each, S <= 8 G of them).  With the weights of
+// the sentences in front summed to w, of all to W, those of a sentence on XCD x begin at dealt_from(w) and end where the
+// next one's begin: a few more or less per XCD, and 8 G / W per unit of weight, give or take one, in all.
+__host__ __device__ __forceinline__ uint32_t dealt_from(uint32_t w, uint32_t x, uint32_t W, uint32_t G) { return (w * G + (x * W >> 3)) / W; }
+__host__ __device__ __forceinline__ uint32_t dealt_sentence(uint32_t b, uint32_t x, uint32_t S, uint32_t G) {   // (equal weights)
+    return ((b + 1u) * S - (x * S >> 3) - 1u) / G;
+}
+// Whether shares as large as the lists are worth working out: the longest list takes its equal share of the workgroups
+// twice as long as all of them together would take even ones, and three tiles more.  (One list of 32 sentences x 10 beams, V = 40000,
+// d = 1000 fp32, four times the others: 108 us a step with equal shares, 69 so; of 64: 176, 97; eight sentences, one list three
+// times their mean: 56, 49.  Below, equal shares of XcdTiles are the better ones: eight sentences, four of them three times as
+// long as the others, 60 us, 67 where all tiles are cut evenly.)
+__host__ __device__ __forceinline__ bool dealt_by_count(uint32_t most, uint32_t sum, uint32_t S, uint32_t G) {   // (in tiles)
+    return S <= 4u * G && G <= 192u && sum < (1u << 23) && (float)most * (float)S > 2.f * (float)sum + 24.f * (float)G;
+}
+// A list's weight: its tiles, or as much as a workgroup takes (8 G (least) >= sum + S (least) >= W; W < 2^24 + 4 G).
+__host__ __device__ __forceinline__ uint32_t least_weight(uint32_t sum, uint32_t S, uint32_t G) { return (sum + 8u * G - S - 1u) / (8u * G - S); }
+// What number `first` of the `mine` workgroups a sentence has on an XCD takes, with `before` of its `all` on the XCDs in
+// front: of the tiles that all sentences share they take turns, of the others every XCD has its share.
+__host__ __device__ __forceinline__ TileRun dealt_run(uint32_t ntiles, uint32_t shared, uint32_t first, uint32_t mine, uint32_t before, uint32_t all) {
+    const uint32_t cut = shared < ntiles ? shared : ntiles, at = before + first;
+    const uint32_t begin = cut + (uint32_t)((uint64_t)(ntiles - cut) * before / all) + first;
+    const uint32_t end = cut + (uint32_t)((uint64_t)(ntiles - cut) * (before + mine) / all);
+    const uint32_t head = cut > at ? (cut - at + all - 1u) / all : 0u;
+    return {head + (end > begin ? (end - begin + mine - 1u) / mine : 0u), head, at, all, begin - head * mine, mine};
+}
 
 // Eight hidden values as the A operands of three v_mfma_f32_16x16x32_bf16: their planes.
 __device__ __forceinline__ void split_planes8(const float (&x)[8], uint4 (&out)[3]) {
@@ -971,8 +1007,8 @@ constexpr int kStreamTiles = 32;   // tiles of a block, whose candidates come to
 constexpr int stream_ts(int KSN, int MT) { return KSN == 4 ? (MT == 1 ? 2 : 1) : KSN == 1 ? (MT == 1 ? 4 : 2) : MT == 1 ? 2 : 1; }
 // Workgroups per CU: the registers of the A operands, and LDS -- of one row group of long rows, 76 KB, two.
 constexpr int stream_wgs(bool bf16, int MT, int KSN, int PARTS) { return KSN == 4 && MT == 1 ? 2 : (bf16 ? 3 : 1) * MT * KSN * PARTS * 4 <= (bf16 ? 96 : 80) ? 3 : 2; }
-// Its LDS: the waves' partial tiles, the waves' rings, two blocks of candidates, and for an even cut the tiles in front of
-// every 64 sentences.  (The same for any number of sentences.  With tables of all of them only one workgroup of long rows
+// Its LDS: the waves' partial tiles, the waves' rings, two blocks of candidates, and what the workgroup takes (for an even cut,
+// the tiles in front of every 64 sentences).  (The same for any number of sentences.  With tables of all of them only one workgroup of long rows
 // ran on a CU from 510 sentences on: fp32, V = 5000, d = 1000: 600 x 2 beams 188 us a step, 83 so; 2048 x 1 542, 199.)
 template <int MT, int KSN> struct StreamLds {
     static constexpr int TS = KSN == 4 ? 1 : stream_ts(KSN, MT);                   // tiles of a unit
@@ -991,12 +1027,66 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
     }
 }
 
-template <typename ET, int MT, int KSN, int PARTS, bool DEALT>
+// The sentence of workgroup bx of XCD x, its candidates and its tiles: one wave's work.  s0: its sentence where the lists
+// are about equally long.
+struct StreamDeal { uint32_t s, C; TileRun run; };
+__device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ count, int V, uint32_t S, uint32_t G, uint32_t per,
+                                                  uint32_t shared, uint32_t x, uint32_t bx, uint32_t s0) {
+    const uint32_t ln = lane_id();
+    auto tiles = [&](uint32_t at) { return ((uint32_t)count[min(at, S - 1u)] + kTileN - 1u) / kTileN; };   // (no branch around the load)
+    StreamDeal dl;
+    dl.s = s0;
+    uint32_t w0 = s0, w1 = s0 + 1u, W = S, most = 0, sum = 0;
+    const int own = count ? count[s0] : V;
+    if (count) {
+        constexpr uint32_t AT_ONCE = 6;
+        for (uint32_t c = 0; c < S; c += AT_ONCE * kWave) {
+            uint32_t n[AT_ONCE];
+#pragma unroll
+            for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles(c + j * kWave + ln);
+#pragma unroll
+            for (uint32_t j = 0; j < AT_ONCE; ++j) { most = max(most, n[j]); sum += c + j * kWave + ln < S ? n[j] : 0u; }
+        }
+        most = (uint32_t)wave_max_f32((float)most);
+        sum = wave_sum(sum);
+    }
+    const bool by_count = dealt_by_count(most, sum, S, G);
+    if (by_count) {
+        const uint32_t least = least_weight(sum, S, G);
+        W = 0;
+        for (uint32_t c = 0; c < S; c += kWave) W += wave_sum(c + ln < S ? max(tiles(c + ln), least) : 0u);
+        uint32_t front = 0;
+        for (uint32_t c = 0; c < S; c += kWave) {
+            const uint32_t w = c + ln < S ? max(tiles(c + ln), least) : 0u, incl = front + wave_incl_scan(w);
+            const uint64_t begun = __ballot(c + ln < S && dealt_from(incl - w, x, W, G) <= bx);   // (the last of them has bx)
+            if (begun == 0ull) break;
+            const int i = kWave - 1 - __clzll(begun);
+            dl.s = c + i;
+            w1 = wave_read_lane(incl, i);
+            w0 = w1 - wave_read_lane(w, i);
+            front = wave_read_lane(incl, kWave - 1);
+        }
+    }
+    dl.C = (uint32_t)__builtin_amdgcn_readfirstlane(by_count ? count[dl.s] : own);
+    const uint32_t nt = (dl.C + kTileN - 1u) / kTileN;
+    if (per > 0 && !by_count) {
+        const XcdTiles xt = xcd_tiles(nt, shared, dl.s, x);
+        const uint32_t first = bx - dl.s * per;
+        dl.run = xcd_run(xt, x, first, per, xt.n > first ? (xt.n - first + per - 1u) / per : 0u);
+    } else {                                                                  // (lane i: XCD i)
+        const uint32_t b0 = dealt_from(w0, ln & 7u, W, G), n = dealt_from(w1, ln & 7u, W, G) - b0;
+        const uint32_t incl = wave_incl_scan(ln < 8u ? n : 0u), mine = wave_read_lane(n, (int)x);
+        dl.run = dealt_run(nt, shared, bx - wave_read_lane(b0, (int)x), mine, wave_read_lane(incl, (int)x) - mine, wave_read_lane(incl, 7));
+    }
+    return dl;
+}
+
+template <typename ET, int MT, int KSN, int PARTS, bool EVEN>
 __global__ void __launch_bounds__(256, (stream_wgs(sizeof(ET) == 2, MT, KSN, PARTS)))
 k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
                 int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence; <= 16 MT*/,
                 int wgs /*workgroups per XCD and row group*/, int ngroups,
-                int per /*workgroups per XCD and sentence; DEALT: 1; -1: none stays with a sentence*/,
+                int per /*workgroups per XCD and sentence; 0: dealt*/,
                 int shared, const int32_t* __restrict__ cand, const int32_t* __restrict__ count, int V,
                 float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
     constexpr bool BF = sizeof(ET) == 2;
@@ -1018,7 +1108,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     float (*red)[GT][MT][4][kWave] = reinterpret_cast<float (*)[GT][MT][4][kWave]>(sm);   // [wave]
     static_assert(Lds::kRed >= (PARTS - 1) * KSN * 64, "");
     int32_t* ids = reinterpret_cast<int32_t*>(sm + Lds::kIds);                         // [two blocks of tiles][16]
-    uint32_t* chunk_pref = reinterpret_cast<uint32_t*>(sm + Lds::kPref);                   // [64]: tiles in front of every 64 sentences
+    uint32_t* shares = reinterpret_cast<uint32_t*>(sm + Lds::kPref);                       // [64]: a StreamDeal; EVEN: tiles in front of every 64 sentences
     // grid = 8 * wgs * ngroups; ids go round the XCDs, the row groups of one block of tiles follow each other on one
     const uint32_t xcd = blockIdx.x & 7u, slot_x = blockIdx.x >> 3;
     const uint32_t bx = slot_x / (uint32_t)ngroups;
@@ -1029,41 +1119,35 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
     LSH_TRACE_WG(0);
-    // Who takes what.  A workgroup knows its sentence before any count, and takes turns with the sentence's others:
+    // Who takes what.  A workgroup has one sentence, and all or some of the sentence's workgroups take turns:
     //   per > 0: workgroup i of a sentence's `per` on this XCD has the tiles i, i + per, ... of those of the XCD (XcdTiles);
-    //   DEALT, where that would leave many without work: XCD x has for sentence s the workgroups from (s wgs + r) / S on, r =
-    //     x S / 8, a few more or less per XCD and nearly the same number in all.  Of the tiles that all sentences share
-    //     they take turns, of the others every XCD has its share;
-    //   per < 0 (more sentences than workgroups): all tiles of all sentences in a row, cut evenly; an XCD has whole
-    //   sentences so far as that goes (a workgroup that took an eighth of a list of eight tiles went through a sentence per tile).
-    // (40 sentences x 6, d = 1096 fp32: 47.4 us a step cut evenly, 37.9 dealt; 33 x 15: 53.3, 45.9; what is to be known for dealing
-    // costs a microsecond: 8 x 5, d = 1024 bf16: 10.3 us with per, 10.9 dealt; hence a kernel of its own.)
-    int s = 0, own_count = 0;
-    uint32_t first = 0, every = 1, before = 0, mine = 0, all = 1, seg = 0, seg_end = 0, wg_end = 0;
-    const bool own = DEALT || per > 0;
-    if (own) {
-        const uint32_t uS = (uint32_t)S, G = (uint32_t)wgs;
-        s = (int)(!DEALT ? bx / (uint32_t)per : ((bx + 1u) * uS - (xcd * uS >> 3) - 1u) / G);
-        s = __builtin_amdgcn_readfirstlane(s);
-        own_count = count ? count[s] : V;
-        // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
-        const char* hb = reinterpret_cast<const char*>(H + ((size_t)s * B + row0) * d);
-        for (uint32_t at = tid * 128u; at < (uint32_t)(Bg * d) * 4u; at += 256u * 128u) load_to_lds4(hb + at, ring);
-        if (!DEALT) {
-            first = bx - (uint32_t)s * (uint32_t)per;
-            every = (uint32_t)per;
+    //   per = 0, where that would leave many without work, and where lists are of very different lengths: as dealt_from and
+    //   dealt_run say.  (40 sentences x 6, d = 1096 fp32: 48 us cut evenly, 40 dealt; 33 x 15: 44, 39.5.)
+    //   EVEN (so many sentences that this would give some of them half as many workgroups as others): the tiles of all
+    //   sentences in a row, cut evenly.
+    int s = 0, C = 0;
+    TileRun run{};
+    uint32_t seg = 0, seg_end = 0, wg_end = 0;
+    auto count_of = [&](int at) { const int n = count ? count[min(at, S - 1)] : V; return at < S ? n : 0; };
+    if constexpr (!EVEN) {
+        const uint32_t s0 = per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs);
+        if (q == 0) {
+            const StreamDeal dl = stream_deal(count, V, (uint32_t)S, (uint32_t)wgs, (uint32_t)per, (uint32_t)shared, xcd, bx, s0);
+            if (ln == 0) {
+                shares[0] = dl.s; shares[1] = dl.C; shares[2] = dl.run.n; shares[3] = dl.run.head;
+                shares[4] = dl.run.a0; shares[5] = dl.run.a1; shares[6] = dl.run.b0; shares[7] = dl.run.b1;
+            }
         } else {
-            const uint32_t r = (ln & 7u) * uS >> 3;                           // (lane x: XCD x)
-            const uint32_t b0 = ((uint32_t)s * G + r) / uS, b1 = ((uint32_t)(s + 1) * G + r) / uS;
-            const uint32_t incl = wave_incl_scan(ln < 8 ? b1 - b0 : 0u);
-            all = wave_read_lane(incl, 7);
-            mine = every = wave_read_lane(b1 - b0, (int)xcd);
-            before = wave_read_lane(incl, (int)xcd) - mine;
-            first = bx - wave_read_lane(b0, (int)xcd);
+            // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the counts are on their way
+            const char* hb = reinterpret_cast<const char*>(H + ((size_t)s0 * B + row0) * d);
+            for (uint32_t at = (tid - kWave) * 128u; at < (uint32_t)(Bg * d) * 4u; at += 192u * 128u) load_to_lds4(hb + at, ring);
         }
-    }
-    auto count_of = [&](int at) { const int n = count ? count[min(at, S - 1)] : V; return at < S ? n : 0; };   // (no branch around the load)
-    if (!own) {   // (every wave for itself, to the same result)
+        lds_barrier();
+        const uint4 x = reinterpret_cast<const uint4*>(shares)[0], y = reinterpret_cast<const uint4*>(shares)[1];
+        s = wave_read_lane(x.x, 0); C = wave_read_lane(x.y, 0);
+        run = {wave_read_lane(x.z, 0), wave_read_lane(x.w, 0), wave_read_lane(y.x, 0), wave_read_lane(y.y, 0), wave_read_lane(y.z, 0), wave_read_lane(y.w, 0)};
+        if (run.n == 0) { wait_vmem<0>(); return; }
+    } else {   // (every wave for itself, to the same result)
         static_assert(kMaxSentencesLogits <= kWave * kWave, "a lane per 64 sentences");
         constexpr int AHEAD = 8;
         uint32_t total = 0, in_front = ~0u;                                   // (lane c: tiles in front of sentence 64 c)
@@ -1077,7 +1161,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                 total += wave_sum(ntiles_of(n[j]));
             }
         }
-        chunk_pref[ln] = in_front;
+        shares[ln] = in_front;
         const uint32_t per_wg = (total + 8u * (uint32_t)wgs - 1u) / (8u * (uint32_t)wgs);
         seg = min(total, (xcd * (uint32_t)wgs + bx) * per_wg);
         wg_end = min(total, seg + per_wg);
@@ -1101,42 +1185,18 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     for (int i = 0; i < KSN; ++i) loff[i] = (uint32_t)(16 * (swz ^ (i * RPI >> SH))) + (uint32_t)(k0 * (int)sizeof(ET));
     const uint32_t ld_bytes = (uint32_t)(ld * (int64_t)sizeof(ET));           // (the host: below 2^31)
     for (;;) {
-        int C;
-        int n;                                                                // tiles of this workgroup, one after the other:
-        XcdTiles xt{};                                                        // of the XCD's, from `first` on; or, dealt:
-        uint32_t head = 0, rest0 = 0;                                         // `head` shared ones, then from rest0 on
-        if (own) {
-            C = __builtin_amdgcn_readfirstlane(own_count);
-            if (!DEALT) {
-                xt = xcd_tiles(ntiles_of(C), (uint32_t)shared, (uint32_t)s, xcd);
-                n = xt.n > first ? (int)((xt.n - first + every - 1u) / every) : 0;
-            } else {
-                const uint32_t nt = ntiles_of(C), cut = min((uint32_t)shared, nt), at = before + first;
-                auto share = [&](uint32_t w) { return cut + (uint32_t)((uint64_t)(nt - cut) * w / all); };
-                head = cut > at ? (cut - at + all - 1u) / all : 0u;
-                rest0 = share(before) + first;
-                const uint32_t end = share(before + mine);
-                n = (int)(head + (end > rest0 ? (end - rest0 + every - 1u) / every : 0u));
-            }
-            n = __builtin_amdgcn_readfirstlane(n);
-            if (n == 0) { wait_vmem<0>(); return; }
-        } else {
-            // the last sentence with at most `seg` tiles in front of it
-            const uint32_t in_front = chunk_pref[ln];
-            const int c = kWave - 1 - __clzll(__ballot(in_front <= seg)), at = c * kWave + ln, mine_c = count_of(at);
-            const uint32_t incl = wave_read_lane(in_front, c) + wave_incl_scan(ntiles_of(mine_c)), pref = incl - ntiles_of(mine_c);
+        if constexpr (EVEN) {   // the last sentence with at most `seg` tiles in front of it
+            const uint32_t in_front = shares[ln];
+            const int c = kWave - 1 - __clzll(__ballot(in_front <= seg)), at = c * kWave + ln, mine = count_of(at);
+            const uint32_t incl = wave_read_lane(in_front, c) + wave_incl_scan(ntiles_of(mine)), pref = incl - ntiles_of(mine);
             const int i = kWave - 1 - __clzll(__ballot(at < S && pref <= seg));
             s = c * kWave + i;
-            C = wave_read_lane((uint32_t)mine_c, i);
-            first = seg - wave_read_lane(pref, i);
+            C = wave_read_lane((uint32_t)mine, i);
             seg_end = min(wg_end, wave_read_lane(incl, i));
-            xt = {0u, 0u, ntiles_of(C)};
-            n = (int)(seg_end - seg);
+            run = {seg_end - seg, 0u, 0u, 0u, seg - wave_read_lane(pref, i), 1u};
         }
-        auto tile_of = [&](int t) __attribute__((always_inline)) { 
-            const uint32_t u = (uint32_t)t;
-            return (int)(!DEALT ? xcd_tile(xt, xcd, first + u * every) : u < head ? before + first + u * all : rest0 + (u - head) * every);
-        };
+        const int n = (int)run.n;
+        auto tile_of = [&](int t) __attribute__((always_inline)) { return (int)run.tile((uint32_t)t); };
         // candidates of block b (kStreamTiles tiles): two loads per wave
         auto load_ids = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
@@ -1389,7 +1449,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             lds_barrier();
         }
         LSH_TRACE_WG(15);
-        if (own) return;
+        if (!EVEN) return;
         seg = seg_end;
         if (seg == wg_end) return;
         __syncthreads();                                                      // (the candidates are read no more)

@@ -3,6 +3,7 @@
 // V = 2^24, d not a multiple of 4).  Built by tests/test_host_plans.py with hipcc
 // and run on the CPU; no GPU call is made (the kernels in the headers are compiled but never launched).  Every region must start aligned, lie behind its
 // predecessor and end inside what the size function reports.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -139,6 +140,94 @@ static void check_stream() {
     check_stream_regions<1, 1>(); check_stream_regions<1, 2>(); check_stream_regions<1, 4>();
     check_stream_regions<2, 1>(); check_stream_regions<2, 2>(); check_stream_regions<2, 4>();
 }
+// Counts the tiles of a run.
+static void take(const TileRun& r, std::vector<int>& seen) {
+    for (uint32_t u = 0; u < r.n; ++u) {
+        CHECK(r.tile(u) < seen.size() && (u == 0 || r.tile(u) > r.tile(u - 1)), "tile %u of %zu", r.tile(u), seen.size());
+        if (r.tile(u) < seen.size()) ++seen[r.tile(u)];
+    }
+}
+// Sentences dealt to workgroups: every workgroup has one sentence, every sentence a workgroup at least, and all its
+// tiles are taken once.
+static void check_dealt() {
+    for (uint32_t G : {1u, 2u, 21u, 64u, 96u})
+        for (uint32_t S = 1; S <= 8 * G; S += S < 40 ? 1 : S < 8 * G - 4 ? 13 : 1) {
+            std::vector<uint32_t> all(S, 0);
+            for (uint32_t x = 0; x < 8; ++x) {
+                CHECK(dealt_from(0, x, S, G) == 0 && dealt_from(S, x, S, G) == G, "S=%u G=%u", S, G);
+                for (uint32_t s = 0; s < S; ++s) {
+                    const uint32_t b0 = dealt_from(s, x, S, G), b1 = dealt_from(s + 1, x, S, G);
+                    all[s] += b1 - b0;
+                    for (uint32_t b = b0; b < b1; ++b) CHECK(dealt_sentence(b, x, S, G) == s, "workgroup %u of XCD %u (S=%u G=%u)", b, x, S, G);
+                }
+            }
+            for (uint32_t s = 0; s < S; ++s) CHECK(all[s] >= 8 * G / S && all[s] <= 8 * G / S + 1, "sentence %u has %u workgroups (S=%u G=%u)", s, all[s], S, G);
+            for (uint32_t s : {0u, S / 2, S - 1})
+                for (uint32_t n : {0u, 1u, 9u, 130u, 1003u})
+                    for (uint32_t shared : {0u, 1u, 62u, 5000u}) {
+                        std::vector<int> seen(n, 0);
+                        uint32_t before = 0;
+                        for (uint32_t x = 0; x < 8; ++x) {
+                            const uint32_t mine = dealt_from(s + 1, x, S, G) - dealt_from(s, x, S, G);
+                            for (uint32_t i = 0; i < mine; ++i) take(dealt_run(n, shared, i, mine, before, all[s]), seen);
+                            before += mine;
+                        }
+                        for (uint32_t i = 0; i < n; ++i) CHECK(seen[i] == 1, "tile %u of %u dealt %d times (S=%u G=%u)", i, n, seen[i], S, G);
+                    }
+        }
+}
+// Sentences dealt to workgroups by their lists' lengths, where the kernel does so: every workgroup is of one sentence, every
+// sentence has one at least, all its tiles are taken once, and none takes twice its share of the weights.
+static void check_dealt_by_count() {
+    int unequal = 0;
+    uint64_t rnd = 0x9E3779B97F4A7C15ull;
+    for (uint32_t G : {8u, 32u, 60u, 64u, 96u, 192u})
+        for (uint32_t S : {2u, 3u, 8u, 33u, 64u, 65u, 100u, 384u, 768u})
+            for (int kind = 0; kind < 6; ++kind) {
+                std::vector<uint32_t> n(S), weight(S), front(S + 1, 0);
+                uint32_t most = 0, sum = 0;
+                for (uint32_t s = 0; s < S; ++s) {
+                    rnd ^= rnd << 13; rnd ^= rnd >> 7; rnd ^= rnd << 17;
+                    n[s] = kind == 0 ? 100 : kind == 1 ? (s == S / 2 ? 2000 : 150) : kind == 2 ? (s ? 0 : 777) : kind == 3 ? (s % 5 ? 1 : 5000)
+                         : kind == 4 ? (uint32_t)(rnd >> 54) * (uint32_t)(rnd % 7 == 0) * 20 : (s + 1 == S ? 1u << 20 : 3);
+                    most = std::max(most, n[s]);
+                    sum += n[s];
+                }
+                if (!dealt_by_count(most, sum, S, G)) continue;
+                ++unequal;
+                const uint32_t least = least_weight(sum, S, G);
+                for (uint32_t s = 0; s < S; ++s) { weight[s] = std::max(n[s], least); front[s + 1] = front[s] + weight[s]; }
+                const uint32_t W = front[S];
+                CHECK((uint64_t)W * G + (7ull * W >> 3) < (1ull << 32), "overflow (S=%u G=%u kind=%d)", S, G, kind);
+                for (uint32_t s = 0; s < S; ++s) {
+                    uint32_t all = 0, before = 0;
+                    for (uint32_t x = 0; x < 8; ++x) all += dealt_from(front[s + 1], x, W, G) - dealt_from(front[s], x, W, G);
+                    CHECK(all > 0 && (double)n[s] * 8 * G <= 2.0 * all * W, "%u workgroups for %u tiles (S=%u G=%u kind=%d)", all, n[s], S, G, kind);
+                    std::vector<int> seen(n[s], 0);
+                    for (uint32_t x = 0; x < 8 && all; ++x) {
+                        const uint32_t mine = dealt_from(front[s + 1], x, W, G) - dealt_from(front[s], x, W, G);
+                        for (uint32_t i = 0; i < mine; ++i) take(dealt_run(n[s], 62, i, mine, before, all), seen);
+                        before += mine;
+                    }
+                    CHECK(std::all_of(seen.begin(), seen.end(), [](int k) { return k == 1; }), "tiles of sentence %u (S=%u G=%u kind=%d)", s, S, G, kind);
+                }
+            }
+    CHECK(unequal > 40 && !dealt_by_count(100, 100, 1, 64) && !dealt_by_count(1 << 20, 1 << 20, 1, 64), "%d unequal ones", unequal);
+}
+// An XCD's tiles by turns, and in pieces.
+static void check_xcd_runs() {
+    for (uint32_t n : {0u, 1u, 9u, 130u, 1003u})
+        for (uint32_t shared : {0u, 1u, 62u, 5000u})
+            for (uint32_t every : {1u, 2u, 3u, 64u}) {
+                std::vector<int> seen(n, 0), pieces(n, 0);
+                for (uint32_t x = 0; x < 8; ++x) {
+                    const XcdTiles t = xcd_tiles(n, shared, 0, x);
+                    for (uint32_t f = 0; f < every; ++f) take(xcd_run(t, x, f, every, t.n > f ? (t.n - f + every - 1) / every : 0), seen);
+                    for (uint32_t f = 0; f < t.n; f += every) take(xcd_run(t, x, f, 1, std::min(every, t.n - f)), pieces);
+                }
+                for (uint32_t i = 0; i < n; ++i) CHECK(seen[i] == 1 && pieces[i] == 1, "tile %u of %u (every %u)", i, n, every);
+            }
+}
 static void check_xcd_tiles() {
     for (uint32_t n : {0u, 1u, 7u, 8u, 9u, 130u, 1003u})
         for (uint32_t shared : {0u, 1u, 8u, 62u, 125u, 5000u})
@@ -216,6 +305,9 @@ int main() {
             for (int d : {8, 50, 1000, 1024, 1026, 4099}) check_hlds(S, rows, d);
     check_stream();
     check_xcd_tiles();
+    check_xcd_runs();
+    check_dealt();
+    check_dealt_by_count();
     CHECK(2 * rows_lds_bytes(5) <= kLdsLimit && 2 * few_lds_bytes<float>(3) <= kLdsLimit && 2 * few_lds_bytes<uint16_t>(2) <= kLdsLimit,
           "full-vocabulary kernels: two workgroups do not share a CU");
     CHECK(estage_lds_bytes() <= kLdsLimit, "estage LDS");

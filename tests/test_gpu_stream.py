@@ -78,6 +78,27 @@ def test_sentences_dealt_to_workgroups(S, d, bf16):
 
 
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("S,B", [(8, 12), (33, 3), (70, 3)])
+@pytest.mark.parametrize("d", [100, 700])
+def test_lists_of_different_lengths(d, S, B, bf16):
+    """A few lists many times as long as the others: their sentences get more workgroups."""
+    V = 24000
+    rng = np.random.default_rng(S + d)
+    E = rng.standard_normal((V, d)).astype(np.float32) / np.sqrt(d)
+    E[:V // 2] = E[0] + 0.01 * E[:V // 2]                # (half of all words share their codes)
+    E = E.astype(np.float32)
+    perms = np.stack([rng.permutation(d)[:8] for _ in range(12)]).astype(np.int32)
+    gc = GpuCase(workloads.f32_to_bf16_bits(E) if bf16 else E, perms, np.arange(600, dtype=np.int32), 3)
+    H = (3.0 * rng.standard_normal((S, B, d))).astype(np.float32)
+    H[1] = 3.0 * np.sqrt(d) * E[0]
+    H[S - 2, 0] = H[1, 0]
+    H = H.reshape(S * B, d)
+    counts = [len(gc.index.candidates(H[s * B:(s + 1) * B], gc.topfreq)) for s in range(S)]
+    assert counts[1] > 4 * np.median(counts)
+    run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
 @pytest.mark.parametrize("B", [3, 18])
 @pytest.mark.parametrize("d", [40, 100, 200, 300, 600, 1000, 1500, 2047])
 def test_tiles_cut_evenly(d, B, bf16):
