@@ -936,3 +936,48 @@ def test_argument_validation_returns_codes_and_leaves_outputs_untouched():
     bad[0, 0] = cfg.d
     with pytest.raises(lsh.LshBeamError):
         lsh.build_tables(gc.E_dev, bad, cfg.K, cfg.W)
+
+
+# ---------------------------------------------------------------------------------------------
+# where the fused plan ends
+# ---------------------------------------------------------------------------------------------
+
+@pytest.mark.parametrize("S,B,d,bf16", [(1, 26, 1000, False), (1, 17, 1536, False), (2, 32, 1072, True), (3, 20, 216, False)])
+def test_two_row_groups_of_few_tiles_stay_with_the_fused_sums(S, B, d, bf16):
+    """17 to 32 beams: logits no further from fp64 than those of the fused kernel, which sums 16 parts of the row."""
+    import torch
+    V = 12000
+    rng = np.random.default_rng(d + B)
+    E = (rng.standard_normal((V, d)) / np.sqrt(d)).astype(np.float32)
+    bits = workloads.f32_to_bf16_bits(E)
+    if bf16:
+        E = (bits.astype(np.uint32) << 16).view(np.float32)
+    perms = np.stack([rng.permutation(d)[:8] for _ in range(32)]).astype(np.int32)
+    gc = GpuCase(bits if bf16 else E, perms, np.arange(900, dtype=np.int32), 8)
+    H = (4.0 * rng.standard_normal((S * B, d))).astype(np.float32)
+    bs = np.zeros(S * B, np.float32)
+
+    def error():
+        sp, ws = gc.step(H, bs, S, B)[3:]
+        at, pitch = (4 * S * V + 255) // 256 * 256 + 256, (V + 63) // 64 * 64
+        logits = ws[at:at + 4 * S * B * pitch].view(torch.float32).view(S, B, pitch).cpu().numpy()
+        r = []
+        for s in range(S):
+            e, h = E[gc.tables.debug_candidates(ws, sp, s)].astype(np.float64), H[s * B:(s + 1) * B].astype(np.float64)
+            r.append((logits[s, :, :len(e)] - h @ e.T) / (np.abs(h) @ np.abs(e).T))
+        return np.sqrt(np.mean(np.concatenate(r, axis=1) ** 2))
+    got = error()
+    gc.tables.set_options(fused=1)
+    assert got <= 1.02 * error(), (got, error())
+
+
+def test_threshold_lists_end_the_fused_plan_earlier():
+    """Lists of words that collide several times are longer than expected where words are clustered: with 1.7 tiles expected
+    for each workgroup the fused plan is left, with 1.4 it is not."""
+    from paper_1806_00588_amd import binding
+    rng = np.random.default_rng(5)
+    E = rng.standard_normal((6000, 40)).astype(np.float32)
+    perms = np.stack([rng.permutation(40)[:4] for _ in range(9)]).astype(np.int32)
+    gc = GpuCase(E, perms, np.arange(1740, dtype=np.int32), 3)
+    assert not binding.step_is_fused(gc.tables, binding.step_params(4, 3, 1740, 3))
+    assert binding.step_is_fused(gc.tables, binding.step_params(4, 3, 1400, 3))
