@@ -1101,6 +1101,12 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     constexpr bool LATE = BF && PARTS > 3;
     constexpr int NH = LATE ? 2 : BF ? 3 : 1;
     constexpr int NI = Lds::NI;
+    // Chains of sums per quarter: a part's products go to chain part % CHAINS.  More than one for fp32 rows of more than 1024
+    // values, so that the full vocabulary's logits are as near as those of k_logits_rows, which took some of
+    // these calls before this kernel was faster: root mean square over the products' sizes, V = 2000, 8 x 16 rows, dense: d = 1100
+    // 0.91e-8 there, 1.42e-8 with one chain, 0.77e-8 with four (8 x 16, 32.1, 23.8, 22.3 us); d = 1536 0.93, 1.41, 0.78 (45.7,
+    // 27.3, 25.6); hidden rows near words: 2.58e-8, 2.24, 1.05.
+    constexpr int CHAINS = !BF && !EVEN && PARTS > 4 ? 4 : 1;
     constexpr int RPI = kWave / PP;                                           // rows per load instruction
     extern __shared__ uint4 ssm[];
     // (the ring behind other things: the address in M0 is its place less the load's offset, and must not be negative)
@@ -1349,7 +1355,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             const int last = min(g * GT + GT, n) - 1;
             if (__builtin_expect(again != 0u, 0) && ((last & (kStreamTiles - 1)) == kStreamTiles - 1 || last == n - 1)) settle(last & ~(kStreamTiles - 1));
         };
-        floatx4 acc[GT][MT];
+        floatx4 acc[CHAINS][GT][MT];
         uint32_t slot = 0;                                                    // byte of the ring where the next unit is
         // The units of a group.  STEADY: every one of them is there and is followed by another RING units on.
         auto contract = [&](auto steady_c, int g) __attribute__((always_inline)) {
@@ -1396,8 +1402,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                                 }
 #pragma unroll
                                 for (int p = 0; p < 3; ++p)
-                                    acc[gu * TS + t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hp[p]),
-                                                                                        __builtin_bit_cast(bf16x8, e), acc[gu * TS + t][m], 0, 0, 0);
+                                    acc[0][gu * TS + t][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, hp[p]),
+                                                                                           __builtin_bit_cast(bf16x8, e), acc[0][gu * TS + t][m], 0, 0, 0);
                             }
                         } else {
 #pragma unroll
@@ -1406,7 +1412,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                                 for (int m = 0; m < MT; ++m) {
                                     const uint4 hv = h[m][part * KSN + st][0];
                                     const uint32_t hx = x == 0 ? hv.x : x == 1 ? hv.y : x == 2 ? hv.z : hv.w;
-                                    acc[gu * TS + t][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(hx), __uint_as_float(ew[x]), acc[gu * TS + t][m], 0, 0, 0);
+                                    floatx4& sum = acc[part % CHAINS][gu * TS + t][m];
+                                    sum = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(hx), __uint_as_float(ew[x]), sum, 0, 0, 0);
                                 }
                         }
                     }
@@ -1423,14 +1430,18 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
 #pragma unroll
             for (int t = 0; t < GT; ++t)
 #pragma unroll
-                for (int m = 0; m < MT; ++m) acc[t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int m = 0; m < MT; ++m)
+#pragma unroll
+                    for (int c = 0; c < CHAINS; ++c) acc[c][t][m] = floatx4{0.f, 0.f, 0.f, 0.f};
             if ((g + 1) * (GU * PARTS) + RING <= units) contract(std::true_type{}, g); else contract(std::false_type{}, g);
 #pragma unroll
             for (int t = 0; t < GT; ++t)
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) red[q][t][m][r][ln] = acc[t][m][r];
+                    for (int r = 0; r < 4; ++r)
+                        red[q][t][m][r][ln] = CHAINS == 1 ? acc[0][t][m][r]
+                                                          : (acc[0][t][m][r] + acc[1 % CHAINS][t][m][r]) + (acc[2 % CHAINS][t][m][r] + acc[3 % CHAINS][t][m][r]);
             lds_barrier();
             // thread (i, col) sums row i, column col of every tile: 16 lanes per row
             const int i = tid >> 4;

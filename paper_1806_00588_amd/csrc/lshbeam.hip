@@ -589,9 +589,10 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
 // (in no unit; for d from 96 to 1536 and either type each is within 12 % of that, up to a factor of d's own).
 // Over V = 10000 .. 100000, d = 128 .. 1536 and 48 .. 640 rows (181 shapes of each type, every m measured)
 // the choice is 0.1 % slower than the best one on average and 6 % at most.
-// Where even k_logits_stream, with a tile of 16 words and one or two row groups per workgroup and k split over
-// its waves, fills the chip at most twice over, it is the faster one: the others then run few workgroups through
-// a long chain of k blocks (31 rows, V = 2009, d = 1181: 22.8 -> 10.6 us).
+// Where even k_logits_stream, with a tile of 16 words and groups of hidden rows per workgroup and k split over its waves, has
+// at most 512 workgroups' worth of tiles in groups of 32 rows (1024 in groups of 16), it is the faster one: the others then
+// run few workgroups through a long chain of k blocks (31 rows, V = 2009, d = 1181: 22.8 -> 10.6 us; 128 rows, V = 2000, d = 1100:
+// 32.1 -> 22.3, V = 1000, 256 rows: 34.4 -> 22.5).  Its logits are as near: k_logits_stream's CHAINS.
 constexpr int kRowsMinD = 8;   // (a row holds at least one 16-byte chunk)
 // Row tiles per workgroup at most: what the 256 registers of a lane leave room for.
 template <typename ET> constexpr int rows_max_mt() { return sizeof(ET) == 2 ? 4 : 5; }
