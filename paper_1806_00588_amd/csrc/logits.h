@@ -1019,6 +1019,12 @@ template <int MT, int KSN> struct StreamLds {
     static constexpr size_t kIds = kRed + kRings, kPref = kIds + (size_t)2 * kStreamTiles * kTileN * 4;
     static constexpr size_t kBytes = kPref + kWave * 4;
 };
+// Whether steps of a row's last part that are past its end are left out: of two or three parts of rows that have such steps, and
+// where a step is dear.  (The branches cost more than they save where there are none.  fp32, us a step without and with them:
+// 100 x 24 beams, d = 264, V = 30000, five steps of eight: 148, 120; d = 520, nine of twelve: 196, 178; d = 400, seven of eight:
+// 140, 132; d = 512, all eight: 137.6, 138.9; 32 x 10, d = 264: 37.6, 35.1; d = 512: 37.2, 37.5; d = 800, 13 of 16: 48.3, 48.2.)
+constexpr bool stream_may_trim(int PARTS) { return PARTS == 2 || PARTS == 3; }
+constexpr bool stream_must_trim(bool bf16, int PARTS) { return bf16 && PARTS > 3; }
 // f(integral_constant 0), ..., f(integral_constant N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) {
@@ -1081,7 +1087,7 @@ __device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ co
     return dl;
 }
 
-template <typename ET, int MT, int KSN, int PARTS, bool EVEN>
+template <typename ET, int MT, int KSN, int PARTS, bool EVEN, bool TRIM>
 __global__ void __launch_bounds__(256, (stream_wgs(sizeof(ET) == 2, MT, KSN, PARTS)))
 k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
                 int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence; <= 16 MT*/,
@@ -1380,9 +1386,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                 __builtin_amdgcn_sched_barrier(0);
                 static_for<KSN>([&](auto st_c) __attribute__((always_inline)) {
                     constexpr int st = decltype(st_c)::value;
-                    // (steps past the quarter meet zeros.  Where a step is dear they are left out; elsewhere the branch
-                    // costs more: 32 x 10 beams, d = 1000: 33.3 us, 34.3 with it)
-                    const bool is_step = !LATE || part < PARTS - 1 || st == 0 || st < last_steps;   // (uniform)
+                    // (steps past the quarter meet zeros, or, TRIM, are left out)
+                    const bool is_step = !TRIM || part < PARTS - 1 || st == 0 || st < last_steps;   // (uniform)
 #pragma unroll
                     for (int t = 0; t < TS && is_step; ++t) {
                         const uint4 e = ev[t][st];

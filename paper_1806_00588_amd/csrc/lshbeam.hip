@@ -428,12 +428,12 @@ inline bool names_hlds(const lsh_tables* t) {
     return t->opt[kOptLogitsHlds] != kAuto || t->opt[kOptHldsRows] != kAuto || t->opt[kOptHldsRem] != kAuto ||
            t->opt[kOptLogitsPlanes] != kAuto;
 }
-// k_logits_stream: steps of 64 bytes per unit and parts of a wave's quarter of the row.
-struct StreamPlan { int ksn, parts; };
+// k_logits_stream: steps of 64 bytes per unit and parts of a wave's quarter of the row; whether the last has fewer steps.
+struct StreamPlan { int ksn, parts; bool short_last; };
 template <typename ET> StreamPlan stream_plan(int d) {
     constexpr int kstep = 4 * ElemTraits<ET>::VEC;
     const int nst = ((d + kstep - 1) / kstep + 3) / 4;
-    return nst <= 1 ? StreamPlan{1, 1} : nst <= 4 ? StreamPlan{2, (nst + 1) / 2} : StreamPlan{4, (nst + 3) / 4};
+    return nst <= 1 ? StreamPlan{1, 1, false} : nst <= 4 ? StreamPlan{2, (nst + 1) / 2, nst % 2 != 0} : StreamPlan{4, (nst + 3) / 4, nst % 4 != 0};
 }
 // Hidden rows per workgroup (0: the kernel does not take the step): more than 16 beams in even groups of at most 16, every
 // group with its own pass over the candidate rows (from the XCD's L2), or of at most 32 where the rows are so short that
@@ -472,8 +472,10 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     if (!same) per = 0;
     if (per > 0) wgs = per * sp->S;
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \
-    launch(cx, 1, even ? k_logits_stream<ET, MTV, KSNV, PV, true> : k_logits_stream<ET, MTV, KSNV, PV, false>, dim3(8 * wgs * ngroups), dim3(256), StreamLds<MTV, KSNV>::kBytes, \
-           (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per, shared, cand, count, t->V, w.logits, \
+    launch(cx, 1, even ? k_logits_stream<ET, MTV, KSNV, PV, true, stream_may_trim(PV) || stream_must_trim(sizeof(ET) == 2, PV)>  \
+                  : p.short_last && stream_may_trim(PV) ? k_logits_stream<ET, MTV, KSNV, PV, false, stream_may_trim(PV) || stream_must_trim(sizeof(ET) == 2, PV)> \
+                  : k_logits_stream<ET, MTV, KSNV, PV, false, stream_must_trim(sizeof(ET) == 2, PV)>,             \
+           dim3(8 * wgs * ngroups), dim3(256), StreamLds<MTV, KSNV>::kBytes, (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per, shared, cand, count, t->V, w.logits, \
            w.cpitch, w.records())
 #define LSH_STREAM2(KSNV, PV) do { if (rows > kTileM) LSH_STREAM(2, KSNV, PV); else LSH_STREAM(1, KSNV, PV); } while (0)
     if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2 && p.parts == 2) LSH_STREAM2(2, 2); else if (p.ksn == 2) LSH_STREAM2(2, 1);
@@ -657,10 +659,12 @@ hipError_t allow_logits_lds() {
     LSH_ALLOW(1, 16, U1, false); LSH_ALLOW(2, 16, U2W, false);
     if constexpr (std::is_same<ET, uint16_t>::value) LSH_ALLOW(1, 8, U1, true);
 #undef LSH_ALLOW
-#define LSH_ALLOW(...)                                                                              \
+#define LSH_ALLOW(MTV, KSNV, PV)                                                                        \
     do {                                                                                            \
-        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, __VA_ARGS__, false>>();        \
-        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, __VA_ARGS__, true>>();         \
+        constexpr bool must = stream_must_trim(sizeof(ET) == 2, PV), may = stream_may_trim(PV) || must; \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, must>>();    \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, may>>();     \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, true, may>>();      \
     } while (0)
     LSH_ALLOW(1, 1, 1); LSH_ALLOW(1, 2, 1); LSH_ALLOW(1, 4, 2); LSH_ALLOW(1, 4, 3); LSH_ALLOW(1, 4, 4);
     LSH_ALLOW(2, 1, 1); LSH_ALLOW(2, 2, 1); LSH_ALLOW(1, 2, 2); LSH_ALLOW(2, 2, 2);

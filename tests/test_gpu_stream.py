@@ -48,6 +48,17 @@ def test_many_tiles(shape, bf16):
         run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
 
 
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("d", [132, 192, 196, 256, 260, 320, 384, 448, 508, 512, 520, 580, 700, 768])
+def test_last_parts_of_every_length(d, bf16):
+    """Rows of two and three parts whose last has one, some or all of its steps, with and without a partial chunk (bf16: of
+    one and two), in one and two row groups."""
+    rng, gc = _case(500, d + (2 if d % 3 == 0 else 0), 150, bf16)
+    for S, B in [(9, 5), (9, 18)]:
+        H = (3.0 * rng.standard_normal((S * B, gc.d))).astype(np.float32)
+        run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
+
+
 @pytest.mark.parametrize("run", [2, 3, 5, 16])
 @pytest.mark.parametrize("B", [1, 2, 7, 16])
 def test_winners_that_share_a_tile(B, run):
