@@ -437,19 +437,21 @@ template <typename ET> StreamPlan stream_plan(int d) {
 }
 // Hidden rows per workgroup (0: the kernel does not take the step): more than 16 beams in even groups of at most 16, every
 // group with its own pass over the candidate rows (from the XCD's L2), or of at most 32 where the rows are so short that
-// this pass is what counts, or the call so large.  fp32, d = 1000, V = 40000: 1 x 32 beams 40 us with 32 rows per
-// workgroup, 33 with 16; 9 x 17: 50, 48; d = 512, V = 20000: 9 x 32 44, 38; 32 x 50 118, 125; d = 256, V = 10000: 9 x 32
-// 29, 28; 64 x 20 43, 48.  Two parts, from 96 groups of 16 on (V = 40000 / 107641 with 16-bit codes, groups of 16, of 32): 48 x 24,
-// d = 295, 110, 96 / 58, 54; d = 512 103, 93 / 58, 57; 32 x 31, d = 512 85, 82 / 51, 52; 21 x 31 67, 71 / 42, 48.  (The longest
-// bf16 rows, four parts, need 16 registers more
-// than there are; the spills cost less than the other kernel does: 32 sentences x 10 beams, V = 40000, 34 us against
-// 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
+// this pass is what counts.  fp32, d = 1000, V = 40000: 1 x 32 beams 40 us with 32 rows per workgroup, 33 with 16; 9 x 17: 50, 48;
+// d = 256, V = 10000: 9 x 32 29, 28; 64 x 20 43, 48.  Rows of two parts: groups of 32 where these hold no more empty rows than groups
+// of 16 would, up to seven steps always (16 and 32 rows; 20 x 20, V = 40000: d = 264 52.0, 45.8; d = 440 54.1, 47.8; 16 x 28,
+// V = 10000: 38.6, 36.6; 39.9, 38.2; full vocabulary of 2000, 128 rows, d = 264: 14.7, 14.0; d = 448: 15.9, 16.1), with eight from
+// nine expected tiles for each of the 256 CUs on (d = 512: 32 x 31, V = 40000, 86, 80; 20 x 20 53.9, 52.2; 10 x 90, V = 20000, 113, 105;
+// 8 x 32, V = 40000, 44.5, 47; 16 x 28, V = 10000, 40, 40.8); three groups of 16 stay (24 x 40, V = 60000, 189, 200).  (The longest
+// bf16 rows, four parts, need 16 registers more than there are; the spills cost less than the other kernel does: 32 sentences x 10
+// beams, V = 40000, 34 us against 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
 template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
     if (!has_chunks(t) || t->ld * (int64_t)sizeof(ET) >= (int64_t)1 << 31) return 0;
     const StreamPlan p = stream_plan<ET>(t->d);
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
-    const bool two = sp->B > kTileM && (p.ksn < 4 || (sizeof(ET) == 4 && p.parts == 2 &&
-                                                                      sp->S * ((sp->B + kTileM - 1) / kTileM) >= 96));
+    const bool whole = (sp->B + kTileM - 1) / kTileM % 2 == 0;   // groups of 32 have no more padding than groups of 16
+    const bool two = sp->B > kTileM && (p.ksn < 4 || (sizeof(ET) == 4 && p.parts == 2 && whole &&
+                                                      (t->d <= 448 || sp->S * expected_candidates(t, sp) >= 2304 * kTileN)));
     const int most = two ? 2 * kTileM : kTileM, groups = (sp->B + most - 1) / most;
     return (sp->B + groups - 1) / groups;
 }

@@ -59,6 +59,16 @@ def test_last_parts_of_every_length(d, bf16):
         run_and_check(None, gc, H, rng.standard_normal(S * B).astype(np.float32), S, B)
 
 
+@pytest.mark.parametrize("V,T", [(1500, 40), (20000, 700)], ids=["few", "many"])
+@pytest.mark.parametrize("B", [17, 32, 33, 50])
+@pytest.mark.parametrize("d", [300, 450, 512])
+def test_row_groups_of_two_parts(d, B, V, T):
+    """Two, three and four times 16 rows, on either side of the tiles from which groups of 32 are taken."""
+    rng, gc = _case(V, d, T, False)
+    H = (3.0 * rng.standard_normal((4 * B, d))).astype(np.float32)
+    run_and_check(None, gc, H, rng.standard_normal(4 * B).astype(np.float32), 4, B)
+
+
 @pytest.mark.parametrize("run", [2, 3, 5, 16])
 @pytest.mark.parametrize("B", [1, 2, 7, 16])
 def test_winners_that_share_a_tile(B, run):
