@@ -294,13 +294,13 @@ bool step_is_fused(const lsh_tables* t, const lsh_step_params* sp) {
     //   one row group, 2.4 with long fp32 rows (d = 1000: 4 x 12 beams, 1.9 tiles, 23.2 / 27.4; 6 x 8, 2.4, 26.1 / 26.7;
     //   8 x 4, 2.6, 27.3 / 24.7), 1.9 with shorter ones (d = 512: 8 x 12, 1.9, 20.7 / 22.9; 12 x 8, 2.4, 22.2 / 21.7), 1.8 with bf16
     //   (d = 1024: 3 x 16, 1.6, 22.0 / 25.0; 4 x 12, 1.9, 24.7 / 23.9; V = 100000: 2 x 12, 2.05, 26.8 / 26.1);
-    //   two, and lists of words that collide `threshold` times, where clustered words make them longer than expected, 1.5.
-    //   (Two groups of d = 1000, V = 40000: 1 x 26, 0.7, 25.6 / 30.1; 1 x 32, 0.8, 36.0 / 33.4; 2 x 24, 1.4, 31.3 / 33.0; d = 1536, 1 x 17,
+    //   two, 1.5 (d = 1000, V = 40000: 1 x 26, 0.7, 25.6 / 30.1; 1 x 32, 0.8, 36.0 / 33.4; 2 x 24, 1.4, 31.3 / 33.0; d = 1536, 1 x 17,
     //   24.1 / 29.5; d = 512 bf16, 2 x 24, 25.8 / 28.4.  The fused kernel's sums, of 16 waves' instead of 4, are also nearer: 1.0e-8 of
-    //   the products' sizes against 1.7e-8.  118 bands, t = 3, d = 216, 4 x 9, 1.6 and 6.3 in fact: 40.9 / 36.6.)
+    //   the products' sizes against 1.7e-8.)  With a hit threshold, clustered words make the lists longer than expected, which does not
+    //   decide it: 118 bands, t = 3, d = 216, 4 x 9 beams, 40.9 / 36.6; 173 bands, t = 4, d = 88, 4 x 1, 22.2 / 24.2.
     const double tiles = sp->S * expected_candidates(t, sp) / (256 * kTileN);
     if (!possible || sp->S * MT > 8 || MT > 2) return false;
-    return tiles <= (MT == 2 || sp->threshold > 1 ? 1.5 : t->dtype != LSH_F32 ? 1.8 : t->d > 512 ? 2.4 : 1.9);
+    return tiles <= (MT == 2 ? 1.5 : t->dtype != LSH_F32 ? 1.8 : t->d > 512 ? 2.4 : 1.9);
 }
 
 // LDS words for the staged hidden rows of a step: room for all B rows of a sentence (up to

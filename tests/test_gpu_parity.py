@@ -969,15 +969,3 @@ def test_two_row_groups_of_few_tiles_stay_with_the_fused_sums(S, B, d, bf16):
     got = error()
     gc.tables.set_options(fused=1)
     assert got <= 1.02 * error(), (got, error())
-
-
-def test_threshold_lists_end_the_fused_plan_earlier():
-    """Lists of words that collide several times are longer than expected where words are clustered: with 1.7 tiles expected
-    for each workgroup the fused plan is left, with 1.4 it is not."""
-    from paper_1806_00588_amd import binding
-    rng = np.random.default_rng(5)
-    E = rng.standard_normal((6000, 40)).astype(np.float32)
-    perms = np.stack([rng.permutation(40)[:4] for _ in range(9)]).astype(np.int32)
-    gc = GpuCase(E, perms, np.arange(1740, dtype=np.int32), 3)
-    assert not binding.step_is_fused(gc.tables, binding.step_params(4, 3, 1740, 3))
-    assert binding.step_is_fused(gc.tables, binding.step_params(4, 3, 1400, 3))
