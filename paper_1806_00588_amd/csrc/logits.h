@@ -675,12 +675,11 @@ __host__ __device__ __forceinline__ bool dealt_by_count(uint32_t most, uint32_t 
 }
 // A list's weight: its tiles, or as much as a workgroup takes (8 G (least) >= sum + S (least) >= W; W < 2^24 + 4 G).
 __host__ __device__ __forceinline__ uint32_t least_weight(uint32_t sum, uint32_t S, uint32_t G) { return (sum + 8u * G - S - 1u) / (8u * G - S); }
-// What number `first` of the `mine` workgroups a sentence has on an XCD takes, with `before` of its `all` on the XCDs in
-// front: of the tiles that all sentences share they take turns, of the others every XCD has its share.
+// What number `first` of the `mine` workgroups a sentence has on an XCD takes, with `before` of its `all` < 4096 on the XCDs in
+// front (ntiles <= 2^20): of the tiles that all sentences share they take turns, of the others every XCD has its share.
 __host__ __device__ __forceinline__ TileRun dealt_run(uint32_t ntiles, uint32_t shared, uint32_t first, uint32_t mine, uint32_t before, uint32_t all) {
     const uint32_t cut = shared < ntiles ? shared : ntiles, at = before + first;
-    const uint32_t begin = cut + (uint32_t)((uint64_t)(ntiles - cut) * before / all) + first;
-    const uint32_t end = cut + (uint32_t)((uint64_t)(ntiles - cut) * (before + mine) / all);
+    const uint32_t begin = cut + (ntiles - cut) * before / all + first, end = cut + (ntiles - cut) * (before + mine) / all;
     const uint32_t head = cut > at ? (cut - at + all - 1u) / all : 0u;
     return {head + (end > begin ? (end - begin + mine - 1u) / mine : 0u), head, at, all, begin - head * mine, mine};
 }
@@ -1042,24 +1041,39 @@ __device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ co
     auto tiles = [&](uint32_t at) { return ((uint32_t)count[min(at, S - 1u)] + kTileN - 1u) / kTileN; };   // (no branch around the load)
     StreamDeal dl;
     dl.s = s0;
-    uint32_t w0 = s0, w1 = s0 + 1u, W = S, most = 0, sum = 0;
+    uint32_t most = 0, sum = 0, first = 0, mine = 0, before = 0, all = 1;
+    // (lane i: XCD i)
+    auto workgroups = [&](uint32_t w0, uint32_t w1, uint32_t W) {
+        const uint32_t b0 = dealt_from(w0, ln & 7u, W, G), n = dealt_from(w1, ln & 7u, W, G) - b0, incl = wave_incl_scan(ln < 8u ? n : 0u);
+        mine = wave_read_lane(n, (int)x);
+        before = wave_read_lane(incl, (int)x) - mine;
+        all = wave_read_lane(incl, 7);
+        first = bx - wave_read_lane(b0, (int)x);
+    };
     const int own = count ? count[s0] : V;
     if (count) {
         constexpr uint32_t AT_ONCE = 6;
-        for (uint32_t c = 0; c < S; c += AT_ONCE * kWave) {
-            uint32_t n[AT_ONCE];
+        uint32_t n[AT_ONCE];
 #pragma unroll
-            for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles(c + j * kWave + ln);
+        for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles(j * kWave + ln);
+        if (per == 0) workgroups(s0, s0 + 1u, S);   // (while the counts are on their way)
+        for (uint32_t c = 0;;) {
 #pragma unroll
             for (uint32_t j = 0; j < AT_ONCE; ++j) { most = max(most, n[j]); sum += c + j * kWave + ln < S ? n[j] : 0u; }
+            c += AT_ONCE * kWave;
+            if (c >= S) break;
+#pragma unroll
+            for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles(c + j * kWave + ln);
         }
         most = (uint32_t)wave_max_f32((float)most);
         sum = wave_sum(sum);
+    } else if (per == 0) {
+        workgroups(s0, s0 + 1u, S);
     }
     const bool by_count = dealt_by_count(most, sum, S, G);
     if (by_count) {
         const uint32_t least = least_weight(sum, S, G);
-        W = 0;
+        uint32_t W = 0, w0 = 0, w1 = 1;
         for (uint32_t c = 0; c < S; c += kWave) W += wave_sum(c + ln < S ? max(tiles(c + ln), least) : 0u);
         uint32_t front = 0;
         for (uint32_t c = 0; c < S; c += kWave) {
@@ -1072,17 +1086,16 @@ __device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ co
             w0 = w1 - wave_read_lane(w, i);
             front = wave_read_lane(incl, kWave - 1);
         }
+        workgroups(w0, w1, W);
     }
     dl.C = (uint32_t)__builtin_amdgcn_readfirstlane(by_count ? count[dl.s] : own);
     const uint32_t nt = (dl.C + kTileN - 1u) / kTileN;
     if (per > 0 && !by_count) {
         const XcdTiles xt = xcd_tiles(nt, shared, dl.s, x);
-        const uint32_t first = bx - dl.s * per;
+        first = bx - dl.s * per;
         dl.run = xcd_run(xt, x, first, per, xt.n > first ? (xt.n - first + per - 1u) / per : 0u);
-    } else {                                                                  // (lane i: XCD i)
-        const uint32_t b0 = dealt_from(w0, ln & 7u, W, G), n = dealt_from(w1, ln & 7u, W, G) - b0;
-        const uint32_t incl = wave_incl_scan(ln < 8u ? n : 0u), mine = wave_read_lane(n, (int)x);
-        dl.run = dealt_run(nt, shared, bx - wave_read_lane(b0, (int)x), mine, wave_read_lane(incl, (int)x) - mine, wave_read_lane(incl, 7));
+    } else {
+        dl.run = dealt_run(nt, shared, first, mine, before, all);
     }
     return dl;
 }

@@ -467,10 +467,18 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     int wgs = (int)std::min<int64_t>((tiles_n + 7) / 8, std::max(1, t->option(kOptLogitsGrid, 256 * stream_wgs(sizeof(ET) == 2, rows > kTileM ? 2 : 1, p.ksn, p.parts)) / 8 / ngroups));
     int per = wgs / sp->S;
     // A workgroup stays with one sentence: where the same number for every sentence leaves at most an eighth of them without
-    // work, or dealt to them, where no sentence gets less than seven eighths of its share (and two at least, so that shares can
-    // follow the lists' lengths).  Otherwise an even cut: V = 20000, d = 1000 fp32, 300 x 2 beams, 110 us a step dealt, 75 cut
-    // evenly; 90 x 20, 166, 122; V = 10000, d = 700, 200 x 3, 100, 85; the other way V = 20000, d = 1000, 100 x 5, 68, 70.
-    const bool same = per * sp->S * 8 >= wgs * 7, even = !same && (sp->S > 4 * wgs || 8 * wgs / sp->S * sp->S < 7 * wgs);
+    // work; or dealt to them, unless some sentence would get less than nine tenths of its share and that costs its workgroups more
+    // tiles than an even cut costs (two, six with bf16 words), or less than two workgroups, so that shares could not follow the lists'
+    // lengths.  us a step dealt, cut evenly: V = 20000, d = 1000 fp32, 300 x 2 beams 110, 75; 90 x 20 166, 122; V = 10000, d = 700, 200 x 3,
+    // lists of 1140, 100, 85, of 450 54, 49 (bf16 54, 50 and 35, 36.5); V = 42000, d = 288, 37 x 43, 208, 178; V = 48000, d = 1072 bf16, 37 x 17, 67, 74;
+    // V = 20000, d = 1000, 100 x 5, 68, 70; V = 200000, d = 1024 bf16, 33 x 15, 143, 154.
+    const bool same = per * sp->S * 8 >= wgs * 7;
+    bool even = !same && (sp->S > 4 * wgs || wgs >= 512);
+    if (!same && !even) {
+        const double each = sp->S * expected_candidates(t, sp) / (8.0 * kTileN * wgs);   // tiles for a workgroup
+        const double most = 8.0 * wgs / (8 * wgs / sp->S * sp->S);                       // the largest share's part of that
+        even = most > 1.0 / 0.9 && each * (most - 1.0) > (sizeof(ET) == 2 ? 6.0 : 2.0);
+    }
     if (!same) per = 0;
     if (per > 0) wgs = per * sp->S;
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \

@@ -212,6 +212,8 @@ static void check_dealt_by_count() {
                     CHECK(std::all_of(seen.begin(), seen.end(), [](int k) { return k == 1; }), "tiles of sentence %u (S=%u G=%u kind=%d)", s, S, G, kind);
                 }
             }
+    for (uint32_t before : {0u, 1u, 2047u, 4094u})   // the largest list and number of workgroups
+        CHECK(dealt_run(1u << 20, 0, 0, 1, before, 4095).b0 == ((uint64_t)before << 20) / 4095, "share %u", before);
     CHECK(unequal > 40 && !dealt_by_count(100, 100, 1, 64) && !dealt_by_count(1 << 20, 1 << 20, 1, 64), "%d unequal ones", unequal);
 }
 // An XCD's tiles by turns, and in pieces.
