@@ -27,6 +27,7 @@
 #include "candidates.h"
 #include "fused.h"
 #include "logits.h"
+#include "report.h"
 #include "select.h"
 #include "workspace.h"
 
@@ -854,46 +855,6 @@ struct BuildBlock {  // what a build works in, kept for the next one
     ~BuildBlock() { release_block(dev, kBuildBlock, block, idle); }
 };
 
-// Pinned host words that a build's kernels report to (a copy of them from the device, and the wait for the copy, was
-// 10 us of a build).  One page for the life of the process serves the builds that run at the same time; what it does
-// not hold has memory of its own.
-struct Report {
-    static constexpr int kPlaces = 16;
-    uint32_t* words = nullptr;
-    int place = -1;
-    bool idle = false;   // no kernel that may write to it is under way
-    static std::mutex mu;
-    static uint32_t* page;
-    static uint32_t used;   // bit i: place i
-    hipError_t take() {
-        constexpr size_t n = kBuildBeginBlocks * sizeof(uint32_t);
-        {
-            std::lock_guard<std::mutex> lock(mu);
-            if (!page) {
-                const hipError_t e = hipHostMalloc((void**)&page, kPlaces * n, hipHostMallocPortable);
-                if (e != hipSuccess) { page = nullptr; return e; }
-            }
-            for (int i = 0; i < kPlaces && place < 0; ++i)
-                if (!(used >> i & 1u)) { used |= 1u << i; place = i; words = page + (size_t)i * kBuildBeginBlocks; }
-        }
-        if (place < 0) {
-            const hipError_t e = hipHostMalloc((void**)&words, n, hipHostMallocPortable);
-            if (e != hipSuccess) { words = nullptr; return e; }
-        }
-        std::memset(words, 0, n);
-        return hipSuccess;
-    }
-    ~Report() {
-        if (words && place < 0) (void)hipHostFree(words);   // (waits)
-        if (place < 0 || !idle) return;                     // (a build that failed half-way: the place is lost)
-        std::lock_guard<std::mutex> lock(mu);
-        used &= ~(1u << place);
-    }
-};
-std::mutex Report::mu;
-uint32_t* Report::page = nullptr;
-uint32_t Report::used = 0;
-
 template <typename ET>
 hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, int d, const int32_t* perms, int P, int K,
                             int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride) {
@@ -957,6 +918,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     int32_t *key_code = nullptr, *code_buf[2] = {}, *id_buf[2] = {};
     const size_t status_words = 3 * (size_t)W;
     Report report;
+    static_assert(Report::kWords >= kBuildBeginBlocks, "a word per workgroup of k_build_begin");
     HIP_TRY(report.take());
     BuildBlock work;   // (what only the build needs)
     work.dev = t->device;
@@ -1009,6 +971,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
                            attempt || (with_tables && !blind) ? nullptr : perms_in, (int)n_perms, t->d, t->perms_dev, report.words,
                            t->tickets_dev, (int)n_tickets);
     };
+    report.idle = false;
     begin(0, nullptr, blind);
     HIP_TRY(t->dtype == LSH_F32
         ? launch_row_codes<float>(st, (const float*)t->E, t->ld, V, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V)

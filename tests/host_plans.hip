@@ -12,6 +12,7 @@
 #include "../paper_1806_00588_amd/csrc/candidates.h"
 #include "../paper_1806_00588_amd/csrc/fused.h"
 #include "../paper_1806_00588_amd/csrc/logits.h"
+#include "../paper_1806_00588_amd/csrc/report.h"
 #include "../paper_1806_00588_amd/csrc/select.h"
 #include "../paper_1806_00588_amd/csrc/workspace.h"
 
@@ -278,7 +279,26 @@ static void check_nth_set_bit() {
     }
 }
 
+// The places that builds report to: one that no kernel was given comes back (a build that runs out of memory has one and
+// launches nothing), one that may still be written to does not.
+static void check_reports() {
+    static uint32_t page[Report::kPlaces * Report::kWords];
+    Report::page = page;   // (there is no GPU to pin it for)
+    for (int i = 0; i < 3 * Report::kPlaces; ++i) {
+        Report r;
+        CHECK(r.take() == hipSuccess && r.place == 0 && r.words == page, "place %d after %d builds", r.place, i);
+    }
+    {
+        Report r, q;
+        CHECK(r.take() == hipSuccess && q.take() == hipSuccess && r.place == 0 && q.place == 1, "places %d, %d", r.place, q.place);
+        r.idle = false;
+    }
+    Report r;
+    CHECK(r.take() == hipSuccess && r.place == 1, "place %d", r.place);
+}
+
 int main() {
+    check_reports();
     check_small_div_margin();
     check_nth_set_bit();
     // workspace: the largest accepted S, B, V and their neighbours, ragged V
