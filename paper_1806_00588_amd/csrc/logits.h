@@ -1143,7 +1143,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     char* ring = sm + Lds::kRed + q * (RING * NI * 1024);
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
-    LSH_TRACE_WG(0);
+    LSH_TRACE_WG(8);
     // Who takes what.  A workgroup has one sentence, and all or some of the sentence's workgroups take turns:
     //   per > 0: workgroup i of a sentence's `per` on this XCD has the tiles i, i + per, ... of those of the XCD (XcdTiles);
     //   per = 0, where that would leave many without work, and where lists are of very different lengths: as dealt_from and
@@ -1235,7 +1235,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         load_ids(0);
         wait_vmem<0>();
         lds_barrier();
-        LSH_TRACE_WG(1);
+        LSH_TRACE_WG(9);
         const int groups = (n + GT - 1) / GT, sets = (n + TS - 1) / TS, units = sets * PARTS;
         // unit u = part u % PARTS of the TS tiles of set u / PARTS; ptr: the addresses of its tiles' part 0
         const char* ptr[TS][KSN];
@@ -1312,7 +1312,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         }
         __builtin_amdgcn_s_waitcnt(0x0F70);                                   // vmcnt(0): the compiler must not wait for them in the loop
         __builtin_amdgcn_sched_barrier(0);
-        LSH_TRACE_WG(2);
+        LSH_TRACE_WG(10);
         float out[GT][MT];
         // thread (i, col) has row 16 m + i, column col of every tile: 16 lanes per row (waves without rows: nothing)
         float* lrow = logits + ((size_t)s * B + row0 + (tid >> 4)) * cpitch + col;
@@ -1477,7 +1477,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             if ((g * GT & (kStreamTiles - 1)) == GT && g * GT / kStreamTiles * kStreamTiles + kStreamTiles < n) load_ids(g * GT / kStreamTiles + 1);
             lds_barrier();
         }
-        LSH_TRACE_WG(15);
+        LSH_TRACE_WG(11);
         if (!EVEN) return;
         seg = seg_end;
         if (seg == wg_end) return;

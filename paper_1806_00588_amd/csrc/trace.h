@@ -9,27 +9,32 @@
 namespace lshbeam {
 constexpr int kTraceKernels = 4, kTraceSlots = 16;
 __device__ unsigned long long g_trace[kTraceKernels][kTraceSlots];
-constexpr int kTraceWgs = 512, kTraceWgSlots = 8;
-__device__ unsigned long long g_trace_wg[kTraceWgs][kTraceWgSlots];  // per workgroup (one kernel)
+// per workgroup: 0 .. 3 candidates.h, 4 .. 7 the fused kernels, 8 .. 11 k_logits_stream (which runs behind k_candidates)
+constexpr int kTraceWgs = 512, kTraceWgSlots = 12;
+__device__ unsigned long long g_trace_wg[kTraceWgs][kTraceWgSlots];
 }
 #define LSH_TRACE(kernel, slot)                                                   \
     do {                                                                          \
+        static_assert((kernel) < lshbeam::kTraceKernels && (slot) < lshbeam::kTraceSlots, "trace slot"); \
         if (blockIdx.x == 0 && threadIdx.x == 0)                                  \
             lshbeam::g_trace[kernel][slot] = wall_clock64();                      \
     } while (0)
 // thread 0 of whichever workgroup passes (for code only one workgroup of a launch runs)
 #define LSH_TRACE_ANY(kernel, slot)                                               \
     do {                                                                          \
+        static_assert((kernel) < lshbeam::kTraceKernels && (slot) < lshbeam::kTraceSlots, "trace slot"); \
         if (threadIdx.x == 0) lshbeam::g_trace[kernel][slot] = wall_clock64();    \
     } while (0)
 // the latest time any workgroup of the launch passes the point
 #define LSH_TRACE_LATEST(kernel, slot)                                            \
     do {                                                                          \
+        static_assert((kernel) < lshbeam::kTraceKernels && (slot) < lshbeam::kTraceSlots, "trace slot"); \
         if (threadIdx.x == 0) atomicMax(&lshbeam::g_trace[kernel][slot], wall_clock64()); \
     } while (0)
-// thread 0 of every workgroup (of the one kernel that uses this macro)
+// thread 0 of every workgroup
 #define LSH_TRACE_WG(slot)                                                        \
     do {                                                                          \
+        static_assert((slot) < lshbeam::kTraceWgSlots, "trace slot");             \
         if (threadIdx.x == 0 && blockIdx.x < lshbeam::kTraceWgs)                  \
             lshbeam::g_trace_wg[blockIdx.x][slot] = wall_clock64();               \
     } while (0)

@@ -16,3 +16,11 @@ def test_workspace_and_lds_plans_stay_in_bounds(tmp_path):
     run = subprocess.run([exe], capture_output=True, text=True)
     assert run.returncode == 0, run.stdout[-4000:] + run.stderr[-2000:]
     assert "host plans ok" in run.stdout
+
+
+def test_every_trace_point_has_its_place():
+    """A build with phase timestamps: every point of every kernel writes inside the arrays (a static_assert in the macros)."""
+    hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+    run = subprocess.run([hipcc, "--offload-arch=gfx950", "--cuda-device-only", "-fsyntax-only", "-std=c++17", "-w", "-DLSHBEAM_TRACE",
+                          os.path.join(ROOT, "paper_1806_00588_amd", "csrc", "lshbeam.hip")], capture_output=True, text=True)
+    assert run.returncode == 0, run.stderr[-3000:]
