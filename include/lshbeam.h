@@ -75,7 +75,8 @@ lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const l
  * next build on the device: at most 192 MiB together, until lsh_release_kept or until a build runs out of memory. */
 void lsh_free_tables(lsh_tables* t);
 
-/* Gives the kept memory of all devices back to the driver (waits for them). */
+/* Gives the kept memory of all devices back to the driver (waits for them, and up to 2 ms more until what the current device
+ * gave back shows in its free memory). */
 void lsh_release_kept(void);
 
 /* Per-call shape of a decode step; the paper's remaining hyper-parameters {B, T, t}. */

@@ -715,12 +715,14 @@ KeptBlock swap_kept(int dev, KeptKind kind, KeptBlock b) {
     if (b.bytes + others <= kKeptBytes) std::swap(b, g_kept[dev][kind]);
     return b;
 }
-size_t give_back_kept(int dev = -1) {   // bytes given back on that device
+// Returns what that device's free memory grows by at least: blocks are in pages of 2 MiB (smaller ones share them).
+size_t give_back_kept(int dev = -1) {
+    constexpr size_t kPage = (size_t)2 << 20;
     size_t bytes = 0;
     for (int d = 0; d < kMaxDevices; ++d)
         for (int k = 0; k < kKeptKinds; ++k) {
             const KeptBlock b = swap_kept(d, (KeptKind)k, KeptBlock{});
-            if (b.p && d == dev) bytes += b.bytes;
+            if (b.p && d == dev && b.bytes >= kPage) bytes += (b.bytes + kPage - 1) / kPage * kPage;
             if (b.p) (void)hipFree(b.p);
         }
     return bytes;
@@ -1249,15 +1251,15 @@ void lsh_free_tables(lsh_tables* t) {
 }
 
 void lsh_release_kept(void) {
-    // (hipMemGetInfo shows a released block up to some milliseconds late; who asks for the memory may look there first)
+    // (One release in eight shows in hipMemGetInfo up to 0.15 ms after hipFree has returned, and who asks for the memory may look
+    // there first.  At most 2 ms: somebody else may have taken it meanwhile.)
     size_t before = 0, now = 0, total = 0;
     int dev = -1;
     const bool look = hipGetDevice(&dev) == hipSuccess && hipMemGetInfo(&before, &total) == hipSuccess;
-    const size_t bytes = give_back_kept(dev) >> 21 << 21;
-    for (int i = 0; look && bytes && i < 100; ++i) {
-        if (hipMemGetInfo(&now, &total) != hipSuccess || now >= before + bytes) break;
-        std::this_thread::sleep_for(std::chrono::microseconds(200));
-    }
+    const size_t bytes = give_back_kept(look ? dev : -1);
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    while (bytes && hipMemGetInfo(&now, &total) == hipSuccess && now < before + bytes && std::chrono::steady_clock::now() < until)
+        std::this_thread::sleep_for(std::chrono::microseconds(20));
 }
 
 lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const lsh_build_params* p,

@@ -108,3 +108,24 @@ def test_a_handle_holds_its_tables_and_no_more():
     assert free - torch.cuda.mem_get_info()[0] == kept
     binding.release_kept()
     assert torch.cuda.mem_get_info()[0] == free
+
+
+def test_released_memory_shows_at_once():
+    """After release_kept the free memory holds all of what was kept, blocks of whole and of partial 2 MiB pages, each time."""
+    import time
+    import torch
+    import paper_1806_00588_amd as lsh
+    from paper_1806_00588_amd import binding
+    V, d, K, u, W = 30000, 20, 16, 4, 12
+    rng = np.random.default_rng(11)
+    E = to_dev(rng.standard_normal((500, d)).astype(np.float32)[rng.integers(0, 500, V)])
+    perms = to_dev(np.stack([rng.permutation(d)[:K] for _ in range(u * W)]).astype(np.int32))
+    lsh.build_tables(E, perms, K, W).close()
+    binding.release_kept()
+    time.sleep(0.05)
+    free = torch.cuda.mem_get_info()[0]
+    for _ in range(30):
+        lsh.build_tables(E, perms, K, W).close()
+        assert torch.cuda.mem_get_info()[0] < free
+        binding.release_kept()
+        assert torch.cuda.mem_get_info()[0] == free
