@@ -47,6 +47,34 @@ def test_build_matches_the_oracle(shape):
             assert np.array_equal(gc.tables.debug_bucket(w, int(k)), gc.index.bucket(w, int(k)))
 
 
+@pytest.mark.parametrize("V,d,K,u,W,direct", [(20000, 40, 4, 7, 3, True), (5000, 40, 4, 7, 3, False), (9000, 30, 2, 13, 4, True),
+                                              (70000, 200, 16, 4, 8, True), (30000, 24, 16, 4, 12, False)])
+def test_direct_tables_of_codes_of_several_passes(V, d, K, u, W, direct):
+    """Codes of 13 to 16 bits, sorted in two passes: direct tables where cuckoo tables for the keys would be no smaller (their
+    number known to be large, or counted), cuckoo tables otherwise; bucket for bucket, absent codes too, and the lists of a
+    hit threshold, which read where the vocabulary slices begin in a span."""
+    rng = np.random.default_rng(V)
+    E = rng.standard_normal((V, d)).astype(np.float32)
+    if V == 30000:                                  # (few codes come up)
+        E = E[rng.integers(0, 500, V)]
+    perms = np.stack([rng.permutation(d)[:K] for _ in range(u * W)]).astype(np.int32)
+    gc = GpuCase(E, perms, np.arange(40, dtype=np.int32), W)
+    bits = u * (K - 1).bit_length()
+    assert (gc.tables.debug_cuckoo_shape(0)[0] == 2 << bits) == direct
+    for w in (0, W - 1):
+        keys, offs, words = gc.tables.debug_csr(w)
+        okeys = np.sort(gc.index.bucket_keys(w))
+        assert np.array_equal(keys, okeys) and np.array_equal(words, np.concatenate([gc.index.bucket(w, int(k)) for k in okeys]))
+        for k in okeys[:: len(okeys) // 40]:
+            assert np.array_equal(gc.tables.debug_bucket(w, int(k)), gc.index.bucket(w, int(k)))
+        for k in np.setdiff1d(np.arange(0, 1 << bits, (1 << bits) // 50), okeys)[:10]:
+            assert gc.tables.debug_bucket(w, int(k)) is None
+    H = E[[7, V // 2, V - 1]] + 0.05 * rng.standard_normal((3, d)).astype(np.float32)
+    for t in (1, 2):
+        _, _, _, sp, ws = gc.step(H, np.zeros(3, np.float32), 1, 3, threshold=t)
+        assert np.array_equal(gc.tables.debug_candidates(ws, sp, 0), gc.oracle_sentence(H, np.zeros(3), 3, threshold=t).cand)
+
+
 @pytest.mark.parametrize("V", [1, 127, 129, 513, 2048 * 4 + 1, 40001])
 def test_slices_of_direct_tables(V):
     """Codes few enough for direct tables: the slots and the places where the vocabulary slices begin in every span
