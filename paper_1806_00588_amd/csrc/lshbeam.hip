@@ -687,6 +687,38 @@ hipError_t allow_logits_lds() {
     return e;
 }
 
+// What allow_whole_lds does, for every kernel of a step (about a hundred: asked for one by one they took 1 to 2 us of every build).
+hipError_t allow_step_lds(int dev) {
+    static std::atomic<uint64_t> done{0};  // one bit per device
+    const uint64_t bit = (dev >= 0 && dev < 64) ? (1ull << dev) : 0ull;
+    if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
+    hipError_t e = hipSuccess;
+#define LSH_ALLOW(...) do { if (e == hipSuccess) e = (__VA_ARGS__); } while (0)
+    LSH_ALLOW(allow_whole_lds<k_candidates>());
+    LSH_ALLOW(allow_whole_lds<k_hit_rows>());
+    LSH_ALLOW(allow_whole_lds<k_union_compact>());
+    LSH_ALLOW(allow_whole_lds<k_part_bitmaps>());
+#define LSH_ALLOW_FUSED(ET, AL)                                          \
+    LSH_ALLOW((allow_whole_lds<k_union_logits<ET, AL, false>>()));         \
+    LSH_ALLOW((allow_whole_lds<k_union_logits<ET, AL, true>>()));          \
+    LSH_ALLOW((allow_whole_lds<k_cand_logits<ET, AL, false>>()));          \
+    LSH_ALLOW((allow_whole_lds<k_cand_logits<ET, AL, true>>()))
+    LSH_ALLOW_FUSED(float, true);
+    LSH_ALLOW_FUSED(float, false);
+    LSH_ALLOW_FUSED(uint16_t, true);
+    LSH_ALLOW_FUSED(uint16_t, false);
+#undef LSH_ALLOW_FUSED
+    LSH_ALLOW(allow_logits_lds<float>());
+    LSH_ALLOW(allow_logits_lds<uint16_t>());
+    LSH_ALLOW((allow_whole_lds<k_logits_estage<3, false>>()));
+    LSH_ALLOW((allow_whole_lds<k_logits_estage<4, false>>()));
+    LSH_ALLOW((allow_whole_lds<k_logits_estage<3, true>>()));
+    LSH_ALLOW((allow_whole_lds<k_logits_estage<4, true>>()));
+#undef LSH_ALLOW
+    if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+    return e;
+}
+
 #define HIP_TRY(expr)                                   \
     do {                                                \
         hipError_t e_ = (expr);                         \
@@ -1308,26 +1340,7 @@ lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const l
     }
     t->wg_union_logits_lds = (int)(union_logits_lds_words(t->V) * sizeof(uint32_t));
     t->wg_fused_lds = (int)(fused_lds_words(t->V, t->P, t->K, candidates_min_stage(t->d)) * sizeof(uint32_t));
-    HIP_TRY(allow_whole_lds<k_candidates>());
-    HIP_TRY(allow_whole_lds<k_hit_rows>());
-    HIP_TRY(allow_whole_lds<k_union_compact>());
-    HIP_TRY(allow_whole_lds<k_part_bitmaps>());
-#define LSH_ALLOW_FUSED(ET, AL)                                          \
-    HIP_TRY((allow_whole_lds<k_union_logits<ET, AL, false>>()));         \
-    HIP_TRY((allow_whole_lds<k_union_logits<ET, AL, true>>()));          \
-    HIP_TRY((allow_whole_lds<k_cand_logits<ET, AL, false>>()));          \
-    HIP_TRY((allow_whole_lds<k_cand_logits<ET, AL, true>>()))
-    LSH_ALLOW_FUSED(float, true);
-    LSH_ALLOW_FUSED(float, false);
-    LSH_ALLOW_FUSED(uint16_t, true);
-    LSH_ALLOW_FUSED(uint16_t, false);
-#undef LSH_ALLOW_FUSED
-    HIP_TRY(allow_logits_lds<float>());
-    HIP_TRY(allow_logits_lds<uint16_t>());
-    HIP_TRY((allow_whole_lds<k_logits_estage<3, false>>()));
-    HIP_TRY((allow_whole_lds<k_logits_estage<4, false>>()));
-    HIP_TRY((allow_whole_lds<k_logits_estage<3, true>>()));
-    HIP_TRY((allow_whole_lds<k_logits_estage<4, true>>()));
+    HIP_TRY(allow_step_lds(t->device));
     guard.t = nullptr;
     *out = t;
     return LSH_OK;
