@@ -1755,12 +1755,12 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
                 if (r != q) rp[(r < q ? r : r - 1) * kWave + ln] = acc[r];
         }
 #ifdef LSHBEAM_TRACE
-        if ((nt - j0) / G < 5) LSH_TRACE(1, 3 + 2 * ((nt - j0) / G));
+        LSH_TRACE_UPTO(1, 3 + 2 * ((nt - j0) / G), 11);
 #endif
         if (more) store_row(buf ^ 1);   // the other half was last read before the previous barrier
         __syncthreads();
 #ifdef LSHBEAM_TRACE
-        if ((nt - j0) / G < 5) LSH_TRACE(1, 4 + 2 * ((nt - j0) / G));
+        LSH_TRACE_UPTO(1, 4 + 2 * ((nt - j0) / G), 12);
 #endif
         if (g < MT) {
             // x = sum over the four slices in slice order (this wave's own share in its place)

@@ -19,6 +19,13 @@ __device__ unsigned long long g_trace_wg[kTraceWgs][kTraceWgSlots];
         if (blockIdx.x == 0 && threadIdx.x == 0)                                  \
             lshbeam::g_trace[kernel][slot] = wall_clock64();                      \
     } while (0)
+// a slot known when it runs, `most` at most
+#define LSH_TRACE_UPTO(kernel, slot, most)                                        \
+    do {                                                                          \
+        static_assert((kernel) < lshbeam::kTraceKernels && (most) < lshbeam::kTraceSlots, "trace slot"); \
+        if (blockIdx.x == 0 && threadIdx.x == 0 && (slot) <= (most))              \
+            lshbeam::g_trace[kernel][slot] = wall_clock64();                      \
+    } while (0)
 // thread 0 of whichever workgroup passes (for code only one workgroup of a launch runs)
 #define LSH_TRACE_ANY(kernel, slot)                                               \
     do {                                                                          \
@@ -53,5 +60,6 @@ extern "C" __attribute__((used)) int lsh_trace_read_wg(unsigned long long* out_h
 #define LSH_TRACE_WG(slot) do { } while (0)
 #define LSH_TRACE_ANY(kernel, slot) do { } while (0)
 #define LSH_TRACE(kernel, slot) do { } while (0)
+#define LSH_TRACE_UPTO(kernel, slot, most) do { } while (0)
 #define LSH_TRACE_LATEST(kernel, slot) do { } while (0)
 #endif
