@@ -665,13 +665,15 @@ __host__ __device__ __forceinline__ uint32_t dealt_from(uint32_t w, uint32_t x, 
 __host__ __device__ __forceinline__ uint32_t dealt_sentence(uint32_t b, uint32_t x, uint32_t S, uint32_t G) {   // (equal weights)
     return ((b + 1u) * S - (x * S >> 3) - 1u) / G;
 }
-// Whether shares as large as the lists are worth working out: the longest list takes its equal share of the workgroups
-// twice as long as all of them together would take even ones, and three tiles more.  (One list of 32 sentences x 10 beams, V = 40000,
-// d = 1000 fp32, four times the others: 108 us a step with equal shares, 69 so; of 64: 176, 97; eight sentences, one list three
-// times their mean: 56, 49.  Below, equal shares of XcdTiles are the better ones: eight sentences, four of them three times as
-// long as the others, 60 us, 67 where all tiles are cut evenly.)
-__host__ __device__ __forceinline__ bool dealt_by_count(uint32_t most, uint32_t sum, uint32_t S, uint32_t G) {   // (in tiles)
-    return S <= 4u * G && G <= 192u && sum < (1u << 23) && (float)most * (float)S > 2.f * (float)sum + 24.f * (float)G;
+// Whether shares as large as the lists are worth working out: with equal ones the longest list takes twice as long as all of them
+// together would with even ones, and three tiles more; with short rows, 1.3 times.  us a step, equal shares and so: d = 1000 fp32,
+// V = 40000, one list of 32 x 10 beams four times the others 108, 69; of 64 x 10 176, 97; eight sentences, one list three times their
+// mean 56, 49; d = 300, lists from 4000 to 14000, 64 x 10 155, 148; 40 x 6 84, 73; d = 88, V = 170000, 64 x 10 379, 324; 15 x 26 461, 421.  Long
+// rows lose more by leaving the XCD that has them for other sentences (64 x 10, V = 200000, d = 1024 bf16, a longest list of 1.5 times the
+// mean: 475, 694; V = 40000, d = 1000 fp32: 226, 279; of 1.8 times: 461, 499; 239, 201).
+__host__ __device__ __forceinline__ bool dealt_by_count(uint32_t most, uint32_t sum, uint32_t S, uint32_t G, int row_bytes) {   // (in tiles)
+    return S <= 4u * G && G <= 192u && sum < (1u << 23) &&
+           (float)most * (float)S > (row_bytes <= 1600 ? 1.3f : 2.f) * (float)sum + 24.f * (float)G;
 }
 // A list's weight: its tiles, or as much as a workgroup takes (8 G (least) >= sum + S (least) >= W; W < 2^24 + 4 G).
 __host__ __device__ __forceinline__ uint32_t least_weight(uint32_t sum, uint32_t S, uint32_t G) { return (sum + 8u * G - S - 1u) / (8u * G - S); }
@@ -1036,7 +1038,7 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
 // are about equally long.
 struct StreamDeal { uint32_t s, C; TileRun run; };
 __device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ count, int V, uint32_t S, uint32_t G, uint32_t per,
-                                                  uint32_t shared, uint32_t x, uint32_t bx, uint32_t s0) {
+                                                  uint32_t shared, uint32_t x, uint32_t bx, uint32_t s0, int row_bytes) {
     const uint32_t ln = lane_id();
     auto tiles = [&](uint32_t at) { return ((uint32_t)count[min(at, S - 1u)] + kTileN - 1u) / kTileN; };   // (no branch around the load)
     StreamDeal dl;
@@ -1070,7 +1072,7 @@ __device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ co
     } else if (per == 0) {
         workgroups(s0, s0 + 1u, S);
     }
-    const bool by_count = dealt_by_count(most, sum, S, G);
+    const bool by_count = dealt_by_count(most, sum, S, G, row_bytes);
     if (by_count) {
         const uint32_t least = least_weight(sum, S, G);
         uint32_t W = 0, w0 = 0, w1 = 1;
@@ -1157,7 +1159,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     if constexpr (!EVEN) {
         const uint32_t s0 = per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs);
         if (q == 0) {
-            const StreamDeal dl = stream_deal(count, V, (uint32_t)S, (uint32_t)wgs, (uint32_t)per, (uint32_t)shared, xcd, bx, s0);
+            const StreamDeal dl = stream_deal(count, V, (uint32_t)S, (uint32_t)wgs, (uint32_t)per, (uint32_t)shared, xcd, bx, s0, d * (int)sizeof(ET));
             if (ln == 0) {
                 shares[0] = dl.s; shares[1] = dl.C; shares[2] = dl.run.n; shares[3] = dl.run.head;
                 shares[4] = dl.run.a0; shares[5] = dl.run.a1; shares[6] = dl.run.b0; shares[7] = dl.run.b1;

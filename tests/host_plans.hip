@@ -194,7 +194,8 @@ static void check_dealt_by_count() {
                     most = std::max(most, n[s]);
                     sum += n[s];
                 }
-                if (!dealt_by_count(most, sum, S, G)) continue;
+                if (!dealt_by_count(most, sum, S, G, 1000)) continue;
+                CHECK(!dealt_by_count(most, sum, S, G, 4000) || (uint64_t)most * S > 2ull * sum, "a line for long rows (S=%u G=%u kind=%d)", S, G, kind);
                 ++unequal;
                 const uint32_t least = least_weight(sum, S, G);
                 for (uint32_t s = 0; s < S; ++s) { weight[s] = std::max(n[s], least); front[s + 1] = front[s] + weight[s]; }
@@ -215,7 +216,7 @@ static void check_dealt_by_count() {
             }
     for (uint32_t before : {0u, 1u, 2047u, 4094u})   // the largest list and number of workgroups
         CHECK(dealt_run(1u << 20, 0, 0, 1, before, 4095).b0 == ((uint64_t)before << 20) / 4095, "share %u", before);
-    CHECK(unequal > 40 && !dealt_by_count(100, 100, 1, 64) && !dealt_by_count(1 << 20, 1 << 20, 1, 64), "%d unequal ones", unequal);
+    CHECK(unequal > 40 && !dealt_by_count(100, 100, 1, 64, 1000) && !dealt_by_count(1 << 20, 1 << 20, 1, 64, 4000), "%d unequal ones", unequal);
 }
 // An XCD's tiles by turns, and in pieces.
 static void check_xcd_runs() {
