@@ -1034,72 +1034,62 @@ template <int N, int I = 0, typename F> __device__ __forceinline__ void static_f
     }
 }
 
-// The sentence of workgroup bx of XCD x, its candidates and its tiles: one wave's work.  s0: its sentence where the lists
-// are about equally long.
+__device__ __forceinline__ TileRun uniform(const TileRun& r) {
+    return {wave_read_lane(r.n, 0), wave_read_lane(r.head, 0), wave_read_lane(r.a0, 0), wave_read_lane(r.a1, 0), wave_read_lane(r.b0, 0), wave_read_lane(r.b1, 0)};
+}
+// The sentence of workgroup bx of XCD x, its candidates and its tiles.
 struct StreamDeal { uint32_t s, C; TileRun run; };
-__device__ __forceinline__ StreamDeal stream_deal(const int32_t* __restrict__ count, int V, uint32_t S, uint32_t G, uint32_t per,
-                                                  uint32_t shared, uint32_t x, uint32_t bx, uint32_t s0, int row_bytes) {
+// w0: weights of the sentences in front of s, w1: with its own, W: of all.
+__device__ __forceinline__ StreamDeal deal_by_weight(uint32_t s, uint32_t C, uint32_t w0, uint32_t w1, uint32_t W, uint32_t G,
+                                                     uint32_t shared, uint32_t x, uint32_t bx) {
+    const uint32_t ln = lane_id();                                            // (lane i: XCD i)
+    const uint32_t b0 = dealt_from(w0, ln & 7u, W, G), n = dealt_from(w1, ln & 7u, W, G) - b0, incl = wave_incl_scan(ln < 8u ? n : 0u);
+    const uint32_t mine = wave_read_lane(n, (int)x), before = wave_read_lane(incl, (int)x) - mine;
+    return {s, C, dealt_run((C + kTileN - 1u) / kTileN, shared, bx - wave_read_lane(b0, (int)x), mine, before, wave_read_lane(incl, 7))};
+}
+// The same number for every sentence (per > 0), or dealt as equally as they come.
+__device__ __forceinline__ StreamDeal deal_equally(const int32_t* __restrict__ count, int V, uint32_t S, uint32_t G, uint32_t per,
+                                                   uint32_t shared, uint32_t x, uint32_t bx, uint32_t s) {
+    const uint32_t C = (uint32_t)__builtin_amdgcn_readfirstlane(count ? count[s] : V);
+    if (per == 0) return deal_by_weight(s, C, s, s + 1u, S, G, shared, x, bx);
+    const XcdTiles xt = xcd_tiles((C + kTileN - 1u) / kTileN, shared, s, x);
+    const uint32_t first = bx - s * per;
+    return {s, C, xcd_run(xt, x, first, per, xt.n > first ? (xt.n - first + per - 1u) / per : 0u)};
+}
+__device__ __forceinline__ uint32_t tiles_in(const int32_t* __restrict__ count, uint32_t s, uint32_t S) {   // (no branch around the load)
+    return ((uint32_t)count[min(s, S - 1u)] + kTileN - 1u) / kTileN;
+}
+// Whether the lists' lengths ask for shares by weight (dealt_by_count); the tiles of all lists.
+__device__ __forceinline__ bool lists_differ(const int32_t* __restrict__ count, uint32_t S, uint32_t G, int row_bytes, uint32_t* all) {
+    constexpr uint32_t AT_ONCE = 6;
     const uint32_t ln = lane_id();
-    auto tiles = [&](uint32_t at) { return ((uint32_t)count[min(at, S - 1u)] + kTileN - 1u) / kTileN; };   // (no branch around the load)
-    StreamDeal dl;
-    dl.s = s0;
-    uint32_t most = 0, sum = 0, first = 0, mine = 0, before = 0, all = 1;
-    // (lane i: XCD i)
-    auto workgroups = [&](uint32_t w0, uint32_t w1, uint32_t W) {
-        const uint32_t b0 = dealt_from(w0, ln & 7u, W, G), n = dealt_from(w1, ln & 7u, W, G) - b0, incl = wave_incl_scan(ln < 8u ? n : 0u);
-        mine = wave_read_lane(n, (int)x);
-        before = wave_read_lane(incl, (int)x) - mine;
-        all = wave_read_lane(incl, 7);
-        first = bx - wave_read_lane(b0, (int)x);
-    };
-    const int own = count ? count[s0] : V;
-    if (count) {
-        constexpr uint32_t AT_ONCE = 6;
+    uint32_t most = 0, sum = 0;
+    for (uint32_t c = 0; c < S; c += AT_ONCE * kWave) {
         uint32_t n[AT_ONCE];
 #pragma unroll
-        for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles(j * kWave + ln);
-        if (per == 0) workgroups(s0, s0 + 1u, S);   // (while the counts are on their way)
-        for (uint32_t c = 0;;) {
+        for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles_in(count, c + j * kWave + ln, S);
 #pragma unroll
-            for (uint32_t j = 0; j < AT_ONCE; ++j) { most = max(most, n[j]); sum += c + j * kWave + ln < S ? n[j] : 0u; }
-            c += AT_ONCE * kWave;
-            if (c >= S) break;
-#pragma unroll
-            for (uint32_t j = 0; j < AT_ONCE; ++j) n[j] = tiles(c + j * kWave + ln);
-        }
-        most = (uint32_t)wave_max_f32((float)most);
-        sum = wave_sum(sum);
-    } else if (per == 0) {
-        workgroups(s0, s0 + 1u, S);
+        for (uint32_t j = 0; j < AT_ONCE; ++j) { most = max(most, n[j]); sum += c + j * kWave + ln < S ? n[j] : 0u; }
     }
-    const bool by_count = dealt_by_count(most, sum, S, G, row_bytes);
-    if (by_count) {
-        const uint32_t least = least_weight(sum, S, G);
-        uint32_t W = 0, w0 = 0, w1 = 1;
-        for (uint32_t c = 0; c < S; c += kWave) W += wave_sum(c + ln < S ? max(tiles(c + ln), least) : 0u);
-        uint32_t front = 0;
-        for (uint32_t c = 0; c < S; c += kWave) {
-            const uint32_t w = c + ln < S ? max(tiles(c + ln), least) : 0u, incl = front + wave_incl_scan(w);
-            const uint64_t begun = __ballot(c + ln < S && dealt_from(incl - w, x, W, G) <= bx);   // (the last of them has bx)
-            if (begun == 0ull) break;
-            const int i = kWave - 1 - __clzll(begun);
-            dl.s = c + i;
-            w1 = wave_read_lane(incl, i);
-            w0 = w1 - wave_read_lane(w, i);
-            front = wave_read_lane(incl, kWave - 1);
-        }
-        workgroups(w0, w1, W);
+    *all = wave_sum(sum);
+    return dealt_by_count((uint32_t)wave_max_f32((float)most), *all, S, G, row_bytes);
+}
+__device__ __forceinline__ StreamDeal deal_by_count(const int32_t* __restrict__ count, uint32_t S, uint32_t G, uint32_t sum,
+                                                    uint32_t shared, uint32_t x, uint32_t bx) {
+    const uint32_t ln = lane_id(), least = least_weight(sum, S, G);
+    uint32_t W = 0, w0 = 0, w1 = 1, s = 0, front = 0;
+    for (uint32_t c = 0; c < S; c += kWave) W += wave_sum(c + ln < S ? max(tiles_in(count, c + ln, S), least) : 0u);
+    for (uint32_t c = 0; c < S; c += kWave) {
+        const uint32_t w = c + ln < S ? max(tiles_in(count, c + ln, S), least) : 0u, incl = front + wave_incl_scan(w);
+        const uint64_t begun = __ballot(c + ln < S && dealt_from(incl - w, x, W, G) <= bx);   // (the last of them has bx)
+        if (begun == 0ull) break;
+        const int i = kWave - 1 - __clzll(begun);
+        s = c + i;
+        w1 = wave_read_lane(incl, i);
+        w0 = w1 - wave_read_lane(w, i);
+        front = wave_read_lane(incl, kWave - 1);
     }
-    dl.C = (uint32_t)__builtin_amdgcn_readfirstlane(by_count ? count[dl.s] : own);
-    const uint32_t nt = (dl.C + kTileN - 1u) / kTileN;
-    if (per > 0 && !by_count) {
-        const XcdTiles xt = xcd_tiles(nt, shared, dl.s, x);
-        first = bx - dl.s * per;
-        dl.run = xcd_run(xt, x, first, per, xt.n > first ? (xt.n - first + per - 1u) / per : 0u);
-    } else {
-        dl.run = dealt_run(nt, shared, first, mine, before, all);
-    }
-    return dl;
+    return deal_by_weight(s, (uint32_t)__builtin_amdgcn_readfirstlane(count[s]), w0, w1, W, G, shared, x, bx);
 }
 
 template <typename ET, int MT, int KSN, int PARTS, bool EVEN, bool TRIM>
@@ -1157,23 +1147,13 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     uint32_t seg = 0, seg_end = 0, wg_end = 0;
     auto count_of = [&](int at) { const int n = count ? count[min(at, S - 1)] : V; return at < S ? n : 0; };
     if constexpr (!EVEN) {
-        const uint32_t s0 = per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs);
-        if (q == 0) {
-            const StreamDeal dl = stream_deal(count, V, (uint32_t)S, (uint32_t)wgs, (uint32_t)per, (uint32_t)shared, xcd, bx, s0, d * (int)sizeof(ET));
-            if (ln == 0) {
-                shares[0] = dl.s; shares[1] = dl.C; shares[2] = dl.run.n; shares[3] = dl.run.head;
-                shares[4] = dl.run.a0; shares[5] = dl.run.a1; shares[6] = dl.run.b0; shares[7] = dl.run.b1;
-            }
-        } else {
-            // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the counts are on their way
-            const char* hb = reinterpret_cast<const char*>(H + ((size_t)s0 * B + row0) * d);
+        const uint32_t s0 = __builtin_amdgcn_readfirstlane(per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs));
+        // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
+        const char* hb = reinterpret_cast<const char*>(H + ((size_t)s0 * B + row0) * d);
+        if (q > 0)
             for (uint32_t at = (tid - kWave) * 128u; at < (uint32_t)(Bg * d) * 4u; at += 192u * 128u) load_to_lds4(hb + at, ring);
-        }
-        lds_barrier();
-        const uint4 x = reinterpret_cast<const uint4*>(shares)[0], y = reinterpret_cast<const uint4*>(shares)[1];
-        s = wave_read_lane(x.x, 0); C = wave_read_lane(x.y, 0);
-        run = {wave_read_lane(x.z, 0), wave_read_lane(x.w, 0), wave_read_lane(y.x, 0), wave_read_lane(y.y, 0), wave_read_lane(y.z, 0), wave_read_lane(y.w, 0)};
-        if (run.n == 0) { wait_vmem<0>(); return; }
+        const StreamDeal dl = deal_equally(count, V, (uint32_t)S, (uint32_t)wgs, (uint32_t)per, (uint32_t)shared, xcd, bx, s0);
+        s = (int)dl.s; C = (int)dl.C; run = uniform(dl.run);
     } else {   // (every wave for itself, to the same result)
         static_assert(kMaxSentencesLogits <= kWave * kWave, "a lane per 64 sentences");
         constexpr int AHEAD = 8;
@@ -1222,21 +1202,52 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
             seg_end = min(wg_end, wave_read_lane(incl, i));
             run = {seg_end - seg, 0u, 0u, 0u, seg - wave_read_lane(pref, i), 1u};
         }
-        const int n = (int)run.n;
+        int n = (int)run.n;
         auto tile_of = [&](int t) __attribute__((always_inline)) { return (int)run.tile((uint32_t)t); };
         // candidates of block b (kStreamTiles tiles): two loads per wave
+        auto load_ids1 = [&](int b, int e) __attribute__((always_inline)) {       // 64 of them, from the e-th on
+            const int c = min(tile_of(min(b * kStreamTiles + (e + ln) / kTileN, n - 1)) * kTileN + col, C - 1);   // clamped columns are never stored
+            int32_t* to = ids + (b & 1) * kStreamTiles * kTileN + e;
+            if (cand) load_to_lds4(cand + (size_t)s * V + c, to); else to[ln] = c;
+        };
         auto load_ids = [&](int b) __attribute__((always_inline)) {
 #pragma unroll
-            for (int j = 0; j < kStreamTiles * kTileN / 256; ++j) {
-                const int e = q * (kStreamTiles * kTileN / 4) + j * kWave;
-                const int c = min(tile_of(min(b * kStreamTiles + (e + ln) / kTileN, n - 1)) * kTileN + col, C - 1);   // clamped columns are never stored
-                int32_t* to = ids + (b & 1) * kStreamTiles * kTileN + e;
-                if (cand) load_to_lds4(cand + (size_t)s * V + c, to); else to[ln] = c;
-            }
+            for (int j = 0; j < kStreamTiles * kTileN / 256; ++j) load_ids1(b, q * (kStreamTiles * kTileN / 4) + j * kWave);
         };
-        load_ids(0);
+        if (EVEN || (q > 0 && n > 0)) load_ids(0);
+        if constexpr (!EVEN) {
+            // (The first wave reads all counts while the others' candidates come, its own share of those among them: 0.6 us less than
+            // before them.)
+            if (q == 1 || q == 2) { if (n > 0) load_ids1(0, (q - 1) * kWave); }
+            if (q == 0) {
+                uint32_t all = 0;
+                const bool differ = count && lists_differ(count, (uint32_t)S, (uint32_t)wgs, d * (int)sizeof(ET), &all);
+                if (differ) {
+                    const StreamDeal dl = deal_by_count(count, (uint32_t)S, (uint32_t)wgs, all, (uint32_t)shared, xcd, bx);
+                    if (ln == 0) {
+                        shares[0] = dl.s; shares[1] = dl.C; shares[2] = dl.run.n; shares[3] = dl.run.head;
+                        shares[4] = dl.run.a0; shares[5] = dl.run.a1; shares[6] = dl.run.b0; shares[7] = dl.run.b1;
+                    }
+                }
+                if (ln == 0) shares[8] = differ;
+            }
+        }
         wait_vmem<0>();
         lds_barrier();
+        if constexpr (!EVEN) {
+            if (wave_read_lane(shares[8], 0)) {
+                const uint4 x = reinterpret_cast<const uint4*>(shares)[0], y = reinterpret_cast<const uint4*>(shares)[1];
+                s = wave_read_lane(x.x, 0); C = wave_read_lane(x.y, 0);
+                run = uniform(TileRun{x.z, x.w, y.x, y.y, y.z, y.w});
+                n = (int)run.n;
+                if (n > 0) {
+                    load_ids(0);
+                    wait_vmem<0>();
+                    lds_barrier();
+                }
+            }
+            if (n == 0) return;
+        }
         LSH_TRACE_WG(9);
         const int groups = (n + GT - 1) / GT, sets = (n + TS - 1) / TS, units = sets * PARTS;
         // unit u = part u % PARTS of the TS tiles of set u / PARTS; ptr: the addresses of its tiles' part 0
