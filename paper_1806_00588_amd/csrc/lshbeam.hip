@@ -440,11 +440,11 @@ template <typename ET> StreamPlan stream_plan(int d) {
 // group with its own pass over the candidate rows (from the XCD's L2), or of at most 32 where the rows are so short that
 // this pass is what counts.  fp32, d = 1000, V = 40000: 1 x 32 beams 40 us with 32 rows per workgroup, 33 with 16; 9 x 17: 50, 48;
 // d = 256, V = 10000: 9 x 32 29, 28; 64 x 20 43, 48.  Rows of two parts: groups of 32 where these hold no more empty rows than groups
-// of 16 would, up to seven steps always (16 and 32 rows; 20 x 20, V = 40000: d = 264 52.0, 45.8; d = 440 54.1, 47.8; 16 x 28,
-// V = 10000: 38.6, 36.6; 39.9, 38.2; full vocabulary of 2000, 128 rows, d = 264: 14.7, 14.0; d = 448: 15.9, 16.1), with eight from
-// nine expected tiles for each of the 256 CUs on (d = 512: 32 x 31, V = 40000, 86, 80; 20 x 20 53.9, 52.2; 10 x 90, V = 20000, 113, 105;
-// 8 x 32, V = 40000, 44.5, 47; 16 x 28, V = 10000, 40, 40.8); three groups of 16 stay (24 x 40, V = 60000, 189, 200).  (The longest
-// bf16 rows, four parts, need 16 registers more than there are; the spills cost less than the other kernel does: 32 sentences x 10
+// of 16 would, up to six steps always, with seven from four expected tiles for each of the 256 CUs on, with eight from nine (us with
+// 16 and 32 rows; d = 264: 20 x 20, V = 40000, 52.0, 45.8, 16 x 28, V = 10000, 38.6, 36.6, full vocabulary of 2000, 128 rows, 14.7, 14.0; d = 440:
+// 54.1, 47.8, 39.9, 38.2, 15.9, 16.1; d = 448, 10 x 18, V = 14000, 2.8 tiles, 30.5, 31.7; d = 512: 32 x 31, V = 40000, 86, 80, 20 x 20 53.9, 52.2, 10 x 90,
+// V = 20000, 113, 105, 8 x 32, V = 40000, 44.5, 47); three groups of 16 stay (24 x 40, V = 60000, 189, 200).  (The longest bf16
+// rows, four parts, need 16 registers more than there are; the spills cost less than the other kernel does: 32 sentences x 10
 // beams, V = 40000, 34 us against 67 of k_logits_hlds for d = 1664, 35 against 76 for 2048.)
 template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_params* sp) {
     if (!has_chunks(t) || t->ld * (int64_t)sizeof(ET) >= (int64_t)1 << 31) return 0;
@@ -452,7 +452,7 @@ template <typename ET> int stream_rows(const lsh_tables* t, const lsh_step_param
     if (p.parts > (sizeof(ET) == 2 ? 4 : 8)) return 0;
     const bool whole = (sp->B + kTileM - 1) / kTileM % 2 == 0;   // groups of 32 have no more padding than groups of 16
     const bool two = sp->B > kTileM && (p.ksn < 4 || (sizeof(ET) == 4 && p.parts == 2 && whole &&
-                                                      (t->d <= 448 || sp->S * expected_candidates(t, sp) >= 2304 * kTileN)));
+                                                      (t->d <= 384 || sp->S * expected_candidates(t, sp) >= (t->d <= 448 ? 1024 : 2304) * kTileN)));
     const int most = two ? 2 * kTileM : kTileM, groups = (sp->B + most - 1) / most;
     return (sp->B + groups - 1) / groups;
 }

@@ -61,7 +61,7 @@ def test_last_parts_of_every_length(d, bf16):
 
 @pytest.mark.parametrize("V,T", [(1500, 40), (20000, 700)], ids=["few", "many"])
 @pytest.mark.parametrize("B", [17, 32, 33, 50])
-@pytest.mark.parametrize("d", [300, 450, 512])
+@pytest.mark.parametrize("d", [300, 430, 512])
 def test_row_groups_of_two_parts(d, B, V, T):
     """Two, three and four times 16 rows, on either side of the tiles from which groups of 32 are taken."""
     rng, gc = _case(V, d, T, False)
