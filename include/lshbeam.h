@@ -64,9 +64,10 @@ typedef struct {
  *              (Eq. 5: Permute_p(x)[k] = x[perms[p][k]]).  Copied; validated to lie in [0, d).
  * Computes the band code of every row on the device (ties in the argmax go to the lowest k),
  * groups word ids by band code into one flat array per band (ids ascending inside a span; a device
- * radix sort of every band) and stores (start, length) of every span in a two-choice
- * cuckoo table per band (parallel insertion on the device; the host takes over if a band cannot be
- * placed).
+ * radix sort of every band) and stores (start, length) of every span in a table per band: a two-choice
+ * cuckoo table (parallel insertion on the device; the host takes over if a band cannot be placed) or,
+ * where a slot for every code there can be needs no more room or little, a direct one: a cuckoo table
+ * whose two hash functions are the code itself.
  * Synchronous.  On success *out receives the handle. */
 lsh_status lsh_build_tables(const void* E_dev, const int32_t* perms_dev, const lsh_build_params* p,
                             void* hip_stream, lsh_tables** out);
@@ -244,7 +245,7 @@ lsh_status lsh_debug_logprobs(const lsh_tables* t, const void* workspace_dev,
  *   "stage_rows"     n: the hashing stage in LDS is sized for at most n rows (0: the minimum)
  * Two more are read from the environment by lsh_build_tables only: LSHBEAM_HOST_BUILD=1 (bucket and
  * cuckoo tables built on the host) and LSHBEAM_CUCKOO_CHAIN=n (eviction chains of the device
- * build cut at n; for tests of its retry path). */
+ * build cut at n, and cuckoo tables where direct ones would be made; for tests of its retry path). */
 #define LSH_OPTION_AUTO (-1)
 lsh_status lsh_set_option(lsh_tables* t, const char* name, int32_t value);
 lsh_status lsh_get_option(const lsh_tables* t, const char* name, int32_t* value_out);

@@ -989,7 +989,7 @@ k_logits_hlds(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
 // LDS.  What bounds it then is the instructions a wave issues (with every row in L2 it took as long), and how
 // much of what several sentences want one L2 serves.  32 sentences x 10 beams, V = 40000, d = 1000 fp32 (261 MB of
 // rows): 38 -> 33 us since the kernel works addresses out once per tile, has its loads between the matrix
-// instructions and four units of them in flight; 64 x 10, V = 200000, d = 1024 bf16 (1.38 GB): 183 -> 139 us, 9.9 TB/s
+// instructions and four units of them in flight; 64 x 10, V = 200000, d = 1024 bf16 (1.38 GB): 183 -> 136 us, 10 TB/s
 // of rows; 8 x 5, d = 1024 bf16: 11.4 -> 10.4 us.
 //
 // The four waves of a workgroup share a tile, each with a quarter of k, and keep the A operands of all MT * 16
@@ -1140,7 +1140,7 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     //   per > 0: workgroup i of a sentence's `per` on this XCD has the tiles i, i + per, ... of those of the XCD (XcdTiles);
     //   per = 0, where that would leave many without work, and where lists are of very different lengths: as dealt_from and
     //   dealt_run say.  (40 sentences x 6, d = 1096 fp32: 48 us cut evenly, 40 dealt; 33 x 15: 44, 39.5.)
-    //   EVEN (so many sentences that this would give some of them half as many workgroups as others): the tiles of all
+    //   EVEN (more sentences than such shares suit: launch_logits_stream): the tiles of all
     //   sentences in a row, cut evenly.
     int s = 0, C = 0;
     TileRun run{};
