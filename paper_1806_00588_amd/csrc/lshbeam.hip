@@ -1234,7 +1234,13 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
            sp->B, beam_scores_dev, w.lse, out_beam_dev, out_word_dev, out_score_dev,                   \
            fused ? std::max(0, t->option(kOptFusedTile, 0)) : 0, rec_groups)
         // (the fused kernels leave rich records, k_logits_estage one record for a group of tiles)
-        if (fused) LSH_SELECT(true, false); else if (wide) LSH_SELECT(false, false, true); else if (rec_groups > 0) LSH_SELECT(false, true); else LSH_SELECT(false, false);
+        if (wide) LSH_SELECT(false, false, true);
+        else if (rec_groups > 0) LSH_SELECT(false, true);
+        else if (fused && sp->B <= kSelWaves) LSH_SELECT(true, false, false, 16);
+        else if (fused) LSH_SELECT(true, false, false, 64);   // (of at most 32, by the rule; any number, by option)
+        else if (sp->B <= kSelWaves) LSH_SELECT(false, false, false, 16);
+        else if (sp->B <= 4 * kSelWaves) LSH_SELECT(false, false, false, 64);
+        else LSH_SELECT(false, false, false, 0);
 #undef LSH_SELECT
     }
     HIP_TRY(hipGetLastError());

@@ -401,6 +401,41 @@ __device__ __forceinline__ uint32_t select_front_grouped(SelShared& sh, int s, c
     return tau;
 }
 
+// Ranks the mr <= 64 keys of sh.list by ballot: in every wave lane j holds entry j, wave w ranks entries 4w .. 4w + 3; the
+// B best are written out.  verdict: sh.misc[6] is set if one of them is marked (a second largest) in sh.open_list.
+__device__ __forceinline__ void rank_by_ballots(SelShared& sh, int mr, bool verdict, int B, size_t o0, int32_t* out_beam,
+                                                int32_t* out_word, float* out_score) {
+    const int ln = lane_id(), wv = wave_id();
+    const uint64_t mine = (ln < mr) ? sh.list[ln] : 0ull;
+    const uint32_t second = (verdict && ln < mr && sh.open_list[ln] != 0u) ? 1u : 0u;
+    const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
+    uint64_t key = 0;
+    uint32_t rank = 0xFFFFFFFFu, sec = 0;
+#pragma unroll
+    for (int q = 0; q < kWave / kSelWaves; ++q) {
+        const int e = wv * (kWave / kSelWaves) + q;   // (wave-uniform)
+        if (e >= mr) break;
+        const uint64_t ke = ((uint64_t)wave_read_lane(hi, e) << 32) | wave_read_lane(lo, e);
+        const uint32_t r = (uint32_t)__popcll(__ballot(mine > ke));
+        const uint32_t se = wave_read_lane(second, e);
+        if (ln == q) { key = ke; rank = r; sec = se; }
+    }
+    if (rank < (uint32_t)B) {   // (lanes 0..3 at most)
+        if (sec) sh.misc[6] = 1u;
+        const size_t o = o0 + rank;
+        const float score = key_value(key);
+        const uint32_t idx = key_index(key);
+        const bool none = score == -INFINITY || score != score;
+        out_beam[o] = none ? -1 : (int)(idx >> 24);
+        out_word[o] = none ? -1 : (int)(idx & 0xFFFFFFu);
+        out_score[o] = none ? -INFINITY : score;
+    }
+    if (wv == 0)
+        for (int e = ln + min(mr, B); e < B; e += kWave) {
+            out_beam[o0 + e] = -1; out_word[o0 + e] = -1; out_score[o0 + e] = -INFINITY;
+        }
+}
+
 // The whole selection for the shape the fused kernels usually serve -- rich records, at most 16
 // beams (a wave per hidden row), at most 512 tiles (eight records per lane) -- written out on its
 // own, because this kernel is bound by instruction issue as much as by its trips to memory: the
@@ -535,37 +570,8 @@ __device__ __forceinline__ bool select_rich_small_body(SelShared& sh, int s, flo
     __syncthreads();
     const size_t o0 = (size_t)s * B;
     LSH_TRACE_ANY(2, 3);
-    // Ranks by ballot: in every wave lane j holds entry j, wave w ranks entries 4w .. 4w + 3; the B best are
-    // written out.  False (uniform): one of them is a second largest (`verdict`).
     auto rank_and_write = [&](int mr, bool verdict) {
-        const uint64_t mine = (ln < mr) ? sh.list[ln] : 0ull;
-        const uint32_t second = (verdict && ln < mr && sh.open_list[ln] != 0u) ? 1u : 0u;
-        const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
-        uint64_t key = 0;
-        uint32_t rank = 0xFFFFFFFFu, sec = 0;
-#pragma unroll
-        for (int q = 0; q < kWave / kSelWaves; ++q) {
-            const int e = wv * (kWave / kSelWaves) + q;   // (wave-uniform)
-            if (e >= mr) break;
-            const uint64_t ke = ((uint64_t)wave_read_lane(hi, e) << 32) | wave_read_lane(lo, e);
-            const uint32_t r = (uint32_t)__popcll(__ballot(mine > ke));
-            const uint32_t se = wave_read_lane(second, e);
-            if (ln == q) { key = ke; rank = r; sec = se; }
-        }
-        if (rank < (uint32_t)B) {   // (lanes 0..3 at most)
-            if (sec) sh.misc[6] = 1u;
-            const size_t o = o0 + rank;
-            const float score = key_value(key);
-            const uint32_t idx = key_index(key);
-            const bool none = score == -INFINITY || score != score;
-            out_beam[o] = none ? -1 : (int)(idx >> 24);
-            out_word[o] = none ? -1 : (int)(idx & 0xFFFFFFu);
-            out_score[o] = none ? -INFINITY : score;
-        }
-        if (wv == 0)
-            for (int e = ln + min(mr, B); e < B; e += kWave) {
-                out_beam[o0 + e] = -1; out_word[o0 + e] = -1; out_score[o0 + e] = -INFINITY;
-            }
+        rank_by_ballots(sh, mr, verdict, B, o0, out_beam, out_word, out_score);
         if (!verdict) return true;
         LSH_TRACE_ANY(2, 4);
         __syncthreads();
@@ -644,14 +650,171 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
                                                   out_score, open);
 }
 
-template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false, bool WIDE = false>
+// The selection's first half with every row's records in registers, written out on its own for the same reason: the rows'
+// log-sum-exps, tau, the tiles that reach it and, their words' ids asked for beside the logits, the keys that do.  The list is in
+// sh.list, its length in sh.misc[4]; false (uniform): more tiles reach tau than the workgroup opens at once, and nothing is final.
+// LPR lanes per hidden row: 64, a wave, up to 16 beams (plain records; the log-sum-exps as in the general path, operation for
+// operation); 16 up to 64 beams, all rows at once (a wave for several rows, one after the other, spends most of its
+// instructions on reductions over 64 lanes).  Against the general path, which asks for a winner's id once it is known and ranks by
+// LDS atomics: k_select 5.7 -> 4.4 us (8 x 5 beams, 140 tiles), 6.7 -> 5.1 (32 x 10), 10.0 -> 7.5 (64 x 10, 650 tiles); a step of 12 x 26
+// beams, d = 1096 bf16, V = 11600, 33.1 -> 29.6, of 7 x 55, d = 320, V = 7900, 38.5 -> 33.8.
+constexpr int kListOpen = kSelThreads / 16 * 4;   // tiles opened: four for every 16 lanes
+template <int LPR, bool SAME_KERNEL, int Q, typename REC>
+__device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], int ntiles, int B,
+                                                 float* lse_out, const OpenSrc& open) {
+    static_assert(LPR == kWave || LPR == 16, "");
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
+    const int row = tid / LPR, c = tid & (LPR - 1);
+    const bool has_row = row < B;                      // (LPR = 64: uniform)
+    if (tid == 0) { sh.misc[4] = 0; sh.misc[5] = 0; sh.misc[6] = 0; }
+    uint32_t best = 0, tau = 0;
+    float lse = 0.f;
+    // (a NaN, of a row that holds one, reaches nothing: such a row has no results, the others have theirs)
+    auto reaches = [&](float x, uint32_t least) {
+        const float sc = bsi + (x - lse);
+        return sc > -INFINITY && f32_sortable(sc + 0.0f) >= least;
+    };
+    if (has_row) {
+        float m = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int q0 = 0; q0 < Q; q0 += kSelBatch) {   // (the general path's batches)
+            float bm = -INFINITY;
+#pragma unroll
+            for (int q = q0; q < Q && q < q0 + kSelBatch; ++q) {
+                if (c + q * LPR >= ntiles) rec[q] = empty_record<REC>();
+                bm = fmaxf(bm, rec[q].x);
+            }
+            if (bm > m) { sum *= __expf(m - bm); m = bm; }
+            if (m != -INFINITY) {
+#pragma unroll
+                for (int q = q0; q < Q && q < q0 + kSelBatch; ++q) sum += rec[q].y * __expf(rec[q].x - m);   // padding: 0 * 0
+            }
+        }
+        float M, part;
+        if constexpr (LPR == kWave) M = wave_max_f32(m); else M = row16_max(m);
+        const float mine = (m == -INFINITY) ? 0.f : sum * __expf(m - M);
+        if constexpr (LPR == kWave) part = wave_sum_f32(mine); else part = row16_sum(mine);
+        lse = M + logf(part);
+        if (c == 0) { lse_out[s * B + row] = lse; sh.lse[row] = lse; sh.bs[row] = bsi; }
+        best = reaches(m, 0u) ? f32_sortable(bsi + (m - lse) + 0.0f) : 0u;
+    }
+    LSH_TRACE_ANY(2, 1);
+    if constexpr (LPR == kWave) {
+        const uint32_t kth = has_row ? wave_kth_largest_sort(best, B) : 0u;
+        if (ln == 0) sh.wtau[wv] = kth;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < kSelWaves; ++w) tau = max(tau, sh.wtau[w]);
+    } else {
+        tau = block_kth_largest_lb(best, B, &sh);
+    }
+    LSH_TRACE_ANY(2, 2);
+    // the row's tiles that reach tau, one list reservation per wave
+    {
+        uint32_t hits = 0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+            hits |= (has_row && c + q * LPR < ntiles && reaches(rec[q].x, tau)) ? 1u << q : 0u;
+        if (__ballot(hits != 0) != 0ull) {   // (uniform)
+            const uint32_t n = (uint32_t)__popc(hits), incl = wave_incl_scan(n);
+            uint32_t base = 0;
+            if (ln == 0) base = atomicAdd(&sh.misc[5], wave_read_lane(incl, kWave - 1));
+            uint32_t pos = wave_read_lane(base, 0) + incl - n;
+            for (uint32_t left = hits; left; left &= left - 1u, ++pos)
+                if (pos < (uint32_t)kListOpen) sh.open_list[pos] = ((uint32_t)row << 20) | (uint32_t)(c + (__ffs(left) - 1) * LPR);
+        }
+    }
+    // (plain loads below: none of them may come from a cache line fetched before the other workgroups' stores)
+    if constexpr (SAME_KERNEL) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    __syncthreads();
+    LSH_TRACE_ANY(2, 7);
+    const int n_open = (int)sh.misc[5];
+    if (n_open > kListOpen) return false;
+    auto open_tiles = [&](auto in_flight) {
+        constexpr int U = decltype(in_flight)::value;
+        float x[U];
+        int32_t id[U];
+        int i[U];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = (tid >> 4) + u * (kSelThreads / 16);
+            const uint32_t ent = sh.open_list[max(min(j, n_open - 1), 0)];
+            i[u] = j < n_open ? (int)(ent >> 20) : 0;
+            const int at = j < n_open ? (int)(ent & 0xFFFFFu) * open.tn + (ln & 15) : open.C;
+            ok[u] = at < open.C && (ln & 15) < open.tn;
+            x[u] = open.logits[(size_t)i[u] * open.cpitch + (ok[u] ? at : 0)];
+            id[u] = open.cand ? open.cand[ok[u] ? at : 0] : at;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float sc = sh.bs[i[u]] + (x[u] - sh.lse[i[u]]);
+            ok[u] = ok[u] && sc > -INFINITY && f32_sortable(sc + 0.0f) >= tau;
+            const uint64_t bal = __ballot(ok[u]);
+            if (bal == 0ull) continue;   // (uniform)
+            uint32_t base = 0;
+            if (ln == 0) base = atomicAdd(&sh.misc[4], (uint32_t)__popcll(bal));
+            const uint32_t pos = wave_read_lane(base, 0) + lanes_below(bal);
+            static_assert(kListOpen * kTileN <= kSelListCap, "room for every column of every opened tile");
+            if (ok[u]) sh.list[pos] = make_key(sc, ((uint32_t)i[u] << 24) | (uint32_t)id[u]);
+        }
+    };
+    if (n_open <= kSelThreads / 16) open_tiles(std::integral_constant<int, 1>{});
+    else open_tiles(std::integral_constant<int, 4>{});
+    LSH_TRACE_ANY(2, 8);
+    return true;
+}
+// At most 16 tiles' records for a lane: 1024 tiles up to 16 beams, 256 beyond.  *C_out: the list's length.
+template <int LPR, bool SAME_KERNEL, typename REC>
+__device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* records, int64_t ppitch, int C_at,
+                                            const int32_t* count, int V, int B, const float* beam_scores, float* lse_out,
+                                            int tile_forced, const float* logits, int64_t cpitch, const int32_t* cand, int* C_out) {
+    const int row = threadIdx.x / LPR, c = threadIdx.x & (LPR - 1);
+    LSH_TRACE_ANY(2, 0);
+    // (as in select_rich_small: four records per lane before the list's length is known, what it needs beyond after that)
+    constexpr int MOST = 2 * kSelBatch;
+    REC rec[MOST];
+    const REC* pr = records + ((size_t)s * B + min(row, B - 1)) * ppitch;
+    float bsi = 0.f;
+    if (row < B) {
+        bsi = beam_scores[s * B + row];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) rec[q] = load_record<SAME_KERNEL>(pr + min((int64_t)(c + q * LPR), ppitch - 1));
+    }
+    const int C = C_at >= 0 ? C_at : (count ? count[s] : V);
+    const int tn = sizeof(REC) == sizeof(float4) ? select_tile_width(C, tile_forced, ppitch) : kTileN;
+    const int ntiles = (C + tn - 1) / tn;
+    *C_out = C;
+    const OpenSrc open{logits + (size_t)s * B * cpitch, cpitch, cand ? cand + (size_t)s * V : nullptr, C, tn};
+    if (ntiles == 0 || ntiles > MOST * LPR) return false;   // (uniform, like every return here)
+    if (ntiles <= 4 * LPR) {
+        REC few[4] = {rec[0], rec[1], rec[2], rec[3]};
+        return select_list_body<LPR, SAME_KERNEL, 4>(sh, s, bsi, few, ntiles, B, lse_out, open);
+    }
+    auto more = [&](auto upto) {
+        constexpr int Q = decltype(upto)::value;
+        REC all[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            all[q] = q < 4 ? rec[q < 4 ? q : 0] : empty_record<REC>();
+            if (q >= 4 && row < B && q * LPR < ntiles) all[q] = load_record<SAME_KERNEL>(pr + min((int64_t)(c + q * LPR), ppitch - 1));
+        }
+        return select_list_body<LPR, SAME_KERNEL, Q>(sh, s, bsi, all, ntiles, B, lse_out, open);
+    };
+    if (ntiles <= kSelBatch * LPR) return more(std::integral_constant<int, kSelBatch>{});
+    return more(std::integral_constant<int, MOST>{});
+}
+
+// BEAMS: 16, 64: the sentence has at most 16, or 17 to 64; 0: more; -1: any number.  (A kernel holds the code for its own beams: 53 to
+// 60 KB instead of 83, each launch fetches what it runs of it anew.)
+template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false, bool WIDE = false, int BEAMS = -1>
 __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const float* logits, int64_t cpitch,
                                                 const TileRecord* records, const int32_t* ids2, int64_t ppitch,
                                                 const int32_t* cand, const int32_t* count, int C_known,
                                                 int V, int B, const float* beam_scores, float* lse_out,
                                                 int32_t* out_beam, int32_t* out_word, float* out_score,
                                                 int tile_forced = 0, int rec_groups = 0) {
-    if constexpr (RICH) {
+    if constexpr (RICH && (BEAMS == 16 || BEAMS < 0)) {
         if (B <= kSelWaves) {
             int C_seen = C_known;
             if (select_rich_small<SAME_KERNEL>(sh, s, records, ids2, ppitch, count, C_known, V, B, beam_scores, lse_out,
@@ -661,7 +824,29 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
             __syncthreads();    // (not this shape, or a tile may hide a winner: everybody has read the verdict)
         }
     }
+    bool listed = false;   // (uniform) sh.list has the keys that can win
     typedef typename std::conditional<RICH, float4, float2>::type REC;
+    constexpr bool FEW = !RICH && (BEAMS == 16 || BEAMS < 0), MANY = BEAMS == 64 || BEAMS < 0;
+    if constexpr (!GROUPS && !WIDE && (FEW || MANY)) {
+        const bool few = FEW && B <= kSelWaves, many = MANY && B > kSelWaves && B <= 4 * kSelWaves;
+        if (few || many) {
+            int C_seen = C_known;
+            const REC* recs = reinterpret_cast<const REC*>(records);
+            if constexpr (FEW)
+                if (few) listed = select_list<kWave, SAME_KERNEL>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
+                                                                  tile_forced, logits, cpitch, cand, &C_seen);
+            if constexpr (MANY)
+                if (many) listed = select_list<16, SAME_KERNEL>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
+                                                                tile_forced, logits, cpitch, cand, &C_seen);
+            C_known = C_seen;
+            __syncthreads();
+            if (listed && sh.misc[4] <= (uint32_t)kWave) {
+                rank_by_ballots(sh, (int)sh.misc[4], false, B, (size_t)s * B, out_beam, out_word, out_score);
+                LSH_TRACE_ANY(2, 5);
+                return;
+            }
+        }
+    }
     const REC* partials = reinterpret_cast<const REC*>(records);
     // batches of tile maxima a wave keeps in registers between the passes (rich records: also the
     // second largest and both ids, so one batch only)
@@ -676,12 +861,12 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     // iteration wait for a memory round trip (and for the records requested ahead of it).
     float bs_pre = 0.f;
     constexpr bool grouped = GROUPS;
-    if (!grouped && wv + ln * kSelWaves < B) bs_pre = beam_scores[s * B + wv + ln * kSelWaves];   // (B <= 256: ln < 16)
+    if (!grouped && !listed && wv + ln * kSelWaves < B) bs_pre = beam_scores[s * B + wv + ln * kSelWaves];   // (B <= 256: ln < 16)
     REC first_batch[kSelBatch];
     int32_t first_ids2[kSelBatch];
 #pragma unroll
     for (int q = 0; q < kSelBatch; ++q) { first_batch[q] = empty_record<REC>(); first_ids2[q] = -1; }
-    if (wv < B && !grouped) {
+    if (wv < B && !grouped && !listed) {
         const size_t r0 = ((size_t)s * B + wv) * ppitch;
 #pragma unroll
         for (int q = 0; q < kSelBatch; ++q) {
@@ -701,7 +886,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     static_assert(!(GROUPS && RICH), "rich records are per tile");
     const int nrec = ntiles;
     const float* lg = logits + (size_t)s * B * cpitch;
-    if (tid == 0) { sh.misc[4] = 0; sh.misc[5] = 0; sh.misc[6] = 0; }
+    if (!listed && tid == 0) { sh.misc[4] = 0; sh.misc[5] = 0; sh.misc[6] = 0; }
     // Ranks the m <= kSelRankCap keys of sh.list by counting (the inner loop split over the
     // workgroup: thread t compares key e = t % m with one of `parts` slices of the list); ends
     // with a barrier, ranks in sh.rank.
@@ -748,8 +933,9 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     };
 
     const ScoreSrc src{lg, cpitch, B, C, sh.lse, sh.bs};
-    uint32_t tau;
-    if (grouped) {
+    uint32_t tau = 0;
+    if (listed) {
+    } else if (grouped) {
         __syncthreads();   // (the counters)
         tau = select_front_grouped(sh, s, reinterpret_cast<const float2*>(records), ppitch, ntiles, rec_groups, B,
                                    beam_scores, lse_out);
@@ -1070,7 +1256,8 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     //     when that makes one round trip to memory of two (the logits were written by other
     //     XCDs: every sweep batch is a cold read)
     const uint32_t n_open = sh.misc[5];
-    if (WIDE && n_open <= (uint32_t)kSelOpenCap) {
+    if (listed) {
+    } else if (WIDE && n_open <= (uint32_t)kSelOpenCap) {
         // (a wide tile: four consecutive columns per lane, two sweeps in flight)
         for (uint32_t g0 = (uint32_t)(tid >> 4); g0 < n_open; g0 += 2 * (kSelThreads / 16)) {
             float4 x[2];
@@ -1106,6 +1293,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
             for (uint32_t g0 = (uint32_t)(tid >> 4); g0 < n_open; g0 += U * (kSelThreads / 16)) {
                 float x[U], lsev[U], bsq[U];
                 int c[U], iq[U];
+                int32_t id[U];   // (asked for beside the logit: one trip to memory less where the results are written)
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     const uint32_t j = g0 + u * (kSelThreads / 16);
@@ -1114,6 +1302,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
                     const int cc = (int)(ent & 0xFFFFFu) * tn + (ln & 15);
                     c[u] = (j < n_open && (ln & 15) < tn && cc < C) ? cc : -1;
                     x[u] = lg[(size_t)iq[u] * cpitch + max(c[u], 0)];
+                    id[u] = cand ? cand[(size_t)s * V + max(c[u], 0)] : c[u];
                     lsev[u] = sh.lse[iq[u]];
                     bsq[u] = sh.bs[iq[u]];
                 }
@@ -1123,7 +1312,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
                     if (c[u] >= 0 && f32_sortable(sc + 0.0f) >= tau) {
                         const uint32_t pos = atomicAdd(&sh.misc[4], 1u);
                         if (pos < (uint32_t)kSelListCap)
-                            sh.list[pos] = make_key(sc, ((uint32_t)iq[u] << 24) | (uint32_t)c[u]);
+                            sh.list[pos] = make_key(sc, ((uint32_t)iq[u] << 24) | (uint32_t)id[u]);
                     }
                 }
             }
@@ -1170,20 +1359,22 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
         __syncthreads();
         m = (int)sh.misc[4];
     }
+    bool ids_in_keys = true;
     if (m > kSelRankCap) {
         __syncthreads();
         block_radix_select(src, B, &sh);
         m = B;
+        ids_in_keys = false;
     }
     rank_list(m);
     LSH_TRACE_ANY(2, 4);
-    emit(m, false);
+    emit(m, ids_in_keys);
     LSH_TRACE_ANY(2, 5);
 }
 
 // grid = S workgroups (one per sentence), kSelThreads threads: the selection as a kernel of its
 // own, after kernels that left rich (fused plans) or plain tile records.
-template <bool RICH, bool GROUPS, bool WIDE = false>
+template <bool RICH, bool GROUPS, bool WIDE = false, int BEAMS = -1>
 __global__ void __launch_bounds__(kSelThreads)
 k_select(const float* __restrict__ logits, int64_t cpitch, const TileRecord* __restrict__ records,
          const int32_t* __restrict__ ids2, int64_t ppitch, const int32_t* __restrict__ cand,
@@ -1191,7 +1382,7 @@ k_select(const float* __restrict__ logits, int64_t cpitch, const TileRecord* __r
          float* __restrict__ lse_out /*[R]*/, int32_t* __restrict__ out_beam,
          int32_t* __restrict__ out_word, float* __restrict__ out_score, int tile_forced, int rec_groups) {
     __shared__ SelShared sh;
-    select_sentence<RICH, false, GROUPS, WIDE>(sh, (int)blockIdx.x, logits, cpitch, records, ids2, ppitch, cand, count, -1,
+    select_sentence<RICH, false, GROUPS, WIDE, BEAMS>(sh, (int)blockIdx.x, logits, cpitch, records, ids2, ppitch, cand, count, -1,
                                          V, B, beam_scores, lse_out, out_beam, out_word, out_score, tile_forced,
                                          rec_groups);
 }
