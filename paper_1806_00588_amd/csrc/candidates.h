@@ -318,8 +318,8 @@ inline void set_derived(CandArgs& a) {
 // probes, bucket walk and the top-frequent words.  Only the sentence's rows [row_begin, row_end)
 // are hashed (row_end < 0: all B).  Called by all kCandThreads threads of a workgroup with
 // candidates_lds_words() words of LDS; ends with a workgroup barrier.
-// DEEP (for the kernels that have the registers): walks of more than eight elements per thread
-// keep twelve span reads in flight, and the second thousand of top-frequent ids is asked for up
+// DEEP (for the kernels that have the registers): walks of more than two groups of ids per thread
+// keep four or eight span reads in flight, and the second thousand of top-frequent ids is asked for up
 // front too.
 template <bool DEEP = false>
 __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, uint32_t* smem,
@@ -518,41 +518,46 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
             LSH_TRACE_WG(3);
             continue;
         }
+        const uint32_t my_groups = len ? (len + (((uint32_t)((size_t)w * V + start)) & 3u) + 3u) >> 2 : 0u;
         uint32_t total;
-        const uint32_t incl = block_incl_scan(len, wsum, &total);
+        const uint32_t incl = block_incl_scan(my_groups, wsum, &total);
         LSH_TRACE(0, 4);
-        p_start[tid] = start;
-        p_band[tid] = w;
-        p_pref[tid] = incl - len;
+        p_pref[tid] = incl - my_groups;
         __syncthreads();
-        // Algorithm 1 lines 3-6 as a flat walk over all spans of the chunk: element e belongs
-        // to the last pair whose exclusive prefix is <= e.  An index past the end is clamped for
-        // the load and skipped for the mark: hundreds of atomics on the last element's word
-        // would serialise.  Long walks (several elements per thread) keep four span reads in
-        // flight per thread (twelve beyond eight elements per thread: a round is a trip to
-        // memory), short ones two: with four, every thread searches four times even when the
-        // chunk has fewer elements than that.
+        // Algorithm 1 lines 3-6 as a flat walk over the aligned groups of four ids of all spans of the chunk: group e
+        // belongs to the last pair whose exclusive prefix is <= e.  (By single ids, four times the searches, ten reads of LDS at
+        // unlike banks each: of 12000 ids of 160 spans, 64 x 10 beams, V = 200000, 5.7 us, 3 so.)  An index past the end is clamped
+        // for the load and skipped for the mark: hundreds of atomics on the last group's words would serialise.  Long walks
+        // keep four reads in flight per thread (eight beyond eight groups per thread: a round is a trip to memory), short ones two.
+        const int4* __restrict__ words4 = reinterpret_cast<const int4*>(words);
         auto walk = [&](auto width_tag) {
             constexpr int NW = decltype(width_tag)::value;
             for (uint32_t e0 = tid; e0 < total; e0 += NW * kCandThreads) {
                 uint32_t e[NW];
                 int l[NW];
-                int32_t id[NW];
+                int4 grp[NW];
 #pragma unroll
                 for (int q = 0; q < NW; ++q) e[q] = min(e0 + (uint32_t)(q * kCandThreads), total - 1);
 #pragma unroll
                 for (int q = 0; q < NW; ++q) l[q] = last_not_above(p_pref, e[q]);
 #pragma unroll
-                for (int q = 0; q < NW; ++q)
-                    id[q] = words[(size_t)p_band[l[q]] * V + p_start[l[q]] + (e[q] - p_pref[l[q]])];
+                for (int q = 0; q < NW; ++q) {
+                    e[q] -= p_pref[l[q]];   // (the group's number in its span)
+                    grp[q] = words4[(size_t)p_start[l[q]] + e[q]];
+                }
 #pragma unroll
-                for (int q = 0; q < NW; ++q)
-                    if (e0 + (uint32_t)(q * kCandThreads) < total)
-                        atomicOr(&bm[id[q] >> 5], 1u << (id[q] & 31));
+                for (int q = 0; q < NW; ++q) {
+                    const uint32_t lm = p_band[l[q]], smis = lm >> 30, send = smis + (lm & 0x3FFFFFFFu), p0 = 4u * e[q];
+                    const int32_t ids[4] = {grp[q].x, grp[q].y, grp[q].z, grp[q].w};
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (e0 + (uint32_t)(q * kCandThreads) < total && p0 + c >= smis && p0 + c < send)
+                            atomicOr(&bm[ids[c] >> 5], 1u << (ids[c] & 31));
+                }
             }
         };
-        if (DEEP && total > 8u * kCandThreads) walk(std::integral_constant<int, 12>{});
-        else if (total > 4u * kCandThreads) walk(std::integral_constant<int, 4>{});
+        if (DEEP && total > 8u * kCandThreads) walk(std::integral_constant<int, 8>{});
+        else if (DEEP && total > 2u * kCandThreads) walk(std::integral_constant<int, 4>{});
         else walk(std::integral_constant<int, 2>{});
         __syncthreads();
         LSH_TRACE(0, 5);
@@ -575,28 +580,33 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
 // in LDS instead (word, output offset) and, after a barrier, expanded by ALL waves, 32 lanes per
 // word, one lane per bit, so that the stores are contiguous.  Dense words beyond the list's
 // capacity are expanded by their own wave, two at a time.
-// Called by all kCandThreads threads; wsum is LDS scratch of >= kCandWaves + 1 words, dlist LDS
+// PARTS workgroups with the same bitmap share the work: wave w of workgroup `part` has range w PARTS + part of 16 PARTS, and every
+// workgroup counts all of them.
+// Called by all kCandThreads threads; wsum is LDS scratch of 16 PARTS words, ndense one word, dlist LDS
 // room for dcap entries.
-__device__ __forceinline__ void compact_bitmap(const uint32_t* bm, int nwords, uint32_t* wsum,
+template <int PARTS>
+__device__ __forceinline__ void compact_bitmap(const uint32_t* bm, int nwords, uint32_t* wsum, uint32_t* ndense,
                                                uint2* dlist, int dcap, int32_t* __restrict__ out,
-                                               int32_t* __restrict__ count_out) {
+                                               int32_t* __restrict__ count_out, int part) {
+    static_assert(kCandWaves * PARTS <= kWave, "a lane per range");
     const int tid = threadIdx.x, wv = wave_id(), ln = lane_id();
-    int per_wave = (nwords + kCandWaves - 1) / kCandWaves;
-    per_wave = (per_wave + kWave - 1) / kWave * kWave;
-    const int wbeg = wv * per_wave;
-    const int wend = min(nwords, wbeg + per_wave);
-    uint32_t cnt = 0;
-    for (int i = wbeg + ln; i < wend; i += kWave) cnt += __popc(bm[i]);
-    cnt = wave_sum(cnt);
-    if (ln == 0) wsum[wv] = cnt;
-    if (tid == 0) wsum[kCandWaves] = 0;  // entries on the dense list
-    __syncthreads();
-    uint32_t running = 0, total = 0;
-    for (int i = 0; i < kCandWaves; ++i) {
-        const uint32_t x = wsum[i];
-        if (i < wv) running += x;
-        total += x;
+    int per_range = (nwords + kCandWaves * PARTS - 1) / (kCandWaves * PARTS);
+    per_range = (per_range + kWave - 1) / kWave * kWave;
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) {
+        const int beg = (wv * PARTS + p) * per_range, end = min(nwords, beg + per_range);
+        uint32_t cnt = 0;
+        for (int i = beg + ln; i < end; i += kWave) cnt += __popc(bm[i]);
+        cnt = wave_sum(cnt);
+        if (ln == 0) wsum[wv * PARTS + p] = cnt;
     }
+    if (tid == 0) *ndense = 0;  // entries on the dense list
+    __syncthreads();
+    const int range = __builtin_amdgcn_readfirstlane(wv * PARTS + part);
+    const uint32_t in_range = ln < kCandWaves * PARTS ? wsum[ln] : 0u, upto = wave_incl_scan(in_range);
+    uint32_t running = wave_read_lane(upto - in_range, range);
+    const uint32_t total = wave_read_lane(upto, kWave - 1);
+    const int wbeg = range * per_range, wend = min(nwords, wbeg + per_range);
     const int half = ln >> 5, hbit = ln & 31;
     for (int i0 = wbeg; i0 < wend; i0 += kWave) {
         const int i = i0 + ln;
@@ -615,7 +625,7 @@ __device__ __forceinline__ void compact_bitmap(const uint32_t* bm, int nwords, u
         }
         if (dmask) {  // wave-uniform
             uint32_t base = 0;
-            if (ln == 0) base = atomicAdd(&wsum[kCandWaves], (uint32_t)__popcll(dmask));
+            if (ln == 0) base = atomicAdd(ndense, (uint32_t)__popcll(dmask));
             base = wave_read_lane(base, 0);
             const uint32_t pos = base + lanes_below(dmask);
             const bool listed = dense && pos < (uint32_t)dcap;
@@ -639,10 +649,10 @@ __device__ __forceinline__ void compact_bitmap(const uint32_t* bm, int nwords, u
         }
         running += wave_read_lane(incl, kWave - 1);
     }
-    if (tid == 0) *count_out = (int32_t)total;
+    if (part == 0 && tid == 0) *count_out = (int32_t)total;
     __syncthreads();
     // the listed dense words: half a wave per word, all waves
-    const int nlisted = (int)min(wsum[kCandWaves], (uint32_t)dcap);
+    const int nlisted = (int)min(*ndense, (uint32_t)dcap);
     for (int k = 2 * wv + half; k < nlisted; k += 2 * kCandWaves) {
         const uint2 ent = dlist[k];
         const uint32_t wbits = bm[ent.x];
@@ -658,17 +668,24 @@ __host__ __device__ inline size_t union_compact_lds_words(int V) {
     return (size_t)bitmap_words_padded(V) + 64 + 2 * (size_t)kUnionDenseCap;
 }
 
-// One workgroup per sentence.  Requires W <= kCandThreads.
+// Requires W <= kCandThreads.  Where the chip has CUs for them and the bitmap is long, kCandParts workgroups per sentence: each makes
+// the whole bitmap, which takes no longer beside the others, and writes a part of the list.  One workgroup alone is bound by
+// instruction issue there: with V = 200000 a wave expands seven times 64 words (4.8 us).  With the walk by groups, 64 x 10 beams,
+// V = 200000: 18.9 -> 13.1 us; a step of 13 x 6, V = 111500: 20.3 -> 18.8.  V = 40000, two times 64 words: 8 x 5 7.9, 7.9; 32 x 10 8.2, 7.9;
+// 5 x 17, V = 39989, 8.8, 9.3.  Workgroup p S + s is part p of sentence s, so that the parts of a sentence are mostly on one XCD.
+constexpr int kCandParts = 4;
+inline bool candidates_split(int S, int V) { return S * kCandParts <= 256 && V > 2 * kCandWaves * kWave * 32; }
+template <int PARTS>
 __global__ void __launch_bounds__(kCandThreads)
-k_candidates(CandArgs a, int32_t* __restrict__ cand, int32_t* __restrict__ count) {
+k_candidates(CandArgs a, int S, int32_t* __restrict__ cand, int32_t* __restrict__ count) {
     extern __shared__ uint32_t smem[];
-    const int s = blockIdx.x;
+    const int part = PARTS == 1 ? 0 : blockIdx.x / S, s = PARTS == 1 ? blockIdx.x : blockIdx.x - part * S;
     const int nwords = (a.V + 31) >> 5;
     uint32_t* wsum = smem + candidates_lds_words(a.V, a.P, a.K, a.stage_words) - 64;
     build_presence_bitmap<true>(a, s, smem);
-    // (the staged hidden rows are no longer needed: their room takes the dense-word list)
+    // (the staged hidden rows are no longer needed: their room takes the dense-word list; nor are the prefixes in front of wsum)
     uint2* dlist = reinterpret_cast<uint2*>(smem + bitmap_words_padded(a.V));
-    compact_bitmap(smem, nwords, wsum, dlist, a.stage_words / 2, cand + (size_t)s * a.V, count + s);
+    compact_bitmap<PARTS>(smem, nwords, wsum, wsum - 1, dlist, a.stage_words / 2, cand + (size_t)s * a.V, count + s, part);
     LSH_TRACE(0, 6);
 }
 
@@ -925,7 +942,7 @@ k_union_compact(const uint32_t* __restrict__ row_bitmaps, int B, int V,
     __syncthreads();
     mark_id_list<true>(bm, V, topfreq, T, tf_first, tf_second);
     __syncthreads();
-    compact_bitmap(bm, nwords, wsum, dlist, kUnionDenseCap, cand + (size_t)s * V, count + s);
+    compact_bitmap<1>(bm, nwords, wsum, wsum + kCandWaves, dlist, kUnionDenseCap, cand + (size_t)s * V, count + s, 0);
 }
 
 }  // namespace lshbeam

@@ -694,7 +694,8 @@ hipError_t allow_step_lds(int dev) {
     if (bit && (done.load(std::memory_order_acquire) & bit)) return hipSuccess;
     hipError_t e = hipSuccess;
 #define LSH_ALLOW(...) do { if (e == hipSuccess) e = (__VA_ARGS__); } while (0)
-    LSH_ALLOW(allow_whole_lds<k_candidates>());
+    LSH_ALLOW(allow_whole_lds<k_candidates<1>>());
+    LSH_ALLOW(allow_whole_lds<k_candidates<kCandParts>>());
     LSH_ALLOW(allow_whole_lds<k_hit_rows>());
     LSH_ALLOW(allow_whole_lds<k_union_compact>());
     LSH_ALLOW(allow_whole_lds<k_part_bitmaps>());
@@ -1212,8 +1213,10 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
             cand = w.cand;
             count = w.count;
         } else if (!sp->full_vocab) {
-            launch(cx, 0, k_candidates, dim3(sp->S), dim3(kCandThreads),
-                   candidates_lds_words(t->V, t->P, t->K, stage) * sizeof(uint32_t), ca, w.cand, w.count);
+            const size_t lds = candidates_lds_words(t->V, t->P, t->K, stage) * sizeof(uint32_t);
+            if (candidates_split(sp->S, t->V))
+                launch(cx, 0, k_candidates<kCandParts>, dim3(sp->S * kCandParts), dim3(kCandThreads), lds, ca, sp->S, w.cand, w.count);
+            else launch(cx, 0, k_candidates<1>, dim3(sp->S), dim3(kCandThreads), lds, ca, sp->S, w.cand, w.count);
             cand = w.cand;
             count = w.count;
         }
