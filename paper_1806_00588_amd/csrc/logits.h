@@ -1869,6 +1869,21 @@ __device__ __forceinline__ Chunk16U<ET> load_chunk_end(const ET* row, int k, int
     if (s & (4 * ONE)) { c.w[0] = 0u; c.w[1] = 0u; c.w[2] = 0u; c.w[3] = 0u; }
     return c;
 }
+// The same shifts of a chunk that is here already: without its first s elements, zeros behind.  (Called from load_chunk_end it cost
+// k_logits_few 14 registers and, 27 rows, V = 51168, d = 1312, 32 us of 88.)
+template <typename ET>
+__device__ __forceinline__ void drop_front(Chunk16U<ET>& c, int s) {
+    if constexpr (sizeof(ET) == 2) {
+        if (s & 1) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c.w[i] = (c.w[i] >> 16) | (i < 3 ? c.w[i < 3 ? i + 1 : 3] << 16 : 0u);
+        }
+    }
+    constexpr int ONE = 4 / (int)sizeof(ET);        // elements per word
+    if (s & ONE) { c.w[0] = c.w[1]; c.w[1] = c.w[2]; c.w[2] = c.w[3]; c.w[3] = 0u; }
+    if (s & (2 * ONE)) { c.w[0] = c.w[2]; c.w[1] = c.w[3]; c.w[2] = 0u; c.w[3] = 0u; }
+    if (s & (4 * ONE)) { c.w[0] = 0u; c.w[1] = 0u; c.w[2] = 0u; c.w[3] = 0u; }
+}
 template <typename ET> __device__ __forceinline__ bf16x8 as_bf16x8(const Chunk16U<ET>& c) {
     return __builtin_bit_cast(bf16x8, make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]));
 }
@@ -2241,6 +2256,213 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
         for (int m = 0; m < MT; ++m) acc[m][0] += low[m];
     }
     finish_wide<BF>(acc, E, ld, d, H, 0, word0, R, V, logits, cpitch, recs, reinterpret_cast<float2*>(sm + 2 * kBuf));
+}
+
+// The same where the hidden rows fit in LDS whole, which is what most calls of few rows have: one workgroup per CU loads them once
+// and shares out the words, so that nothing but E passes through the CU's load path afterwards (k_logits_few's workgroups, of
+// 64 words each, read all hidden rows for every 256 KB of E), no barrier stands in the loop and every CU has the same to
+// do: 625 workgroups of V = 40000 were two on some CUs and three on others.  A wave has `rounds` times 16 words in a row, sixteen
+// chunks of every lane on their way, the next tile's while one is finished; every workgroup leaves ONE record per hidden row, for its
+// 16 W rounds words, as the selection is bound by what one CU pulls in.  The sums are k_logits_few's, bit for bit.
+// us a step, k_logits_few and so: 12 rows, V = 40000, d = 1000 46.6, 42.5 (the pass over cold E 37.9 -> 35.7, selection 8.3 -> 6.2); 45
+// rows, V = 94357, d = 216 56, 45; 22 rows, V = 97522, d = 80 35, 26; 22 rows, V = 140258, d = 1016 155, 151; bf16: 4 rows, V = 129085,
+// d = 336 32, 29.
+constexpr int kPassRing = 16;    // chunks of a lane on their way
+constexpr int kPassWaves = 12;   // at most: registers for the ring and the operands on their way from LDS
+template <typename ET> __host__ __device__ inline int pass_pitch(int d) {   // elements per hidden row and plane, zeros past d
+    constexpr int KSTEP = 64 / (int)sizeof(ET);
+    int p = (d + KSTEP - 1) / KSTEP * KSTEP;
+    while (sizeof(ET) == 2 ? p % 64 != 8 : p % 32 != 4) p += sizeof(ET) == 2 ? 8 : 4;
+    return p;
+}
+template <typename ET> __host__ __device__ inline size_t pass_lds_bytes(int MT, int d) {
+    return (size_t)few_planes<ET>() * MT * kTileM * pass_pitch<ET>(d) * sizeof(ET) + (size_t)kPassWaves * MT * kTileM * sizeof(float2);
+}
+template <typename ET, int MT>
+__global__ void __launch_bounds__(kPassWaves * kWave)
+k_logits_pass(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int R, int V, int rounds,
+              float* __restrict__ logits, int64_t cpitch, TileRecords recs) {
+    constexpr bool BF = sizeof(ET) == 2;
+    constexpr int NP = few_planes<ET>(), CK = 16 / (int)sizeof(ET), KSTEP = 4 * CK, RING = kPassRing;
+    extern __shared__ uint4 psm[];
+    char* sm = reinterpret_cast<char*>(psm);
+    const int pitch = pass_pitch<ET>(d), row_bytes = pitch * (int)sizeof(ET), plane = MT * kTileM * row_bytes;
+    float2* part = reinterpret_cast<float2*>(sm + NP * plane);               // [waves][16 MT]
+    const int tid = threadIdx.x, ln = lane_id(), wv = __builtin_amdgcn_readfirstlane(wave_id()), W = blockDim.x >> 6;
+    const int col = ln & 15, kk = ln >> 4;
+    const int nst = (d + KSTEP - 1) / KSTEP, groups = (nst + RING - 1) / RING;
+    const int64_t tile0 = ((int64_t)blockIdx.x * W + wv) * rounds;
+    Chunk16U<ET> e[RING];
+    const char* base = nullptr;                               // the tile's first row (uniform)
+    uint32_t mine = 0;                                        // this lane's row from there, in bytes (the host: 16 rows below 2^31)
+    const int last = d - CK;
+    // (steps past the row: one address for all lanes, which costs the load path next to nothing, and no branch around the load)
+    auto load = [&](int st) {
+        const uint32_t at = mine + (uint32_t)min(st * KSTEP + kk * CK, last) * (uint32_t)sizeof(ET);
+        const uint32_t in_row = __builtin_amdgcn_readfirstlane(st < nst ? ~0u : 0u);
+        return *reinterpret_cast<const Chunk16U<ET>*>(base + (at & in_row));
+    };
+    auto begin = [&](int64_t tile) {
+        base = reinterpret_cast<const char*>(E + tile * kTileN * ld);
+        mine = (uint32_t)min(col, (int)(V - 1 - tile * kTileN)) * (uint32_t)(ld * (int64_t)sizeof(ET));
+#pragma unroll
+        for (int j = 0; j < RING / 2; ++j) e[j] = load(j);
+        if (nst > RING / 2)   // (uniform)
+#pragma unroll
+            for (int j = RING / 2; j < RING; ++j) e[j] = load(j);
+    };
+    const bool works = tile0 * kTileN < V;   // (uniform)
+    // Hidden rows, zeros past d and for rows past R; asked for ahead of the first words, all at once.
+    const int quads = pitch >> 2, rows = min(R, MT * kTileM);  // (four elements)
+    auto zero_rows = [&](char* of) {
+        float4* to = reinterpret_cast<float4*>(of + rows * row_bytes);
+        for (int i = tid; i < (MT * kTileM - rows) * row_bytes / 16; i += W * kWave) to[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    };
+    if constexpr (!BF) {
+        const int whole = d >> 2, pieces = (whole + kWave - 1) / kWave, pad = quads - whole;
+        for (int u = wv, r = 0; u < rows * pieces; u += W) {  // (uniform)
+            while ((r + 1) * pieces <= u) ++r;
+            const int q = (u - r * pieces) * kWave + ln;
+            if (q < whole) load_to_lds16(H + (size_t)r * d + 4 * q, sm + r * row_bytes + (q - ln) * 16);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if (works) begin(tile0);
+        __builtin_amdgcn_sched_barrier(0);
+        for (int i = tid; i < rows * pad; i += W * kWave) {
+            const int r = small_div(i, pad), q = whole + i - r * pad;
+            float x[4] = {0.f, 0.f, 0.f, 0.f};
+            if (q == whole)
+#pragma unroll
+                for (int k = 0; k < 3; ++k) if (4 * q + k < d) x[k] = H[(size_t)r * d + 4 * q + k];
+            *reinterpret_cast<float4*>(sm + r * row_bytes + 16 * q) = make_float4(x[0], x[1], x[2], x[3]);
+        }
+        zero_rows(sm);
+        if (works) wait_vmem<RING / 2>(); else wait_vmem<0>();   // (as many loads of words at least are younger)
+    } else {
+        constexpr int AT_ONCE = 8;   // (loads behind the words' would wait for those)
+        bool begun = false;
+        for (int i0 = tid; i0 - tid < rows * quads; i0 += AT_ONCE * W * kWave) {   // (uniform)
+            Float4U v[AT_ONCE];
+            int r[AT_ONCE], q[AT_ONCE];
+#pragma unroll
+            for (int a = 0; a < AT_ONCE; ++a) {
+                const int i = min(i0 + a * W * kWave, rows * quads - 1);       // (the last one again)
+                r[a] = small_div(i, quads);
+                q[a] = i - r[a] * quads;
+                v[a] = *reinterpret_cast<const Float4U*>(H + (size_t)r[a] * d + min(4 * q[a], d - 4));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (!begun && works) begin(tile0);
+            __builtin_amdgcn_sched_barrier(0);
+            begun = true;
+#pragma unroll
+            for (int a = 0; a < AT_ONCE; ++a) {
+                const int drop = max(4 * q[a] - (d - 4), 0);
+                const float y[4] = {v[a].x, v[a].y, v[a].z, v[a].w};
+                float x[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int from = k + drop;
+                    x[k] = from == 0 ? y[0] : from == 1 ? y[1] : from == 2 ? y[2] : from == 3 ? y[3] : 0.f;
+                }
+                store_planes4(sm + r[a] * row_bytes + 8 * q[a], plane, x);
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) zero_rows(sm + p * plane);
+    }
+    lds_barrier();
+    float run_max[MT], run_sum[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) { run_max[m] = -INFINITY; run_sum[m] = 0.f; }
+    const char* hb = sm + col * row_bytes + 16 * kk;
+    for (int r = 0; r < rounds && (tile0 + r) * kTileN < V; ++r) {           // (uniform)
+        const int word0 = (int)(tile0 + r) * kTileN;
+        floatx4 acc[MT], low[MT];                             // low: bf16, as in k_logits_rows
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[m] = low[m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        auto use = [&](int st, const Chunk16U<ET>& c) {
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const char* at = hb + st * 64 + m * kTileM * row_bytes;
+                if constexpr (BF) {
+#pragma unroll
+                    for (int p = 0; p < NP; ++p) {
+                        floatx4& to = p ? low[m] : acc[m];
+                        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(c), *reinterpret_cast<const bf16x8*>(at + p * plane), to, 0, 0, 0);
+                    }
+                } else {
+                    const float4 b = *reinterpret_cast<const float4*>(at);
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(c.w[0]), b.x, acc[m], 0, 0, 0);
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(c.w[1]), b.y, acc[m], 0, 0, 0);
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(c.w[2]), b.z, acc[m], 0, 0, 0);
+                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(c.w[3]), b.w, acc[m], 0, 0, 0);
+                }
+            }
+        };
+        for (int g = 0; g + 1 < groups; ++g) {
+#pragma unroll
+            for (int j = 0; j < RING; ++j) {
+                use(g * RING + j, e[j]);
+                e[j] = load((g + 1) * RING + j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const int st0 = (groups - 1) * RING, end = nst - 1 - st0;              // the row's last step, which may reach past its end
+        Chunk16U<ET> tail = e[0];
+#pragma unroll
+        for (int j = 0; j < RING; ++j) {
+            if (j < end) use(st0 + j, e[j]);   // (uniform)
+            if (j == end) tail = e[j];
+            if (j % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // (all operands at once would take too many registers)
+        }
+        drop_front(tail, max(0, min((nst - 1) * KSTEP + kk * CK - last, CK)));
+        use(nst - 1, tail);
+        if (r + 1 < rounds && word0 + kTileN < V) begin(tile0 + r + 1);         // (on its way while this one is finished)
+        __builtin_amdgcn_sched_barrier(0);
+        // lane (col, kk): hidden row 16 m + col, words word0 + 4 kk + (0..3)
+        const int w = word0 + 4 * kk;
+        float x[MT * 4];
+#pragma unroll
+        for (int i = 0; i < MT * 4; ++i) x[i] = BF ? acc[i / 4][i % 4] + low[i / 4][i % 4] : acc[i / 4][i % 4];
+        if constexpr (BF)
+            settle_non_finite(x, [&](int i) {
+                int me = col, at = w;
+                asm volatile("" : "+v"(me), "+v"(at));   // (nothing of this is worked out in advance)
+                return plain_dot(E + (int64_t)min(at + i % 4, V - 1) * ld, H + (size_t)min(i / 4 * kTileM + me, R - 1) * d, d);
+            });
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+            const int row = m * kTileM + col;
+            if (row < R && w < V)   // (columns past V inside the row's pitch are never read)
+                *reinterpret_cast<float4*>(&logits[(size_t)row * cpitch + w]) = make_float4(x[4 * m], x[4 * m + 1], x[4 * m + 2], x[4 * m + 3]);
+            float mx = -INFINITY, se = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) mx = fmaxf(mx, w + i < V ? x[4 * m + i] : -INFINITY);
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+#pragma unroll
+            for (int i = 0; i < 4; ++i) se += w + i < V ? exp_below(x[4 * m + i], mx) : 0.f;
+            se += __shfl_xor(se, 16);
+            se += __shfl_xor(se, 32);
+            const float hi = fmaxf(run_max[m], mx);
+            run_sum[m] = run_sum[m] * exp_below(run_max[m], hi) + se * exp_below(mx, hi);
+            run_max[m] = hi;
+        }
+    }
+    if (kk == 0)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) part[wv * (MT * kTileM) + m * kTileM + col] = make_float2(run_max[m], run_sum[m]);
+    lds_barrier();
+    if (tid < MT * kTileM && tid < R) {
+        float2 a = part[tid];
+        for (int o = 1; o < W; ++o) {
+            const float2 q = part[o * (MT * kTileM) + tid];   // (a wave past V: -inf, 0)
+            const float hi = fmaxf(a.x, q.x);
+            a = make_float2(hi, a.y * exp_below(a.x, hi) + q.y * exp_below(q.x, hi));
+        }
+        reinterpret_cast<float2*>(recs.rec)[(size_t)tid * recs.pitch + blockIdx.x] = a;
+    }
 }
 
 }  // namespace lshbeam

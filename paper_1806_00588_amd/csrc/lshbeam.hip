@@ -596,7 +596,7 @@ int launch_logits(const StepCtx& cx, const float* H, const lsh_step_params* sp,
 }
 
 // Full vocabulary: one matrix product over all hidden rows of the call.  Up to 48 rows (fp32; 32 with bf16
-// words) the pass over E is what counts: k_logits_few.  Beyond that k_logits_rows; its row groups are as
+// words) the pass over E is what counts: k_logits_pass or k_logits_few.  Beyond that k_logits_rows; its row groups are as
 // even as they come in units of 16 rows, and among the splits the accumulators leave room for, the one
 // with the least work on the fullest CU is taken: two workgroups of m row tiles on a CU take 3 + m, one alone 1.5 + 0.6 m
 // (in no unit; for d from 96 to 1536 and either type each is within 12 % of that, up to a factor of d's own).
@@ -621,11 +621,46 @@ bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an optio
            t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto &&
            t->option(kOptLogitsPlanes, 1) != 0;
 }
+// Waves of a workgroup of k_logits_pass and how many times 16 words for each: the least that 256 workgroups have in all, and of
+// those the most waves; eight at least where there is work for them (d = 1200, V = 59224, 15 rows: three times with five waves 72 us a
+// step, k_logits_few 68, so 64).
+struct PassPlan { int waves, rounds; };
+inline PassPlan pass_plan(int V) {
+    const int64_t tiles = (V + kTileN - 1) / kTileN;
+    PassPlan best{0, 0};
+    for (int W = tiles >= 8 * 256 ? 8 : 4; W <= kPassWaves; ++W) {
+        const int rounds = (int)((tiles + 256 * W - 1) / (256 * W));
+        if (!best.waves || W * rounds <= best.waves * best.rounds) best = {W, rounds};
+    }
+    return best;
+}
+// Returns the words a record is for.
 template <typename ET>
-void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspace& w) {
+int launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspace& w) {
     const lsh_tables* t = cx.t;
     const int tiles = (R + kTileM - 1) / kTileM;
     constexpr int WF = sizeof(ET) == 2 ? 4 : 2, FEW = sizeof(ET) == 2 ? 2 : 3;
+    // Not where a workgroup's words are hardly more than the hidden rows it has to load first (us a step, so and k_logits_few; bytes
+    // of a workgroup's words over those of the hidden rows: d = 528, V = 6443, 35 rows, 1.3, 26.1 / 23.2; d = 168 bf16, V = 16122, 24, 0.7,
+    // 15.4 / 13.3; d = 160, V = 9866, 20, 2.0, 14.5 / 14.1; d = 80 bf16, V = 43245, 24, 1.8, 15.8 / 16.6; d = 153, V = 7365, 24, 2.0, 14.9 /
+    // 16.0; d = 312, V = 94945, 3, 24, 37 / 40; d = 216, V = 94357, 45, 8, 45 / 56; d = 88, V = 160617, 6, 40, 22 / 31).  Nor of bf16 words with
+    // 6 to 11 times 16 for a workgroup, whose rows are a burst and no stream (d = 520, V = 31623, 2 rows, 19.1 / 16.6; d = 296, V = 25204,
+    // 15.7 / 13.9; but d = 440, V = 9605, 12.3 / 12.9, d = 304, V = 84695, 22.3 / 25.2, d = 1448, V = 189305, 131 / 140).
+    const PassPlan p = pass_plan(t->V);
+    const int words = p.waves * p.rounds * kTileN;
+    const size_t lds = pass_lds_bytes<ET>(tiles, t->d);
+    constexpr int PASS = sizeof(ET) == 2 ? 1 : 3;   // (row groups; two of bf16 words, V = 191422, d = 912: 134 us, 119)
+    if (tiles <= PASS && lds <= kMaxDynLds && t->ld * (int64_t)sizeof(ET) < (int64_t)1 << 27 &&
+        2.0 * words * t->d * sizeof(ET) >= 3.0 * lds && (sizeof(ET) == 4 || p.waves * p.rounds <= 5 || p.waves * p.rounds > 11)) {
+        const dim3 grid((unsigned)((t->V + words - 1) / words)), block(p.waves * kWave);
+#define LSH_PASS(MTV)                                                                                                \
+    launch(cx, 1, k_logits_pass<ET, MTV>, grid, block, lds, (const ET*)t->E, t->ld, t->d, H, R, t->V, \
+           p.rounds, w.logits, w.cpitch, w.records())
+        if (tiles == 1) LSH_PASS(1);
+        else if constexpr (PASS == 3) { if (tiles == 2) LSH_PASS(2); else LSH_PASS(3); }
+#undef LSH_PASS
+        return words;
+    }
     if (tiles <= FEW) {
         const dim3 grid((unsigned)((t->V + kWideN - 1) / kWideN)), block(256);
 #define LSH_FEW(MTV)                                                                                           \
@@ -633,7 +668,7 @@ void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspac
            w.logits, w.cpitch, w.records())
         if (tiles == 1) LSH_FEW(1); else if (tiles == 2) LSH_FEW(2); else LSH_FEW(3);
 #undef LSH_FEW
-        return;
+        return kWideN;
     }
     const int gx = (t->V + 64 * WF - 1) / (64 * WF);
     int mt = rows_max_mt<ET>();
@@ -655,6 +690,7 @@ void launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspac
         default: if constexpr (rows_max_mt<ET>() == 5) LSH_ROWS(5);
     }
 #undef LSH_ROWS
+    return kWideN;
 }
 
 template <typename ET>
@@ -696,6 +732,10 @@ hipError_t allow_step_lds(int dev) {
 #define LSH_ALLOW(...) do { if (e == hipSuccess) e = (__VA_ARGS__); } while (0)
     LSH_ALLOW(allow_whole_lds<k_candidates<1>>());
     LSH_ALLOW(allow_whole_lds<k_candidates<kCandParts>>());
+    LSH_ALLOW((allow_whole_lds<k_logits_pass<float, 1>>()));
+    LSH_ALLOW((allow_whole_lds<k_logits_pass<float, 2>>()));
+    LSH_ALLOW((allow_whole_lds<k_logits_pass<float, 3>>()));
+    LSH_ALLOW((allow_whole_lds<k_logits_pass<uint16_t, 1>>()));
     LSH_ALLOW(allow_whole_lds<k_hit_rows>());
     LSH_ALLOW(allow_whole_lds<k_union_compact>());
     LSH_ALLOW(allow_whole_lds<k_part_bitmaps>());
@@ -1157,7 +1197,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
         parts = w.row_bitmaps;
     }
     bool selected = false;   // the step's tail already ran inside the fused kernel
-    bool wide = false;       // tile records of kWideN columns
+    bool wide = false;       // tile records of rec_groups columns
     int rec_groups = 0;      // tile records per hidden row, if not one per tile (launch_logits)
     if (fused) {
         // One launch per step: the last workgroup of each sentence also runs the selection
@@ -1225,8 +1265,8 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
         lsh_step_params rows = *sp;
         if (sp->full_vocab) { rows.S = 1; rows.B = sp->S * sp->B; }
         wide = takes_rows(t, sp);
-        if (wide && t->dtype == LSH_F32) launch_logits_rows<float>(cx, H_dev, rows.B, w);
-        else if (wide) launch_logits_rows<uint16_t>(cx, H_dev, rows.B, w);
+        if (wide && t->dtype == LSH_F32) rec_groups = launch_logits_rows<float>(cx, H_dev, rows.B, w);
+        else if (wide) rec_groups = launch_logits_rows<uint16_t>(cx, H_dev, rows.B, w);
         else if (t->dtype == LSH_F32) rec_groups = launch_logits<float>(cx, H_dev, &rows, cand, count, w, fold ? &un : nullptr);
         else launch_logits<uint16_t>(cx, H_dev, &rows, cand, count, w);
     }
@@ -1237,7 +1277,9 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
            sp->B, beam_scores_dev, w.lse, out_beam_dev, out_word_dev, out_score_dev,                   \
            fused ? std::max(0, t->option(kOptFusedTile, 0)) : 0, rec_groups)
         // (the fused kernels leave rich records, k_logits_estage one record for a group of tiles)
-        if (wide) LSH_SELECT(false, false, true);
+        if (wide && sp->B <= kSelWaves && t->V <= 1024 * rec_groups) LSH_SELECT(false, false, true, 16);   // (as many records as lists take)
+        else if (wide && sp->B > kSelWaves && sp->B <= 4 * kSelWaves && t->V <= 512 * rec_groups) LSH_SELECT(false, false, true, 64);
+        else if (wide) LSH_SELECT(false, false, true, 0);
         else if (rec_groups > 0) LSH_SELECT(false, true);
         else if (fused && sp->B <= kSelWaves) LSH_SELECT(true, false, false, 16);
         else if (fused) LSH_SELECT(true, false, false, 64);   // (of at most 32, by the rule; any number, by option)

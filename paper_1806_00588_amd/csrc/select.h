@@ -659,7 +659,7 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
 // LDS atomics: k_select 5.7 -> 4.4 us (8 x 5 beams, 140 tiles), 6.7 -> 5.1 (32 x 10), 10.0 -> 7.5 (64 x 10, 650 tiles); a step of 12 x 26
 // beams, d = 1096 bf16, V = 11600, 33.1 -> 29.6, of 7 x 55, d = 320, V = 7900, 38.5 -> 33.8.
 constexpr int kListOpen = kSelThreads / 16 * 4;   // tiles opened: four for every 16 lanes
-template <int LPR, bool SAME_KERNEL, int Q, typename REC>
+template <int LPR, bool SAME_KERNEL, bool WIDE, int Q, typename REC>
 __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], int ntiles, int B,
                                                  float* lse_out, const OpenSrc& open) {
     static_assert(LPR == kWave || LPR == 16, "");
@@ -730,6 +730,40 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     LSH_TRACE_ANY(2, 7);
     const int n_open = (int)sh.misc[5];
     if (n_open > kListOpen) return false;
+    if constexpr (WIDE) {   // 64 columns at a time, four consecutive ones per lane; all words, so that columns are ids
+        constexpr int U = 2, SWEEP = kSelThreads / 16;
+        const int parts = (open.tn + 63) >> 6, n_parts = n_open * parts;
+        for (int base = 0; base < n_parts; base += U * SWEEP) {   // (uniform)
+            float4 x[U];
+            int i[U], at[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = base + (tid >> 4) + u * SWEEP, jj = min(j, n_parts - 1), e = parts == 1 ? jj : jj / parts;
+                const uint32_t ent = sh.open_list[e];
+                const int in = (jj - e * parts) * 64 + 4 * (ln & 15), cc = (int)(ent & 0xFFFFFu) * open.tn + in;
+                i[u] = (int)(ent >> 20);
+                at[u] = j < n_parts && in < open.tn && cc < open.C ? cc : open.C;
+                x[u] = *reinterpret_cast<const float4*>(open.logits + (size_t)i[u] * open.cpitch + (at[u] < open.C ? cc : 0));
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float lsev = sh.lse[i[u]], bsv = sh.bs[i[u]], xs[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float sc = bsv + (xs[e] - lsev);
+                    const bool ok = at[u] + e < open.C && sc > -INFINITY && f32_sortable(sc + 0.0f) >= tau;
+                    const uint64_t bal = __ballot(ok);
+                    if (bal == 0ull) continue;   // (uniform)
+                    uint32_t first = 0;
+                    if (ln == 0) first = atomicAdd(&sh.misc[4], (uint32_t)__popcll(bal));
+                    const uint32_t pos = wave_read_lane(first, 0) + lanes_below(bal);
+                    if (ok && pos < (uint32_t)kSelListCap) sh.list[pos] = make_key(sc, ((uint32_t)i[u] << 24) | (uint32_t)(at[u] + e));
+                }
+            }
+        }
+        LSH_TRACE_ANY(2, 8);
+        return true;   // (more keys than the list holds: the caller sees)
+    }
     auto open_tiles = [&](auto in_flight) {
         constexpr int U = decltype(in_flight)::value;
         float x[U];
@@ -764,16 +798,18 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     LSH_TRACE_ANY(2, 8);
     return true;
 }
-// At most 16 tiles' records for a lane: 1024 tiles up to 16 beams, 256 beyond.  *C_out: the list's length.
-template <int LPR, bool SAME_KERNEL, typename REC>
+// At most 16 or 32 tiles' records for a lane: 1024 tiles up to 16 beams, 512 beyond.  *C_out: the list's length.  WIDE: records of
+// tile_forced columns.
+template <int LPR, bool SAME_KERNEL, bool WIDE, typename REC>
 __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* records, int64_t ppitch, int C_at,
                                             const int32_t* count, int V, int B, const float* beam_scores, float* lse_out,
                                             int tile_forced, const float* logits, int64_t cpitch, const int32_t* cand, int* C_out) {
     const int row = threadIdx.x / LPR, c = threadIdx.x & (LPR - 1);
     LSH_TRACE_ANY(2, 0);
     // (as in select_rich_small: four records per lane before the list's length is known, what it needs beyond after that)
-    constexpr int MOST = 2 * kSelBatch;
-    REC rec[MOST];
+    constexpr int MOST = LPR == kWave ? 2 * kSelBatch : 4 * kSelBatch;
+    if (C_at < 0 && !count) C_at = V;
+    REC rec[4];
     const REC* pr = records + ((size_t)s * B + min(row, B - 1)) * ppitch;
     float bsi = 0.f;
     if (row < B) {
@@ -781,15 +817,15 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
 #pragma unroll
         for (int q = 0; q < 4; ++q) rec[q] = load_record<SAME_KERNEL>(pr + min((int64_t)(c + q * LPR), ppitch - 1));
     }
-    const int C = C_at >= 0 ? C_at : (count ? count[s] : V);
-    const int tn = sizeof(REC) == sizeof(float4) ? select_tile_width(C, tile_forced, ppitch) : kTileN;
+    const int C = C_at >= 0 ? C_at : count[s];
+    const int tn = WIDE ? tile_forced : sizeof(REC) == sizeof(float4) ? select_tile_width(C, tile_forced, ppitch) : kTileN;
     const int ntiles = (C + tn - 1) / tn;
     *C_out = C;
     const OpenSrc open{logits + (size_t)s * B * cpitch, cpitch, cand ? cand + (size_t)s * V : nullptr, C, tn};
     if (ntiles == 0 || ntiles > MOST * LPR) return false;   // (uniform, like every return here)
     if (ntiles <= 4 * LPR) {
         REC few[4] = {rec[0], rec[1], rec[2], rec[3]};
-        return select_list_body<LPR, SAME_KERNEL, 4>(sh, s, bsi, few, ntiles, B, lse_out, open);
+        return select_list_body<LPR, SAME_KERNEL, WIDE, 4>(sh, s, bsi, few, ntiles, B, lse_out, open);
     }
     auto more = [&](auto upto) {
         constexpr int Q = decltype(upto)::value;
@@ -799,9 +835,11 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
             all[q] = q < 4 ? rec[q < 4 ? q : 0] : empty_record<REC>();
             if (q >= 4 && row < B && q * LPR < ntiles) all[q] = load_record<SAME_KERNEL>(pr + min((int64_t)(c + q * LPR), ppitch - 1));
         }
-        return select_list_body<LPR, SAME_KERNEL, Q>(sh, s, bsi, all, ntiles, B, lse_out, open);
+        return select_list_body<LPR, SAME_KERNEL, WIDE, Q>(sh, s, bsi, all, ntiles, B, lse_out, open);
     };
     if (ntiles <= kSelBatch * LPR) return more(std::integral_constant<int, kSelBatch>{});
+    if constexpr (LPR < kWave)
+        if (ntiles <= 2 * kSelBatch * LPR) return more(std::integral_constant<int, 2 * kSelBatch>{});
     return more(std::integral_constant<int, MOST>{});
 }
 
@@ -827,19 +865,23 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     bool listed = false;   // (uniform) sh.list has the keys that can win
     typedef typename std::conditional<RICH, float4, float2>::type REC;
     constexpr bool FEW = !RICH && (BEAMS == 16 || BEAMS < 0), MANY = BEAMS == 64 || BEAMS < 0;
-    if constexpr (!GROUPS && !WIDE && (FEW || MANY)) {
+    if constexpr (!GROUPS && (FEW || MANY)) {
         const bool few = FEW && B <= kSelWaves, many = MANY && B > kSelWaves && B <= 4 * kSelWaves;
         if (few || many) {
             int C_seen = C_known;
             const REC* recs = reinterpret_cast<const REC*>(records);
             if constexpr (FEW)
-                if (few) listed = select_list<kWave, SAME_KERNEL>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
-                                                                  tile_forced, logits, cpitch, cand, &C_seen);
+                if (few) listed = select_list<kWave, SAME_KERNEL, WIDE>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
+                                                                  WIDE ? rec_groups : tile_forced, logits, cpitch, cand, &C_seen);
             if constexpr (MANY)
-                if (many) listed = select_list<16, SAME_KERNEL>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
-                                                                tile_forced, logits, cpitch, cand, &C_seen);
+                if (many) listed = select_list<16, SAME_KERNEL, WIDE>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
+                                                                WIDE ? rec_groups : tile_forced, logits, cpitch, cand, &C_seen);
             C_known = C_seen;
             __syncthreads();
+            if (WIDE && sh.misc[4] > (uint32_t)kSelListCap) {   // (uniform)
+                listed = false;
+                __syncthreads();
+            }
             if (listed && sh.misc[4] <= (uint32_t)kWave) {
                 rank_by_ballots(sh, (int)sh.misc[4], false, B, (size_t)s * B, out_beam, out_word, out_score);
                 LSH_TRACE_ANY(2, 5);
@@ -879,7 +921,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     // candidates per tile: 16, what the fused kernel that wrote the records was told to use, or the
     // wide tiles of the kernels that serve the full vocabulary
     static_assert(!(WIDE && (RICH || GROUPS)), "wide records are plain pairs, one per wide tile");
-    const int tn = RICH ? select_tile_width(C, tile_forced, ppitch) : WIDE ? kWideN : 16;
+    const int tn = RICH ? select_tile_width(C, tile_forced, ppitch) : WIDE ? rec_groups : 16;   // (WIDE: its columns, a multiple of 16)
     const int ntiles = (C + tn - 1) / tn;
     // GROUPS: the records stand for groups of tiles (select_front_grouped; rec_groups = the
     // workgroups per sentence of the kernel that wrote them; at most 64 beams)
@@ -1258,18 +1300,19 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     const uint32_t n_open = sh.misc[5];
     if (listed) {
     } else if (WIDE && n_open <= (uint32_t)kSelOpenCap) {
-        // (a wide tile: four consecutive columns per lane, two sweeps in flight)
-        for (uint32_t g0 = (uint32_t)(tid >> 4); g0 < n_open; g0 += 2 * (kSelThreads / 16)) {
+        // (a wide tile: 64 columns at a time, four consecutive ones per lane, two sweeps in flight)
+        const uint32_t parts = (uint32_t)(tn + 63) >> 6, n_parts = n_open * parts;   // (4096 x 1024 at most)
+        for (uint32_t g0 = (uint32_t)(tid >> 4); g0 < n_parts; g0 += 2 * (kSelThreads / 16)) {
             float4 x[2];
             int iq[2], c[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const uint32_t j = g0 + u * (kSelThreads / 16);
-                const uint32_t ent = sh.open_list[min(j, n_open - 1)];
+                const uint32_t jj = min(j, n_parts - 1), at = parts == 1 ? jj : jj / parts, ent = sh.open_list[at];
                 iq[u] = (int)(ent >> 20);
-                const int cc = (int)(ent & 0xFFFFFu) * tn + 4 * (ln & 15);   // (the row pitch is a multiple of 64)
-                c[u] = j < n_open ? cc : C;
-                x[u] = *reinterpret_cast<const float4*>(lg + (size_t)iq[u] * cpitch + cc);
+                const int in = (int)(jj - at * parts) * 64 + 4 * (ln & 15), cc = (int)(ent & 0xFFFFFu) * tn + in;
+                c[u] = j < n_parts && in < tn && cc < C ? cc : C;
+                x[u] = *reinterpret_cast<const float4*>(lg + (size_t)iq[u] * cpitch + (c[u] < C ? cc : 0));   // (the row pitch is a multiple of 64)
             }
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
