@@ -2261,8 +2261,9 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
 // The same where the hidden rows fit in LDS whole, which is what most calls of few rows have: one workgroup per CU loads them once
 // and shares out the words, so that nothing but E passes through the CU's load path afterwards (k_logits_few's workgroups, of
 // 64 words each, read all hidden rows for every 256 KB of E), no barrier stands in the loop and every CU has the same to
-// do: 625 workgroups of V = 40000 were two on some CUs and three on others.  A wave has `rounds` times 16 words in a row, sixteen
-// chunks of every lane on their way, the next tile's while one is finished; every workgroup leaves ONE record per hidden row, for its
+// do: 625 workgroups of V = 40000 were two on some CUs and three on others.  A wave has `rounds` times 16 words in a row, eight to
+// sixteen chunks of every lane on their way (all sixteen always, no branch for rows of up to eight steps: 1 % faster for d = 1000, 2 to 9 %
+// slower for d = 99 to 176), the next tile's while one is finished; every workgroup leaves ONE record per hidden row, for its
 // 16 W rounds words, as the selection is bound by what one CU pulls in.  The sums are k_logits_few's, bit for bit.
 // us a step, k_logits_few and so: 12 rows, V = 40000, d = 1000 46.6, 42.5 (the pass over cold E 37.9 -> 35.7, selection 8.3 -> 6.2); 45
 // rows, V = 94357, d = 216 56, 45; 22 rows, V = 97522, d = 80 35, 26; 22 rows, V = 140258, d = 1016 155, 151; bf16: 4 rows, V = 129085,
