@@ -652,13 +652,13 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
 
 // The selection's first half with every row's records in registers, written out on its own for the same reason: the rows'
 // log-sum-exps, tau, the tiles that reach it and, their words' ids asked for beside the logits, the keys that do.  The list is in
-// sh.list, its length in sh.misc[4]; false (uniform): more tiles reach tau than the workgroup opens at once, and nothing is final.
+// sh.list, its length in sh.misc[4], which may be more than it holds; false (uniform): more tiles reach tau than the list of tiles
+// holds, and nothing is final.
 // LPR lanes per hidden row: 64, a wave, up to 16 beams (plain records; the log-sum-exps as in the general path, operation for
 // operation); 16 up to 64 beams, all rows at once (a wave for several rows, one after the other, spends most of its
 // instructions on reductions over 64 lanes).  Against the general path, which asks for a winner's id once it is known and ranks by
 // LDS atomics: k_select 5.7 -> 4.4 us (8 x 5 beams, 140 tiles), 6.7 -> 5.1 (32 x 10), 10.0 -> 7.5 (64 x 10, 650 tiles); a step of 12 x 26
 // beams, d = 1096 bf16, V = 11600, 33.1 -> 29.6, of 7 x 55, d = 320, V = 7900, 38.5 -> 33.8.
-constexpr int kListOpen = kSelThreads / 16 * 4;   // tiles opened: four for every 16 lanes
 template <int LPR, bool SAME_KERNEL, bool WIDE, int Q, typename REC>
 __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], int ntiles, int B,
                                                  float* lse_out, const OpenSrc& open) {
@@ -721,7 +721,7 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
             if (ln == 0) base = atomicAdd(&sh.misc[5], wave_read_lane(incl, kWave - 1));
             uint32_t pos = wave_read_lane(base, 0) + incl - n;
             for (uint32_t left = hits; left; left &= left - 1u, ++pos)
-                if (pos < (uint32_t)kListOpen) sh.open_list[pos] = ((uint32_t)row << 20) | (uint32_t)(c + (__ffs(left) - 1) * LPR);
+                if (pos < (uint32_t)kSelOpenCap) sh.open_list[pos] = ((uint32_t)row << 20) | (uint32_t)(c + (__ffs(left) - 1) * LPR);
         }
     }
     // (plain loads below: none of them may come from a cache line fetched before the other workgroups' stores)
@@ -729,7 +729,7 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     __syncthreads();
     LSH_TRACE_ANY(2, 7);
     const int n_open = (int)sh.misc[5];
-    if (n_open > kListOpen) return false;
+    if (n_open > kSelOpenCap) return false;
     if constexpr (WIDE) {   // 64 columns at a time, four consecutive ones per lane; all words, so that columns are ids
         constexpr int U = 2, SWEEP = kSelThreads / 16;
         const int parts = (open.tn + 63) >> 6, n_parts = n_open * parts;
@@ -764,7 +764,10 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
         LSH_TRACE_ANY(2, 8);
         return true;   // (more keys than the list holds: the caller sees)
     }
-    auto open_tiles = [&](auto in_flight) {
+    // Four tiles for every 16 lanes at a time.  Scores that lie close together (a soft softmax, ties) open several hundred; left to the
+    // general path from 257 on, which begins again, the selection after hit thresholds took 10.6 us for 3 x 17 beams, V = 12500, d = 96 (9.6
+    // without the list), 16.4 (15.6) for 3 x 40, V = 9700, d = 144.
+    auto open_tiles = [&](auto in_flight, int first) {
         constexpr int U = decltype(in_flight)::value;
         float x[U];
         int32_t id[U];
@@ -772,7 +775,7 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
         bool ok[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int j = (tid >> 4) + u * (kSelThreads / 16);
+            const int j = first + (tid >> 4) + u * (kSelThreads / 16);
             const uint32_t ent = sh.open_list[max(min(j, n_open - 1), 0)];
             i[u] = j < n_open ? (int)(ent >> 20) : 0;
             const int at = j < n_open ? (int)(ent & 0xFFFFFu) * open.tn + (ln & 15) : open.C;
@@ -789,12 +792,12 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
             uint32_t base = 0;
             if (ln == 0) base = atomicAdd(&sh.misc[4], (uint32_t)__popcll(bal));
             const uint32_t pos = wave_read_lane(base, 0) + lanes_below(bal);
-            static_assert(kListOpen * kTileN <= kSelListCap, "room for every column of every opened tile");
-            if (ok[u]) sh.list[pos] = make_key(sc, ((uint32_t)i[u] << 24) | (uint32_t)id[u]);
+            if (ok[u] && pos < (uint32_t)kSelListCap) sh.list[pos] = make_key(sc, ((uint32_t)i[u] << 24) | (uint32_t)id[u]);
         }
     };
-    if (n_open <= kSelThreads / 16) open_tiles(std::integral_constant<int, 1>{});
-    else open_tiles(std::integral_constant<int, 4>{});
+    if (n_open <= kSelThreads / 16) open_tiles(std::integral_constant<int, 1>{}, 0);
+    else
+        for (int first = 0; first < n_open; first += 4 * (kSelThreads / 16)) open_tiles(std::integral_constant<int, 4>{}, first);   // (uniform)
     LSH_TRACE_ANY(2, 8);
     return true;
 }
@@ -878,7 +881,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
                                                                 WIDE ? rec_groups : tile_forced, logits, cpitch, cand, &C_seen);
             C_known = C_seen;
             __syncthreads();
-            if (WIDE && sh.misc[4] > (uint32_t)kSelListCap) {   // (uniform)
+            if (listed && sh.misc[4] > (uint32_t)kSelListCap) {   // (uniform)
                 listed = false;
                 __syncthreads();
             }

@@ -1,12 +1,25 @@
 """The selection where its number of records per lane and of lanes per hidden row changes: lists of 64, 128, 256, 512 and 1024
 tiles and one word more, 1 to 65 beams; scores apart, tied by the hundred (more tiles than are opened at once, more keys than
-are ranked by ballot) and all the same (the exact select).  The list is all of V: every word is a top-frequent one."""
+are ranked by ballot) and all the same (the exact select).  The list is all of V: every word is a top-frequent one.  Of equal scores
+the lower beam comes first, then the lower word."""
 import numpy as np
 import pytest
 
 from gpu_harness import GpuCase, assert_close_logprobs, assert_topb_matches
 
 pytestmark = pytest.mark.gpu
+
+
+def assert_order_of_ties(gb, gw, gs, distinct):
+    """Word w has the embedding of word w % distinct, so that the logits of such words are equal bit for bit: equal scores in order of
+    beam and word, and of equal words of a beam the lowest."""
+    n = int((gb >= 0).sum())
+    for r in range(1, n):
+        if gs[r] == gs[r - 1]:
+            assert (gb[r - 1], gw[r - 1]) < (gb[r], gw[r]), r
+    have = set(zip(gb[:n].tolist(), gw[:n].tolist()))
+    for b, w in have:
+        assert w < distinct or (b, w - distinct) in have, (b, w)
 
 
 @pytest.mark.parametrize("V", [16, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 16384, 16385])
@@ -28,3 +41,22 @@ def test_records_per_lane(V, B):
             assert len(ref.cand) == V
             assert_close_logprobs(gc.tables.debug_logprobs(ws, sp, s, cap=V), ref)
             assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
+            assert_order_of_ties(gb[s], gw[s], gs[s], distinct)
+
+
+# tiles that reach the threshold, and keys: 200 of each; 257 to some thousand; as many as the lists hold; more than they hold
+@pytest.mark.parametrize("fused", [0, 1])
+@pytest.mark.parametrize("V,distinct,B", [(8000, 40, 1), (8000, 40, 16), (8000, 40, 17), (8000, 40, 64), (8000, 20, 10), (8000, 20, 32),
+                                          (4096, 1, 16), (8192, 2, 32), (16000, 4, 2), (16384, 16, 4)])
+def test_tied_rows(V, distinct, B, fused):
+    """Hidden rows and beam scores the same too: beam 0 has all results, the lowest copies of the best word, in order."""
+    rng = np.random.default_rng(V + B + distinct)
+    d = 16
+    perms = np.stack([rng.permutation(d)[:4] for _ in range(4)]).astype(np.int32)
+    E = rng.standard_normal((distinct, d)).astype(np.float32)[np.arange(V) % distinct]
+    gc = GpuCase(E, perms, np.arange(V, dtype=np.int32), 2)
+    gc.tables.set_options(fused=fused)
+    h = rng.standard_normal(d).astype(np.float32)
+    best = int(np.argmax(E[:distinct].astype(np.float64) @ h))
+    gb, gw, gs, _, _ = gc.step(np.tile(h, (B, 1)), np.full(B, -1.5, np.float32), 1, B)
+    assert np.all(gb == 0) and np.array_equal(gw[0], best + distinct * np.arange(B)) and np.all(gs == gs[0, 0])
