@@ -710,7 +710,7 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     }
     LSH_TRACE_ANY(2, 2);
     // the row's tiles that reach tau, one list reservation per wave
-    {
+    auto list_tiles = [&]() {
         uint32_t hits = 0;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
@@ -723,22 +723,37 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
             for (uint32_t left = hits; left; left &= left - 1u, ++pos)
                 if (pos < (uint32_t)kSelOpenCap) sh.open_list[pos] = ((uint32_t)row << 20) | (uint32_t)(c + (__ffs(left) - 1) * LPR);
         }
-    }
+    };
+    list_tiles();
     // (plain loads below: none of them may come from a cache line fetched before the other workgroups' stores)
     if constexpr (SAME_KERNEL) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     __syncthreads();
     LSH_TRACE_ANY(2, 7);
-    const int n_open = (int)sh.misc[5];
+    int n_open = (int)sh.misc[5];
+    // One row's own B-th best is a loose tau where other rows are close behind, and a record of several hundred words is dear to
+    // open: for more than two sweeps the B-th best of all rows' lanes is found and the tiles are listed again (16 rows of
+    // bf16 words, V = 98195, d = 112, records of 384 words: 47 -> 7.9 us; records of 64 words 13.1).
+    constexpr int U = 2, WIDE_SWEEP = kSelThreads / 16;   // (WIDE: parts in flight per 16 lanes, parts per sweep)
+    const int parts = (open.tn + 63) >> 6;
+    if constexpr (WIDE && LPR == kWave) {
+        if (n_open * parts > 2 * U * WIDE_SWEEP) {   // (uniform; at most 16 x 1024 tiles of 2^10 parts)
+            tau = max(tau, block_kth_largest_lb(best, B, &sh));   // (its first barrier: everybody has read n_open)
+            if (tid == 0) sh.misc[5] = 0;
+            __syncthreads();
+            list_tiles();
+            __syncthreads();
+            n_open = (int)sh.misc[5];
+        }
+    }
     if (n_open > kSelOpenCap) return false;
     if constexpr (WIDE) {   // 64 columns at a time, four consecutive ones per lane; all words, so that columns are ids
-        constexpr int U = 2, SWEEP = kSelThreads / 16;
-        const int parts = (open.tn + 63) >> 6, n_parts = n_open * parts;
-        for (int base = 0; base < n_parts; base += U * SWEEP) {   // (uniform)
+        const int n_parts = n_open * parts;
+        for (int base = 0; base < n_parts; base += U * WIDE_SWEEP) {   // (uniform)
             float4 x[U];
             int i[U], at[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                const int j = base + (tid >> 4) + u * SWEEP, jj = min(j, n_parts - 1), e = parts == 1 ? jj : jj / parts;
+                const int j = base + (tid >> 4) + u * WIDE_SWEEP, jj = min(j, n_parts - 1), e = parts == 1 ? jj : jj / parts;
                 const uint32_t ent = sh.open_list[e];
                 const int in = (jj - e * parts) * 64 + 4 * (ln & 15), cc = (int)(ent & 0xFFFFFu) * open.tn + in;
                 i[u] = (int)(ent >> 20);

@@ -132,3 +132,15 @@ def assert_topb_matches(gb, gw, gs, ref: Ref, bs, tol=TOL_F32):
             assert abs(mine - osc[r]) <= 2 * bound, (r, (b, w), (int(ob[r]), int(ow[r])), mine, osc[r])
     assert np.all(np.diff(gs[:n_valid].astype(np.float64)) <= 0)
     return sum(1 for r in range(n_valid) if (int(gb[r]), int(gw[r])) != (int(ob[r]), int(ow[r])))
+
+
+def assert_order_of_ties(gb, gw, gs, distinct):
+    """Word w has the embedding of word w % distinct, so that the logits of such words are equal bit for bit: equal scores in order of
+    beam and word, and of equal words of a beam the lowest."""
+    n = int((gb >= 0).sum())
+    for r in range(1, n):
+        if gs[r] == gs[r - 1]:
+            assert (gb[r - 1], gw[r - 1]) < (gb[r], gw[r]), r
+    have = set(zip(gb[:n].tolist(), gw[:n].tolist()))
+    for b, w in have:
+        assert w < distinct or (b, w - distinct) in have, (b, w)

@@ -5,21 +5,9 @@ the lower beam comes first, then the lower word."""
 import numpy as np
 import pytest
 
-from gpu_harness import GpuCase, assert_close_logprobs, assert_topb_matches
+from gpu_harness import GpuCase, assert_close_logprobs, assert_order_of_ties, assert_topb_matches
 
 pytestmark = pytest.mark.gpu
-
-
-def assert_order_of_ties(gb, gw, gs, distinct):
-    """Word w has the embedding of word w % distinct, so that the logits of such words are equal bit for bit: equal scores in order of
-    beam and word, and of equal words of a beam the lowest."""
-    n = int((gb >= 0).sum())
-    for r in range(1, n):
-        if gs[r] == gs[r - 1]:
-            assert (gb[r - 1], gw[r - 1]) < (gb[r], gw[r]), r
-    have = set(zip(gb[:n].tolist(), gw[:n].tolist()))
-    for b, w in have:
-        assert w < distinct or (b, w - distinct) in have, (b, w)
 
 
 @pytest.mark.parametrize("V", [16, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 16384, 16385])
