@@ -1278,12 +1278,15 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
            fused ? std::max(0, t->option(kOptFusedTile, 0)) : 0, rec_groups)
         // (the fused kernels leave rich records, k_logits_estage one record for a group of tiles)
         if (wide && sp->B <= kSelWaves && t->V <= 1024 * rec_groups) LSH_SELECT(false, false, true, 16);   // (as many records as lists take)
-        else if (wide && sp->B > kSelWaves && sp->B <= 4 * kSelWaves && t->V <= 512 * rec_groups) LSH_SELECT(false, false, true, 64);
+        else if (wide && sp->B > kSelWaves && sp->B <= 2 * kSelWaves && t->V <= 512 * rec_groups) LSH_SELECT(false, false, true, 32);
+        else if (wide && sp->B > 2 * kSelWaves && sp->B <= 4 * kSelWaves && t->V <= 512 * rec_groups) LSH_SELECT(false, false, true, 64);
         else if (wide) LSH_SELECT(false, false, true, 0);
         else if (rec_groups > 0) LSH_SELECT(false, true);
         else if (fused && sp->B <= kSelWaves) LSH_SELECT(true, false, false, 16);
-        else if (fused) LSH_SELECT(true, false, false, 64);   // (of at most 32, by the rule; any number, by option)
+        else if (fused && sp->B <= 2 * kSelWaves) LSH_SELECT(true, false, false, 32);
+        else if (fused) LSH_SELECT(true, false, false, 64);   // (by option, any number)
         else if (sp->B <= kSelWaves) LSH_SELECT(false, false, false, 16);
+        else if (sp->B <= 2 * kSelWaves) LSH_SELECT(false, false, false, 32);
         else if (sp->B <= 4 * kSelWaves) LSH_SELECT(false, false, false, 64);
         else LSH_SELECT(false, false, false, 0);
 #undef LSH_SELECT

@@ -655,14 +655,15 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
 // sh.list, its length in sh.misc[4], which may be more than it holds; false (uniform): more tiles reach tau than the list of tiles
 // holds, and nothing is final.
 // LPR lanes per hidden row: 64, a wave, up to 16 beams (plain records; the log-sum-exps as in the general path, operation for
-// operation); 16 up to 64 beams, all rows at once (a wave for several rows, one after the other, spends most of its
-// instructions on reductions over 64 lanes).  Against the general path, which asks for a winner's id once it is known and ranks by
+// operation); 32 up to 32 beams and 16 up to 64, all rows at once (a wave for several rows, one after the other, spends most of its
+// instructions on reductions over 64 lanes; with 16 lanes for each of 17 rows, 5 of the 16 waves had all the work: 250, 375 and
+// 500 tiles 6.3, 7.8 and 8.2 us so, 5.5, 6.5 and 6.8 with 32, 7.3, 7.8 and 7.9 by the general path).  Against the general path, which asks for a winner's id once it is known and ranks by
 // LDS atomics: k_select 5.7 -> 4.4 us (8 x 5 beams, 140 tiles), 6.7 -> 5.1 (32 x 10), 10.0 -> 7.5 (64 x 10, 650 tiles); a step of 12 x 26
 // beams, d = 1096 bf16, V = 11600, 33.1 -> 29.6, of 7 x 55, d = 320, V = 7900, 38.5 -> 33.8.
 template <int LPR, bool SAME_KERNEL, bool WIDE, int Q, typename REC>
 __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], int ntiles, int B,
                                                  float* lse_out, const OpenSrc& open) {
-    static_assert(LPR == kWave || LPR == 16, "");
+    static_assert(LPR == kWave || LPR == 32 || LPR == 16, "");
     const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
     const int row = tid / LPR, c = tid & (LPR - 1);
     const bool has_row = row < B;                      // (LPR = 64: uniform)
@@ -692,8 +693,10 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
         }
         float M, part;
         if constexpr (LPR == kWave) M = wave_max_f32(m); else M = row16_max(m);
+        if constexpr (LPR == 32) M = fmaxf(M, __shfl_xor(M, 16));
         const float mine = (m == -INFINITY) ? 0.f : sum * __expf(m - M);
         if constexpr (LPR == kWave) part = wave_sum_f32(mine); else part = row16_sum(mine);
+        if constexpr (LPR == 32) part += __shfl_xor(part, 16);
         lse = M + logf(part);
         if (c == 0) { lse_out[s * B + row] = lse; sh.lse[row] = lse; sh.bs[row] = bsi; }
         best = reaches(m, 0u) ? f32_sortable(bsi + (m - lse) + 0.0f) : 0u;
@@ -825,7 +828,7 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
     const int row = threadIdx.x / LPR, c = threadIdx.x & (LPR - 1);
     LSH_TRACE_ANY(2, 0);
     // (as in select_rich_small: four records per lane before the list's length is known, what it needs beyond after that)
-    constexpr int MOST = LPR == kWave ? 2 * kSelBatch : 4 * kSelBatch;
+    constexpr int MOST = LPR == 16 ? 4 * kSelBatch : 2 * kSelBatch;
     if (C_at < 0 && !count) C_at = V;
     REC rec[4];
     const REC* pr = records + ((size_t)s * B + min(row, B - 1)) * ppitch;
@@ -856,13 +859,13 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
         return select_list_body<LPR, SAME_KERNEL, WIDE, Q>(sh, s, bsi, all, ntiles, B, lse_out, open);
     };
     if (ntiles <= kSelBatch * LPR) return more(std::integral_constant<int, kSelBatch>{});
-    if constexpr (LPR < kWave)
+    if constexpr (MOST > 2 * kSelBatch)
         if (ntiles <= 2 * kSelBatch * LPR) return more(std::integral_constant<int, 2 * kSelBatch>{});
     return more(std::integral_constant<int, MOST>{});
 }
 
-// BEAMS: 16, 64: the sentence has at most 16, or 17 to 64; 0: more; -1: any number.  (A kernel holds the code for its own beams: 53 to
-// 60 KB instead of 83, each launch fetches what it runs of it anew.)
+// BEAMS: 16, 32, 64: the sentence has at most 16, 17 to 32, 33 to 64; 0: more; -1: any number.  (A kernel holds the code for its own
+// beams: 53 to 60 KB instead of 83, each launch fetches what it runs of it anew.)
 template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false, bool WIDE = false, int BEAMS = -1>
 __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const float* logits, int64_t cpitch,
                                                 const TileRecord* records, const int32_t* ids2, int64_t ppitch,
@@ -882,15 +885,19 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
     }
     bool listed = false;   // (uniform) sh.list has the keys that can win
     typedef typename std::conditional<RICH, float4, float2>::type REC;
-    constexpr bool FEW = !RICH && (BEAMS == 16 || BEAMS < 0), MANY = BEAMS == 64 || BEAMS < 0;
-    if constexpr (!GROUPS && (FEW || MANY)) {
-        const bool few = FEW && B <= kSelWaves, many = MANY && B > kSelWaves && B <= 4 * kSelWaves;
-        if (few || many) {
+    constexpr bool FEW = !RICH && (BEAMS == 16 || BEAMS < 0), SOME = BEAMS == 32 || BEAMS < 0, MANY = BEAMS == 64 || BEAMS < 0;
+    if constexpr (!GROUPS && (FEW || SOME || MANY)) {
+        const bool few = FEW && B <= kSelWaves, some = SOME && B > kSelWaves && B <= 2 * kSelWaves;
+        const bool many = MANY && B > 2 * kSelWaves && B <= 4 * kSelWaves;
+        if (few || some || many) {
             int C_seen = C_known;
             const REC* recs = reinterpret_cast<const REC*>(records);
             if constexpr (FEW)
                 if (few) listed = select_list<kWave, SAME_KERNEL, WIDE>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
                                                                   WIDE ? rec_groups : tile_forced, logits, cpitch, cand, &C_seen);
+            if constexpr (SOME)
+                if (some) listed = select_list<32, SAME_KERNEL, WIDE>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
+                                                                WIDE ? rec_groups : tile_forced, logits, cpitch, cand, &C_seen);
             if constexpr (MANY)
                 if (many) listed = select_list<16, SAME_KERNEL, WIDE>(sh, s, recs, ppitch, C_known, count, V, B, beam_scores, lse_out,
                                                                 WIDE ? rec_groups : tile_forced, logits, cpitch, cand, &C_seen);

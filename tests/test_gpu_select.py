@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("V", [16, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 16384, 16385])
-@pytest.mark.parametrize("B", [1, 16, 17, 40, 64, 65])
+@pytest.mark.parametrize("B", [1, 16, 17, 32, 33, 40, 64, 65])
 def test_records_per_lane(V, B):
     rng = np.random.default_rng(V + B)
     d, S = 16, 2
