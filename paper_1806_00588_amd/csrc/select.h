@@ -286,6 +286,16 @@ __device__ __forceinline__ float4 load_record(const float4* p) {
         return *p;
     }
 }
+// (max, sum exp) alone of either
+template <bool SAME_KERNEL, typename REC>
+__device__ __forceinline__ float2 load_pair(const REC* p) {
+    if constexpr (SAME_KERNEL) {
+        const unsigned long long a = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return make_float2(__uint_as_float((uint32_t)a), __uint_as_float((uint32_t)(a >> 32)));
+    } else {
+        return *reinterpret_cast<const float2*>(p);
+    }
+}
 template <bool SAME_KERNEL>
 __device__ __forceinline__ int32_t load_id2(const int32_t* p) {
     if constexpr (SAME_KERNEL) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -660,8 +670,11 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
 // 500 tiles 6.3, 7.8 and 8.2 us so, 5.5, 6.5 and 6.8 with 32, 7.3, 7.8 and 7.9 by the general path).  Against the general path, which asks for a winner's id once it is known and ranks by
 // LDS atomics: k_select 5.7 -> 4.4 us (8 x 5 beams, 140 tiles), 6.7 -> 5.1 (32 x 10), 10.0 -> 7.5 (64 x 10, 650 tiles); a step of 12 x 26
 // beams, d = 1096 bf16, V = 11600, 33.1 -> 29.6, of 7 x 55, d = 320, V = 7900, 38.5 -> 33.8.
-template <int LPR, bool SAME_KERNEL, bool WIDE, int Q, typename REC>
-__device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], int ntiles, int B,
+// LONG: more tiles than the lanes have registers for.  Their records are read twice, eight of a lane at a time and the next eight on
+// their way, the second time from this XCD's L2.  (Left to the general path such a list cost its first records for nothing: 25000
+// candidates, 8 beams, 10.7 us without lists, 11.5 then, 8.7 so; 12000, 20 beams, 10.0, 11.0, 9.4; 64 beams 24.7, 26.2, 19.5.)
+template <int LPR, bool SAME_KERNEL, bool WIDE, int Q, bool LONG, typename REC>
+__device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], const REC* pr, int ntiles, int B,
                                                  float* lse_out, const OpenSrc& open) {
     static_assert(LPR == kWave || LPR == 32 || LPR == 16, "");
     const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
@@ -674,6 +687,26 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     auto reaches = [&](float x, uint32_t least) {
         const float sc = bsi + (x - lse);
         return sc > -INFINITY && f32_sortable(sc + 0.0f) >= least;
+    };
+    auto for_the_rest = [&](auto use) {
+        if constexpr (LONG) {
+            constexpr int STEP = kSelBatch * LPR;
+            float2 now[kSelBatch], next[kSelBatch];
+            auto load = [&](float2 (&p)[kSelBatch], int t0) {
+#pragma unroll
+                for (int q = 0; q < kSelBatch; ++q) p[q] = load_pair<SAME_KERNEL>(pr + min(t0 + c + q * LPR, ntiles - 1));
+            };
+            load(now, Q * LPR);
+            for (int t0 = Q * LPR; t0 < ntiles; t0 += STEP) {   // (uniform)
+                load(next, t0 + STEP);
+#pragma unroll
+                for (int q = 0; q < kSelBatch; ++q)
+                    if (t0 + c + q * LPR >= ntiles) now[q] = empty_record<float2>();
+                use(now, t0);
+#pragma unroll
+                for (int q = 0; q < kSelBatch; ++q) now[q] = next[q];
+            }
+        }
     };
     if (has_row) {
         float m = -INFINITY, sum = 0.f;
@@ -691,6 +724,16 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
                 for (int q = q0; q < Q && q < q0 + kSelBatch; ++q) sum += rec[q].y * __expf(rec[q].x - m);   // padding: 0 * 0
             }
         }
+        for_the_rest([&](const float2 (&p)[kSelBatch], int) {
+            float bm = p[0].x;
+#pragma unroll
+            for (int q = 1; q < kSelBatch; ++q) bm = fmaxf(bm, p[q].x);
+            if (bm > m) { sum *= __expf(m - bm); m = bm; }
+            if (m != -INFINITY) {
+#pragma unroll
+                for (int q = 0; q < kSelBatch; ++q) sum += p[q].y * __expf(p[q].x - m);
+            }
+        });
         float M, part;
         if constexpr (LPR == kWave) M = wave_max_f32(m); else M = row16_max(m);
         if constexpr (LPR == 32) M = fmaxf(M, __shfl_xor(M, 16));
@@ -713,19 +756,28 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     }
     LSH_TRACE_ANY(2, 2);
     // the row's tiles that reach tau, one list reservation per wave
+    auto list_hits = [&](uint32_t hits, int t0) {   // bit q: tile t0 + c + q LPR of this lane's row
+        if (__ballot(hits != 0) == 0ull) return;   // (uniform)
+        const uint32_t n = (uint32_t)__popc(hits), incl = wave_incl_scan(n);
+        uint32_t base = 0;
+        if (ln == 0) base = atomicAdd(&sh.misc[5], wave_read_lane(incl, kWave - 1));
+        uint32_t pos = wave_read_lane(base, 0) + incl - n;
+        for (uint32_t left = hits; left; left &= left - 1u, ++pos)
+            if (pos < (uint32_t)kSelOpenCap) sh.open_list[pos] = ((uint32_t)row << 20) | (uint32_t)(t0 + c + (__ffs(left) - 1) * LPR);
+    };
     auto list_tiles = [&]() {
         uint32_t hits = 0;
 #pragma unroll
         for (int q = 0; q < Q; ++q)
             hits |= (has_row && c + q * LPR < ntiles && reaches(rec[q].x, tau)) ? 1u << q : 0u;
-        if (__ballot(hits != 0) != 0ull) {   // (uniform)
-            const uint32_t n = (uint32_t)__popc(hits), incl = wave_incl_scan(n);
-            uint32_t base = 0;
-            if (ln == 0) base = atomicAdd(&sh.misc[5], wave_read_lane(incl, kWave - 1));
-            uint32_t pos = wave_read_lane(base, 0) + incl - n;
-            for (uint32_t left = hits; left; left &= left - 1u, ++pos)
-                if (pos < (uint32_t)kSelOpenCap) sh.open_list[pos] = ((uint32_t)row << 20) | (uint32_t)(c + (__ffs(left) - 1) * LPR);
-        }
+        list_hits(hits, 0);
+        if (LONG && wv * (kWave / LPR) < B)   // (uniform)
+            for_the_rest([&](const float2 (&p)[kSelBatch], int t0) {
+                uint32_t more = 0;
+#pragma unroll
+                for (int q = 0; q < kSelBatch; ++q) more |= (has_row && reaches(p[q].x, tau)) ? 1u << q : 0u;   // (padding: -inf)
+                list_hits(more, t0);
+            });
     };
     list_tiles();
     // (plain loads below: none of them may come from a cache line fetched before the other workgroups' stores)
@@ -782,9 +834,8 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
         LSH_TRACE_ANY(2, 8);
         return true;   // (more keys than the list holds: the caller sees)
     }
-    // Four tiles for every 16 lanes at a time.  Scores that lie close together (a soft softmax, ties) open several hundred; left to the
-    // general path from 257 on, which begins again, the selection after hit thresholds took 10.6 us for 3 x 17 beams, V = 12500, d = 96 (9.6
-    // without the list), 16.4 (15.6) for 3 x 40, V = 9700, d = 144.
+    // Four tiles for every 16 lanes at a time.  Scores that lie close together (a soft softmax, ties) open several hundred: 20 beams, 8000
+    // candidates, hidden rows of length 0.5, 8.2 us; left to the general path from 257 tiles on, which begins again, 17.3 (8.9 alone).
     auto open_tiles = [&](auto in_flight, int first) {
         constexpr int U = decltype(in_flight)::value;
         float x[U];
@@ -819,8 +870,8 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     LSH_TRACE_ANY(2, 8);
     return true;
 }
-// At most 16 or 32 tiles' records for a lane: 1024 tiles up to 16 beams, 512 beyond.  *C_out: the list's length.  WIDE: records of
-// tile_forced columns.
+// Records in registers: 16 or 32 of a lane, 1024 tiles for at most 16 beams and 512 for more.  *C_out: the list's length.  WIDE: records
+// of tile_forced columns, no more than that.
 template <int LPR, bool SAME_KERNEL, bool WIDE, typename REC>
 __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* records, int64_t ppitch, int C_at,
                                             const int32_t* count, int V, int B, const float* beam_scores, float* lse_out,
@@ -843,12 +894,12 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
     const int ntiles = (C + tn - 1) / tn;
     *C_out = C;
     const OpenSrc open{logits + (size_t)s * B * cpitch, cpitch, cand ? cand + (size_t)s * V : nullptr, C, tn};
-    if (ntiles == 0 || ntiles > MOST * LPR) return false;   // (uniform, like every return here)
+    if (ntiles == 0 || (WIDE && ntiles > MOST * LPR)) return false;   // (uniform, like every return here)
     if (ntiles <= 4 * LPR) {
         REC few[4] = {rec[0], rec[1], rec[2], rec[3]};
-        return select_list_body<LPR, SAME_KERNEL, WIDE, 4>(sh, s, bsi, few, ntiles, B, lse_out, open);
+        return select_list_body<LPR, SAME_KERNEL, WIDE, 4, false>(sh, s, bsi, few, pr, ntiles, B, lse_out, open);
     }
-    auto more = [&](auto upto) {
+    auto more = [&](auto upto, auto and_longer) {
         constexpr int Q = decltype(upto)::value;
         REC all[Q];
 #pragma unroll
@@ -856,12 +907,14 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
             all[q] = q < 4 ? rec[q < 4 ? q : 0] : empty_record<REC>();
             if (q >= 4 && row < B && q * LPR < ntiles) all[q] = load_record<SAME_KERNEL>(pr + min((int64_t)(c + q * LPR), ppitch - 1));
         }
-        return select_list_body<LPR, SAME_KERNEL, WIDE, Q>(sh, s, bsi, all, ntiles, B, lse_out, open);
+        return select_list_body<LPR, SAME_KERNEL, WIDE, Q, decltype(and_longer)::value>(sh, s, bsi, all, pr, ntiles, B, lse_out, open);
     };
-    if (ntiles <= kSelBatch * LPR) return more(std::integral_constant<int, kSelBatch>{});
+    if (ntiles <= kSelBatch * LPR) return more(std::integral_constant<int, kSelBatch>{}, std::false_type{});
     if constexpr (MOST > 2 * kSelBatch)
-        if (ntiles <= 2 * kSelBatch * LPR) return more(std::integral_constant<int, 2 * kSelBatch>{});
-    return more(std::integral_constant<int, MOST>{});
+        if (ntiles <= 2 * kSelBatch * LPR) return more(std::integral_constant<int, 2 * kSelBatch>{}, std::false_type{});
+    if constexpr (!WIDE)
+        if (ntiles > MOST * LPR) return more(std::integral_constant<int, 2 * kSelBatch>{}, std::true_type{});
+    return more(std::integral_constant<int, MOST>{}, std::false_type{});
 }
 
 // BEAMS: 16, 32, 64: the sentence has at most 16, 17 to 32, 33 to 64; 0: more; -1: any number.  (A kernel holds the code for its own

@@ -1,5 +1,5 @@
 """The selection where its number of records per lane and of lanes per hidden row changes: lists of 64, 128, 256, 512 and 1024
-tiles and one word more, 1 to 65 beams; scores apart, tied by the hundred (more tiles than are opened at once, more keys than
+tiles and one word more, and of several times what fits in registers, 1 to 65 beams; scores apart, tied by the hundred (more tiles than are opened at once, more keys than
 are ranked by ballot) and all the same (the exact select).  The list is all of V: every word is a top-frequent one.  Of equal scores
 the lower beam comes first, then the lower word."""
 import numpy as np
@@ -10,7 +10,7 @@ from gpu_harness import GpuCase, assert_close_logprobs, assert_order_of_ties, as
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("V", [16, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 16384, 16385])
+@pytest.mark.parametrize("V", [16, 1024, 1025, 2048, 2049, 4096, 4097, 8193, 16384, 16385, 24577, 40003])
 @pytest.mark.parametrize("B", [1, 16, 17, 32, 33, 40, 64, 65])
 def test_records_per_lane(V, B):
     rng = np.random.default_rng(V + B)
