@@ -116,7 +116,7 @@ struct SelShared {
     uint32_t misc[8];
 };
 
-// A lower bound tau of the k-th largest of the workgroup's 1024 thread values (k in 1..1024)
+// A lower bound tau of the k-th largest of the workgroup's 1024 N thread values (k in 1..1024 N)
 // that at least k and at most k + kSelSlack values reach (more only if more than that are equal
 // in all resolved digits): radix descent, 8 bits per pass, on an LDS histogram.  A pass: clear
 // the 256 bins, every thread still matching the resolved prefix adds itself to its digit's bin
@@ -126,22 +126,26 @@ struct SelShared {
 // bin's lower edge.  Three barriers per pass and at most four passes, against one barrier per
 // bit for a bitwise descent.
 constexpr uint32_t kSelSlack = 8;
-__device__ __forceinline__ uint32_t block_kth_largest_lb(uint32_t v, int k, SelShared* sh) {
+template <int N>
+__device__ __forceinline__ uint32_t block_kth_largest_lb(const uint32_t (&v)[N], int k, SelShared* sh) {
     const int tid = threadIdx.x, ln = lane_id();
     uint32_t prefix = 0, mask = 0, remaining = (uint32_t)k;
     for (int shift = 24; shift >= 0; shift -= 8) {
         if (tid < 256) sh->hist[tid] = 0;
         __syncthreads();
-        const bool act = (v & mask) == prefix;
-        const uint32_t digit = (v >> shift) & 255u;
-        const uint64_t actm = __ballot(act);
-        if (actm) {
-            const int first = __ffsll((unsigned long long)actm) - 1;
-            const uint32_t d0 = wave_read_lane(digit, first);
-            if (__ballot(act && digit == d0) == actm) {
-                if (ln == first) atomicAdd(&sh->hist[d0], (uint32_t)__popcll(actm));
-            } else if (act) {
-                atomicAdd(&sh->hist[digit], 1u);
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const bool act = (v[j] & mask) == prefix;
+            const uint32_t digit = (v[j] >> shift) & 255u;
+            const uint64_t actm = __ballot(act);
+            if (actm) {
+                const int first = __ffsll((unsigned long long)actm) - 1;
+                const uint32_t d0 = wave_read_lane(digit, first);
+                if (__ballot(act && digit == d0) == actm) {
+                    if (ln == first) atomicAdd(&sh->hist[d0], (uint32_t)__popcll(actm));
+                } else if (act) {
+                    atomicAdd(&sh->hist[digit], 1u);
+                }
             }
         }
         __syncthreads();
@@ -171,6 +175,10 @@ __device__ __forceinline__ uint32_t block_kth_largest_lb(uint32_t v, int k, SelS
         if (cnt <= remaining + kSelSlack) break;
     }
     return prefix;
+}
+__device__ __forceinline__ uint32_t block_kth_largest_lb(uint32_t v, int k, SelShared* sh) {
+    const uint32_t one[1] = {v};
+    return block_kth_largest_lb(one, k, sh);
 }
 
 // Everything a sweep over the sentence's scores needs.
@@ -674,14 +682,20 @@ __device__ __forceinline__ bool select_rich_small(SelShared& sh, int s, const Ti
 // their way, the second time from this XCD's L2.  (Left to the general path such a list cost its first records for nothing: 25000
 // candidates, 8 beams, 10.7 us without lists, 11.5 then, 8.7 so; 12000, 20 beams, 10.0, 11.0, 9.4; 64 beams 24.7, 26.2, 19.5.)
 template <int LPR, bool SAME_KERNEL, bool WIDE, int Q, bool LONG, typename REC>
-__device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], const REC* pr, int ntiles, int B,
-                                                 float* lse_out, const OpenSrc& open) {
+__device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi, REC (&rec)[Q], const REC* records, int64_t ppitch,
+                                                 int ntiles, int B, float* lse_out, const OpenSrc& open) {
     static_assert(LPR == kWave || LPR == 32 || LPR == 16, "");
     const int tid = threadIdx.x, ln = lane_id(), wv = wave_id();
     const int row = tid / LPR, c = tid & (LPR - 1);
     const bool has_row = row < B;                      // (LPR = 64: uniform)
+    const REC* pr = records + ((size_t)s * B + min(row, B - 1)) * ppitch;
     if (tid == 0) { sh.misc[4] = 0; sh.misc[5] = 0; sh.misc[6] = 0; }
-    uint32_t best = 0, tau = 0;
+    // 64 maxima of every row, however many lanes it has: where one row has all the best scores and no more maxima than there are
+    // results, tau is another row's and the whole row is listed.  us a step, the general path, a maximum per lane and so, hidden rows of length 0.03:
+    // 2 x 30 beams, all of V = 14549, d = 80 bf16, 16.0, 25.3, 15.4; 3 x 40, all of V = 6755, 16.5, 25.5, 15.3; length 0.3: 2 x 62 of
+    // V = 67223, d = 480 bf16, 61, 84, 60.
+    constexpr int MAXIMA = kWave / LPR;                // of a lane, each over every MAXIMA-th record
+    uint32_t best[MAXIMA] = {}, tau = 0;
     float lse = 0.f;
     // (a NaN, of a row that holds one, reaches nothing: such a row has no results, the others have theirs)
     auto reaches = [&](float x, uint32_t least) {
@@ -709,15 +723,23 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
         }
     };
     if (has_row) {
-        float m = -INFINITY, sum = 0.f;
+        float m = -INFINITY, sum = 0.f, mx[MAXIMA];
+#pragma unroll
+        for (int j = 0; j < MAXIMA; ++j) mx[j] = -INFINITY;
+        auto all_max = [&]() {
+            float x = mx[0];
+#pragma unroll
+            for (int j = 1; j < MAXIMA; ++j) x = fmaxf(x, mx[j]);
+            return x;
+        };
 #pragma unroll
         for (int q0 = 0; q0 < Q; q0 += kSelBatch) {   // (the general path's batches)
-            float bm = -INFINITY;
 #pragma unroll
             for (int q = q0; q < Q && q < q0 + kSelBatch; ++q) {
                 if (c + q * LPR >= ntiles) rec[q] = empty_record<REC>();
-                bm = fmaxf(bm, rec[q].x);
+                mx[q % MAXIMA] = fmaxf(mx[q % MAXIMA], rec[q].x);
             }
+            const float bm = all_max();
             if (bm > m) { sum *= __expf(m - bm); m = bm; }
             if (m != -INFINITY) {
 #pragma unroll
@@ -725,9 +747,9 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
             }
         }
         for_the_rest([&](const float2 (&p)[kSelBatch], int) {
-            float bm = p[0].x;
 #pragma unroll
-            for (int q = 1; q < kSelBatch; ++q) bm = fmaxf(bm, p[q].x);
+            for (int q = 0; q < kSelBatch; ++q) mx[q % MAXIMA] = fmaxf(mx[q % MAXIMA], p[q].x);
+            const float bm = all_max();
             if (bm > m) { sum *= __expf(m - bm); m = bm; }
             if (m != -INFINITY) {
 #pragma unroll
@@ -742,11 +764,12 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
         if constexpr (LPR == 32) part += __shfl_xor(part, 16);
         lse = M + logf(part);
         if (c == 0) { lse_out[s * B + row] = lse; sh.lse[row] = lse; sh.bs[row] = bsi; }
-        best = reaches(m, 0u) ? f32_sortable(bsi + (m - lse) + 0.0f) : 0u;
+#pragma unroll
+        for (int j = 0; j < MAXIMA; ++j) best[j] = reaches(mx[j], 0u) ? f32_sortable(bsi + (mx[j] - lse) + 0.0f) : 0u;
     }
     LSH_TRACE_ANY(2, 1);
     if constexpr (LPR == kWave) {
-        const uint32_t kth = has_row ? wave_kth_largest_sort(best, B) : 0u;
+        const uint32_t kth = has_row ? wave_kth_largest_sort(best[0], B) : 0u;
         if (ln == 0) sh.wtau[wv] = kth;
         __syncthreads();
 #pragma unroll
@@ -785,20 +808,32 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     __syncthreads();
     LSH_TRACE_ANY(2, 7);
     int n_open = (int)sh.misc[5];
-    // One row's own B-th best is a loose tau where other rows are close behind, and a record of several hundred words is dear to
-    // open: for more than two sweeps the B-th best of all rows' lanes is found and the tiles are listed again (16 rows of
-    // bf16 words, V = 98195, d = 112, records of 384 words: 47 -> 7.9 us; records of 64 words 13.1).
+    // tau is still loose where a few of the lanes' maxima stand for most of the best tiles, and for up to 16 beams, one row's B-th best, where
+    // other rows are close behind.  For more than two sweeps (WIDE) or one (else) the listed tiles' maxima are read again, their B-th best is
+    // found and the tiles are listed anew (16 rows of bf16 words, V = 98195, d = 112, records of 384 words: 47 -> 7.9 us).
     constexpr int U = 2, WIDE_SWEEP = kSelThreads / 16;   // (WIDE: parts in flight per 16 lanes, parts per sweep)
-    const int parts = (open.tn + 63) >> 6;
-    if constexpr (WIDE && LPR == kWave) {
-        if (n_open * parts > 2 * U * WIDE_SWEEP) {   // (uniform; at most 16 x 1024 tiles of 2^10 parts)
-            tau = max(tau, block_kth_largest_lb(best, B, &sh));   // (its first barrier: everybody has read n_open)
-            if (tid == 0) sh.misc[5] = 0;
-            __syncthreads();
-            list_tiles();
-            __syncthreads();
-            n_open = (int)sh.misc[5];
+    const int parts = WIDE ? (open.tn + 63) >> 6 : 1;
+    if (n_open * parts > 4 * WIDE_SWEEP) {   // (uniform; at most 2^15 tiles of 2^10 parts, 2^23 of one)
+        constexpr int PER = kSelOpenCap / kSelThreads;
+        float2 p[PER];
+        uint32_t mine = 0;
+        int of[PER];
+        const int n = min(n_open, kSelOpenCap);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            const uint32_t ent = sh.open_list[min(tid + k * kSelThreads, n - 1)];
+            of[k] = (int)(ent >> 20);
+            p[k] = load_pair<SAME_KERNEL>(records + ((size_t)s * B + of[k]) * ppitch + (ent & 0xFFFFFu));
         }
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            if (tid + k * kSelThreads < n) mine = max(mine, f32_sortable(sh.bs[of[k]] + (p[k].x - sh.lse[of[k]]) + 0.0f));
+        tau = max(tau, block_kth_largest_lb(mine, B, &sh));   // (its first barrier: everybody has read n_open and the list)
+        if (tid == 0) sh.misc[5] = 0;
+        __syncthreads();
+        list_tiles();
+        __syncthreads();
+        n_open = (int)sh.misc[5];
     }
     if (n_open > kSelOpenCap) return false;
     if constexpr (WIDE) {   // 64 columns at a time, four consecutive ones per lane; all words, so that columns are ids
@@ -897,7 +932,7 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
     if (ntiles == 0 || (WIDE && ntiles > MOST * LPR)) return false;   // (uniform, like every return here)
     if (ntiles <= 4 * LPR) {
         REC few[4] = {rec[0], rec[1], rec[2], rec[3]};
-        return select_list_body<LPR, SAME_KERNEL, WIDE, 4, false>(sh, s, bsi, few, pr, ntiles, B, lse_out, open);
+        return select_list_body<LPR, SAME_KERNEL, WIDE, 4, false>(sh, s, bsi, few, records, ppitch, ntiles, B, lse_out, open);
     }
     auto more = [&](auto upto, auto and_longer) {
         constexpr int Q = decltype(upto)::value;
@@ -907,7 +942,7 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
             all[q] = q < 4 ? rec[q < 4 ? q : 0] : empty_record<REC>();
             if (q >= 4 && row < B && q * LPR < ntiles) all[q] = load_record<SAME_KERNEL>(pr + min((int64_t)(c + q * LPR), ppitch - 1));
         }
-        return select_list_body<LPR, SAME_KERNEL, WIDE, Q, decltype(and_longer)::value>(sh, s, bsi, all, pr, ntiles, B, lse_out, open);
+        return select_list_body<LPR, SAME_KERNEL, WIDE, Q, decltype(and_longer)::value>(sh, s, bsi, all, records, ppitch, ntiles, B, lse_out, open);
     };
     if (ntiles <= kSelBatch * LPR) return more(std::integral_constant<int, kSelBatch>{}, std::false_type{});
     if constexpr (MOST > 2 * kSelBatch)

@@ -1,6 +1,6 @@
 """The selection where its number of records per lane and of lanes per hidden row changes: lists of 64, 128, 256, 512 and 1024
-tiles and one word more, and of several times what fits in registers, 1 to 65 beams; scores apart, tied by the hundred (more tiles than are opened at once, more keys than
-are ranked by ballot) and all the same (the exact select).  The list is all of V: every word is a top-frequent one.  Of equal scores
+tiles and one word more, and of several times what fits in registers, 1 to 65 beams; scores apart, close together, tied by the hundred
+(more tiles than are opened at once, more keys than are ranked by ballot) and all the same (the exact select).  The list is all of V: every word is a top-frequent one.  Of equal scores
 the lower beam comes first, then the lower word."""
 import numpy as np
 import pytest
@@ -30,6 +30,27 @@ def test_records_per_lane(V, B):
             assert_close_logprobs(gc.tables.debug_logprobs(ws, sp, s, cap=V), ref)
             assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
             assert_order_of_ties(gb[s], gw[s], gs[s], distinct)
+
+
+# 2000 words: no more tiles than are opened at once for any threshold; then some hundred to several thousand (more than are listed)
+# reach a row's or the lanes' threshold, and the listed ones' own is found.  The first beam far ahead: all results are of one row.
+@pytest.mark.parametrize("full", [False, True])
+@pytest.mark.parametrize("V", [2000, 8193, 16384, 40003])
+@pytest.mark.parametrize("B", [2, 16, 17, 32, 33, 50, 64])
+def test_close_scores(V, B, full):
+    rng = np.random.default_rng(V + B)
+    d, S = 16, 2
+    perms = np.stack([rng.permutation(d)[:4] for _ in range(4)]).astype(np.int32)
+    gc = GpuCase(rng.standard_normal((V, d)).astype(np.float32), perms, np.arange(V, dtype=np.int32), 2)
+    gc.tables.set_options(fused=0)
+    H = (0.05 * rng.standard_normal((S * B, d))).astype(np.float32)
+    for bs in (-np.sort(rng.random(S * B)).astype(np.float32) * 0.05, np.where(np.arange(S * B) % B == 0, 0, -9).astype(np.float32)):
+        gb, gw, gs, sp, ws = gc.step(H, bs, S, B, full_vocab=full)
+        for s in range(S):
+            rows = slice(s * B, (s + 1) * B)
+            ref = gc.oracle_sentence(H[rows], bs[rows], B, full_vocab=full)
+            assert_close_logprobs(gc.tables.debug_logprobs(ws, sp, s, cap=V), ref)
+            assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
 
 
 # tiles that reach the threshold, and keys: 200 of each; 257 to some thousand; as many as the lists hold; more than they hold
