@@ -691,10 +691,12 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     const REC* pr = records + ((size_t)s * B + min(row, B - 1)) * ppitch;
     if (tid == 0) { sh.misc[4] = 0; sh.misc[5] = 0; sh.misc[6] = 0; }
     // 64 maxima of every row, however many lanes it has: where one row has all the best scores and no more maxima than there are
-    // results, tau is another row's and the whole row is listed.  us a step, the general path, a maximum per lane and so, hidden rows of length 0.03:
-    // 2 x 30 beams, all of V = 14549, d = 80 bf16, 16.0, 25.3, 15.4; 3 x 40, all of V = 6755, 16.5, 25.5, 15.3; length 0.3: 2 x 62 of
-    // V = 67223, d = 480 bf16, 61, 84, 60.
-    constexpr int MAXIMA = kWave / LPR;                // of a lane, each over every MAXIMA-th record
+    // results, tau is another row's and the whole row is listed.  us a step, the general path, a maximum per lane and so, hidden rows of length
+    // 0.03: 2 x 30 beams, all of V = 14549, d = 80 bf16, 16.0, 25.3, 15.4; 3 x 40, all of V = 6755, 16.5, 25.5, 15.3; length 0.3: 2 x 62 of
+    // V = 67223, d = 480 bf16, 61, 84, 60.  Rows of at most 128 tiles are soon opened, and four maxima 1 us more (one sentence of 53 beams,
+    // all of V = 1324, scores apart: 10.2 -> 11.8): the second look below sees to them.
+    constexpr bool SHORT = LPR < kWave && Q * LPR <= 128;
+    constexpr int MAXIMA = SHORT ? 1 : kWave / LPR;    // of a lane, each over every MAXIMA-th record
     uint32_t best[MAXIMA] = {}, tau = 0;
     float lse = 0.f;
     // (a NaN, of a row that holds one, reaches nothing: such a row has no results, the others have theirs)
@@ -809,11 +811,13 @@ __device__ __forceinline__ bool select_list_body(SelShared& sh, int s, float bsi
     LSH_TRACE_ANY(2, 7);
     int n_open = (int)sh.misc[5];
     // tau is still loose where a few of the lanes' maxima stand for most of the best tiles, and for up to 16 beams, one row's B-th best, where
-    // other rows are close behind.  For more than two sweeps (WIDE) or one (else) the listed tiles' maxima are read again, their B-th best is
-    // found and the tiles are listed anew (16 rows of bf16 words, V = 98195, d = 112, records of 384 words: 47 -> 7.9 us).
+    // other rows are close behind.  For more than two sweeps (WIDE) or one (else), of SHORT rows for many more tiles than results, the
+    // listed tiles' maxima are read again, their B-th best is found and the tiles are listed anew (16 rows of bf16 words, V = 98195,
+    // d = 112, records of 384 words: 47 -> 7.9 us; SHORT: 2 x 31 beams, all of V = 5951, length 0.03, 20.8 -> 14).
     constexpr int U = 2, WIDE_SWEEP = kSelThreads / 16;   // (WIDE: parts in flight per 16 lanes, parts per sweep)
     const int parts = WIDE ? (open.tn + 63) >> 6 : 1;
-    if (n_open * parts > 4 * WIDE_SWEEP) {   // (uniform; at most 2^15 tiles of 2^10 parts, 2^23 of one)
+    const int soon = !SHORT ? 4 * WIDE_SWEEP : WIDE ? max(WIDE_SWEEP, B + 24) : 2 * B + 32;
+    if (n_open * parts > soon) {   // (uniform; at most 2^15 tiles of 2^10 parts, 2^24 of one)
         constexpr int PER = kSelOpenCap / kSelThreads;
         float2 p[PER];
         uint32_t mine = 0;
