@@ -8,6 +8,7 @@
 namespace lshbeam {
 
 constexpr int kWave = 64;
+constexpr size_t kMaxDynLds = 160 * 1024 - 1024;   // LDS that a kernel may ask for at launch
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 __device__ __forceinline__ int wave_id() { return threadIdx.x >> 6; }

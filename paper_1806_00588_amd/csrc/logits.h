@@ -2279,6 +2279,48 @@ template <typename ET> __host__ __device__ inline int pass_pitch(int d) {   // e
 template <typename ET> __host__ __device__ inline size_t pass_lds_bytes(int MT, int d) {
     return (size_t)few_planes<ET>() * MT * kTileM * pass_pitch<ET>(d) * sizeof(ET) + (size_t)kPassWaves * MT * kTileM * sizeof(float2);
 }
+template <typename ET> constexpr int pass_most_tiles() { return sizeof(ET) == 2 ? 1 : 3; }   // (row groups; two of bf16 words, V = 191422, d = 912: 134 us, k_logits_few 119)
+// Waves of a workgroup and how many times 16 words for each: the least that 256 workgroups have in all, and of those the most waves;
+// eight at least where there is work for them (d = 1200, V = 59224, 15 rows: three times with five waves 72 us a step, k_logits_few 68).
+// waves = 0: k_logits_few has the call (B: beams of a sentence; ld: elements).  The lines are drawn through 1489 (fp32) and 1530
+// (bf16) shapes of d = 16 to 1536, V = 8200 to 250000, both kernels measured on each; numbers are means of a step so over one of k_logits_few.
+//   fp32, more than 16 words for a wave: 0.52 to 0.94, but 1.03 where nine waves at most have more than 2 MB.  16 words for nine waves or
+//   more 0.95.  With fewer waves (V <= 32768) k_logits_few's several small workgroups on a CU are as fast: 1.02 on average up to d = 128 and 1.06
+//   with four waves; but 0.95 where its blocks of 128 values are nearly a third padding, 0.94 for rows of one or two whole lines of 128 bytes
+//   and five waves, 0.97 for one row group of long rows (d >= 600; d > 128 with five waves) and 0.95 for three.  Rows of two to four whole blocks 1.08.
+//   bf16, whose three planes of hidden rows stand in front of half the bytes: 1.1 to 1.4 for V < 70000, but 0.93 for long rows of
+//   few words, where k_logits_few is a chain of blocks in two workgroups per CU.  From 33 times 16 words for a workgroup on 0.89; from 19 on 0.95 for d >= 144 and
+//   0.92 with more than eight beams (the selection reads 64 words' records), else 1.1; 17 and 18 for d >= 600 0.94, else 1.1.
+struct PassPlan { int waves, rounds; };
+template <typename ET>
+inline PassPlan pass_plan(int R, int B, int V, int d, int64_t ld) {
+    constexpr PassPlan no{0, 0};
+    const int groups = (R + kTileM - 1) / kTileM;
+    if (groups > pass_most_tiles<ET>() || pass_lds_bytes<ET>(groups, d) > kMaxDynLds || ld * (int64_t)sizeof(ET) >= (int64_t)1 << 27) return no;
+    const int64_t tiles = (V + kTileN - 1) / kTileN;
+    PassPlan p = no;
+    for (int W = tiles >= 8 * 256 ? 8 : 4; W <= kPassWaves; ++W) {
+        const int rounds = (int)((tiles + 256 * W - 1) / (256 * W));
+        if (!p.waves || W * rounds <= p.waves * p.rounds) p = {W, rounds};
+    }
+    const int each = p.waves * p.rounds;                                        // times 16 words, a workgroup
+    const int64_t bytes = (int64_t)each * kTileN * d * (int64_t)sizeof(ET);     // of its words
+    bool pays;
+    if (sizeof(ET) == 2) {
+        pays = each >= 33 || (each >= 19 && (d >= 144 || B > 8)) || (each >= 17 && d >= 600) ||
+               (each == 5 && d >= 900);
+    } else if (p.rounds <= 2 && d % kFewK == 0 && d > kFewK && d <= 4 * kFewK) {
+        pays = false;
+    } else if (p.rounds >= 2 || p.waves >= 9) {
+        pays = p.waves > 9 || bytes <= (int64_t)2 << 20;
+    } else {
+        const int padded = (d + kFewK - 1) / kFewK * kFewK;
+        const bool lines = d <= 64 && ld % 32 == 0, more_waves = p.waves >= 5;
+        pays = (d > kFewK && 5 * padded >= 7 * d) || (more_waves && lines) || (groups == 1 && (d >= 600 || (more_waves && d > kFewK))) ||
+               (groups == 3 && more_waves && (d <= 64 || d > kFewK));
+    }
+    return pays ? p : no;
+}
 template <typename ET, int MT>
 __global__ void __launch_bounds__(kPassWaves * kWave)
 k_logits_pass(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int R, int V, int rounds,

@@ -63,7 +63,6 @@ hipError_t scratch_of_device(int dev, void** out) {
 
 constexpr int kMaxV = 1 << 24;
 constexpr int kMaxB = 256;
-constexpr size_t kMaxDynLds = 160 * 1024 - 1024;
 constexpr int kTicketSlots = 256;   // workspaces per handle that can take the one-launch plan
 constexpr int kTicketBlock = 64;    // counters per workspace = sentences of a fused step at most
 
@@ -621,37 +620,17 @@ bool takes_rows(const lsh_tables* t, const lsh_step_params* sp) {   // (an optio
            t->opt[kOptLogitsHlds] == kAuto && t->opt[kOptHldsRows] == kAuto && t->opt[kOptLogitsGrid] == kAuto &&
            t->option(kOptLogitsPlanes, 1) != 0;
 }
-// Waves of a workgroup of k_logits_pass and how many times 16 words for each: the least that 256 workgroups have in all, and of
-// those the most waves; eight at least where there is work for them (d = 1200, V = 59224, 15 rows: three times with five waves 72 us a
-// step, k_logits_few 68, so 64).
-struct PassPlan { int waves, rounds; };
-inline PassPlan pass_plan(int V) {
-    const int64_t tiles = (V + kTileN - 1) / kTileN;
-    PassPlan best{0, 0};
-    for (int W = tiles >= 8 * 256 ? 8 : 4; W <= kPassWaves; ++W) {
-        const int rounds = (int)((tiles + 256 * W - 1) / (256 * W));
-        if (!best.waves || W * rounds <= best.waves * best.rounds) best = {W, rounds};
-    }
-    return best;
-}
 // Returns the words a record is for.
 template <typename ET>
-int launch_logits_rows(const StepCtx& cx, const float* H, int R, const Workspace& w) {
+int launch_logits_rows(const StepCtx& cx, const float* H, int R, int B, const Workspace& w) {
     const lsh_tables* t = cx.t;
     const int tiles = (R + kTileM - 1) / kTileM;
     constexpr int WF = sizeof(ET) == 2 ? 4 : 2, FEW = sizeof(ET) == 2 ? 2 : 3;
-    // Not where a workgroup's words are hardly more than the hidden rows it has to load first (us a step, so and k_logits_few; bytes
-    // of a workgroup's words over those of the hidden rows: d = 528, V = 6443, 35 rows, 1.3, 26.1 / 23.2; d = 168 bf16, V = 16122, 24, 0.7,
-    // 15.4 / 13.3; d = 160, V = 9866, 20, 2.0, 14.5 / 14.1; d = 80 bf16, V = 43245, 24, 1.8, 15.8 / 16.6; d = 153, V = 7365, 24, 2.0, 14.9 /
-    // 16.0; d = 312, V = 94945, 3, 24, 37 / 40; d = 216, V = 94357, 45, 8, 45 / 56; d = 88, V = 160617, 6, 40, 22 / 31).  Nor of bf16 words with
-    // 6 to 11 times 16 for a workgroup, whose rows are a burst and no stream (d = 520, V = 31623, 2 rows, 19.1 / 16.6; d = 296, V = 25204,
-    // 15.7 / 13.9; but d = 440, V = 9605, 12.3 / 12.9, d = 304, V = 84695, 22.3 / 25.2, d = 1448, V = 189305, 131 / 140).
-    const PassPlan p = pass_plan(t->V);
-    const int words = p.waves * p.rounds * kTileN;
-    const size_t lds = pass_lds_bytes<ET>(tiles, t->d);
-    constexpr int PASS = sizeof(ET) == 2 ? 1 : 3;   // (row groups; two of bf16 words, V = 191422, d = 912: 134 us, 119)
-    if (tiles <= PASS && lds <= kMaxDynLds && t->ld * (int64_t)sizeof(ET) < (int64_t)1 << 27 &&
-        2.0 * words * t->d * sizeof(ET) >= 3.0 * lds && (sizeof(ET) == 4 || p.waves * p.rounds <= 5 || p.waves * p.rounds > 11)) {
+    const PassPlan p = pass_plan<ET>(R, B, t->V, t->d, t->ld);
+    if (p.waves) {
+        constexpr int PASS = pass_most_tiles<ET>();
+        const int words = p.waves * p.rounds * kTileN;
+        const size_t lds = pass_lds_bytes<ET>(tiles, t->d);
         const dim3 grid((unsigned)((t->V + words - 1) / words)), block(p.waves * kWave);
 #define LSH_PASS(MTV)                                                                                                \
     launch(cx, 1, k_logits_pass<ET, MTV>, grid, block, lds, (const ET*)t->E, t->ld, t->d, H, R, t->V, \
@@ -1265,8 +1244,8 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
         lsh_step_params rows = *sp;
         if (sp->full_vocab) { rows.S = 1; rows.B = sp->S * sp->B; }
         wide = takes_rows(t, sp);
-        if (wide && t->dtype == LSH_F32) rec_groups = launch_logits_rows<float>(cx, H_dev, rows.B, w);
-        else if (wide) rec_groups = launch_logits_rows<uint16_t>(cx, H_dev, rows.B, w);
+        if (wide && t->dtype == LSH_F32) rec_groups = launch_logits_rows<float>(cx, H_dev, rows.B, sp->B, w);
+        else if (wide) rec_groups = launch_logits_rows<uint16_t>(cx, H_dev, rows.B, sp->B, w);
         else if (t->dtype == LSH_F32) rec_groups = launch_logits<float>(cx, H_dev, &rows, cand, count, w, fold ? &un : nullptr);
         else launch_logits<uint16_t>(cx, H_dev, &rows, cand, count, w);
     }

@@ -29,7 +29,7 @@ static int failures = 0;
         }                                                                 \
     } while (0)
 
-constexpr size_t kLdsLimit = 160 * 1024 - 1024;   // what the host allows a kernel to ask for
+constexpr size_t kLdsLimit = kMaxDynLds;   // what the host allows a kernel to ask for
 
 static void check_workspace(int S, int B, int V, bool full) {
     char* base = reinterpret_cast<char*>((uintptr_t)1 << 40);   // never dereferenced
@@ -298,7 +298,32 @@ static void check_reports() {
     CHECK(r.take() == hipSuccess && r.place == 1, "place %d", r.place);
 }
 
-int main() {
+// "bytes of an element, hidden rows, beams, V, d, pitch" from stdin: waves and rounds of k_logits_pass, 0 0 where k_logits_few has the call.
+static int print_pass_plans() {
+    int size, R, B, V, d;
+    long long ld;
+    while (std::scanf("%d %d %d %d %d %lld", &size, &R, &B, &V, &d, &ld) == 6) {
+        const PassPlan p = size == 2 ? pass_plan<uint16_t>(R, B, V, d, ld) : pass_plan<float>(R, B, V, d, ld);
+        std::printf("%d %d\n", p.waves, p.rounds);
+    }
+    return 0;
+}
+
+// Every word has its wave and round, at most 256 workgroups, the operands in LDS and 32-bit offsets.
+template <typename ET>
+static void check_pass(int R, int V, int d, int64_t ld) {
+    const PassPlan p = pass_plan<ET>(R, std::min(R, 12), V, d, ld);
+    if (!p.waves) return;
+    const int tiles = (V + kTileN - 1) / kTileN, groups = (R + kTileM - 1) / kTileM;
+    const int64_t words = (int64_t)p.waves * p.rounds * kTileN;
+    CHECK(p.waves >= 4 && p.waves <= kPassWaves && words * 256 >= V, "R=%d V=%d d=%d", R, V, d);
+    CHECK((int64_t)p.waves * p.rounds <= (tiles + 255) / 256 + 4 * p.rounds, "R=%d V=%d d=%d", R, V, d);
+    CHECK(groups <= pass_most_tiles<ET>() && pass_lds_bytes<ET>(groups, d) <= kLdsLimit && pass_pitch<ET>(d) >= d, "R=%d V=%d d=%d", R, V, d);
+    CHECK((kTileN - 1) * ld * (int64_t)sizeof(ET) + d * (int64_t)sizeof(ET) < (int64_t)1 << 31, "R=%d V=%d d=%d", R, V, d);
+}
+
+int main(int argc, char**) {
+    if (argc > 1) return print_pass_plans();
     check_reports();
     check_small_div_margin();
     check_nth_set_bit();
@@ -326,6 +351,13 @@ int main() {
     for (int S : {1, 32, 64, 4096})
         for (int rows : {1, 10, 16, 32})
             for (int d : {8, 50, 1000, 1024, 1026, 4099}) check_hlds(S, rows, d);
+    for (int R : {1, 16, 17, 32, 33, 48, 49})
+        for (int V = 8200; V < 600000; V += V / 37)
+            for (int d : {8, 16, 255, 256, 600, 1000, 1536, 4000})
+                for (int64_t ld : {(int64_t)d, (int64_t)d + 3, (int64_t)1 << 24, (int64_t)1 << 26}) {
+                    check_pass<float>(R, V, d, ld);
+                    check_pass<uint16_t>(R, V, d, ld);
+                }
     check_stream();
     check_xcd_tiles();
     check_xcd_runs();

@@ -16,6 +16,11 @@ _BOTH = ("fp32", "bf16")
 _DRIVERS = {
     "rows": (4, 20, 9000, True, {}, _HIDDEN, _BOTH),
     "few": (1, 12, 9000, True, {}, _HIDDEN, _BOTH),
+    "few, two row groups": (2, 12, 9000, True, {}, _HIDDEN, _BOTH),
+    "few, three row groups": (4, 12, 9000, True, {}, _HIDDEN, ("fp32",)),
+    "pass": (1, 12, 78000, True, {}, _HIDDEN, _BOTH),
+    "pass, two row groups": (2, 12, 33000, True, {}, _HIDDEN, ("fp32",)),
+    "pass, three row groups": (4, 11, 33000, True, {}, _HIDDEN, ("fp32",)),
     "stream": (9, 5, 1200, False, {}, (24, 200, 203), _BOTH),
     "stream, two row groups": (9, 20, 1200, False, {}, (200, 203), _BOTH),
     "stream, four parts": (9, 3, 1200, False, {}, (1540,), ("bf16",)),

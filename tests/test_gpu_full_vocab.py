@@ -47,7 +47,7 @@ def _logits(gc, H, S, B):
 
 @pytest.mark.parametrize("n", [1, 2, 4, 16, 0], ids=lambda n: "%d" % n if n else "all")
 @pytest.mark.parametrize("case", [("rows", 9000, 5, 16, False), ("rows", 9000, 5, 16, True), ("few", 9000, 2, 12, False),
-                                  ("few", 9000, 2, 12, True)],
+                                  ("few", 9000, 2, 12, True), ("pass", 33000, 1, 12, False), ("pass", 78000, 1, 12, True)],
                          ids=lambda c: "%s-%s" % (c[0], "bf16" if c[4] else "fp32"))
 def test_logits_are_as_near_as_fp32_sums(case, n):
     """Logits with n products that are not zero (0: all) against fp64, beside a chain of fused multiply-adds in fp32.

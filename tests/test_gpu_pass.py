@@ -1,6 +1,6 @@
-"""All words, a few hidden rows: every split of the words over waves and rounds (one wave of 16 words to several rounds of twelve), rows
-of less than a step, of a ring of steps and one more element, rows that end inside a chunk, one to three groups of hidden rows,
-pitched rows of E."""
+"""All words, a few hidden rows (k_logits_pass): splits of the words over four to twelve waves and one to five rounds, rows of less than a
+step of 64 bytes, of one, of a ring of 16 steps, one element less and one more, rows that end inside a chunk, one to three groups of
+hidden rows, pitched rows of E.  That the calls are this kernel's is checked with the other plans (test_host_plans.py)."""
 import numpy as np
 import pytest
 
@@ -9,18 +9,30 @@ from gpu_harness import GpuCase, assert_close_logprobs, assert_order_of_ties, as
 
 pytestmark = pytest.mark.gpu
 
+# type, V, d, pitch, S, B, waves of a workgroup, times 16 words for each
+SHAPES = [
+    ("fp32", 57345, 8, 11, 1, 1, 8, 2), ("fp32", 66001, 16, 19, 1, 16, 9, 2), ("fp32", 34000, 19, 22, 1, 16, 9, 1),
+    ("fp32", 8225, 150, 153, 2, 8, 4, 1), ("fp32", 12289, 257, 260, 1, 17, 4, 1), ("fp32", 17001, 255, 258, 1, 5, 5, 1),
+    ("fp32", 22003, 32, 64, 3, 5, 6, 1), ("fp32", 26001, 300, 303, 1, 48, 7, 1), ("fp32", 31000, 601, 604, 1, 12, 8, 1),
+    ("fp32", 33001, 1000, 1000, 1, 12, 9, 1), ("fp32", 38000, 48, 51, 2, 20, 10, 1), ("fp32", 44003, 100, 103, 1, 3, 11, 1),
+    ("fp32", 48001, 641, 644, 3, 11, 12, 1), ("fp32", 75001, 33, 36, 4, 4, 10, 2), ("fp32", 86003, 20, 23, 1, 31, 11, 2),
+    ("fp32", 93001, 64, 64, 1, 48, 12, 2), ("fp32", 100003, 256, 259, 2, 2, 9, 3), ("fp32", 137003, 17, 20, 1, 7, 12, 3),
+    ("fp32", 125003, 9, 12, 1, 20, 8, 4), ("fp32", 200003, 16, 16, 1, 2, 10, 5),
+    ("bf16", 140001, 24, 27, 1, 1, 12, 3), ("bf16", 150001, 32, 32, 2, 8, 10, 4), ("bf16", 200003, 33, 36, 1, 16, 10, 5),
+    ("bf16", 100003, 513, 516, 3, 5, 9, 3), ("bf16", 80001, 512, 512, 1, 12, 10, 2), ("bf16", 90003, 511, 514, 2, 3, 11, 2),
+    ("bf16", 70001, 601, 604, 1, 3, 9, 2), ("bf16", 90003, 40, 43, 1, 12, 11, 2), ("bf16", 17003, 1001, 1004, 1, 7, 5, 1),
+    ("bf16", 125003, 150, 150, 4, 4, 8, 4),
+]
 
-@pytest.mark.parametrize("ty", ["fp32", "bf16"])
-@pytest.mark.parametrize("V,d,S,B", [(8209, 8, 1, 1), (8210, 19, 1, 16), (8225, 255, 2, 8), (16385, 256, 1, 5), (12289, 257, 1, 17),
-                                     (9001, 513, 3, 16), (36881, 64, 1, 16), (49153, 100, 1, 3), (100003, 33, 4, 4), (20011, 1000, 1, 12),
-                                     (70001, 48, 1, 48), (40001, 641, 3, 13)])
-def test_all_words_few_rows(V, d, S, B, ty):
+
+@pytest.mark.parametrize("ty,V,d,pitch,S,B,waves,rounds", SHAPES)
+def test_all_words_few_rows(ty, V, d, pitch, S, B, waves, rounds):
     rng = np.random.default_rng(V + d + B)
     E = (rng.standard_normal((V, d)) / np.sqrt(d)).astype(np.float32)
     if ty == "bf16":
         E = workloads.f32_to_bf16_bits(E)
     perms = np.stack([rng.permutation(d)[:4] for _ in range(2)]).astype(np.int32)
-    pitched = np.zeros((V, d + 3), E.dtype)
+    pitched = np.zeros((V, pitch), E.dtype)
     pitched[:, :d] = E
     gc = GpuCase(E, perms, np.arange(4, dtype=np.int32), 2, E_dev=to_dev(pitched)[:, :d])
     H = (4.0 * rng.standard_normal((S * B, d))).astype(np.float32)
@@ -34,8 +46,8 @@ def test_all_words_few_rows(V, d, S, B, ty):
         assert_topb_matches(gb[s], gw[s], gs[s], ref, bs[rows])
 
 
-# Records of 256 and 384 words (k_logits_pass) and of 64 (k_logits_few; 64 rows: k_logits_rows): a few tiles opened, more than two
-# sweeps (the threshold is found again), more keys than the list holds and more tiles than its list (the general path).
+# Records of 256 and 352 words (k_logits_pass; of bf16 words 9 to 16 beams) and of 64 (k_logits_few; 64 rows: k_logits_rows): a few tiles
+# opened, more than two sweeps (the threshold is found again), more keys than the list holds and more tiles than its list (the general path).
 @pytest.mark.parametrize("V,d,ty", [(50003, 64, "fp32"), (90001, 64, "bf16"), (20011, 16, "fp32")])
 @pytest.mark.parametrize("distinct", [1, 40, 400, 2000])
 @pytest.mark.parametrize("B", [1, 12, 16, 17, 40, 64])
