@@ -16,9 +16,9 @@
 // memory scan by lane 0 of each warp.  With t = 1 only "hit at least once" matters, so L
 // collapses to one bit per word per sentence; V bits fit in LDS (25 KB at V = 200k), the marks
 // are idempotent LDS atomic ORs, and compaction is a popcount + wave prefix sum.  Unequal span
-// lengths (the paper's warp-divergence problem) are handled by flattening: span lengths are
-// prefix-summed across all (row, band) pairs and the flat element range is dealt to threads
-// evenly, each finding its span by binary search.
+// lengths (the paper's warp-divergence problem) are handled by flattening: the spans' numbers of
+// aligned groups of four ids are prefix-summed across all (row, band) pairs and the flat range of
+// groups is dealt to threads evenly, each finding its span by binary search.
 #pragma once
 #include <type_traits>
 #include "device_utils.h"
@@ -337,9 +337,9 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
     const int bmw = bitmap_words_padded(V);
     float* stage = reinterpret_cast<float*>(bm + bmw);     // the chunk's hidden rows [rows][d]
     int32_t* lperms = reinterpret_cast<int32_t*>(bm + bmw + stage_words);  // perms [P][K]
-    uint32_t* p_start = bm + bmw + stage_words + P * K;    // span start of each pair in the chunk
-    uint32_t* p_band = p_start + kCandThreads;             // its band
-    uint32_t* p_pref = p_band + kCandThreads;              // exclusive prefix of span lengths
+    uint32_t* p_group = bm + bmw + stage_words + P * K;    // first group of four ids of each pair's span in the chunk
+    uint32_t* p_len = p_group + kCandThreads;              // its length | misalignment << 30
+    uint32_t* p_pref = p_len + kCandThreads;               // exclusive prefix of the spans' numbers of groups
     uint32_t* wsum = p_pref + kCandThreads;                // scan scratch (>= kCandWaves + 1)
 
     const int tid = threadIdx.x;
@@ -482,8 +482,8 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
         {
             const size_t flat = (size_t)w * V + start;
             const uint32_t mis = (uint32_t)flat & 3u;
-            p_start[tid] = (uint32_t)(flat >> 2);               // first group (W * V < 2^34)
-            p_band[tid] = len | (mis << 30);                    // (len <= V <= 2^24)
+            p_group[tid] = (uint32_t)(flat >> 2);               // first group (W * V < 2^34)
+            p_len[tid] = len | (mis << 30);                     // (len <= V <= 2^24)
             if (((len + mis + 3) >> 2) > (uint32_t)(subs * kDirectGroups)) wsum[kDirectFlag] = 1u;
         }
         __syncthreads();  // codes[] aliases p_pref
@@ -491,7 +491,7 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
         LSH_TRACE_WG(2);
         if (wsum[kDirectFlag] == 0u) {   // (uniform)
             const int sub = small_div(tid, npairs), pair = tid - sub * npairs;
-            const uint32_t g0 = p_start[pair], lm = p_band[pair];
+            const uint32_t g0 = p_group[pair], lm = p_len[pair];
             const uint32_t slen = lm & 0x3FFFFFFFu, smis = lm >> 30;
             const uint32_t ngroups = (sub < subs && slen) ? (slen + smis + 3) >> 2 : 0u;
             const int4* __restrict__ words4 = reinterpret_cast<const int4*>(words);
@@ -543,11 +543,11 @@ __device__ __forceinline__ void build_presence_bitmap(const CandArgs& a, int s, 
 #pragma unroll
                 for (int q = 0; q < NW; ++q) {
                     e[q] -= p_pref[l[q]];   // (the group's number in its span)
-                    grp[q] = words4[(size_t)p_start[l[q]] + e[q]];
+                    grp[q] = words4[(size_t)p_group[l[q]] + e[q]];
                 }
 #pragma unroll
                 for (int q = 0; q < NW; ++q) {
-                    const uint32_t lm = p_band[l[q]], smis = lm >> 30, send = smis + (lm & 0x3FFFFFFFu), p0 = 4u * e[q];
+                    const uint32_t lm = p_len[l[q]], smis = lm >> 30, send = smis + (lm & 0x3FFFFFFFu), p0 = 4u * e[q];
                     const int32_t ids[4] = {grp[q].x, grp[q].y, grp[q].z, grp[q].w};
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
