@@ -419,8 +419,10 @@ __device__ __forceinline__ uint32_t select_front_grouped(SelShared& sh, int s, c
     return tau;
 }
 
-// Ranks the mr <= 64 keys of sh.list by ballot: in every wave lane j holds entry j, wave w ranks entries 4w .. 4w + 3; the
-// B best are written out.  verdict: sh.misc[6] is set if one of them is marked (a second largest) in sh.open_list.
+// Ranks the mr <= 64 keys of sh.list by ballot ("which keys are larger?"; real keys are never 0): in every wave lane j holds
+// entry j, wave w ranks entries 4w .. 4w + 3; the B best are written out.  verdict: sh.misc[6] is set if one of them is marked (a
+// second largest) in sh.open_list.  (One wave ranking all keys by a loop of lane broadcasts took 0.6 us; all 16 waves ranking all keys,
+// to save the barrier, was slower still: they share four instruction issuers.)
 __device__ __forceinline__ void rank_by_ballots(SelShared& sh, int mr, bool verdict, int B, size_t o0, int32_t* out_beam,
                                                 int32_t* out_word, float* out_score) {
     const int ln = lane_id(), wv = wave_id();
@@ -1284,42 +1286,9 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
         LSH_TRACE_ANY(2, 6);
         const int mr = (int)sh.misc[4];
         if (mr <= kWave) {
-            // The usual case, a few dozen keys: in every wave lane j holds key j, and wave w ranks
-            // keys 4w .. 4w + 3, each by one ballot ("which keys are larger?").  A key among the
-            // B best is written out at once; if one of them is a second largest, the verdict word
-            // sends everybody on to the general path, which writes all B results again.  (One
-            // wave ranking all keys by a loop of lane broadcasts took 0.6 us; all 16 waves ranking
-            // all keys, to save the barrier, was slower still: they share four instruction issuers.)
-            {
-                const uint64_t mine = (ln < mr) ? sh.list[ln] : 0ull;   // (real keys are never 0)
-                const uint32_t second = (ln < mr && sh.open_list[ln] != 0u) ? 1u : 0u;
-                const uint32_t lo = (uint32_t)mine, hi = (uint32_t)(mine >> 32);
-                uint64_t key = 0;
-                uint32_t rank = 0xFFFFFFFFu, sec = 0;
-#pragma unroll
-                for (int q = 0; q < kWave / kSelWaves; ++q) {
-                    const int e = wv * (kWave / kSelWaves) + q;   // (wave-uniform)
-                    if (e >= mr) break;
-                    const uint64_t ke = ((uint64_t)wave_read_lane(hi, e) << 32) | wave_read_lane(lo, e);
-                    const uint32_t r = (uint32_t)__popcll(__ballot(mine > ke));
-                    const uint32_t se = wave_read_lane(second, e);
-                    if (ln == q) { key = ke; rank = r; sec = se; }
-                }
-                if (rank < (uint32_t)B) {   // (lanes 0..3 at most)
-                    if (sec) sh.misc[6] = 1u;
-                    const size_t o = o0 + rank;
-                    const float score = key_value(key);
-                    const uint32_t idx = key_index(key);
-                    const bool none = score == -INFINITY || score != score;
-                    out_beam[o] = none ? -1 : (int)(idx >> 24);
-                    out_word[o] = none ? -1 : (int)(idx & 0xFFFFFFu);
-                    out_score[o] = none ? -INFINITY : score;
-                }
-                if (wv == 0)
-                    for (int e = ln + min(mr, B); e < B; e += kWave) {
-                        out_beam[o0 + e] = -1; out_word[o0 + e] = -1; out_score[o0 + e] = -INFINITY;
-                    }
-            }
+            // The usual case, a few dozen keys.  A key among the B best is written out at once; if one of them is a
+            // second largest, the verdict word sends everybody on to the general path, which writes all B results again.
+            rank_by_ballots(sh, mr, true, B, o0, out_beam, out_word, out_score);
             LSH_TRACE_ANY(2, 4);
             __syncthreads();
             if (sh.misc[6] == 0u) {
