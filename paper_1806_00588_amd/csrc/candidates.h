@@ -670,9 +670,11 @@ __host__ __device__ inline size_t union_compact_lds_words(int V) {
 
 // Requires W <= kCandThreads.  Where the chip has CUs for them and the bitmap is long, kCandParts workgroups per sentence: each makes
 // the whole bitmap, which takes no longer beside the others, and writes a part of the list.  One workgroup alone is bound by
-// instruction issue there: with V = 200000 a wave expands seven times 64 words (4.8 us).  With the walk by groups, 64 x 10 beams,
-// V = 200000: 18.9 -> 13.1 us; a step of 13 x 6, V = 111500: 20.3 -> 18.8.  V = 40000, two times 64 words: 8 x 5 7.9, 7.9; 32 x 10 8.2, 7.9;
-// 5 x 17, V = 39989, 8.8, 9.3.  Workgroup p S + s is part p of sentence s, so that the parts of a sentence are mostly on one XCD.
+// instruction issue there: with V = 200000 a wave expands seven times 64 words (4.8 us).  The line is at three times 64 words for a wave.
+// us a step with four less one with one (d = 256 bf16, 1000 to 2000 top-frequent words), V = 40000, 50000 / 65600, 80000, 100000, 200000:
+// 8 x 5 beams +0.2, +0.1 / -0.1, -0.3, -0.4, -1.3; 5 x 17 -0.1, -0.2 / -0.5, -0.7, -0.8, -1.8; 32 x 10 +0.1, +0.1 / -0.5, -0.7, -0.7, -1.7;
+// 13 x 6 0.0, -0.2 / -0.5, -0.7, -0.8, -1.6; 64 x 10 -0.6, -0.5 / -0.6, -0.9, -1.0, -2.4.  Workgroup p S + s is part p of sentence s, so that the
+// parts of a sentence are on one XCD where S is a multiple of 8.
 constexpr int kCandParts = 4;
 inline bool candidates_split(int S, int V) { return S * kCandParts <= 256 && V > 2 * kCandWaves * kWave * 32; }
 template <int PARTS>

@@ -26,7 +26,8 @@
 //                    pieces, hidden rows in registers (up to 32 beams at a time);
 //   k_logits_estage  33..64 beams, fp32 rows of 513 to 1024 values: the same change of places, all
 //                    beams at once;
-//   k_logits_few, k_logits_rows   the full vocabulary: all hidden rows of the call against all words;
+//   k_logits_pass, k_logits_few, k_logits_rows   the full vocabulary: all hidden rows of the call against all words (up to 48
+//                    rows that fit in LDS and suit its split; up to 48; more);
 //   k_logits_hlds    one wave per tile, the sentence's hidden rows staged in LDS: rows of more than 2048
 //                    values, and where an option names it;
 //   k_logits<WAVES>  a workgroup of 16 or 4 waves per (tile, row group), k split over the waves: rows
@@ -1812,8 +1813,8 @@ k_logits_estage(const float* __restrict__ E, int64_t ld, int d, const float* __r
 
 // Full vocabulary: every hidden row meets every word, so sentences do not matter and the contraction
 // is one matrix product, R rows x V words.  (Taken sentence by sentence each of them gathered all of
-// E again: 32 sentences x 160 MB.)  Few rows: bound by the one pass over E (k_logits_few); many: by the
-// matrix pipe.
+// E again: 32 sentences x 160 MB.)  Few rows: bound by the one pass over E (k_logits_few, k_logits_pass
+// below); many: by the matrix pipe.
 //
 // A workgroup of four waves makes MT * 16 rows x 64 WF words, in blocks of 32 k, on bf16 matrix instructions.  The
 // hidden rows pass through LDS (double-buffered, as three bf16 planes, split on the way in).  bf16 words meet
@@ -2265,7 +2266,7 @@ k_logits_few(const ET* __restrict__ E, int64_t ld, int d, const float* __restric
 // sixteen chunks of every lane on their way (all sixteen always, no branch for rows of up to eight steps: 1 % faster for d = 1000, 2 to 9 %
 // slower for d = 99 to 176), the next tile's while one is finished; every workgroup leaves ONE record per hidden row, for its
 // 16 W rounds words, as the selection is bound by what one CU pulls in.  The sums are k_logits_few's, bit for bit.
-// us a step, k_logits_few and so: 12 rows, V = 40000, d = 1000 46.6, 42.5 (the pass over cold E 37.9 -> 35.7, selection 8.3 -> 6.2); 45
+// us a step, k_logits_few and so: 12 rows, V = 40000, d = 1000 46.7, 41.9 (the pass over cold E 37.6, 36.4, selection 8.4, 5.5); 45
 // rows, V = 94357, d = 216 56, 45; 22 rows, V = 97522, d = 80 35, 26; 22 rows, V = 140258, d = 1016 155, 151; bf16: 4 rows, V = 129085,
 // d = 336 32, 29.
 constexpr int kPassRing = 16;    // chunks of a lane on their way
@@ -2380,7 +2381,7 @@ k_logits_pass(const ET* __restrict__ E, int64_t ld, int d, const float* __restri
             *reinterpret_cast<float4*>(sm + r * row_bytes + 16 * q) = make_float4(x[0], x[1], x[2], x[3]);
         }
         zero_rows(sm);
-        if (works) wait_vmem<RING / 2>(); else wait_vmem<0>();   // (as many loads of words at least are younger)
+        if (works) wait_vmem<RING / 2>(); else wait_vmem<0>();   // (as many loads of words at least are younger; waves that fill the padding have waited there for all of theirs)
     } else {
         constexpr int AT_ONCE = 8;   // (loads behind the words' would wait for those)
         bool begun = false;

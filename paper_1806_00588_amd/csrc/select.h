@@ -959,7 +959,7 @@ __device__ __forceinline__ bool select_list(SelShared& sh, int s, const REC* rec
 }
 
 // BEAMS: 16, 32, 64: the sentence has at most 16, 17 to 32, 33 to 64; 0: more; -1: any number.  (A kernel holds the code for its own
-// beams: 53 to 60 KB instead of 83, each launch fetches what it runs of it anew.)
+// beams, 34 to 122 KB, as each launch fetches what it runs of it anew.)
 template <bool RICH, bool SAME_KERNEL = false, bool GROUPS = false, bool WIDE = false, int BEAMS = -1>
 __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const float* logits, int64_t cpitch,
                                                 const TileRecord* records, const int32_t* ids2, int64_t ppitch,
