@@ -1145,6 +1145,26 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     char* ring = sm + Lds::kRed + q * (RING * NI * 1024);
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
+    const int nks = (d + KSTEP - 1) / KSTEP, nst = (nks + 3) >> 2, k0 = q * nst * KSTEP;   // steps of a wave's quarter
+    // bf16 words: the hidden rows of the sentence known in front come to the ring, where nothing is yet, while the count and the
+    // candidates are on their way: as many units (part p of row group m is number m PARTS + p) as it holds.  (A lane that loads its
+    // operand itself, two pieces of 16 bytes, has every 16 lanes touch 16 rows twice.  64 x 10 beams, V = 200000, d = 1024: 150.2 ->
+    // 148.2 us a step; eight steps of 8 x 5, V = 40000: 190.8 -> 190.3.  With fp32 words, one piece: 32 x 10, d = 1000, 44.7 -> 45.1.)
+    // Pieces of a row lie as those of the words do, in blocks of PPH.
+    constexpr int SB = VEC / 4, PPH = 4 * KSN * SB < 16 ? 4 * KSN * SB : 16, SUBS = 4 * KSN * SB / PPH, SHH = PPH == 4 ? 2 : PPH == 8 ? 1 : 0;
+    constexpr int HELD = RING * NI / (KSN * SB), STAGED = EVEN || !BF ? 0 : HELD < MT * PARTS ? HELD : MT * PARTS;
+    auto stage_hidden = [&](int at_s) __attribute__((always_inline)) {
+        const float* hb = H + ((size_t)at_s * B + row0) * d;
+        const int lrow = ln / PPH, lp = ln % PPH;
+#pragma unroll
+        for (int i = 0; i < STAGED * SUBS; ++i)
+#pragma unroll
+            for (int j = 0; j < PPH / 4; ++j) {
+                const int part = i / SUBS % PARTS, row = j * (kWave / PPH) + lrow, p = i % SUBS * PPH + (lp ^ (row >> SHH));
+                const int k = p / SB < 4 * (nst - part * KSN) ? k0 + part * (KSN * KSTEP) + p / SB * VEC : d;
+                load_to_lds16(hb + (size_t)min(i / SUBS / PARTS * kTileM + row, Bg - 1) * d + min(k, d - VEC) + 4 * (p % SB), ring + i * (PPH * 256) + j * 1024);
+            }
+    };
     LSH_TRACE_WG(8);
     // Who takes what.  A workgroup has one sentence, and all or some of the sentence's workgroups take turns:
     //   per > 0: workgroup i of a sentence's `per` on this XCD has the tiles i, i + per, ... of those of the XCD (XcdTiles);
@@ -1155,13 +1175,16 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     int s = 0, C = 0;
     TileRun run{};
     uint32_t seg = 0, seg_end = 0, wg_end = 0;
+    bool moved = EVEN;                                                        // (uniform) the hidden rows in the ring are not these
     auto count_of = [&](int at) { const int n = count ? count[min(at, S - 1)] : V; return at < S ? n : 0; };
     if constexpr (!EVEN) {
         const uint32_t s0 = __builtin_amdgcn_readfirstlane(per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs));
-        // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
-        const char* hb = reinterpret_cast<const char*>(H + ((size_t)s0 * B + row0) * d);
-        if (q > 0)
-            for (uint32_t at = (tid - kWave) * 128u; at < (uint32_t)(Bg * d) * 4u; at += 192u * 128u) load_to_lds4(hb + at, ring);
+        if constexpr (STAGED > 0) stage_hidden((int)s0);
+        else {   // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
+            const char* hb = reinterpret_cast<const char*>(H + ((size_t)s0 * B + row0) * d);
+            if (q > 0)
+                for (uint32_t at = (tid - kWave) * 128u; at < (uint32_t)(Bg * d) * 4u; at += 192u * 128u) load_to_lds4(hb + at, ring);
+        }
         const StreamDeal dl = deal_equally(count, V, (uint32_t)S, (uint32_t)wgs, (uint32_t)per, (uint32_t)shared, xcd, bx, s0);
         s = (int)dl.s; C = (int)dl.C; run = uniform(dl.run);
     } else {   // (every wave for itself, to the same result)
@@ -1184,7 +1207,6 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         wg_end = min(total, seg + per_wg);
         if (seg == wg_end) return;
     }
-    const int nks = (d + KSTEP - 1) / KSTEP, nst = (nks + 3) >> 2, k0 = q * nst * KSTEP;   // steps of a wave's quarter
     // parts of which the wave's quarter has every piece, inside the row
     const int last_steps = nst - (PARTS - 1) * KSN;                           // steps of the last part
     uint32_t whole_parts = 0;
@@ -1245,7 +1267,8 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         wait_vmem<0>();
         lds_barrier();
         if constexpr (!EVEN) {
-            if (wave_read_lane(shares[8], 0)) {
+            moved = wave_read_lane(shares[8], 0) != 0u;
+            if (moved) {
                 const uint4 x = reinterpret_cast<const uint4*>(shares)[0], y = reinterpret_cast<const uint4*>(shares)[1];
                 s = wave_read_lane(x.x, 0); C = wave_read_lane(x.y, 0);
                 run = uniform(TileRun{x.z, x.w, y.x, y.y, y.z, y.w});
@@ -1297,25 +1320,38 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                 load_to_lds16_at<(decltype(t)::value * KSN + i) * 1024, off>(from[decltype(t)::value][i], at);
             });
         };
-        static_for<RING>([&](auto u_c) __attribute__((always_inline)) {
-            constexpr int u = decltype(u_c)::value;
-            using Part = std::integral_constant<int, u % PARTS>;
-            if (u < units) {
-                if constexpr (u % PARTS == 0) address(u / PARTS);
-                locate(Part{});
-                static_for<KSN>([&](auto i) __attribute__((always_inline)) { fill1(Part{}, ring_at + u * (NI * 1024), i); });
-            }
-        });
+        auto fill_ring = [&]() __attribute__((always_inline)) {
+            static_for<RING>([&](auto u_c) __attribute__((always_inline)) {
+                constexpr int u = decltype(u_c)::value;
+                using Part = std::integral_constant<int, u % PARTS>;
+                if (u < units) {
+                    if constexpr (u % PARTS == 0) address(u / PARTS);
+                    locate(Part{});
+                    static_for<KSN>([&](auto i) __attribute__((always_inline)) { fill1(Part{}, ring_at + u * (NI * 1024), i); });
+                }
+            });
+        };
         // A operands: hidden row col of every row group (clamped: results dropped), zeros past d; a partial chunk
         // holds the row's last VEC values, those counted already replaced by zero, as `fill1` reads it
         uint4 h[MT][PARTS * KSN][NH];
         const float* hb = H + ((size_t)s * B + row0) * d;
+        auto keep = [&](int m, int st, float (&x)[VEC]) __attribute__((always_inline)) {
+            const int k = st < nst ? k0 + st * KSTEP + kq * VEC : d, drop = k - min(k, d - VEC);
 #pragma unroll
-        for (int m = 0; m < MT; ++m) {
-            const float* hrow = hb + (size_t)min(m * kTileM + col, Bg - 1) * d;
+            for (int e = 0; e < VEC; ++e) x[e] = e >= drop ? x[e] : 0.f;
+            if constexpr (LATE) {
 #pragma unroll
-            for (int st = 0; st < PARTS * KSN; ++st) {
-                const int k = st < nst ? k0 + st * KSTEP + kq * VEC : d, at = min(k, d - VEC), drop = k - at;
+                for (int e = 0; e < 2; ++e)
+                    h[m][st][e] = make_uint4(__float_as_uint(x[4 * e]), __float_as_uint(x[4 * e + 1]), __float_as_uint(x[4 * e + 2]), __float_as_uint(x[4 * e + 3]));
+            } else if constexpr (BF) split_planes8(x, h[m][st]);
+            else h[m][st][0] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+        };
+        auto load_hidden = [&](auto from_c) __attribute__((always_inline)) {       // units from the from-th on
+#pragma unroll
+            for (int i = decltype(from_c)::value * KSN; i < MT * PARTS * KSN; ++i) {
+                const int m = i / (PARTS * KSN), st = i % (PARTS * KSN);
+                const float* hrow = hb + (size_t)min(m * kTileM + col, Bg - 1) * d;
+                const int k = st < nst ? k0 + st * KSTEP + kq * VEC : d, at = min(k, d - VEC);
                 float x[VEC];
 #pragma unroll
                 for (int e = 0; e < VEC; e += 4) {
@@ -1323,17 +1359,30 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
                     x[e] = v.x; x[e + 1] = v.y; x[e + 2] = v.z; x[e + 3] = v.w;
                 }
                 if ((st & (BF ? 1 : 3)) == (BF ? 1 : 3)) __builtin_amdgcn_sched_barrier(0);   // (a few addresses at a time)
-#pragma unroll
-                for (int e = 0; e < VEC; ++e) x[e] = e >= drop ? x[e] : 0.f;
-                if constexpr (LATE) {
-#pragma unroll
-                    for (int e = 0; e < 2; ++e)
-                        h[m][st][e] = make_uint4(__float_as_uint(x[4 * e]), __float_as_uint(x[4 * e + 1]), __float_as_uint(x[4 * e + 2]), __float_as_uint(x[4 * e + 3]));
-                } else if constexpr (BF) split_planes8(x, h[m][st]);
-                else h[m][st][0] = make_uint4(__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3]));
+                keep(m, st, x);
             }
+        };
+        if (STAGED == 0 || moved) {   // (uniform)
+            fill_ring();
+            load_hidden(std::integral_constant<int, 0>{});
+        } else {
+#pragma unroll
+            for (int i = 0; i < STAGED * KSN; ++i) {
+                float x[VEC];
+#pragma unroll
+                for (int e = 0; e < SB; ++e) {
+                    const int p = (i % KSN * 4 + kq) * SB + e;                // (p / PPH does not depend on the lane)
+                    const uint4 v = *reinterpret_cast<const uint4*>(ring + (i / KSN * SUBS + (i % KSN * 4 * SB) / PPH) * (PPH * 256) + (col * PPH + ((p % PPH) ^ (col >> SHH))) * 16);
+                    x[4 * e] = __uint_as_float(v.x); x[4 * e + 1] = __uint_as_float(v.y); x[4 * e + 2] = __uint_as_float(v.z); x[4 * e + 3] = __uint_as_float(v.w);
+                }
+                keep(i / (PARTS * KSN), i % (PARTS * KSN), x);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // (they have left the ring)
+            __builtin_amdgcn_sched_barrier(0);
+            fill_ring();
+            load_hidden(std::integral_constant<int, STAGED>{});
         }
-        __builtin_amdgcn_s_waitcnt(0x0F70);                                   // vmcnt(0): the compiler must not wait for them in the loop
+        if (STAGED < MT * PARTS || moved) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the compiler must not wait for them in the loop
         __builtin_amdgcn_sched_barrier(0);
         LSH_TRACE_WG(10);
         float out[GT][MT];
