@@ -195,6 +195,19 @@ __device__ __forceinline__ void load_to_lds4(const void* from, void* to) {
     const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
 }
+// Matrix operands straight from memory.  A lane's operand is 16 bytes of row lane % 16, so that neighbouring lanes, loading their own,
+// read different rows, and a load of 1 KB takes the CU's address unit 66 cycles (all CUs together 9.7 TB/s, out of L2 too);
+// with four neighbouring lanes on neighbouring bytes of a row it takes 23 to 28 (24 TB/s).  So lane 4 c + p loads piece p of row
+// c, and quads_to_operand hands it to lane 16 p + c.
+__device__ __forceinline__ int quad_row() { return lane_id() >> 2; }
+__device__ __forceinline__ int quad_piece() { return lane_id() & 3; }
+template <typename T> __device__ __forceinline__ T quads_to_operand(T v) {
+    static_assert(sizeof(T) == 4, "");
+    const int ln = lane_id();
+    return __builtin_bit_cast(T, __builtin_amdgcn_ds_bpermute(16 * (ln & 15) + 4 * (ln >> 4), __builtin_bit_cast(int, v)));
+}
+// The value that operand lane quad_row() (piece 0) holds.
+__device__ __forceinline__ int32_t operand_to_quads(int32_t v) { return __builtin_amdgcn_ds_bpermute(4 * quad_row(), v); }
 // At most N loads and stores of this wave are still under way.
 template <int N> __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 

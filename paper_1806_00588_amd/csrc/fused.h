@@ -69,7 +69,7 @@ struct TailArgs {
 // `tile_ids` has kFusedRound * 16 words, `wsum` >= 17, `red` is the cross-wave reduction buffer;
 // h_lds (or null) are the sentence's hidden rows staged in LDS as [B][d].
 constexpr int kCoopBits = 8;   // list positions of one tile in one thread from which its wave shares the work
-template <typename ET, bool CHUNKS, bool ONE_LAUNCH>
+template <typename ET, bool CHUNKS, bool ONE_LAUNCH, bool QUADS = false>
 __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* wsum, uint32_t* tile_ids,
                                                   float (*red)[4][kWave], const float* h_lds,
                                                   const ET* __restrict__ E, int64_t ld, int d,
@@ -144,7 +144,7 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
             if (tid < kTileN && in_list)
                 store_shared_result<ONE_LAUNCH>(&cand[(size_t)s * V + nt * tn + col], id);
             LSH_TRACE(1, 2);
-            logits_tile_all_rows<ET, kFusedWaves, 64 / kFusedWaves, CHUNKS, 0, true, ONE_LAUNCH>(
+            logits_tile_all_rows<ET, kFusedWaves, 64 / kFusedWaves, CHUNKS, 0, true, ONE_LAUNCH, QUADS>(
                 E, ld, d, H, B, s, nt, C, (int64_t)id, logits, cpitch, recs, red, h_lds, 0, 0, -1, tn);
         }
         // (a tile ends with a barrier: the table is free for the next round)
@@ -182,8 +182,11 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
 }
 
 // grid = S * G workgroups: workgroup b works for sentence b % S and takes that sentence's tiles
-// (b / S), (b / S) + G, ...
-template <typename ET, bool CHUNKS, bool ONE_LAUNCH>
+// (b / S), (b / S) + G, ...  QUADS: for long rows; a tile's 64 KB come in half a microsecond less (d = 1000, one sentence of
+// 12 beams: 16.2 -> 15.8 us a step; with d = 64 the way through the lanes would cost 0.3 us, a look at d in the kernel 0.1.  Hidden rows from
+// memory, in k_union_logits, loaded so as well: 0.5 us lost of 32 with lists of 300 tiles).
+constexpr int kQuadsMinSteps = kFusedWaves + 1;   // steps of 64 bytes of a row: more than one a wave
+template <typename ET, bool CHUNKS, bool ONE_LAUNCH, bool QUADS = false>
 __global__ void __launch_bounds__(kCandThreads)
 k_cand_logits(CandArgs a, const ET* __restrict__ E, int64_t ld, int S, int32_t* __restrict__ cand,
               int32_t* __restrict__ count, float* __restrict__ logits, int64_t cpitch,
@@ -204,7 +207,7 @@ k_cand_logits(CandArgs a, const ET* __restrict__ E, int64_t ld, int S, int32_t* 
     const float* h_lds = nullptr;
     if (a.rows_chunk >= B)
         h_lds = reinterpret_cast<const float*>(smem + bitmap_words_padded(V));
-    tiles_from_bitmap<ET, CHUNKS, ONE_LAUNCH>(bm, wsum, tile_ids, red, h_lds, E, ld, a.d, a.H, B, V, s, g, G, cand,
+    tiles_from_bitmap<ET, CHUNKS, ONE_LAUNCH, QUADS>(bm, wsum, tile_ids, red, h_lds, E, ld, a.d, a.H, B, V, s, g, G, cand,
                                    count, logits, cpitch, recs, tail, smem);
     LSH_TRACE_WG(6);
 }

@@ -48,6 +48,9 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 template <typename ET> struct ElemTraits;
 template <> struct ElemTraits<float> {
     static constexpr int VEC = 4;  // elements per 16-byte load
+    __device__ static __forceinline__ void widen(const uint4& v, float (&out)[4]) {
+        out[0] = __uint_as_float(v.x); out[1] = __uint_as_float(v.y); out[2] = __uint_as_float(v.z); out[3] = __uint_as_float(v.w);
+    }
     __device__ static __forceinline__ void load16(const float* p, float (&out)[4]) {   // (any alignment)
         const Float4U v = *reinterpret_cast<const Float4U*>(p);
         out[0] = v.x; out[1] = v.y; out[2] = v.z; out[3] = v.w;
@@ -55,6 +58,14 @@ template <> struct ElemTraits<float> {
 };
 template <> struct ElemTraits<uint16_t> {
     static constexpr int VEC = 8;
+    __device__ static __forceinline__ void widen(const uint4& v, float (&out)[8]) {
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            out[2 * i] = __uint_as_float(w[i] << 16);
+            out[2 * i + 1] = __uint_as_float(w[i] & 0xFFFF0000u);
+        }
+    }
     __device__ static __forceinline__ void load16(const uint16_t* p, float (&out)[8]) {
         const Chunk16U<uint16_t> v = *reinterpret_cast<const Chunk16U<uint16_t>*>(p);
 #pragma unroll
@@ -182,7 +193,8 @@ __device__ __forceinline__ void tile_record_store(const TileRecords& recs, size_
 // address they start at (d = 1001 fp32, rows 4 bytes off a multiple of 16: element by element was three times
 // slower); the chunk that would reach past the row's end is read from the row's last VEC elements instead, of
 // which those that were counted already are zeroed on both sides.  Otherwise elements are read one by one.
-template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int MTB = 1, bool RICH = false, bool SHARE = false>
+// QUADS (with CHUNKS): lanes load candidates' chunks for each other (quads_to_operand); the same sums.
+template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int MTB = 1, bool RICH = false, bool SHARE = false, bool QUADS = false>
 __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld, int d,
                                             const float* __restrict__ H, int B, int s, int mt,
                                             int nt, int C, int64_t j, float* __restrict__ logits,
@@ -199,8 +211,8 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
     const int col = ln & 15, kq = ln >> 4;
     const int nks = (d + KSTEP - 1) / KSTEP;
     const int n0 = nt * tn;
-    const bool col_used = col < tn;   // lanes of unused columns load no candidate row
-    const ET* erow = E + j * ld;
+    const bool col_used = (QUADS ? quad_row() : col) < tn;   // lanes of unused columns load no candidate row
+    const ET* erow = E + (QUADS ? (int64_t)operand_to_quads((int32_t)j) : j) * ld;
     // the sentence's hidden rows, from LDS when the caller has them staged there ([B][d]);
     // rows beyond B are clamped like the candidate: never stored
     const float* hrow[MTB];
@@ -215,10 +227,27 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
     for (int m = 0; m < MTB; ++m) acc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
     for (int ks0 = wv; ks0 < nks; ks0 += WAVES * UNROLL) {
         float ev[UNROLL][VEC], hv[MTB][UNROLL][VEC];
+        uint4 raw[UNROLL];
 #pragma unroll
         for (int uu = 0; uu < UNROLL; ++uu) {
             const int k = (ks0 + uu * WAVES) * KSTEP + kq * VEC;
-            if (CHUNKS) {
+            if constexpr (QUADS) {
+                const int kl = (ks0 + uu * WAVES) * KSTEP + quad_piece() * VEC;
+                raw[uu] = make_uint4(0u, 0u, 0u, 0u);
+                if (kl < d && col_used) {
+                    const Chunk16U<ET> c = *reinterpret_cast<const Chunk16U<ET>*>(erow + min(kl, d - VEC));
+                    raw[uu] = make_uint4(c.w[0], c.w[1], c.w[2], c.w[3]);
+                }
+#pragma unroll
+                for (int m = 0; m < MTB; ++m)
+#pragma unroll
+                    for (int q = 0; q < VEC; q += 4) {
+                        Float4U h4 = {0.f, 0.f, 0.f, 0.f};
+                        if (k < d) h4 = *reinterpret_cast<const Float4U*>(hrow[m] + min(k, d - VEC) + q);
+                        hv[m][uu][q] = h4.x; hv[m][uu][q + 1] = h4.y;
+                        hv[m][uu][q + 2] = h4.z; hv[m][uu][q + 3] = h4.w;
+                    }
+            } else if (CHUNKS) {
                 if (k < d) {
                     const int at = min(k, d - VEC);
                     if (col_used) {
@@ -252,6 +281,11 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
                     for (int m = 0; m < MTB; ++m) hv[m][uu][q] = in ? hrow[m][k + q] : 0.f;
                 }
             }
+        }
+        if constexpr (QUADS) {
+#pragma unroll
+            for (int uu = 0; uu < UNROLL; ++uu)
+                ElemTraits<ET>::widen(make_uint4(quads_to_operand(raw[uu].x), quads_to_operand(raw[uu].y), quads_to_operand(raw[uu].z), quads_to_operand(raw[uu].w)), ev[uu]);
         }
         if (CHUNKS && d % VEC != 0) {   // (uniform) leading elements of a row's last chunk that were counted before
 #pragma unroll
@@ -305,7 +339,7 @@ __device__ __forceinline__ void logits_tile(const ET* __restrict__ E, int64_t ld
 
 // All row groups of one tile of candidates, the candidate rows being read once for up to four
 // groups (64 beams) at a time.
-template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int FIXED_MT = 0, bool RICH = false, bool SHARE = false>
+template <typename ET, int WAVES, int UNROLL, bool CHUNKS, int FIXED_MT = 0, bool RICH = false, bool SHARE = false, bool QUADS = false>
 __device__ __forceinline__ void logits_tile_all_rows(const ET* __restrict__ E, int64_t ld, int d,
                                                      const float* __restrict__ H, int B, int s,
                                                      int nt, int C, int64_t j,
@@ -323,18 +357,18 @@ __device__ __forceinline__ void logits_tile_all_rows(const ET* __restrict__ E, i
     // instantiated, so its registers do not count against the others)
     const int MT = FIXED_MT ? FIXED_MT : ((row_hi < 0 ? B : row_hi - row_lo) + kTileM - 1) / kTileM;
     if (MT == 1) {
-        logits_tile<ET, WAVES, UNROLL, CHUNKS, 1, RICH, SHARE>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
+        logits_tile<ET, WAVES, UNROLL, CHUNKS, 1, RICH, SHARE, QUADS>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     } else if (MT == 2) {
-        logits_tile<ET, WAVES, U2, CHUNKS, 2, RICH, SHARE>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
+        logits_tile<ET, WAVES, U2, CHUNKS, 2, RICH, SHARE, QUADS>(E, ld, d, H, B, s, 0, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     } else if (ElemTraits<ET>::VEC > 4) {  // bf16: twice the registers per load, two groups at most
         for (int mt = 0; mt < MT; mt += 2)
-            logits_tile<ET, WAVES, U2, CHUNKS, 2, RICH, SHARE>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
+            logits_tile<ET, WAVES, U2, CHUNKS, 2, RICH, SHARE, QUADS>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     } else {
         for (int mt = 0; mt < MT; mt += 4)
-            logits_tile<ET, WAVES, U4, CHUNKS, 4, RICH, SHARE>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
+            logits_tile<ET, WAVES, U4, CHUNKS, 4, RICH, SHARE, QUADS>(E, ld, d, H, B, s, mt, nt, C, j, logits, cpitch,
             recs, red, h_lds, h_pitch, row_lo, row_hi, tn);
     }
 }

@@ -722,6 +722,7 @@ hipError_t allow_step_lds(int dev) {
     LSH_ALLOW((allow_whole_lds<k_union_logits<ET, AL, false>>()));         \
     LSH_ALLOW((allow_whole_lds<k_union_logits<ET, AL, true>>()));          \
     LSH_ALLOW((allow_whole_lds<k_cand_logits<ET, AL, false>>()));          \
+    LSH_ALLOW((allow_whole_lds<k_cand_logits<ET, AL, false, AL>>()));     \
     LSH_ALLOW((allow_whole_lds<k_cand_logits<ET, AL, true>>()))
     LSH_ALLOW_FUSED(float, true);
     LSH_ALLOW_FUSED(float, false);
@@ -1203,11 +1204,17 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
 #undef LSH_UNION_LOGITS
         } else {
             const size_t lds = fused_lds_words(t->V, t->P, t->K, stage) * sizeof(uint32_t);
-#define LSH_CAND_LOGITS(ET, AL, OL)                                                               \
-    launch(cx, 1, k_cand_logits<ET, AL, OL>, grid, block, lds, ca, (const ET*)t->E, t->ld, sp->S,  \
+#define LSH_CAND_LOGITS(...)                                                                      \
+    launch(cx, 1, k_cand_logits<__VA_ARGS__>, grid, block, lds, ca, (decltype(e))t->E, t->ld, sp->S,  \
            w.cand, w.count, w.logits, w.cpitch, w.records(), tail)
-#define LSH_CAND_LOGITS2(ET, AL) \
-    do { if (selected) LSH_CAND_LOGITS(ET, AL, true); else LSH_CAND_LOGITS(ET, AL, false); } while (0)
+#define LSH_CAND_LOGITS2(ET, AL)                                                                  \
+    do {                                                                                         \
+        const ET* e = nullptr;                                                                   \
+        constexpr int kStep = 4 * ElemTraits<ET>::VEC;                                           \
+        if (selected) LSH_CAND_LOGITS(ET, AL, true);                                             \
+        else if (AL && (t->d + kStep - 1) / kStep >= kQuadsMinSteps) LSH_CAND_LOGITS(ET, AL, false, AL); \
+        else LSH_CAND_LOGITS(ET, AL, false);                                                     \
+    } while (0)
             if (f32) { if (al) LSH_CAND_LOGITS2(float, true); else LSH_CAND_LOGITS2(float, false); }
             else { if (al) LSH_CAND_LOGITS2(uint16_t, true); else LSH_CAND_LOGITS2(uint16_t, false); }
 #undef LSH_CAND_LOGITS2
