@@ -691,14 +691,23 @@ k_candidates(CandArgs a, int S, int32_t* __restrict__ cand, int32_t* __restrict_
     LSH_TRACE(0, 6);
 }
 
+// What further workgroups of a launch that hashes do, those from Args::first on: nothing, there are none.
+struct Alone {
+    struct Args { int first; };
+    static constexpr bool kAny = false;
+    static __device__ void run(const Args&, uint32_t*) {}
+};
+
 // Sentences with many beams: the hidden rows of a sentence are hashed a chunk at a time, so one
 // workgroup per sentence serialises ceil(B / rows per chunk) rounds of dependent memory round
 // trips.  Here the sentence is cut into `nparts` parts of `part_rows` rows, one workgroup each;
 // every part leaves its own V-bit bitmap (without the top-frequent words) in global memory at
 // part_bitmaps[(s * nparts + part) * ceil(V/32)], and the consumer ORs the parts (Eq. 3's union).
+template <class Beside>
 __global__ void __launch_bounds__(kCandThreads)
-k_part_bitmaps(CandArgs a, int part_rows, int nparts, uint32_t* __restrict__ part_bitmaps) {
+k_part_bitmaps(CandArgs a, int part_rows, int nparts, uint32_t* __restrict__ part_bitmaps, typename Beside::Args beside) {
     extern __shared__ uint32_t smem[];
+    if (Beside::kAny && (int)blockIdx.x >= beside.first) return Beside::run(beside, smem);
     const int s = blockIdx.x / nparts, part = blockIdx.x - s * nparts;
     const int nwords = (a.V + 31) >> 5;
     a.T = 0;
@@ -728,9 +737,11 @@ constexpr int kHitListMin = 2048, kHitListMax = 16384;  // load-list entries per
 // grid = S*B*kHitSlices workgroups (hidden row r = block / kHitSlices, slice q = block %
 // kHitSlices).  Requires W <= kCandThreads (one span per thread), W * V < 2^30 (a 16-byte group
 // index and a 4-bit mask share a word) and list_cap >= kHitListMin.
+template <class Beside>
 __global__ void __launch_bounds__(kCandThreads)
-k_hit_rows(CandArgs a, int t, int list_cap, uint32_t* __restrict__ row_bitmaps /*[S*B, nwords]*/) {
+k_hit_rows(CandArgs a, int t, int list_cap, uint32_t* __restrict__ row_bitmaps /*[S*B, nwords]*/, typename Beside::Args beside) {
     extern __shared__ uint32_t smem[];
+    if (Beside::kAny && (int)blockIdx.x >= beside.first) return Beside::run(beside, smem);
     const int V = a.V, d = a.d, P = a.P, K = a.K, W = a.W, bits = a.bits;
     const int u = P / W;
     const int nwords = (V + 31) >> 5;

@@ -58,6 +58,43 @@ struct TailArgs {
     int tile_forced;             // 1..15: candidates per tile instead of 16 (option fused_tile)
 };
 
+// The first tiles of every list, made beside the hashing (k_hit_rows, k_part_bitmaps).  The top-frequent words are members of every
+// candidate list, and a vocabulary sorted by frequency has them first: the ids 0, 1, 2, ... stand at the positions 0, 1, 2, ... of
+// every list, whatever the hashing finds.  Their logits need nothing that the hashing makes, and that runs on a few dozen CUs.  So its launch
+// has further workgroups that contract the sentences' hidden rows with the words 0 .. 16 tiles - 1 and leave logits and
+// records where the tiles of a list that begins with them have theirs, with the same sums.  Whether a list does is seen once its
+// bitmap is there (tiles_done); if not, its tiles are made as if nothing had been.
+struct FirstTiles {
+    const void* E;
+    int64_t ld;
+    const float* H;
+    int d, S, B;
+    int tiles;     // of 16 words; 0: none are made
+    int first;     // first workgroup of the launch that makes them
+    float* logits;
+    int64_t cpitch;
+    TileRecords recs;
+};
+constexpr int kFirstTilesMost = 2 * kWave;   // a lane of tiles_done per bitmap word
+template <typename ET> struct FirstTilesBeside {
+    using Args = FirstTiles;
+    static constexpr bool kAny = true;
+    static __device__ __forceinline__ void run(const Args& a, uint32_t* smem) {
+        float (*red)[4][kWave] = reinterpret_cast<float (*)[4][kWave]>(smem);
+        for (int i = (int)blockIdx.x - a.first; i < a.tiles * a.S; i += (int)gridDim.x - a.first) {
+            const int s = i % a.S, nt = i / a.S;
+            logits_tile_all_rows<ET, kFusedWaves, 64 / kFusedWaves, true, 0, true>(
+                static_cast<const ET*>(a.E), a.ld, a.d, a.H, a.B, s, nt, (nt + 1) * kTileN, nt * kTileN + (lane_id() & 15), a.logits, a.cpitch, a.recs, red);
+        }
+    }
+};
+// How many of a list's first `tiles` tiles are made: all of them, or none.  Called by whole waves, with the list's bitmap.
+__device__ __forceinline__ int tiles_done(const uint32_t* bm, int tiles) {
+    const int ln = lane_id(), n = tiles * kTileN - 32 * ln;                   // (at most 64 words)
+    const uint32_t want = n >= 32 ? 0xFFFFFFFFu : n > 0 ? 0xFFFFu : 0u;       // (a multiple of 16)
+    return tiles > 0 && __ballot((want & ~(want ? bm[ln] : 0u)) != 0u) == 0ull ? tiles : 0;
+}
+
 // What follows the bitmap in both fused kernels.  Thread t owns a contiguous run of bitmap words;
 // a workgroup scan of the runs' popcounts tells it which output positions of the ascending
 // candidate list its set bits are.  The workgroup's tiles (g, g + G, ...) are taken kFusedRound at
@@ -77,7 +114,8 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
                                                   int g, int G, int32_t* __restrict__ cand,
                                                   int32_t* __restrict__ count,
                                                   float* __restrict__ logits, int64_t cpitch,
-                                                  TileRecords recs, const TailArgs& tail, uint32_t* smem) {
+                                                  TileRecords recs, const TailArgs& tail, uint32_t* smem, int done = 0) {
+    // (done: tiles of the list that are made already, the words 0 .. 16 done - 1)
     const int tid = threadIdx.x, ln = lane_id();
     const int nwords = (V + 31) >> 5;
     const int per_thread = (nwords + kCandThreads - 1) / kCandThreads;
@@ -92,16 +130,18 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
 
     const int tn = select_tile_width(C, tail.tile_forced, recs.pitch);
     const int ntiles = tn == kTileN ? (C + kTileN - 1) >> 4 : (C + tn - 1) / tn;   // (no division in the usual case)
-    const int col = ln & 15;
-    for (int base = 0; g + base * G < ntiles; base += kFusedRound) {
-        // ids of the tiles g + (base + k) G, k < kFusedRound, into tile_ids[k][16].  A thread
+    const int col = ln & 15, g0 = done + g;                               // the workgroup's first tile
+    if (g == 0)
+        for (int i = tid; i < done * kTileN; i += kCandThreads) store_shared_result<ONE_LAUNCH>(&cand[(size_t)s * V + i], i);
+    for (int base = 0; g0 + base * G < ntiles; base += kFusedRound) {
+        // ids of the tiles g0 + (base + k) G, k < kFusedRound, into tile_ids[k][16].  A thread
         // with a few of a tile's positions walks its set bits itself.  One with kCoopBits or more
         // -- the dense words of the top-frequent ids put a whole tile into one thread, and sixteen
         // dependent steps of a single lane were the longest thing such a workgroup did -- hands
         // them to the lanes of its wave: lane c finds the c-th of them by rank (popcounts of the
         // owner's words, then a five-step search inside the word).
         for (int k = 0; k < kFusedRound; ++k) {
-            const int nt = g + (base + k) * G;
+            const int nt = g0 + (base + k) * G;
             if (nt >= ntiles) break;
             const uint32_t lo = max(run, (uint32_t)(nt * tn));
             const uint32_t hi = min(min(run + mine, (uint32_t)(nt * tn + tn)), (uint32_t)C);
@@ -135,7 +175,7 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
         }
         __syncthreads();
         for (int k = 0; k < kFusedRound; ++k) {
-            const int nt = g + (base + k) * G;
+            const int nt = g0 + (base + k) * G;
             if (nt >= ntiles) break;
             // this lane's candidate: output position 16 nt + col of the ascending list (lanes past
             // the end of the list take the tile's first candidate; such columns are never stored)
@@ -155,9 +195,9 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
 
     // ---- the step's tail, by the last workgroup of the sentence to get here ----
     SelShared& sh = *reinterpret_cast<SelShared*>(smem);   // (bitmap, prefix, stage: all done with)
-    const int participants = min(G, ntiles);               // workgroups of this sentence with tiles
-    if (ntiles > 0) {
-        if (g >= ntiles) return;
+    const int participants = min(G, ntiles - done);        // workgroups of this sentence with tiles
+    if (ntiles > done) {
+        if (g0 >= ntiles) return;
         // what the finishing workgroup reads of this one (logits, records, ids) went through to
         // memory (store_shared_result): once every wave's stores have completed, the ticket
         LSH_TRACE_LATEST(1, 12);
@@ -174,7 +214,7 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
         if (sh.misc[7] == 0u) return;
         LSH_TRACE_ANY(1, 14);
     } else if (g != 0) {
-        return;                // an empty list: workgroup 0 of the sentence pads the outputs
+        return;                // an empty list, or all made: workgroup 0 of the sentence ends the step
     }
     select_sentence<true, true>(sh, s, logits, cpitch, recs.rec, recs.id2, recs.pitch, cand, nullptr, C, V, B,
                           tail.beam_scores, tail.lse, tail.out_beam, tail.out_word, tail.out_score,
@@ -227,7 +267,7 @@ __global__ void __launch_bounds__(kCandThreads)
 k_union_logits(const uint32_t* __restrict__ part_bitmaps, int nparts, const int32_t* __restrict__ topfreq,
                int T, const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S,
                int B, int V, int32_t* __restrict__ cand, int32_t* __restrict__ count,
-               float* __restrict__ logits, int64_t cpitch, TileRecords recs, TailArgs tail) {
+               float* __restrict__ logits, int64_t cpitch, TileRecords recs, TailArgs tail, int first_tiles /*FirstTiles::tiles*/) {
     extern __shared__ uint32_t smem[];
     const int tid = threadIdx.x;
     const int s = blockIdx.x % S;
@@ -244,7 +284,7 @@ k_union_logits(const uint32_t* __restrict__ part_bitmaps, int nparts, const int3
     mark_id_list(bm, V, topfreq, T, tf_first);
     __syncthreads();
     tiles_from_bitmap<ET, CHUNKS, ONE_LAUNCH>(bm, wsum, tile_ids, red, nullptr, E, ld, d, H, B, V, s, g, G, cand,
-                                   count, logits, cpitch, recs, tail, smem);
+                                   count, logits, cpitch, recs, tail, smem, tiles_done(bm, first_tiles));
 }
 
 }  // namespace lshbeam

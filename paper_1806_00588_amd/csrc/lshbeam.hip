@@ -332,6 +332,23 @@ int part_rows_of(const lsh_tables* t, const lsh_step_params* sp, int stage_words
 // Whether a row of E holds a 16-byte chunk: what every contraction but the elementwise forms needs.
 inline bool has_chunks(const lsh_tables* t) { return t->d >= (t->dtype == LSH_F32 ? 4 : 8); }
 
+// The first tiles that the launch of `blocks` hashing workgroups makes beside them for the fused kernel that follows: one for each CU
+// that does not hash, as far as the T top-frequent words, if they are the ids from 0 on, fill whole tiles.  They pay where they
+// save that kernel's workgroups a tile each; else they cost 1 % (what they read delays the hashing).  How long the lists will be is not known
+// (near words hit more often than by chance: up to ten times what is expected with high thresholds), so: from 0.64 expected tiles per
+// workgroup on and if they are a fifth of a tile for each.  us a step without and with them, expected tiles per workgroup: 500 bands, t = 5, d = 1000,
+// V = 40000, 12 beams 0.65: 32.1, 28.9; t = 8, d = 314, V = 1139, 4 x 2 beams 1.11: 21.9, 20.0; t = 5, d = 80, bf16, 4 x 1 0.89: 22.6, 21.6; t = 4, d = 753,
+// 4 x 5 1.27: 26.1, 26.3; t = 7, d = 672, 3 x 6 0.82: 23.0, 23.4; below the line t = 5, d = 792 bf16, 4 x 10 0.63: 24.3, 24.6; t = 8,
+// d = 520, 3 x 2 0.51: 19.0, 19.6; t = 5, d = 352 bf16, 2 x 17 0.20: 21.7, 22.6; t = 6, d = 119, 20 beams 0.36: 28.3, 26.6.
+FirstTiles first_tiles_plan(const lsh_tables* t, const lsh_step_params* sp, const float* H, const Workspace& w, int blocks) {
+    FirstTiles f{t->E, t->ld, H, t->d, sp->S, sp->B, 0, blocks, w.logits, w.cpitch, w.records()};
+    if (!has_chunks(t) || t->option(kOptFusedTile, 0) > 0 || t->opt[kOptFusedGrid] != kAuto) return f;
+    const int wgs = 256 / sp->S, n = std::min({(int)std::min<int64_t>(sp->T, t->V) / kTileN, kFirstTilesMost, std::max(0, 256 - blocks) / (int)sp->S});
+    if (5 * n >= wgs && expected_candidates(t, sp) >= 0.64 * kTileN * wgs) f.tiles = n;
+    return f;
+}
+inline int first_tiles_blocks(const FirstTiles& f) { return std::min(f.tiles * f.S, std::max(0, 256 - f.first)); }
+
 template <typename ET, int WAVES>
 void launch_logits_w(const StepCtx& cx, int grid, bool chunks, const float* H,
                      const lsh_step_params* sp, const int32_t* cand, const int32_t* count,
@@ -715,9 +732,13 @@ hipError_t allow_step_lds(int dev) {
     LSH_ALLOW((allow_whole_lds<k_logits_pass<float, 2>>()));
     LSH_ALLOW((allow_whole_lds<k_logits_pass<float, 3>>()));
     LSH_ALLOW((allow_whole_lds<k_logits_pass<uint16_t, 1>>()));
-    LSH_ALLOW(allow_whole_lds<k_hit_rows>());
+    LSH_ALLOW(allow_whole_lds<k_hit_rows<Alone>>());
+    LSH_ALLOW(allow_whole_lds<k_hit_rows<FirstTilesBeside<float>>>());
+    LSH_ALLOW(allow_whole_lds<k_hit_rows<FirstTilesBeside<uint16_t>>>());
     LSH_ALLOW(allow_whole_lds<k_union_compact>());
-    LSH_ALLOW(allow_whole_lds<k_part_bitmaps>());
+    LSH_ALLOW(allow_whole_lds<k_part_bitmaps<Alone>>());
+    LSH_ALLOW(allow_whole_lds<k_part_bitmaps<FirstTilesBeside<float>>>());
+    LSH_ALLOW(allow_whole_lds<k_part_bitmaps<FirstTilesBeside<uint16_t>>>());
 #define LSH_ALLOW_FUSED(ET, AL)                                          \
     LSH_ALLOW((allow_whole_lds<k_union_logits<ET, AL, false>>()));         \
     LSH_ALLOW((allow_whole_lds<k_union_logits<ET, AL, true>>()));          \
@@ -1163,17 +1184,29 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
     // hit threshold is above 1 (Eq. 9-10), one per part of the sentence when it has many beams.
     const uint32_t* parts = nullptr;
     int nparts = 0;
+    FirstTiles first{};
     if (!sp->full_vocab && sp->threshold > 1) {
-        launch(cx, 3, k_hit_rows, dim3(sp->S * sp->B * kHitSlices), dim3(kCandThreads), (size_t)t->wg_hit_rows_lds,
-               ca, (int)sp->threshold, t->hit_list_cap, w.row_bitmaps);
+        const int blocks = sp->S * sp->B * kHitSlices;
+        if (fused) first = first_tiles_plan(t, sp, H_dev, w, blocks);
+        const dim3 grid(blocks + first_tiles_blocks(first)), block(kCandThreads);
+#define LSH_HIT_ROWS(BESIDE, ...) launch(cx, 3, k_hit_rows<BESIDE>, grid, block, (size_t)t->wg_hit_rows_lds, ca, (int)sp->threshold, t->hit_list_cap, w.row_bitmaps, __VA_ARGS__)
+        if (!first.tiles) LSH_HIT_ROWS(Alone, Alone::Args{});
+        else if (t->dtype == LSH_F32) LSH_HIT_ROWS(FirstTilesBeside<float>, first);
+        else LSH_HIT_ROWS(FirstTilesBeside<uint16_t>, first);
+#undef LSH_HIT_ROWS
         parts = w.row_bitmaps;
         nparts = sp->B;
     } else if (const int pr = part_rows_of(t, sp, stage)) {
         nparts = (sp->B + pr - 1) / pr;
         ca.stage_words = candidates_min_stage(t->d);
         set_derived(ca);
-        launch(cx, 4, k_part_bitmaps, dim3(sp->S * nparts), dim3(kCandThreads), (size_t)t->wg_candidates_lds,
-               ca, pr, nparts, w.row_bitmaps);
+        if (fused) first = first_tiles_plan(t, sp, H_dev, w, sp->S * nparts);
+        const dim3 grid(sp->S * nparts + first_tiles_blocks(first)), block(kCandThreads);
+#define LSH_PARTS(BESIDE, ...) launch(cx, 4, k_part_bitmaps<BESIDE>, grid, block, (size_t)t->wg_candidates_lds, ca, pr, nparts, w.row_bitmaps, __VA_ARGS__)
+        if (!first.tiles) LSH_PARTS(Alone, Alone::Args{});
+        else if (t->dtype == LSH_F32) LSH_PARTS(FirstTilesBeside<float>, first);
+        else LSH_PARTS(FirstTilesBeside<uint16_t>, first);
+#undef LSH_PARTS
         parts = w.row_bitmaps;
     }
     bool selected = false;   // the step's tail already ran inside the fused kernel
@@ -1195,7 +1228,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
 #define LSH_UNION_LOGITS(ET, AL, OL)                                                              \
     launch(cx, 1, k_union_logits<ET, AL, OL>, grid, block, lds, parts, nparts, topfreq_dev, sp->T, \
            (const ET*)t->E, t->ld, t->d, H_dev, sp->S, sp->B, t->V, w.cand, w.count, w.logits,    \
-           w.cpitch, w.records(), tail)
+           w.cpitch, w.records(), tail, first.tiles)
 #define LSH_UNION_LOGITS2(ET, AL) \
     do { if (selected) LSH_UNION_LOGITS(ET, AL, true); else LSH_UNION_LOGITS(ET, AL, false); } while (0)
             if (f32) { if (al) LSH_UNION_LOGITS2(float, true); else LSH_UNION_LOGITS2(float, false); }
