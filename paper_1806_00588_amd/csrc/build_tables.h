@@ -2,7 +2,8 @@
 // lookup", first step: T_w = {band code: [word ids]} flattened, CuckooT_w = {band code:
 // (start, length)}).
 //
-//   1. k_build_begin: permutations checked and copied, hash parameters drawn, tables cleared.
+//   1. k_build_begin: permutations checked and copied, hash parameters drawn, tables cleared.  (Where the scan
+//      writes the slots there is nothing to clear, and the first workgroups of k_row_codes do the rest: BuildFirst.)
 //   2. k_row_codes (candidates.h): band codes of every embedding row, [W, V].
 //   3. Every band's words are grouped by code, ids ascending inside a code: a stable radix sort of
 //      the code alone (words start in id order), up to kRadixBits bits of it per pass -- ONE pass for
@@ -96,7 +97,7 @@ __host__ __device__ inline BandMeta direct_band_meta(int w, int lg) {
 // copied, entries outside [0, d) replaced by 0 and reported (bad_perms[block], zeroed before, in host memory), the tickets zeroed.
 __global__ void __launch_bounds__(256)
 k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W, uint32_t cap, int lg, bool direct, uint64_t seed,
-              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed, uint32_t* __restrict__ n_keys,
+              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed,
               const int32_t* __restrict__ perms_in, int n_perms, int d, int32_t* __restrict__ perms,
               uint32_t* __restrict__ bad_perms, unsigned int* __restrict__ tickets, int n_tickets) {
     const int w = blockIdx.y, tid = threadIdx.x;
@@ -105,7 +106,6 @@ k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W,
         const bool again = !redo || redo[w];
         if (first == 0) {
             failed[w] = 0u;
-            if (n_keys) n_keys[w] = 0u;
             if (again) bands[w] = direct ? direct_band_meta(w, lg) : draw_band_meta(seed, w, W, attempt, 1u << lg, lg);
         }
         if (again)
@@ -127,14 +127,54 @@ k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W,
     if (tid == 0 && bad) bad_perms[blockIdx.x] = 1u;
 }
 
-// ---- the sort: grid (chunks, W) each ------------------------------------------------------------
+// The same for direct tables whose slots the scan writes, by the first workgroups of k_row_codes: 2 us and a kernel boundary less.
+struct BuildFirst {
+    const int32_t* perms_in;
+    int32_t* perms;
+    uint32_t* bad_perms;
+    BandMeta* bands;
+    uint32_t* n_keys;
+    unsigned int* tickets;
+    int n_perms, d, W, lg, n_tickets;
+    __device__ __forceinline__ void run() const {
+        if (blockIdx.x >= (uint32_t)kBuildBeginBlocks) return;
+        const int at = (int)(blockIdx.x * blockDim.x + threadIdx.x), step = min((int)gridDim.x, kBuildBeginBlocks) * (int)blockDim.x;
+        for (int i = at; i < n_perms; i += step) {
+            const int32_t x = perms_in[i];
+            const bool ok = (uint32_t)x < (uint32_t)d;
+            perms[i] = ok ? x : 0;
+            if (!ok) bad_perms[blockIdx.x] = 1u;
+        }
+        for (int i = at; i < n_tickets; i += step) tickets[i] = 0u;
+        for (int w = at; w < W; w += step) {
+            n_keys[w] = 0u;
+            bands[w] = direct_band_meta(w, lg);
+        }
+    }
+};
+
+// ---- the sort: a workgroup per chunk and band ------------------------------------------------------
+
+// Whose chunk a workgroup takes.  Workgroup ids go round the eight XCDs: of eight bands each has its chunks on one XCD, so
+// that a line which chunks of the scatter write 4 bytes at a time is put together in one L2 and leaves it once.  Bands of a last round
+// of fewer than eight have theirs on all, as their XCDs alone would be busy.  V = 40000, 8 bands of 12 bits: scatter 11.6 -> 10.1 us.
+struct BandChunk {
+    int w, c;
+    __device__ __forceinline__ BandChunk(int chunks, int W) {
+        const int id = (int)blockIdx.x, rounds = W >> 3, slot = id >> 3;
+        if (id < 8 * rounds * chunks) { w = slot / chunks; c = slot - w * chunks; w = 8 * w + (id & 7); }
+        else { w = id / chunks; c = id - w * chunks; }
+    }
+};
 
 // counts[w][chunk][digit] (16 bits, digits in pairs); groups[w][chunk][group]: their sums over kScanDigits digits
 __global__ void __launch_bounds__(kRadixThreads)
-k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, RadixChunks ch, int shift, int digits,
+k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, int W, RadixChunks ch, int shift, int digits,
               uint32_t* __restrict__ counts, uint32_t* __restrict__ groups) {
     extern __shared__ uint32_t hist[];
-    const int tid = threadIdx.x, w = blockIdx.y, c = blockIdx.x;
+    const int tid = threadIdx.x, chunks = ch.count();
+    const BandChunk bc(chunks, W);
+    const int w = bc.w, c = bc.c;
     for (int i = tid; i < digits / 2; i += kRadixThreads) hist[i] = 0u;
     __syncthreads();
     int64_t begin, end;
@@ -146,7 +186,7 @@ k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, RadixChun
         atomicAdd(&hist[dg >> 1], (dg & 1u) ? 65536u : 1u);
     }
     __syncthreads();
-    uint32_t* out = counts + ((size_t)w * gridDim.x + c) * (digits / 2);
+    uint32_t* out = counts + ((size_t)w * chunks + c) * (digits / 2);
     for (int i = tid; i < digits / 2; i += kRadixThreads) out[i] = hist[i];
     const int ng = (digits + kScanDigits - 1) / kScanDigits;
     for (int g = wave_id(); g < ng; g += kRadixWaves) {
@@ -156,7 +196,7 @@ k_radix_count(const int32_t* __restrict__ codes /*[W, V]*/, int64_t V, RadixChun
             n += (x & 0xFFFFu) + (x >> 16);
         }
         n = wave_sum(n);
-        if (lane_id() == 0) groups[((size_t)w * gridDim.x + c) * ng + g] = n;
+        if (lane_id() == 0) groups[((size_t)w * chunks + c) * ng + g] = n;
     }
 }
 
@@ -239,18 +279,20 @@ k_radix_scan(const uint32_t* __restrict__ counts, const uint32_t* __restrict__ g
 // per digit bit.  (The vector instructions of the ballots bound it -- about 100 per 64 words -- which is why
 // a band is cut into chunks.)  ids_in == null: ids are the positions.
 __global__ void __launch_bounds__(kRadixThreads)
-k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict__ ids_in, int64_t V, RadixChunks ch, int shift,
+k_radix_scatter(const int32_t* __restrict__ codes_in, const int32_t* __restrict__ ids_in, int64_t V, int W, RadixChunks ch, int shift,
                 int bits, const uint32_t* __restrict__ starts, int32_t* __restrict__ codes_out,
                 int32_t* __restrict__ ids_out) {
     extern __shared__ uint32_t rsm[];
     const int digits = 1 << bits;
     uint32_t* base = rsm;                                                   // [digit]
     uint16_t* wpos = reinterpret_cast<uint16_t*>(rsm + digits);             // [wave][digit]
-    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id(), w = blockIdx.y, c = blockIdx.x;
+    const int tid = threadIdx.x, ln = lane_id(), wv = wave_id(), chunks = ch.count();
+    const BandChunk bc(chunks, W);
+    const int w = bc.w, c = bc.c;
     const int32_t* src = codes_in + (size_t)w * V;
     uint32_t* wpos32 = rsm + digits;
     for (int i = tid; i < digits * kRadixWaves / 2; i += kRadixThreads) wpos32[i] = 0u;   // (digits >= 2)
-    const uint2* st = reinterpret_cast<const uint2*>(starts) + ((size_t)w * gridDim.x + c) * (digits / 2);
+    const uint2* st = reinterpret_cast<const uint2*>(starts) + ((size_t)w * chunks + c) * (digits / 2);
     uint2* base2 = reinterpret_cast<uint2*>(base);
 #pragma unroll 4
     for (int i = tid; i < digits / 2; i += kRadixThreads) base2[i] = st[i];

@@ -931,18 +931,18 @@ struct BuildBlock {  // what a build works in, kept for the next one
     ~BuildBlock() { release_block(dev, kBuildBlock, block, idle); }
 };
 
-template <typename ET>
+template <typename ET, class FIRST = NotFirst>
 hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, int d, const int32_t* perms, int P, int K,
-                            int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride) {
+                            int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride, FIRST first = {}) {
     const bool ahead = row_codes_ahead(d, sizeof(ET), P, K);
-    const hipError_t e = ahead ? allow_whole_lds<k_row_codes<ET, true>>() : allow_whole_lds<k_row_codes<ET, false>>();
+    const hipError_t e = ahead ? allow_whole_lds<k_row_codes<ET, true, FIRST>>() : allow_whole_lds<k_row_codes<ET, false, FIRST>>();
     if (e != hipSuccess) return e;
     const int lg = row_codes_lg_rows(n, d, sizeof(ET), P, ahead);
     const size_t lds = row_codes_lds(1 << lg, d, sizeof(ET), P, ahead);
     int64_t groups = (n + (1 << lg) - 1) >> lg;
     if (ahead) groups = std::min<int64_t>(groups, 256 * std::min<size_t>(8, 158 * 1024 / lds));   // (as many as run at a time)
-    hipLaunchKernelGGL((ahead ? k_row_codes<ET, true> : k_row_codes<ET, false>), dim3((unsigned)groups), dim3(kRowCodeThreads),
-                       lds, st, X, ld, n, d, perms, P, K, W, bits, lg, out, row_stride, band_stride);
+    hipLaunchKernelGGL((ahead ? k_row_codes<ET, true, FIRST> : k_row_codes<ET, false, FIRST>), dim3((unsigned)groups), dim3(kRowCodeThreads),
+                       lds, st, X, ld, n, d, perms, P, K, W, bits, lg, out, row_stride, band_stride, first);
     return hipGetLastError();
 }
 
@@ -1042,16 +1042,23 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     const dim3 begin_grid(kBuildBeginBlocks, (unsigned)W + 1), b256(256);
     auto begin = [&](int attempt, const uint32_t* redo, bool with_tables) {
         hipLaunchKernelGGL(k_build_begin, begin_grid, b256, 0, st, table, t->bands_dev, (int)W,
-                           with_tables && !emit ? 1u << lg : 0u, lg, direct, seed, attempt, redo, stat.failed[attempt & 1],
-                           emit ? stat.n_keys : nullptr,
+                           with_tables ? 1u << lg : 0u, lg, direct, seed, attempt, redo, stat.failed[attempt & 1],
                            attempt || (with_tables && !blind) ? nullptr : perms_in, (int)n_perms, t->d, t->perms_dev, report.words,
                            t->tickets_dev, (int)n_tickets);
     };
     report.idle = false;
-    begin(0, nullptr, blind);
-    HIP_TRY(t->dtype == LSH_F32
-        ? launch_row_codes<float>(st, (const float*)t->E, t->ld, V, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V)
-        : launch_row_codes<uint16_t>(st, (const uint16_t*)t->E, t->ld, V, t->d, t->perms_dev, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V));
+    auto row_codes = [&](const int32_t* perms, auto first) {
+        return t->dtype == LSH_F32
+            ? launch_row_codes(st, (const float*)t->E, t->ld, V, t->d, perms, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V, first)
+            : launch_row_codes(st, (const uint16_t*)t->E, t->ld, V, t->d, perms, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V, first);
+    };
+    if (emit) {
+        HIP_TRY(row_codes(perms_in, BuildFirst{perms_in, t->perms_dev, report.words, t->bands_dev, stat.n_keys, t->tickets_dev, (int)n_perms,
+                                               t->d, (int)W, lg, (int)n_tickets}));
+    } else {
+        begin(0, nullptr, blind);
+        HIP_TRY(row_codes(t->perms_dev, NotFirst{}));
+    }
 
     std::vector<uint32_t> status(status_words);
     auto wait = [&]() -> lsh_status {
@@ -1072,12 +1079,12 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
         return rc != LSH_OK ? rc : build_on_host(t, st, host_rng);
     }
 
-    const dim3 sort_grid((unsigned)chunks, (unsigned)W), sort_block(kRadixThreads);
+    const dim3 sort_grid((unsigned)chunks * (unsigned)W), key_grid((unsigned)chunks, (unsigned)W), sort_block(kRadixThreads);
     HIP_TRY(allow_whole_lds<k_radix_scatter>());
     const int32_t *codes_in = t->codes_dev, *ids_in = nullptr;
     for (int p = 0; p < passes; ++p) {
         const int shift = p * pass_bits;
-        hipLaunchKernelGGL(k_radix_count, sort_grid, sort_block, (size_t)digits * 2, st, codes_in, V, ch, shift, digits, counts, groups);
+        hipLaunchKernelGGL(k_radix_count, sort_grid, sort_block, (size_t)digits * 2, st, codes_in, V, (int)W, ch, shift, digits, counts, groups);
         const dim3 scan_grid((unsigned)groups_n, (unsigned)W), scan_block(kScanDigits / 2);
         if (emit)
             hipLaunchKernelGGL(k_radix_scan<true>, scan_grid, scan_block, 0, st, (const uint32_t*)counts, (const uint32_t*)groups, ch,
@@ -1086,7 +1093,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
             hipLaunchKernelGGL(k_radix_scan<false>, scan_grid, scan_block, 0, st, (const uint32_t*)counts, (const uint32_t*)groups, ch,
                                digits, starts, nullptr, nullptr, nullptr);
         int32_t* ids_out = p == passes - 1 ? t->words_dev : id_buf[p & 1];
-        hipLaunchKernelGGL(k_radix_scatter, sort_grid, sort_block, radix_scatter_lds(digits), st, codes_in, ids_in, V, ch,
+        hipLaunchKernelGGL(k_radix_scatter, sort_grid, sort_block, radix_scatter_lds(digits), st, codes_in, ids_in, V, (int)W, ch,
                            shift, pass_bits, (const uint32_t*)starts, code_buf[p & 1], ids_out);
         codes_in = code_buf[p & 1];
         ids_in = ids_out;
@@ -1108,8 +1115,8 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
         return rc != LSH_OK ? rc : finish([](int64_t) { return -1; }, [&](int64_t w) { return direct_band_meta((int)w, lg); });
     }
     // (the counters are free again: at least one per chunk and band)
-    hipLaunchKernelGGL(k_key_count, sort_grid, sort_block, 0, st, codes_in, V, ch, counts);
-    hipLaunchKernelGGL(k_key_emit, sort_grid, sort_block, 0, st, codes_in, V, ch, (const uint32_t*)counts, key_code,
+    hipLaunchKernelGGL(k_key_count, key_grid, sort_block, 0, st, codes_in, V, ch, counts);
+    hipLaunchKernelGGL(k_key_emit, key_grid, sort_block, 0, st, codes_in, V, ch, (const uint32_t*)counts, key_code,
                        key_start, key_pitch, stat.n_keys);
     if (!blind) {
         lsh_status rc = read_status();
