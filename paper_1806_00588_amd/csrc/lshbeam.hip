@@ -270,12 +270,13 @@ hipError_t allow_whole_lds() {
 }
 
 // How many candidates a sentence's list will hold at least: its top-frequent words and what its hidden rows
-// hit by chance (bands independent, codes evenly spread; rows near clustered words hit more).
-inline double expected_candidates(const lsh_tables* t, const lsh_step_params* sp) {
-    const double m = t->W * std::pow((double)t->K, -(double)t->u);   // expected bands in which a row and a word collide
+// hit by chance (bands independent, codes evenly spread; rows near clustered words hit more).  For a guess that is too high as
+// often as too low: `crowding`, how many more collide because codes are not evenly spread, and `near`, words close to each hidden row.
+inline double expected_candidates(const lsh_tables* t, const lsh_step_params* sp, double crowding = 1.0, double near = 0.0) {
+    const double m = crowding * t->W * std::pow((double)t->K, -(double)t->u);   // expected bands in which a row and a word collide
     double below = 0.0, p = std::exp(-m);
     for (int i = 0; i < std::min<int>(sp->threshold, 64); ++i) { below += p; p *= m / (i + 1); }
-    const double missed = (1.0 - std::min(1.0, (double)sp->T / t->V)) * std::pow(std::min(1.0, below), sp->B);
+    const double missed = (1.0 - std::min(1.0, (double)sp->T / t->V)) * std::pow(std::max(0.0, std::min(1.0, below) - near / t->V), sp->B);
     return t->V * (1.0 - missed);
 }
 
@@ -334,17 +335,18 @@ inline bool has_chunks(const lsh_tables* t) { return t->d >= (t->dtype == LSH_F3
 
 // The first tiles that the launch of `blocks` hashing workgroups makes beside them for the fused kernel that follows: one for each CU
 // that does not hash, as far as the T top-frequent words, if they are the ids from 0 on, fill whole tiles.  They pay where they
-// save that kernel's workgroups a tile each; else they cost 1 % (what they read delays the hashing).  How long the lists will be is not known
-// (near words hit more often than by chance: up to ten times what is expected with high thresholds), so: from 0.64 expected tiles per
-// workgroup on and if they are a fifth of a tile for each.  us a step without and with them, expected tiles per workgroup: 500 bands, t = 5, d = 1000,
-// V = 40000, 12 beams 0.65: 32.1, 28.9; t = 8, d = 314, V = 1139, 4 x 2 beams 1.11: 21.9, 20.0; t = 5, d = 80, bf16, 4 x 1 0.89: 22.6, 21.6; t = 4, d = 753,
-// 4 x 5 1.27: 26.1, 26.3; t = 7, d = 672, 3 x 6 0.82: 23.0, 23.4; below the line t = 5, d = 792 bf16, 4 x 10 0.63: 24.3, 24.6; t = 8,
-// d = 520, 3 x 2 0.51: 19.0, 19.6; t = 5, d = 352 bf16, 2 x 17 0.20: 21.7, 22.6; t = 6, d = 119, 20 beams 0.36: 28.3, 26.6.
+// save that kernel's workgroups a tile each (159 drawn shapes, lists of a tile and more for each workgroup: 0.945 of the time in the geometric
+// mean, down to 0.84); with shorter lists most steps take 0.3 to 0.5 us more, as what they read delays the hashing (1.012).
+// So: where the list is expected to have 0.95 tiles for each workgroup, with codes that crowd by a fifth and 40 near words for a
+// hidden row (real lists over that guess: 0.63 off in the root mean square of the logarithm, 0.82 without), and they are a fifth of a tile
+// for each.  Over those shapes 0.9714 of the time without them; 0.66 tiles by chance alone, the best line for that, 0.9728.  us a step without and
+// with them: 500 bands, t = 5, d = 1000, V = 40000, 12 beams 32.0, 29.0; 4 x 2 beams, t = 4, d = 688 bf16, V = 3637 24.2, 20.6; 4 x 7, t = 5,
+// d = 792, V = 3755 (0.51 of a tile) 24.3, 24.6.
 FirstTiles first_tiles_plan(const lsh_tables* t, const lsh_step_params* sp, const float* H, const Workspace& w, int blocks) {
     FirstTiles f{t->E, t->ld, H, t->d, sp->S, sp->B, 0, blocks, w.logits, w.cpitch, w.records()};
     if (!has_chunks(t) || t->option(kOptFusedTile, 0) > 0 || t->opt[kOptFusedGrid] != kAuto) return f;
     const int wgs = 256 / sp->S, n = std::min({(int)std::min<int64_t>(sp->T, t->V) / kTileN, kFirstTilesMost, std::max(0, 256 - blocks) / (int)sp->S});
-    if (5 * n >= wgs && expected_candidates(t, sp) >= 0.64 * kTileN * wgs) f.tiles = n;
+    if (5 * n >= wgs && expected_candidates(t, sp, 1.2, 40.0) >= 0.95 * kTileN * wgs) f.tiles = n;
     return f;
 }
 inline int first_tiles_blocks(const FirstTiles& f) { return std::min(f.tiles * f.S, std::max(0, 256 - f.first)); }
