@@ -22,8 +22,8 @@
 // What bounds it is the pass over the embedding rows (2); the rest is a chain of short kernels.  Nothing
 // is copied to the host before the whole chain is under way where tables for the most keys a band can have
 // are small or nearly full (lshbeam.hip); parameters are drawn on the device, and one wait ends the build (with a copy
-// of the status words where something was inserted).  V = 40000, d = 1000 fp32, 8 bands of 12 bits, with the first step on the tables: 111 us, of which 30 us
-// k_row_codes (160 MB at 5.4 TB/s), 25 us the sort and the slots (count 4.8, scan 6.5, scatter 11) and 17 us the step;
+// of the status words where something was inserted).  V = 40000, d = 1000 fp32, 8 bands of 12 bits, with the first step on the tables: 107 us, of which 30 us
+// k_row_codes (160 MB at 5.4 TB/s), 23 us the sort and the slots (count 4.8, scan 6.5, scatter 10) and 16 us the step;
 // with cuckoo insertion for these codes 156, or 206 where it failed once; with the scan in one workgroup per band and a
 // sum over the chunks in front in every workgroup of the scatter 130.
 #pragma once
