@@ -3,7 +3,7 @@
 // (start, length)}).
 //
 //   1. k_build_begin: permutations checked and copied, hash parameters drawn, tables cleared.  (Where the scan
-//      writes the slots there is nothing to clear, and the first workgroups of k_row_codes do the rest: BuildFirst.)
+//      writes the slots there is nothing to clear, and with few permutations the first workgroups of k_row_codes do the rest: BuildFirst.)
 //   2. k_row_codes (candidates.h): band codes of every embedding row, [W, V].
 //   3. Every band's words are grouped by code, ids ascending inside a code: a stable radix sort of
 //      the code alone (words start in id order), up to kRadixBits bits of it per pass -- ONE pass for
@@ -97,7 +97,7 @@ __host__ __device__ inline BandMeta direct_band_meta(int w, int lg) {
 // copied, entries outside [0, d) replaced by 0 and reported (bad_perms[block], zeroed before, in host memory), the tickets zeroed.
 __global__ void __launch_bounds__(256)
 k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W, uint32_t cap, int lg, bool direct, uint64_t seed,
-              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed,
+              int attempt, const uint32_t* __restrict__ redo, uint32_t* __restrict__ failed, uint32_t* __restrict__ n_keys,
               const int32_t* __restrict__ perms_in, int n_perms, int d, int32_t* __restrict__ perms,
               uint32_t* __restrict__ bad_perms, unsigned int* __restrict__ tickets, int n_tickets) {
     const int w = blockIdx.y, tid = threadIdx.x;
@@ -106,6 +106,7 @@ k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W,
         const bool again = !redo || redo[w];
         if (first == 0) {
             failed[w] = 0u;
+            if (n_keys) n_keys[w] = 0u;
             if (again) bands[w] = direct ? direct_band_meta(w, lg) : draw_band_meta(seed, w, W, attempt, 1u << lg, lg);
         }
         if (again)
@@ -127,8 +128,9 @@ k_build_begin(uint64_t* __restrict__ table, BandMeta* __restrict__ bands, int W,
     if (tid == 0 && bad) bad_perms[blockIdx.x] = 1u;
 }
 
-// The same for direct tables whose slots the scan writes, by the first workgroups of k_row_codes: 2 us and a kernel boundary less.
+// The same for direct tables whose slots the scan writes, by the first workgroups of k_row_codes AHEAD: 2 us and a kernel boundary less.
 struct BuildFirst {
+    static constexpr bool kRaw = true;
     const int32_t* perms_in;
     int32_t* perms;
     uint32_t* bad_perms;

@@ -933,19 +933,24 @@ struct BuildBlock {  // what a build works in, kept for the next one
     ~BuildBlock() { release_block(dev, kBuildBlock, block, idle); }
 };
 
+// (`first` with kRaw: where row_codes_ahead)
 template <typename ET, class FIRST = NotFirst>
 hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, int d, const int32_t* perms, int P, int K,
                             int W, int bits, int32_t* out, int64_t row_stride, int64_t band_stride, FIRST first = {}) {
     const bool ahead = row_codes_ahead(d, sizeof(ET), P, K);
-    const hipError_t e = ahead ? allow_whole_lds<k_row_codes<ET, true, FIRST>>() : allow_whole_lds<k_row_codes<ET, false, FIRST>>();
-    if (e != hipSuccess) return e;
     const int lg = row_codes_lg_rows(n, d, sizeof(ET), P, ahead);
     const size_t lds = row_codes_lds(1 << lg, d, sizeof(ET), P, ahead);
     int64_t groups = (n + (1 << lg) - 1) >> lg;
     if (ahead) groups = std::min<int64_t>(groups, 256 * std::min<size_t>(8, 158 * 1024 / lds));   // (as many as run at a time)
-    hipLaunchKernelGGL((ahead ? k_row_codes<ET, true, FIRST> : k_row_codes<ET, false, FIRST>), dim3((unsigned)groups), dim3(kRowCodeThreads),
-                       lds, st, X, ld, n, d, perms, P, K, W, bits, lg, out, row_stride, band_stride, first);
-    return hipGetLastError();
+    auto go = [&](auto ahead_c, auto f) -> hipError_t {
+        constexpr auto kernel = k_row_codes<ET, decltype(ahead_c)::value, decltype(f)>;
+        const hipError_t e = allow_whole_lds<kernel>();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3(kRowCodeThreads), lds, st, X, ld, n, d, perms, P, K, W, bits, lg, out,
+                           row_stride, band_stride, f);
+        return hipGetLastError();
+    };
+    return ahead ? go(std::true_type{}, first) : go(std::false_type{}, NotFirst{});
 }
 
 // The table build (build_tables.h).  The bucket and cuckoo tables are made on the device; `on_host`, a band
@@ -1044,7 +1049,8 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
     const dim3 begin_grid(kBuildBeginBlocks, (unsigned)W + 1), b256(256);
     auto begin = [&](int attempt, const uint32_t* redo, bool with_tables) {
         hipLaunchKernelGGL(k_build_begin, begin_grid, b256, 0, st, table, t->bands_dev, (int)W,
-                           with_tables ? 1u << lg : 0u, lg, direct, seed, attempt, redo, stat.failed[attempt & 1],
+                           with_tables && !emit ? 1u << lg : 0u, lg, direct, seed, attempt, redo, stat.failed[attempt & 1],
+                           emit ? stat.n_keys : nullptr,
                            attempt || (with_tables && !blind) ? nullptr : perms_in, (int)n_perms, t->d, t->perms_dev, report.words,
                            t->tickets_dev, (int)n_tickets);
     };
@@ -1054,7 +1060,7 @@ lsh_status build_all(lsh_tables* t, hipStream_t st, const int32_t* perms_in, uin
             ? launch_row_codes(st, (const float*)t->E, t->ld, V, t->d, perms, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V, first)
             : launch_row_codes(st, (const uint16_t*)t->E, t->ld, V, t->d, perms, t->P, t->K, t->W, t->bits, t->codes_dev, 1, V, first);
     };
-    if (emit) {
+    if (emit && row_codes_ahead(t->d, t->dtype == LSH_F32 ? 4 : 2, t->P, t->K)) {
         HIP_TRY(row_codes(perms_in, BuildFirst{perms_in, t->perms_dev, report.words, t->bands_dev, stat.n_keys, t->tickets_dev, (int)n_perms,
                                                t->d, (int)W, lg, (int)n_tickets}));
     } else {
