@@ -215,6 +215,9 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
         LSH_TRACE_ANY(1, 14);
     } else if (g != 0) {
         return;                // an empty list, or all made: workgroup 0 of the sentence ends the step
+    } else {                   // (the ids that its waves have just stored are read by others of them)
+        publish_wait();
+        __syncthreads();
     }
     select_sentence<true, true>(sh, s, logits, cpitch, recs.rec, recs.id2, recs.pitch, cand, nullptr, C, V, B,
                           tail.beam_scores, tail.lse, tail.out_beam, tail.out_word, tail.out_score,
