@@ -1065,10 +1065,21 @@ constexpr bool stream_must_trim(bool bf16, int PARTS) { return bf16 && PARTS > 3
 // fifth slower and then had the CU to itself, half used.  (The first 256 workgroups of a launch go to a CU each.)  So the waves of the
 // others have the higher priority in a part of their groups of tiles: in five of eight, and as good as always in the first eight,
 // for workgroups that have no more.  64 x 10 beams, V = 200000, d = 1024 bf16: workgroups took 74 to 109 us for equal shares, 101 to
-// 120 so; sentences that go through the vocabulary side by side also find more in L2; a step 154.4 -> 144.0 us (half of the groups
-// 145.8, six of eight 146.4, all of them 154.2); 32 x 10, V = 40000, d = 1000 fp32, four groups: 45.5 -> 44.4 (half 45.4).
+// 120 so; a step over one input 154.4 -> 144.0 us (half of the groups 145.8, six of eight 146.4, all of them 154.2), over changing ones 157.2 ->
+// 150.2; 32 x 10, V = 40000, d = 1000 fp32, four groups: 45.5 -> 44.4 (half 45.4).  Where three share a CU the second and the third have it: 20 x 20 to
+// 60 x 24 beams, d = 100 to 512 bf16, V = 60000 0.98 to 1.00 of the time, 24 x 32, d = 100 45.7 -> 44.5; fp32 20 x 20, d = 200 42.7 -> 42.3, 60 x 30,
+// d = 300 120.6 -> 118.7, d = 64 98.2 -> 98.8; up to 6 hidden rows 1.00 to 1.004.
 constexpr uint32_t kCus = 256;
 __device__ __forceinline__ bool young_first(int g) { return (g < 8 ? 0xFE : 0xB6) >> (g & 7) & 1; }
+// Whether the hidden rows (bf16 words; that many in a workgroup's group) come through LDS (STAGE).  A lane that loads its operand itself, two
+// pieces of 16 bytes, has every 16 lanes touch as many rows twice as there are hidden rows, 16 at most; through LDS each takes a trip more, and
+// rows that only fill a group of 16 cost as much as others.  us a step without and with (V = 40000 .. 60000): d = 1536, 32 x 16 beams 44.3, 39.8, 24 x 6
+// 28.9, 27.3, 24 x 3 26.1, 25.3, 40 x 1 26.9, 26.7; d = 1064 (two of three parts in the ring) 40.0, 38.6, 28.2, 27.6, 26.0, 26.1, 24 x 2 24.0, 24.3; d = 1024
+// 36.0, 34.1, 24.9, 24.6, 23.0, 22.8, 40 x 1 23.7, 23.9; d = 640 35.5, 34.5, 25.1, 25.1, 23.5, 23.6, 24 x 2 22.2, 22.5; d = 512 29.5, 27.7, 24 x 8 21.9, 21.8, 24 x 4
+// 19.9, 20.1, 24 x 2 18.9, 19.3; d = 256 27.4, 26.7, 20.4, 20.3, 18.0, 18.2; d = 96 29.6, 29.5, 20.0, 20.3, 24 x 12 22.1, 22.4; two row groups: 24 x 32, d = 512 45.9,
+// 43.9, d = 256 40.1, 39.1, d = 100 45.0, 44.5.  64 x 10, V = 200000, d = 1024 99.6, 98.3 (lists of 6000).  With fp32 words, one piece: 32 x 10, d = 1000, 44.7, 45.1.
+// Units that the ring does not hold are loaded behind it; their lines brought to L2 in front cost more (32 x 10, d = 1536 34.5 -> 34.9; 8 x 32, d = 512 32.0 -> 32.4).
+constexpr bool stream_stages(bool bf16, int KSN, int rows) { return bf16 && rows >= (KSN == 4 ? 3 : KSN == 2 ? 8 : 17); }
 // f(integral_constant 0), ..., f(integral_constant N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) {
@@ -1135,7 +1146,8 @@ __device__ __forceinline__ StreamDeal deal_by_count(const int32_t* __restrict__ 
     return deal_by_weight(s, (uint32_t)__builtin_amdgcn_readfirstlane(count[s]), w0, w1, W, G, shared, x, bx);
 }
 
-template <typename ET, int MT, int KSN, int PARTS, bool EVEN, bool TRIM>
+// STAGE: see stream_stages.
+template <typename ET, int MT, int KSN, int PARTS, bool EVEN, bool TRIM, bool STAGE = false>
 __global__ void __launch_bounds__(256, (stream_wgs(sizeof(ET) == 2, MT, KSN, PARTS)))
 k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __restrict__ H, int S, int B,
                 int group_rows /*row group g takes rows [g, g + 1) * group_rows of every sentence; <= 16 MT*/,
@@ -1180,13 +1192,12 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     const uint32_t ring_at = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)ring);
     auto ntiles_of = [&](int C) { return (uint32_t)((C + kTileN - 1) / kTileN); };
     const int nks = (d + KSTEP - 1) / KSTEP, nst = (nks + 3) >> 2, k0 = q * nst * KSTEP;   // steps of a wave's quarter
-    // bf16 words: the hidden rows of the sentence known in front come to the ring, where nothing is yet, while the count and the
-    // candidates are on their way: as many units (part p of row group m is number m PARTS + p) as it holds.  (A lane that loads its
-    // operand itself, two pieces of 16 bytes, has every 16 lanes touch 16 rows twice.  64 x 10 beams, V = 200000, d = 1024: 150.2 ->
-    // 148.2 us a step; eight steps of 8 x 5, V = 40000: 190.8 -> 190.3.  With fp32 words, one piece: 32 x 10, d = 1000, 44.7 -> 45.1.)
-    // Pieces of a row lie as those of the words do, in blocks of PPH.
+    // STAGE: as many units of the hidden rows of the sentence known in front (part p of row group m is number m PARTS + p) as the ring
+    // holds come there, where nothing is yet, while the count and the candidates are on their way.  Pieces of a row lie as those of
+    // the words do, in blocks of PPH.
     constexpr int SB = VEC / 4, PPH = 4 * KSN * SB < 16 ? 4 * KSN * SB : 16, SUBS = 4 * KSN * SB / PPH, SHH = PPH == 4 ? 2 : PPH == 8 ? 1 : 0;
-    constexpr int HELD = RING * NI / (KSN * SB), STAGED = EVEN || !BF ? 0 : HELD < MT * PARTS ? HELD : MT * PARTS;
+    constexpr int UNITS = MT * PARTS, HELD = RING * NI / (KSN * SB), STAGED = !STAGE ? 0 : HELD < UNITS ? HELD : UNITS;
+    static_assert(!STAGE || !EVEN, "an even cut knows no sentence in front");
     auto stage_hidden = [&](int at_s) __attribute__((always_inline)) {
         const float* hb = H + ((size_t)at_s * B + row0) * d;
         const int lrow = ln / PPH, lp = ln % PPH;
@@ -1209,10 +1220,11 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
     int s = 0, C = 0;
     TileRun run{};
     uint32_t seg = 0, seg_end = 0, wg_end = 0;
-    bool moved = EVEN;                                                        // (uniform) the hidden rows in the ring are not these
+    uint32_t s0 = 0;                                                          // the sentence known in front
+    bool moved = false;                                                       // (uniform) it is another now
     auto count_of = [&](int at) { const int n = count ? count[min(at, S - 1)] : V; return at < S ? n : 0; };
     if constexpr (!EVEN) {
-        const uint32_t s0 = __builtin_amdgcn_readfirstlane(per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs));
+        s0 = __builtin_amdgcn_readfirstlane(per > 0 ? bx / (uint32_t)per : dealt_sentence(bx, xcd, (uint32_t)S, (uint32_t)wgs));
         if constexpr (STAGED > 0) stage_hidden((int)s0);
         else {   // the hidden rows' lines into this XCD's L2 (and the ring, where nothing is yet) while the count is on its way
             const char* hb = reinterpret_cast<const char*>(H + ((size_t)s0 * B + row0) * d);
@@ -1301,12 +1313,12 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         wait_vmem<0>();
         lds_barrier();
         if constexpr (!EVEN) {
-            moved = wave_read_lane(shares[8], 0) != 0u;
-            if (moved) {
+            if (wave_read_lane(shares[8], 0)) {
                 const uint4 x = reinterpret_cast<const uint4*>(shares)[0], y = reinterpret_cast<const uint4*>(shares)[1];
                 s = wave_read_lane(x.x, 0); C = wave_read_lane(x.y, 0);
                 run = uniform(TileRun{x.z, x.w, y.x, y.y, y.z, y.w});
                 n = (int)run.n;
+                moved = s != (int)s0;
                 if (n > 0) {
                     load_ids(0);
                     wait_vmem<0>();
@@ -1399,24 +1411,25 @@ k_logits_stream(const ET* __restrict__ E, int64_t ld, int d, const float* __rest
         if (STAGED == 0 || moved) {   // (uniform)
             fill_ring();
             load_hidden(std::integral_constant<int, 0>{});
-        } else {
+        } else {   // (the candidates are asked for before the values are split: 12 x 12 beams, d = 640, V = 100000 31.8 -> 31.1 us a step)
+            float x[STAGED * KSN + 1][VEC];
 #pragma unroll
-            for (int i = 0; i < STAGED * KSN; ++i) {
-                float x[VEC];
+            for (int i = 0; i < STAGED * KSN; ++i)
 #pragma unroll
                 for (int e = 0; e < SB; ++e) {
                     const int p = (i % KSN * 4 + kq) * SB + e;                // (p / PPH does not depend on the lane)
                     const uint4 v = *reinterpret_cast<const uint4*>(ring + (i / KSN * SUBS + (i % KSN * 4 * SB) / PPH) * (PPH * 256) + (col * PPH + ((p % PPH) ^ (col >> SHH))) * 16);
-                    x[4 * e] = __uint_as_float(v.x); x[4 * e + 1] = __uint_as_float(v.y); x[4 * e + 2] = __uint_as_float(v.z); x[4 * e + 3] = __uint_as_float(v.w);
+                    x[i][4 * e] = __uint_as_float(v.x); x[i][4 * e + 1] = __uint_as_float(v.y); x[i][4 * e + 2] = __uint_as_float(v.z); x[i][4 * e + 3] = __uint_as_float(v.w);
                 }
-                keep(i / (PARTS * KSN), i % (PARTS * KSN), x);
-            }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // (they have left the ring)
             __builtin_amdgcn_sched_barrier(0);
             fill_ring();
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < STAGED * KSN; ++i) keep(i / (PARTS * KSN), i % (PARTS * KSN), x[i]);
             load_hidden(std::integral_constant<int, STAGED>{});
         }
-        if (STAGED < MT * PARTS || moved) __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the compiler must not wait for them in the loop
+        if (STAGED < UNITS || moved) __builtin_amdgcn_s_waitcnt(0x0F70);       // vmcnt(0): the compiler must not wait for them in the loop
         __builtin_amdgcn_sched_barrier(0);
         LSH_TRACE_WG(10);
         float out[GT][MT];

@@ -500,12 +500,18 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     }
     if (!same) per = 0;
     if (per > 0) wgs = per * sp->S;
+    const bool stage = stream_stages(sizeof(ET) == 2, p.ksn, rows);
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \
-    launch(cx, 1, even ? k_logits_stream<ET, MTV, KSNV, PV, true, stream_may_trim(PV) || stream_must_trim(sizeof(ET) == 2, PV)>  \
-                  : p.short_last && stream_may_trim(PV) ? k_logits_stream<ET, MTV, KSNV, PV, false, stream_may_trim(PV) || stream_must_trim(sizeof(ET) == 2, PV)> \
-                  : k_logits_stream<ET, MTV, KSNV, PV, false, stream_must_trim(sizeof(ET) == 2, PV)>,             \
-           dim3(8 * wgs * ngroups), dim3(256), StreamLds<MTV, KSNV>::kBytes, (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per, shared, cand, count, t->V, w.logits, \
-           w.cpitch, w.records())
+    do {                                                                                                      \
+        constexpr bool must = stream_must_trim(sizeof(ET) == 2, PV), may = stream_may_trim(PV) || must;       \
+        constexpr bool SOME = stream_stages(sizeof(ET) == 2, KSNV, kTileM * MTV), ALL = stream_stages(sizeof(ET) == 2, KSNV, kTileM * (MTV - 1) + 1);  \
+        const bool trim = may && p.short_last;                                                                \
+        launch(cx, 1, even ? k_logits_stream<ET, MTV, KSNV, PV, true, may>                                    \
+                      : trim ? (stage ? k_logits_stream<ET, MTV, KSNV, PV, false, may, SOME> : k_logits_stream<ET, MTV, KSNV, PV, false, may, ALL>) \
+                      : stage ? k_logits_stream<ET, MTV, KSNV, PV, false, must, SOME> : k_logits_stream<ET, MTV, KSNV, PV, false, must, ALL>,     \
+               dim3(8 * wgs * ngroups), dim3(256), StreamLds<MTV, KSNV>::kBytes, (const ET*)t->E, t->ld, t->d, H, sp->S, sp->B, rows, wgs, ngroups, per, shared, cand, count, \
+               t->V, w.logits, w.cpitch, w.records());                                                        \
+    } while (0)
 #define LSH_STREAM2(KSNV, PV) do { if (rows > kTileM) LSH_STREAM(2, KSNV, PV); else LSH_STREAM(1, KSNV, PV); } while (0)
     if (p.ksn == 1) LSH_STREAM2(1, 1); else if (p.ksn == 2 && p.parts == 2) LSH_STREAM2(2, 2); else if (p.ksn == 2) LSH_STREAM2(2, 1);
     else if constexpr (sizeof(ET) == 2) switch (p.parts) { case 2: LSH_STREAM(1, 4, 2); break; case 3: LSH_STREAM(1, 4, 3); break; default: LSH_STREAM(1, 4, 4); }
@@ -707,8 +713,11 @@ hipError_t allow_logits_lds() {
 #define LSH_ALLOW(MTV, KSNV, PV)                                                                        \
     do {                                                                                            \
         constexpr bool must = stream_must_trim(sizeof(ET) == 2, PV), may = stream_may_trim(PV) || must; \
-        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, must>>();    \
-        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, may>>();     \
+        constexpr bool SOME = stream_stages(sizeof(ET) == 2, KSNV, kTileM * MTV), ALL = stream_stages(sizeof(ET) == 2, KSNV, kTileM * (MTV - 1) + 1);  \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, must, SOME>>();  \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, may, SOME>>();   \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, must, ALL>>();   \
+        if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, may, ALL>>();    \
         if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, true, may>>();      \
     } while (0)
     LSH_ALLOW(1, 1, 1); LSH_ALLOW(1, 2, 1); LSH_ALLOW(1, 4, 2); LSH_ALLOW(1, 4, 3); LSH_ALLOW(1, 4, 4);
