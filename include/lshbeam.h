@@ -237,6 +237,8 @@ lsh_status lsh_debug_logprobs(const lsh_tables* t, const void* workspace_dev,
  *   "logits_estage"  0: 33..64 beams take the grouped driver instead of candidate rows through LDS
  *   "estage_union"   0: sentences hashed in parts get their candidate list from a kernel of its own
  *                    before that driver, instead of inside it
+ *   "first_tiles"    n: where the fused kernel follows a hashing kernel, up to n tiles at the head of every list are
+ *                    made beside the hashing (0: none), as far as there are top-frequent words and idle CUs
  *   "hlds_rem"       n: a last round of tiles filling at most 1/n of the waves is split over k (4)
  *   "logits_planes"  0: no bf16 planes: bf16 rows are widened to fp32 instead of meeting planes of H,
  *                    and the full vocabulary's fp32 rows take the fp32 instructions

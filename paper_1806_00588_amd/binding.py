@@ -27,7 +27,7 @@ EXPORTED_SYMBOLS = (
 OPTION_AUTO = -1
 OPTION_NAMES = ("fused", "fused_grid", "logits_grid", "logits_waves", "logits_hlds", "logits_estage",
                 "hlds_rem", "logits_planes", "hlds_rows", "part_rows", "stage_rows", "one_launch", "fused_tile",
-                "estage_union")
+                "estage_union", "first_tiles")
 
 
 class LshBeamError(RuntimeError):

@@ -59,11 +59,12 @@ struct TailArgs {
 };
 
 // The first tiles of every list, made beside the hashing (k_hit_rows, k_part_bitmaps).  The top-frequent words are members of every
-// candidate list, and a vocabulary sorted by frequency has them first: the ids 0, 1, 2, ... stand at the positions 0, 1, 2, ... of
-// every list, whatever the hashing finds.  Their logits need nothing that the hashing makes, and that runs on a few dozen CUs.  So its launch
-// has further workgroups that contract the sentences' hidden rows with the words 0 .. 16 tiles - 1 and leave logits and
-// records where the tiles of a list that begins with them have theirs, with the same sums.  Whether a list does is seen once its
-// bitmap is there (tiles_done); if not, its tiles are made as if nothing had been.
+// candidate list, and of a vocabulary sorted by frequency they are the lowest ids: a list of them that begins 0, 1, 2, ... has these ids
+// stand at the positions 0, 1, 2, ... of every candidate list, whatever the hashing finds.  Their logits need nothing that the hashing
+// makes, and that runs on a few dozen CUs.  So its launch has further workgroups that contract the sentences' hidden rows with the words
+// 0 .. 16 tiles - 1 and leave logits and records where the tiles of such a candidate list have theirs, with the same sums.  They, and later
+// k_union_logits, look whether the top-frequent list begins so (starts_with_ids); if not, they make nothing and every tile is made there.
+// (4 us of tiles that nobody used: 1 x 30 beams, d = 1536, V = 40000, top-frequent words anywhere, hashed in parts 35.9 us a step, 30.4 so.)
 struct FirstTiles {
     const void* E;
     int64_t ld;
@@ -71,16 +72,33 @@ struct FirstTiles {
     int d, S, B;
     int tiles;     // of 16 words; 0: none are made
     int first;     // first workgroup of the launch that makes them
+    const int32_t* topfreq;
     float* logits;
     int64_t cpitch;
     TileRecords recs;
 };
-constexpr int kFirstTilesMost = 2 * kWave;   // a lane of tiles_done per bitmap word
+constexpr int kFirstTilesMost = 2 * kCandThreads / kTileN;   // a thread looks at two ids
+// Of a workgroup that holds the first of its list's ids in `mine` (any value past the list): *other becomes 1 if one of the first n is not the
+// number of its place.  `other` is 0 before and to be read behind a barrier.
+__device__ __forceinline__ void starts_with_ids(const int32_t* __restrict__ list, int32_t mine, int n, uint32_t* other) {
+    const int tid = threadIdx.x, i = tid + kCandThreads;
+    if ((tid < n && mine != tid) || (i < n && list[i] != i)) *other = 1u;
+}
 template <typename ET> struct FirstTilesBeside {
     using Args = FirstTiles;
     static constexpr bool kAny = true;
+    static_assert(kFusedWaves * 4 * kWave + 1 <= 3 * kCandThreads + kHitListMin && kFusedWaves * 4 * kWave + 1 <= kCandStage,
+                  "its LDS is that of k_hit_rows and of k_part_bitmaps");
     static __device__ __forceinline__ void run(const Args& a, uint32_t* smem) {
         float (*red)[4][kWave] = reinterpret_cast<float (*)[4][kWave]>(smem);
+        uint32_t* other = smem + kFusedWaves * 4 * kWave;
+        const int n = a.tiles * kTileN, tid = threadIdx.x;
+        const int32_t mine = tid < n ? a.topfreq[tid] : -1;
+        if (tid == 0) *other = 0u;
+        __syncthreads();
+        starts_with_ids(a.topfreq, mine, n, other);
+        __syncthreads();
+        if (*other) return;
         for (int i = (int)blockIdx.x - a.first; i < a.tiles * a.S; i += (int)gridDim.x - a.first) {
             const int s = i % a.S, nt = i / a.S;
             logits_tile_all_rows<ET, kFusedWaves, 64 / kFusedWaves, true, 0, true>(
@@ -88,12 +106,6 @@ template <typename ET> struct FirstTilesBeside {
         }
     }
 };
-// How many of a list's first `tiles` tiles are made: all of them, or none.  Called by whole waves, with the list's bitmap.
-__device__ __forceinline__ int tiles_done(const uint32_t* bm, int tiles) {
-    const int ln = lane_id(), n = tiles * kTileN - 32 * ln;                   // (at most 64 words)
-    const uint32_t want = n >= 32 ? 0xFFFFFFFFu : n > 0 ? 0xFFFFu : 0u;       // (a multiple of 16)
-    return tiles > 0 && __ballot((want & ~(want ? bm[ln] : 0u)) != 0u) == 0ull ? tiles : 0;
-}
 
 // What follows the bitmap in both fused kernels.  Thread t owns a contiguous run of bitmap words;
 // a workgroup scan of the runs' popcounts tells it which output positions of the ascending
@@ -282,12 +294,15 @@ k_union_logits(const uint32_t* __restrict__ part_bitmaps, int nparts, const int3
     float (*red)[4][kWave] = reinterpret_cast<float (*)[4][kWave]>(tile_ids + kFusedTileIdWords);
 
     const int32_t tf_first = (tid < T) ? topfreq[tid] : -1;
+    uint32_t* other = wsum + 32;                                          // (the scan's scratch is wsum[0..16])
+    if (tid == 0) *other = 0u;
     union_row_bitmaps(part_bitmaps + (size_t)s * nparts * nwords, nparts, nwords, bm);
     __syncthreads();
     mark_id_list(bm, V, topfreq, T, tf_first);
+    if (first_tiles > 0) starts_with_ids(topfreq, tf_first, first_tiles * kTileN, other);
     __syncthreads();
     tiles_from_bitmap<ET, CHUNKS, ONE_LAUNCH>(bm, wsum, tile_ids, red, nullptr, E, ld, d, H, B, V, s, g, G, cand,
-                                   count, logits, cpitch, recs, tail, smem, tiles_done(bm, first_tiles));
+                                   count, logits, cpitch, recs, tail, smem, *other ? 0 : first_tiles);
 }
 
 }  // namespace lshbeam

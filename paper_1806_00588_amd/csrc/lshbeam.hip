@@ -83,13 +83,13 @@ struct KeptBlock { void* p = nullptr; size_t bytes = 0; };   // device memory th
 enum Opt {
     kOptFused, kOptFusedGrid, kOptLogitsGrid, kOptLogitsWaves, kOptLogitsHlds, kOptLogitsEstage,
     kOptHldsRem, kOptLogitsPlanes, kOptHldsRows, kOptPartRows, kOptStageRows, kOptOneLaunch, kOptFusedTile,
-    kOptEstageUnion, kNumOpts
+    kOptEstageUnion, kOptFirstTiles, kNumOpts
 };
 constexpr int kAuto = -1;
 const char* const kOptNames[kNumOpts] = {
     "fused", "fused_grid", "logits_grid", "logits_waves", "logits_hlds", "logits_estage",
     "hlds_rem", "logits_planes", "hlds_rows", "part_rows", "stage_rows", "one_launch", "fused_tile",
-    "estage_union"};
+    "estage_union", "first_tiles"};
 
 }  // namespace
 
@@ -334,7 +334,7 @@ int part_rows_of(const lsh_tables* t, const lsh_step_params* sp, int stage_words
 inline bool has_chunks(const lsh_tables* t) { return t->d >= (t->dtype == LSH_F32 ? 4 : 8); }
 
 // The first tiles that the launch of `blocks` hashing workgroups makes beside them for the fused kernel that follows: one for each CU
-// that does not hash, as far as the T top-frequent words, if they are the ids from 0 on, fill whole tiles.  They pay where they
+// that does not hash, as far as the T top-frequent words fill whole tiles (option first_tiles: so many at most).  They pay where they
 // save that kernel's workgroups a tile each (159 drawn shapes, lists of a tile and more for each workgroup: 0.945 of the time in the geometric
 // mean, down to 0.84); with shorter lists most steps take 0.3 to 0.5 us more, as what they read delays the hashing (1.012).
 // So: where the list is expected to have 0.95 tiles for each workgroup, with codes that crowd by a fifth and 40 near words for a
@@ -342,11 +342,12 @@ inline bool has_chunks(const lsh_tables* t) { return t->d >= (t->dtype == LSH_F3
 // for each.  Over those shapes 0.9714 of the time without them; 0.66 tiles by chance alone, the best line for that, 0.9728.  us a step without and
 // with them: 500 bands, t = 5, d = 1000, V = 40000, 12 beams 32.0, 29.0; 4 x 2 beams, t = 4, d = 688 bf16, V = 3637 24.2, 20.6; 4 x 7, t = 5,
 // d = 792, V = 3755 (0.51 of a tile) 24.3, 24.6.
-FirstTiles first_tiles_plan(const lsh_tables* t, const lsh_step_params* sp, const float* H, const Workspace& w, int blocks) {
-    FirstTiles f{t->E, t->ld, H, t->d, sp->S, sp->B, 0, blocks, w.logits, w.cpitch, w.records()};
+FirstTiles first_tiles_plan(const lsh_tables* t, const lsh_step_params* sp, const float* H, const int32_t* topfreq, const Workspace& w, int blocks) {
+    FirstTiles f{t->E, t->ld, H, t->d, sp->S, sp->B, 0, blocks, topfreq, w.logits, w.cpitch, w.records()};
     if (!has_chunks(t) || t->option(kOptFusedTile, 0) > 0 || t->opt[kOptFusedGrid] != kAuto) return f;
     const int wgs = 256 / sp->S, n = std::min({(int)std::min<int64_t>(sp->T, t->V) / kTileN, kFirstTilesMost, std::max(0, 256 - blocks) / (int)sp->S});
-    if (5 * n >= wgs && expected_candidates(t, sp, 1.2, 40.0) >= 0.95 * kTileN * wgs) f.tiles = n;
+    if (t->opt[kOptFirstTiles] != kAuto) f.tiles = std::min(n, t->opt[kOptFirstTiles]);
+    else if (5 * n >= wgs && expected_candidates(t, sp, 1.2, 40.0) >= 0.95 * kTileN * wgs) f.tiles = n;
     return f;
 }
 inline int first_tiles_blocks(const FirstTiles& f) { return std::min(f.tiles * f.S, std::max(0, 256 - f.first)); }
@@ -1211,7 +1212,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
     FirstTiles first{};
     if (!sp->full_vocab && sp->threshold > 1) {
         const int blocks = sp->S * sp->B * kHitSlices;
-        if (fused) first = first_tiles_plan(t, sp, H_dev, w, blocks);
+        if (fused) first = first_tiles_plan(t, sp, H_dev, topfreq_dev, w, blocks);
         const dim3 grid(blocks + first_tiles_blocks(first)), block(kCandThreads);
 #define LSH_HIT_ROWS(BESIDE, ...) launch(cx, 3, k_hit_rows<BESIDE>, grid, block, (size_t)t->wg_hit_rows_lds, ca, (int)sp->threshold, t->hit_list_cap, w.row_bitmaps, __VA_ARGS__)
         if (!first.tiles) LSH_HIT_ROWS(Alone, Alone::Args{});
@@ -1224,7 +1225,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
         nparts = (sp->B + pr - 1) / pr;
         ca.stage_words = candidates_min_stage(t->d);
         set_derived(ca);
-        if (fused) first = first_tiles_plan(t, sp, H_dev, w, sp->S * nparts);
+        if (fused) first = first_tiles_plan(t, sp, H_dev, topfreq_dev, w, sp->S * nparts);
         const dim3 grid(sp->S * nparts + first_tiles_blocks(first)), block(kCandThreads);
 #define LSH_PARTS(BESIDE, ...) launch(cx, 4, k_part_bitmaps<BESIDE>, grid, block, (size_t)t->wg_candidates_lds, ca, pr, nparts, w.row_bitmaps, __VA_ARGS__)
         if (!first.tiles) LSH_PARTS(Alone, Alone::Args{});
