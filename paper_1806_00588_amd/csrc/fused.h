@@ -78,6 +78,22 @@ struct FirstTiles {
     TileRecords recs;
 };
 constexpr int kFirstTilesMost = 2 * kCandThreads / kTileN;   // a thread looks at two ids
+// The first tiles that the launch of `blocks` hashing workgroups makes beside them for the fused kernel that follows: one for each CU
+// that does not hash, as far as the top-frequent words fill whole tiles (option first_tiles: so many at most).  They pay where they save that
+// kernel's workgroups a tile each, 420 drawn calls with words in clusters of 5, 40 and 400 (a list's tiles for each workgroup : time with them over
+// time without, geometric mean): below 0.9 1.01, 0.2 to 0.5 us, as what they read delays the hashing; 1 to 1.2 0.918, 1.2 to 1.6 0.927, 1.6 to 3
+// 0.95, beyond 0.99.  So: where chance alone is expected to give each workgroup 0.55 of a tile (real lists hold that and more: 0.9666 of the
+// time, at worst 1.025; 0.9598 would be all that can be had; from 0.4 on 0.9658, 0.7 0.9683, 1.0 0.9735), and the first tiles are a fifth of one for each.
+// Two row groups take longer for a tile of long rows than the hashing does, and lists of short codes are as long as chance makes them: from one tile
+// on (0.9734, at worst 1.095; from 0.9 on 0.9722, 1.168; from 0.55 on 0.9885, 1.197.  1 x 30 beams, d = 1536, V = 40000, 0.9 of a tile: 30.4
+// us a step, 35.4 with them).  us a step without and with them: 500 bands, t = 5, d = 1000, V = 40000, 12 beams 31.8, 28.8; 4 x 2 beams, t = 4, d = 688 bf16,
+// V = 3637 23.9, 20.1.  Top-frequent lists that do not begin 0, 1, 2, ...: the first of these 32.3 with the kernel that would make them, 32.2 without.
+// (words: those that a sentence's list is expected to hold by chance; wanted: the option, or -1.)
+inline int first_tiles_count(int S, int B, int T, int V, int blocks, double words, int wanted) {
+    const int wgs = 256 / S, n = std::min({std::min(T, V) / kTileN, kFirstTilesMost, std::max(0, 256 - blocks) / S});
+    if (wanted >= 0) return std::min(n, wanted);
+    return 5 * n >= wgs && words >= (B > kTileM ? 1.0 : 0.55) * kTileN * wgs ? n : 0;
+}
 // Of a workgroup that holds the first of its list's ids in `mine` (any value past the list): *other becomes 1 if one of the first n is not the
 // number of its place.  `other` is 0 before and to be read behind a barrier.
 __device__ __forceinline__ void starts_with_ids(const int32_t* __restrict__ list, int32_t mine, int n, uint32_t* other) {

@@ -270,13 +270,12 @@ hipError_t allow_whole_lds() {
 }
 
 // How many candidates a sentence's list will hold at least: its top-frequent words and what its hidden rows
-// hit by chance (bands independent, codes evenly spread; rows near clustered words hit more).  For a guess that is too high as
-// often as too low: `crowding`, how many more collide because codes are not evenly spread, and `near`, words close to each hidden row.
-inline double expected_candidates(const lsh_tables* t, const lsh_step_params* sp, double crowding = 1.0, double near = 0.0) {
-    const double m = crowding * t->W * std::pow((double)t->K, -(double)t->u);   // expected bands in which a row and a word collide
+// hit by chance (bands independent, codes evenly spread; rows near clustered words hit more).
+inline double expected_candidates(const lsh_tables* t, const lsh_step_params* sp) {
+    const double m = t->W * std::pow((double)t->K, -(double)t->u);   // expected bands in which a row and a word collide
     double below = 0.0, p = std::exp(-m);
     for (int i = 0; i < std::min<int>(sp->threshold, 64); ++i) { below += p; p *= m / (i + 1); }
-    const double missed = (1.0 - std::min(1.0, (double)sp->T / t->V)) * std::pow(std::max(0.0, std::min(1.0, below) - near / t->V), sp->B);
+    const double missed = (1.0 - std::min(1.0, (double)sp->T / t->V)) * std::pow(std::min(1.0, below), sp->B);
     return t->V * (1.0 - missed);
 }
 
@@ -333,21 +332,11 @@ int part_rows_of(const lsh_tables* t, const lsh_step_params* sp, int stage_words
 // Whether a row of E holds a 16-byte chunk: what every contraction but the elementwise forms needs.
 inline bool has_chunks(const lsh_tables* t) { return t->d >= (t->dtype == LSH_F32 ? 4 : 8); }
 
-// The first tiles that the launch of `blocks` hashing workgroups makes beside them for the fused kernel that follows: one for each CU
-// that does not hash, as far as the T top-frequent words fill whole tiles (option first_tiles: so many at most).  They pay where they
-// save that kernel's workgroups a tile each (159 drawn shapes, lists of a tile and more for each workgroup: 0.945 of the time in the geometric
-// mean, down to 0.84); with shorter lists most steps take 0.3 to 0.5 us more, as what they read delays the hashing (1.012).
-// So: where the list is expected to have 0.95 tiles for each workgroup, with codes that crowd by a fifth and 40 near words for a
-// hidden row (real lists over that guess: 0.63 off in the root mean square of the logarithm, 0.82 without), and they are a fifth of a tile
-// for each.  Over those shapes 0.9714 of the time without them; 0.66 tiles by chance alone, the best line for that, 0.9728.  us a step without and
-// with them: 500 bands, t = 5, d = 1000, V = 40000, 12 beams 32.0, 29.0; 4 x 2 beams, t = 4, d = 688 bf16, V = 3637 24.2, 20.6; 4 x 7, t = 5,
-// d = 792, V = 3755 (0.51 of a tile) 24.3, 24.6.
+// The first tiles made beside the hashing (first_tiles_count).
 FirstTiles first_tiles_plan(const lsh_tables* t, const lsh_step_params* sp, const float* H, const int32_t* topfreq, const Workspace& w, int blocks) {
     FirstTiles f{t->E, t->ld, H, t->d, sp->S, sp->B, 0, blocks, topfreq, w.logits, w.cpitch, w.records()};
     if (!has_chunks(t) || t->option(kOptFusedTile, 0) > 0 || t->opt[kOptFusedGrid] != kAuto) return f;
-    const int wgs = 256 / sp->S, n = std::min({(int)std::min<int64_t>(sp->T, t->V) / kTileN, kFirstTilesMost, std::max(0, 256 - blocks) / (int)sp->S});
-    if (t->opt[kOptFirstTiles] != kAuto) f.tiles = std::min(n, t->opt[kOptFirstTiles]);
-    else if (5 * n >= wgs && expected_candidates(t, sp, 1.2, 40.0) >= 0.95 * kTileN * wgs) f.tiles = n;
+    f.tiles = first_tiles_count(sp->S, sp->B, sp->T, t->V, blocks, expected_candidates(t, sp), t->opt[kOptFirstTiles]);
     return f;
 }
 inline int first_tiles_blocks(const FirstTiles& f) { return std::min(f.tiles * f.S, std::max(0, 256 - f.first)); }
