@@ -1257,9 +1257,8 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
 #define LSH_CAND_LOGITS2(ET, AL)                                                                  \
     do {                                                                                         \
         const ET* e = nullptr;                                                                   \
-        constexpr int kStep = 4 * ElemTraits<ET>::VEC;                                           \
         if (selected) LSH_CAND_LOGITS(ET, AL, true);                                             \
-        else if (AL && (t->d + kStep - 1) / kStep >= kQuadsMinSteps) LSH_CAND_LOGITS(ET, AL, false, AL); \
+        else if (AL && takes_quads(sizeof(ET) == 2, t->d, t->ld)) LSH_CAND_LOGITS(ET, AL, false, AL); \
         else LSH_CAND_LOGITS(ET, AL, false);                                                     \
     } while (0)
             if (f32) { if (al) LSH_CAND_LOGITS2(float, true); else LSH_CAND_LOGITS2(float, false); }
