@@ -941,6 +941,7 @@ hipError_t launch_row_codes(hipStream_t st, const ET* X, int64_t ld, int64_t n, 
     const size_t lds = row_codes_lds(1 << lg, d, sizeof(ET), P, ahead);
     int64_t groups = (n + (1 << lg) - 1) >> lg;
     if (ahead) groups = std::min<int64_t>(groups, 256 * std::min<size_t>(8, 158 * 1024 / lds));   // (as many as run at a time)
+    if (FIRST::kRaw && !ahead) return hipErrorInvalidValue;   // (what `first` does would be left out)
     auto go = [&](auto ahead_c, auto f) -> hipError_t {
         constexpr auto kernel = k_row_codes<ET, decltype(ahead_c)::value, decltype(f)>;
         const hipError_t e = allow_whole_lds<kernel>();
