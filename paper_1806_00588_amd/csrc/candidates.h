@@ -940,15 +940,16 @@ k_hit_rows(CandArgs a, int t, int list_cap, uint32_t* __restrict__ row_bitmaps /
 // kCandThreads threads, no barrier inside.
 __device__ __forceinline__ void union_row_bitmaps(const uint32_t* __restrict__ rb, int B, int nwords,
                                                   uint32_t* bm) {
-    // Twelve rows' words are asked for together, of the rows that are left two, four or eight (a row twice is as good as once), and of more
-    // than kCandThreads words two of each thread: one trip to memory for 12 rows of 1250 words, where four rows and a word at a time took six.
-    // us a step: 500 bands, 12 beams, V = 40000 29.0 -> 28.5; 4 x 22 beams, V = 90102 69.5 -> 66.1.
-    auto words = [&](auto two_c, int i) __attribute__((always_inline)) {
-        constexpr int N = decltype(two_c)::value;
+    // Two, four, eight or twelve rows' words are asked for together (a row twice is as good as once), of the rows behind a last full twelve four or
+    // eight, and of more than kCandThreads words two of each thread: one trip to memory for 12 rows of 1250 words, where four rows and a word at a
+    // time took six.  us a step: 500 bands, 12 beams, V = 40000 29.0 -> 28.5; 4 x 22 beams, V = 90102 69.5 -> 66.1.  Twelve for the last rows too: 1 x 13,
+    // V = 90000 27.0 instead of 26.1.  (Up to eight rows have a loop of their own: 1 x 5 in the other one 22.8 -> 23.3.)
+    auto words = [&](auto rows_c, auto two_c, int i) __attribute__((always_inline)) {
+        constexpr int MOST = decltype(rows_c)::value, N = decltype(two_c)::value;
         const int at[2] = {i, min(i + kCandThreads, nwords - 1)};
         uint32_t x[N] = {};
-        auto rows = [&](auto rows_c, int b0) __attribute__((always_inline)) {
-            constexpr int ROWS = decltype(rows_c)::value;
+        auto rows = [&](auto n_c, int b0) __attribute__((always_inline)) {
+            constexpr int ROWS = decltype(n_c)::value;
             uint32_t v[ROWS][N];
 #pragma unroll
             for (int b = 0; b < ROWS; ++b)
@@ -959,17 +960,26 @@ __device__ __forceinline__ void union_row_bitmaps(const uint32_t* __restrict__ r
 #pragma unroll
                 for (int e = 0; e < N; ++e) x[e] |= v[b][e];
         };
-        int b0 = 0;
-        for (; B - b0 > 8; b0 += 12) rows(std::integral_constant<int, 12>{}, b0);
-        if (B - b0 > 4) rows(std::integral_constant<int, 8>{}, b0);
-        else if (B - b0 > 2) rows(std::integral_constant<int, 4>{}, b0);
-        else if (B - b0 > 0) rows(std::integral_constant<int, 2>{}, b0);
+        if constexpr (MOST < 12) rows(rows_c, 0);
+        else {
+            int b0 = 0;
+            for (; B - b0 > 8; b0 += 12) rows(rows_c, b0);
+            if (B - b0 > 4) rows(std::integral_constant<int, 8>{}, b0);
+            else if (B - b0 > 0) rows(std::integral_constant<int, 4>{}, b0);
+        }
 #pragma unroll
         for (int e = 0; e < N; ++e) bm[at[e]] = x[e];
     };
-    for (int i = threadIdx.x, i0 = 0; i < nwords; i += 2 * kCandThreads, i0 += 2 * kCandThreads)
-        if (nwords - i0 > kCandThreads) words(std::integral_constant<int, 2>{}, i);   // (uniform)
-        else words(std::integral_constant<int, 1>{}, i);
+    auto all = [&](auto rows_c) __attribute__((always_inline)) {
+        const int tid = threadIdx.x;
+        for (int i = tid; i < nwords; i += 2 * kCandThreads)
+            if (nwords - (i - tid) > kCandThreads) words(rows_c, std::integral_constant<int, 2>{}, i);   // (uniform)
+            else words(rows_c, std::integral_constant<int, 1>{}, i);
+    };
+    if (B <= 2) all(std::integral_constant<int, 2>{});
+    else if (B <= 4) all(std::integral_constant<int, 4>{});
+    else if (B <= 8) all(std::integral_constant<int, 8>{});
+    else all(std::integral_constant<int, 12>{});
 }
 
 // grid = S workgroups: OR of the sentence's B row bitmaps and the top-frequent words, compacted.
