@@ -1079,7 +1079,12 @@ __device__ __forceinline__ bool young_first(int g) { return (g < 8 ? 0xFE : 0xB6
 // 19.9, 20.1, 24 x 2 18.9, 19.3; d = 256 27.4, 26.7, 20.4, 20.3, 18.0, 18.2; d = 96 29.6, 29.5, 20.0, 20.3, 24 x 12 22.1, 22.4; two row groups: 24 x 32, d = 512 45.9,
 // 43.9, d = 256 40.1, 39.1, d = 100 45.0, 44.5.  64 x 10, V = 200000, d = 1024 99.6, 98.3 (lists of 6000).  With fp32 words, one piece: 32 x 10, d = 1000, 44.7, 45.1.
 // Units that the ring does not hold are loaded behind it; their lines brought to L2 in front cost more (32 x 10, d = 1536 34.5 -> 34.9; 8 x 32, d = 512 32.0 -> 32.4).
-constexpr bool stream_stages(bool bf16, int KSN, int rows) { return bf16 && rows >= (KSN == 4 ? 3 : KSN == 2 ? 8 : 17); }
+// Hidden rows of an odd number of values start at odd multiples of 4 bytes, which costs a lane that loads its own 16 bytes more than it costs LDS: 12 x 2, d = 683
+// 21.6, 21.1, d = 1001 21.8, 21.2, d = 511 18.4, 18.1; 40 x 1, d = 901 26.4, 25.8, d = 399 22.0, 21.6; 32 x 4, d = 301 22.9, 22.1; d = 201, 16 x 1 16.1, 16.3, 32 x 2 18.9, 18.7; but
+// d = 602, 32 x 2 23.6, 23.7.
+constexpr bool stream_stages(bool bf16, int KSN, int rows, bool odd) {
+    return bf16 && rows >= (KSN == 1 ? 17 : odd ? 1 : KSN == 2 ? 8 : 3);
+}
 // f(integral_constant 0), ..., f(integral_constant N - 1)
 template <int N, int I = 0, typename F> __device__ __forceinline__ void static_for(F&& f) {
     if constexpr (I < N) {

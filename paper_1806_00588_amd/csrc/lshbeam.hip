@@ -490,11 +490,11 @@ void launch_logits_stream(const StepCtx& cx, int64_t tiles_n, const float* H, co
     }
     if (!same) per = 0;
     if (per > 0) wgs = per * sp->S;
-    const bool stage = stream_stages(sizeof(ET) == 2, p.ksn, rows);
+    const bool stage = stream_stages(sizeof(ET) == 2, p.ksn, rows, t->d % 2 != 0);
 #define LSH_STREAM(MTV, KSNV, PV)                                                                             \
     do {                                                                                                      \
         constexpr bool must = stream_must_trim(sizeof(ET) == 2, PV), may = stream_may_trim(PV) || must;       \
-        constexpr bool SOME = stream_stages(sizeof(ET) == 2, KSNV, kTileM * MTV), ALL = stream_stages(sizeof(ET) == 2, KSNV, kTileM * (MTV - 1) + 1);  \
+        constexpr bool SOME = stream_stages(sizeof(ET) == 2, KSNV, kTileM * MTV, true), ALL = stream_stages(sizeof(ET) == 2, KSNV, kTileM * (MTV - 1) + 1, false);  \
         const bool trim = may && p.short_last;                                                                \
         launch(cx, 1, even ? k_logits_stream<ET, MTV, KSNV, PV, true, may>                                    \
                       : trim ? (stage ? k_logits_stream<ET, MTV, KSNV, PV, false, may, SOME> : k_logits_stream<ET, MTV, KSNV, PV, false, may, ALL>) \
@@ -703,7 +703,7 @@ hipError_t allow_logits_lds() {
 #define LSH_ALLOW(MTV, KSNV, PV)                                                                        \
     do {                                                                                            \
         constexpr bool must = stream_must_trim(sizeof(ET) == 2, PV), may = stream_may_trim(PV) || must; \
-        constexpr bool SOME = stream_stages(sizeof(ET) == 2, KSNV, kTileM * MTV), ALL = stream_stages(sizeof(ET) == 2, KSNV, kTileM * (MTV - 1) + 1);  \
+        constexpr bool SOME = stream_stages(sizeof(ET) == 2, KSNV, kTileM * MTV, true), ALL = stream_stages(sizeof(ET) == 2, KSNV, kTileM * (MTV - 1) + 1, false);  \
         if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, must, SOME>>();  \
         if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, may, SOME>>();   \
         if (e == hipSuccess) e = allow_whole_lds<k_logits_stream<ET, MTV, KSNV, PV, false, must, ALL>>();   \
