@@ -255,14 +255,18 @@ __device__ __forceinline__ void tiles_from_bitmap(const uint32_t* bm, uint32_t* 
 // Whether lanes load candidates' chunks for each other in k_cand_logits (QUADS): rows of more than one step of 64 bytes for each wave, whole
 // chunks.  us a step without and with (one sentence of 12 beams, V = 40000; in brackets 4 x 6, 1 x 20, 2 x 24): fp32 d = 1000 16.2, 15.9 (19.1, 18.6; 21.5, 21.1; 28.1,
 // 27.3), 768 15.9, 15.5 (18.3, 17.6; 21.1, 20.4; 27.2, 26.2), 640 15.9, 15.7, 512 15.2, 15.2 (17.0, 17.1; 19.4, 18.9; 24.0, 23.2), 400 14.9, 14.9, 320 15.1, 15.1, 264 15.0,
-// 15.1; d = 64 would lose 0.3.  bf16 d = 1024 17.3, 16.8 (21.0, 20.1; 21.6, 21.6), 928 17.0, 16.5, 800 16.8, 16.4, 768 16.0, 16.3 (19.3, 19.6), 736 16.8, 16.1, 672 17.0, 16.3, 640 16.4, 16.5,
-// 608 17.0, 16.3, 544 16.7, 16.0, 520 16.9, 16.1.  Rows that end in a partial chunk, whose values are masked behind the exchange, lose: d = 1001 16.5, 17.1
+// 15.1; d = 64 would lose 0.3.  bf16 d = 1536 17.9, 17.4 (21.6, 21.0), 1280 17.0, 17.0 (20.8, 20.3), 1024 17.3, 16.8 (21.0, 20.1; 21.6, 21.6), 928 17.0, 16.5.  bf16 rows of up to 28
+// steps win with up to four sentences, unless they begin at multiples of 256 bytes, where a lane's own pieces are in few lines as it is: d = 800 16.8, 16.4, 736 16.8, 16.1,
+// 672 17.0, 16.3, 608 17.0, 16.3, 544 16.7, 16.0, 520 16.9, 16.1; 768 16.0, 16.3, in rows of 776 16.6, 16.5, of 832 16.0, 16.3, 640 16.4, 16.5, 896 16.6, 16.6; 1 x 4 704 14.6, 14.3, 832 14.7, 14.5, 768 14.1, 14.3; 4 x 6, d = 864 21.1, 20.3, 736
+// 20.2, 19.6, 544 19.7, 19.4, 640 19.5, 19.8; 2 x 10, in rows of 776 19.4, 19.7, of 648 20.1, 20.2; 6 x 4 beams, d = 520 18.7, 19.4, 640 19.3, 19.6, 768 19.3, 19.6, 760 19.2, 19.7 (896 19.7,
+// 19.8, 1024 19.7, 19.7).  Rows that end in a partial chunk, whose values are masked behind the exchange, lose: d = 1001 16.5, 17.1
 // (19.9, 20.7; 22.5, 23.1; 29.5, 31.0), 401 15.2, 15.7, 1281 18.3, 18.9, bf16 d = 1001 in rows of 1008 17.7, 18.3, d = 1004 17.1, 17.1; but not where rows start
 // at odd multiples of 2 bytes, so that a lane's 16 bytes straddle words: bf16 d = 1001 in rows of 1001 19.6, 18.2 (24.9, 23.4), d = 1000 in 1001 18.3, 16.9.
 // (Hidden rows from memory, in k_union_logits, loaded so as well: 0.5 us lost of 32 with lists of 300 tiles.)
-inline bool takes_quads(bool bf16, int d, int64_t ld) {
-    const int vec = bf16 ? 8 : 4;
-    return (d + 4 * vec - 1) / (4 * vec) > kFusedWaves && (d % vec == 0 || (bf16 && ld % 2 != 0));
+inline bool takes_quads(bool bf16, int d, int64_t ld, int S) {
+    const int vec = bf16 ? 8 : 4, steps = (d + 4 * vec - 1) / (4 * vec);
+    if (bf16 && ld % 2 != 0) return steps > kFusedWaves;
+    return steps > kFusedWaves && d % vec == 0 && (!bf16 || steps > 28 || (S <= 4 && ld % 128 != 0));
 }
 
 // grid = S * G workgroups: workgroup b works for sentence b % S and takes that sentence's tiles

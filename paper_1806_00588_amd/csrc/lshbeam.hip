@@ -1259,7 +1259,7 @@ lsh_status decode_step_impl(const lsh_tables* t, const float* H_dev, const float
     do {                                                                                         \
         const ET* e = nullptr;                                                                   \
         if (selected) LSH_CAND_LOGITS(ET, AL, true);                                             \
-        else if (AL && takes_quads(sizeof(ET) == 2, t->d, t->ld)) LSH_CAND_LOGITS(ET, AL, false, AL); \
+        else if (AL && takes_quads(sizeof(ET) == 2, t->d, t->ld, sp->S)) LSH_CAND_LOGITS(ET, AL, false, AL); \
         else LSH_CAND_LOGITS(ET, AL, false);                                                     \
     } while (0)
             if (f32) { if (al) LSH_CAND_LOGITS2(float, true); else LSH_CAND_LOGITS2(float, false); }
