@@ -693,7 +693,7 @@ __host__ __device__ inline size_t union_compact_lds_words(int V) {
 constexpr int kCandParts = 4;
 inline bool candidates_split(int S, int V) { return S * kCandParts <= 256 && V > 2 * kCandWaves * kWave * 32; }
 template <int PARTS>
-__global__ void __launch_bounds__(kCandThreads)
+__global__ void LSH_PAGE_ALIGNED __launch_bounds__(kCandThreads)
 k_candidates(CandArgs a, int S, int32_t* __restrict__ cand, int32_t* __restrict__ count) {
     extern __shared__ uint32_t smem[];
     const int part = PARTS == 1 ? 0 : blockIdx.x / S, s = PARTS == 1 ? blockIdx.x : blockIdx.x - part * S;

@@ -195,6 +195,9 @@ __device__ __forceinline__ void load_to_lds4(const void* from, void* to) {
     const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)to;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(at)), "v"(from) : "m0", "memory");
 }
+// A kernel whose code begins at a multiple of 4 KB.  Short kernels of much code take up to 0.5 us more or less by where their code lies, the same bytes:
+// k_candidates of 5 x 17 beams, d = 1001, at offsets 0xc00, 0xd00 and 0 of a page 8.6, 8.9 to 9.1, 8.3 us, of 32 x 10 7.9, 8.1, 8.1; k_select of these 6.2, 6.1, 5.9 and 4.9, 5.2, 4.9.
+#define LSH_PAGE_ALIGNED __attribute__((aligned(4096)))
 // Matrix operands straight from memory.  A lane's operand is 16 bytes of row lane % 16, so that neighbouring lanes, loading their own,
 // read different rows, and a load of 1 KB takes the CU's address unit 66 cycles (all CUs together 9.7 TB/s, out of L2 too);
 // with four neighbouring lanes on neighbouring bytes of a row it takes 23 to 28 (24 TB/s).  So lane 4 c + p loads piece p of row

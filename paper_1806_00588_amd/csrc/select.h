@@ -1504,7 +1504,7 @@ __device__ __forceinline__ void select_sentence(SelShared& sh, int s, const floa
 // grid = S workgroups (one per sentence), kSelThreads threads: the selection as a kernel of its
 // own, after kernels that left rich (fused plans) or plain tile records.
 template <bool RICH, bool GROUPS, bool WIDE = false, int BEAMS = -1>
-__global__ void __launch_bounds__(kSelThreads)
+__global__ void LSH_PAGE_ALIGNED __launch_bounds__(kSelThreads)
 k_select(const float* __restrict__ logits, int64_t cpitch, const TileRecord* __restrict__ records,
          const int32_t* __restrict__ ids2, int64_t ppitch, const int32_t* __restrict__ cand,
          const int32_t* __restrict__ count, int V, int B, const float* __restrict__ beam_scores,
